@@ -27,33 +27,6 @@ __global__ void k_gemm_naive(int tb, int64_t M, int64_t N, int64_t K, const floa
     C[i * ldc + j] = apply_epi<EPI>(acc, EPI == GCN_EPI_MASK ? Zprev + i * ldzprev + j : nullptr);
 }
 
-// ---- C = A^T B with a long K: each block sums one K range into a partial M x N --------------
-__global__ void k_gemm_tn_partial(int64_t M, int64_t N, int64_t K, int64_t k_per_block, const float* __restrict__ A,
-                                  int64_t lda, const float* __restrict__ B, int64_t ldb, float* __restrict__ part) {
-    const int64_t kb = (int64_t)blockIdx.x * k_per_block;
-    const int64_t ke = kb + k_per_block < K ? kb + k_per_block : K;
-    float* out = part + (int64_t)blockIdx.x * M * N;
-    for (int64_t o = threadIdx.x; o < M * N; o += blockDim.x) {
-        const int64_t i = o / N, j = o % N;
-        float acc = 0.f;
-        for (int64_t k = kb; k < ke; ++k) acc = fmaf(A[k * lda + i], B[k * ldb + j], acc);
-        out[o] = acc;
-    }
-}
-
-template <int EPI>
-__global__ void k_reduce_partials(int64_t count, int64_t N, int parts, const float* __restrict__ part,
-                                  float* __restrict__ C, int64_t ldc, const float* __restrict__ bias,
-                                  const float* __restrict__ Zprev, int64_t ldzprev) {
-    const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (o >= count) return;
-    float acc = 0.f;
-    for (int p = 0; p < parts; ++p) acc += part[(int64_t)p * count + o];   // fixed order
-    const int64_t i = o / N, j = o % N;
-    if (bias) acc += bias[j];
-    C[i * ldc + j] = apply_epi<EPI>(acc, EPI == GCN_EPI_MASK ? Zprev + i * ldzprev + j : nullptr);
-}
-
 // ---- element-wise -----------------------------------------------------------------------------
 __global__ void k_relu(int64_t rows, int32_t cols, const float* __restrict__ Z, int64_t ldz, float* __restrict__ H,
                        int64_t ldh) {
@@ -74,15 +47,32 @@ __global__ void k_relu_mask(int64_t rows, int32_t cols, const float* __restrict_
     out[i * ldo + j] = Zp[i * ldzp + j] > 0.f ? G[i * ldg + j] : 0.f;
 }
 
-__global__ void k_colsum_partial(int64_t rows, int32_t cols, int64_t rows_per_block, const float* __restrict__ G,
-                                 int64_t ldg, float* __restrict__ part) {
+// Column sums: blockDim.x lanes walk the columns (64 or the next power of two above `cols` when that is less),
+// blockDim.y row sets split the workgroup's rows, eight loads in flight each; the row sets are added in order in LDS.
+__global__ __launch_bounds__(256) void k_colsum_partial(int64_t rows, int32_t cols, int64_t rows_per_block,
+                                                        const float* __restrict__ G, int64_t ldg, float* __restrict__ part) {
+    __shared__ float s_sum[256];
     const int64_t rb = (int64_t)blockIdx.x * rows_per_block;
     const int64_t re = rb + rows_per_block < rows ? rb + rows_per_block : rows;
-    for (int j = threadIdx.x; j < cols; j += blockDim.x) {
-        float acc = 0.f;
-        for (int64_t i = rb; i < re; ++i) acc += G[i * ldg + j];
-        part[(int64_t)blockIdx.x * cols + j] = acc;
+    const int j = blockIdx.y * blockDim.x + threadIdx.x;
+    const int ty = threadIdx.y, ny = blockDim.y;
+    float acc = 0.f;
+    if (j < cols) {
+        int64_t i = rb + ty;
+        for (; i + 7 * ny < re; i += 8 * ny) {
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = G[(i + e * ny) * ldg + j];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc += v[e];
+        }
+        for (; i < re; i += ny) acc += G[i * ldg + j];
     }
+    s_sum[ty * blockDim.x + threadIdx.x] = acc;
+    __syncthreads();
+    if (ty != 0 || j >= cols) return;
+    for (int y = 1; y < ny; ++y) acc += s_sum[y * blockDim.x + threadIdx.x];
+    part[(int64_t)blockIdx.x * cols + j] = acc;
 }
 
 __global__ void k_bias_add(int64_t rows, int32_t cols, float* __restrict__ Z, int64_t ldz, const float* __restrict__ bias,
@@ -130,31 +120,17 @@ int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const floa
                      int64_t ldb, float* C, int64_t ldc, const float* bias, int epilogue, const float* Zprev,
                      int64_t ldzprev, hipStream_t s, bool* handled, const float* row_scale, bool* scaled);
 
-// split of the long dimension of the plain (non-MFMA) A^T B kernel
-static void naive_tn_split(int64_t K, int64_t* parts_out, int64_t* kpb_out) {
-    int64_t parts = (K + 1023) / 1024;
-    if (parts > 1024) parts = 1024;
-    if (parts < 1) parts = 1;
-    const int64_t kpb = (K + parts - 1) / parts;
-    parts = (K + kpb - 1) / kpb;
-    if (parts < 1) parts = 1;
-    *parts_out = parts;
-    *kpb_out = kpb;
-}
-
 size_t gemm_mfma_tn_scratch_bytes(int64_t M, int64_t N, int64_t K);
+int reduce_parts_launch(int32_t M, int32_t N, int parts, bool transposed, const float* part, float* C, int64_t ldc,
+                        const float* bias, int epilogue, const float* Zprev, int64_t ldzprev, hipStream_t s);
 
 size_t gemm_tn_scratch_bytes(int64_t M, int64_t N, int64_t K) {
-    int64_t parts = 0, kpb = 0;
-    naive_tn_split(K, &parts, &kpb);
-    const size_t plain = (size_t)parts * M * N * sizeof(float);
-    const size_t mfma = gemm_mfma_tn_scratch_bytes(M, N, K);
-    return plain > mfma ? plain : mfma;              // whichever kernel the operands' alignment selects
+    return gemm_mfma_tn_scratch_bytes(M, N, K);
 }
 
 static void colsum_split(int64_t rows, int64_t* parts_out, int64_t* rpb_out) {
-    int64_t parts = (rows + 4095) / 4096;
-    if (parts > 512) parts = 512;
+    int64_t parts = (rows + 127) / 128;
+    if (parts > 1024) parts = 1024;
     if (parts < 1) parts = 1;
     const int64_t rpb = (rows + parts - 1) / parts;
     *parts_out = (rows + rpb - 1) / rpb;
@@ -176,29 +152,12 @@ int gemm_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const float* A,
     // kernels without a scaling store path leave the row factors to a pass of their own
     auto finish = [&]() { return (row_scale && !scaled) ? scale_rows_launch(M, (int32_t)N, C, ldc, row_scale, C, ldc, s) : (int)GCN_OK; };
     if (handled) return finish();
-    if (!ta) {
-        const int64_t work = M * N;
-        if ((work + 255) / 256 >= (1ll << 31)) return fail(GCN_ERR_RANGE, "gcn_gemm: output too large");
-        switch (epilogue) {
-            case GCN_EPI_NONE: hipLaunchKernelGGL(k_gemm_naive<GCN_EPI_NONE>, dim3(nblocks(work)), dim3(256), 0, s, tb, M, N, K, A, lda, B, ldb, C, ldc, bias, Zprev, ldzprev); break;
-            case GCN_EPI_RELU: hipLaunchKernelGGL(k_gemm_naive<GCN_EPI_RELU>, dim3(nblocks(work)), dim3(256), 0, s, tb, M, N, K, A, lda, B, ldb, C, ldc, bias, Zprev, ldzprev); break;
-            default: hipLaunchKernelGGL(k_gemm_naive<GCN_EPI_MASK>, dim3(nblocks(work)), dim3(256), 0, s, tb, M, N, K, A, lda, B, ldb, C, ldc, bias, Zprev, ldzprev); break;
-        }
-        GCN_LAUNCH_CHECK();
-        return finish();
-    }
-    // ta: split K
-    int64_t parts = 0, kpb = 0;
-    naive_tn_split(K, &parts, &kpb);
-    void* scratch = nullptr;
-    GCN_TRY(scratch_get(&scratch, (size_t)parts * M * N * sizeof(float), s));
-    hipLaunchKernelGGL(k_gemm_tn_partial, dim3((unsigned)parts), dim3(256), 0, s, M, N, K, kpb, A, lda, B, ldb, (float*)scratch);
-    GCN_LAUNCH_CHECK();
-    const int64_t count = M * N;
+    const int64_t work = M * N;
+    if ((work + 255) / 256 >= (1ll << 31)) return fail(GCN_ERR_RANGE, "gcn_gemm: output too large");
     switch (epilogue) {
-        case GCN_EPI_NONE: hipLaunchKernelGGL(k_reduce_partials<GCN_EPI_NONE>, dim3(nblocks(count)), dim3(256), 0, s, count, N, (int)parts, (const float*)scratch, C, ldc, bias, Zprev, ldzprev); break;
-        case GCN_EPI_RELU: hipLaunchKernelGGL(k_reduce_partials<GCN_EPI_RELU>, dim3(nblocks(count)), dim3(256), 0, s, count, N, (int)parts, (const float*)scratch, C, ldc, bias, Zprev, ldzprev); break;
-        default: hipLaunchKernelGGL(k_reduce_partials<GCN_EPI_MASK>, dim3(nblocks(count)), dim3(256), 0, s, count, N, (int)parts, (const float*)scratch, C, ldc, bias, Zprev, ldzprev); break;
+        case GCN_EPI_NONE: hipLaunchKernelGGL(k_gemm_naive<GCN_EPI_NONE>, dim3(nblocks(work)), dim3(256), 0, s, tb, M, N, K, A, lda, B, ldb, C, ldc, bias, Zprev, ldzprev); break;
+        case GCN_EPI_RELU: hipLaunchKernelGGL(k_gemm_naive<GCN_EPI_RELU>, dim3(nblocks(work)), dim3(256), 0, s, tb, M, N, K, A, lda, B, ldb, C, ldc, bias, Zprev, ldzprev); break;
+        default: hipLaunchKernelGGL(k_gemm_naive<GCN_EPI_MASK>, dim3(nblocks(work)), dim3(256), 0, s, tb, M, N, K, A, lda, B, ldb, C, ldc, bias, Zprev, ldzprev); break;
     }
     GCN_LAUNCH_CHECK();
     return finish();
@@ -209,12 +168,12 @@ int colsum_launch(int64_t rows, int32_t cols, const float* G, int64_t ldg, float
     colsum_split(rows, &parts, &rpb);
     void* scratch = nullptr;
     GCN_TRY(scratch_get(&scratch, (size_t)parts * cols * sizeof(float), s));
-    hipLaunchKernelGGL(k_colsum_partial, dim3((unsigned)parts), dim3(64), 0, s, rows, cols, rpb, G, ldg, (float*)scratch);
+    int tx = 64;
+    while (tx > 4 && tx / 2 >= cols) tx /= 2;
+    hipLaunchKernelGGL(k_colsum_partial, dim3((unsigned)parts, (unsigned)((cols + tx - 1) / tx)), dim3(tx, 256 / tx), 0, s, rows,
+                       cols, rpb, G, ldg, (float*)scratch);
     GCN_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_reduce_partials<GCN_EPI_NONE>, dim3(nblocks(cols)), dim3(256), 0, s, (int64_t)cols, (int64_t)cols,
-                       (int)parts, (const float*)scratch, out, (int64_t)cols, (const float*)nullptr, (const float*)nullptr, (int64_t)0);
-    GCN_LAUNCH_CHECK();
-    return GCN_OK;
+    return reduce_parts_launch(1, cols, (int)parts, false, (const float*)scratch, out, cols, nullptr, GCN_EPI_NONE, nullptr, 0, s);
 }
 
 int relu_launch(int64_t rows, int32_t cols, const float* Z, int64_t ldz, float* H, int64_t ldh, hipStream_t s) {

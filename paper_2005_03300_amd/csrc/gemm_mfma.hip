@@ -10,6 +10,8 @@
 //
 // Operand layout of the 16x16x4 instruction (64 lanes): lane l supplies A[i = l%16][k = l/16] and
 // B[k = l/16][j = l%16], and holds D[i = 4*(l/16) + v][j = l%16] in element v of its accumulator.
+#include <atomic>
+
 #include "common.h"
 
 namespace gcn {
@@ -27,9 +29,9 @@ __device__ __forceinline__ float4 stream4(const float* p) {
     return make_float4(v[0], v[1], v[2], v[3]);
 }
 
-__device__ __forceinline__ float4 load4(const float* p, bool aligned, bool nt = false) {
-    if (aligned) return nt ? stream4(p) : *reinterpret_cast<const float4*>(p);
-    f4u v = *reinterpret_cast<const f4u*>(p);
+// 16 bytes at any 4-byte aligned address (the same instruction as for an aligned one).
+__device__ __forceinline__ float4 load4(const float* p) {
+    const f4u v = *reinterpret_cast<const f4u*>(p);
     return make_float4(v.x, v.y, v.z, v.w);
 }
 
@@ -38,6 +40,21 @@ __device__ __forceinline__ float epi(float v, const float* zprev_elem) {
     if (EPI == GCN_EPI_RELU) return v > 0.f ? v : 0.f;
     if (EPI == GCN_EPI_MASK) return *zprev_elem > 0.f ? v : 0.f;
     return v;
+}
+
+// Lane quarter q (16 lanes) holds x[e] = m[q][e]; afterwards it holds m[e][q].
+__device__ __forceinline__ void quarter_transpose(float (&x)[4]) {
+    auto swap = [](float& a, float& b, bool halves) {
+        const unsigned ua = __float_as_uint(a), ub = __float_as_uint(b);
+        const auto v = halves ? __builtin_amdgcn_permlane32_swap(ua, ub, false, false)
+                              : __builtin_amdgcn_permlane16_swap(ua, ub, false, false);
+        a = __uint_as_float(v[0]);
+        b = __uint_as_float(v[1]);
+    };
+    swap(x[0], x[2], true);
+    swap(x[1], x[3], true);
+    swap(x[0], x[1], false);
+    swap(x[2], x[3], false);
 }
 
 struct TallArgs {
@@ -49,20 +66,24 @@ struct TallArgs {
     const float* bias;
     const float* Zprev; int64_t ldzprev;
     int32_t Kpad;      // K rounded up to 16
+    int asc;           // add in ascending k
     int32_t S;         // LDS row stride in floats: 16*NT + 4 (bank-conflict-free B reads)
-    int a_aligned;     // A rows are 16-byte aligned
     const float* row_scale;   // NULL, or one factor per row of C, applied after bias and epilogue (wide store path only)
 };
 
 // TR: the two MFMA operands are swapped, so a lane ends up with four consecutive columns of one
 // row of C (element v of tile t is C[row0 + l%16][16t + 4*(l/16) + v]) and stores them with one
 // 16-byte instruction; needs N % 4 == 0 and 16-byte aligned rows of C (and of Zprev for the mask).
-template <int NT, int EPI, bool TR>
-__global__ __launch_bounds__(256) void k_gemm_tall(TallArgs a) {
+// ASC: the products of an element of C are added in ascending k, like the chain of the plain kernel: an instruction
+// adds its four products in the order of the lane quarters, so quarter kq has to supply k = k0 + 4e + kq to instruction
+// e, and the 16 bytes that it loads at k0 + 4 kq are exchanged between the quarters (a 4 x 4 transposition, four
+// instructions).  Without it instruction e takes k = k0 + 4 kq + e.
+template <int NT, int EPI, bool TR, bool ASC>
+__global__ __launch_bounds__(512) void k_gemm_tall(TallArgs a) {
     extern __shared__ float Bs[];                       // [Kpad][S]
     const int n0 = blockIdx.y * (NT * 16);
     const int ncols = NT * 16;
-    for (int idx = threadIdx.x; idx < a.Kpad * ncols; idx += 256) {
+    for (int idx = threadIdx.x; idx < a.Kpad * ncols; idx += blockDim.x) {
         const int k = idx / ncols, j = idx % ncols;
         float v = 0.f;
         if (k < a.K && n0 + j < a.N) v = a.tb ? a.B[(int64_t)(n0 + j) * a.ldb + k] : a.B[(int64_t)k * a.ldb + n0 + j];
@@ -70,10 +91,10 @@ __global__ __launch_bounds__(256) void k_gemm_tall(TallArgs a) {
     }
     __syncthreads();
 
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
     const int r = lane & 15, kq = lane >> 4;
     const int64_t ntiles = (a.M + 15) / 16;
-    for (int64_t tile = (int64_t)blockIdx.x * 4 + wave; tile < ntiles; tile += (int64_t)gridDim.x * 4) {
+    for (int64_t tile = (int64_t)blockIdx.x * waves + wave; tile < ntiles; tile += (int64_t)gridDim.x * waves) {
         const int64_t row0 = tile * 16;
         int64_t arow = row0 + r;
         if (arow >= a.M) arow = a.M - 1;                // clamp: loads stay in bounds, stores are masked
@@ -86,13 +107,14 @@ __global__ __launch_bounds__(256) void k_gemm_tall(TallArgs a) {
         for (; k0 + 64 <= kfull; k0 += 64) {            // four 16-deep steps per trip: 4 loads in flight
             float4 av[4];
 #pragma unroll
-            for (int s = 0; s < 4; ++s) av[s] = load4(ap + k0 + 16 * s, a.a_aligned);
+            for (int s = 0; s < 4; ++s) av[s] = load4(ap + k0 + 16 * s);
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
-                const float ae[4] = {av[s].x, av[s].y, av[s].z, av[s].w};
+                float ae[4] = {av[s].x, av[s].y, av[s].z, av[s].w};
+                if constexpr (ASC) quarter_transpose(ae);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const float* bp = Bs + (k0 + 16 * s + 4 * kq + e) * a.S + r;
+                    const float* bp = Bs + (k0 + 16 * s + (ASC ? 4 * e + kq : 4 * kq + e)) * a.S + r;
 #pragma unroll
                     for (int t = 0; t < NT; ++t)
                         acc[t] = TR ? __builtin_amdgcn_mfma_f32_16x16x4f32(bp[16 * t], ae[e], acc[t], 0, 0, 0)
@@ -101,11 +123,12 @@ __global__ __launch_bounds__(256) void k_gemm_tall(TallArgs a) {
             }
         }
         for (; k0 < kfull; k0 += 16) {
-            const float4 av = load4(ap + k0, a.a_aligned);
-            const float ae[4] = {av.x, av.y, av.z, av.w};
+            const float4 av = load4(ap + k0);
+            float ae[4] = {av.x, av.y, av.z, av.w};
+            if constexpr (ASC) quarter_transpose(ae);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const float* bp = Bs + (k0 + 4 * kq + e) * a.S + r;
+                const float* bp = Bs + (k0 + (ASC ? 4 * e + kq : 4 * kq + e)) * a.S + r;
 #pragma unroll
                 for (int t = 0; t < NT; ++t)
                     acc[t] = TR ? __builtin_amdgcn_mfma_f32_16x16x4f32(bp[16 * t], ae[e], acc[t], 0, 0, 0)
@@ -117,16 +140,17 @@ __global__ __launch_bounds__(256) void k_gemm_tall(TallArgs a) {
             float tail[4] = {0.f, 0.f, 0.f, 0.f};
             if ((a.K & 3) == 0) {
                 if (k0 + 4 * kq + 4 <= a.K) {
-                    const float4 av = load4(ap + k0, a.a_aligned);
+                    const float4 av = load4(ap + k0);
                     tail[0] = av.x; tail[1] = av.y; tail[2] = av.z; tail[3] = av.w;
                 }
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) tail[e] = k0 + 4 * kq + e < a.K ? ap[k0 + e] : 0.f;
             }
+            if constexpr (ASC) quarter_transpose(tail);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int k = k0 + 4 * kq + e;
+                const int k = k0 + (ASC ? 4 * e + kq : 4 * kq + e);
                 const float ae = tail[e];
                 const float* bp = Bs + k * a.S + r;     // rows K..Kpad-1 of Bs are zero
 #pragma unroll
@@ -282,10 +306,16 @@ __global__ __launch_bounds__(512) void k_gemm_tall_flat(TallArgs a) {
 }
 
 // ---- C = A^T B over a long K ---------------------------------------------------------------------
-// A workgroup takes the rows [kb, ke) of A and B.  Wavefront w owns the 64-wide column groups
-// w, w+4, w+8, ... of A (at most MG of them); inside a group lane i covers columns 4i..4i+3 with one
-// 16-byte load, which makes four M-tiles {4i+t : i} for t = 0..3.  Each step consumes four rows
-// (one per lane quarter).  The partial M x N results go to part[block][M][N].
+// A workgroup takes the rows [kb, ke) of A and B.  The columns of A are cut into groups of 64; inside a group lane i
+// covers columns 4i..4i+3 with one 16-byte load, which makes four M-tiles {4i+t : i} for t = 0..3.  The groups are
+// dealt to `gw` wavefronts (wavefront w owns groups w, w + gw, ... of the workgroup's share, MG of them at most); when
+// there are fewer than four groups the workgroup has `rw` such sets of wavefronts, which take its 16-row trips in turn
+// and whose sums are added in LDS in a fixed order, so that a narrow product writes no more partial results than a
+// wide one.  Each trip consumes 16 rows (four per matrix instruction, one per lane quarter).  blockIdx.y takes 16 NT columns of B, blockIdx.z a share of the
+// column groups of A: any M and N.  The partial M x N results go to part[blockIdx.x][M][N].
+// Bound by the stream of A and B up to about 32 columns of B (128 x 16 over 4.4 M rows: 0.41 ms, 6.1 TB/s) and by the fp32
+// matrix rate and the stream together beyond (256 x 64 over 120 K rows 89 us, 44 TFLOP/s; one thread per output element
+// took 16.5 ms; 602 x 64 over 233 K rows: 0.27 ms, 66 TFLOP/s).
 struct TnArgs {
     int64_t K;
     int32_t M, N;
@@ -293,44 +323,157 @@ struct TnArgs {
     const float* B; int64_t ldb;
     float* part;
     int64_t k_per_block;
-    int a_aligned;
-    int a_stream;      // rows of A are whole 128-byte lines: non-temporal loads
-    int waves;         // wavefronts per workgroup (the column groups are dealt to them round-robin); 4 when NARROW
+    int gw, rw;        // wavefronts per workgroup = gw * rw
 };
 
-template <int MG, int NT, bool NARROW>   // NARROW: MG counts 16-column tiles of A (M <= 16*MG)
+template <int MG, int NT, bool STREAM>
 __global__ __launch_bounds__(512) void k_gemm_tn(TnArgs a) {
+    extern __shared__ float s_part[];                   // rw > 1: [gw][MG * 4 * NT][64][4]
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int gwave = wave % a.gw, rwave = wave / a.gw;
+    const int i = lane & 15, kq = lane >> 4;
+    const int64_t kb = (int64_t)blockIdx.x * a.k_per_block;
+    const int64_t ke = kb + a.k_per_block < a.K ? kb + a.k_per_block : a.K;
+    const int n0 = blockIdx.y * (16 * NT);
+    const int m0 = blockIdx.z * (a.gw * MG * 64);
+    floatx4 acc[MG][4][NT];
+#pragma unroll
+    for (int g = 0; g < MG; ++g)
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int u = 0; u < NT; ++u) acc[g][t][u] = (floatx4){0.f, 0.f, 0.f, 0.f};
+
+    // Lanes past the last column repeat the last four columns of A (the last column of B): no load needs a guard, and
+    // an element that two lanes compute gets the same bits from both.
+    auto mcol = [&](int g, int ii) {
+        const int c = m0 + (gwave + a.gw * g) * 64 + 4 * ii;
+        return c < a.M - 4 ? c : a.M - 4;
+    };
+    auto ncol = [&](int u) {
+        const int c = n0 + 16 * u + i;
+        return c < a.N ? c : a.N - 1;
+    };
+    const float* ap[MG];
+    const float* bp[NT];
+    const int64_t kfirst = kb + 16 * rwave;
+#pragma unroll
+    for (int g = 0; g < MG; ++g) ap[g] = a.A + (kfirst + kq) * a.lda + mcol(g, i);
+#pragma unroll
+    for (int u = 0; u < NT; ++u) bp[u] = a.B + (kfirst + kq) * a.ldb + ncol(u);
+    const int kstep = 16 * a.rw;
+    int64_t k0 = kfirst;
+    // Wavefronts on neighbouring columns share the lines at their edges when rows are not whole lines: kept within four
+    // trips of each other they find them in the caches (300 x 16 over 14.2 M rows 4.20 -> 3.33 ms, 5.4 TB/s).  All
+    // of them take the same number of trips.  Products of 33 columns or more are bound by the matrix rate: no barrier
+    // there (602 x 64: 275 us without, 296 us with).
+    const bool in_step = NT <= 2 && a.rw == 1 && a.gw > 1;
+    int trip = 0;
+    for (; k0 < ke; k0 += kstep) {
+        if (in_step && (++trip & 3) == 0) __builtin_amdgcn_s_barrier();
+        float av[4][MG][4], bv[4][NT];
+        if (k0 + 16 <= ke) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+#pragma unroll
+                for (int u = 0; u < NT; ++u) bv[s][u] = bp[u][4 * s * a.ldb];
+#pragma unroll
+                for (int g = 0; g < MG; ++g) {
+                    const float4 v = STREAM ? stream4(ap[g] + 4 * s * a.lda) : load4(ap[g] + 4 * s * a.lda);
+                    av[s][g][0] = v.x; av[s][g][1] = v.y; av[s][g][2] = v.z; av[s][g][3] = v.w;
+                }
+            }
+        } else {                                        // the last, short trip: rows past the end count as zero
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const bool kok = k0 + 4 * s + kq < ke;
+#pragma unroll
+                for (int u = 0; u < NT; ++u) bv[s][u] = kok ? bp[u][4 * s * a.ldb] : 0.f;
+#pragma unroll
+                for (int g = 0; g < MG; ++g) {
+                    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (kok) v = load4(ap[g] + 4 * s * a.lda);
+                    av[s][g][0] = v.x; av[s][g][1] = v.y; av[s][g][2] = v.z; av[s][g][3] = v.w;
+                }
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < MG; ++g) ap[g] += (int64_t)kstep * a.lda;
+#pragma unroll
+        for (int u = 0; u < NT; ++u) bp[u] += (int64_t)kstep * a.ldb;
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int g = 0; g < MG; ++g)
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+#pragma unroll
+                    for (int u = 0; u < NT; ++u)
+                        acc[g][t][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[s][g][t], bv[s][u], acc[g][t][u], 0, 0, 0);
+    }
+    // the row sets hold partial sums of the same tiles: added in order 0, 1, 2, 3 in LDS
+    for (int w = 1; w < a.rw; ++w) {
+        float4* mine = reinterpret_cast<float4*>(s_part) + (size_t)gwave * (MG * 4 * NT) * 64 + lane;
+        if (rwave == w) {
+#pragma unroll
+            for (int g = 0; g < MG; ++g)
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+#pragma unroll
+                    for (int u = 0; u < NT; ++u) {
+                        const floatx4 v = acc[g][t][u];
+                        mine[((g * 4 + t) * NT + u) * 64] = make_float4(v[0], v[1], v[2], v[3]);
+                    }
+        }
+        __syncthreads();
+        if (rwave == 0) {
+#pragma unroll
+            for (int g = 0; g < MG; ++g)
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+#pragma unroll
+                    for (int u = 0; u < NT; ++u) {
+                        const float4 v = mine[((g * 4 + t) * NT + u) * 64];
+                        acc[g][t][u] += (floatx4){v.x, v.y, v.z, v.w};
+                    }
+        }
+        __syncthreads();
+    }
+    if (rwave != 0) return;
+    float* out = a.part + (int64_t)blockIdx.x * a.M * a.N;
+    // D[ii = 4*kq + v][j = i] of tile (g, t) is C[m = mcol(g, ii) + t][n = ncol(u)]
+#pragma unroll
+    for (int g = 0; g < MG; ++g)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int m = mcol(g, 4 * kq + v);
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int u = 0; u < NT; ++u) out[(int64_t)(m + t) * a.N + ncol(u)] = acc[g][t][u][v];
+        }
+}
+
+// The same for M <= 32 and N <= 32: lane i covers columns i and i+16 of A with 4-byte loads (one M-tile each) and the
+// four wavefronts split the rows.
+template <int MG, int NT>
+__global__ __launch_bounds__(256) void k_gemm_tn_narrow(TnArgs a) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int i = lane & 15, kq = lane >> 4;
     const int64_t kb = (int64_t)blockIdx.x * a.k_per_block;
     const int64_t ke = kb + a.k_per_block < a.K ? kb + a.k_per_block : a.K;
-    constexpr int TT = NARROW ? 1 : 4;                  // M-tiles per column group
-    floatx4 acc[MG][TT][NT];
+    floatx4 acc[MG][NT];
 #pragma unroll
     for (int g = 0; g < MG; ++g)
 #pragma unroll
-        for (int t = 0; t < TT; ++t)
+        for (int u = 0; u < NT; ++u) acc[g][u] = (floatx4){0.f, 0.f, 0.f, 0.f};
+    bool mok[MG], nok[NT];
 #pragma unroll
-            for (int u = 0; u < NT; ++u) acc[g][t][u] = (floatx4){0.f, 0.f, 0.f, 0.f};
-
-    // NARROW (M <= 32): lane i covers columns i, i+16 of A with 4-byte loads (one M-tile each), and
-    // the four wavefronts split the rows instead of the columns.
-    int mcol[MG];
-    int mvalid[MG];                                     // how many of the lane's 4 columns exist
-#pragma unroll
-    for (int g = 0; g < MG; ++g) {
-        mcol[g] = NARROW ? i + 16 * g : (wave + a.waves * g) * 64 + 4 * i;
-        const int left = a.M - mcol[g];
-        mvalid[g] = left >= (NARROW ? 1 : 4) ? (NARROW ? 1 : 4) : (left > 0 ? left : 0);
-    }
-    bool nok[NT];
+    for (int g = 0; g < MG; ++g) mok[g] = 16 * g + i < a.M;
 #pragma unroll
     for (int u = 0; u < NT; ++u) nok[u] = 16 * u + i < a.N;
-    const int kstep = NARROW ? 64 : 16;                 // rows per trip of the whole workgroup
-    const int koff = NARROW ? 16 * wave : 0;
-    for (int64_t k0 = kb + koff; k0 < ke; k0 += kstep) {
-        float av[4][MG][TT];
-        float bv[4][NT];
+    for (int64_t k0 = kb + 16 * wave; k0 < ke; k0 += 64) {
+        float av[4][MG], bv[4][NT];
 #pragma unroll
         for (int s = 0; s < 4; ++s) {                   // issue every load of the trip first
             const int64_t k = k0 + 4 * s + kq;
@@ -340,132 +483,138 @@ __global__ __launch_bounds__(512) void k_gemm_tn(TnArgs a) {
 #pragma unroll
             for (int u = 0; u < NT; ++u) bv[s][u] = (kok && nok[u]) ? brow[16 * u + i] : 0.f;
 #pragma unroll
-            for (int g = 0; g < MG; ++g) {
-                if constexpr (NARROW) {
-                    av[s][g][0] = (kok && mvalid[g]) ? arow[mcol[g]] : 0.f;
-                } else {
-                    if (kok && mvalid[g] == 4) {
-                        const float4 v = load4(arow + mcol[g], a.a_aligned, a.a_stream);
-                        av[s][g][0] = v.x; av[s][g][1] = v.y; av[s][g][2] = v.z; av[s][g][3] = v.w;
-                    } else {
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) av[s][g][t] = (kok && t < mvalid[g]) ? arow[mcol[g] + t] : 0.f;
-                    }
-                }
-            }
+            for (int g = 0; g < MG; ++g) av[s][g] = (kok && mok[g]) ? arow[16 * g + i] : 0.f;
         }
 #pragma unroll
         for (int s = 0; s < 4; ++s)
 #pragma unroll
             for (int g = 0; g < MG; ++g)
 #pragma unroll
-                for (int t = 0; t < TT; ++t)
-#pragma unroll
-                    for (int u = 0; u < NT; ++u)
-                        acc[g][t][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[s][g][t], bv[s][u], acc[g][t][u], 0, 0, 0);
+                for (int u = 0; u < NT; ++u)
+                    acc[g][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[s][g], bv[s][u], acc[g][u], 0, 0, 0);
     }
+    // the four wavefronts hold partial sums of the same tiles: add them in LDS, fixed order
     float* out = a.part + (int64_t)blockIdx.x * a.M * a.N;
-    if constexpr (NARROW) {
-        // the four wavefronts hold partial sums of the same tiles: add them in LDS, fixed order
-        __shared__ float s_red[4][MG][NT][64][4];
+    __shared__ float s_red[4][MG][NT][64][4];
+#pragma unroll
+    for (int g = 0; g < MG; ++g)
+#pragma unroll
+        for (int u = 0; u < NT; ++u)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) s_red[wave][g][u][lane][v] = acc[g][u][v];
+    __syncthreads();
+    if (wave == 0) {
 #pragma unroll
         for (int g = 0; g < MG; ++g)
 #pragma unroll
             for (int u = 0; u < NT; ++u)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) s_red[wave][g][u][lane][v] = acc[g][0][u][v];
-        __syncthreads();
-        if (wave == 0) {
-#pragma unroll
-            for (int g = 0; g < MG; ++g)
-#pragma unroll
-                for (int u = 0; u < NT; ++u)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const float sum = ((s_red[0][g][u][lane][v] + s_red[1][g][u][lane][v]) + s_red[2][g][u][lane][v]) +
-                                          s_red[3][g][u][lane][v];
-                        const int m = 16 * g + 4 * kq + v, n = 16 * u + i;
-                        if (m < a.M && n < a.N) out[(int64_t)m * a.N + n] = sum;
-                    }
-        }
-    } else {
-        // D[ii = 4*kq + v][j = i] of tile (g, t) is C[m = (wave + waves*g)*64 + 4*ii + t][n = 16u + j]
-#pragma unroll
-        for (int g = 0; g < MG; ++g)
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-#pragma unroll
-                for (int u = 0; u < NT; ++u)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int m = (wave + a.waves * g) * 64 + 4 * (4 * kq + v) + t;
-                        const int n = 16 * u + i;
-                        if (m < a.M && n < a.N) out[(int64_t)m * a.N + n] = acc[g][t][u][v];
-                    }
+                for (int v = 0; v < 4; ++v) {
+                    const float sum = ((s_red[0][g][u][lane][v] + s_red[1][g][u][lane][v]) + s_red[2][g][u][lane][v]) +
+                                      s_red[3][g][u][lane][v];
+                    const int m = 16 * g + 4 * kq + v, n = 16 * u + i;
+                    if (m < a.M && n < a.N) out[(int64_t)m * a.N + n] = sum;
+                }
     }
 }
 
-// Stage 1 of the reduction: group g of `groups` sums the partials g, g+groups, g+2*groups, ... in
+// Sum of part[p * count] over p = first, first + step, ... below parts, in ascending order; the loads of eight terms
+// are in flight together (the additions are a serial chain, the loads need not be).
+__device__ __forceinline__ float strided_sum(const float* __restrict__ part, int64_t count, int first, int step, int parts) {
+    float s = 0.f;
+    int p = first;
+    for (; p + 7 * step < parts; p += 8 * step) {
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = part[(int64_t)(p + e * step) * count];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s += v[e];
+    }
+    for (; p < parts; p += step) s += part[(int64_t)p * count];
+    return s;
+}
+
+// Stage 1 of the reduction when there are many partials: group g of `groups` sums the partials g, g+groups, ... in
 // ascending order (coalesced over the output index).
-__global__ void k_tn_fold(int64_t count, int parts, int groups, const float* __restrict__ part, float* __restrict__ out) {
+__global__ __launch_bounds__(256) void k_tn_fold(int64_t count, int parts, int groups, const float* __restrict__ part,
+                                                 float* __restrict__ out) {
     const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int g = blockIdx.y;
     if (o >= count) return;
-    float s = 0.f;
-    for (int p = g; p < parts; p += groups) s += part[(int64_t)p * count + o];
-    out[(int64_t)g * count + o] = s;
+    out[(int64_t)g * count + o] = strided_sum(part + o, count, g, groups, parts);
 }
 
-// Stage 2: sum the (few) groups in ascending order, add the bias, apply the epilogue and store;
-// `transposed` means part holds C^T (N x M row-major).
+// Stage 2: a workgroup takes 64 outputs; wavefront w sums the partials w, w + waves, ... in ascending order, the
+// wavefronts are added in order, then bias, epilogue and store.  `transposed` means part holds C^T (N x M row-major).
 template <int EPI>
-__global__ void k_tn_reduce(int32_t M, int32_t N, int parts, int transposed, const float* __restrict__ part,
-                            float* __restrict__ C, int64_t ldc, const float* __restrict__ bias,
-                            const float* __restrict__ Zprev, int64_t ldzprev) {
-    const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(1024) void k_tn_reduce(int32_t M, int32_t N, int parts, int transposed, const float* __restrict__ part,
+                                                    float* __restrict__ C, int64_t ldc, const float* __restrict__ bias,
+                                                    const float* __restrict__ Zprev, int64_t ldzprev) {
+    __shared__ float s_sum[16][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
     const int64_t count = (int64_t)M * N;
-    if (o >= count) return;
-    const int m = (int)(o / N), n = (int)(o % N);
-    const int64_t src = transposed ? (int64_t)n * M + m : o;
-    float s = 0.f;
-    for (int p = 0; p < parts; ++p) s += part[(int64_t)p * count + src];
+    const int64_t src = (int64_t)blockIdx.x * 64 + lane;
+    if (src < count) s_sum[wave][lane] = strided_sum(part + src, count, wave, waves, parts);
+    __syncthreads();
+    if (wave != 0 || src >= count) return;
+    float s = s_sum[0][lane];
+    for (int w = 1; w < waves; ++w) s += s_sum[w][lane];
+    const int m = (int)(transposed ? src % M : src / N);
+    const int n = (int)(transposed ? src / M : src % N);
     if (bias) s += bias[n];
     C[(int64_t)m * ldc + n] = epi<EPI>(s, EPI == GCN_EPI_MASK ? Zprev + (int64_t)m * ldzprev + n : nullptr);
 }
 
 static inline bool al16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
-template <int NT, bool TR>
-static void launch_tall_tr(const TallArgs& args, int epilogue, dim3 grid, size_t lds, hipStream_t s) {
+// Launches a kernel with dynamic LDS.  More than 64 KB per workgroup has to be asked for, once per kernel and device
+// (a bit per device, set after the request: two threads may both ask, which is harmless).
+template <auto Kernel, typename Args>
+static void launch_lds(dim3 grid, int threads, size_t lds, hipStream_t s, const Args& args) {
+    if (lds > 64 * 1024) {
+        static std::atomic<uint64_t> asked{0};
+        int dev = 0;
+        (void)hipGetDevice(&dev);
+        const uint64_t bit = 1ull << (dev & 63);
+        if (!(asked.load(std::memory_order_relaxed) & bit)) {
+            (void)hipFuncSetAttribute((const void*)Kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+            asked.fetch_or(bit, std::memory_order_relaxed);
+        }
+    }
+    hipLaunchKernelGGL(Kernel, grid, dim3(threads), lds, s, args);
+}
+
+template <int NT, bool TR, bool ASC>
+static void launch_tall_epi(const TallArgs& args, int epilogue, dim3 grid, int threads, size_t lds, hipStream_t s) {
     switch (epilogue) {
-        case GCN_EPI_NONE: hipLaunchKernelGGL((k_gemm_tall<NT, GCN_EPI_NONE, TR>), grid, dim3(256), lds, s, args); break;
-        case GCN_EPI_RELU: hipLaunchKernelGGL((k_gemm_tall<NT, GCN_EPI_RELU, TR>), grid, dim3(256), lds, s, args); break;
-        default: hipLaunchKernelGGL((k_gemm_tall<NT, GCN_EPI_MASK, TR>), grid, dim3(256), lds, s, args); break;
+        case GCN_EPI_NONE: launch_lds<k_gemm_tall<NT, GCN_EPI_NONE, TR, ASC>>(grid, threads, lds, s, args); break;
+        case GCN_EPI_RELU: launch_lds<k_gemm_tall<NT, GCN_EPI_RELU, TR, ASC>>(grid, threads, lds, s, args); break;
+        default: launch_lds<k_gemm_tall<NT, GCN_EPI_MASK, TR, ASC>>(grid, threads, lds, s, args); break;
     }
 }
 
 template <int NT>
-static void launch_tall(const TallArgs& args, int epilogue, dim3 grid, size_t lds, hipStream_t s) {
+static void launch_tall(const TallArgs& args, int epilogue, dim3 grid, int threads, size_t lds, hipStream_t s) {
     // 16-byte stores when every row of C (and of the mask operand) allows them
     const bool wide = (args.N % 4 == 0) && (args.ldc % 4 == 0) && al16(args.C) &&
                       (epilogue != GCN_EPI_MASK || ((args.ldzprev % 4 == 0) && al16(args.Zprev)));
-    if (wide) launch_tall_tr<NT, true>(args, epilogue, grid, lds, s);
-    else launch_tall_tr<NT, false>(args, epilogue, grid, lds, s);
+    if constexpr (NT <= 4) {
+        if (args.asc) {
+            if (wide) launch_tall_epi<NT, true, true>(args, epilogue, grid, threads, lds, s);
+            else launch_tall_epi<NT, false, true>(args, epilogue, grid, threads, lds, s);
+            return;
+        }
+    }
+    if (wide) launch_tall_epi<NT, true, false>(args, epilogue, grid, threads, lds, s);
+    else launch_tall_epi<NT, false, false>(args, epilogue, grid, threads, lds, s);
 }
 
 template <int NT, int KV>
 static void launch_flat_epi(const TallArgs& args, int waves, int epilogue, dim3 grid, size_t lds, hipStream_t s) {
-    // more than 64 KB of LDS per workgroup has to be asked for
     switch (epilogue) {
-        case GCN_EPI_NONE:
-            (void)hipFuncSetAttribute((const void*)k_gemm_tall_flat<NT, GCN_EPI_NONE, KV>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            hipLaunchKernelGGL((k_gemm_tall_flat<NT, GCN_EPI_NONE, KV>), grid, dim3(64 * waves), lds, s, args); break;
-        case GCN_EPI_RELU:
-            (void)hipFuncSetAttribute((const void*)k_gemm_tall_flat<NT, GCN_EPI_RELU, KV>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            hipLaunchKernelGGL((k_gemm_tall_flat<NT, GCN_EPI_RELU, KV>), grid, dim3(64 * waves), lds, s, args); break;
-        default:
-            (void)hipFuncSetAttribute((const void*)k_gemm_tall_flat<NT, GCN_EPI_MASK, KV>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            hipLaunchKernelGGL((k_gemm_tall_flat<NT, GCN_EPI_MASK, KV>), grid, dim3(64 * waves), lds, s, args); break;
+        case GCN_EPI_NONE: launch_lds<k_gemm_tall_flat<NT, GCN_EPI_NONE, KV>>(grid, 64 * waves, lds, s, args); break;
+        case GCN_EPI_RELU: launch_lds<k_gemm_tall_flat<NT, GCN_EPI_RELU, KV>>(grid, 64 * waves, lds, s, args); break;
+        default: launch_lds<k_gemm_tall_flat<NT, GCN_EPI_MASK, KV>>(grid, 64 * waves, lds, s, args); break;
     }
 }
 
@@ -481,66 +630,94 @@ static bool launch_tall_flat(const TallArgs& args, int NT, int KV, int waves, in
     return true;
 }
 
-template <int MG, int NT, bool NARROW>
-static void launch_tn(const TnArgs& args, int blocks, hipStream_t s) {
-    hipLaunchKernelGGL((k_gemm_tn<MG, NT, NARROW>), dim3(blocks), dim3(64 * args.waves), 0, s, args);
+template <int MG, int NT>
+static void launch_tn(const TnArgs& args, bool stream, dim3 grid, hipStream_t s) {
+    const size_t lds = args.rw > 1 ? (size_t)args.gw * MG * 4 * NT * 64 * sizeof(floatx4) : 0;
+    if (stream) launch_lds<k_gemm_tn<MG, NT, true>>(grid, 64 * args.gw * args.rw, lds, s, args);
+    else launch_lds<k_gemm_tn<MG, NT, false>>(grid, 64 * args.gw * args.rw, lds, s, args);
 }
 
-// Launch geometry of the MFMA A^T B product (K long): which operand goes on the 64-column groups, wavefronts
-// per workgroup, split of K, partial buffers.  Returns false when the shape is left to the plain kernel.
+// Launch geometry of the A^T B product (K long): which operand goes on the 64-column groups, wavefronts per
+// workgroup, split of K, partial buffers.  Any shape.
 struct TnShape {
     bool swap, narrow;
     int64_t Mw, Nw, blocks, kpb;
-    int NTn, W, MG, fold;
+    int NT, ny, nz, gw, rw, MG, fold;
     size_t scratch_bytes;
 };
 
-static bool tn_shape(int64_t M, int64_t N, int64_t K, TnShape* g) {
-    if (K < 1024) return false;
+static TnShape tn_shape(int64_t M, int64_t N, int64_t K) {
+    TnShape g;
     // Put the wider of (M, N) on the 64-column groups: if N > M compute C^T = B^T A and let the
     // reduction write it back transposed.
-    g->swap = N > M;
-    g->Mw = g->swap ? N : M;
-    g->Nw = g->swap ? M : N;
-    if (g->Nw > 32 || g->Mw > 1024) return false;        // narrow side up to 32, wide side up to 1024
-    g->NTn = (int)((g->Nw + 15) / 16);
-    g->narrow = g->Mw <= 32;
-    const int groups = (int)((g->Mw + 63) / 64);
-    // wavefronts per workgroup: one per column group up to 8, else the count in 4..8 that leaves the
-    // fewest idle slots (300 columns: 5 groups on 5 wavefronts instead of 2+1+1+1 on 4)
-    int W = 4;
-    if (!g->narrow) {
-        if (groups <= 8) W = groups < 2 ? 2 : groups;
-        else {
+    g.swap = N > M;
+    g.Mw = g.swap ? N : M;
+    g.Nw = g.swap ? M : N;
+    const int nt = (int)((g.Nw + 15) / 16);
+    g.ny = (nt + 3) / 4;                                  // up to 64 columns of B per wavefront, in equal shares
+    g.NT = (nt + g.ny - 1) / g.ny;
+    g.narrow = g.Mw <= 32;
+    const int groups = (int)((g.Mw + 63) / 64);
+    g.rw = 1; g.nz = 1; g.gw = 4;
+    if (g.narrow) {
+        g.MG = (int)((g.Mw + 15) / 16);
+    } else {
+        // column groups per wavefront: what the accumulators leave room for (up to 128 registers)
+        const int mg_max = g.NT >= 3 ? 2 : (g.NT == 2 ? 3 : 4);
+        // wavefronts on different groups: one per group up to 8, else the count in 4..8 that leaves the fewest idle
+        // slots (300 columns: 5 groups on 5 wavefronts instead of 2+1+1+1 on 4)
+        g.gw = groups;
+        if (groups > 8) {
             int best = 1 << 30;
             for (int w = 4; w <= 8; ++w) {
                 const int idle = (groups + w - 1) / w * w - groups;
-                if (idle < best) { best = idle; W = w; }
+                if (idle < best) { best = idle; g.gw = w; }
             }
         }
+        g.rw = g.gw >= 4 ? 1 : 4 / g.gw;                  // 1 group: 4 sets of rows, 2: 2, 3: 1
+        g.MG = (groups + g.gw - 1) / g.gw;
+        if (g.MG > mg_max) g.MG = mg_max;
+        g.nz = (groups + g.gw * g.MG - 1) / (g.gw * g.MG);
     }
-    g->W = W;
-    g->MG = g->narrow ? (int)((g->Mw + 15) / 16) : (groups + W - 1) / W;   // tiles (narrow) or column groups per wavefront
-    int64_t blocks = K / 256;                             // at least 256 rows per workgroup
+    // Workgroups over K: at least two trips of every wavefront each,
+    const int64_t rows = g.narrow ? 64 : 16 * g.rw;       // rows per trip of a workgroup
+    const int64_t count = g.Mw * g.Nw;
+    int64_t blocks = K / (2 * rows);
     // measured: more, shorter workgroups pay when a workgroup has five or more wavefronts (300 columns:
     // 4.13 ms with 2048 workgroups, 3.84 ms with 8192), fewer otherwise (256 columns: 2.69 vs 2.84 ms)
-    // and when it has two or three, so that enough wavefronts exist (128 columns: 1.74 vs 1.47 ms)
-    const int64_t max_blocks = g->narrow ? 2048 : (W >= 5 ? 8192 : (W <= 3 ? 16384 / W : 2048));
-    if (blocks > max_blocks) blocks = max_blocks;
+    int64_t most = g.narrow ? 2048 : (g.gw >= 5 ? 8192 : (g.gw >= 4 ? 2048 : 4096));
+    // the partial results are written and read once more: keep them below an eighth of the operands' bytes, unless
+    // that leaves fewer than 64 workgroups over K (fewer still where the result alone is large)
+    const int64_t fair = K * (g.Mw + g.Nw) / (16 * count);
+    const int64_t least = count >= (1ll << 26) ? 1 : (count > (1ll << 20) ? (1ll << 26) / count : 64);
+    if (most > fair) most = fair < least ? least : fair;
+    if (blocks > most) blocks = most;
     if (blocks < 1) blocks = 1;
     int64_t kpb = (K + blocks - 1) / blocks;
-    kpb = (kpb + 63) & ~63ll;
-    blocks = (K + kpb - 1) / kpb;
-    g->blocks = blocks;
-    g->kpb = kpb;
-    g->fold = blocks > 64 ? 32 : 0;                       // two-stage reduction when there are many partials
-    g->scratch_bytes = (size_t)(blocks + g->fold) * g->Mw * g->Nw * sizeof(float);
-    return true;
+    kpb = (kpb + rows - 1) / rows * rows;
+    g.kpb = kpb;
+    g.blocks = (K + kpb - 1) / kpb;
+    g.fold = g.blocks > 512 ? 64 : 0;                     // two-stage reduction when there are many partials
+    g.scratch_bytes = (size_t)(g.blocks + g.fold) * count * sizeof(float);
+    return g;
+}
+
+// C = the sum of `parts` partial results (each M x N, or N x M when transposed) in a fixed order, plus bias, epilogue.
+int reduce_parts_launch(int32_t M, int32_t N, int parts, bool transposed, const float* part, float* C, int64_t ldc,
+                        const float* bias, int epilogue, const float* Zprev, int64_t ldzprev, hipStream_t s) {
+    const int64_t count = (int64_t)M * N;
+    const dim3 grid((unsigned)((count + 63) / 64)), block(64 * (parts >= 16 ? 16 : parts));
+    switch (epilogue) {
+        case GCN_EPI_NONE: hipLaunchKernelGGL(k_tn_reduce<GCN_EPI_NONE>, grid, block, 0, s, M, N, parts, (int)transposed, part, C, ldc, bias, Zprev, ldzprev); break;
+        case GCN_EPI_RELU: hipLaunchKernelGGL(k_tn_reduce<GCN_EPI_RELU>, grid, block, 0, s, M, N, parts, (int)transposed, part, C, ldc, bias, Zprev, ldzprev); break;
+        default: hipLaunchKernelGGL(k_tn_reduce<GCN_EPI_MASK>, grid, block, 0, s, M, N, parts, (int)transposed, part, C, ldc, bias, Zprev, ldzprev); break;
+    }
+    GCN_LAUNCH_CHECK();
+    return GCN_OK;
 }
 
 size_t gemm_mfma_tn_scratch_bytes(int64_t M, int64_t N, int64_t K) {
-    TnShape g;
-    return tn_shape(M, N, K, &g) ? g.scratch_bytes : 0;
+    return tn_shape(M, N, K).scratch_bytes;
 }
 
 int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, const float* B,
@@ -549,27 +726,33 @@ int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const floa
     *handled = false;
     *scaled = false;
     if (!ta) {
-        if (K > 4096 || N > 4096 || M < 64) return GCN_OK;
+        if (K > 4096 || N > 65535 * 16 || M < 64) return GCN_OK;
         const int nt_total = (int)((N + 15) / 16);
-        // tiles per wavefront: as many as fit (whole rows of C from one wavefront when N <= 256), while
-        // op(B) for them stays within 40 KB of LDS
+        // tiles per wavefront: as many as fit (whole rows of C from one wavefront when N <= 256), while op(B) for them
+        // stays within 40 KB of LDS; up to four tiles in any case, as long as op(B) fits a compute unit's LDS at all
         const int64_t kpad = (K + 15) & ~15ll;
+        auto b_bytes = [&](int tiles) { return (size_t)(kpad * (16 * tiles + 4)) * sizeof(float); };
         int NT = nt_total >= 4 ? 4 : nt_total;
-        if (nt_total >= 16 && kpad * (16 * 16 + 4) * 4 <= 40 * 1024) NT = 16;
-        else if (nt_total >= 8 && kpad * (16 * 8 + 4) * 4 <= 40 * 1024) NT = 8;
+        if (nt_total >= 16 && b_bytes(16) <= 40 * 1024) NT = 16;
+        else if (nt_total >= 8 && b_bytes(8) <= 40 * 1024) NT = 8;
+        // Second operands beyond 64 KB are multiplied in ascending k: 256 x 64 on 120 K rows took 704 us with one thread
+        // per element in that order; keeping the order keeps the bits of the hidden activations, on whose signs
+        // the ReLU decides.
+        const bool ascending = b_bytes(NT) > 64 * 1024;
+        while (NT > 1 && b_bytes(NT) > 150 * 1024) --NT;
         TallArgs args;
         args.M = M; args.N = (int32_t)N; args.K = (int32_t)K;
         args.A = A; args.lda = lda; args.B = B; args.ldb = ldb; args.tb = tb;
         args.C = C; args.ldc = ldc; args.bias = bias; args.Zprev = Zprev; args.ldzprev = ldzprev;
-        args.Kpad = (int32_t)((K + 15) & ~15ll);
+        args.Kpad = (int32_t)kpad;
+        args.asc = ascending;
         args.S = 16 * NT + 4;
-        args.a_aligned = (lda % 4 == 0) && al16(A);
         const bool wide_c = (N % 4 == 0) && (ldc % 4 == 0) && al16(C) &&
                             (epilogue != GCN_EPI_MASK || ((ldzprev % 4 == 0) && al16(Zprev)));
         args.row_scale = wide_c ? row_scale : nullptr;       // the 16-byte store path applies it; else the caller does
         *scaled = args.row_scale != nullptr;
-        const size_t lds = (size_t)args.Kpad * args.S * sizeof(float);
-        if (lds > 64 * 1024) { *scaled = false; return GCN_OK; }
+        const size_t lds = b_bytes(NT);
+        if (lds > 150 * 1024) { *scaled = false; return GCN_OK; }
         const int64_t ntiles = (M + 15) / 16;
         {   // rows that are not whole 128-byte lines, and short rows (up to 208 floats, where the coalesced copy also beats
             // the strided 64-byte pieces: 128 floats 1.02 -> 0.96 ms on 8.7 M rows; at 256 floats it loses, 3.14 -> 3.23 ms):
@@ -583,7 +766,7 @@ int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const floa
             int fw = (int)((150 * 1024 - (int64_t)lds) / ((int64_t)KV * 256 * sizeof(float)));
             fw = fw > 4 ? 4 : fw;
             const size_t lds_flat = lds + (size_t)(fw > 0 ? fw : 1) * KV * 256 * sizeof(float);
-            if (fw >= 2 && wide && lda == K && (K % 4) == 0 && (((K * 4) % 128) != 0 || K <= 208) && K >= 64 && kv_need <= 19 && NT <= 2 && al16(A) &&
+            if (fw >= 2 && wide && !ascending && lda == K && (K % 4) == 0 && (((K * 4) % 128) != 0 || K <= 208) && K >= 64 && kv_need <= 19 && NT <= 2 && al16(A) &&
                 lds_flat <= 150 * 1024 && M >= 4096) {
                 int64_t fb = (ntiles + fw - 1) / fw;
                 const int per_cu = (int)((160 * 1024) / lds_flat);
@@ -597,17 +780,19 @@ int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const floa
                 }
             }
         }
-        int64_t bx = (ntiles + 3) / 4;
-        const int64_t cap = 256 * (lds > 40 * 1024 ? 3 : (lds > 20 * 1024 ? 6 : 8));
+        // eight wavefronts share op(B) when only one or two workgroups fit a compute unit beside each other
+        const int waves = lds > 40 * 1024 ? 8 : 4;
+        int64_t bx = (ntiles + waves - 1) / waves;
+        const int64_t cap = 256 * (lds > 80 * 1024 ? 1 : (lds > 53 * 1024 ? 2 : (lds > 40 * 1024 ? 3 : (lds > 20 * 1024 ? 6 : 8))));
         if (bx > cap) bx = cap;
         const dim3 grid((unsigned)bx, (unsigned)((nt_total + NT - 1) / NT));
         switch (NT) {
-            case 1: launch_tall<1>(args, epilogue, grid, lds, s); break;
-            case 2: launch_tall<2>(args, epilogue, grid, lds, s); break;
-            case 3: launch_tall<3>(args, epilogue, grid, lds, s); break;
-            case 4: launch_tall<4>(args, epilogue, grid, lds, s); break;
-            case 8: launch_tall<8>(args, epilogue, grid, lds, s); break;
-            default: launch_tall<16>(args, epilogue, grid, lds, s); break;
+            case 1: launch_tall<1>(args, epilogue, grid, 64 * waves, lds, s); break;
+            case 2: launch_tall<2>(args, epilogue, grid, 64 * waves, lds, s); break;
+            case 3: launch_tall<3>(args, epilogue, grid, 64 * waves, lds, s); break;
+            case 4: launch_tall<4>(args, epilogue, grid, 64 * waves, lds, s); break;
+            case 8: launch_tall<8>(args, epilogue, grid, 64 * waves, lds, s); break;
+            default: launch_tall<16>(args, epilogue, grid, 64 * waves, lds, s); break;
         }
         GCN_LAUNCH_CHECK();
         *handled = true;
@@ -615,49 +800,42 @@ int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const floa
     }
     // ta: C = A^T B with K long
     if (tb) return GCN_OK;
-    TnShape g;
-    if (!tn_shape(M, N, K, &g)) return GCN_OK;
-    const bool swap = g.swap, narrow = g.narrow;
-    const float* Aw = swap ? B : A;
-    const float* Bw = swap ? A : B;
-    const int64_t ldaw = swap ? ldb : lda, ldbw = swap ? lda : ldb;
-    const int64_t Mw = g.Mw, Nw = g.Nw, blocks = g.blocks, kpb = g.kpb;
-    const int NTn = g.NTn, W = g.W, MG = g.MG, fold = g.fold;
+    const TnShape g = tn_shape(M, N, K);
+    if (g.blocks >= (1ll << 31) || g.ny > 65535 || g.nz > 65535 || M * N >= (1ll << 36)) return fail(GCN_ERR_RANGE, "gcn_gemm: output too large");
     void* scratch = nullptr;
     GCN_TRY(scratch_get(&scratch, g.scratch_bytes, s));
     TnArgs args;
-    args.K = K; args.M = (int32_t)Mw; args.N = (int32_t)Nw;
-    args.A = Aw; args.lda = ldaw; args.B = Bw; args.ldb = ldbw;
-    args.part = (float*)scratch; args.k_per_block = kpb;
-    args.a_aligned = (ldaw % 4 == 0) && al16(Aw);
-    args.a_stream = args.a_aligned && (ldaw % 32 == 0) && (((uintptr_t)Aw & 127u) == 0);
-    args.waves = W;
-#define GCN_TN_CASE(mg, nt) if (!narrow && MG == mg && NTn == nt) launch_tn<mg, nt, false>(args, (int)blocks, s)
+    args.K = K; args.M = (int32_t)g.Mw; args.N = (int32_t)g.Nw;
+    args.A = g.swap ? B : A; args.lda = g.swap ? ldb : lda;
+    args.B = g.swap ? A : B; args.ldb = g.swap ? lda : ldb;
+    args.part = (float*)scratch; args.k_per_block = g.kpb;
+    // rows of A that are whole 128-byte lines, read once: non-temporal loads
+    const bool stream = (args.lda % 32 == 0) && (((uintptr_t)args.A & 127u) == 0) && g.ny == 1;
+    args.gw = g.gw; args.rw = g.rw;
+    const dim3 grid((unsigned)g.blocks, (unsigned)g.ny, (unsigned)g.nz);
+    if (g.narrow) {
+        if (g.MG == 1) hipLaunchKernelGGL((k_gemm_tn_narrow<1, 1>), grid, dim3(256), 0, s, args);
+        else if (g.NT == 1) hipLaunchKernelGGL((k_gemm_tn_narrow<2, 1>), grid, dim3(256), 0, s, args);
+        else hipLaunchKernelGGL((k_gemm_tn_narrow<2, 2>), grid, dim3(256), 0, s, args);
+    }
+#define GCN_TN_CASE(mg, nt) else if (g.MG == mg && g.NT == nt) launch_tn<mg, nt>(args, stream, grid, s)
     GCN_TN_CASE(1, 1); GCN_TN_CASE(2, 1); GCN_TN_CASE(3, 1); GCN_TN_CASE(4, 1);
-    GCN_TN_CASE(1, 2); GCN_TN_CASE(2, 2); GCN_TN_CASE(3, 2); GCN_TN_CASE(4, 2);
-    if (narrow && MG == 1 && NTn == 1) launch_tn<1, 1, true>(args, (int)blocks, s);
-    if (narrow && MG == 2 && NTn == 1) launch_tn<2, 1, true>(args, (int)blocks, s);
-    if (narrow && MG == 2 && NTn == 2) launch_tn<2, 2, true>(args, (int)blocks, s);
+    GCN_TN_CASE(1, 2); GCN_TN_CASE(2, 2); GCN_TN_CASE(3, 2);
+    GCN_TN_CASE(1, 3); GCN_TN_CASE(2, 3); GCN_TN_CASE(1, 4); GCN_TN_CASE(2, 4);
 #undef GCN_TN_CASE
     GCN_LAUNCH_CHECK();
     const int64_t count = M * N;
     const float* red_src = (const float*)scratch;
-    int red_parts = (int)blocks;
-    if (fold) {
-        float* folded = (float*)scratch + blocks * count;
-        hipLaunchKernelGGL(k_tn_fold, dim3((unsigned)((count + 255) / 256), (unsigned)fold), dim3(256), 0, s, count,
-                           (int)blocks, fold, (const float*)scratch, folded);
+    int red_parts = (int)g.blocks;
+    if (g.fold) {
+        float* folded = (float*)scratch + g.blocks * count;
+        hipLaunchKernelGGL(k_tn_fold, dim3((unsigned)((count + 255) / 256), (unsigned)g.fold), dim3(256), 0, s, count,
+                           (int)g.blocks, g.fold, (const float*)scratch, folded);
         GCN_LAUNCH_CHECK();
         red_src = folded;
-        red_parts = fold;
+        red_parts = g.fold;
     }
-    const dim3 rgrid((unsigned)((count + 255) / 256));
-    switch (epilogue) {
-        case GCN_EPI_NONE: hipLaunchKernelGGL(k_tn_reduce<GCN_EPI_NONE>, rgrid, dim3(256), 0, s, (int32_t)M, (int32_t)N, red_parts, (int)swap, red_src, C, ldc, bias, Zprev, ldzprev); break;
-        case GCN_EPI_RELU: hipLaunchKernelGGL(k_tn_reduce<GCN_EPI_RELU>, rgrid, dim3(256), 0, s, (int32_t)M, (int32_t)N, red_parts, (int)swap, red_src, C, ldc, bias, Zprev, ldzprev); break;
-        default: hipLaunchKernelGGL(k_tn_reduce<GCN_EPI_MASK>, rgrid, dim3(256), 0, s, (int32_t)M, (int32_t)N, red_parts, (int)swap, red_src, C, ldc, bias, Zprev, ldzprev); break;
-    }
-    GCN_LAUNCH_CHECK();
+    GCN_TRY(reduce_parts_launch((int32_t)M, (int32_t)N, red_parts, g.swap, red_src, C, ldc, bias, epilogue, Zprev, ldzprev, s));
     *handled = true;
     return GCN_OK;
 }

@@ -108,7 +108,8 @@ static int layer_backward_impl(gcn_csr* a, int32_t f_in, int32_t f_out, const fl
 struct EpochLayout {
     std::vector<size_t> Z, H, T, G;   // byte offsets per layer index 0..L_w-1 (layer l = index + 1)
     size_t S = 0, XS = 0, total = 0;  // XS: pre-scaled SpMM operand of the value-free product
-    size_t scratch = 0, scratch_bytes = 0;   // split-K partials of the weight gradients, loss partials
+    size_t scratch = 0;               // partial sums of the fused last layer, and the next where they do not fit XS
+    size_t part = 0, part_bytes = 0;  // partial sums of the weight gradients and of the loss
     std::vector<int> order;
 };
 
@@ -133,20 +134,25 @@ static EpochLayout epoch_layout(int64_t n, int32_t L, const int32_t* dims, int o
     }
     lay.S = take(smax);
     lay.XS = take(smax);
-    // the partial sums of the reductions over n live in the caller's workspace too, so that an epoch never
-    // touches library-owned scratch (which is per stream and would have to exist before a graph capture)
-    size_t sc = loss_scratch_bytes();
+    // The partial sums of the reductions over n live in the caller's workspace too, so that an epoch never touches
+    // library-owned scratch (which is per stream and would have to exist before a graph capture).  XS is idle outside
+    // the sparse products: it holds the partial sums of the weight gradients and of the loss where it is large
+    // enough, and a region of their own holds what does not fit.
+    size_t sc = loss_scratch_bytes(), tn = sc;
     for (int l = 0; l < L; ++l) {
         const size_t need = gemm_tn_scratch_bytes(dims[l], dims[l + 1], n);
-        if (need > sc) sc = need;
+        if (need > tn) tn = need;
     }
+    const size_t xs_bytes = smax * sizeof(float);
+    if (tn > xs_bytes && tn > sc) sc = tn;
     // the fused last layer (SpMM-first order; a single layer can be put into that order by the pre-aggregated epoch)
     if ((lay.order[L - 1] == GCN_ORDER_SPMM_FIRST || L == 1) && fused_last_supported(dims[L - 1], dims[L])) {
         const size_t need = fused_last_scratch_bytes(n, dims[L]);
         if (need > sc) sc = need;
     }
-    lay.scratch_bytes = sc;
     lay.scratch = take((sc + sizeof(float) - 1) / sizeof(float));
+    lay.part = tn > xs_bytes ? lay.scratch : lay.XS;
+    lay.part_bytes = tn > xs_bytes ? sc : xs_bytes;
     lay.total = off;
     return lay;
 }
@@ -230,7 +236,7 @@ static int epoch_impl(gcn_csr* a, int32_t L_w, const int32_t* dims, const float*
     hipStream_t s = (hipStream_t)stream;
     char* ws = (char*)workspace;
     auto at = [&](size_t off) { return (float*)(ws + off); };
-    ScratchScope scratch_scope(ws + lay.scratch, lay.scratch_bytes);
+    ScratchScope scratch_scope(ws + lay.part, lay.part_bytes);
     // With P0 = A^T H0 given, layer 1 runs in SpMM-first order on it: Z^1 = P0 W^1, Y^1 = P0^T G^1, and
     // neither direction needs a sparse product.
     auto layer_order = [&](int l) { return (l == 0 && P0) ? (int)GCN_ORDER_SPMM_FIRST : lay.order[l]; };

@@ -1,0 +1,94 @@
+"""Kernels and dispatch rules at the sizes where they can go wrong: tile edges, remainders, smallest and largest of a
+range.  Every comparison is against the CPU oracle."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+from util import assert_close
+
+pytestmark = pytest.mark.gpu
+
+
+def G():
+    import paper_2005_03300_amd as g
+    return g
+
+
+def dev(x):
+    return torch.from_numpy(np.ascontiguousarray(x)).cuda()
+
+
+def host(x):
+    return x.detach().cpu().numpy()
+
+
+@pytest.mark.parametrize("K,M,N", [
+    (1, 70, 70), (15, 64, 33), (17, 33, 33), (63, 65, 40), (130, 48, 34),          # fewer rows than a workgroup's trip
+    (5000, 64, 41), (3001, 41, 64), (4096, 64, 64), (3000, 65, 17),                # one and two column groups, four and two row sets
+    (2001, 192, 48), (2500, 256, 64), (3007, 602, 64), (1500, 256, 100),           # three, four and ten groups; 16 to 64 columns of B
+    (1100, 520, 130), (700, 1100, 65), (900, 2100, 20),                            # more columns than one workgroup takes
+    (300_000, 64, 64), (200_000, 64, 16)])                                         # two-stage reduction of the partial results
+def test_gemm_tn_any_shape(K, M, N):
+    g = G()
+    H = synth.normal_features(K, M, 41)
+    S = synth.normal_features(K, N, 42)
+    Yd = torch.full((M, N), float("nan"), device="cuda")
+    g.gcn_gemm(1, 0, dev(H), dev(S), Yd)
+    first = host(Yd)
+    want = H.astype(np.float64).T @ S.astype(np.float64)
+    assert_close(first, want, f"TN {K}: {M}x{N}")
+    g.gcn_gemm(1, 0, dev(H), dev(S), Yd)
+    np.testing.assert_array_equal(first.view(np.uint32), host(Yd).view(np.uint32))
+
+
+def test_gemm_tn_epilogues_and_pitch():
+    g = G()
+    K, M, N = 3000, 70, 50
+    H = synth.normal_features(K, M, 43)
+    S = synth.normal_features(K, N, 44)
+    bias = synth.normal_features(1, N, 45)[0]
+    Zp = synth.normal_features(M, N, 46)
+    Hd = dev(np.concatenate([H, np.full((K, 7), np.nan, np.float32)], 1))[:, :M]
+    Cd = torch.full((M, N + 3), float("nan"), device="cuda")
+    want = H.astype(np.float64).T @ S.astype(np.float64)
+    g.gcn_gemm(1, 0, Hd, dev(S), Cd[:, :N], bias=dev(bias), epilogue=g.EPI_RELU)
+    assert np.all(np.isnan(host(Cd)[:, N:]))
+    assert_close(host(Cd)[:, :N], np.maximum(want + bias, 0), "TN + bias + relu")
+    g.gcn_gemm(1, 0, Hd, dev(S), Cd[:, :N], epilogue=g.EPI_MASK, Zprev=dev(Zp))
+    assert_close(host(Cd)[:, :N], np.where(Zp > 0, want, 0), "TN + mask")
+
+
+@pytest.mark.parametrize("M,K,N", [(4100, 256, 64), (2049, 602, 64), (1000, 602, 256), (130, 1000, 48), (70, 1900, 20),
+                                   (65, 2300, 17), (300, 240, 41), (1025, 512, 32)])
+def test_gemm_nn_wide_second_operand(M, K, N):
+    """op(B) between 40 KB and a compute unit's LDS, in one or several column passes, and beyond it."""
+    g = G()
+    A = synth.normal_features(M, K, 47)
+    B = synth.normal_features(K, N, 48)
+    Cd = torch.full((M, N), float("nan"), device="cuda")
+    g.gcn_gemm(0, 0, dev(A), dev(B), Cd)
+    want = A.astype(np.float64) @ B.astype(np.float64)
+    assert_close(host(Cd), want, f"NN {M}x{K}x{N}")
+    Zp = synth.normal_features(M, N, 49)
+    g.gcn_gemm(0, 1, dev(A), dev(np.ascontiguousarray(B.T)), Cd, epilogue=g.EPI_MASK, Zprev=dev(Zp))
+    assert_close(host(Cd), np.where(Zp > 0, want, 0), f"NT + mask {M}x{K}x{N}")
+
+
+@pytest.mark.parametrize("n,f", [(1, 1), (127, 3), (129, 41), (5000, 64), (4097, 65), (2500, 130), (200_001, 5)])
+def test_bias_gradient(n, f):
+    """dbias of the per-layer backward call: column sums of G."""
+    g = G()
+    src = np.arange(n, dtype=np.int32)
+    a = g.gcn_csr_create(n, dev(src), dev(np.roll(src, 1)), g.ADD_SELF_LOOPS | g.NORM_ROW | g.BUILD_TRANSPOSE)
+    Gm = synth.normal_features(n, f, 50)
+    Hin = synth.normal_features(n, f, 51)
+    W = torch.eye(f, device="cuda")
+    S, Y, db = torch.empty(n, f, device="cuda"), torch.empty(f, f, device="cuda"), torch.full((f,), float("nan"), device="cuda")
+    g.gcn_layer_backward(a, dev(Hin), None, W, dev(Gm), S, S, Y, None, order=g.ORDER_GEMM_FIRST, dbias=db)
+    want = Gm.astype(np.float64).sum(0)
+    assert np.all(np.abs(host(db) - want) <= 1e-5 * np.sqrt(n) * np.maximum(1.0, np.abs(want)))
+    a.close()
