@@ -20,6 +20,8 @@
  *     can be captured in a HIP graph from their first call on.  Nothing the library has handed to a kernel is
  *     freed before gcn_csr_destroy (a larger buffer replaces a smaller one, which is kept), so graphs captured
  *     earlier stay valid.
+ *   - A matrix that gcn_csr_create symmetrised and did not normalise by rows equals its transpose bit by bit: it is
+ *     stored once, and gcn_csr_arrays gives the same arrays for both.
  *   - Library-owned scratch exists only for the stand-alone gcn_gemm (ta = 1), gcn_softmax_nll* and the bias
  *     gradient of gcn_layer_backward: one buffer per (device, stream), grown on demand by the first call that
  *     needs more (an allocation), never shared between streams; gcn_scratch_release frees all of them.  The
@@ -307,7 +309,9 @@ int gcn_epoch_view(int64_t n, int32_t L_w, const int32_t* dims, int order, void*
 int gcn_config(int key, int value);
 int gcn_csr_config(gcn_csr* a, int key, int value);
 
-/* Frees the library-owned per-stream scratch (after waiting for the device); later calls allocate it again. */
+/* Frees the library-owned per-stream scratch (after waiting for the device); later calls allocate it again.  Also gives
+ * back what the library keeps of destroyed matrices and of graph construction to build the next matrix from: at most 1/64
+ * of the device's memory, which an allocation of this library that would fail otherwise takes too. */
 int gcn_scratch_release(void);
 
 /* With GCN_CFG_TIMING = 1 the SpMM main kernel is bracketed by HIP events on its own stream.

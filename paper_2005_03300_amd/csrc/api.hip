@@ -4,6 +4,7 @@
 
 #include <atomic>
 #include <mutex>
+#include <unordered_map>
 #include <vector>
 
 #include "common.h"
@@ -27,21 +28,167 @@ int fail(int code, const char* fmt, ...) {
     return code;
 }
 
+// ---- device memory ---------------------------------------------------------------------------
+namespace {
+struct Block { void* p; size_t bytes; int device; };
+std::mutex g_pool_mu;
+std::vector<Block> g_pool;                          // given back and kept, oldest first
+std::unordered_map<void*, Block> g_live;            // handed out
+
+int current_device() {
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    return dev;
+}
+
+// takes the smallest block of `list` that holds `bytes` and is not larger than `most`
+bool take_block(std::vector<Block>& list, int dev, size_t bytes, size_t most, Block* out) {
+    int best = -1;
+    for (int i = 0; i < (int)list.size(); ++i)
+        if (list[i].device == dev && list[i].bytes >= bytes && list[i].bytes <= most &&
+            (best < 0 || list[i].bytes < list[best].bytes))
+            best = i;
+    if (best < 0) return false;
+    *out = list[best];
+    list.erase(list.begin() + best);
+    return true;
+}
+
+size_t pool_limit(int dev) {
+    static std::mutex mu;
+    static size_t limit[64] = {};
+    if (dev < 0 || dev >= 64) dev = 0;
+    std::lock_guard<std::mutex> lk(mu);
+    if (!limit[dev]) {
+        size_t total = 0;
+        hipDeviceProp_t prop;
+        if (hipGetDeviceProperties(&prop, dev) == hipSuccess) total = prop.totalGlobalMem;
+        limit[dev] = total / 64 + 1;
+    }
+    return limit[dev];
+}
+}  // namespace
+
+void device_pool_release() {
+    std::vector<Block> all;
+    {
+        std::lock_guard<std::mutex> lk(g_pool_mu);
+        all.swap(g_pool);
+    }
+    for (auto& b : all) (void)hipFree(b.p);
+}
+
 int device_alloc(void** p, size_t bytes) {
     *p = nullptr;
-    if (bytes == 0) bytes = 16;
+    const size_t unit = bytes >= (1u << 20) ? (size_t)1 << 16 : 512;
+    bytes = bytes == 0 ? unit : (bytes + unit - 1) / unit * unit;
+    const int dev = current_device();
+    Block b;
+    {
+        std::lock_guard<std::mutex> lk(g_pool_mu);
+        if (take_block(g_pool, dev, bytes, bytes + bytes / 8 + 4096, &b)) {
+            g_live[b.p] = b;
+            *p = b.p;
+            return GCN_OK;
+        }
+    }
     hipError_t e = hipMalloc(p, bytes);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        device_pool_release();
+        e = hipMalloc(p, bytes);
+    }
     if (e != hipSuccess) {
         (void)hipGetLastError();
         *p = nullptr;
         return fail(e == hipErrorOutOfMemory ? GCN_ERR_OOM : GCN_ERR_HIP, "hipMalloc(%zu) failed: %s", bytes,
                     hipGetErrorString(e));
     }
+    std::lock_guard<std::mutex> lk(g_pool_mu);
+    g_live[*p] = Block{*p, bytes, dev};
     return GCN_OK;
 }
 
 void device_free(void* p) {
-    if (p) (void)hipFree(p);
+    if (!p) return;
+    std::vector<Block> out;
+    {
+        std::lock_guard<std::mutex> lk(g_pool_mu);
+        auto it = g_live.find(p);
+        if (it == g_live.end()) {
+            out.push_back({p, 0, 0});
+        } else {
+            const Block b = it->second;
+            g_live.erase(it);
+            const size_t limit = pool_limit(b.device);
+            if (b.bytes > limit) {
+                out.push_back(b);
+            } else {
+                size_t held = b.bytes;
+                for (auto& x : g_pool)
+                    if (x.device == b.device) held += x.bytes;
+                for (size_t i = 0; i < g_pool.size() && held > limit;) {
+                    if (g_pool[i].device != b.device) { ++i; continue; }
+                    held -= g_pool[i].bytes;
+                    out.push_back(g_pool[i]);
+                    g_pool.erase(g_pool.begin() + (long)i);
+                }
+                g_pool.push_back(b);
+            }
+        }
+    }
+    for (auto& x : out) (void)hipFree(x.p);
+}
+
+// ---- temporaries of graph construction ---------------------------------------------------------
+namespace {
+struct Build {
+    hipStream_t stream;
+    std::vector<Block> spare;                       // dropped by this build, reusable on its stream
+};
+thread_local Build* g_build = nullptr;
+constexpr size_t BUILD_SPARE_MAX = (size_t)1 << 30; // larger temporaries leave at once: they decide the peak
+}  // namespace
+
+BuildScope::BuildScope(hipStream_t s) : owner(g_build == nullptr) {
+    if (owner) g_build = new Build{s, {}};
+}
+BuildScope::~BuildScope() {
+    if (!owner) return;
+    Build* b = g_build;
+    g_build = nullptr;
+    (void)hipStreamSynchronize(b->stream);
+    for (auto& x : b->spare) device_free(x.p);
+    delete b;
+}
+
+int temp_alloc(void** p, size_t bytes) {
+    Block b;
+    if (g_build && take_block(g_build->spare, current_device(), bytes, 2 * bytes + 65536, &b)) {
+        *p = b.p;
+        return GCN_OK;
+    }
+    return device_alloc(p, bytes);
+}
+
+void temp_free(void* p) {
+    if (!p) return;
+    if (g_build) {
+        Block b{p, 0, 0};
+        {
+            std::lock_guard<std::mutex> lk(g_pool_mu);
+            auto it = g_live.find(p);
+            if (it != g_live.end()) b = it->second;
+        }
+        if (b.bytes > 0 && b.bytes <= BUILD_SPARE_MAX) {
+            g_build->spare.push_back(b);
+            return;
+        }
+        (void)hipStreamSynchronize(g_build->stream);
+    } else {
+        (void)hipDeviceSynchronize();
+    }
+    device_free(p);
 }
 
 // ---- per-stream scratch ------------------------------------------------------------------------
@@ -128,7 +275,7 @@ Config& config() {
 int g_last_schedule = 0;
 
 static std::atomic<int64_t> g_builds{0};
-void count_build() { g_builds.fetch_add(1); }
+void count_build(const Matrix& m) { g_builds.fetch_add(m.both ? 2 : 1); }
 
 // ---- event timing ---------------------------------------------------------------------------
 struct TimedSpan { hipEvent_t a, b; int phase; };
@@ -323,9 +470,13 @@ int gcn_timing_read(int64_t* launches, double* total_ms) {
 
 int gcn_csr_destroy(gcn_csr* a) {
     if (!a) return GCN_OK;
+    // what the matrix owns is given back to be used again: nothing queued on its device may still need it
+    const int dev = current_device();
+    if (dev != a->device) (void)hipSetDevice(a->device);
     (void)hipDeviceSynchronize();
+    if (dev != a->device) (void)hipSetDevice(dev);
     free_matrix(a->A);
-    free_matrix(a->At);
+    if (!a->symmetric) free_matrix(a->At);
     device_free(a->carry2);
     device_free(a->deg);
     device_free(a->inv_sqrt_deg);
@@ -344,6 +495,7 @@ int gcn_scratch_release(void) {
     for (void* p : g_scratch_retired) device_free(p);
     g_arenas.clear();
     g_scratch_retired.clear();
+    device_pool_release();
     return GCN_OK;
 }
 
@@ -370,7 +522,7 @@ int gcn_csr_arrays(const gcn_csr* a, int transposed, const int64_t** rowptr, con
                    const float** val, const int32_t** deg) {
     if (!a) return fail(GCN_ERR_BADARG, "gcn_csr_arrays: NULL matrix");
     if (transposed && !a->has_t) return fail(GCN_ERR_NOTRANSPOSE, "matrix was built without GCN_BUILD_TRANSPOSE");
-    const Matrix& m = transposed ? a->At : a->A;
+    const Matrix& m = matrix_of(a, transposed);
     if (rowptr) *rowptr = m.rowptr;
     if (colidx) *colidx = m.colidx;
     if (val) *val = m.val;
@@ -382,7 +534,7 @@ int gcn_csr_export(const gcn_csr* a, int transposed, int64_t* rowptr, int32_t* c
                    void* stream) {
     if (!a) return fail(GCN_ERR_BADARG, "gcn_csr_export: NULL matrix");
     if (transposed && !a->has_t) return fail(GCN_ERR_NOTRANSPOSE, "matrix was built without GCN_BUILD_TRANSPOSE");
-    const Matrix& m = transposed ? a->At : a->A;
+    const Matrix& m = matrix_of(a, transposed);
     hipStream_t s = (hipStream_t)stream;
     if (rowptr) GCN_HIP_TRY(hipMemcpyAsync(rowptr, m.rowptr, ((size_t)m.nrows + 1) * sizeof(int64_t), hipMemcpyDeviceToDevice, s));
     if (colidx && a->nnz) GCN_HIP_TRY(hipMemcpyAsync(colidx, m.colidx, (size_t)a->nnz * sizeof(int32_t), hipMemcpyDeviceToDevice, s));

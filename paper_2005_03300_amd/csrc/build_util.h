@@ -11,13 +11,6 @@ static inline unsigned blocks_for(int64_t work, int per_block = TPB) {
     return (unsigned)(b < 1 ? 1 : b);
 }
 
-struct TempBuf {   // frees on scope exit
-    void* p = nullptr;
-    ~TempBuf() { device_free(p); }
-    int alloc(size_t bytes) { device_free(p); return device_alloc(&p, bytes); }
-    template <typename T> T* as() const { return (T*)p; }
-};
-
 // Bits needed for the values 0 .. n-1 (at least 1, at most 32).
 static inline unsigned bits_for(int64_t n) {
     unsigned b = 1;
@@ -27,11 +20,11 @@ static inline unsigned bits_for(int64_t n) {
 
 // ---- kernels used by more than one construction source (one copy per source file) ----
 
-// Sorted distinct keys -> colidx and rowptr.  Entry k is the first of every row in
-// (row(k-1), row(k)], so its thread writes rowptr for those rows; the last entry's thread also
-// closes all rows behind it.
-static __global__ void k_compress(int64_t nnz, int64_t n, const uint64_t* __restrict__ keys,
-                           int64_t* __restrict__ rowptr, int32_t* __restrict__ colidx) {
+// Sorted distinct keys -> colidx and rowptr.  A key holds its row from bit `rshift` up and its column from bit `cshift`
+// up (one of them 0; `cmask` cuts the column out).  Entry k is the first of every row in (row(k-1), row(k)], so its
+// thread writes rowptr for those rows; the last entry's thread also closes all rows behind it.
+static __global__ void k_compress(int64_t nnz, int64_t n, const uint64_t* __restrict__ keys, unsigned rshift, uint64_t rmask,
+                                  unsigned cshift, uint64_t cmask, int64_t* __restrict__ rowptr, int32_t* __restrict__ colidx) {
     int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (nnz == 0) {
         for (int64_t r = k; r <= n; r += (int64_t)gridDim.x * blockDim.x) rowptr[r] = 0;
@@ -39,9 +32,9 @@ static __global__ void k_compress(int64_t nnz, int64_t n, const uint64_t* __rest
     }
     if (k >= nnz) return;
     uint64_t key = keys[k];
-    int64_t r = (int64_t)(key >> 32);
-    int64_t rp = k > 0 ? (int64_t)(keys[k - 1] >> 32) : -1;
-    colidx[k] = (int32_t)(key & 0xffffffffu);
+    int64_t r = (int64_t)((key >> rshift) & rmask);
+    int64_t rp = k > 0 ? (int64_t)((keys[k - 1] >> rshift) & rmask) : -1;
+    colidx[k] = (int32_t)((key >> cshift) & cmask);
     for (int64_t q = rp + 1; q <= r; ++q) rowptr[q] = k;
     if (k == nnz - 1)
         for (int64_t q = r + 1; q <= n; ++q) rowptr[q] = nnz;

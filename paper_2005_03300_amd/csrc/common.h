@@ -128,6 +128,7 @@ struct Matrix {
     int64_t n_fix = -1;          // -1: no list (every chunk is examined)
     int64_t nsub = 0, nchunks = 0;
     int32_t max_degree = 0;
+    bool both = false;           // this matrix is A and A^T (gcn_csr::symmetric): its other orders count for both
     // Other stored orders of the matrix, built on first use (or by a prepare call) and kept until the
     // matrix is destroyed.  blk / swp / hub are the copies the latest product used; a product that needs
     // another key (block width; lane groups, task height and long-row threshold; hub settings) parks the
@@ -161,6 +162,7 @@ struct gcn_csr {
     int64_t n = 0, ncols = 0, nnz = 0;   // A is n x ncols (square unless made by gcn_csr_create_from_csr_rect)
     int device = 0;
     bool has_t = false;
+    bool symmetric = false;      // A^T is A, entry by entry and value by value: At is not used, A serves both
     gcn::Matrix A, At;
     int32_t* deg = nullptr;      // [n] entries per row of A
     float* inv_sqrt_deg = nullptr; // [n] (float)(1/sqrt(deg)); set only when this library normalised the matrix
@@ -181,10 +183,37 @@ struct gcn_csr {
 
 namespace gcn {
 
+// Device memory of the library.  Blocks that are given back are kept for the next matrix, so that building one does not
+// pay for mapping and clearing memory each time (a graph of 16 M pairs: 5 of 14 ms, and up to 40 ms more when other
+// memory of the process had just been released): at most 1/64 of the device's memory, the oldest leave first,
+// everything leaves when an allocation fails and in gcn_scratch_release.  device_free may only be called when no
+// queued work uses the block any more, on any stream.
 int device_alloc(void** p, size_t bytes);
 template <typename T>
 int device_alloc_t(T** p, size_t count) { return device_alloc((void**)p, count * sizeof(T)); }
 void device_free(void* p);
+void device_pool_release();
+
+// While one of these is alive on a thread, the temporaries of graph construction (TempBuf) that the thread allocates
+// and drops are reused in stream order, without waiting; the destructor waits for the stream and gives them back.
+// Every entry point that builds something opens one; an inner one joins the outer.
+struct BuildScope {
+    explicit BuildScope(hipStream_t s);
+    ~BuildScope();
+    bool owner;
+};
+int temp_alloc(void** p, size_t bytes);
+void temp_free(void* p);
+struct TempBuf {   // given back on scope exit
+    void* p = nullptr;
+    TempBuf() = default;
+    TempBuf(const TempBuf&) = delete;
+    TempBuf& operator=(const TempBuf&) = delete;
+    ~TempBuf() { temp_free(p); }
+    int alloc(size_t bytes) { temp_free(p); p = nullptr; return temp_alloc(&p, bytes ? bytes : 16); }
+    void drop() { temp_free(p); p = nullptr; }
+    template <typename T> T* as() const { return (T*)p; }
+};
 
 // Library-owned scratch for the split-K partial sums of the weight-gradient product, the column sums and the
 // loss: one buffer per (device, stream), so calls on different streams never share it.  It grows on demand; the
@@ -208,11 +237,15 @@ size_t loss_scratch_bytes();
 struct DeviceInfo { int cus; int64_t l2_bytes; };
 const DeviceInfo& device_info();
 
+// op(A) as stored
+inline Matrix& matrix_of(gcn_csr* a, int trans) { return (trans && !a->symmetric) ? a->At : a->A; }
+inline const Matrix& matrix_of(const gcn_csr* a, int trans) { return (trans && !a->symmetric) ? a->At : a->A; }
+
 Config& config();                               // the process-wide settings (gcn_config)
 inline const Config& cfg_of(const gcn_csr* a) { return a->own_cfg ? a->cfg : config(); }
 // schedule taken by the most recent sparse product of this process (GCN_SCHED_*), for tests and reports
 extern int g_last_schedule;
-void count_build();
+void count_build(const Matrix& m);
 
 // event bracketing of the dominant kernel (GCN_CFG_TIMING)
 void timing_begin(hipStream_t s, int phase = GCN_PHASE_SPMM_KERNEL);

@@ -5,9 +5,9 @@
 // D^-1/2 (A+I) D^-1/2); section "Communication Schemes and their Analyses" keeps both A and A^T
 // so that neither product needs a transposition (or, here, floating-point atomics) at run time.
 //
-// Entries are encoded as 64-bit keys row<<32|col; a radix sort of the keys followed by the
-// removal of equal neighbours yields the canonical row-major order with ascending columns.  The
-// device-wide sort, selection and prefix sum are the ones of prims.h.
+// Entries are encoded as 64-bit keys row<<cbits|col with cbits the bits of a column (so that the sort takes no pass over
+// unused bits); a radix sort of the keys followed by the removal of equal neighbours yields the canonical row-major
+// order with ascending columns.  The device-wide sort, selection and prefix sum are the ones of prims.h.
 #include <cstring>
 #include <new>
 
@@ -16,8 +16,6 @@
 #include "build_util.h"
 
 namespace gcn {
-
-static constexpr uint64_t INVALID_KEY = ~0ull;
 
 // ---- kernels ---------------------------------------------------------------------------------
 
@@ -29,50 +27,64 @@ __global__ void k_check_ids(int64_t m, int64_t n, const int32_t* __restrict__ sr
     if (u < 0 || v < 0 || u >= n || v >= n) *bad = 1;
 }
 
-// One key per stored direction of each input pair; pairs with u == v become INVALID_KEY, which
-// sorts behind every real key.  Self loops are appended after the 'mult*m' edge keys.
+// One key per stored direction of each input pair.  A pair with u == v is dropped: with self loops its key is that of
+// the diagonal entry, which exists anyway; without, it becomes the key n<<cbits, which sorts behind every real one.
+// The diagonal is appended after the 'mult*m' keys of the pairs.
 __global__ void k_make_keys(int64_t m, int64_t n, const int32_t* __restrict__ src,
-                            const int32_t* __restrict__ dst, int symmetrise, int self_loops,
+                            const int32_t* __restrict__ dst, int symmetrise, int self_loops, unsigned cbits,
                             uint64_t* __restrict__ keys) {
     int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     int mult = symmetrise ? 2 : 1;
     if (t < m) {
-        uint64_t u = (uint32_t)src[t], v = (uint32_t)dst[t];
-        bool loop = (u == v);
-        keys[t * mult] = loop ? INVALID_KEY : (u << 32 | v);
-        if (symmetrise) keys[t * mult + 1] = loop ? INVALID_KEY : (v << 32 | u);
+        const uint64_t u = (uint32_t)src[t], v = (uint32_t)dst[t];
+        const bool drop = u == v && !self_loops;
+        const uint64_t none = (uint64_t)n << cbits;
+        keys[t * mult] = drop ? none : (u << cbits | v);
+        if (symmetrise) keys[t * mult + 1] = drop ? none : (v << cbits | u);
     } else if (self_loops && t < m + n) {
         uint64_t i = (uint64_t)(t - m);
-        keys[m * mult + (t - m)] = i << 32 | i;
+        keys[m * mult + (t - m)] = i << cbits | i;
     }
 }
 
-__global__ void k_degrees(int64_t n, const int64_t* __restrict__ rowptr, int32_t* __restrict__ deg,
-                          int32_t* __restrict__ max_deg, unsigned long long* __restrict__ n_nonempty) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int32_t d = 0;
-    if (i < n) {
-        d = (int32_t)(rowptr[i + 1] - rowptr[i]);
+// A fixed number of workgroups strides over the rows, so that there are few atomics on the two counters (one per
+// wavefront of 64 rows took 385 us on a million rows, nearly all of it waiting for the counters' one address).
+__global__ __launch_bounds__(256) void k_degrees(int64_t n, const int64_t* __restrict__ rowptr, int32_t* __restrict__ deg,
+                                                 int32_t* __restrict__ max_deg, unsigned long long* __restrict__ n_nonempty) {
+    int32_t m = 0;
+    unsigned nz = 0;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+        const int32_t d = (int32_t)(rowptr[i + 1] - rowptr[i]);
         if (deg) deg[i] = d;
+        m = d > m ? d : m;
+        nz += d > 0;
     }
-    // one integer atomic per wavefront instead of one per row
-    int32_t m = d;
+    if (!max_deg) return;
 #pragma unroll
     for (int s = 32; s >= 1; s >>= 1) {
         const int32_t o = __shfl_xor(m, s, 64);
         m = o > m ? o : m;
+        nz += __shfl_xor(nz, s, 64);
     }
-    const unsigned long long nz = __popcll(__ballot(d > 0));
-    if ((threadIdx.x & 63) == 0) {
-        if (max_deg) atomicMax(max_deg, m);
-        if (n_nonempty && nz) atomicAdd(n_nonempty, nz);
+    __shared__ int32_t s_m[4];
+    __shared__ unsigned s_nz[4];
+    if ((threadIdx.x & 63) == 0) { s_m[threadIdx.x >> 6] = m; s_nz[threadIdx.x >> 6] = nz; }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < 4; ++w) { m = s_m[w] > m ? s_m[w] : m; nz += s_nz[w]; }
+        atomicMax(max_deg, m);
+        if (nz) atomicAdd(n_nonempty, (unsigned long long)nz);
     }
+}
+static unsigned degree_blocks(int64_t n) {
+    const int64_t b = (n + 1023) / 1024;
+    return (unsigned)(b < 1 ? 1 : (b > 512 ? 512 : b));
 }
 
 // val(i,j) = (float)(1 / sqrt(d_i d_j)): exact integer product in double, correctly rounded
 // square root and division, one rounding to float -- the same value on any IEEE machine.
 // norm 2 is the row normalisation D^-1 (A+I): val(i,j) = (float)(1 / d_i).
-__global__ void k_values(int64_t nnz, const uint64_t* __restrict__ keys, const int32_t* __restrict__ deg,
+__global__ void k_values(int64_t nnz, const uint64_t* __restrict__ keys, unsigned cbits, const int32_t* __restrict__ deg,
                          int norm, float* __restrict__ val) {
     int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= nnz) return;
@@ -81,7 +93,7 @@ __global__ void k_values(int64_t nnz, const uint64_t* __restrict__ keys, const i
         return;
     }
     uint64_t key = keys[k];
-    double di = (double)deg[key >> 32], dj = (double)deg[key & 0xffffffffu];
+    double di = (double)deg[key >> cbits], dj = (double)deg[key & ((1ull << cbits) - 1)];
     if (norm == 2) val[k] = (float)__ddiv_rn(1.0, di);
     else {
         // a vertex whose row is empty (no self loops, no outgoing edge) scales by 0: D^-1/2 as a pseudo-inverse,
@@ -91,14 +103,11 @@ __global__ void k_values(int64_t nnz, const uint64_t* __restrict__ keys, const i
     }
 }
 
-__global__ void k_swap_halves(int64_t nnz, const uint64_t* __restrict__ keys, uint64_t* __restrict__ out) {
-    int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < nnz) out[k] = (keys[k] << 32) | (keys[k] >> 32);
-}
-
-// keys row<<32|col from compressed rows: thread k finds its row by bisection on rowptr.
-__global__ void k_keys_from_csr(int64_t nnz, int64_t n, const int64_t* __restrict__ rowptr,
-                                const int32_t* __restrict__ colidx, uint64_t* __restrict__ keys) {
+// keys row<<cbits|col from compressed rows: thread k finds its row by bisection on rowptr.  *bad is set unless the columns
+// ascend strictly inside every row and lie in [0, ncols).
+__global__ void k_keys_from_csr(int64_t nnz, int64_t n, int64_t ncols, const int64_t* __restrict__ rowptr,
+                                const int32_t* __restrict__ colidx, unsigned cbits, uint64_t* __restrict__ keys,
+                                int* __restrict__ bad) {
     int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= nnz) return;
     int64_t lo = 0, hi = n;   // largest r with rowptr[r] <= k
@@ -106,7 +115,9 @@ __global__ void k_keys_from_csr(int64_t nnz, int64_t n, const int64_t* __restric
         int64_t mid = (lo + hi) >> 1;
         if (rowptr[mid] <= k) lo = mid; else hi = mid;
     }
-    keys[k] = ((uint64_t)lo << 32) | (uint32_t)colidx[k];
+    const int32_t c = colidx[k];
+    if (c < 0 || c >= ncols || (k > rowptr[lo] && colidx[k - 1] >= c)) *bad = 1;
+    keys[k] = ((uint64_t)lo << cbits) | (uint32_t)c;
 }
 
 __global__ void k_validate_rowptr(int64_t n, const int64_t* __restrict__ rowptr, int* __restrict__ bad) {
@@ -114,14 +125,6 @@ __global__ void k_validate_rowptr(int64_t n, const int64_t* __restrict__ rowptr,
     if (i >= n) return;
     if (i == 0 && rowptr[0] != 0) *bad = 1;
     if (rowptr[i + 1] < rowptr[i]) *bad = 1;
-}
-
-// after k_keys_from_csr: keys must be strictly increasing and columns inside [0,n)
-__global__ void k_validate_keys(int64_t nnz, int64_t n, const uint64_t* __restrict__ keys, int* __restrict__ bad) {
-    int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= nnz) return;
-    if ((keys[k] & 0xffffffffu) >= (uint64_t)n) *bad = 1;
-    if (k > 0 && keys[k] <= keys[k - 1]) *bad = 1;
 }
 
 __global__ void k_fill_f32(int64_t count, float v, float* __restrict__ out) {
@@ -149,17 +152,14 @@ __global__ void k_ne_rowptr(int64_t n_ne, int64_t nnz, const int32_t* __restrict
 
 // ---- host helpers ---------------------------------------------------------------------------------
 
-static int sort_keys(uint64_t* in, uint64_t* out, int64_t count, int64_t n, hipStream_t s) {
-    unsigned end_bit = 64;   // INVALID_KEY uses every bit
-    (void)n;
-    return prims::sort_keys<uint64_t>(in, out, (size_t)count, end_bit, s);
-}
-
-// From sorted distinct keys (row<<32|col) fill rowptr/colidx of `m` (allocates them).
-static int compress_keys(Matrix& m, int64_t n, int64_t nnz, const uint64_t* keys, hipStream_t s) {
+// From sorted distinct keys (row<<cbits|col, ordered by row; or by column when `by_col`, then the roles change) fill
+// rowptr/colidx of `m` (allocates them).
+static int compress_keys(Matrix& m, int64_t n, int64_t nnz, const uint64_t* keys, unsigned cbits, bool by_col, hipStream_t s) {
     GCN_TRY(device_alloc_t(&m.rowptr, (size_t)n + 1));
     GCN_TRY(device_alloc_t(&m.colidx, (size_t)nnz));
-    hipLaunchKernelGGL(k_compress, dim3(blocks_for(nnz)), dim3(TPB), 0, s, nnz, n, keys, m.rowptr, m.colidx);
+    const uint64_t cmask = (1ull << cbits) - 1;
+    if (by_col) hipLaunchKernelGGL(k_compress, dim3(blocks_for(nnz)), dim3(TPB), 0, s, nnz, n, keys, 0u, cmask, cbits, ~0ull, m.rowptr, m.colidx);
+    else hipLaunchKernelGGL(k_compress, dim3(blocks_for(nnz)), dim3(TPB), 0, s, nnz, n, keys, cbits, ~0ull, 0u, cmask, m.rowptr, m.colidx);
     GCN_LAUNCH_CHECK();
     return GCN_OK;
 }
@@ -198,7 +198,6 @@ int build_fix_list(const uint32_t* flags, const int32_t* sub_row, const int64_t*
         GCN_HIP_TRY(hipMemcpyAsync(*list, sel.p, (size_t)nsel * 4, hipMemcpyDeviceToDevice, s));
         hipLaunchKernelGGL(k_add_one, dim3(blocks_for(nsel)), dim3(TPB), 0, s, nsel, *list);
         GCN_LAUNCH_CHECK();
-        GCN_HIP_TRY(hipStreamSynchronize(s));
     }
     *count = nsel;
     return GCN_OK;
@@ -210,7 +209,7 @@ int build_schedule(Matrix& m, int64_t n, int64_t nnz, hipStream_t s) {
     TempBuf counters;
     GCN_TRY(counters.alloc(16));
     GCN_HIP_TRY(hipMemsetAsync(counters.p, 0, 16, s));
-    hipLaunchKernelGGL(k_degrees, dim3(blocks_for(n)), dim3(TPB), 0, s, n, m.rowptr, (int32_t*)nullptr,
+    hipLaunchKernelGGL(k_degrees, dim3(degree_blocks(n)), dim3(256), 0, s, n, m.rowptr, (int32_t*)nullptr,
                        (int32_t*)counters.p, (unsigned long long*)((char*)counters.p + 8));
     GCN_LAUNCH_CHECK();
     struct { int32_t maxd; int32_t pad; unsigned long long nne; } h;
@@ -230,7 +229,6 @@ int build_schedule(Matrix& m, int64_t n, int64_t nnz, hipStream_t s) {
         GCN_TRY(device_alloc_t(&m.empty_rows, (size_t)(n - m.n_ne)));
         IsEmpty epred{m.rowptr};
         GCN_TRY(prims::select_indices(n, epred, m.empty_rows, nullptr, s));
-        GCN_HIP_TRY(hipStreamSynchronize(s));
         rp = m.ne_rowptr;
     }
     GCN_TRY(device_alloc_t(&m.flags, (size_t)m.nsub + SUBS_PER_CHUNK));   // padded: one chunk of zero words
@@ -243,27 +241,21 @@ int build_schedule(Matrix& m, int64_t n, int64_t nnz, hipStream_t s) {
         hipLaunchKernelGGL(k_sub_rows, dim3(blocks_for(m.nsub)), dim3(TPB), 0, s, m.nsub, m.n_ne, rp, m.sub_row);
         GCN_LAUNCH_CHECK();
     }
-    GCN_HIP_TRY(hipStreamSynchronize(s));
     if (nnz > 0) GCN_TRY(build_fix_list(m.flags, m.sub_row, rp, m.nchunks, &m.fix_list, &m.n_fix, s));
     return GCN_OK;
 }
 
-// A^T of `a` from A's sorted keys and values: swap key halves, stable radix sort with the values
-// as payload.  Within a column the rows keep their ascending order.
-static int build_transpose(gcn_csr* a, const uint64_t* keys, uint64_t* scratch_keys, hipStream_t s) {
+// A^T of `a` from A's sorted keys and values: a stable radix sort by the column bits alone (inside a column the rows keep
+// their ascending order) with the values as payload.
+static int build_transpose(gcn_csr* a, const uint64_t* keys, unsigned cbits, uint64_t* scratch_keys, hipStream_t s) {
     const int64_t nnz = a->nnz, n = a->ncols;            // A^T has ncols rows
-    TempBuf kin, vtmp;
-    GCN_TRY(kin.alloc((size_t)nnz * 8));
     GCN_TRY(device_alloc_t(&a->At.val, (size_t)nnz));
-    hipLaunchKernelGGL(k_swap_halves, dim3(blocks_for(nnz)), dim3(TPB), 0, s, nnz, keys, kin.as<uint64_t>());
-    GCN_LAUNCH_CHECK();
-    unsigned end_bit = 32 + bits_for(n);                 // low half: rows of A, high half: its columns
-    GCN_TRY((prims::sort_pairs<uint64_t, float>(kin.as<uint64_t>(), scratch_keys, a->A.val, a->At.val, (size_t)nnz,
-                                                end_bit, s)));
+    if (nnz > 0)
+        GCN_TRY((prims::radix_sort<uint64_t, float>(keys, scratch_keys, a->A.val, a->At.val, (size_t)nnz, cbits, false, s, 0,
+                                                    false)));
     a->At.nrows = n;
     a->At.ncols = a->n;
-    GCN_TRY(compress_keys(a->At, n, nnz, scratch_keys, s));
-    GCN_HIP_TRY(hipStreamSynchronize(s));
+    GCN_TRY(compress_keys(a->At, n, nnz, scratch_keys, cbits, true, s));
     GCN_TRY(build_schedule(a->At, n, nnz, s));
     a->has_t = true;
     return GCN_OK;
@@ -274,6 +266,7 @@ static int create_impl(gcn_csr* a, int64_t n, int64_t m, const int32_t* src, con
     const bool sym = flags & GCN_SYMMETRISE, loops = flags & GCN_ADD_SELF_LOOPS;
     const int mult = sym ? 2 : 1;
     const int64_t cap = m * mult + (loops ? n : 0);
+    const unsigned cbits = bits_for(n), kbits = cbits + bits_for(n + 1);
 
     TempBuf bad;
     GCN_TRY(bad.alloc(sizeof(int)));
@@ -293,16 +286,17 @@ static int create_impl(gcn_csr* a, int64_t n, int64_t m, const int32_t* src, con
     int64_t nnz = 0;
     if (cap > 0) {
         hipLaunchKernelGGL(k_make_keys, dim3(blocks_for(m + (loops ? n : 0))), dim3(TPB), 0, s, m, n, src, dst,
-                           (int)sym, (int)loops, k0.as<uint64_t>());
+                           (int)sym, (int)loops, cbits, k0.as<uint64_t>());
         GCN_LAUNCH_CHECK();
-        GCN_TRY(sort_keys(k0.as<uint64_t>(), k1.as<uint64_t>(), cap, n, s));
+        GCN_TRY((prims::radix_sort<uint64_t, prims::NoValue>(k0.as<uint64_t>(), k1.as<uint64_t>(), nullptr, nullptr,
+                                                             (size_t)cap, loops ? cbits + bits_for(n) : kbits, false, s, 0, false)));
         int64_t hcnt = 0;
         uint64_t last = 0;
         GCN_TRY(prims::unique_keys(k1.as<uint64_t>(), k0.as<uint64_t>(), cap, &hcnt, s));
-        if (hcnt > 0) {
+        if (hcnt > 0 && !loops) {
             GCN_HIP_TRY(hipMemcpyAsync(&last, k0.as<uint64_t>() + (hcnt - 1), 8, hipMemcpyDeviceToHost, s));
             GCN_HIP_TRY(hipStreamSynchronize(s));
-            if (last == INVALID_KEY) hcnt -= 1;
+            if (last == ((uint64_t)n << cbits)) hcnt -= 1;
         }
         nnz = hcnt;
     }
@@ -311,14 +305,14 @@ static int create_impl(gcn_csr* a, int64_t n, int64_t m, const int32_t* src, con
     a->ncols = n;
     a->nnz = nnz;
     a->A.nrows = a->A.ncols = n;
-    GCN_TRY(compress_keys(a->A, n, nnz, keys, s));
+    GCN_TRY(compress_keys(a->A, n, nnz, keys, cbits, false, s));
     GCN_TRY(device_alloc_t(&a->deg, (size_t)n));
     GCN_TRY(device_alloc_t(&a->A.val, (size_t)nnz));
-    hipLaunchKernelGGL(k_degrees, dim3(blocks_for(n)), dim3(TPB), 0, s, n, a->A.rowptr, a->deg, (int32_t*)nullptr,
+    hipLaunchKernelGGL(k_degrees, dim3(degree_blocks(n)), dim3(256), 0, s, n, a->A.rowptr, a->deg, (int32_t*)nullptr,
                        (unsigned long long*)nullptr);
     GCN_LAUNCH_CHECK();
     if (nnz > 0) {
-        hipLaunchKernelGGL(k_values, dim3(blocks_for(nnz)), dim3(TPB), 0, s, nnz, keys, a->deg,
+        hipLaunchKernelGGL(k_values, dim3(blocks_for(nnz)), dim3(TPB), 0, s, nnz, keys, cbits, a->deg,
                            (flags & GCN_NORM_ROW) ? 2 : ((flags & GCN_NORM_SYM) ? 1 : 0), a->A.val);
         GCN_LAUNCH_CHECK();
     }
@@ -326,9 +320,15 @@ static int create_impl(gcn_csr* a, int64_t n, int64_t m, const int32_t* src, con
         GCN_TRY(device_alloc_t(&a->inv_sqrt_deg, (size_t)n));
         GCN_TRY(inv_sqrt_deg_launch(n, a->deg, a->inv_sqrt_deg, s));
     }
-    GCN_HIP_TRY(hipStreamSynchronize(s));
     GCN_TRY(build_schedule(a->A, n, nnz, s));
-    if (flags & GCN_BUILD_TRANSPOSE) GCN_TRY(build_transpose(a, keys, k1.as<uint64_t>(), s));
+    if (flags & GCN_BUILD_TRANSPOSE) {
+        // Both directions of every pair are stored and the value formula (1, or 1/sqrt(d_i d_j)) is symmetric: A^T is A,
+        // bit by bit, and one set of arrays and schedules serves both.
+        a->symmetric = sym && !(flags & GCN_NORM_ROW);
+        a->A.both = a->symmetric;
+        if (a->symmetric) a->has_t = true;
+        else GCN_TRY(build_transpose(a, keys, cbits, k1.as<uint64_t>(), s));
+    }
     return GCN_OK;
 }
 
@@ -356,6 +356,7 @@ static int from_csr_impl(gcn_csr* a, int64_t n, int64_t ncols, const int64_t* ro
     GCN_TRY(device_alloc_t(&a->A.val, (size_t)nnz));
     GCN_TRY(device_alloc_t(&a->deg, (size_t)n));
     GCN_HIP_TRY(hipMemcpyAsync(a->A.rowptr, rowptr, ((size_t)n + 1) * 8, hipMemcpyDeviceToDevice, s));
+    const unsigned cbits = bits_for(ncols);
     TempBuf keys, k1;
     GCN_TRY(keys.alloc((size_t)nnz * 8));
     if (nnz > 0) {
@@ -365,24 +366,20 @@ static int from_csr_impl(gcn_csr* a, int64_t n, int64_t ncols, const int64_t* ro
             hipLaunchKernelGGL(k_fill_f32, dim3(blocks_for(nnz)), dim3(TPB), 0, s, nnz, 1.0f, a->A.val);
             GCN_LAUNCH_CHECK();
         }
-        hipLaunchKernelGGL(k_keys_from_csr, dim3(blocks_for(nnz)), dim3(TPB), 0, s, nnz, n, a->A.rowptr, a->A.colidx,
-                           keys.as<uint64_t>());
-        GCN_LAUNCH_CHECK();
-        hipLaunchKernelGGL(k_validate_keys, dim3(blocks_for(nnz)), dim3(TPB), 0, s, nnz, ncols, keys.as<uint64_t>(),
-                           bad.as<int>());
+        hipLaunchKernelGGL(k_keys_from_csr, dim3(blocks_for(nnz)), dim3(TPB), 0, s, nnz, n, ncols, a->A.rowptr, a->A.colidx,
+                           cbits, keys.as<uint64_t>(), bad.as<int>());
         GCN_LAUNCH_CHECK();
         GCN_HIP_TRY(hipMemcpyAsync(&hbad, bad.p, sizeof(int), hipMemcpyDeviceToHost, s));
         GCN_HIP_TRY(hipStreamSynchronize(s));
         if (hbad) return fail(GCN_ERR_UNSORTED, "gcn_csr_create_from_csr: columns must be strictly ascending per row and inside [0,n)");
     }
-    hipLaunchKernelGGL(k_degrees, dim3(blocks_for(n)), dim3(TPB), 0, s, n, a->A.rowptr, a->deg, (int32_t*)nullptr,
+    hipLaunchKernelGGL(k_degrees, dim3(degree_blocks(n)), dim3(256), 0, s, n, a->A.rowptr, a->deg, (int32_t*)nullptr,
                        (unsigned long long*)nullptr);
     GCN_LAUNCH_CHECK();
-    GCN_HIP_TRY(hipStreamSynchronize(s));
     GCN_TRY(build_schedule(a->A, n, nnz, s));
     if (flags & GCN_BUILD_TRANSPOSE) {
         GCN_TRY(k1.alloc((size_t)nnz * 8));
-        GCN_TRY(build_transpose(a, keys.as<uint64_t>(), k1.as<uint64_t>(), s));
+        GCN_TRY(build_transpose(a, keys.as<uint64_t>(), cbits, k1.as<uint64_t>(), s));
     }
     return GCN_OK;
 }
@@ -426,6 +423,7 @@ int gcn_csr_create(gcn_csr** out, int64_t n, int64_t n_edges, const int32_t* src
     gcn_csr* a = new (std::nothrow) gcn_csr();
     if (!a) return fail(GCN_ERR_OOM, "host allocation failed");
     (void)hipGetDevice(&a->device);
+    BuildScope scope((hipStream_t)stream);
     int rc = create_impl(a, n, n_edges, src, dst, flags, (hipStream_t)stream);
     if (rc != GCN_OK) {
         gcn_csr_destroy(a);
@@ -444,6 +442,7 @@ int gcn_csr_create_from_csr(gcn_csr** out, int64_t n, const int64_t* rowptr, con
     gcn_csr* a = new (std::nothrow) gcn_csr();
     if (!a) return fail(GCN_ERR_OOM, "host allocation failed");
     (void)hipGetDevice(&a->device);
+    BuildScope scope((hipStream_t)stream);
     int rc = from_csr_impl(a, n, n, rowptr, colidx, val, flags, (hipStream_t)stream);
     if (rc != GCN_OK) {
         gcn_csr_destroy(a);
@@ -462,6 +461,7 @@ int gcn_csr_create_from_csr_rect(gcn_csr** out, int64_t n_rows, int64_t n_cols, 
     gcn_csr* a = new (std::nothrow) gcn_csr();
     if (!a) return fail(GCN_ERR_OOM, "host allocation failed");
     (void)hipGetDevice(&a->device);
+    BuildScope scope((hipStream_t)stream);
     int rc = from_csr_impl(a, n_rows, n_cols, rowptr, colidx, val, flags, (hipStream_t)stream);
     if (rc != GCN_OK) {
         gcn_csr_destroy(a);
@@ -476,6 +476,7 @@ int gcn_radix_sort(int64_t n, int key_bytes, const void* keys_in, void* keys_out
     using gcn::fail;
     if (n < 0 || end_bit < 0) return fail(GCN_ERR_BADARG, "gcn_radix_sort: negative size");
     if (n == 0) return GCN_OK;
+    BuildScope scope((hipStream_t)stream);
     if (!keys_in || !keys_out || keys_in == keys_out) return fail(GCN_ERR_BADARG, "gcn_radix_sort: keys NULL or in place");
     if (payload_bytes != 0 && (!payload_in || !payload_out || payload_in == payload_out))
         return fail(GCN_ERR_BADARG, "gcn_radix_sort: payload NULL or in place");
@@ -491,6 +492,7 @@ int gcn_radix_sort(int64_t n, int key_bytes, const void* keys_in, void* keys_out
 int gcn_exclusive_scan_i64(int64_t n, const int64_t* in, int64_t* out, void* stream) {
     if (n < 0) return gcn::fail(GCN_ERR_BADARG, "gcn_exclusive_scan_i64: negative size");
     if (n == 0) return GCN_OK;
+    BuildScope scope((hipStream_t)stream);
     if (!in || !out) return gcn::fail(GCN_ERR_BADARG, "gcn_exclusive_scan_i64: NULL pointer");
     return gcn::prims::exclusive_scan<int64_t>(in, out, (size_t)n, (hipStream_t)stream);
 }
@@ -499,6 +501,7 @@ int gcn_unique_u64(int64_t n, const uint64_t* keys_in, uint64_t* keys_out, int64
     if (n < 0 || !count) return gcn::fail(GCN_ERR_BADARG, "gcn_unique_u64: negative size or NULL count");
     *count = 0;
     if (n == 0) return GCN_OK;
+    BuildScope scope((hipStream_t)stream);
     if (!keys_in || !keys_out || keys_in == keys_out) return gcn::fail(GCN_ERR_BADARG, "gcn_unique_u64: keys NULL or in place");
     return gcn::prims::unique_keys(keys_in, keys_out, n, count, (hipStream_t)stream);
 }

@@ -55,7 +55,7 @@ static int layer_forward_impl(gcn_csr* a, int32_t f_in, int32_t f_out, const flo
     if (order == GCN_ORDER_GEMM_FIRST) {
         const float* ps = pre_scale(a, t_scratch);
         GCN_TRY(timed_gemm(0, 0, n, f_out, f_in, Hin, ldh, W, f_out, T, f_out, nullptr, GCN_EPI_NONE, nullptr, 0, s, ps));
-        GCN_TRY(norm_spmm(a, a->At, f_out, T, f_out, t_scratch ? T : xs, Z, f_out,
+        GCN_TRY(norm_spmm(a, matrix_of(a, 1), f_out, T, f_out, t_scratch ? T : xs, Z, f_out,
                           (in_place && !bias) ? GCN_EPI_RELU : GCN_EPI_NONE, nullptr, 0, s, ps != nullptr));
         if (bias) {
             PhaseTimer pt(s, GCN_PHASE_OTHER);
@@ -63,7 +63,7 @@ static int layer_forward_impl(gcn_csr* a, int32_t f_in, int32_t f_out, const flo
         }
     } else {
         // t_given: T already holds A^T Hin (aggregated once by the caller; Hin itself is not read)
-        if (!t_given) GCN_TRY(norm_spmm(a, a->At, f_in, Hin, ldh, xs, T, f_in, GCN_EPI_NONE, nullptr, 0, s));
+        if (!t_given) GCN_TRY(norm_spmm(a, matrix_of(a, 1), f_in, Hin, ldh, xs, T, f_in, GCN_EPI_NONE, nullptr, 0, s));
         GCN_TRY(timed_gemm(0, 0, n, f_out, f_in, T, f_in, W, f_out, Z, f_out, bias,
                             in_place ? GCN_EPI_RELU : GCN_EPI_NONE, nullptr, 0, s));
     }
@@ -86,7 +86,7 @@ static int layer_backward_impl(gcn_csr* a, int32_t f_in, int32_t f_out, const fl
     }
     if (order == GCN_ORDER_GEMM_FIRST) {
         // S = A G;  Y = Hin^T S;  Gprev = (S W^T) (.) sigma'(Zprev)
-        GCN_TRY(norm_spmm(a, a->A, f_out, G, f_out, xs, S, f_out, GCN_EPI_NONE, nullptr, 0, s));
+        GCN_TRY(norm_spmm(a, matrix_of(a, 0), f_out, G, f_out, xs, S, f_out, GCN_EPI_NONE, nullptr, 0, s));
         GCN_TRY(timed_gemm(1, 0, f_in, f_out, n, Hin, ldh, S, f_out, Y, f_out, nullptr, GCN_EPI_NONE, nullptr, 0, s));
         if (Gprev)
             GCN_TRY(timed_gemm(0, 1, n, f_in, f_out, S, f_out, W, f_out, Gprev, f_in, nullptr, GCN_EPI_MASK, Zprev, f_in, s));
@@ -97,7 +97,7 @@ static int layer_backward_impl(gcn_csr* a, int32_t f_in, int32_t f_out, const fl
         if (Gprev) {
             const float* ps = pre_scale(a, s_scratch);
             GCN_TRY(timed_gemm(0, 1, n, f_in, f_out, G, f_out, W, f_out, S, f_in, nullptr, GCN_EPI_NONE, nullptr, 0, s, ps));
-            GCN_TRY(norm_spmm(a, a->A, f_in, S, f_in, s_scratch ? S : xs, Gprev, f_in, GCN_EPI_MASK, Zprev, f_in, s,
+            GCN_TRY(norm_spmm(a, matrix_of(a, 0), f_in, S, f_in, s_scratch ? S : xs, Gprev, f_in, GCN_EPI_MASK, Zprev, f_in, s,
                               ps != nullptr));
         }
     }
@@ -253,7 +253,7 @@ static int epoch_impl(gcn_csr* a, int32_t L_w, const int32_t* dims, const float*
         const bool is_last = (l == last);
         if (is_last && fuse) {
             if (!(l == 0 && P0))
-                GCN_TRY(norm_spmm(a, a->At, dims[l], Hin, dims[l], at(lay.XS), layer_T(l), dims[l], GCN_EPI_NONE, nullptr, 0, s));
+                GCN_TRY(norm_spmm(a, matrix_of(a, 1), dims[l], Hin, dims[l], at(lay.XS), layer_T(l), dims[l], GCN_EPI_NONE, nullptr, 0, s));
             break;
         }
         GCN_TRY(layer_forward_impl(a, dims[l], dims[l + 1], Hin, dims[l], W[l], nullptr, at(lay.Z[l]),
@@ -276,7 +276,7 @@ static int epoch_impl(gcn_csr* a, int32_t L_w, const int32_t* dims, const float*
         if (l == last && fuse) {
             // Y^L and S = G^L (W^L)^T are done; what is left of Equation 2 is the sparse product
             if (l > 0)
-                GCN_TRY(norm_spmm(a, a->A, dims[l], at(lay.S), dims[l], at(lay.S), at(lay.G[l - 1]), dims[l], GCN_EPI_MASK,
+                GCN_TRY(norm_spmm(a, matrix_of(a, 0), dims[l], at(lay.S), dims[l], at(lay.S), at(lay.G[l - 1]), dims[l], GCN_EPI_MASK,
                                   at(lay.Z[l - 1]), dims[l], s, pre_scale(a, true) != nullptr));
             continue;
         }
@@ -301,8 +301,8 @@ int gcn_epoch_prepare(gcn_csr* a, int32_t L_w, const int32_t* dims, int order, v
     for (int l = 0; l < L_w; ++l) {
         const int ord = resolve_order(order, dims[l], dims[l + 1]);
         const int32_t fw = ord == GCN_ORDER_GEMM_FIRST ? dims[l + 1] : dims[l];     // width of this layer's sparse products
-        GCN_TRY(spmm_prepare(a, a->At, fw, s));                                      // forward: A^T
-        if (ord == GCN_ORDER_GEMM_FIRST || l > 0) GCN_TRY(spmm_prepare(a, a->A, fw, s));   // backward: A
+        GCN_TRY(spmm_prepare(a, matrix_of(a, 1), fw, s));                                      // forward: A^T
+        if (ord == GCN_ORDER_GEMM_FIRST || l > 0) GCN_TRY(spmm_prepare(a, matrix_of(a, 0), fw, s));   // backward: A
     }
     GCN_HIP_TRY(hipStreamSynchronize(s));
     return GCN_OK;

@@ -3,8 +3,8 @@
 // (of which the removal of equal neighbours is one use).  Hand-written for 64-wide wavefronts;
 // all of them are used only while a matrix or a schedule is built, never inside an epoch.
 //
-// Every function here is synchronous with respect to its stream when it returns: temporary buffers
-// are owned by the call and released before it ends.
+// The functions queue their work on the stream and return; select waits for the stream when the caller asks for the
+// count.  Temporary buffers are reused in stream order by the BuildScope that every caller has open.
 #pragma once
 #include <type_traits>
 
@@ -23,12 +23,7 @@ constexpr int RS_RADIX = 256;              // 8-bit digits
 
 struct NoValue {};
 
-struct Scratch {   // frees on scope exit
-    void* p = nullptr;
-    ~Scratch() { device_free(p); }
-    int alloc(size_t bytes) { device_free(p); p = nullptr; return device_alloc(&p, bytes ? bytes : 16); }
-    template <typename T> T* as() const { return (T*)p; }
-};
+using Scratch = TempBuf;
 
 // ---- wavefront and workgroup scans -----------------------------------------------------------------
 
@@ -110,7 +105,6 @@ template <typename T> int exclusive_scan(const T* in, T* out, size_t n, hipStrea
     if (ntiles == 1) {
         hipLaunchKernelGGL(k_scan_tiles<T>, dim3(1), dim3(P_TPB), 0, s, in, out, n, (const T*)nullptr);
         GCN_LAUNCH_CHECK();
-        GCN_HIP_TRY(hipStreamSynchronize(s));
         return GCN_OK;
     }
     Scratch sums;
@@ -120,48 +114,68 @@ template <typename T> int exclusive_scan(const T* in, T* out, size_t n, hipStrea
     GCN_TRY(exclusive_scan<T>(sums.as<T>(), sums.as<T>(), ntiles, s));
     hipLaunchKernelGGL(k_scan_tiles<T>, dim3((unsigned)ntiles), dim3(P_TPB), 0, s, in, out, n, (const T*)sums.as<T>());
     GCN_LAUNCH_CHECK();
-    GCN_HIP_TRY(hipStreamSynchronize(s));
     return GCN_OK;
 }
 
 // ---- ordered selection -----------------------------------------------------------------------------
 // pred(i) decides whether index i is kept; emit(i, pos) stores it as the pos-th kept one.  Kept
 // indices keep their order.  Both functors are called once per index in each of two passes.
+// A tile's indices are dealt out 64 at a time to the wavefronts, so that neighbouring lanes read and write neighbouring
+// elements; a wavefront counts and ranks its 64 by ballot (unique over 34.6 M keys: 505 -> 200 us).
+
+constexpr int SEL_ITEMS = 16;
+constexpr int SEL_TILE = P_TPB * SEL_ITEMS;
 
 template <typename Pred>
 __global__ __launch_bounds__(P_TPB) void k_select_count(int64_t n, Pred pred, int64_t* __restrict__ tile_cnt) {
     __shared__ int part[P_WAVES];
-    const int64_t base = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)threadIdx.x * SCAN_ITEMS;
-    int c = 0;
+    const int64_t base = (int64_t)blockIdx.x * SEL_TILE + threadIdx.x;
+    int c = 0;                                     // the same in every lane of a wavefront
 #pragma unroll
-    for (int k = 0; k < SCAN_ITEMS; ++k)
-        if (base + k < n && pred(base + k)) ++c;
-    int total;
-    block_exclusive_sum(c, part, total);
-    if (threadIdx.x == 0) tile_cnt[blockIdx.x] = total;
+    for (int k = 0; k < SEL_ITEMS; ++k) {
+        const int64_t i = base + (int64_t)k * P_TPB;
+        c += __popcll(__ballot(i < n && pred(i)));
+    }
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int64_t t = 0;
+        for (int w = 0; w < P_WAVES; ++w) t += part[w];
+        tile_cnt[blockIdx.x] = t;
+    }
 }
 
 template <typename Pred, typename Emit>
 __global__ __launch_bounds__(P_TPB) void k_select_emit(int64_t n, Pred pred, Emit emit,
                                                       const int64_t* __restrict__ tile_off) {
-    __shared__ int part[P_WAVES];
-    const int64_t base = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)threadIdx.x * SCAN_ITEMS;
-    unsigned keep = 0;
-    int c = 0;
+    __shared__ int cnt[SEL_ITEMS * P_WAVES];       // kept indices of every 64, in index order
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int64_t base = (int64_t)blockIdx.x * SEL_TILE + threadIdx.x;
+    unsigned long long kept[SEL_ITEMS];
 #pragma unroll
-    for (int k = 0; k < SCAN_ITEMS; ++k)
-        if (base + k < n && pred(base + k)) { keep |= 1u << k; ++c; }
-    int total;
-    int64_t pos = tile_off[blockIdx.x] + block_exclusive_sum(c, part, total);
+    for (int k = 0; k < SEL_ITEMS; ++k) {
+        const int64_t i = base + (int64_t)k * P_TPB;
+        kept[k] = __ballot(i < n && pred(i));
+        if (lane == 0) cnt[k * P_WAVES + w] = __popcll(kept[k]);
+    }
+    __syncthreads();
+    static_assert(SEL_ITEMS * P_WAVES == 64, "one wavefront scans the counts");
+    if (w == 0) {
+        const int c = cnt[lane];
+        cnt[lane] = (int)wave_inclusive_sum((unsigned)c) - c;
+    }
+    __syncthreads();
+    const int64_t off = tile_off[blockIdx.x];
 #pragma unroll
-    for (int k = 0; k < SCAN_ITEMS; ++k)
-        if (keep >> k & 1u) emit(base + k, pos++);
+    for (int k = 0; k < SEL_ITEMS; ++k)
+        if (kept[k] >> lane & 1ull)
+            emit(base + (int64_t)k * P_TPB, off + cnt[k * P_WAVES + w] + __popcll(kept[k] & ((1ull << lane) - 1ull)));
 }
 
 template <typename Pred, typename Emit> int select(int64_t n, Pred pred, Emit emit, int64_t* count, hipStream_t s) {
     if (count) *count = 0;
     if (n <= 0) return GCN_OK;
-    const int64_t ntiles = (n + SCAN_TILE - 1) / SCAN_TILE;
+    const int64_t ntiles = (n + SEL_TILE - 1) / SEL_TILE;
     if (ntiles >= (1ll << 31)) return fail(GCN_ERR_RANGE, "select: %lld candidates are too many", (long long)n);
     Scratch cnt;
     GCN_TRY(cnt.alloc((size_t)(ntiles + 1) * 8));
@@ -172,10 +186,9 @@ template <typename Pred, typename Emit> int select(int64_t n, Pred pred, Emit em
     hipLaunchKernelGGL((k_select_emit<Pred, Emit>), dim3((unsigned)ntiles), dim3(P_TPB), 0, s, n, pred, emit,
                        (const int64_t*)cnt.as<int64_t>());
     GCN_LAUNCH_CHECK();
-    int64_t total = 0;
-    GCN_HIP_TRY(hipMemcpyAsync(&total, cnt.as<int64_t>() + ntiles, 8, hipMemcpyDeviceToHost, s));
+    if (!count) return GCN_OK;
+    GCN_HIP_TRY(hipMemcpyAsync(count, cnt.as<int64_t>() + ntiles, 8, hipMemcpyDeviceToHost, s));
     GCN_HIP_TRY(hipStreamSynchronize(s));
-    if (count) *count = total;
     return GCN_OK;
 }
 
@@ -210,8 +223,12 @@ inline int unique_keys(const uint64_t* in, uint64_t* out, int64_t n, int64_t* co
 // the lowest digit upwards sort the keys and equal keys keep their input order.  A pass takes three
 // steps: every workgroup counts the digits of its tile of RS_TILE keys; an exclusive prefix sum of
 // the counts laid out digit-major (digit d of tile t at d*ntiles + t) gives each (digit, tile) its
-// first output position; the workgroup then reads the tile again, 256 keys at a time, ranks each
-// key among the tile's earlier keys of the same digit and stores it (and its payload).
+// first output position; the workgroup then reads the tile again and stores it.  There a wavefront owns
+// 64 RS_ITEMS consecutive keys and ranks each among its own earlier keys of the same digit (ballots and a counter per
+// digit in LDS that only this wavefront touches: no barrier); one prefix sum over digits and wavefronts turns the ranks
+// into positions inside the tile, the keys go to those positions in LDS, and leave from there in order, so that the
+// keys of one digit are written as one run (32 of them on average).  Bound by memory: 34.6 M 8-byte keys take 391 us per
+// pass when every key is stored from where it was read, about 152 us this way.
 
 template <typename K> __device__ inline unsigned digit_of(K key, unsigned shift, unsigned mask, unsigned flip) {
     return ((unsigned)(key >> shift) & mask) ^ flip;
@@ -275,53 +292,110 @@ __global__ __launch_bounds__(P_TPB) void k_radix_tile_hist(const K* __restrict__
     hist[(size_t)threadIdx.x * ntiles + blockIdx.x] = (Off)h[threadIdx.x];
 }
 
+constexpr int RS_TPB = 512;
+constexpr int RS_WAVES = RS_TPB / 64;
+constexpr int RS_ITEMS = RS_TILE / RS_TPB;         // keys per thread
+
+template <typename K, typename V> constexpr size_t radix_lds_bytes() {
+    constexpr size_t v = std::is_same<V, NoValue>::value ? 0 : sizeof(V);
+    return (size_t)RS_TILE * (sizeof(K) > v ? sizeof(K) : v);
+}
+
 template <typename K, typename V, typename Off>
-__global__ __launch_bounds__(P_TPB) void k_radix_scatter(const K* __restrict__ kin, K* __restrict__ kout,
-                                                        const V* __restrict__ vin, V* __restrict__ vout, size_t n,
-                                                        unsigned shift, unsigned mask, unsigned flip, size_t ntiles,
-                                                        const Off* __restrict__ first) {
-    __shared__ Off next[RS_RADIX];                 // output position of the tile's next key of each digit
-    __shared__ unsigned wcnt[P_WAVES][RS_RADIX];   // this round's keys of each digit, by wavefront
+__global__ __launch_bounds__(RS_TPB) void k_radix_scatter(const K* __restrict__ kin, K* __restrict__ kout,
+                                                         const V* __restrict__ vin, V* __restrict__ vout, size_t n,
+                                                         unsigned shift, unsigned mask, unsigned flip, size_t ntiles,
+                                                         const Off* __restrict__ first) {
+    extern __shared__ __align__(16) unsigned char s_tile[];    // the tile's keys, then its payload, in output order
+    __shared__ unsigned cnt[RS_WAVES][RS_RADIX];    // keys of each digit by wavefront; then their first place in the tile
+    __shared__ Off place[RS_RADIX];                 // output position of a digit's keys less their place in the tile
+    __shared__ unsigned part[RS_RADIX / 64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    next[threadIdx.x] = first[(size_t)threadIdx.x * ntiles + blockIdx.x];
-#pragma unroll
-    for (int i = 0; i < P_WAVES; ++i) wcnt[i][threadIdx.x] = 0;
-    __syncthreads();
     const size_t base = (size_t)blockIdx.x * RS_TILE;
-    for (int r = 0; r < RS_ROUNDS; ++r) {
-        const size_t i = base + (size_t)r * P_TPB + threadIdx.x;
-        if (base + (size_t)r * P_TPB >= n) break;              // uniform over the workgroup
-        const bool valid = i < n;
-        K key = 0;
-        unsigned d = 0;
-        if (valid) { key = kin[i]; d = digit_of(key, shift, mask, flip); }
-        // lanes of this wavefront that hold the same digit
-        unsigned long long peers = __ballot(valid);
+    const int left = n - base < (size_t)RS_TILE ? (int)(n - base) : RS_TILE;
+    for (int i = threadIdx.x; i < RS_WAVES * RS_RADIX; i += RS_TPB) (&cnt[0][0])[i] = 0;
+    const int t0 = w * 64 * RS_ITEMS + lane;        // the thread's keys are t0 + 64 k
+    K key[RS_ITEMS];
+#pragma unroll
+    for (int k = 0; k < RS_ITEMS; ++k) {
+        key[k] = 0;
+        if (t0 + 64 * k < left) key[k] = kin[base + t0 + 64 * k];
+    }
+    __syncthreads();
+    unsigned rank[RS_ITEMS];
+#pragma unroll
+    for (int k = 0; k < RS_ITEMS; ++k) {
+        const bool valid = t0 + 64 * k < left;
+        const unsigned d = digit_of(key[k], shift, mask, flip);
+        unsigned long long peers = __ballot(valid);             // lanes of this wavefront that hold the same digit
 #pragma unroll
         for (int b = 0; b < 8; ++b) {
             const bool bit = d >> b & 1u;
             const unsigned long long have = __ballot(valid && bit);
             peers &= bit ? have : ~have;
         }
-        const int rank = __popcll(peers & ((1ull << lane) - 1ull));
-        if (valid && rank == 0) wcnt[w][d] = (unsigned)__popcll(peers);
-        __syncthreads();
-        Off pos = 0;
-        if (valid) {
-            pos = next[d] + (Off)rank;
-            for (int i2 = 0; i2 < w; ++i2) pos += (Off)wcnt[i2][d];
-        }
-        __syncthreads();
-        {
-            unsigned t = 0;
+        const unsigned before = (unsigned)__popcll(peers & ((1ull << lane) - 1ull));
+        unsigned seen = 0;
+        if (valid) seen = cnt[w][d];
+        // the wavefront's LDS operations complete in program order; the fences keep the compiler to it
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (valid && before == 0) cnt[w][d] = seen + (unsigned)__popcll(peers);
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        rank[k] = seen + before;
+    }
+    __syncthreads();
+    // first place in the tile of every (digit, wavefront)
+    unsigned mine = 0, inc = 0;
+    if (threadIdx.x < RS_RADIX) {
 #pragma unroll
-            for (int i2 = 0; i2 < P_WAVES; ++i2) { t += wcnt[i2][threadIdx.x]; wcnt[i2][threadIdx.x] = 0; }
-            next[threadIdx.x] += (Off)t;
+        for (int i = 0; i < RS_WAVES; ++i) {
+            const unsigned c = cnt[i][threadIdx.x];
+            cnt[i][threadIdx.x] = mine;
+            mine += c;
         }
+        inc = wave_inclusive_sum(mine);
+        if (lane == 63) part[w] = inc;
+    }
+    __syncthreads();
+    if (threadIdx.x < RS_RADIX) {
+        unsigned start = inc - mine;
+        for (int i = 0; i < w; ++i) start += part[i];
+#pragma unroll
+        for (int i = 0; i < RS_WAVES; ++i) cnt[i][threadIdx.x] += start;
+        place[threadIdx.x] = first[(size_t)threadIdx.x * ntiles + blockIdx.x] - (Off)start;
+    }
+    __syncthreads();
+    K* sk = reinterpret_cast<K*>(s_tile);
+#pragma unroll
+    for (int k = 0; k < RS_ITEMS; ++k) {
+        rank[k] += cnt[w][digit_of(key[k], shift, mask, flip)];
+        if (t0 + 64 * k < left) sk[rank[k]] = key[k];
+    }
+    __syncthreads();
+    Off pos[RS_ITEMS];
+#pragma unroll
+    for (int k = 0; k < RS_ITEMS; ++k) {
+        const int j = threadIdx.x + k * RS_TPB;
+        pos[k] = 0;
+        if (j < left) {
+            const K out = sk[j];
+            pos[k] = place[digit_of(out, shift, mask, flip)] + (Off)j;
+            kout[pos[k]] = out;
+        }
+    }
+    if constexpr (!std::is_same<V, NoValue>::value) {
+        V* sv = reinterpret_cast<V*>(s_tile);
         __syncthreads();
-        if (valid) {
-            kout[pos] = key;
-            if constexpr (!std::is_same<V, NoValue>::value) vout[pos] = vin[i];
+#pragma unroll
+        for (int k = 0; k < RS_ITEMS; ++k)
+            if (t0 + 64 * k < left) sv[rank[k]] = vin[base + t0 + 64 * k];
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < RS_ITEMS; ++k) {
+            const int j = threadIdx.x + k * RS_TPB;
+            if (j < left) vout[pos[k]] = sv[j];
         }
     }
 }
@@ -339,6 +413,9 @@ int radix_passes(const K* kin, K* kout, const V* vin, V* vout, size_t n, const u
     }
     const K* ksrc = kin;
     const V* vsrc = vin;
+    constexpr size_t lds = radix_lds_bytes<K, V>();
+    if (lds > 48 * 1024)      // with the static part more than the 64 KB a workgroup gets without asking
+        GCN_HIP_TRY(hipFuncSetAttribute((const void*)k_radix_scatter<K, V, Off>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     for (int p = 0; p < npass; ++p) {
         const bool to_out = ((npass - 1 - p) % 2) == 0;      // the last pass lands in the caller's output
         K* kdst = to_out ? kout : tk.as<K>();
@@ -348,57 +425,66 @@ int radix_passes(const K* kin, K* kout, const V* vin, V* vout, size_t n, const u
                            masks[p], flip, ntiles, hist.as<Off>());
         GCN_LAUNCH_CHECK();
         GCN_TRY(exclusive_scan<Off>(hist.as<Off>(), hist.as<Off>(), ntiles * RS_RADIX, s));
-        hipLaunchKernelGGL((k_radix_scatter<K, V, Off>), dim3((unsigned)ntiles), dim3(P_TPB), 0, s, ksrc, kdst, vsrc,
+        hipLaunchKernelGGL((k_radix_scatter<K, V, Off>), dim3((unsigned)ntiles), dim3(RS_TPB), lds, s, ksrc, kdst, vsrc,
                            vdst, n, shifts[p], masks[p], flip, ntiles, (const Off*)hist.as<Off>());
         GCN_LAUNCH_CHECK();
         ksrc = kdst;
         vsrc = vdst;
     }
-    GCN_HIP_TRY(hipStreamSynchronize(s));
     return GCN_OK;
 }
 
 // Stable sort of n keys by their bits [0, end_bit), ascending or descending; the payload (if V is
 // not NoValue) moves with its key.  The inputs are left as they were; outputs must not overlap them.
 // Digit positions at which every key holds the same byte are skipped.
+// first_bit > 0: the bits below it are known to be in order already (or not to matter).  probe == false: every digit
+// position is taken to vary (the caller packed its keys), which saves a pass over them and a wait for the stream.
 template <typename K, typename V>
-int radix_sort(const K* kin, K* kout, const V* vin, V* vout, size_t n, unsigned end_bit, bool descending, hipStream_t s) {
+int radix_sort(const K* kin, K* kout, const V* vin, V* vout, size_t n, unsigned end_bit, bool descending, hipStream_t s,
+               unsigned first_bit = 0, bool probe = true) {
     constexpr bool HAS_V = !std::is_same<V, NoValue>::value;
     constexpr int NB = sizeof(K);
     if (n == 0) return GCN_OK;
     if (end_bit > 8 * NB) end_bit = 8 * NB;
     const size_t ntiles = (n + RS_TILE - 1) / RS_TILE;
     if (ntiles >= (1ull << 31)) return fail(GCN_ERR_RANGE, "radix_sort: %zu keys are too many", n);
-    Scratch bh;
-    GCN_TRY(bh.alloc(NB * RS_RADIX * 8));
-    GCN_HIP_TRY(hipMemsetAsync(bh.p, 0, NB * RS_RADIX * 8, s));
-    hipLaunchKernelGGL(k_radix_byte_hist<K>, dim3((unsigned)ntiles), dim3(P_TPB), 0, s, kin, n,
-                       bh.as<unsigned long long>());
-    GCN_LAUNCH_CHECK();
-    unsigned long long h[NB * RS_RADIX];
-    GCN_HIP_TRY(hipMemcpyAsync(h, bh.p, sizeof(h), hipMemcpyDeviceToHost, s));
-    GCN_HIP_TRY(hipStreamSynchronize(s));
     unsigned shifts[NB], masks[NB];
     int npass = 0;
-    for (int p = 0; p * 8 < (int)end_bit; ++p) {
-        const unsigned width = end_bit - 8 * p < 8 ? end_bit - 8 * p : 8;
-        const unsigned mask = (1u << width) - 1u;
-        // bins of the masked digit: fold the byte histogram
-        bool trivial = false;
-        for (unsigned d = 0; d <= mask && !trivial; ++d) {
-            unsigned long long c = 0;
-            for (unsigned hi = d; hi < RS_RADIX; hi += mask + 1) c += h[p * RS_RADIX + hi];
-            trivial = (c == n);
+    if (!probe) {
+        for (unsigned lo = first_bit; lo < end_bit; lo += 8) {
+            shifts[npass] = lo;
+            masks[npass] = (1u << (end_bit - lo < 8 ? end_bit - lo : 8)) - 1u;
+            ++npass;
         }
-        if (trivial) continue;
-        shifts[npass] = 8 * p;
-        masks[npass] = mask;
-        ++npass;
+    } else {
+        Scratch bh;
+        GCN_TRY(bh.alloc(NB * RS_RADIX * 8));
+        GCN_HIP_TRY(hipMemsetAsync(bh.p, 0, NB * RS_RADIX * 8, s));
+        hipLaunchKernelGGL(k_radix_byte_hist<K>, dim3((unsigned)ntiles), dim3(P_TPB), 0, s, kin, n,
+                           bh.as<unsigned long long>());
+        GCN_LAUNCH_CHECK();
+        unsigned long long h[NB * RS_RADIX];
+        GCN_HIP_TRY(hipMemcpyAsync(h, bh.p, sizeof(h), hipMemcpyDeviceToHost, s));
+        GCN_HIP_TRY(hipStreamSynchronize(s));
+        for (int p = 0; p * 8 < (int)end_bit; ++p) {
+            const unsigned width = end_bit - 8 * p < 8 ? end_bit - 8 * p : 8;
+            const unsigned mask = (1u << width) - 1u;
+            // bins of the masked digit: fold the byte histogram
+            bool trivial = false;
+            for (unsigned d = 0; d <= mask && !trivial; ++d) {
+                unsigned long long c = 0;
+                for (unsigned hi = d; hi < RS_RADIX; hi += mask + 1) c += h[p * RS_RADIX + hi];
+                trivial = (c == n);
+            }
+            if (trivial) continue;
+            shifts[npass] = 8 * p;
+            masks[npass] = mask;
+            ++npass;
+        }
     }
     if (npass == 0) {
         GCN_HIP_TRY(hipMemcpyAsync(kout, kin, n * sizeof(K), hipMemcpyDeviceToDevice, s));
         if (HAS_V) GCN_HIP_TRY(hipMemcpyAsync((void*)vout, (const void*)vin, n * sizeof(V), hipMemcpyDeviceToDevice, s));
-        GCN_HIP_TRY(hipStreamSynchronize(s));
         return GCN_OK;
     }
     // positions are 64-bit whatever n is (their table is 1/32 of the keys' size): one code path at every size

@@ -80,7 +80,7 @@ __global__ void k_set_i64(int64_t* p, int64_t v) { *p = v; }
 void free_blocked(Blocked& b);
 
 int build_blocked(Matrix& m, int64_t nnz, int64_t cpb, hipStream_t s) {
-    count_build();
+    count_build(m);
     free_blocked(m.blk);
     Blocked& b = m.blk;
     if (nnz <= 0 || cpb <= 0) return fail(GCN_ERR_BADARG, "build_blocked: empty matrix or bad block width");
@@ -98,8 +98,8 @@ int build_blocked(Matrix& m, int64_t nnz, int64_t cpb, hipStream_t s) {
     const unsigned end_bit = 32 + bits_for(nblocks + 1);
     GCN_TRY((prims::sort_pairs<uint64_t, uint64_t>(k0.as<uint64_t>(), k1.as<uint64_t>(), p0.as<uint64_t>(),
                                                    p1.as<uint64_t>(), (size_t)nnz, end_bit, s)));
-    k0.alloc(16);                                        // release the unsorted copies early
-    p0.alloc(16);
+    k0.drop();                                           // release the unsorted copies early
+    p0.drop();
 
     const size_t padded = (size_t)nsub + SUBS_PER_CHUNK;
     GCN_TRY(device_alloc_t(&b.flags, padded));
@@ -137,7 +137,7 @@ int build_blocked(Matrix& m, int64_t nnz, int64_t cpb, hipStream_t s) {
     GCN_TRY(prims::sort_keys<uint64_t>(rq0.as<uint64_t>(), rq1.as<uint64_t>(), (size_t)R, end_bit2, s));
     GCN_TRY(device_alloc_t(&b.rq_ptr, (size_t)n + 1));
     GCN_TRY(device_alloc_t(&b.rq_idx, (size_t)R));
-    hipLaunchKernelGGL(k_compress, dim3(blocks_for(R)), dim3(TPB), 0, s, R, n, rq1.as<uint64_t>(), b.rq_ptr, b.rq_idx);
+    hipLaunchKernelGGL(k_compress, dim3(blocks_for(R)), dim3(TPB), 0, s, R, n, rq1.as<uint64_t>(), 32u, ~0ull, 0u, 0xffffffffull, b.rq_ptr, b.rq_idx);
     GCN_LAUNCH_CHECK();
     GCN_HIP_TRY(hipStreamSynchronize(s));
     b.cols_per_block = cpb;
@@ -284,7 +284,7 @@ __global__ void k_heavy_len(int64_t nh, const int32_t* __restrict__ rows, const 
 }
 
 int build_sweep(Matrix& m, int64_t nnz, int32_t groups, int32_t rb, int32_t heavy_th, hipStream_t s) {
-    count_build();
+    count_build(m);
     free_sweep(m.swp);
     Sweep& w = m.swp;
     if (nnz <= 0 || rb <= 0 || rb > 256 || (groups != 8 && groups != 16))
@@ -308,13 +308,13 @@ int build_sweep(Matrix& m, int64_t nnz, int32_t groups, int32_t rb, int32_t heav
     const unsigned end_bit = cbits + tbits + 1;
     GCN_TRY((prims::sort_pairs<uint64_t, SweepPayload>(k0.as<uint64_t>(), k1.as<uint64_t>(), p0.as<SweepPayload>(),
                                                        p1.as<SweepPayload>(), (size_t)nnz, end_bit, s)));
-    k0.alloc(16);
-    p0.alloc(16);
+    k0.drop();
+    p0.drop();
     GCN_TRY(seg.alloc(((size_t)ntasks + 1) * 8));
     hipLaunchKernelGGL(k_sweep_seg_ptr, dim3(blocks_for(ntasks + 1)), dim3(TPB), 0, s, ntasks, nnz, cbits, heavy_key,
                        k1.as<uint64_t>(), seg.as<int64_t>());
     GCN_LAUNCH_CHECK();
-    k1.alloc(16);
+    k1.drop();
 
     // pass 1: steps per task; then the longest-first order and the offsets of the tasks
     GCN_TRY(device_alloc_t(&w.task_base, (size_t)ntasks));
@@ -477,7 +477,7 @@ __global__ void k_hub_hot_rowptr(int64_t nh, int64_t nnz_hot, const int32_t* __r
 void free_hub(Hub& h);
 
 int build_hub(Matrix& m, int64_t nnz, int64_t H, int64_t cpb, int32_t dmin, hipStream_t s) {
-    count_build();
+    count_build(m);
     free_hub(m.hub);
     Hub& h = m.hub;
     h.state = -1;                                            // until everything below has succeeded
@@ -554,8 +554,8 @@ int build_hub(Matrix& m, int64_t nnz, int64_t H, int64_t cpb, int32_t dmin, hipS
                        hrows.as<int32_t>(), m.rowptr, pos.as<int64_t>(), hot->rowptr);
     GCN_LAUNCH_CHECK();
     GCN_HIP_TRY(hipStreamSynchronize(s));
-    flag.alloc(16);
-    pos.alloc(16);
+    flag.drop();
+    pos.drop();
     GCN_TRY(build_schedule(*rest, n, nnz_rest, s));
     hot->nsub = (nnz_hot + SUB - 1) / SUB;
     hot->nchunks = (nnz_hot + CHUNK - 1) / CHUNK;

@@ -843,6 +843,7 @@ int want_blocked(Matrix& m, int64_t nnz, int64_t cpb, hipStream_t s) {
             m.blk_parked.erase(m.blk_parked.begin() + (long)i);
             return GCN_OK;
         }
+    BuildScope scope(s);
     return build_blocked(m, nnz, cpb, s);
 }
 
@@ -859,6 +860,7 @@ int want_sweep(Matrix& m, int64_t nnz, int32_t groups, int32_t rb, int32_t th, h
             m.swp_parked.erase(m.swp_parked.begin() + (long)i);
             return GCN_OK;
         }
+    BuildScope scope(s);
     return build_sweep(m, nnz, groups, rb, th, s);
 }
 
@@ -879,10 +881,12 @@ static int want_hub(Matrix& m, const Config& cfg, int64_t nnz, int64_t H, int64_
             m.hub_parked.erase(m.hub_parked.begin() + (long)i);
             return GCN_OK;
         }
+    BuildScope scope(s);
     const int rc = build_hub(m, nnz, H, cpb, cfg.hub_dmin, s);
     if (rc != GCN_OK) {
         // the copy is an optimisation: without it (for instance out of memory) the plain kernel runs
         if (forced) return rc;
+        (void)hipStreamSynchronize(s);
         free_hub(m.hub);
         m.hub.state = -1;
     }
@@ -1049,16 +1053,16 @@ extern "C" int gcn_spmm(gcn_csr* a, int trans, int32_t f, const float* X, int64_
         SpmmOpt o;
         o.pattern = true;
         o.row_scale = a->inv_sqrt_deg;
-        return spmm_launch(a, trans ? a->At : a->A, f, a->xs, f, Z, ldz, epilogue, Zprev, ldzprev, s_of(stream), o);
+        return spmm_launch(a, matrix_of(a, trans), f, a->xs, f, Z, ldz, epilogue, Zprev, ldzprev, s_of(stream), o);
     }
-    return spmm_launch(a, trans ? a->At : a->A, f, X, ldx, Z, ldz, epilogue, Zprev, ldzprev, (hipStream_t)stream);
+    return spmm_launch(a, matrix_of(a, trans), f, X, ldx, Z, ldz, epilogue, Zprev, ldzprev, (hipStream_t)stream);
 }
 
 extern "C" int gcn_spmm_prepare(gcn_csr* a, int trans, int32_t f, void* stream) {
     if (!a || f <= 0) return fail(GCN_ERR_BADARG, "gcn_spmm_prepare: NULL matrix or f <= 0");
     if (trans && !a->has_t) return fail(GCN_ERR_NOTRANSPOSE, "gcn_spmm_prepare: trans=1 needs GCN_BUILD_TRANSPOSE");
     if (use_value_free(a)) GCN_TRY(grow_retire(a, &a->xs, &a->xs_bytes, (size_t)a->n * (size_t)f * sizeof(float)));
-    return spmm_prepare(a, trans ? a->At : a->A, f, (hipStream_t)stream);
+    return spmm_prepare(a, matrix_of(a, trans), f, (hipStream_t)stream);
 }
 
 extern "C" int gcn_spmm_describe(gcn_csr* a, int trans, int32_t f, char* out, size_t out_bytes, void* stream) {
@@ -1069,7 +1073,7 @@ extern "C" int gcn_spmm_describe(gcn_csr* a, int trans, int32_t f, char* out, si
     o.dry = true;
     o.describe = &text;
     o.pattern = use_value_free(a);
-    GCN_TRY(spmm_launch(a, trans ? a->At : a->A, f, nullptr, f, nullptr, f, GCN_EPI_NONE, nullptr, 0, (hipStream_t)stream, o));
+    GCN_TRY(spmm_launch(a, matrix_of(a, trans), f, nullptr, f, nullptr, f, GCN_EPI_NONE, nullptr, 0, (hipStream_t)stream, o));
     if (o.pattern) text += "; value-free (operand rows pre-scaled by d^-1/2, output rows scaled)";
     snprintf(out, out_bytes, "%s", text.c_str());
     return GCN_OK;
@@ -1107,7 +1111,7 @@ extern "C" int gcn_spmm_static(gcn_csr* a, int trans, int32_t f, const float* X,
     int dev = -1;
     GCN_HIP_TRY(hipGetDevice(&dev));
     if (dev != a->device) return fail(GCN_ERR_BADARG, "gcn_spmm_static: the matrix lives on device %d, current device is %d", a->device, dev);
-    Matrix& m = trans ? a->At : a->A;
+    Matrix& m = matrix_of(a, trans);
     const size_t need = (size_t)m.nchunks * (size_t)f * sizeof(float);
     if (need > STATIC_SCRATCH_BYTES)
         return fail(GCN_ERR_WORKSPACE, "gcn_spmm_static: needs %zu bytes of scratch (%lld stored entries / 512, rounded up, x %d floats), the fixed "
@@ -1129,5 +1133,5 @@ extern "C" int gcn_spmm_pattern(gcn_csr* a, int trans, int32_t f, const float* X
     o.pattern = true;
     o.row_scale = row_scale;
     PhaseTimer whole(s_of(stream), GCN_PHASE_SPMM);
-    return spmm_launch(a, trans ? a->At : a->A, f, X, ldx, Z, ldz, epilogue, Zprev, ldzprev, (hipStream_t)stream, o);
+    return spmm_launch(a, matrix_of(a, trans), f, X, ldx, Z, ldz, epilogue, Zprev, ldzprev, (hipStream_t)stream, o);
 }

@@ -92,3 +92,62 @@ def test_bias_gradient(n, f):
     want = Gm.astype(np.float64).sum(0)
     assert np.all(np.abs(host(db) - want) <= 1e-5 * np.sqrt(n) * np.maximum(1.0, np.abs(want)))
     a.close()
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 511, 513, 8191, 8192, 8193, 16_385, 70_001])
+@pytest.mark.parametrize("width", [0, 1, 2, 3])
+def test_radix_sort_tile_edges(n, width):
+    """Keys that put whole wavefronts, whole tiles or single keys on one digit; payloads of every size."""
+    g = G()
+    rs = np.random.default_rng(61 + width)
+    for keys in (rs.integers(0, 1 << 40, n, dtype=np.uint64), np.arange(n, dtype=np.uint64) // np.uint64(64),
+                 np.full(n, 77, np.uint64), rs.integers(0, 2, n, dtype=np.uint64) * np.uint64(0xFF00FF)):
+        pay = None
+        if width:
+            pay = rs.integers(-(1 << 31), 1 << 31, (n, width), dtype=np.int64).astype(np.int32)
+            pay[:, 0] = np.arange(n, dtype=np.int32)
+        order = np.argsort(keys, kind="stable")
+        out, pout = g.gcn_radix_sort(dev(keys.view(np.int64)), None if pay is None else dev(pay))
+        assert np.array_equal(host(out).view(np.uint64), keys[order])
+        if width:
+            assert np.array_equal(host(pout), pay[order])
+
+
+@pytest.mark.parametrize("n", [1, 2, 255, 256, 257, 4097])
+@pytest.mark.parametrize("loops", [False, True])
+def test_csr_create_at_powers_of_two_of_n(n, loops):
+    """Packed keys at vertex counts where a column takes one bit more, with and without the diagonal: against the oracle,
+    A and A^T, for symmetric (one set of arrays for both) and directed input."""
+    g = G()
+    rs = np.random.default_rng(62 + n)
+    src, dst = [rs.integers(0, n, 6 * n, dtype=np.int64).astype(np.int32) for _ in range(2)]
+    src[:3] = dst[:3] = n - 1                                       # loops in the input, at the largest id
+    for sym in (False, True):
+        A = oracle.build_csr(n, src, dst, symmetrise=sym, self_loops=loops, norm="sym" if sym else "none")
+        flags = g.BUILD_TRANSPOSE | (g.ADD_SELF_LOOPS if loops else 0) | ((g.SYMMETRISE | g.NORM_SYM) if sym else 0)
+        a = g.gcn_csr_create(n, dev(src), dev(dst), flags)
+        for trans, want in ((False, A), (True, oracle.transpose(A))):
+            rowptr, colidx, val, deg = [host(t) for t in a.arrays(trans)]
+            assert np.array_equal(rowptr, want.rowptr) and np.array_equal(colidx, want.colidx)
+            assert np.array_equal(val.view(np.uint32), want.val.view(np.uint32))
+        a.close()
+
+
+def test_matrices_of_changing_size_reuse_memory_safely():
+    """Matrices come and go on two streams while products on others are still checked: blocks given back by one are taken
+    by the next."""
+    g = G()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    for k in range(6):
+        n = [5000, 1200, 40_000][k % 3]
+        rs = np.random.default_rng(70 + k)
+        src, dst = [rs.integers(0, n, 8 * n, dtype=np.int64).astype(np.int32) for _ in range(2)]
+        A = oracle.build_csr(n, src, dst)
+        X = synth.normal_features(n, 16, 71 + k)
+        with torch.cuda.stream(streams[k % 2]):
+            a = g.gcn_csr_create(n, dev(src), dev(dst), g.SYMMETRISE | g.ADD_SELF_LOOPS | g.NORM_SYM | g.BUILD_TRANSPOSE)
+            Z = torch.empty(n, 16, device="cuda")
+            g.gcn_spmm(a, 1, dev(X), Z)
+            a.close()
+            assert_close(host(Z), oracle.spmm(A, X), f"matrix {k}")
+    g.gcn_scratch_release()
