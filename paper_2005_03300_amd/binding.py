@@ -49,6 +49,27 @@ def lib():
         L.gcn_version.restype = C.c_char_p
         L.gcn_epoch_workspace_bytes.restype = C.c_size_t
         L.gcn_build_count.restype = C.c_int64
+        # Argument types of the compute calls: plain Python numbers then pass as they are.  Without them every argument
+        # is wrapped in an object of its own, which made a product of a small graph wait for the host (8.7 us per call).
+        p, i, i32, i64, f32, sz = C.c_void_p, C.c_int, C.c_int32, C.c_int64, C.c_float, C.c_size_t
+        L.gcn_spmm.argtypes = [p, i, i32, p, i64, p, i64, i, p, i64, p]
+        L.gcn_spmm_static.argtypes = L.gcn_spmm.argtypes
+        L.gcn_spmm_pattern.argtypes = [p, i, i32, p, i64, p, i64, p, i, p, i64, p]
+        L.gcn_scale_rows.argtypes = [i64, i32, p, i64, p, p, i64, p]
+        L.gcn_gemm.argtypes = [i, i, i64, i64, i64, p, i64, p, i64, p, i64, p, i, p, i64, p]
+        L.gcn_relu.argtypes = [i64, i32, p, i64, p, i64, p]
+        L.gcn_relu_mask.argtypes = [i64, i32, p, i64, p, i64, p, i64, p]
+        L.gcn_softmax_nll.argtypes = [i64, i32, p, i64, p, p, p, i64, p]
+        L.gcn_softmax_nll_masked.argtypes = [i64, i32, p, i64, p, i64, p, p, i64, p]
+        L.gcn_layer_forward.argtypes = [p, i32, i32, p, i64, p, p, p, p, p, i, i, p]
+        L.gcn_layer_backward.argtypes = [p, i32, i32, p, i64, p, p, p, p, p, p, p, p, i, p]
+        L.gcn_epoch.argtypes = [p, i32, p, p, p, p, p, f32, p, p, sz, i, p]
+        L.gcn_epoch_masked.argtypes = [p, i32, p, p, p, i64, p, p, f32, p, p, sz, i, p]
+        L.gcn_epoch_preaggregated.argtypes = L.gcn_epoch_masked.argtypes
+        global _raw_stream, _device, _f32, _i32
+        import torch
+        _raw_stream, _device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+        _f32, _i32 = torch.float32, torch.int32
         _lib = L
     return _lib
 
@@ -59,24 +80,32 @@ def _check(rc: int):
 
 
 def _stream():
-    import torch
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current stream's handle (0: the default stream)."""
+    return C.c_void_p(_now())
+
+
+def _now() -> int:
+    return _raw_stream(_device())
 
 
 def _ptr(t):
     return C.c_void_p(0 if t is None else t.data_ptr())
 
 
+def _at(t) -> int:
+    return 0 if t is None else t.data_ptr()
+
+
 def _ld(t) -> int:
-    assert t.dim() == 2 and (t.shape[1] == 1 or t.stride(1) == 1), "rows must be contiguous"
-    return t.stride(0) if t.shape[0] > 1 else max(t.stride(0), t.shape[1])
+    rows, cols = t.shape
+    s0, s1 = t.stride()
+    assert cols == 1 or s1 == 1, "rows must be contiguous"
+    return s0 if rows > 1 else max(s0, cols)
 
 
 def _dev(t, dtype=None):
-    import torch
     assert t.is_cuda, "device tensor expected"
-    if dtype is not None:
-        assert t.dtype == dtype, (t.dtype, dtype)
+    assert dtype is None or t.dtype == dtype, (t.dtype, dtype)
     return t
 
 
@@ -169,51 +198,51 @@ def gcn_csr_create_from_csr_rect(n_rows: int, n_cols: int, rowptr, colidx, val, 
     return Csr(out.value)
 
 
+def _product(a: Csr, trans: int, X, Z):
+    """Checks the operands of a sparse product; returns its width and the leading dimensions."""
+    assert X.is_cuda and Z.is_cuda, "device tensor expected"
+    assert X.dtype is _f32 and Z.dtype is _f32, (X.dtype, Z.dtype)
+    rows, f = X.shape
+    assert tuple(Z.shape) == ((a.n_cols if trans else a.n_rows), f)
+    assert rows == (a.n_rows if trans else a.n_cols)
+    return f, _ld(X), _ld(Z)
+
+
 def gcn_spmm(a: Csr, trans: int, X, Z, epilogue: int = EPI_NONE, Zprev=None):
-    import torch
-    _dev(X, torch.float32), _dev(Z, torch.float32)
-    f = X.shape[1]
-    xr, zr = (a.n_rows, a.n_cols) if trans else (a.n_cols, a.n_rows)
-    assert X.shape[0] == xr and tuple(Z.shape) == (zr, f)
-    _check(lib().gcn_spmm(a._h, int(trans), C.c_int32(f), _ptr(X), C.c_int64(_ld(X)), _ptr(Z), C.c_int64(_ld(Z)),
-                          int(epilogue), _ptr(Zprev), C.c_int64(_ld(Zprev) if Zprev is not None else 0), _stream()))
+    L = _lib or lib()
+    f, ldx, ldz = _product(a, trans, X, Z)
+    rc = L.gcn_spmm(a._h, trans, f, X.data_ptr(), ldx, Z.data_ptr(), ldz, epilogue, _at(Zprev),
+                    0 if Zprev is None else _ld(Zprev), _raw_stream(_device()))
+    if rc:
+        _check(rc)
     return Z
 
 
 def gcn_spmm_static(a: Csr, trans: int, X, Z, epilogue: int = EPI_NONE, Zprev=None):
-    import torch
-    _dev(X, torch.float32), _dev(Z, torch.float32)
-    f = X.shape[1]
-    xr, zr = (a.n_rows, a.n_cols) if trans else (a.n_cols, a.n_rows)
-    assert X.shape[0] == xr and tuple(Z.shape) == (zr, f)
-    _check(lib().gcn_spmm_static(a._h, int(trans), C.c_int32(f), _ptr(X), C.c_int64(_ld(X)), _ptr(Z),
-                                 C.c_int64(_ld(Z)), int(epilogue), _ptr(Zprev),
-                                 C.c_int64(_ld(Zprev) if Zprev is not None else 0), _stream()))
+    L = _lib or lib()
+    f, ldx, ldz = _product(a, trans, X, Z)
+    _check(L.gcn_spmm_static(a._h, trans, f, X.data_ptr(), ldx, Z.data_ptr(), ldz, epilogue, _at(Zprev),
+                             0 if Zprev is None else _ld(Zprev), _now()))
     return Z
 
 
 def gcn_spmm_pattern(a: Csr, trans: int, X, Z, row_scale=None, epilogue: int = EPI_NONE, Zprev=None):
-    import torch
-    _dev(X, torch.float32), _dev(Z, torch.float32)
-    f = X.shape[1]
-    xr, zr = (a.n_rows, a.n_cols) if trans else (a.n_cols, a.n_rows)
-    assert X.shape[0] == xr and tuple(Z.shape) == (zr, f)
+    L = _lib or lib()
+    f, ldx, ldz = _product(a, trans, X, Z)
     if row_scale is not None:
-        _dev(row_scale, torch.float32)
-        assert row_scale.numel() == zr and row_scale.is_contiguous()
-    _check(lib().gcn_spmm_pattern(a._h, int(trans), C.c_int32(f), _ptr(X), C.c_int64(_ld(X)), _ptr(Z),
-                                  C.c_int64(_ld(Z)), _ptr(row_scale), int(epilogue), _ptr(Zprev),
-                                  C.c_int64(_ld(Zprev) if Zprev is not None else 0), _stream()))
+        _dev(row_scale, _f32)
+        assert row_scale.numel() == Z.shape[0] and row_scale.is_contiguous()
+    _check(L.gcn_spmm_pattern(a._h, trans, f, X.data_ptr(), ldx, Z.data_ptr(), ldz, _at(row_scale), epilogue, _at(Zprev),
+                              0 if Zprev is None else _ld(Zprev), _now()))
     return Z
 
 
 def gcn_scale_rows(X, scale, Y):
-    import torch
-    _dev(X, torch.float32), _dev(scale, torch.float32), _dev(Y, torch.float32)
+    L = _lib or lib()
+    _dev(X, _f32), _dev(scale, _f32), _dev(Y, _f32)
     rows, cols = X.shape
     assert tuple(Y.shape) == (rows, cols) and scale.numel() == rows and scale.is_contiguous()
-    _check(lib().gcn_scale_rows(C.c_int64(rows), C.c_int32(cols), _ptr(X), C.c_int64(_ld(X)), _ptr(scale), _ptr(Y),
-                                C.c_int64(_ld(Y)), _stream()))
+    _check(L.gcn_scale_rows(rows, cols, X.data_ptr(), _ld(X), scale.data_ptr(), Y.data_ptr(), _ld(Y), _now()))
     return Y
 
 
@@ -226,61 +255,60 @@ def gcn_csr_inv_sqrt_degrees(a: Csr, out):
 
 
 def gcn_gemm(ta: int, tb: int, A, B, Cm, bias=None, epilogue: int = EPI_NONE, Zprev=None):
-    import torch
-    _dev(A, torch.float32), _dev(B, torch.float32), _dev(Cm, torch.float32)
+    L = _lib or lib()
+    _dev(A, _f32), _dev(B, _f32), _dev(Cm, _f32)
     M, N = Cm.shape
     K = A.shape[0] if ta else A.shape[1]
-    _check(lib().gcn_gemm(int(ta), int(tb), C.c_int64(M), C.c_int64(N), C.c_int64(K), _ptr(A), C.c_int64(_ld(A)),
-                          _ptr(B), C.c_int64(_ld(B)), _ptr(Cm), C.c_int64(_ld(Cm)), _ptr(bias), int(epilogue),
-                          _ptr(Zprev), C.c_int64(_ld(Zprev) if Zprev is not None else 0), _stream()))
+    _check(L.gcn_gemm(int(ta), int(tb), M, N, K, A.data_ptr(), _ld(A), B.data_ptr(), _ld(B), Cm.data_ptr(), _ld(Cm), _at(bias),
+                      int(epilogue), _at(Zprev), 0 if Zprev is None else _ld(Zprev), _now()))
     return Cm
 
 
 def gcn_relu(Z, H):
-    _check(lib().gcn_relu(C.c_int64(Z.shape[0]), C.c_int32(Z.shape[1]), _ptr(Z), C.c_int64(_ld(Z)), _ptr(H),
-                          C.c_int64(_ld(H)), _stream()))
+    L = _lib or lib()
+    _check(L.gcn_relu(Z.shape[0], Z.shape[1], Z.data_ptr(), _ld(Z), H.data_ptr(), _ld(H), _now()))
     return H
 
 
 def gcn_relu_mask(G, Zprev, out):
-    _check(lib().gcn_relu_mask(C.c_int64(G.shape[0]), C.c_int32(G.shape[1]), _ptr(G), C.c_int64(_ld(G)), _ptr(Zprev),
-                               C.c_int64(_ld(Zprev)), _ptr(out), C.c_int64(_ld(out)), _stream()))
+    L = _lib or lib()
+    _check(L.gcn_relu_mask(G.shape[0], G.shape[1], G.data_ptr(), _ld(G), Zprev.data_ptr(), _ld(Zprev), out.data_ptr(),
+                           _ld(out), _now()))
     return out
 
 
 def gcn_softmax_nll(Z, labels, loss, G=None):
-    import torch
-    _dev(Z, torch.float32), _dev(labels, torch.int32), _dev(loss, torch.float32)
-    _check(lib().gcn_softmax_nll(C.c_int64(Z.shape[0]), C.c_int32(Z.shape[1]), _ptr(Z), C.c_int64(_ld(Z)),
-                                 _ptr(labels), _ptr(loss), _ptr(G), C.c_int64(_ld(G) if G is not None else 0),
-                                 _stream()))
+    L = _lib or lib()
+    _dev(Z, _f32), _dev(labels, _i32), _dev(loss, _f32)
+    _check(L.gcn_softmax_nll(Z.shape[0], Z.shape[1], Z.data_ptr(), _ld(Z), labels.data_ptr(), loss.data_ptr(), _at(G),
+                             0 if G is None else _ld(G), _now()))
     return loss
 
 
 def gcn_softmax_nll_masked(Z, labels, n_labelled: int, loss, G=None):
-    import torch
-    _dev(Z, torch.float32), _dev(labels, torch.int32), _dev(loss, torch.float32)
-    _check(lib().gcn_softmax_nll_masked(C.c_int64(Z.shape[0]), C.c_int32(Z.shape[1]), _ptr(Z), C.c_int64(_ld(Z)),
-                                        _ptr(labels), C.c_int64(n_labelled), _ptr(loss), _ptr(G),
-                                        C.c_int64(_ld(G) if G is not None else 0), _stream()))
+    L = _lib or lib()
+    _dev(Z, _f32), _dev(labels, _i32), _dev(loss, _f32)
+    _check(L.gcn_softmax_nll_masked(Z.shape[0], Z.shape[1], Z.data_ptr(), _ld(Z), labels.data_ptr(), n_labelled,
+                                    loss.data_ptr(), _at(G), 0 if G is None else _ld(G), _now()))
     return loss
 
 
 def gcn_layer_forward(a: Csr, Hin, W, Z, Hout, T, order: int = ORDER_AUTO, act: int = ACT_RELU, bias=None):
+    L = _lib or lib()
     f_in, f_out = W.shape
     assert W.is_contiguous() and Z.is_contiguous() and T.is_contiguous()
     assert Hout is None or Hout.is_contiguous()
-    _check(lib().gcn_layer_forward(a._h, C.c_int32(f_in), C.c_int32(f_out), _ptr(Hin), C.c_int64(_ld(Hin)), _ptr(W),
-                                   _ptr(bias), _ptr(Z), _ptr(Hout), _ptr(T), int(order), int(act), _stream()))
+    _check(L.gcn_layer_forward(a._h, f_in, f_out, _at(Hin), _ld(Hin), W.data_ptr(), _at(bias), Z.data_ptr(), _at(Hout),
+                               T.data_ptr(), int(order), int(act), _now()))
 
 
 def gcn_layer_backward(a: Csr, Hin, Zprev, W, G, T, S, Y, Gprev, order: int = ORDER_AUTO, dbias=None):
+    L = _lib or lib()
     f_in, f_out = W.shape
     for t in (W, G, S, Y):
         assert t.is_contiguous()
-    _check(lib().gcn_layer_backward(a._h, C.c_int32(f_in), C.c_int32(f_out), _ptr(Hin),
-                                    C.c_int64(_ld(Hin) if Hin is not None else 0), _ptr(Zprev), _ptr(W), _ptr(G),
-                                    _ptr(T), _ptr(S), _ptr(Y), _ptr(dbias), _ptr(Gprev), int(order), _stream()))
+    _check(L.gcn_layer_backward(a._h, f_in, f_out, _at(Hin), 0 if Hin is None else _ld(Hin), _at(Zprev), W.data_ptr(),
+                                G.data_ptr(), _at(T), S.data_ptr(), Y.data_ptr(), _at(dbias), _at(Gprev), int(order), _now()))
 
 
 def _dims_array(dims):
@@ -291,39 +319,37 @@ def gcn_epoch_workspace_bytes(n: int, dims, order: int = ORDER_AUTO) -> int:
     return int(lib().gcn_epoch_workspace_bytes(C.c_int64(n), C.c_int32(len(dims) - 1), _dims_array(dims), int(order)))
 
 
+def _pointers(tensors):
+    return (C.c_void_p * len(tensors))(*[t.data_ptr() for t in tensors])
+
+
 def gcn_epoch(a: Csr, dims, H0, labels, W, Y, lr: float, loss, workspace, order: int = ORDER_AUTO):
+    lib_ = _lib or lib()
     L = len(dims) - 1
     assert len(W) == L and len(Y) == L and H0.is_contiguous()
-    Wp = (C.c_void_p * L)(*[w.data_ptr() for w in W])
-    Yp = (C.c_void_p * L)(*[y.data_ptr() for y in Y])
-    _check(lib().gcn_epoch(a._h, C.c_int32(L), _dims_array(dims), _ptr(H0), _ptr(labels), Wp, Yp, C.c_float(lr),
-                           _ptr(loss), _ptr(workspace), C.c_size_t(workspace.numel() * workspace.element_size()),
-                           int(order), _stream()))
+    _check(lib_.gcn_epoch(a._h, L, _dims_array(dims), _at(H0), _at(labels), _pointers(W), _pointers(Y), lr, _at(loss),
+                          _at(workspace), workspace.numel() * workspace.element_size(), int(order), _now()))
     return loss
 
 
 def gcn_epoch_masked(a: Csr, dims, H0, labels, n_labelled: int, W, Y, lr: float, loss, workspace,
                      order: int = ORDER_AUTO):
+    lib_ = _lib or lib()
     L = len(dims) - 1
     assert len(W) == L and len(Y) == L and H0.is_contiguous()
-    Wp = (C.c_void_p * L)(*[w.data_ptr() for w in W])
-    Yp = (C.c_void_p * L)(*[y.data_ptr() for y in Y])
-    _check(lib().gcn_epoch_masked(a._h, C.c_int32(L), _dims_array(dims), _ptr(H0), _ptr(labels),
-                                  C.c_int64(n_labelled), Wp, Yp, C.c_float(lr), _ptr(loss), _ptr(workspace),
-                                  C.c_size_t(workspace.numel() * workspace.element_size()), int(order), _stream()))
+    _check(lib_.gcn_epoch_masked(a._h, L, _dims_array(dims), _at(H0), _at(labels), n_labelled, _pointers(W), _pointers(Y), lr,
+                                 _at(loss), _at(workspace), workspace.numel() * workspace.element_size(), int(order), _now()))
     return loss
 
 
 def gcn_epoch_preaggregated(a: Csr, dims, P0, labels, n_labelled: int, W, Y, lr: float, loss, workspace,
                             order: int = ORDER_AUTO):
+    lib_ = _lib or lib()
     L = len(dims) - 1
     assert len(W) == L and len(Y) == L and P0.is_contiguous() and tuple(P0.shape) == (a.n, dims[0])
-    Wp = (C.c_void_p * L)(*[w.data_ptr() for w in W])
-    Yp = (C.c_void_p * L)(*[y.data_ptr() for y in Y])
-    _check(lib().gcn_epoch_preaggregated(a._h, C.c_int32(L), _dims_array(dims), _ptr(P0), _ptr(labels),
-                                         C.c_int64(n_labelled), Wp, Yp, C.c_float(lr), _ptr(loss), _ptr(workspace),
-                                         C.c_size_t(workspace.numel() * workspace.element_size()), int(order),
-                                         _stream()))
+    _check(lib_.gcn_epoch_preaggregated(a._h, L, _dims_array(dims), _at(P0), _at(labels), n_labelled, _pointers(W),
+                                        _pointers(Y), lr, _at(loss), _at(workspace),
+                                        workspace.numel() * workspace.element_size(), int(order), _now()))
     return loss
 
 
