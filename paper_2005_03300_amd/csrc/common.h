@@ -5,6 +5,7 @@
 #include <stdint.h>
 #include <stdio.h>
 
+#include <atomic>
 #include <string>
 #include <vector>
 
@@ -59,8 +60,8 @@ struct Blocked {
     uint32_t* flags = nullptr;   // [nsub + pad]
     int32_t* sub_row = nullptr;  // [nsub + pad]
     int64_t* rp = nullptr;       // [R+1] first entry of each partial row
-    int32_t* fix_list = nullptr; // [n_fix] chunks that lead the continuation of a row begun in an earlier chunk
-    int64_t n_fix = -1;          // -1: no list (every chunk is examined)
+    int4* fix_list = nullptr;    // [n_fix] the rows that cross chunks (see build_fix_list)
+    int64_t n_fix = 0, n_fix_long = 0;   // the first n_fix_long of them cover a whole further chunk
     int64_t* rq_ptr = nullptr;   // [n+1]  row i owns partial rows rq_idx[rq_ptr[i] .. rq_ptr[i+1])
     int32_t* rq_idx = nullptr;   // [R]    ascending block order inside a row
 };
@@ -124,8 +125,8 @@ struct Matrix {
     int64_t* ne_rowptr = nullptr;// [n_ne+1] rowptr restricted to non-empty rows, or NULL (= rowptr)
     int32_t* empty_rows = nullptr;// [nrows - n_ne] the rows without entries, or NULL when there are none
     int64_t n_ne = 0;
-    int32_t* fix_list = nullptr; // [n_fix] chunks that lead the continuation of a row begun in an earlier chunk
-    int64_t n_fix = -1;          // -1: no list (every chunk is examined)
+    int4* fix_list = nullptr;    // [n_fix] the rows that cross chunks (see build_fix_list)
+    int64_t n_fix = 0, n_fix_long = 0;   // the first n_fix_long of them cover a whole further chunk
     int64_t nsub = 0, nchunks = 0;
     int32_t max_degree = 0;
     bool both = false;           // this matrix is A and A^T (gcn_csr::symmetric): its other orders count for both
@@ -258,9 +259,27 @@ struct PhaseTimer {
     ~PhaseTimer() { timing_end(s, phase); }
 };
 
+// Launches a kernel with dynamic LDS.  More than 64 KB per workgroup (static part included) has to be asked for, once
+// per kernel, device and size (two threads may both ask, which is harmless).
+template <auto Kernel, typename Args>
+void launch_lds(dim3 grid, int threads, size_t lds, hipStream_t s, const Args& args) {
+    if (lds > 44 * 1024) {
+        static std::atomic<size_t> asked[64];
+        int dev = 0;
+        (void)hipGetDevice(&dev);
+        if (asked[dev & 63].load(std::memory_order_relaxed) < lds) {
+            (void)hipFuncSetAttribute((const void*)Kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            asked[dev & 63].store(lds, std::memory_order_relaxed);
+        }
+    }
+    hipLaunchKernelGGL(Kernel, grid, dim3(threads), lds, s, args);
+}
+
 int build_schedule(Matrix& m, int64_t n, int64_t nnz, hipStream_t s);
-int build_fix_list(const uint32_t* flags, const int32_t* sub_row, const int64_t* rp, int64_t nchunks, int32_t** list,
-                   int64_t* count, hipStream_t s);
+// One record per row whose entries run on into further chunks: x, y = the first and the last of them, z = the row (its
+// index among the non-empty rows).  Rows that leave no row start in chunk x come first (n_long of them).
+int build_fix_list(const uint32_t* flags, const int32_t* sub_row, const int64_t* rp, int64_t nnz, int4** list,
+                   int64_t* count, int64_t* n_long, hipStream_t s);
 int build_blocked(Matrix& m, int64_t nnz, int64_t cols_per_block, hipStream_t s);
 // make m.blk / m.swp the copy with the given key: the current one, a parked one, or a newly built one
 int want_blocked(Matrix& m, int64_t nnz, int64_t cols_per_block, hipStream_t s);

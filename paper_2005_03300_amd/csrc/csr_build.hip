@@ -165,38 +165,49 @@ static int compress_keys(Matrix& m, int64_t n, int64_t nnz, const uint64_t* keys
 }
 
 // The chunks c >= 1 whose first entry continues a row begun earlier and that are the first such chunk
-// of that row: exactly the chunks for which the fix-up kernel has work.
+// of that row: exactly the chunks for which the fix-up kernel has work.  `covered`: only those in which no row starts,
+// otherwise only the others.
 struct LeadsCarry {
     const uint32_t* flags;
     const int32_t* sub_row;
     const int64_t* rp;
-    __device__ bool operator()(const int32_t& c0) const {
-        const int64_t c = (int64_t)c0 + 1;
+    int64_t nnz;
+    bool covered;
+    __device__ bool operator()(const int64_t& c0) const {
+        const int64_t c = c0 + 1;
         const int64_t j0 = c * SUBS_PER_CHUNK;
         if (flags[j0] & 1u) return false;
-        return c == rp[sub_row[j0]] / CHUNK + 1;
+        const int32_t q = sub_row[j0];
+        if (c != rp[q] / CHUNK + 1) return false;
+        const int64_t end = (c + 1) * CHUNK < nnz ? (c + 1) * CHUNK : nnz;
+        return (rp[q + 1] >= end) == covered;
     }
 };
 
-__global__ void k_add_one(int64_t count, int32_t* __restrict__ v) {
+__global__ void k_fix_records(int64_t count, const int32_t* __restrict__ sel, const int32_t* __restrict__ sub_row,
+                              const int64_t* __restrict__ rp, int4* __restrict__ list) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < count) v[t] += 1;
+    if (t >= count) return;
+    const int32_t c = sel[t] + 1;
+    const int32_t q = sub_row[(int64_t)c * SUBS_PER_CHUNK];
+    list[t] = make_int4(c, (int32_t)((rp[q + 1] - 1) / CHUNK), q, 0);
 }
 
-int build_fix_list(const uint32_t* flags, const int32_t* sub_row, const int64_t* rp, int64_t nchunks, int32_t** list,
-                   int64_t* count, hipStream_t s) {
-    *count = 0;
+int build_fix_list(const uint32_t* flags, const int32_t* sub_row, const int64_t* rp, int64_t nnz, int4** list,
+                   int64_t* count, int64_t* n_long, hipStream_t s) {
+    *count = *n_long = 0;
+    const int64_t nchunks = (nnz + CHUNK - 1) / CHUNK;
     if (nchunks <= 1) return GCN_OK;
-    if (nchunks >= (1ll << 31)) { *count = -1; return GCN_OK; }          // keep the exhaustive form
+    if (nchunks >= (1ll << 31)) return fail(GCN_ERR_RANGE, "schedule: too many chunks");
     TempBuf sel;
     GCN_TRY(sel.alloc((size_t)(nchunks - 1) * 4));
-    LeadsCarry pred{flags, sub_row, rp};
-    int64_t nsel = 0;
-    GCN_TRY(prims::select_indices(nchunks - 1, pred, sel.as<int32_t>(), &nsel, s));
+    int64_t n_short = 0;
+    GCN_TRY(prims::select_indices(nchunks - 1, LeadsCarry{flags, sub_row, rp, nnz, true}, sel.as<int32_t>(), n_long, s));
+    GCN_TRY(prims::select_indices(nchunks - 1, LeadsCarry{flags, sub_row, rp, nnz, false}, sel.as<int32_t>() + *n_long, &n_short, s));
+    const int64_t nsel = *n_long + n_short;
     if (nsel > 0) {
         GCN_TRY(device_alloc_t(list, (size_t)nsel));
-        GCN_HIP_TRY(hipMemcpyAsync(*list, sel.p, (size_t)nsel * 4, hipMemcpyDeviceToDevice, s));
-        hipLaunchKernelGGL(k_add_one, dim3(blocks_for(nsel)), dim3(TPB), 0, s, nsel, *list);
+        hipLaunchKernelGGL(k_fix_records, dim3(blocks_for(nsel)), dim3(TPB), 0, s, nsel, sel.as<int32_t>(), sub_row, rp, *list);
         GCN_LAUNCH_CHECK();
     }
     *count = nsel;
@@ -241,7 +252,7 @@ int build_schedule(Matrix& m, int64_t n, int64_t nnz, hipStream_t s) {
         hipLaunchKernelGGL(k_sub_rows, dim3(blocks_for(m.nsub)), dim3(TPB), 0, s, m.nsub, m.n_ne, rp, m.sub_row);
         GCN_LAUNCH_CHECK();
     }
-    if (nnz > 0) GCN_TRY(build_fix_list(m.flags, m.sub_row, rp, m.nchunks, &m.fix_list, &m.n_fix, s));
+    if (nnz > 0) GCN_TRY(build_fix_list(m.flags, m.sub_row, rp, nnz, &m.fix_list, &m.n_fix, &m.n_fix_long, s));
     return GCN_OK;
 }
 

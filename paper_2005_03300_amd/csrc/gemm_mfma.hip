@@ -10,8 +10,6 @@
 //
 // Operand layout of the 16x16x4 instruction (64 lanes): lane l supplies A[i = l%16][k = l/16] and
 // B[k = l/16][j = l%16], and holds D[i = 4*(l/16) + v][j = l%16] in element v of its accumulator.
-#include <atomic>
-
 #include "common.h"
 
 namespace gcn {
@@ -566,23 +564,6 @@ __global__ __launch_bounds__(1024) void k_tn_reduce(int32_t M, int32_t N, int pa
 }
 
 static inline bool al16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
-
-// Launches a kernel with dynamic LDS.  More than 64 KB per workgroup has to be asked for, once per kernel and device
-// (a bit per device, set after the request: two threads may both ask, which is harmless).
-template <auto Kernel, typename Args>
-static void launch_lds(dim3 grid, int threads, size_t lds, hipStream_t s, const Args& args) {
-    if (lds > 64 * 1024) {
-        static std::atomic<uint64_t> asked{0};
-        int dev = 0;
-        (void)hipGetDevice(&dev);
-        const uint64_t bit = 1ull << (dev & 63);
-        if (!(asked.load(std::memory_order_relaxed) & bit)) {
-            (void)hipFuncSetAttribute((const void*)Kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-            asked.fetch_or(bit, std::memory_order_relaxed);
-        }
-    }
-    hipLaunchKernelGGL(Kernel, grid, dim3(threads), lds, s, args);
-}
 
 template <int NT, bool TR, bool ASC>
 static void launch_tall_epi(const TallArgs& args, int epilogue, dim3 grid, int threads, size_t lds, hipStream_t s) {

@@ -143,7 +143,7 @@ int build_blocked(Matrix& m, int64_t nnz, int64_t cpb, hipStream_t s) {
     b.cols_per_block = cpb;
     b.nblocks = (int32_t)nblocks;
     b.nrows = R;
-    GCN_TRY(build_fix_list(b.flags, b.sub_row, b.rp, (nnz + CHUNK - 1) / CHUNK, &b.fix_list, &b.n_fix, s));
+    GCN_TRY(build_fix_list(b.flags, b.sub_row, b.rp, nnz, &b.fix_list, &b.n_fix, &b.n_fix_long, s));
     return GCN_OK;
 }
 
@@ -398,7 +398,7 @@ int build_sweep(Matrix& m, int64_t nnz, int32_t groups, int32_t rb, int32_t heav
         hipLaunchKernelGGL(k_sub_rows, dim3(blocks_for(h->nsub)), dim3(TPB), 0, s, h->nsub, h->n_ne, h->ne_rowptr, h->sub_row);
         GCN_LAUNCH_CHECK();
         GCN_HIP_TRY(hipStreamSynchronize(s));
-        GCN_TRY(build_fix_list(h->flags, h->sub_row, h->ne_rowptr, h->nchunks, &h->fix_list, &h->n_fix, s));
+        GCN_TRY(build_fix_list(h->flags, h->sub_row, h->ne_rowptr, nnz_heavy, &h->fix_list, &h->n_fix, &h->n_fix_long, s));
     }
     GCN_HIP_TRY(hipStreamSynchronize(s));
     w.groups = groups;

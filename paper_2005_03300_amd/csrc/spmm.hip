@@ -17,6 +17,7 @@
 // from there; the gathered rows of X are read with one 16-byte load per lane.
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 #include <string>
 
 #include "common.h"
@@ -24,9 +25,6 @@
 namespace gcn {
 
 static constexpr int WAVES_PER_BLOCK = 4;
-#ifndef SPLIT_UNROLL
-#define SPLIT_UNROLL 4
-#endif
 static constexpr int SUB_STRIDE = SUB + 4;                         // LDS padding: groups hit different banks
 static constexpr int LDS_PER_WAVE = SUBS_PER_CHUNK * SUB_STRIDE;   // ints
 
@@ -39,8 +37,8 @@ struct SplitArgs {
     const int32_t* sub_row;
     const int32_t* ne_rows;   // NULL: row index == non-empty-row index
     const int64_t* rp;        // rowptr over non-empty rows
-    const int32_t* fix_list;  // chunks with work for the fix-up kernel (n_fix of them), or n_fix < 0: all chunks
-    int64_t n_fix;
+    const int4* fix_list;     // the rows that cross chunks: n_fix of them (see build_fix_list)
+    int64_t n_fix, n_fix_long;  // the first n_fix_long of them cover a whole further chunk
     int64_t nnz, nsub, nchunks;
     int32_t f;
     const float* X;
@@ -66,14 +64,14 @@ __device__ __forceinline__ float4 stream_load_f4(const float* p) {
     return make_float4(v.x, v.y, v.z, v.w);
 }
 
-template <int VEC> struct Vec;
-template <> struct Vec<4> { using T = float4; };
-template <> struct Vec<1> { using T = float; };
+// 16 bytes at any 4-byte aligned address: the same instruction as for an aligned one, so one kernel serves every width
+// and leading dimension.
+struct __attribute__((packed, aligned(4))) f4u { float x, y, z, w; };
 
 template <int VEC>
 __device__ __forceinline__ void load_vec(float (&d)[VEC], const float* p) {
     if constexpr (VEC == 4) {
-        float4 v = *reinterpret_cast<const float4*>(p);
+        const f4u v = *reinterpret_cast<const f4u*>(p);
         d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
     } else {
         d[0] = *p;
@@ -83,10 +81,29 @@ __device__ __forceinline__ void load_vec(float (&d)[VEC], const float* p) {
 template <int VEC>
 __device__ __forceinline__ void store_vec(float* p, const float (&d)[VEC]) {
     if constexpr (VEC == 4) {
-        *reinterpret_cast<float4*>(p) = make_float4(d[0], d[1], d[2], d[3]);
+        *reinterpret_cast<f4u*>(p) = f4u{d[0], d[1], d[2], d[3]};
     } else {
         *p = d[0];
     }
+}
+
+// The columns of one lane in panel `y` of an operand of width f: VEC of them from `col0` (false: none).  A width that is
+// no multiple of 4 ends with a lane that repeats columns of its left neighbour, so that its 16 bytes stay inside
+// the row; both compute and store the same values.  When fewer than four columns are left for the last panel it
+// takes four more from the panel before, so that the repetition stays inside one wavefront (and a matrix with
+// a mask that is the output itself works).
+template <int LPR, int VEC>
+__device__ __forceinline__ bool lane_columns(int f, int y, int ny, int li, int* col0) {
+    constexpr int W = LPR * VEC;
+    int first = y * W, end = first + W < f ? first + W : f;
+    if constexpr (VEC == 4) {
+        const bool thin = ny > 1 && f - (ny - 1) * W < 4;
+        if (thin && y == ny - 1) first -= 4;
+        if (thin && y == ny - 2) end -= 4;
+    }
+    const int c = first + li * VEC;
+    *col0 = c + VEC <= end ? c : end - VEC;
+    return c < end;
 }
 
 template <int VEC, int EPI>
@@ -113,21 +130,24 @@ __device__ __forceinline__ void epilogue_store(float* z, const float* zprev, flo
 // The work of one workgroup: the four chunks 4*grp .. 4*grp+3 of the matrix described by `a`.
 // s_col / s_val: the workgroup's staging arrays, [WAVES_PER_BLOCK][LDS_PER_WAVE] each (owned by the kernel,
 // so that two instantiations of this body in one kernel share them).
-template <int LPR, int VEC, int EPI>
+template <int LPR, int VEC, int EPI, int UNR>
 __device__ __forceinline__ void split_body(const SplitArgs& a, int64_t grp, int32_t (*s_col)[LDS_PER_WAVE],
                                            float (*s_val)[LDS_PER_WAVE]) {
     constexpr int G = 64 / LPR;                 // lane groups per wavefront
     constexpr int NW = SUBS_PER_CHUNK / G;      // flag words per group
-    static_assert(NW >= 1, "a group needs at least one flag word");
-    constexpr int UNR = SPLIT_UNROLL;           // gathers in flight per lane group
+    static_assert(NW >= 1 && G > 1, "a group needs at least one flag word");
+    static_assert(UNR % 4 == 0 && SUB % UNR == 0, "gathers in flight per lane group");
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t c = grp * WAVES_PER_BLOCK + wave;
     if (c >= a.nchunks) return;                 // whole wavefront leaves; no block-wide barrier below
     const int g = lane / LPR, li = lane % LPR;
-    const int col0 = blockIdx.y * (LPR * VEC) + li * VEC;
-    const bool col_ok = col0 < a.f;
+    int col0;
+    const bool col_ok = lane_columns<LPR, VEC>(a.f, blockIdx.y, gridDim.y, li, &col0);
     const int64_t k0 = c * CHUNK;
+    const int64_t knext = k0 + CHUNK;
+    // (flags is padded by a chunk of zero words)
+    const bool continued = knext < a.nnz && !(a.flags[(c + 1) * SUBS_PER_CHUNK] & 1u);
 
     // ---- stage the chunk's column indices and values in LDS (coalesced 16-byte loads) ----
     int32_t* lc = s_col[wave];
@@ -250,13 +270,10 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int64_t grp, int3
         }
     }
     float T[VEC];
-    int stop_next = 0;
-    if constexpr (G > 1) {
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) T[v] = __shfl_down(R[v], LPR, 64);
-        stop_next = __shfl_down(stop, LPR, 64);
-    }
-    if (G == 1 || g == G - 1) {
+    for (int v = 0; v < VEC; ++v) T[v] = __shfl_down(R[v], LPR, 64);
+    int stop_next = __shfl_down(stop, LPR, 64);
+    if (g == G - 1) {
 #pragma unroll
         for (int v = 0; v < VEC; ++v) T[v] = 0.f;
         stop_next = 0;
@@ -267,8 +284,7 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int64_t grp, int3
         // the row opened last in this slice: add what later groups of this wavefront hold for it
 #pragma unroll
         for (int v = 0; v < VEC; ++v) acc[v] += T[v];
-        const int64_t knext = k0 + CHUNK;
-        const bool runs_on = !stop_next && knext < a.nnz && !(a.flags[(c + 1) * SUBS_PER_CHUNK] & 1u);
+        const bool runs_on = !stop_next && continued;
         const int64_t row = a.ne_rows ? a.ne_rows[q] : q;
         if (runs_on) store_vec<VEC>(a.Z + row * a.ldz + col0, acc);     // finished by k_spmm_fixup
         else epilogue_store<VEC, EPI>(a.Z + row * a.ldz + col0,
@@ -277,11 +293,250 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int64_t grp, int3
     }
 }
 
-template <int LPR, int VEC, int EPI>
+template <int LPR, int VEC, int EPI, int UNR>
 __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_split(SplitArgs a) {
     __shared__ int32_t s_col[WAVES_PER_BLOCK][LDS_PER_WAVE];
     __shared__ float s_val[WAVES_PER_BLOCK][LDS_PER_WAVE];
-    split_body<LPR, VEC, EPI>(a, blockIdx.x, s_col, s_val);
+    split_body<LPR, VEC, EPI, UNR>(a, blockIdx.x, s_col, s_val);
+}
+
+// The same product for matrices of few chunks, which is a chain of memory latencies, launches and first executions of
+// instructions that wait for each other.  A lane group fetches the 32 rows of X of a flag word at once, leaves them in LDS and
+// walks them there; in the walk the end of a row is only noted (some of the 16 groups of a wavefront have one at
+// nearly every step, and storing it there took longer than everything else), the rows are stored afterwards, one of every
+// group at a time.  A row that ends in the chunk after the one it starts in is finished here: a workgroup takes
+// three chunks, its fourth wavefront sums the head of the chunk behind them, and heads are passed to the wavefront before
+// through LDS; a fix-up launch follows only when a row covers a whole further chunk.  The sums are those of
+// k_spmm_split and k_spmm_fixup, term by term.  1000 rows of 17 entries at 16 columns: 9.7 + 3.9 -> 7.7 us.
+template <int LPR, int EPI>
+__global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_few(SplitArgs a) {
+    constexpr int VEC = 4;
+    constexpr int G = 64 / LPR, NW = SUBS_PER_CHUNK / G, OWN = WAVES_PER_BLOCK - 1;
+    extern __shared__ float4 s_x[];                             // [WAVES_PER_BLOCK][SUB][64]: entry e of every lane group
+    __shared__ int32_t s_col[WAVES_PER_BLOCK][LDS_PER_WAVE];
+    __shared__ float s_val[WAVES_PER_BLOCK][LDS_PER_WAVE];
+    __shared__ float s_head[WAVES_PER_BLOCK][LPR * VEC];        // sum of the entries before the chunk's first row start
+    __shared__ int s_starts[WAVES_PER_BLOCK];                   // whether the chunk has a row start at all
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int g = lane / LPR, li = lane % LPR;
+    const int64_t c = (int64_t)blockIdx.x * OWN + wave;
+    const bool active = c < a.nchunks, mine = active && wave < OWN;
+    int col0;
+    const bool col_ok = lane_columns<LPR, VEC>(a.f, blockIdx.y, gridDim.y, li, &col0);
+    const int64_t k0 = c * CHUNK, j0 = c * SUBS_PER_CHUNK + (int64_t)g * NW;
+    float acc[VEC] = {}, head[VEC] = {}, T[VEC] = {};
+    int32_t q = 0;
+    bool owned = false, runs_on = false;
+    if (active) {
+        // (flags is padded by a chunk of zero words)
+        const bool continued = k0 + CHUNK < a.nnz && !(a.flags[(c + 1) * SUBS_PER_CHUNK] & 1u);
+        uint32_t mask = a.flags[j0];
+        q = a.sub_row[j0];
+        int32_t* lc = s_col[wave];
+        float* lv = s_val[wave];
+#pragma unroll
+        for (int t = 0; t < CHUNK / 256; ++t) {
+            const int i = t * 256 + lane * 4;
+            const int64_t k = k0 + i;
+            int4 cc = make_int4(0, 0, 0, 0);
+            float4 vv = make_float4(1.f, 1.f, 1.f, 1.f);        // value-free: only the column stream is read
+            if (k + 4 <= a.nnz) {
+                cc = *reinterpret_cast<const int4*>(a.colidx + k);
+                if (a.val) vv = *reinterpret_cast<const float4*>(a.val + k);
+            } else {
+                if (k + 0 < a.nnz) { cc.x = a.colidx[k + 0]; if (a.val) vv.x = a.val[k + 0]; }
+                if (k + 1 < a.nnz) { cc.y = a.colidx[k + 1]; if (a.val) vv.y = a.val[k + 1]; }
+                if (k + 2 < a.nnz) { cc.z = a.colidx[k + 2]; if (a.val) vv.z = a.val[k + 2]; }
+            }
+            const int p = i + (i >> 5) * (SUB_STRIDE - SUB);
+            *reinterpret_cast<int4*>(lc + p) = cc;
+            *reinterpret_cast<float4*>(lv + p) = vv;
+        }
+        // each wavefront reads only what it wrote; LDS operations of one wavefront complete in order
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        q -= (int32_t)(mask & 1u);              // a start bit at the very first entry re-increments q
+        float4* const lx = s_x + wave * (SUB * 64) + lane;
+        const float* xbase = a.X + col0;
+        for (int w = 0; w < NW; ++w) {
+            if (w > 0) mask = a.flags[j0 + w];
+            const int64_t left = a.nnz - (j0 + w) * SUB;
+            const int cnt = left >= SUB ? SUB : (left > 0 ? (int)left : 0);
+            const int base = (g * NW + w) * SUB_STRIDE;
+            float x[SUB][VEC];
+#pragma unroll
+            for (int e = 0; e < SUB; ++e) load_vec<VEC>(x[e], xbase + (int64_t)lc[base + e] * a.ldx);   // past the end: row 0
+#pragma unroll
+            for (int e = 0; e < SUB; ++e)
+                lx[e * 64] = e < cnt ? make_float4(x[e][0], x[e][1], x[e][2], x[e][3]) : make_float4(0.f, 0.f, 0.f, 0.f);
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            // the walk: where an entry starts a row, the fragment before it takes the entry's place in LDS
+#pragma unroll 1
+            for (int b = 0; b < SUB; b += 8) {
+                float4 xe[8];
+                float v[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) { xe[e] = lx[(b + e) * 64]; v[e] = lv[base + b + e]; }
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    if (mask >> (b + e) & 1u) {
+                        lx[(b + e) * 64] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+                        acc[0] = acc[1] = acc[2] = acc[3] = 0.f;
+                    }
+                    acc[0] = fmaf(v[e], xe[e].x, acc[0]); acc[1] = fmaf(v[e], xe[e].y, acc[1]);
+                    acc[2] = fmaf(v[e], xe[e].z, acc[2]); acc[3] = fmaf(v[e], xe[e].w, acc[3]);
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            // the fragments: the first belongs to a row begun earlier, the others are whole rows
+            for (uint32_t m = mask; m; m &= m - 1) {
+                const float4 f4 = lx[(__ffs(m) - 1) * 64];
+                float frag[VEC] = {f4.x, f4.y, f4.z, f4.w};
+                if (!owned) {
+#pragma unroll
+                    for (int u = 0; u < VEC; ++u) head[u] = frag[u];
+                    owned = true;
+                } else if (col_ok && mine) {
+                    const int64_t row = a.ne_rows ? a.ne_rows[q] : q;
+                    epilogue_store<VEC, EPI>(a.Z + row * a.ldz + col0,
+                                             EPI == GCN_EPI_MASK ? a.Zprev + row * a.ldzprev + col0 : nullptr, frag,
+                                             a.row_scale ? a.row_scale[row] : 1.f, a.defer && a.defer[row]);
+                }
+                q += 1;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+        if (!owned) {                           // the whole slice lies inside one row
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) { head[v] = acc[v]; acc[v] = 0.f; }
+        }
+        // join fragments across groups: R_g = head_g + (owned_g ? 0 : R_{g+1}), left in head
+        int stop = owned ? 1 : 0;
+#pragma unroll
+        for (int d = 1; d < G; d <<= 1) {
+            float Rp[VEC];
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) Rp[v] = __shfl_down(head[v], d * LPR, 64);
+            const int sp = __shfl_down(stop, d * LPR, 64);
+            if (g + d < G && !stop) {
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) head[v] += Rp[v];
+                stop = sp;
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) T[v] = __shfl_down(head[v], LPR, 64);
+        int stop_next = __shfl_down(stop, LPR, 64);
+        if (g == G - 1) {
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) T[v] = 0.f;
+            stop_next = 0;
+        }
+        runs_on = !stop_next && continued;
+        if (g == 0) {
+            if (a.n_fix > 0 && col_ok && mine) store_vec<VEC>(a.carry + c * a.f + col0, head);
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) s_head[wave][li * VEC + v] = head[v];
+            if (li == 0) s_starts[wave] = stop;
+        }
+    }
+    __syncthreads();
+    if (owned && col_ok && mine) {
+        // the row opened last in this slice: add what later groups of this wavefront hold for it, then the next chunk
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) acc[v] += T[v];
+        if (runs_on && s_starts[wave + 1]) {
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) acc[v] += s_head[wave + 1][li * VEC + v];
+            runs_on = false;
+        }
+        const int64_t row = a.ne_rows ? a.ne_rows[q] : q;
+        if (runs_on) store_vec<VEC>(a.Z + row * a.ldz + col0, acc);     // finished by k_spmm_fixup
+        else epilogue_store<VEC, EPI>(a.Z + row * a.ldz + col0,
+                                      EPI == GCN_EPI_MASK ? a.Zprev + row * a.ldzprev + col0 : nullptr, acc,
+                                      a.row_scale ? a.row_scale[row] : 1.f, a.defer && a.defer[row]);
+    }
+}
+
+// Matrices of few rows, all of them short (SHORT_ROW entries at the most): a lane group takes a row, one wavefront per
+// workgroup so that a thousand rows spread over 63 compute units.  Nothing is staged or joined: the chain is row
+// pointer, indices, gathers (32 in flight), sums, store, and an empty row is simply a sum of nothing.  The sums are those
+// of the nonzero-split kernels, term by term: there a row is cut where a lane group's slice of SLICE entries or a chunk
+// ends, and with at most SHORT_ROW entries it has three pieces, F + (H1 + H2), or (F + H1) + H2 when H2 is in the
+// next chunk.  1000 rows of 17 entries at 16 columns: 6.3 us; k_spmm_few 7.7;
+// k_spmm_split 9.7 and k_spmm_fixup 3.9.
+static constexpr int SHORT_ROW = 64;
+
+template <int LPR, int EPI>
+__global__ __launch_bounds__(64) void k_spmm_short(SplitArgs a, int64_t nrows) {
+    constexpr int VEC = 4;
+    constexpr int SLICE = CHUNK / (64 / LPR);
+    static_assert(SHORT_ROW <= 2 * SLICE, "at most three pieces");
+    constexpr int U = 32, PER = U / LPR;                        // entries per round, loads of a lane per round
+    const int lane = threadIdx.x, li = lane % LPR;
+    const int64_t row = ((int64_t)blockIdx.x * 64 + lane) / LPR;
+    int col0;
+    const bool col_ok = lane_columns<LPR, VEC>(a.f, blockIdx.y, gridDim.y, li, &col0);
+    int64_t rs = 0;
+    int len = 0;
+    if (row < nrows) {
+        rs = a.rp[row];
+        len = (int)(a.rp[row + 1] - rs);
+    }
+    const int b1 = SLICE - (int)(rs & (SLICE - 1)), b2 = b1 + SLICE;       // where the second and the third piece begin
+    const bool third_apart = ((rs + b2) & (CHUNK - 1)) == 0;
+    float acc[VEC] = {}, first[VEC] = {}, second[VEC] = {};
+    const float* xbase = a.X + col0;
+    for (int base = 0; __any(base < len); base += U) {
+        int32_t c[PER];
+        float v[PER];
+#pragma unroll
+        for (int t = 0; t < PER; ++t) {
+            const int k = base + li + LPR * t;
+            c[t] = 0;
+            v[t] = 1.f;
+            if (k < len) {
+                c[t] = a.colidx[rs + k];
+                if (a.val) v[t] = a.val[rs + k];
+            }
+        }
+        float x[U][VEC];
+#pragma unroll
+        for (int e = 0; e < U; ++e) {
+            const int32_t col = __shfl(c[e / LPR], e % LPR, LPR);          // past the end: row 0, not used
+            load_vec<VEC>(x[e], xbase + (int64_t)col * a.ldx);
+        }
+#pragma unroll
+        for (int e = 0; e < U; ++e) {
+            const float ve = __shfl(v[e / LPR], e % LPR, LPR);
+            const int k = base + e;
+            if (k < len) {
+                if (k == b1) {
+#pragma unroll
+                    for (int u = 0; u < VEC; ++u) { first[u] = acc[u]; acc[u] = 0.f; }
+                }
+                if (k == b2) {
+#pragma unroll
+                    for (int u = 0; u < VEC; ++u) { second[u] = acc[u]; acc[u] = 0.f; }
+                }
+#pragma unroll
+                for (int u = 0; u < VEC; ++u) acc[u] = fmaf(ve, x[e][u], acc[u]);
+            }
+        }
+    }
+    if (row >= nrows || !col_ok) return;
+    if (len > b2) {
+#pragma unroll
+        for (int u = 0; u < VEC; ++u) acc[u] = third_apart ? (first[u] + second[u]) + acc[u] : first[u] + (second[u] + acc[u]);
+    } else if (len > b1) {
+#pragma unroll
+        for (int u = 0; u < VEC; ++u) acc[u] = first[u] + acc[u];
+    }
+    epilogue_store<VEC, EPI>(a.Z + row * a.ldz + col0, EPI == GCN_EPI_MASK ? a.Zprev + row * a.ldzprev + col0 : nullptr, acc,
+                             a.row_scale ? a.row_scale[row] : 1.f, a.defer && a.defer[row]);
 }
 
 // Two matrices in one launch: of every ra + rb consecutive workgroups the first ra work on `a` (with
@@ -294,43 +549,47 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_split_pair(SplitA
     __shared__ int32_t s_col[WAVES_PER_BLOCK][LDS_PER_WAVE];
     __shared__ float s_val[WAVES_PER_BLOCK][LDS_PER_WAVE];
     const unsigned q = blockIdx.x / 8, r = (blockIdx.x + q) % 8;
-    if ((int)r < ra) split_body<LPR, VEC, EPI>(a, (int64_t)q * ra + r, s_col, s_val);
-    else split_body<LPR, VEC, GCN_EPI_NONE>(b, (int64_t)q * rb + (r - ra), s_col, s_val);
+    if ((int)r < ra) split_body<LPR, VEC, EPI, 4>(a, (int64_t)q * ra + r, s_col, s_val);
+    else split_body<LPR, VEC, GCN_EPI_NONE, 4>(b, (int64_t)q * rb + (r - ra), s_col, s_val);
 }
 
-// Adds, in ascending chunk order, the carries of the chunks a row runs on into, then applies the
-// epilogue.  One LPR-lane group per chunk; only the first continuation chunk of a row acts.
+// Adds, in ascending chunk order, the carries of the chunks a row runs on into, then applies the epilogue.  One LPR-lane
+// group per such row; its record (x, y: the first and the last chunk it runs on into, z: the row) was worked out when
+// the schedule was built, so that the carries and the row's sum so far are fetched right away.  A row of 60 K entries
+// has 120 carries: eight are in flight at a time, the additions stay in order.
 template <int LPR, int VEC, int EPI>
 __global__ __launch_bounds__(256) void k_spmm_fixup(SplitArgs a) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int li = (int)(t % LPR);
-    int64_t c = t / LPR + 1;                    // chunk 0 starts a row by definition
-    if (a.n_fix >= 0) {                         // only the listed chunks have work
-        if (t / LPR >= a.n_fix) return;
-        c = a.fix_list[t / LPR];
-    }
-    if (c >= a.nchunks) return;
+    if (t / LPR >= a.n_fix) return;
     const int col0 = blockIdx.y * (LPR * VEC) + li * VEC;
     if (col0 >= a.f) return;
-    const int64_t j0 = c * SUBS_PER_CHUNK;
-    if (a.flags[j0] & 1u) return;               // the chunk starts on a row start: no carry-in
-    const int32_t q = a.sub_row[j0];
-    const int64_t rs = a.rp[q], re = a.rp[q + 1];
-    if (c != rs / CHUNK + 1) return;            // an earlier chunk leads this row
-    const int64_t c_last = (re - 1) / CHUNK;
-    float sum[VEC];
+    const int4 rec = a.fix_list[t / LPR];
+    const int64_t row = a.ne_rows ? a.ne_rows[rec.z] : rec.z;
+    float* z = a.Z + row * a.ldz + col0;
+    float cur[VEC], sum[VEC];
+    load_vec<VEC>(cur, z);
 #pragma unroll
     for (int v = 0; v < VEC; ++v) sum[v] = 0.f;
-    for (int64_t cc = c; cc <= c_last; ++cc) {
-        float part[VEC];
-        load_vec<VEC>(part, a.carry + cc * a.f + col0);
+    const float* part = a.carry + (int64_t)rec.x * a.f + col0;
+    int left = rec.y - rec.x + 1;
+    for (; left >= 8; left -= 8) {
+        float x[8][VEC];
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) sum[v] += part[v];
+        for (int e = 0; e < 8; ++e) load_vec<VEC>(x[e], part + (int64_t)e * a.f);
+        part += (int64_t)8 * a.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) sum[v] += x[e][v];
     }
-    const int64_t row = a.ne_rows ? a.ne_rows[q] : q;
-    float* z = a.Z + row * a.ldz + col0;
-    float cur[VEC];
-    load_vec<VEC>(cur, z);
+    for (; left > 0; --left) {
+        float x[VEC];
+        load_vec<VEC>(x, part);
+        part += a.f;
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) sum[v] += x[v];
+    }
 #pragma unroll
     for (int v = 0; v < VEC; ++v) cur[v] += sum[v];
     epilogue_store<VEC, EPI>(z, EPI == GCN_EPI_MASK ? a.Zprev + row * a.ldzprev + col0 : nullptr, cur,
@@ -347,12 +606,20 @@ __global__ void k_zero_empty_rows(int64_t n, const int64_t* __restrict__ rowptr,
     if (rowptr[i + 1] == rowptr[i]) Z[i * ldz + j] = 0.f;
 }
 
-// The same from the list of empty rows that the schedule keeps (only their elements are touched).
-__global__ void k_zero_listed_rows(int64_t count, const int32_t* __restrict__ rows, int32_t f, float* __restrict__ Z,
-                                   int64_t ldz) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t q = t / f;
-    if (q < count) Z[(int64_t)rows[q] * ldz + (int)(t % f)] = 0.f;
+// The same from the list of empty rows that the schedule keeps (only their elements are touched): `lanes` lanes of 16
+// bytes per row, the last one repeating columns where f is no multiple of 4; VEC = 1 below four columns.
+template <int VEC>
+__global__ __launch_bounds__(256) void k_zero_listed_rows(int64_t count, uint32_t lanes, const int32_t* __restrict__ rows, int32_t f,
+                                                          float* __restrict__ Z, int64_t ldz) {
+    const uint32_t per = 256 / lanes;                    // rows per workgroup and step (lanes <= 256)
+    const uint32_t r = threadIdx.x / lanes, li = threadIdx.x % lanes;
+    if (r >= per) return;
+    const int step = (int)lanes * VEC;
+    const float zero[VEC] = {};
+    for (int64_t q = (int64_t)blockIdx.x * per + r; q < count; q += (int64_t)gridDim.x * per) {
+        float* z = Z + (int64_t)rows[q] * ldz;
+        for (int c = (int)li * VEC; c < f; c += step) store_vec<VEC>(z + (c + VEC <= f ? c : f - VEC), zero);
+    }
 }
 
 // Reference-shaped kernel: one thread per output element walks its row.  Kept as a selectable
@@ -389,28 +656,91 @@ static size_t occupancy_pad(int lpr, int lds_kb) {
 }
 
 template <int LPR, int VEC>
-static int launch_split(const SplitArgs& args, int epilogue, hipStream_t s) {
+static int launch_fixup(const SplitArgs& args, int epilogue, hipStream_t s) {
+    if (args.n_fix == 0) return GCN_OK;
+    const dim3 grid((unsigned)((args.n_fix * LPR + 255) / 256), (unsigned)((args.f + LPR * VEC - 1) / (LPR * VEC)));
+    switch (epilogue) {
+        case GCN_EPI_NONE: hipLaunchKernelGGL((k_spmm_fixup<LPR, VEC, GCN_EPI_NONE>), grid, dim3(256), 0, s, args); break;
+        case GCN_EPI_RELU: hipLaunchKernelGGL((k_spmm_fixup<LPR, VEC, GCN_EPI_RELU>), grid, dim3(256), 0, s, args); break;
+        default: hipLaunchKernelGGL((k_spmm_fixup<LPR, VEC, GCN_EPI_MASK>), grid, dim3(256), 0, s, args); break;
+    }
+    GCN_LAUNCH_CHECK();
+    return GCN_OK;
+}
+
+template <int LPR, int VEC, int UNR>
+static int launch_split_unr(const SplitArgs& args, int epilogue, hipStream_t s) {
     const int tile = LPR * VEC;
-    const unsigned ytiles = (unsigned)((args.f + tile - 1) / tile);
-    const dim3 grid((unsigned)((args.nchunks + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK), ytiles);
-    const int64_t fix_threads = (args.n_fix >= 0 ? args.n_fix : args.nchunks - 1) * LPR;
-    const dim3 fgrid((unsigned)((fix_threads + 255) / 256), ytiles);
+    const dim3 grid((unsigned)((args.nchunks + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK), (unsigned)((args.f + tile - 1) / tile));
+    const dim3 block(64 * WAVES_PER_BLOCK);
+    const size_t pad = occupancy_pad(LPR, args.lds_kb);
     timing_begin(s);
     switch (epilogue) {
-        case GCN_EPI_NONE: hipLaunchKernelGGL((k_spmm_split<LPR, VEC, GCN_EPI_NONE>), grid, dim3(64 * WAVES_PER_BLOCK), occupancy_pad(LPR, args.lds_kb), s, args); break;
-        case GCN_EPI_RELU: hipLaunchKernelGGL((k_spmm_split<LPR, VEC, GCN_EPI_RELU>), grid, dim3(64 * WAVES_PER_BLOCK), occupancy_pad(LPR, args.lds_kb), s, args); break;
-        default: hipLaunchKernelGGL((k_spmm_split<LPR, VEC, GCN_EPI_MASK>), grid, dim3(64 * WAVES_PER_BLOCK), occupancy_pad(LPR, args.lds_kb), s, args); break;
+        case GCN_EPI_NONE: hipLaunchKernelGGL((k_spmm_split<LPR, VEC, GCN_EPI_NONE, UNR>), grid, block, pad, s, args); break;
+        case GCN_EPI_RELU: hipLaunchKernelGGL((k_spmm_split<LPR, VEC, GCN_EPI_RELU, UNR>), grid, block, pad, s, args); break;
+        default: hipLaunchKernelGGL((k_spmm_split<LPR, VEC, GCN_EPI_MASK, UNR>), grid, block, pad, s, args); break;
     }
     timing_end(s);
     GCN_LAUNCH_CHECK();
-    if (fix_threads > 0) {
-        switch (epilogue) {
-            case GCN_EPI_NONE: hipLaunchKernelGGL((k_spmm_fixup<LPR, VEC, GCN_EPI_NONE>), fgrid, dim3(256), 0, s, args); break;
-            case GCN_EPI_RELU: hipLaunchKernelGGL((k_spmm_fixup<LPR, VEC, GCN_EPI_RELU>), fgrid, dim3(256), 0, s, args); break;
-            default: hipLaunchKernelGGL((k_spmm_fixup<LPR, VEC, GCN_EPI_MASK>), fgrid, dim3(256), 0, s, args); break;
+    return GCN_OK;
+}
+
+template <int LPR, int VEC>
+static int launch_split(const SplitArgs& args, int epilogue, hipStream_t s) {
+    const int64_t panels = (args.f + LPR * VEC - 1) / (LPR * VEC), waves = args.nchunks * panels;
+    if constexpr (VEC == 4) {
+        // as long as the workgroups of three chunks run side by side (their LDS allows one per compute unit)
+        if (waves <= (int64_t)device_info().cus * (WAVES_PER_BLOCK - 1)) {
+            const dim3 grid((unsigned)((args.nchunks + WAVES_PER_BLOCK - 2) / (WAVES_PER_BLOCK - 1)), (unsigned)panels);
+            constexpr size_t lds = WAVES_PER_BLOCK * SUB * 64 * sizeof(float4);
+            SplitArgs few = args;
+            few.n_fix = args.n_fix_long;                  // they come first in the list
+            timing_begin(s);
+            switch (epilogue) {
+                case GCN_EPI_NONE: launch_lds<k_spmm_few<LPR, GCN_EPI_NONE>>(grid, 64 * WAVES_PER_BLOCK, lds, s, few); break;
+                case GCN_EPI_RELU: launch_lds<k_spmm_few<LPR, GCN_EPI_RELU>>(grid, 64 * WAVES_PER_BLOCK, lds, s, few); break;
+                default: launch_lds<k_spmm_few<LPR, GCN_EPI_MASK>>(grid, 64 * WAVES_PER_BLOCK, lds, s, few); break;
+            }
+            timing_end(s);
+            GCN_LAUNCH_CHECK();
+            if (few.f % 4 != 0) return launch_fixup<16, 1>(few, epilogue, s);
+            return launch_fixup<LPR, VEC>(few, epilogue, s);
         }
-        GCN_LAUNCH_CHECK();
     }
+    // Few wavefronts (less than four per SIMD) cannot hide the gathers' latency behind each other: there every lane group
+    // keeps 16 gathers in flight instead of 4.
+    if (waves < (int64_t)device_info().cus * 16) GCN_TRY((launch_split_unr<LPR, VEC, 16>(args, epilogue, s)));
+    else GCN_TRY((launch_split_unr<LPR, VEC, 4>(args, epilogue, s)));
+    // the fix-up reads and writes rows of Z: no column may belong to two lanes there
+    if (VEC == 4 && args.f % 4 != 0) return launch_fixup<16, 1>(args, epilogue, s);
+    return launch_fixup<LPR, VEC>(args, epilogue, s);
+}
+
+// Whether a matrix goes through k_spmm_short: its rows are all short, and all wavefronts are resident at once (eight per
+// compute unit at this kernel's registers).  With more rows the even chunks of k_spmm_split win (rows of 21 entries at 16
+// columns: 20 K rows 9.7 against 11.0 us, 50 K rows 17.7 against 14.2).
+static bool short_rows(const Matrix& m, int32_t f) {
+    const int lpr = f <= 16 ? 4 : 8;
+    return f >= 4 && m.max_degree <= SHORT_ROW && m.nrows * lpr * ((f + 4 * lpr - 1) / (4 * lpr)) <= (int64_t)device_info().cus * 8 * 64;
+}
+
+static int launch_short(const SplitArgs& args, int64_t nrows, int epilogue, hipStream_t s) {
+    auto go = [&](auto lpr) {
+        constexpr int LPR = decltype(lpr)::value;
+        const dim3 grid((unsigned)((nrows * LPR + 63) / 64), (unsigned)((args.f + 4 * LPR - 1) / (4 * LPR)));
+        switch (epilogue) {
+            case GCN_EPI_NONE: hipLaunchKernelGGL((k_spmm_short<LPR, GCN_EPI_NONE>), grid, dim3(64), 0, s, args, nrows); break;
+            case GCN_EPI_RELU: hipLaunchKernelGGL((k_spmm_short<LPR, GCN_EPI_RELU>), grid, dim3(64), 0, s, args, nrows); break;
+            default: hipLaunchKernelGGL((k_spmm_short<LPR, GCN_EPI_MASK>), grid, dim3(64), 0, s, args, nrows); break;
+        }
+    };
+    timing_begin(s);
+    // the lane layout of run_split: the pieces of a row follow from it
+    if (args.f <= 16) go(std::integral_constant<int, 4>());
+    else if (args.f > 32 && args.f % 4 != 0) go(std::integral_constant<int, 16>());
+    else go(std::integral_constant<int, 8>());
+    timing_end(s);
+    GCN_LAUNCH_CHECK();
     return GCN_OK;
 }
 
@@ -425,8 +755,9 @@ __global__ __launch_bounds__(256) void k_block_reduce(int64_t n, int32_t f, int3
                                                       int64_t ldzprev, int accumulate) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t i = t / lanes;
-    const int col0 = (int)(t % lanes) * VEC;
+    int col0 = (int)(t % lanes) * VEC;
     if (i >= n) return;
+    if (col0 + VEC > f) col0 = f - VEC;              // the last lane of a ragged width repeats columns (accumulate: f % VEC == 0)
     const int64_t row = row_map ? row_map[i] : i;    // a row-subset matrix writes only its own rows
     float acc[VEC];
 #pragma unroll
@@ -446,7 +777,7 @@ template <int VEC>
 static int launch_block_reduce(int64_t n, int32_t f, const Blocked& b, const int32_t* row_map, const float* row_scale,
                                int accumulate, const float* P, float* Z,
                                int64_t ldz, int epilogue, const float* Zprev, int64_t ldzprev, hipStream_t s) {
-    const int lanes = f / VEC;
+    const int lanes = (f + VEC - 1) / VEC;
     const int64_t threads = n * lanes;
     const dim3 grid((unsigned)((threads + 255) / 256));
     switch (epilogue) {
@@ -610,28 +941,22 @@ static int launch_sweep(const SweepArgs& args, int64_t ntasks, int sweep_waves, 
 }
 
 // Chooses the lane layout for one nonzero-split product and launches it.
-static int run_split(const SplitArgs& args, int epilogue, hipStream_t s, bool l2_resident = false) {
+static int run_split(const SplitArgs& args, int epilogue, hipStream_t s, int64_t xrows, bool l2_resident = false) {
     const int32_t f = args.f;
-    const bool vec4 = (f % 4 == 0) && (args.ldx % 4 == 0) && (args.ldz % 4 == 0) && aligned16(args.X) && aligned16(args.Z) &&
-                      (epilogue != GCN_EPI_MASK || ((args.ldzprev % 4 == 0) && aligned16(args.Zprev)));
-    if (vec4) {
-        // Wider operands are processed in panels of 32 columns (one 128-byte line per gathered row):
-        // the panel of X that the gathers touch is 4x smaller than at f = 128, so far more of it stays
-        // in L2, at the price of re-reading the index/value stream once per panel.
-        // When the gathers are served by the L2 anyway (column-blocked copy) panels of 64 are better: half
-        // the passes over the index/value stream and half the requests (config 3 at f = 128: 3.55 -> 3.27 ms;
-        // config 2, bound by line fills: 1.46 -> 1.69 ms, so not there).
-        if (f >= 64 && l2_resident) return launch_split<16, 4>(args, epilogue, s);
-        if (f > 32) return launch_split<8, 4>(args, epilogue, s);
-        const int lanes = f / 4;
-        if (lanes <= 4) return launch_split<4, 4>(args, epilogue, s);
-        return launch_split<8, 4>(args, epilogue, s);
-    }
-    if (f <= 4) return launch_split<4, 1>(args, epilogue, s);
-    if (f <= 8) return launch_split<8, 1>(args, epilogue, s);
-    if (f <= 16) return launch_split<16, 1>(args, epilogue, s);
-    if (f <= 32) return launch_split<32, 1>(args, epilogue, s);
-    return launch_split<64, 1>(args, epilogue, s);
+    if (f < 4) return launch_split<4, 1>(args, epilogue, s);
+    if (f <= 16) return launch_split<4, 4>(args, epilogue, s);
+    if (f <= 32) return launch_split<8, 4>(args, epilogue, s);
+    // Wider operands are processed in panels of 32 columns (one 128-byte line per gathered row): the panel of X that the
+    // gathers touch is 4x smaller than at f = 128, so far more of it stays in L2, at the price of re-reading the
+    // index/value stream once per panel.
+    // When the gathers are served by the L2 anyway (column-blocked copy) panels of 64 are better: half the passes over
+    // the index/value stream and half the requests (config 3 at f = 128: 3.55 -> 3.27 ms; config 2, bound by line
+    // fills: 1.46 -> 1.69 ms, so not there).  Rows that are not whole 16-byte pieces straddle lines
+    // wherever they are cut: one panel up to 64 columns (41 columns, 1 M rows: 1.20 ms in two panels, 0.89 in one), more
+    // of them while the operand stays within the last-level cache.
+        const bool ragged = f % 4 != 0 && (f <= 64 || xrows * f * 4 <= (128ll << 20));
+    if ((f >= 64 && l2_resident) || ragged) return launch_split<16, 4>(args, epilogue, s);
+    return launch_split<8, 4>(args, epilogue, s);
 }
 
 // How many column blocks to cut X into so that one block of the gathered panel stays in one L2
@@ -652,6 +977,23 @@ static int64_t choose_blocks(const Config& cfg, int64_t nrows, int64_t ncols, in
     const int64_t cap = (nnz / (nrows > 0 ? nrows : 1)) / per_block;
     if (want <= cap) return want;
     return (cap >= 2 && 4 * cap >= want) ? cap : 1;
+}
+
+static int zero_empty_rows(const Matrix& m, int32_t f, float* Z, int64_t ldz, hipStream_t s) {
+    const int64_t n_empty = m.nrows - m.n_ne;
+    if (m.empty_rows && n_empty > 0) {
+        const int vec = f >= 4 ? 4 : 1;
+        const int lanes = (f + vec - 1) / vec < 256 ? (f + vec - 1) / vec : 256;
+        const int64_t per = 256 / lanes, want = (n_empty + per - 1) / per;
+        const dim3 grid((unsigned)(want < 16384 ? want : 16384));
+        if (vec == 4) hipLaunchKernelGGL(k_zero_listed_rows<4>, grid, dim3(256), 0, s, n_empty, (uint32_t)lanes, m.empty_rows, f, Z, ldz);
+        else hipLaunchKernelGGL(k_zero_listed_rows<1>, grid, dim3(256), 0, s, n_empty, (uint32_t)lanes, m.empty_rows, f, Z, ldz);
+    } else {
+        const int64_t work = m.nrows * f;
+        hipLaunchKernelGGL(k_zero_empty_rows, dim3((unsigned)((work + 255) / 256)), dim3(256), 0, s, m.nrows, m.rowptr, f, Z, ldz);
+    }
+    GCN_LAUNCH_CHECK();
+    return GCN_OK;
 }
 
 // The nonzero-split product of one stored matrix -- the whole matrix, or the heavy rows of a sweep
@@ -684,12 +1026,10 @@ static int run_matrix(gcn_csr* a, Matrix& mm, const int32_t* row_map, int64_t nn
         if (o.dry) return GCN_OK;
         args.colidx = b.colidx; args.val = o.pattern ? nullptr : b.val; args.flags = b.flags; args.sub_row = b.sub_row;
         args.ne_rows = nullptr; args.rp = b.rp; args.row_scale = nullptr;     // the scale belongs to the reduced row
-        args.fix_list = b.fix_list; args.n_fix = b.n_fix;
+        args.fix_list = b.fix_list; args.n_fix = b.n_fix; args.n_fix_long = b.n_fix_long;
         args.Z = a->partial; args.ldz = f; args.Zprev = nullptr; args.ldzprev = 0;
-        GCN_TRY(run_split(args, GCN_EPI_NONE, s, true));
-        const bool vec4 = (f % 4 == 0) && (ldz % 4 == 0) && aligned16(Z) &&
-                          (epilogue != GCN_EPI_MASK || ((ldzprev % 4 == 0) && aligned16(Zprev)));
-        if (vec4) return launch_block_reduce<4>(mm.nrows, f, b, row_map, o.row_scale, o.accumulate ? 1 : 0, a->partial, Z, ldz, epilogue, Zprev, ldzprev, s);
+        GCN_TRY(run_split(args, GCN_EPI_NONE, s, mm.ncols, true));
+        if (f >= 4) return launch_block_reduce<4>(mm.nrows, f, b, row_map, o.row_scale, o.accumulate ? 1 : 0, a->partial, Z, ldz, epilogue, Zprev, ldzprev, s);
         return launch_block_reduce<1>(mm.nrows, f, b, row_map, o.row_scale, o.accumulate ? 1 : 0, a->partial, Z, ldz, epilogue, Zprev, ldzprev, s);
     }
     if (o.describe) {
@@ -703,22 +1043,14 @@ static int run_matrix(gcn_csr* a, Matrix& mm, const int32_t* row_map, int64_t nn
     args.defer = o.defer;
     args.ne_rows = row_map ? row_map : mm.ne_rows;
     args.rp = mm.ne_rowptr ? mm.ne_rowptr : mm.rowptr;
-    args.fix_list = mm.fix_list; args.n_fix = mm.n_fix;
+    args.fix_list = mm.fix_list; args.n_fix = mm.n_fix; args.n_fix_long = mm.n_fix_long;
     args.Z = Z; args.ldz = ldz; args.Zprev = Zprev; args.ldzprev = ldzprev;
-    return run_split(args, epilogue, s);
-}
-
-static int zero_empty_rows(const Matrix& m, int32_t f, float* Z, int64_t ldz, hipStream_t s) {
-    const int64_t n_empty = m.nrows - m.n_ne;
-    if (m.empty_rows && n_empty > 0) {
-        const int64_t work = n_empty * f;
-        hipLaunchKernelGGL(k_zero_listed_rows, dim3((unsigned)((work + 255) / 256)), dim3(256), 0, s, n_empty, m.empty_rows, f, Z, ldz);
-    } else {
-        const int64_t work = m.nrows * f;
-        hipLaunchKernelGGL(k_zero_empty_rows, dim3((unsigned)((work + 255) / 256)), dim3(256), 0, s, m.nrows, m.rowptr, f, Z, ldz);
+    if (!row_map && short_rows(mm, f)) {
+        args.rp = mm.rowptr;
+        return launch_short(args, mm.nrows, epilogue, s);
     }
-    GCN_LAUNCH_CHECK();
-    return GCN_OK;
+    if (!row_map && mm.n_ne < mm.nrows) GCN_TRY(zero_empty_rows(mm, f, Z, ldz, s));
+    return run_split(args, epilogue, s, mm.ncols);
 }
 
 // ---- hub schedule -----------------------------------------------------------------------------------------
@@ -765,21 +1097,8 @@ static int launch_pair(const SplitArgs& ra_args, const SplitArgs& rb_args, int e
     }
     timing_end(s);
     GCN_LAUNCH_CHECK();
-    const SplitArgs* both[2] = {&ra_args, &rb_args};
-    for (int k = 0; k < 2; ++k) {
-        const SplitArgs& args = *both[k];
-        const int64_t fix_threads = (args.n_fix >= 0 ? args.n_fix : args.nchunks - 1) * LPR;
-        if (fix_threads <= 0) continue;
-        const dim3 fgrid((unsigned)((fix_threads + 255) / 256), ytiles);
-        const int epi = k == 0 ? epilogue : GCN_EPI_NONE;
-        switch (epi) {
-            case GCN_EPI_NONE: hipLaunchKernelGGL((k_spmm_fixup<LPR, 4, GCN_EPI_NONE>), fgrid, dim3(256), 0, s, args); break;
-            case GCN_EPI_RELU: hipLaunchKernelGGL((k_spmm_fixup<LPR, 4, GCN_EPI_RELU>), fgrid, dim3(256), 0, s, args); break;
-            default: hipLaunchKernelGGL((k_spmm_fixup<LPR, 4, GCN_EPI_MASK>), fgrid, dim3(256), 0, s, args); break;
-        }
-        GCN_LAUNCH_CHECK();
-    }
-    return GCN_OK;
+    GCN_TRY((launch_fixup<LPR, 4>(ra_args, epilogue, s)));
+    return launch_fixup<LPR, 4>(rb_args, GCN_EPI_NONE, s);
 }
 
 // Z = A_rest X (long rows stored raw) and the partial rows of A_hot X_hot in one paired launch, then
@@ -814,14 +1133,14 @@ static int run_hub(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx
     ar.colidx = rest.colidx; ar.val = o.pattern ? nullptr : rest.val; ar.flags = rest.flags; ar.sub_row = rest.sub_row;
     ar.row_scale = o.row_scale; ar.defer = h.defer;
     ar.ne_rows = rest.ne_rows; ar.rp = rest.ne_rowptr ? rest.ne_rowptr : rest.rowptr;
-    ar.fix_list = rest.fix_list; ar.n_fix = rest.n_fix;
+    ar.fix_list = rest.fix_list; ar.n_fix = rest.n_fix; ar.n_fix_long = rest.n_fix_long;
     ar.nnz = h.nnz_rest; ar.nsub = rest.nsub; ar.nchunks = rest.nchunks; ar.f = f;
     ar.X = X; ar.ldx = ldx; ar.Z = Z; ar.ldz = ldz; ar.Zprev = Zprev; ar.ldzprev = ldzprev; ar.carry = a->carry;
     SplitArgs ah;                                  // A_hot over the packed rows, into the partial rows
     ah.lds_kb = ar.lds_kb;
     ah.colidx = b.colidx; ah.val = o.pattern ? nullptr : b.val; ah.flags = b.flags; ah.sub_row = b.sub_row;
     ah.row_scale = nullptr; ah.defer = nullptr; ah.ne_rows = nullptr; ah.rp = b.rp;
-    ah.fix_list = b.fix_list; ah.n_fix = b.n_fix;
+    ah.fix_list = b.fix_list; ah.n_fix = b.n_fix; ah.n_fix_long = b.n_fix_long;
     ah.nnz = h.nnz_hot; ah.nsub = hot.nsub; ah.nchunks = hot.nchunks; ah.f = f;
     ah.X = h.xhot; ah.ldx = f; ah.Z = a->partial; ah.ldz = f; ah.Zprev = nullptr; ah.ldzprev = 0; ah.carry = a->carry2;
     if (f > 16) GCN_TRY(launch_pair<8>(ar, ah, epilogue, s));
@@ -1001,7 +1320,6 @@ int spmm_launch(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx, f
         return GCN_OK;
     }
     took(a, nblocks >= 2 ? GCN_SCHED_BLOCKED : GCN_SCHED_SPLIT);
-    if (!o.dry && nblocks < 2 && m.n_ne < n) GCN_TRY(zero_empty_rows(m, f, Z, ldz, s));
     return run_matrix(a, m, nullptr, nnz, nblocks, f, X, ldx, Z, ldz, epilogue, Zprev, ldzprev, o, s);
 }
 
@@ -1117,8 +1435,7 @@ extern "C" int gcn_spmm_static(gcn_csr* a, int trans, int32_t f, const float* X,
         return fail(GCN_ERR_WORKSPACE, "gcn_spmm_static: needs %zu bytes of scratch (%lld stored entries / 512, rounded up, x %d floats), the fixed "
                     "array holds %zu; use gcn_spmm", need, (long long)a->nnz, (int)f, STATIC_SCRATCH_BYTES);
     hipStream_t s = (hipStream_t)stream;
-    if (a->nnz == 0 || m.n_ne < m.nrows) GCN_TRY(zero_empty_rows(m, f, Z, ldz, s));
-    if (a->nnz == 0) return GCN_OK;
+    if (a->nnz == 0) return zero_empty_rows(m, f, Z, ldz, s);
     float* carry = nullptr;
     GCN_TRY(static_scratch(&carry));
     took(a, GCN_SCHED_SPLIT);

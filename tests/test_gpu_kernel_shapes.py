@@ -151,3 +151,65 @@ def test_matrices_of_changing_size_reuse_memory_safely():
             a.close()
             assert_close(host(Z), oracle.spmm(A, X), f"matrix {k}")
     g.gcn_scratch_release()
+
+
+def _rows_matrix(lengths, ncols, seed):
+    """A rectangular matrix with the given row lengths (0 allowed), random ascending columns and values."""
+    rs = np.random.default_rng(seed)
+    rowptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    col = [np.sort(rs.choice(ncols, k, replace=False)) for k in lengths if k]
+    colidx = (np.concatenate(col) if col else np.zeros(0)).astype(np.int32)
+    return rowptr, colidx, rs.standard_normal(colidx.size).astype(np.float32)
+
+
+@pytest.mark.parametrize("f", [1, 3, 4, 5, 7, 16, 17, 31, 33, 41, 64, 65, 66, 67, 130])
+@pytest.mark.parametrize("shape", ["ends_on_chunk", "crosses_one", "covers_chunks", "mixed", "one_row"])
+def test_spmm_rows_across_chunks_any_width(f, shape):
+    """Rows that end on, cross or cover the 512-entry chunks of the nonzero-split kernels (also in the last, short chunk),
+    at widths that are no multiple of a lane's 16 bytes; operands with a pitch; every epilogue."""
+    g = G()
+    lengths = {"ends_on_chunk": [512, 256, 256, 100, 412, 512, 3], "crosses_one": [300] * 12 + [1, 0, 511, 2],
+               "covers_chunks": [5, 1600, 3, 512, 1024, 509, 1000], "mixed": [0, 1, 700, 0, 31, 32, 33, 1500, 20, 0, 64, 0],
+               "one_row": [1700]}[shape]
+    n, nc = len(lengths), 2000
+    rowptr, colidx, val = _rows_matrix(lengths, nc, 80)
+    a = g.gcn_csr_create_from_csr_rect(n, nc, dev(rowptr), dev(colidx), dev(val), g.BUILD_TRANSPOSE)
+    A = np.zeros((n, nc))
+    for i in range(n):
+        A[i, colidx[rowptr[i]:rowptr[i + 1]]] = val[rowptr[i]:rowptr[i + 1]]
+    X = synth.normal_features(nc, f, 81)
+    Zp = synth.normal_features(n, f, 82)
+    Xd = dev(np.concatenate([X, np.full((nc, 3), np.nan, np.float32)], 1))[:, :f]
+    want = A @ X.astype(np.float64)
+    for epi, ref in ((g.EPI_NONE, want), (g.EPI_RELU, np.maximum(want, 0)), (g.EPI_MASK, np.where(Zp > 0, want, 0))):
+        Zd = torch.full((n, f + 5), float("nan"), device="cuda")
+        g.gcn_spmm(a, 0, Xd, Zd[:, :f], epi, dev(Zp) if epi == g.EPI_MASK else None)
+        assert_close(host(Zd)[:, :f], ref, f"{shape} f={f} epilogue {epi}")
+        assert np.all(np.isnan(host(Zd)[:, f:]))
+    Xt = synth.normal_features(n, f, 83)
+    Zt = torch.full((nc, f), float("nan"), device="cuda")
+    g.gcn_spmm(a, 1, dev(Xt), Zt)                                   # mostly empty and one-entry rows
+    assert_close(host(Zt), A.T @ Xt.astype(np.float64), f"{shape} transposed f={f}")
+    a.close()
+
+
+@pytest.mark.parametrize("f", [16, 41, 64])
+def test_spmm_few_chunks_and_many_chunks_add_alike(f):
+    """The kernel for matrices of few chunks, the one for more and the one for many keep every row's order of additions:
+    the first rows of a matrix give the same bits whichever kernel runs."""
+    g = G()
+    rs = np.random.default_rng(84)
+    lengths = np.concatenate([rs.integers(0, 90, 3000), [2000, 700], rs.integers(0, 30, 1000)])
+    X = synth.normal_features(5000, f, 85)
+    rowptr, colidx, val = _rows_matrix(lengths, 5000, 86)
+    first = None
+    for repeat in (1, 12, 40):                                      # the same rows again and again behind themselves
+        rp = np.concatenate([[0]] + [rowptr[1:] + k * rowptr[-1] for k in range(repeat)])
+        a = g.gcn_csr_create_from_csr_rect(rp.size - 1, 5000, dev(rp), dev(np.tile(colidx, repeat)), dev(np.tile(val, repeat)), 0)
+        g.gcn_csr_config(a, g.CFG_SPMM_BLOCKS, 1)
+        Z = torch.empty(rp.size - 1, f, device="cuda")
+        g.gcn_spmm(a, 0, dev(X), Z)
+        got = host(Z)[:4000].view(np.uint32)
+        first = got if first is None else first
+        assert np.array_equal(got, first), repeat
+        a.close()
