@@ -261,8 +261,8 @@ struct PhaseTimer {
 
 // Launches a kernel with dynamic LDS.  More than 64 KB per workgroup (static part included) has to be asked for, once
 // per kernel, device and size (two threads may both ask, which is harmless).
-template <auto Kernel, typename Args>
-void launch_lds(dim3 grid, int threads, size_t lds, hipStream_t s, const Args& args) {
+template <auto Kernel, typename... Args>
+void launch_lds(dim3 grid, int threads, size_t lds, hipStream_t s, const Args&... args) {
     if (lds > 44 * 1024) {
         static std::atomic<size_t> asked[64];
         int dev = 0;
@@ -272,7 +272,7 @@ void launch_lds(dim3 grid, int threads, size_t lds, hipStream_t s, const Args& a
             asked[dev & 63].store(lds, std::memory_order_relaxed);
         }
     }
-    hipLaunchKernelGGL(Kernel, grid, dim3(threads), lds, s, args);
+    hipLaunchKernelGGL(Kernel, grid, dim3(threads), lds, s, args...);
 }
 
 int build_schedule(Matrix& m, int64_t n, int64_t nnz, hipStream_t s);

@@ -470,10 +470,9 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_few(SplitArgs a) 
 // k_spmm_split 9.7 and k_spmm_fixup 3.9.
 static constexpr int SHORT_ROW = 64;
 
-template <int LPR, int EPI>
+template <int LPR, int SLICE, int EPI>
 __global__ __launch_bounds__(64) void k_spmm_short(SplitArgs a, int64_t nrows) {
     constexpr int VEC = 4;
-    constexpr int SLICE = CHUNK / (64 / LPR);
     static_assert(SHORT_ROW <= 2 * SLICE, "at most three pieces");
     constexpr int U = 32, PER = U / LPR;                        // entries per round, loads of a lane per round
     const int lane = threadIdx.x, li = lane % LPR;
@@ -537,6 +536,260 @@ __global__ __launch_bounds__(64) void k_spmm_short(SplitArgs a, int64_t nrows) {
     }
     epilogue_store<VEC, EPI>(a.Z + row * a.ldz + col0, EPI == GCN_EPI_MASK ? a.Zprev + row * a.ldzprev + col0 : nullptr, acc,
                              a.row_scale ? a.row_scale[row] : 1.f, a.defer && a.defer[row]);
+}
+
+// Widths above 32 that are no multiple of four.  They used to run with one float per lane, a wavefront adding up a chunk of
+// 512 entries on its own, 164 bytes at a time for 41 columns.  Here a workgroup of 256 takes a chunk in two halves: all
+// lanes fetch the half's rows of X (16 bytes per lane, `lanes` lanes per row, the last one repeating some columns) into LDS,
+// 16 rows per lane group in flight; then the lane groups take the rows of the result, one after another, and walk
+// their entries in LDS.  A row's part in a chunk stays one serial sum, as it was, so every sum keeps its order and
+// with it the sign that a ReLU further on may decide by.  41 columns, 0.6 M entries: 76 -> 33 us; 1.9 M: 121 -> 85
+// (k_spmm_ragged_many: 66 and 106).
+static constexpr int HALF = CHUNK / 2;
+
+template <int EPI>
+__global__ __launch_bounds__(256, 3) void k_spmm_ragged(SplitArgs a, int lanes) {
+    constexpr int VEC = 4, NE = 16;                             // most rows of X a lane group fetches per half
+    constexpr int LONG = 24;                                    // parts from here on go to a whole wavefront
+    extern __shared__ float4 s_x[];                             // [HALF][lanes]
+    __shared__ int32_t s_col[HALF];
+    __shared__ float s_val[HALF];
+    __shared__ int s_pos[HALF + 2];                             // where the parts of rows begin; their number behind them
+    __shared__ int s_cnt[4];
+    __shared__ float s_open[3][64];                             // the sum that goes on into a half
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int groups = 256 / lanes, grp = tid / lanes, li = tid - grp * lanes;
+    const bool works = grp < groups;
+    const int64_t c = blockIdx.x;
+    int col0;
+    const bool col_ok = lane_columns<16, VEC>(a.f, blockIdx.y, gridDim.y, li, &col0) && works;
+    const float* const xbase = a.X + col0;
+    // the panel's columns first .. first + width - 1, and where a single lane finds column `lane` of them in a row of s_x
+    // (those behind the last whole four sit in the place of the lane that repeats columns)
+    int first = 0;
+    lane_columns<16, VEC>(a.f, blockIdx.y, gridDim.y, 0, &first);
+    int last4 = 0;
+    lane_columns<16, VEC>(a.f, blockIdx.y, gridDim.y, lanes - 1, &last4);
+    const int width = last4 + VEC - first, pitch = lanes * VEC;
+    const int whole = width / VEC * VEC, slot = lane < whole ? lane : whole + lane - (width - VEC);
+    if (tid < 64) s_open[0][tid] = 0.f;
+    int owned = 0;                                              // row starts of this chunk so far
+    int half = 0;
+    int32_t q = 0;                                              // row of the half's part 0
+    auto store_row = [&](int32_t r, int col, auto& v) {
+        constexpr int N = sizeof(v) / sizeof(float);
+        const int64_t row = a.ne_rows ? a.ne_rows[r] : r;
+        epilogue_store<N, EPI>(a.Z + row * a.ldz + col, EPI == GCN_EPI_MASK ? a.Zprev + row * a.ldzprev + col : nullptr, v,
+                               a.row_scale ? a.row_scale[row] : 1.f, a.defer && a.defer[row]);
+    };
+    for (; half < 2; ++half) {
+        const int64_t k0 = c * CHUNK + half * HALF;
+        if (k0 >= a.nnz) break;
+        const int cnt = a.nnz - k0 < HALF ? (int)(a.nnz - k0) : HALF;
+        const int64_t j0 = k0 / SUB;
+        bool start = false;
+        if (tid < cnt) {
+            s_col[tid] = a.colidx[k0 + tid];
+            s_val[tid] = a.val ? a.val[k0 + tid] : 1.f;
+            start = a.flags[j0 + (tid >> 5)] >> (tid & 31) & 1u;
+        }
+        q = a.sub_row[j0] - (int32_t)(a.flags[j0] & 1u);
+        const unsigned long long starts = __ballot(start);
+        if (lane == 0) s_cnt[wave] = __popcll(starts);
+        __syncthreads();
+        int before = __popcll(starts & ((1ull << lane) - 1ull)), np = 0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            if (w < wave) before += s_cnt[w];
+            np += s_cnt[w];
+        }
+        if (start) s_pos[before + 1] = tid;
+        if (tid == 0) { s_pos[0] = 0; s_pos[np + 1] = cnt; }
+        {
+            float x[NE][VEC];
+#pragma unroll
+            for (int i = 0; i < NE; ++i) {
+                const int e = grp + i * groups;
+                if (works && e < cnt) load_vec<VEC>(x[i], xbase + (int64_t)s_col[e] * a.ldx);
+            }
+#pragma unroll
+            for (int i = 0; i < NE; ++i) {
+                const int e = grp + i * groups;
+                if (works && e < cnt) s_x[e * lanes + li] = make_float4(x[i][0], x[i][1], x[i][2], x[i][3]);
+            }
+        }
+        __syncthreads();
+        // Long parts: a wavefront takes one, a column per lane (one addition per entry instead of four in a row).
+        const float* const xs = reinterpret_cast<const float*>(s_x);
+        for (int p = wave; p <= np; p += 4) {
+            const int beg = s_pos[p], end = s_pos[p + 1];
+            if (end - beg < LONG || lane >= width) continue;
+            float acc = p == 0 ? s_open[half][lane] : 0.f;
+            int e = beg;
+            const float* xc = xs + (size_t)e * pitch + slot;
+            for (; e + 16 <= end; e += 16, xc += 16 * pitch) {
+                float x[16], v[16];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) { x[i] = xc[i * pitch]; v[i] = s_val[e + i]; }
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc = fmaf(v[i], x[i], acc);
+            }
+            for (; e < end; ++e, xc += pitch) acc = fmaf(s_val[e], *xc, acc);
+            float out[1] = {acc};
+            if (p == np) s_open[half + 1][lane] = acc;
+            else if (p > 0 || owned) store_row(q + p, first + lane, out);
+            else a.carry[c * a.f + first + lane] = acc;
+        }
+        // Short parts: a lane group takes one, four columns per lane.
+        for (int p = grp; works && p <= np; p += groups) {
+            const int end = s_pos[p + 1];
+            int e = s_pos[p];
+            if (end - e >= LONG) continue;
+            float acc[VEC] = {};
+            if (p == 0) {
+#pragma unroll
+                for (int u = 0; u < VEC; ++u) acc[u] = s_open[half][col0 - first + u];
+            }
+#pragma unroll 2
+            for (; e < end; ++e) {
+                const float4 x = s_x[e * lanes + li];
+                const float v = s_val[e];
+                acc[0] = fmaf(v, x.x, acc[0]); acc[1] = fmaf(v, x.y, acc[1]);
+                acc[2] = fmaf(v, x.z, acc[2]); acc[3] = fmaf(v, x.w, acc[3]);
+            }
+            if (!col_ok) continue;
+            if (p == np) {
+#pragma unroll
+                for (int u = 0; u < VEC; ++u) s_open[half + 1][col0 - first + u] = acc[u];
+            }
+            else if (p > 0 || owned) store_row(q + p, col0, acc);
+            else store_vec<VEC>(a.carry + c * a.f + col0, acc);         // the entries before the chunk's first row start
+        }
+        owned += np;
+        q += np;
+        __syncthreads();
+    }
+    if (tid >= width) return;
+    float acc[1] = {s_open[half][tid]};
+    if (!owned) {                                               // the whole chunk lies inside one row
+        a.carry[c * a.f + first + tid] = acc[0];
+        return;
+    }
+    const int64_t knext = (c + 1) * CHUNK;
+    const bool continued = knext < a.nnz && !(a.flags[(c + 1) * SUBS_PER_CHUNK] & 1u);
+    if (continued) {                                            // finished by k_spmm_fixup
+        const int64_t row = a.ne_rows ? a.ne_rows[q] : q;
+        a.Z[row * a.ldz + first + tid] = acc[0];
+    } else store_row(q, first + tid, acc);
+}
+
+// The same for many chunks, where there are enough of them to fill the GPU with one lane group (16 lanes, 64 columns) per
+// chunk: four chunks per wavefront, each walked from end to end, the indices of a flag word staged at a time and the
+// next ones fetched meanwhile.  (k_spmm_ragged leaves all but one of its lane groups idle where a row covers a chunk, and
+// that shows once the GPU is full.)  41 columns, 32 M entries: 1028 -> 927 us (k_spmm_ragged 1270).
+template <int EPI>
+__global__ __launch_bounds__(64) void k_spmm_ragged_many(SplitArgs a) {
+    constexpr int VEC = 4, LPR = 16, UNR = 8;
+    constexpr int GROUPS = 64 / LPR, PER = SUB / LPR;           // lane groups per wavefront, entries staged by a lane
+    __shared__ __align__(16) int32_t s_col[GROUPS][SUB_STRIDE];
+    __shared__ __align__(16) float s_val[GROUPS][SUB_STRIDE];
+    const int lane = threadIdx.x, li = lane & 15;
+    const int64_t c = (int64_t)blockIdx.x * 4 + (lane >> 4);
+    const bool active = c < a.nchunks;
+    int col0;
+    const bool col_ok = lane_columns<LPR, VEC>(a.f, blockIdx.y, gridDim.y, li, &col0) && active;
+    const int64_t k0 = c * CHUNK, j0 = c * SUBS_PER_CHUNK;
+    int32_t* const lc = s_col[lane / LPR];
+    float* const lv = s_val[lane / LPR];
+    const float* const xbase = a.X + col0;
+    bool continued = false;
+    int32_t q = 0;
+    uint32_t mask_next = 0;
+    int32_t cn[PER];
+    float vn[PER];
+    auto fetch = [&](int w) {                                   // flag word w of the chunk
+        const int64_t k = (j0 + w) * SUB + li * PER;
+        mask_next = active ? a.flags[j0 + w] : 0u;
+#pragma unroll
+        for (int t = 0; t < PER; ++t) { cn[t] = 0; vn[t] = 1.f; }
+        if (!active) return;
+        if (k + PER <= a.nnz) {
+            const int2 x = *reinterpret_cast<const int2*>(a.colidx + k);
+            cn[0] = x.x; cn[1] = x.y;
+            if (a.val) {
+                const float2 y = *reinterpret_cast<const float2*>(a.val + k);
+                vn[0] = y.x; vn[1] = y.y;
+            }
+        } else {
+#pragma unroll
+            for (int t = 0; t < PER; ++t)
+                if (k + t < a.nnz) { cn[t] = a.colidx[k + t]; if (a.val) vn[t] = a.val[k + t]; }
+        }
+    };
+    if (active) {
+        continued = k0 + CHUNK < a.nnz && !(a.flags[(c + 1) * SUBS_PER_CHUNK] & 1u);
+        q = a.sub_row[j0];
+    }
+    fetch(0);
+    q -= (int32_t)(mask_next & 1u);             // a start bit at the very first entry re-increments q
+    float acc[VEC] = {}, head[VEC] = {};
+    bool owned = false;
+    for (int w = 0; w < SUBS_PER_CHUNK; ++w) {
+        uint32_t mask = mask_next;
+        const int64_t left = active ? a.nnz - (j0 + w) * SUB : 0;
+        const int cnt = left >= SUB ? SUB : (left > 0 ? (int)left : 0);
+#pragma unroll
+        for (int t = 0; t < PER; ++t) { lc[li * PER + t] = cn[t]; lv[li * PER + t] = vn[t]; }
+        // LDS operations of one wavefront complete in order; the fences keep the compiler to it
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (w + 1 < SUBS_PER_CHUNK) fetch(w + 1);
+        for (int b = 0; b < cnt; b += UNR) {
+            float x[UNR][VEC], v[UNR];
+#pragma unroll
+            for (int e = 0; e < UNR; ++e) {
+                v[e] = lv[b + e];
+                load_vec<VEC>(x[e], xbase + (int64_t)lc[b + e] * a.ldx);    // past the end: row 0, not used
+            }
+#pragma unroll
+            for (int e = 0; e < UNR; ++e) {
+                if (b + e < cnt) {
+                    if (mask & 1u) {            // entry starts a row: close the fragment before it
+                        if (owned) {
+                            if (col_ok) {
+                                const int64_t row = a.ne_rows ? a.ne_rows[q] : q;
+                                epilogue_store<VEC, EPI>(a.Z + row * a.ldz + col0,
+                                                         EPI == GCN_EPI_MASK ? a.Zprev + row * a.ldzprev + col0 : nullptr,
+                                                         acc, a.row_scale ? a.row_scale[row] : 1.f,
+                                                         a.defer && a.defer[row]);
+                            }
+                        } else {
+#pragma unroll
+                            for (int u = 0; u < VEC; ++u) head[u] = acc[u];
+                            owned = true;
+                        }
+                        q += 1;
+#pragma unroll
+                        for (int u = 0; u < VEC; ++u) acc[u] = 0.f;
+                    }
+                    mask >>= 1;
+#pragma unroll
+                    for (int u = 0; u < VEC; ++u) acc[u] = fmaf(v[e], x[e][u], acc[u]);
+                }
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    if (!col_ok) return;
+    store_vec<VEC>(a.carry + c * a.f + col0, owned ? head : acc);        // without a row start the whole chunk is inside one row
+    if (owned) {
+        const int64_t row = a.ne_rows ? a.ne_rows[q] : q;
+        if (continued) store_vec<VEC>(a.Z + row * a.ldz + col0, acc);     // finished by k_spmm_fixup
+        else epilogue_store<VEC, EPI>(a.Z + row * a.ldz + col0,
+                                      EPI == GCN_EPI_MASK ? a.Zprev + row * a.ldzprev + col0 : nullptr, acc,
+                                      a.row_scale ? a.row_scale[row] : 1.f, a.defer && a.defer[row]);
+    }
 }
 
 // Two matrices in one launch: of every ra + rb consecutive workgroups the first ra work on `a` (with
@@ -703,7 +956,6 @@ static int launch_split(const SplitArgs& args, int epilogue, hipStream_t s) {
             }
             timing_end(s);
             GCN_LAUNCH_CHECK();
-            if (few.f % 4 != 0) return launch_fixup<16, 1>(few, epilogue, s);
             return launch_fixup<LPR, VEC>(few, epilogue, s);
         }
     }
@@ -711,34 +963,64 @@ static int launch_split(const SplitArgs& args, int epilogue, hipStream_t s) {
     // keeps 16 gathers in flight instead of 4.
     if (waves < (int64_t)device_info().cus * 16) GCN_TRY((launch_split_unr<LPR, VEC, 16>(args, epilogue, s)));
     else GCN_TRY((launch_split_unr<LPR, VEC, 4>(args, epilogue, s)));
-    // the fix-up reads and writes rows of Z: no column may belong to two lanes there
-    if (VEC == 4 && args.f % 4 != 0) return launch_fixup<16, 1>(args, epilogue, s);
     return launch_fixup<LPR, VEC>(args, epilogue, s);
+}
+
+static int launch_ragged(const SplitArgs& args, int epilogue, hipStream_t s) {
+    const unsigned panels = (unsigned)((args.f + 63) / 64);
+    timing_begin(s);
+    if (args.nchunks * panels <= (int64_t)device_info().cus * 16) {
+        const int lanes = args.f >= 64 ? 16 : (args.f + 3) / 4;
+        const dim3 grid((unsigned)args.nchunks, panels);
+        const size_t lds = (size_t)HALF * lanes * sizeof(float4);
+        switch (epilogue) {
+            case GCN_EPI_NONE: launch_lds<k_spmm_ragged<GCN_EPI_NONE>>(grid, 256, lds, s, args, lanes); break;
+            case GCN_EPI_RELU: launch_lds<k_spmm_ragged<GCN_EPI_RELU>>(grid, 256, lds, s, args, lanes); break;
+            default: launch_lds<k_spmm_ragged<GCN_EPI_MASK>>(grid, 256, lds, s, args, lanes); break;
+        }
+    } else {
+        const dim3 grid((unsigned)((args.nchunks + 3) / 4), panels);
+        switch (epilogue) {
+            case GCN_EPI_NONE: hipLaunchKernelGGL(k_spmm_ragged_many<GCN_EPI_NONE>, grid, dim3(64), 0, s, args); break;
+            case GCN_EPI_RELU: hipLaunchKernelGGL(k_spmm_ragged_many<GCN_EPI_RELU>, grid, dim3(64), 0, s, args); break;
+            default: hipLaunchKernelGGL(k_spmm_ragged_many<GCN_EPI_MASK>, grid, dim3(64), 0, s, args); break;
+        }
+    }
+    timing_end(s);
+    GCN_LAUNCH_CHECK();
+    // the fix-up reads and writes rows of Z: no column may belong to two lanes there
+    return launch_fixup<16, 1>(args, epilogue, s);
 }
 
 // Whether a matrix goes through k_spmm_short: its rows are all short, and all wavefronts are resident at once (eight per
 // compute unit at this kernel's registers).  With more rows the even chunks of k_spmm_split win (rows of 21 entries at 16
 // columns: 20 K rows 9.7 against 11.0 us, 50 K rows 17.7 against 14.2).
 static bool short_rows(const Matrix& m, int32_t f) {
-    const int lpr = f <= 16 ? 4 : 8;
+    const int lpr = f % 4 == 0 ? (f <= 16 ? 4 : 8) : (f <= 8 ? 2 : (f <= 16 ? 4 : (f <= 32 ? 8 : 16)));
     return f >= 4 && m.max_degree <= SHORT_ROW && m.nrows * lpr * ((f + 4 * lpr - 1) / (4 * lpr)) <= (int64_t)device_info().cus * 8 * 64;
 }
 
 static int launch_short(const SplitArgs& args, int64_t nrows, int epilogue, hipStream_t s) {
-    auto go = [&](auto lpr) {
-        constexpr int LPR = decltype(lpr)::value;
+    auto go = [&](auto lpr, auto slice) {
+        constexpr int LPR = decltype(lpr)::value, SLICE = decltype(slice)::value;
         const dim3 grid((unsigned)((nrows * LPR + 63) / 64), (unsigned)((args.f + 4 * LPR - 1) / (4 * LPR)));
         switch (epilogue) {
-            case GCN_EPI_NONE: hipLaunchKernelGGL((k_spmm_short<LPR, GCN_EPI_NONE>), grid, dim3(64), 0, s, args, nrows); break;
-            case GCN_EPI_RELU: hipLaunchKernelGGL((k_spmm_short<LPR, GCN_EPI_RELU>), grid, dim3(64), 0, s, args, nrows); break;
-            default: hipLaunchKernelGGL((k_spmm_short<LPR, GCN_EPI_MASK>), grid, dim3(64), 0, s, args, nrows); break;
+            case GCN_EPI_NONE: hipLaunchKernelGGL((k_spmm_short<LPR, SLICE, GCN_EPI_NONE>), grid, dim3(64), 0, s, args, nrows); break;
+            case GCN_EPI_RELU: hipLaunchKernelGGL((k_spmm_short<LPR, SLICE, GCN_EPI_RELU>), grid, dim3(64), 0, s, args, nrows); break;
+            default: hipLaunchKernelGGL((k_spmm_short<LPR, SLICE, GCN_EPI_MASK>), grid, dim3(64), 0, s, args, nrows); break;
         }
     };
     timing_begin(s);
-    // the lane layout of run_split: the pieces of a row follow from it
-    if (args.f <= 16) go(std::integral_constant<int, 4>());
-    else if (args.f > 32 && args.f % 4 != 0) go(std::integral_constant<int, 16>());
-    else go(std::integral_constant<int, 8>());
+    // lanes per row and slices as in run_split: the pieces of a row follow from them
+    if (args.f % 4 == 0) {
+        if (args.f <= 16) go(std::integral_constant<int, 4>(), std::integral_constant<int, 32>());
+        else go(std::integral_constant<int, 8>(), std::integral_constant<int, 64>());
+    } else {
+        if (args.f <= 8) go(std::integral_constant<int, 2>(), std::integral_constant<int, 64>());
+        else if (args.f <= 16) go(std::integral_constant<int, 4>(), std::integral_constant<int, 128>());
+        else if (args.f <= 32) go(std::integral_constant<int, 8>(), std::integral_constant<int, 256>());
+        else go(std::integral_constant<int, 16>(), std::integral_constant<int, 512>());
+    }
     timing_end(s);
     GCN_LAUNCH_CHECK();
     return GCN_OK;
@@ -941,9 +1223,15 @@ static int launch_sweep(const SweepArgs& args, int64_t ntasks, int sweep_waves, 
 }
 
 // Chooses the lane layout for one nonzero-split product and launches it.
-static int run_split(const SplitArgs& args, int epilogue, hipStream_t s, int64_t xrows, bool l2_resident = false) {
+static int run_split(const SplitArgs& args, int epilogue, hipStream_t s, bool l2_resident = false) {
     const int32_t f = args.f;
     if (f < 4) return launch_split<4, 1>(args, epilogue, s);
+    if (f % 4 != 0) {
+        if (f <= 8) return launch_split<8, 1>(args, epilogue, s);
+        if (f <= 16) return launch_split<16, 1>(args, epilogue, s);
+        if (f <= 32) return launch_split<32, 1>(args, epilogue, s);
+        return launch_ragged(args, epilogue, s);
+    }
     if (f <= 16) return launch_split<4, 4>(args, epilogue, s);
     if (f <= 32) return launch_split<8, 4>(args, epilogue, s);
     // Wider operands are processed in panels of 32 columns (one 128-byte line per gathered row): the panel of X that the
@@ -951,11 +1239,8 @@ static int run_split(const SplitArgs& args, int epilogue, hipStream_t s, int64_t
     // index/value stream once per panel.
     // When the gathers are served by the L2 anyway (column-blocked copy) panels of 64 are better: half the passes over
     // the index/value stream and half the requests (config 3 at f = 128: 3.55 -> 3.27 ms; config 2, bound by line
-    // fills: 1.46 -> 1.69 ms, so not there).  Rows that are not whole 16-byte pieces straddle lines
-    // wherever they are cut: one panel up to 64 columns (41 columns, 1 M rows: 1.20 ms in two panels, 0.89 in one), more
-    // of them while the operand stays within the last-level cache.
-        const bool ragged = f % 4 != 0 && (f <= 64 || xrows * f * 4 <= (128ll << 20));
-    if ((f >= 64 && l2_resident) || ragged) return launch_split<16, 4>(args, epilogue, s);
+    // fills: 1.46 -> 1.69 ms, so not there).
+    if (f >= 64 && l2_resident) return launch_split<16, 4>(args, epilogue, s);
     return launch_split<8, 4>(args, epilogue, s);
 }
 
@@ -1001,7 +1286,7 @@ static int zero_empty_rows(const Matrix& m, int32_t f, float* Z, int64_t ldz, hi
 static int run_matrix(gcn_csr* a, Matrix& mm, const int32_t* row_map, int64_t nnz, int64_t nblocks, int32_t f,
                       const float* X, int64_t ldx, float* Z, int64_t ldz, int epilogue, const float* Zprev,
                       int64_t ldzprev, const SpmmOpt& o, hipStream_t s, float* carry_given = nullptr) {
-    if ((mm.nchunks + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK >= (1ll << 31))
+    if (mm.nchunks >= (1ll << 31))
         return fail(GCN_ERR_RANGE, "gcn_spmm: too many chunks for one launch");
     // carry_given: a buffer of at least nchunks * f floats that the caller of this function provides
     // (only without column blocks); otherwise the handle's own buffer, grown on demand
@@ -1028,7 +1313,7 @@ static int run_matrix(gcn_csr* a, Matrix& mm, const int32_t* row_map, int64_t nn
         args.ne_rows = nullptr; args.rp = b.rp; args.row_scale = nullptr;     // the scale belongs to the reduced row
         args.fix_list = b.fix_list; args.n_fix = b.n_fix; args.n_fix_long = b.n_fix_long;
         args.Z = a->partial; args.ldz = f; args.Zprev = nullptr; args.ldzprev = 0;
-        GCN_TRY(run_split(args, GCN_EPI_NONE, s, mm.ncols, true));
+        GCN_TRY(run_split(args, GCN_EPI_NONE, s, true));
         if (f >= 4) return launch_block_reduce<4>(mm.nrows, f, b, row_map, o.row_scale, o.accumulate ? 1 : 0, a->partial, Z, ldz, epilogue, Zprev, ldzprev, s);
         return launch_block_reduce<1>(mm.nrows, f, b, row_map, o.row_scale, o.accumulate ? 1 : 0, a->partial, Z, ldz, epilogue, Zprev, ldzprev, s);
     }
@@ -1050,7 +1335,7 @@ static int run_matrix(gcn_csr* a, Matrix& mm, const int32_t* row_map, int64_t nn
         return launch_short(args, mm.nrows, epilogue, s);
     }
     if (!row_map && mm.n_ne < mm.nrows) GCN_TRY(zero_empty_rows(mm, f, Z, ldz, s));
-    return run_split(args, epilogue, s, mm.ncols);
+    return run_split(args, epilogue, s);
 }
 
 // ---- hub schedule -----------------------------------------------------------------------------------------

@@ -193,7 +193,7 @@ def test_spmm_rows_across_chunks_any_width(f, shape):
     a.close()
 
 
-@pytest.mark.parametrize("f", [16, 41, 64])
+@pytest.mark.parametrize("f", [7, 16, 21, 33, 41, 64, 67])
 def test_spmm_few_chunks_and_many_chunks_add_alike(f):
     """The kernel for matrices of few chunks, the one for more and the one for many keep every row's order of additions:
     the first rows of a matrix give the same bits whichever kernel runs."""
@@ -203,7 +203,7 @@ def test_spmm_few_chunks_and_many_chunks_add_alike(f):
     X = synth.normal_features(5000, f, 85)
     rowptr, colidx, val = _rows_matrix(lengths, 5000, 86)
     first = None
-    for repeat in (1, 12, 40):                                      # the same rows again and again behind themselves
+    for repeat in (1, 12, 60):                                      # the same rows again and again behind themselves
         rp = np.concatenate([[0]] + [rowptr[1:] + k * rowptr[-1] for k in range(repeat)])
         a = g.gcn_csr_create_from_csr_rect(rp.size - 1, 5000, dev(rp), dev(np.tile(colidx, repeat)), dev(np.tile(val, repeat)), 0)
         g.gcn_csr_config(a, g.CFG_SPMM_BLOCKS, 1)
