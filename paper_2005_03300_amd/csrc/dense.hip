@@ -28,18 +28,22 @@ __global__ void k_gemm_naive(int tb, int64_t M, int64_t N, int64_t K, const floa
 }
 
 // ---- element-wise -----------------------------------------------------------------------------
-__global__ void k_relu(int64_t rows, int32_t cols, const float* __restrict__ Z, int64_t ldz, float* __restrict__ H,
-                       int64_t ldh) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t i = t / cols;
-    const int j = (int)(t % cols);
-    if (i >= rows) return;
-    const float z = Z[i * ldz + j];
-    H[i * ldh + j] = z > 0.f ? z : 0.f;
+// ReLU, and with M the derivative mask, over rows x cols with leading dimensions.  Dense operands come as one row: 16
+// bytes per thread; the others as one thread per element.
+__global__ __launch_bounds__(256) void k_relu_dense(int64_t total, const float* X, const float* M, float* out) {
+    const int64_t t = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
+    if (t + 4 <= total) {
+        const float4 x = *reinterpret_cast<const float4*>(X + t);
+        const float4 m = *reinterpret_cast<const float4*>(M + t);
+        *reinterpret_cast<float4*>(out + t) =
+            make_float4(m.x > 0.f ? x.x : 0.f, m.y > 0.f ? x.y : 0.f, m.z > 0.f ? x.z : 0.f, m.w > 0.f ? x.w : 0.f);
+    } else {
+        for (int64_t e = t; e < total; ++e) out[e] = M[e] > 0.f ? X[e] : 0.f;
+    }
 }
 
-__global__ void k_relu_mask(int64_t rows, int32_t cols, const float* __restrict__ G, int64_t ldg,
-                            const float* __restrict__ Zp, int64_t ldzp, float* __restrict__ out, int64_t ldo) {
+__global__ void k_relu_mask(int64_t rows, int32_t cols, const float* G, int64_t ldg, const float* Zp, int64_t ldzp, float* out,
+                            int64_t ldo) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t i = t / cols;
     const int j = (int)(t % cols);
@@ -75,14 +79,41 @@ __global__ __launch_bounds__(256) void k_colsum_partial(int64_t rows, int32_t co
     part[(int64_t)blockIdx.x * cols + j] = acc;
 }
 
-__global__ void k_bias_add(int64_t rows, int32_t cols, float* __restrict__ Z, int64_t ldz, const float* __restrict__ bias,
-                           int relu) {
+// Z += 1 bias^T over dense rows, as one run of rows * cols floats, 16 bytes per thread and step.  The stride of a thread is a
+// multiple of the row length (the launch picks it so), so its four columns and their biases stay the same: no division
+// in the loop.  Bound by memory (200 K x 64 with H: 154 MB; bias and ReLU in two passes took 50 us).
+__global__ __launch_bounds__(256) void k_bias_add(int64_t total, int32_t cols, int64_t stride, float* __restrict__ Z,
+                                                  const float* __restrict__ bias, int relu, float* __restrict__ H) {
+    const int64_t t0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
+    if (t0 >= stride) return;
+    float b[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) b[e] = bias[(t0 + e) % cols];
+    for (int64_t t = t0; t < total; t += stride) {
+        if (t + 4 <= total) {
+            float4 v = *reinterpret_cast<float4*>(Z + t);
+            v.x += b[0]; v.y += b[1]; v.z += b[2]; v.w += b[3];
+            const float4 r = make_float4(v.x > 0.f ? v.x : 0.f, v.y > 0.f ? v.y : 0.f, v.z > 0.f ? v.z : 0.f, v.w > 0.f ? v.w : 0.f);
+            *reinterpret_cast<float4*>(Z + t) = relu ? r : v;
+            if (H) *reinterpret_cast<float4*>(H + t) = r;
+        } else {
+            for (int e = 0; t + e < total; ++e) {
+                const float v = Z[t + e] + b[e], r = v > 0.f ? v : 0.f;
+                Z[t + e] = relu ? r : v;
+                if (H) H[t + e] = r;
+            }
+        }
+    }
+}
+
+// Any alignment.
+__global__ void k_bias_add_plain(int64_t total, int32_t cols, float* __restrict__ Z, const float* __restrict__ bias, int relu,
+                                 float* __restrict__ H) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t i = t / cols;
-    const int j = (int)(t % cols);
-    if (i >= rows) return;
-    float v = Z[i * ldz + j] + bias[j];
-    Z[i * ldz + j] = (relu && !(v > 0.f)) ? 0.f : v;
+    if (t >= total) return;
+    const float v = Z[t] + bias[t % cols], r = v > 0.f ? v : 0.f;
+    Z[t] = relu ? r : v;
+    if (H) H[t] = r;
 }
 
 // Y[i,:] = scale[i] * X[i,:]; 16 bytes per thread when the layout allows it.
@@ -176,14 +207,33 @@ int colsum_launch(int64_t rows, int32_t cols, const float* G, int64_t ldg, float
     return reduce_parts_launch(1, cols, (int)parts, false, (const float*)scratch, out, cols, nullptr, GCN_EPI_NONE, nullptr, 0, s);
 }
 
-int relu_launch(int64_t rows, int32_t cols, const float* Z, int64_t ldz, float* H, int64_t ldh, hipStream_t s) {
-    hipLaunchKernelGGL(k_relu, dim3(nblocks(rows * cols)), dim3(256), 0, s, rows, cols, Z, ldz, H, ldh);
+static int relu_mask_launch(int64_t rows, int32_t cols, const float* G, int64_t ldg, const float* Zprev, int64_t ldzprev,
+                            float* out, int64_t ldo, hipStream_t s) {
+    const bool dense = (ldg == cols && ldzprev == cols && ldo == cols) || rows == 1;
+    if (dense && (((uintptr_t)G | (uintptr_t)Zprev | (uintptr_t)out) & 15u) == 0)
+        hipLaunchKernelGGL(k_relu_dense, dim3(nblocks((rows * cols + 3) / 4)), dim3(256), 0, s, rows * cols, G, Zprev, out);
+    else
+        hipLaunchKernelGGL(k_relu_mask, dim3(nblocks(rows * cols)), dim3(256), 0, s, rows, cols, G, ldg, Zprev, ldzprev, out, ldo);
     GCN_LAUNCH_CHECK();
     return GCN_OK;
 }
 
-int bias_add_launch(int64_t rows, int32_t cols, float* Z, int64_t ldz, const float* bias, int relu, hipStream_t s) {
-    hipLaunchKernelGGL(k_bias_add, dim3(nblocks(rows * cols)), dim3(256), 0, s, rows, cols, Z, ldz, bias, relu);
+// max(Z, 0) is Z where Z is positive, 0 elsewhere
+int relu_launch(int64_t rows, int32_t cols, const float* Z, int64_t ldz, float* H, int64_t ldh, hipStream_t s) {
+    return relu_mask_launch(rows, cols, Z, ldz, Z, ldz, H, ldh, s);
+}
+
+int bias_add_launch(int64_t rows, int32_t cols, float* Z, const float* bias, int relu, float* H, hipStream_t s) {
+    const int64_t total = rows * cols;
+    if ((((uintptr_t)Z | (uintptr_t)H) & 15u) == 0) {
+        // about 2 M floats per step of the grid (8192 wavefronts), rounded up to whole rows in whole 16-byte pieces
+        const int64_t unit = cols % 4 == 0 ? cols : (cols % 2 == 0 ? 2 * (int64_t)cols : 4 * (int64_t)cols);
+        const int64_t want = total < (2ll << 20) ? total : (2ll << 20);
+        const int64_t stride = (want + unit - 1) / unit * unit;
+        hipLaunchKernelGGL(k_bias_add, dim3(nblocks((stride + 3) / 4)), dim3(256), 0, s, total, cols, stride, Z, bias, relu, H);
+    } else {
+        hipLaunchKernelGGL(k_bias_add_plain, dim3(nblocks(total)), dim3(256), 0, s, total, cols, Z, bias, relu, H);
+    }
     GCN_LAUNCH_CHECK();
     return GCN_OK;
 }
@@ -241,10 +291,7 @@ int gcn_relu_mask(int64_t rows, int32_t cols, const float* G, int64_t ldg, const
                   float* out, int64_t ldo, void* stream) {
     if (!G || !Zprev || !out || rows <= 0 || cols <= 0 || ldg < cols || ldzprev < cols || ldo < cols)
         return fail(GCN_ERR_BADARG, "gcn_relu_mask: bad argument");
-    hipLaunchKernelGGL(k_relu_mask, dim3(nblocks(rows * cols)), dim3(256), 0, (hipStream_t)stream, rows, cols, G, ldg,
-                       Zprev, ldzprev, out, ldo);
-    GCN_LAUNCH_CHECK();
-    return GCN_OK;
+    return relu_mask_launch(rows, cols, G, ldg, Zprev, ldzprev, out, ldo, (hipStream_t)stream);
 }
 
 int gcn_scale_rows(int64_t rows, int32_t cols, const float* X, int64_t ldx, const float* scale, float* Y, int64_t ldy,

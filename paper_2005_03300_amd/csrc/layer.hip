@@ -57,9 +57,11 @@ static int layer_forward_impl(gcn_csr* a, int32_t f_in, int32_t f_out, const flo
         GCN_TRY(timed_gemm(0, 0, n, f_out, f_in, Hin, ldh, W, f_out, T, f_out, nullptr, GCN_EPI_NONE, nullptr, 0, s, ps));
         GCN_TRY(norm_spmm(a, matrix_of(a, 1), f_out, T, f_out, t_scratch ? T : xs, Z, f_out,
                           (in_place && !bias) ? GCN_EPI_RELU : GCN_EPI_NONE, nullptr, 0, s, ps != nullptr));
-        if (bias) {
+        if (bias) {                                  // and the activation, when it goes to a matrix of its own
             PhaseTimer pt(s, GCN_PHASE_OTHER);
-            GCN_TRY(bias_add_launch(n, f_out, Z, f_out, bias, in_place ? 1 : 0, s));
+            const bool both = act == GCN_ACT_RELU && !in_place;
+            GCN_TRY(bias_add_launch(n, f_out, Z, bias, in_place ? 1 : 0, both ? Hout : nullptr, s));
+            if (both) return GCN_OK;
         }
     } else {
         // t_given: T already holds A^T Hin (aggregated once by the caller; Hin itself is not read)
