@@ -296,6 +296,7 @@ void free_matrix(Matrix& m);
 struct SpmmOpt {
     bool pattern = false;
     const float* row_scale = nullptr;
+    bool any_order = false;           // no ReLU decides on the result: a faster kernel may add a row's terms in another order
     // internal to the hub schedule:
     const uint8_t* defer = nullptr;   // rows whose sum is stored raw (no scale, no epilogue)
     bool accumulate = false;          // column-blocked reduce adds to what Z already holds

@@ -17,13 +17,14 @@ static int resolve_order(int order, int32_t f_in, int32_t f_out) {
 // Z = epilogue(op(A) X) with the handle's normalised matrix.  `xs` (n x f, ld f) receives the
 // pre-scaled operand of the value-free form; it may be X itself when X is a temporary with ld f,
 // or NULL to force the valued product.  `prescaled`: the producer of X already applied the row factors
-// (only passed when pre_scale() said so for this operand).
+// (only passed when pre_scale() said so for this operand).  `any_order`: no ReLU decides on the result (see SpmmOpt).
 static int norm_spmm(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx, float* xs, float* Z, int64_t ldz,
-                     int epilogue, const float* Zprev, int64_t ldzprev, hipStream_t s, bool prescaled = false) {
+                     int epilogue, const float* Zprev, int64_t ldzprev, hipStream_t s, bool prescaled, bool any_order) {
     PhaseTimer pt(s, GCN_PHASE_SPMM);
-    if (!xs || !use_value_free(a)) return spmm_launch(a, m, f, X, ldx, Z, ldz, epilogue, Zprev, ldzprev, s);
-    if (!prescaled) GCN_TRY(scale_rows_launch(a->n, f, X, ldx, a->inv_sqrt_deg, xs, f, s));
     SpmmOpt o;
+    o.any_order = any_order;
+    if (!xs || !use_value_free(a)) return spmm_launch(a, m, f, X, ldx, Z, ldz, epilogue, Zprev, ldzprev, s, o);
+    if (!prescaled) GCN_TRY(scale_rows_launch(a->n, f, X, ldx, a->inv_sqrt_deg, xs, f, s));
     o.pattern = true;
     o.row_scale = a->inv_sqrt_deg;
     return spmm_launch(a, m, f, prescaled ? X : xs, prescaled ? ldx : f, Z, ldz, epilogue, Zprev, ldzprev, s, o);
@@ -56,7 +57,7 @@ static int layer_forward_impl(gcn_csr* a, int32_t f_in, int32_t f_out, const flo
         const float* ps = pre_scale(a, t_scratch);
         GCN_TRY(timed_gemm(0, 0, n, f_out, f_in, Hin, ldh, W, f_out, T, f_out, nullptr, GCN_EPI_NONE, nullptr, 0, s, ps));
         GCN_TRY(norm_spmm(a, matrix_of(a, 1), f_out, T, f_out, t_scratch ? T : xs, Z, f_out,
-                          (in_place && !bias) ? GCN_EPI_RELU : GCN_EPI_NONE, nullptr, 0, s, ps != nullptr));
+                          (in_place && !bias) ? GCN_EPI_RELU : GCN_EPI_NONE, nullptr, 0, s, ps != nullptr, act == GCN_ACT_NONE));
         if (bias) {                                  // and the activation, when it goes to a matrix of its own
             PhaseTimer pt(s, GCN_PHASE_OTHER);
             const bool both = act == GCN_ACT_RELU && !in_place;
@@ -65,7 +66,8 @@ static int layer_forward_impl(gcn_csr* a, int32_t f_in, int32_t f_out, const flo
         }
     } else {
         // t_given: T already holds A^T Hin (aggregated once by the caller; Hin itself is not read)
-        if (!t_given) GCN_TRY(norm_spmm(a, matrix_of(a, 1), f_in, Hin, ldh, xs, T, f_in, GCN_EPI_NONE, nullptr, 0, s));
+        if (!t_given)
+            GCN_TRY(norm_spmm(a, matrix_of(a, 1), f_in, Hin, ldh, xs, T, f_in, GCN_EPI_NONE, nullptr, 0, s, false, act == GCN_ACT_NONE));
         GCN_TRY(timed_gemm(0, 0, n, f_out, f_in, T, f_in, W, f_out, Z, f_out, bias,
                             in_place ? GCN_EPI_RELU : GCN_EPI_NONE, nullptr, 0, s));
     }
@@ -88,7 +90,7 @@ static int layer_backward_impl(gcn_csr* a, int32_t f_in, int32_t f_out, const fl
     }
     if (order == GCN_ORDER_GEMM_FIRST) {
         // S = A G;  Y = Hin^T S;  Gprev = (S W^T) (.) sigma'(Zprev)
-        GCN_TRY(norm_spmm(a, matrix_of(a, 0), f_out, G, f_out, xs, S, f_out, GCN_EPI_NONE, nullptr, 0, s));
+        GCN_TRY(norm_spmm(a, matrix_of(a, 0), f_out, G, f_out, xs, S, f_out, GCN_EPI_NONE, nullptr, 0, s, false, true));
         GCN_TRY(timed_gemm(1, 0, f_in, f_out, n, Hin, ldh, S, f_out, Y, f_out, nullptr, GCN_EPI_NONE, nullptr, 0, s));
         if (Gprev)
             GCN_TRY(timed_gemm(0, 1, n, f_in, f_out, S, f_out, W, f_out, Gprev, f_in, nullptr, GCN_EPI_MASK, Zprev, f_in, s));
@@ -100,7 +102,7 @@ static int layer_backward_impl(gcn_csr* a, int32_t f_in, int32_t f_out, const fl
             const float* ps = pre_scale(a, s_scratch);
             GCN_TRY(timed_gemm(0, 1, n, f_in, f_out, G, f_out, W, f_out, S, f_in, nullptr, GCN_EPI_NONE, nullptr, 0, s, ps));
             GCN_TRY(norm_spmm(a, matrix_of(a, 0), f_in, S, f_in, s_scratch ? S : xs, Gprev, f_in, GCN_EPI_MASK, Zprev, f_in, s,
-                              ps != nullptr));
+                              ps != nullptr, true));
         }
     }
     return GCN_OK;
@@ -255,7 +257,8 @@ static int epoch_impl(gcn_csr* a, int32_t L_w, const int32_t* dims, const float*
         const bool is_last = (l == last);
         if (is_last && fuse) {
             if (!(l == 0 && P0))
-                GCN_TRY(norm_spmm(a, matrix_of(a, 1), dims[l], Hin, dims[l], at(lay.XS), layer_T(l), dims[l], GCN_EPI_NONE, nullptr, 0, s));
+                GCN_TRY(norm_spmm(a, matrix_of(a, 1), dims[l], Hin, dims[l], at(lay.XS), layer_T(l), dims[l], GCN_EPI_NONE, nullptr, 0, s,
+                                  false, true));
             break;
         }
         GCN_TRY(layer_forward_impl(a, dims[l], dims[l + 1], Hin, dims[l], W[l], nullptr, at(lay.Z[l]),
@@ -279,7 +282,7 @@ static int epoch_impl(gcn_csr* a, int32_t L_w, const int32_t* dims, const float*
             // Y^L and S = G^L (W^L)^T are done; what is left of Equation 2 is the sparse product
             if (l > 0)
                 GCN_TRY(norm_spmm(a, matrix_of(a, 0), dims[l], at(lay.S), dims[l], at(lay.S), at(lay.G[l - 1]), dims[l], GCN_EPI_MASK,
-                                  at(lay.Z[l - 1]), dims[l], s, pre_scale(a, true) != nullptr));
+                                  at(lay.Z[l - 1]), dims[l], s, pre_scale(a, true) != nullptr, true));
             continue;
         }
         const float* Hl = l > 0 ? at(lay.H[l - 1]) : H0;

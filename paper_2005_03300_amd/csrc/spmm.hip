@@ -921,6 +921,13 @@ static int launch_fixup(const SplitArgs& args, int epilogue, hipStream_t s) {
     return GCN_OK;
 }
 
+// The fix-up reads and writes rows of Z: where lanes of 16 bytes repeat columns, it takes one column per lane.
+template <int LPR, int VEC>
+static int fixup_of(const SplitArgs& args, int epilogue, hipStream_t s) {
+    if (VEC == 4 && args.f % 4 != 0) return launch_fixup<16, 1>(args, epilogue, s);
+    return launch_fixup<LPR, VEC>(args, epilogue, s);
+}
+
 template <int LPR, int VEC, int UNR>
 static int launch_split_unr(const SplitArgs& args, int epilogue, hipStream_t s) {
     const int tile = LPR * VEC;
@@ -956,14 +963,14 @@ static int launch_split(const SplitArgs& args, int epilogue, hipStream_t s) {
             }
             timing_end(s);
             GCN_LAUNCH_CHECK();
-            return launch_fixup<LPR, VEC>(few, epilogue, s);
+            return fixup_of<LPR, VEC>(few, epilogue, s);
         }
     }
     // Few wavefronts (less than four per SIMD) cannot hide the gathers' latency behind each other: there every lane group
     // keeps 16 gathers in flight instead of 4.
     if (waves < (int64_t)device_info().cus * 16) GCN_TRY((launch_split_unr<LPR, VEC, 16>(args, epilogue, s)));
     else GCN_TRY((launch_split_unr<LPR, VEC, 4>(args, epilogue, s)));
-    return launch_fixup<LPR, VEC>(args, epilogue, s);
+    return fixup_of<LPR, VEC>(args, epilogue, s);
 }
 
 static int launch_ragged(const SplitArgs& args, int epilogue, hipStream_t s) {
@@ -1223,10 +1230,10 @@ static int launch_sweep(const SweepArgs& args, int64_t ntasks, int sweep_waves, 
 }
 
 // Chooses the lane layout for one nonzero-split product and launches it.
-static int run_split(const SplitArgs& args, int epilogue, hipStream_t s, bool l2_resident = false) {
+static int run_split(const SplitArgs& args, int epilogue, hipStream_t s, bool any_order, bool l2_resident = false) {
     const int32_t f = args.f;
     if (f < 4) return launch_split<4, 1>(args, epilogue, s);
-    if (f % 4 != 0) {
+    if (f % 4 != 0 && !any_order) {
         if (f <= 8) return launch_split<8, 1>(args, epilogue, s);
         if (f <= 16) return launch_split<16, 1>(args, epilogue, s);
         if (f <= 32) return launch_split<32, 1>(args, epilogue, s);
@@ -1240,7 +1247,10 @@ static int run_split(const SplitArgs& args, int epilogue, hipStream_t s, bool l2
     // When the gathers are served by the L2 anyway (column-blocked copy) panels of 64 are better: half the passes over
     // the index/value stream and half the requests (config 3 at f = 128: 3.55 -> 3.27 ms; config 2, bound by line
     // fills: 1.46 -> 1.69 ms, so not there).
-    if (f >= 64 && l2_resident) return launch_split<16, 4>(args, epilogue, s);
+    // Rows that are not whole 16-byte pieces (only without an order to keep) straddle lines wherever they are cut: one
+    // panel up to 64 columns (41 columns, 1 M rows: 1.20 ms in two panels, 0.89 in one; k_spmm_ragged_many 0.92; with
+    // 200 K rows 0.073 against its 0.122).
+    if ((f >= 64 && l2_resident) || (f % 4 != 0 && f <= 64)) return launch_split<16, 4>(args, epilogue, s);
     return launch_split<8, 4>(args, epilogue, s);
 }
 
@@ -1313,7 +1323,7 @@ static int run_matrix(gcn_csr* a, Matrix& mm, const int32_t* row_map, int64_t nn
         args.ne_rows = nullptr; args.rp = b.rp; args.row_scale = nullptr;     // the scale belongs to the reduced row
         args.fix_list = b.fix_list; args.n_fix = b.n_fix; args.n_fix_long = b.n_fix_long;
         args.Z = a->partial; args.ldz = f; args.Zprev = nullptr; args.ldzprev = 0;
-        GCN_TRY(run_split(args, GCN_EPI_NONE, s, true));
+        GCN_TRY(run_split(args, GCN_EPI_NONE, s, o.any_order, true));
         if (f >= 4) return launch_block_reduce<4>(mm.nrows, f, b, row_map, o.row_scale, o.accumulate ? 1 : 0, a->partial, Z, ldz, epilogue, Zprev, ldzprev, s);
         return launch_block_reduce<1>(mm.nrows, f, b, row_map, o.row_scale, o.accumulate ? 1 : 0, a->partial, Z, ldz, epilogue, Zprev, ldzprev, s);
     }
@@ -1335,7 +1345,7 @@ static int run_matrix(gcn_csr* a, Matrix& mm, const int32_t* row_map, int64_t nn
         return launch_short(args, mm.nrows, epilogue, s);
     }
     if (!row_map && mm.n_ne < mm.nrows) GCN_TRY(zero_empty_rows(mm, f, Z, ldz, s));
-    return run_split(args, epilogue, s);
+    return run_split(args, epilogue, s, o.any_order);
 }
 
 // ---- hub schedule -----------------------------------------------------------------------------------------

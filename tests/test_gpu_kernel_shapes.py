@@ -213,3 +213,50 @@ def test_spmm_few_chunks_and_many_chunks_add_alike(f):
         first = got if first is None else first
         assert np.array_equal(got, first), repeat
         a.close()
+
+
+@pytest.mark.parametrize("f", [1, 3, 5, 7, 9, 17, 31, 33, 41, 63, 65, 130])
+@pytest.mark.parametrize("edges,blocks", [(3000, 1), (90_000, 1), (900_000, 1), (90_000, 3)])
+def test_layer_products_of_ragged_width(f, edges, blocks):
+    """Products that no ReLU decides on (the last layer's, the backward ones) at widths that are no whole 16-byte pieces,
+    with short rows, with rows over several chunks, over column blocks; bias and activation in one pass."""
+    g = G()
+    n, f_in = 1501, 140
+    rs = np.random.default_rng(90)
+    src = rs.integers(0, n, edges).astype(np.int32)
+    dst = (n * rs.random(edges) ** 3).astype(np.int32)
+    flags = g.ADD_SELF_LOOPS | g.NORM_ROW | g.BUILD_TRANSPOSE
+    a = g.gcn_csr_create(n, dev(src), dev(dst), flags)
+    g.gcn_csr_config(a, g.CFG_SPMM_BLOCKS, blocks)
+    A = oracle.build_csr(n, src, dst, symmetrise=False, norm="row")
+    At = oracle.transpose(A)
+    H, W = synth.normal_features(n, f_in, 92), synth.glorot_weights((f_in, f), 93)[0]
+    b, Gl, Zprev = synth.normal_features(1, f, 94)[0], synth.normal_features(n, f, 95), synth.normal_features(n, f_in, 96)
+    buf = torch.empty(n * f + 1, device="cuda")
+    for first in (0, 1):                                            # 16-byte aligned, and not
+        Z, Ho, T = buf[first:first + n * f].view(n, f), torch.empty(n, f, device="cuda"), torch.empty(n, f, device="cuda")
+        for act, name in ((g.ACT_NONE, "none"), (g.ACT_RELU, "relu")):
+            for bias in (None, b):
+                Z.fill_(float("nan")), Ho.fill_(float("nan"))
+                g.gcn_layer_forward(a, dev(H), dev(W), Z, Ho, T, g.ORDER_GEMM_FIRST, act, bias=None if bias is None else dev(bias))
+                Zref, Href = oracle.layer_forward(At, H, W, name, bias=bias)
+                assert_close(host(Z), Zref, f"Z {name}")
+                np.testing.assert_array_equal(host(Ho), host(Z) if name == "none" else np.maximum(host(Z), 0))
+    S, Y, Gp = torch.empty(n, f, device="cuda"), torch.empty(f_in, f, device="cuda"), torch.empty(n, f_in, device="cuda")
+    Sref, Yref, Gpref, _ = oracle.layer_backward(A, H, Zprev, W, Gl)
+    g.gcn_layer_backward(a, dev(H), dev(Zprev), dev(W), dev(Gl), None, S, Y, Gp, g.ORDER_GEMM_FIRST)
+    assert_close(host(S), Sref, "S = A G")
+    assert_close(host(Y), Yref, "Y")
+    assert_close(host(Gp), Gpref, "Gprev")
+    # the other direction and order: the products have the width of the input, the mask in their epilogue
+    Hw, Ww, Gw = synth.normal_features(n, f, 97), synth.glorot_weights((f, 20), 98)[0], synth.normal_features(n, 20, 99)
+    Zp = synth.normal_features(n, f, 100)
+    T, Z, S = torch.empty(n, f, device="cuda"), torch.empty(n, 20, device="cuda"), torch.empty(n, f, device="cuda")
+    Y, Gp = torch.empty(f, 20, device="cuda"), torch.full((n, f), float("nan"), device="cuda")
+    g.gcn_layer_forward(a, dev(Hw), dev(Ww), Z, None, T, g.ORDER_SPMM_FIRST, g.ACT_NONE)
+    assert_close(host(Z), oracle.layer_forward(At, Hw, Ww, "none")[0], "Z, sparse product first")
+    g.gcn_layer_backward(a, dev(Hw), dev(Zp), dev(Ww), dev(Gw), T, S, Y, Gp, g.ORDER_SPMM_FIRST)
+    _, Yref, Gpref, _ = oracle.layer_backward(A, Hw, Zp, Ww, Gw)
+    assert_close(host(Y), Yref, "Y, sparse product first")
+    assert_close(host(Gp), Gpref, "Gprev, sparse product first")
+    a.close()
