@@ -127,136 +127,186 @@ __device__ __forceinline__ void epilogue_store(float* z, const float* zprev, flo
     store_vec<VEC>(z, v);
 }
 
-// The work of one workgroup: the four chunks 4*grp .. 4*grp+3 of the matrix described by `a`.
-// s_col / s_val: the workgroup's staging arrays, [WAVES_PER_BLOCK][LDS_PER_WAVE] each (owned by the kernel,
-// so that two instantiations of this body in one kernel share them).
-template <int LPR, int VEC, int EPI, int UNR>
-__device__ __forceinline__ void split_body(const SplitArgs& a, int64_t grp, int32_t (*s_col)[LDS_PER_WAVE],
-                                           float (*s_val)[LDS_PER_WAVE]) {
-    constexpr int G = 64 / LPR;                 // lane groups per wavefront
-    constexpr int NW = SUBS_PER_CHUNK / G;      // flag words per group
-    static_assert(NW >= 1 && G > 1, "a group needs at least one flag word");
-    static_assert(UNR % 4 == 0 && SUB % UNR == 0, "gathers in flight per lane group");
+// Row `row` of a matrix whose rows are `pitch` bytes apart: one multiply-add of 32 by 32 bits.
+__device__ __forceinline__ const float* at_row(const float* base, uint32_t row, uint32_t pitch) {
+    return reinterpret_cast<const float*>(reinterpret_cast<const char*>(base) + (uint64_t)row * pitch);
+}
 
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t c = grp * WAVES_PER_BLOCK + wave;
-    if (c >= a.nchunks) return;                 // whole wavefront leaves; no block-wide barrier below
-    const int g = lane / LPR, li = lane % LPR;
-    int col0;
-    const bool col_ok = lane_columns<LPR, VEC>(a.f, blockIdx.y, gridDim.y, li, &col0);
-    const int64_t k0 = c * CHUNK;
-    const int64_t knext = k0 + CHUNK;
-    // (flags is padded by a chunk of zero words)
-    const bool continued = knext < a.nnz && !(a.flags[(c + 1) * SUBS_PER_CHUNK] & 1u);
-
-    // ---- stage the chunk's column indices and values in LDS (coalesced 16-byte loads) ----
-    int32_t* lc = s_col[wave];
-    float* lv = s_val[wave];
+// Stages a chunk's column indices and values in LDS (coalesced 16-byte loads); zeros past the end.
+__device__ __forceinline__ void stage_chunk(const SplitArgs& a, int64_t k0, int lane, int32_t* lc, float* lv) {
 #pragma unroll
     for (int t = 0; t < CHUNK / 256; ++t) {
         const int i = t * 256 + lane * 4;
         const int64_t k = k0 + i;
         int4 cc = make_int4(0, 0, 0, 0);
         float4 vv = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (!a.val) {                           // value-free: only the column stream is read
-            vv = make_float4(1.f, 1.f, 1.f, 1.f);
-            if (k + 4 <= a.nnz) {
-                cc = stream_load_i4(a.colidx + k);
-            } else {
-                if (k + 0 < a.nnz) cc.x = a.colidx[k + 0];
-                if (k + 1 < a.nnz) cc.y = a.colidx[k + 1];
-                if (k + 2 < a.nnz) cc.z = a.colidx[k + 2];
-            }
-        } else if (k + 4 <= a.nnz) {
+        if (k + 4 <= a.nnz) {
             cc = stream_load_i4(a.colidx + k);
-            vv = stream_load_f4(a.val + k);
+            if (a.val) vv = stream_load_f4(a.val + k);
         } else {
-            if (k + 0 < a.nnz) { cc.x = a.colidx[k + 0]; vv.x = a.val[k + 0]; }
-            if (k + 1 < a.nnz) { cc.y = a.colidx[k + 1]; vv.y = a.val[k + 1]; }
-            if (k + 2 < a.nnz) { cc.z = a.colidx[k + 2]; vv.z = a.val[k + 2]; }
+            if (k + 0 < a.nnz) { cc.x = a.colidx[k + 0]; if (a.val) vv.x = a.val[k + 0]; }
+            if (k + 1 < a.nnz) { cc.y = a.colidx[k + 1]; if (a.val) vv.y = a.val[k + 1]; }
+            if (k + 2 < a.nnz) { cc.z = a.colidx[k + 2]; if (a.val) vv.z = a.val[k + 2]; }
         }
         const int p = i + (i >> 5) * (SUB_STRIDE - SUB);
         *reinterpret_cast<int4*>(lc + p) = cc;
-        *reinterpret_cast<float4*>(lv + p) = vv;
+        if (a.val) *reinterpret_cast<float4*>(lv + p) = vv;
     }
+}
+
+// What a wavefront keeps in LDS for its chunk.
+template <int VEC>
+struct __attribute__((aligned(16))) WaveLds {
+    int32_t col[LDS_PER_WAVE];
+    float val[LDS_PER_WAVE];                    // values; of a value-free product the factors of the rows begun here
+    int32_t row[CHUNK];                         // the rows begun here; the sign bit says that their sum is stored raw
+    uint32_t flag[SUBS_PER_CHUNK + 4];
+    float head[64 * VEC];
+};
+
+// The work of one workgroup: the four chunks 4*grp .. 4*grp+3 of the matrix described by `a`.
+// lds: one block per wavefront (owned by the kernel, so that two instantiations of this body in one kernel share them).
+//
+// The walk is bound by instructions where X fits the caches, so it holds nothing but one multiply-add per address, the gather,
+// the sums and a test per entry: what a row needs when it ends (its number, its factor) is in LDS before the walk,
+// fetched into registers when the row starts, so that neither a start nor an end waits for memory (with these looked up at
+// the end of a row, every end drained the gathers in flight; and 64-bit row addresses took six instructions, four of
+// them multiplications).  With fewer than 16 lane groups the gathers of four entries are issued before the four before
+// them are summed; with 16 that many rows are in flight anyway, and where the L2s' request rate is the bound more of
+// them are slower (119 M entries over column blocks: 611 us, 620 with two sets).  12 M entries in rows of 236 at 64 columns, operand
+// in the L2s: 187 -> 168 us; 2 M at 32: 34 -> 27; 33 M, packed hub and rest at 16: 318 -> 293; 9 M in rows of 9 at
+// 32: 203 -> 200 (line fills).
+template <int LPR, int VEC, int EPI>
+__device__ __forceinline__ void split_body(const SplitArgs& a, int64_t grp, WaveLds<VEC>* lds) {
+    constexpr int G = 64 / LPR;                 // lane groups per wavefront
+    constexpr int LEN = CHUNK / G, NW = LEN / SUB;              // entries and flag words per group
+    constexpr int UNR = 4;                      // entries fetched together
+    static_assert(NW >= 1 && G > 1, "a group needs at least one flag word");
+
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t c = grp * WAVES_PER_BLOCK + wave;
+    if (c >= a.nchunks) return;                 // whole wavefront leaves; no block-wide barrier below
+    const int g = lane / LPR, li = lane % LPR;
+    int col0;
+    const bool col_ok = lane_columns<LPR, VEC>(a.f, blockIdx.y, gridDim.y, li, &col0);
+    const int64_t k0 = c * CHUNK, j0 = c * SUBS_PER_CHUNK;
+    const int nk = a.nnz - k0 < CHUNK ? (int)(a.nnz - k0) : CHUNK;
+    WaveLds<VEC>& L = lds[wave];
+
+    // ---- stage the chunk: indices, values, flags, the rows begun here ----
+    uint32_t word = 0;
+    if (lane <= SUBS_PER_CHUNK) word = a.flags[j0 + lane];      // padded by a chunk of zero words
+    const int32_t q0 = a.sub_row[j0];           // row of the chunk's first entry
+    int at = a.sub_row[j0 + g * NW];            // and of this group's first
+    stage_chunk(a, k0, lane, L.col, L.val);
+    if (lane <= SUBS_PER_CHUNK) L.flag[lane] = word;
+    const int32_t q1 = q0 + 1 - (int32_t)(__builtin_amdgcn_readfirstlane(word) & 1u);       // the first row begun here
     // each wavefront reads only what it wrote; LDS operations of one wavefront complete in order
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    int begun = 0;                              // row starts of the chunk
+#pragma unroll
+    for (int w = 0; w < SUBS_PER_CHUNK; ++w) begun += __popc(L.flag[w]);
+    begun = __builtin_amdgcn_readfirstlane(begun);
+    at += 1 - (int)(L.flag[g * NW] & 1u) - q1;  // row starts of the chunk before this group's slice
+    for (int i = lane; i < begun; i += 64) {
+        const int32_t row = a.ne_rows ? a.ne_rows[q1 + i] : q1 + i;
+        const bool raw = a.defer && a.defer[row];
+        L.row[i] = row | (raw ? (int32_t)0x80000000 : 0);
+        if (!a.val) L.val[i] = a.row_scale && !raw ? a.row_scale[row] : 1.f;
+    }
+    const bool continued = k0 + CHUNK < a.nnz && !(L.flag[SUBS_PER_CHUNK] & 1u);
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     __builtin_amdgcn_wave_barrier();
 
     // ---- walk this group's slice ----
-    const int64_t j0 = c * SUBS_PER_CHUNK + (int64_t)g * NW;
-    int32_t q = a.sub_row[j0];
-    uint32_t first = a.flags[j0];
-    q -= (int32_t)(first & 1u);                 // a start bit at the very first entry re-increments q
-    float acc[VEC], head[VEC];
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) { acc[e] = 0.f; head[e] = 0.f; }
+    float acc[VEC] = {}, m[VEC] = {};
     bool owned = false;                         // has this group seen a row start yet?
-    const float* xbase = a.X + col0;
-
-    for (int w = 0; w < NW; ++w) {
-        const int64_t j = j0 + w;
-        uint32_t mask = (w == 0) ? first : a.flags[j];
-        const int64_t left = a.nnz - j * SUB;
-        const int cnt = left >= SUB ? SUB : (left > 0 ? (int)left : 0);
-        const int base = (g * NW + w) * SUB_STRIDE;
-        for (int b = 0; b < cnt; b += UNR) {
-            int32_t cs[UNR];
-            float vs[UNR];
+    int32_t row = 0;
+    float scale = 1.f;
+    const float* const xbase = a.X + col0;
+    const uint32_t xpitch = (uint32_t)a.ldx * 4u, zpitch = (uint32_t)a.ldz * 4u, mpitch = (uint32_t)a.ldzprev * 4u;
+    auto z_row = [&]() { return const_cast<float*>(at_row(a.Z + col0, (uint32_t)row & 0x7fffffffu, zpitch)); };
+    auto store_row = [&]() {
+        float v[VEC];
 #pragma unroll
-            for (int h = 0; h < UNR / 4; ++h) {
-                const int4 cc = *reinterpret_cast<const int4*>(lc + base + b + 4 * h);
-                const float4 vv = *reinterpret_cast<const float4*>(lv + base + b + 4 * h);
-                cs[4 * h] = cc.x; cs[4 * h + 1] = cc.y; cs[4 * h + 2] = cc.z; cs[4 * h + 3] = cc.w;
-                vs[4 * h] = vv.x; vs[4 * h + 1] = vv.y; vs[4 * h + 2] = vv.z; vs[4 * h + 3] = vv.w;
-            }
-            float x[UNR][VEC];
+        for (int u = 0; u < VEC; ++u) v[u] = acc[u] * scale;    // exact for scale = 1, which a raw sum has
+        if constexpr (EPI == GCN_EPI_RELU) {
 #pragma unroll
-            for (int e = 0; e < UNR; ++e) {
-                if (b + e < cnt && col_ok) load_vec<VEC>(x[e], xbase + (int64_t)cs[e] * a.ldx);
-                else {
+            for (int u = 0; u < VEC; ++u) v[u] = v[u] > 0.f || row < 0 ? v[u] : 0.f;
+        } else if constexpr (EPI == GCN_EPI_MASK) {
 #pragma unroll
-                    for (int v = 0; v < VEC; ++v) x[e][v] = 0.f;
-                }
-            }
+            for (int u = 0; u < VEC; ++u) v[u] = m[u] > 0.f || row < 0 ? v[u] : 0.f;
+        }
+        store_vec<VEC>(z_row(), v);
+    };
+    auto start_row = [&]() {                    // an entry starts a row: close the fragment before it
+        if (owned) store_row();
+        else {
 #pragma unroll
-            for (int e = 0; e < UNR; ++e) {
-                if (b + e < cnt) {
-                    if (mask & 1u) {            // entry starts a row: close the fragment before it
-                        if (owned) {
-                            if (col_ok) {
-                                const int64_t row = a.ne_rows ? a.ne_rows[q] : q;
-                                epilogue_store<VEC, EPI>(a.Z + row * a.ldz + col0,
-                                                         EPI == GCN_EPI_MASK ? a.Zprev + row * a.ldzprev + col0 : nullptr,
-                                                         acc, a.row_scale ? a.row_scale[row] : 1.f,
-                                                         a.defer && a.defer[row]);
-                            }
-                        } else {
+            for (int u = 0; u < VEC; ++u) L.head[lane * VEC + u] = acc[u];
+        }
+        owned = true;
+        row = L.row[at];
+        if (!a.val) scale = L.val[at];
+        if constexpr (EPI == GCN_EPI_MASK) load_vec<VEC>(m, at_row(a.Zprev + col0, (uint32_t)row & 0x7fffffffu, mpitch));
+        at += 1;
 #pragma unroll
-                            for (int v = 0; v < VEC; ++v) head[v] = acc[v];
-                            owned = true;
-                        }
-                        q += 1;
+        for (int u = 0; u < VEC; ++u) acc[u] = 0.f;
+    };
+    auto fetch = [&](int p, float (&x)[UNR][VEC]) {             // past the end: row 0
+        const int4 cc = *reinterpret_cast<const int4*>(L.col + p + p / SUB * (SUB_STRIDE - SUB));
+        load_vec<VEC>(x[0], at_row(xbase, (uint32_t)cc.x, xpitch));
+        load_vec<VEC>(x[1], at_row(xbase, (uint32_t)cc.y, xpitch));
+        load_vec<VEC>(x[2], at_row(xbase, (uint32_t)cc.z, xpitch));
+        load_vec<VEC>(x[3], at_row(xbase, (uint32_t)cc.w, xpitch));
+    };
+    auto sums = [&](int p, const float (&x)[UNR][VEC], int end) {
+        const uint32_t bits = L.flag[p / SUB] >> (p % SUB);
+        float vs[UNR] = {1.f, 1.f, 1.f, 1.f};
+        if (a.val) {
+            const float4 vv = *reinterpret_cast<const float4*>(L.val + p + p / SUB * (SUB_STRIDE - SUB));
+            vs[0] = vv.x; vs[1] = vv.y; vs[2] = vv.z; vs[3] = vv.w;
+        }
 #pragma unroll
-                        for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
-                    }
-                    mask >>= 1;
+        for (int e = 0; e < UNR; ++e) {
+            if (p + e < end) {
+                if (bits >> e & 1u) start_row();
 #pragma unroll
-                    for (int v = 0; v < VEC; ++v) acc[v] = fmaf(vs[e], x[e][v], acc[v]);
-                }
+                for (int u = 0; u < VEC; ++u) acc[u] = fmaf(vs[e], x[e][u], acc[u]);
             }
         }
+    };
+    if (col_ok) {
+        float xa[UNR][VEC], xb[UNR][VEC];
+        const int from = g * LEN, to = from + LEN;
+        if (LPR > 4 && nk == CHUNK) {
+            fetch(from, xa);
+#pragma unroll 1
+            for (int p = from; p < to; p += 2 * UNR) {
+                fetch(p + UNR, xb);
+                sums(p, xa, CHUNK);
+                if (p + 2 * UNR < to) fetch(p + 2 * UNR, xa);
+                sums(p + UNR, xb, CHUNK);
+            }
+        } else if (nk == CHUNK) {
+#pragma unroll 1
+            for (int p = from; p < to; p += UNR) { fetch(p, xa); sums(p, xa, CHUNK); }
+        } else {                                // the last chunk
+#pragma unroll 1
+            for (int p = from; p < to; p += UNR) { fetch(p, xa); sums(p, xa, nk); }
+        }
     }
-    if (!owned) {                               // the whole slice lies inside one row
+    float R[VEC], T[VEC];                       // R: the entries before the first row start, all of them without one
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) { head[v] = acc[v]; acc[v] = 0.f; }
+    for (int v = 0; v < VEC; ++v) {
+        R[v] = owned ? L.head[lane * VEC + v] : acc[v];
+        if (!owned) acc[v] = 0.f;
+        T[v] = 0.f;
     }
+    int stop = owned ? 1 : 0, stop_next = 0;
 
     // ---- join fragments across groups: R_g = head_g + (owned_g ? 0 : R_{g+1}) ----
-    float R[VEC];
-#pragma unroll
-    for (int v = 0; v < VEC; ++v) R[v] = head[v];
-    int stop = owned ? 1 : 0;
 #pragma unroll
     for (int d = 1; d < G; d <<= 1) {
         float Rp[VEC];
@@ -269,10 +319,9 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int64_t grp, int3
             stop = sp;
         }
     }
-    float T[VEC];
 #pragma unroll
     for (int v = 0; v < VEC; ++v) T[v] = __shfl_down(R[v], LPR, 64);
-    int stop_next = __shfl_down(stop, LPR, 64);
+    stop_next = __shfl_down(stop, LPR, 64);
     if (g == G - 1) {
 #pragma unroll
         for (int v = 0; v < VEC; ++v) T[v] = 0.f;
@@ -284,20 +333,15 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int64_t grp, int3
         // the row opened last in this slice: add what later groups of this wavefront hold for it
 #pragma unroll
         for (int v = 0; v < VEC; ++v) acc[v] += T[v];
-        const bool runs_on = !stop_next && continued;
-        const int64_t row = a.ne_rows ? a.ne_rows[q] : q;
-        if (runs_on) store_vec<VEC>(a.Z + row * a.ldz + col0, acc);     // finished by k_spmm_fixup
-        else epilogue_store<VEC, EPI>(a.Z + row * a.ldz + col0,
-                                      EPI == GCN_EPI_MASK ? a.Zprev + row * a.ldzprev + col0 : nullptr, acc,
-                                      a.row_scale ? a.row_scale[row] : 1.f, a.defer && a.defer[row]);
+        if (!stop_next && continued) store_vec<VEC>(z_row(), acc);      // finished by k_spmm_fixup
+        else store_row();
     }
 }
 
-template <int LPR, int VEC, int EPI, int UNR>
+template <int LPR, int VEC, int EPI>
 __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_split(SplitArgs a) {
-    __shared__ int32_t s_col[WAVES_PER_BLOCK][LDS_PER_WAVE];
-    __shared__ float s_val[WAVES_PER_BLOCK][LDS_PER_WAVE];
-    split_body<LPR, VEC, EPI, UNR>(a, blockIdx.x, s_col, s_val);
+    __shared__ WaveLds<VEC> lds[WAVES_PER_BLOCK];
+    split_body<LPR, VEC, EPI>(a, blockIdx.x, lds);
 }
 
 // The same product for matrices of few chunks, which is a chain of memory latencies, launches and first executions of
@@ -799,11 +843,10 @@ template <int LPR, int VEC, int EPI>
 __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_split_pair(SplitArgs a, SplitArgs b, int ra, int rb) {
     // ra + rb == 8.  Workgroups go to the eight XCDs round-robin; the rotation by q lets every XCD see
     // both kinds of work in turn.
-    __shared__ int32_t s_col[WAVES_PER_BLOCK][LDS_PER_WAVE];
-    __shared__ float s_val[WAVES_PER_BLOCK][LDS_PER_WAVE];
+    __shared__ WaveLds<VEC> lds[WAVES_PER_BLOCK];
     const unsigned q = blockIdx.x / 8, r = (blockIdx.x + q) % 8;
-    if ((int)r < ra) split_body<LPR, VEC, EPI, 4>(a, (int64_t)q * ra + r, s_col, s_val);
-    else split_body<LPR, VEC, GCN_EPI_NONE, 4>(b, (int64_t)q * rb + (r - ra), s_col, s_val);
+    if ((int)r < ra) split_body<LPR, VEC, EPI>(a, (int64_t)q * ra + r, lds);
+    else split_body<LPR, VEC, GCN_EPI_NONE>(b, (int64_t)q * rb + (r - ra), lds);
 }
 
 // Adds, in ascending chunk order, the carries of the chunks a row runs on into, then applies the epilogue.  One LPR-lane
@@ -895,16 +938,14 @@ __global__ void k_spmm_rowwise(int64_t n, const int64_t* __restrict__ rowptr, co
     Z[i * ldz + j] = acc;
 }
 
-// Dynamic LDS on top of the kernel's own 18 KB, to lower the number of resident workgroups.  The kernels
-// with 16 lane groups per wavefront (rows of up to 64 bytes) keep 64 gathers in flight per wavefront; at
-// full occupancy they run slower than with about two thirds of it (measured on config 3: 18 KB per
-// workgroup 0.66 / 0.57 ms valued / value-free, 28 KB 0.58 / 0.55 ms, 32 KB 0.61 / 0.58 ms; plain kernel
-// on config 4 4.40 -> 4.10 ms; long rows of config 5 -0.1 ms).  The 8-group kernels (config 2: 1.44 ->
-// 1.59 ms at half occupancy) and the paired launch (config 4: 3.15 -> 3.34 ms) want it all.
-static size_t occupancy_pad(int lpr, int lds_kb) {
-    if (lpr != 4) return 0;
-    const size_t own = 2 * sizeof(int32_t) * WAVES_PER_BLOCK * LDS_PER_WAVE;     // s_col + s_val
-    const size_t want = (size_t)lds_kb * 1024;
+// Dynamic LDS on top of the kernel's own, to lower the number of resident workgroups.  The kernels with 16 lane groups
+// per wavefront (rows of up to 64 bytes) keep 64 gathers in flight per wavefront and run slower with eight workgroups
+// per compute unit than with five (119 M entries at 16 columns: 0.64 -> 0.62 ms), which the 31 KB of the 16-byte kernel
+// leave by themselves; the one-float kernel takes four (102 M entries at one column: 612 -> 588 us).
+template <int LPR, int VEC>
+static size_t occupancy_pad(int lds_kb) {
+    if (LPR != 4) return 0;
+    const size_t own = VEC == 1 ? (size_t)18 << 10 : WAVES_PER_BLOCK * sizeof(WaveLds<VEC>), want = (size_t)lds_kb << 10;
     return want > own ? want - own : 0;
 }
 
@@ -928,23 +969,6 @@ static int fixup_of(const SplitArgs& args, int epilogue, hipStream_t s) {
     return launch_fixup<LPR, VEC>(args, epilogue, s);
 }
 
-template <int LPR, int VEC, int UNR>
-static int launch_split_unr(const SplitArgs& args, int epilogue, hipStream_t s) {
-    const int tile = LPR * VEC;
-    const dim3 grid((unsigned)((args.nchunks + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK), (unsigned)((args.f + tile - 1) / tile));
-    const dim3 block(64 * WAVES_PER_BLOCK);
-    const size_t pad = occupancy_pad(LPR, args.lds_kb);
-    timing_begin(s);
-    switch (epilogue) {
-        case GCN_EPI_NONE: hipLaunchKernelGGL((k_spmm_split<LPR, VEC, GCN_EPI_NONE, UNR>), grid, block, pad, s, args); break;
-        case GCN_EPI_RELU: hipLaunchKernelGGL((k_spmm_split<LPR, VEC, GCN_EPI_RELU, UNR>), grid, block, pad, s, args); break;
-        default: hipLaunchKernelGGL((k_spmm_split<LPR, VEC, GCN_EPI_MASK, UNR>), grid, block, pad, s, args); break;
-    }
-    timing_end(s);
-    GCN_LAUNCH_CHECK();
-    return GCN_OK;
-}
-
 template <int LPR, int VEC>
 static int launch_split(const SplitArgs& args, int epilogue, hipStream_t s) {
     const int64_t panels = (args.f + LPR * VEC - 1) / (LPR * VEC), waves = args.nchunks * panels;
@@ -966,10 +990,18 @@ static int launch_split(const SplitArgs& args, int epilogue, hipStream_t s) {
             return fixup_of<LPR, VEC>(few, epilogue, s);
         }
     }
-    // Few wavefronts (less than four per SIMD) cannot hide the gathers' latency behind each other: there every lane group
-    // keeps 16 gathers in flight instead of 4.
-    if (waves < (int64_t)device_info().cus * 16) GCN_TRY((launch_split_unr<LPR, VEC, 16>(args, epilogue, s)));
-    else GCN_TRY((launch_split_unr<LPR, VEC, 4>(args, epilogue, s)));
+    const int tile = LPR * VEC;
+    const dim3 grid((unsigned)((args.nchunks + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK), (unsigned)((args.f + tile - 1) / tile));
+    const dim3 block(64 * WAVES_PER_BLOCK);
+    const size_t pad = (occupancy_pad<LPR, VEC>(args.lds_kb));
+    timing_begin(s);
+    switch (epilogue) {
+        case GCN_EPI_NONE: hipLaunchKernelGGL((k_spmm_split<LPR, VEC, GCN_EPI_NONE>), grid, block, pad, s, args); break;
+        case GCN_EPI_RELU: hipLaunchKernelGGL((k_spmm_split<LPR, VEC, GCN_EPI_RELU>), grid, block, pad, s, args); break;
+        default: hipLaunchKernelGGL((k_spmm_split<LPR, VEC, GCN_EPI_MASK>), grid, block, pad, s, args); break;
+    }
+    timing_end(s);
+    GCN_LAUNCH_CHECK();
     return fixup_of<LPR, VEC>(args, epilogue, s);
 }
 
@@ -1528,6 +1560,7 @@ int spmm_launch(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx, f
         return GCN_OK;
     }
     int algo = cfg.spmm_algo;
+    const bool far_rows = ldx >= (1ll << 30) || ldz >= (1ll << 30) || ldzprev >= (1ll << 30);
     const bool vec4_all = (f % 4 == 0) && (ldx % 4 == 0) && (ldz % 4 == 0) && aligned16(X) && aligned16(Z) &&
                           (epilogue != GCN_EPI_MASK || ((ldzprev % 4 == 0) && aligned16(Zprev)));
     const int64_t nblocks = choose_blocks(cfg, n, ncols, nnz, f, 24);
@@ -1543,6 +1576,7 @@ int spmm_launch(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx, f
         algo = (huge && vec4_all && nblocks < 2 && narrow_steps) ? 3 : 2;
     }
     if (algo == 3 && !vec4_all) algo = 2;
+    if (far_rows) algo = 1;              // rows 4 GB and more apart: the others compute row addresses by 32-bit factors
     if ((algo == 2 && cfg.spmm_algo == 0) || algo == 4) {
         // Hub schedule: for operands beyond the L2s when most entries sit in long rows and hot columns
         // (decided from the matrix itself when the copy is built; a rejected shape is remembered).
