@@ -409,7 +409,7 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_few(SplitArgs a) 
             const int base = (g * NW + w) * SUB_STRIDE;
             float x[SUB][VEC];
 #pragma unroll
-            for (int e = 0; e < SUB; ++e) load_vec<VEC>(x[e], xbase + (int64_t)lc[base + e] * a.ldx);   // past the end: row 0
+            for (int e = 0; e < SUB; ++e) load_vec<VEC>(x[e], at_row(xbase, (uint32_t)lc[base + e], (uint32_t)a.ldx * 4u));   // past the end: row 0
 #pragma unroll
             for (int e = 0; e < SUB; ++e)
                 lx[e * 64] = e < cnt ? make_float4(x[e][0], x[e][1], x[e][2], x[e][3]) : make_float4(0.f, 0.f, 0.f, 0.f);
@@ -512,6 +512,20 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_few(SplitArgs a) 
 // ends, and with at most SHORT_ROW entries it has three pieces, F + (H1 + H2), or (F + H1) + H2 when H2 is in the
 // next chunk.  1000 rows of 17 entries at 16 columns: 6.3 us; k_spmm_few 7.7;
 // k_spmm_split 9.7 and k_spmm_fixup 3.9.
+// The value of lane `l` of every group of LPR lanes (l a constant once the loop around is unrolled).
+template <int LPR>
+__device__ __forceinline__ int group_lane(int x, int l) {
+    if constexpr (LPR == 4) {                   // inside four lanes without the LDS
+        switch (l) {
+            case 0: return __builtin_amdgcn_mov_dpp(x, 0x00, 0xf, 0xf, true);
+            case 1: return __builtin_amdgcn_mov_dpp(x, 0x55, 0xf, 0xf, true);
+            case 2: return __builtin_amdgcn_mov_dpp(x, 0xaa, 0xf, 0xf, true);
+            default: return __builtin_amdgcn_mov_dpp(x, 0xff, 0xf, 0xf, true);
+        }
+    }
+    return __shfl(x, l, LPR);
+}
+
 static constexpr int SHORT_ROW = 64;
 
 template <int LPR, int SLICE, int EPI>
@@ -549,12 +563,12 @@ __global__ __launch_bounds__(64) void k_spmm_short(SplitArgs a, int64_t nrows) {
         float x[U][VEC];
 #pragma unroll
         for (int e = 0; e < U; ++e) {
-            const int32_t col = __shfl(c[e / LPR], e % LPR, LPR);          // past the end: row 0, not used
-            load_vec<VEC>(x[e], xbase + (int64_t)col * a.ldx);
+            const int32_t col = group_lane<LPR>(c[e / LPR], e % LPR);      // past the end: row 0, not used
+            load_vec<VEC>(x[e], at_row(xbase, (uint32_t)col, (uint32_t)a.ldx * 4u));
         }
 #pragma unroll
         for (int e = 0; e < U; ++e) {
-            const float ve = __shfl(v[e / LPR], e % LPR, LPR);
+            const float ve = __int_as_float(group_lane<LPR>(__float_as_int(v[e / LPR]), e % LPR));
             const int k = base + e;
             if (k < len) {
                 if (k == b1) {
@@ -654,7 +668,7 @@ __global__ __launch_bounds__(256, 3) void k_spmm_ragged(SplitArgs a, int lanes) 
 #pragma unroll
             for (int i = 0; i < NE; ++i) {
                 const int e = grp + i * groups;
-                if (works && e < cnt) load_vec<VEC>(x[i], xbase + (int64_t)s_col[e] * a.ldx);
+                if (works && e < cnt) load_vec<VEC>(x[i], at_row(xbase, (uint32_t)s_col[e], (uint32_t)a.ldx * 4u));
             }
 #pragma unroll
             for (int i = 0; i < NE; ++i) {
@@ -1193,7 +1207,7 @@ __global__ __launch_bounds__(64) void k_spmm_sweep(SweepArgs a, int64_t first_ta
                 const int rr = __shfl(r[u], src, 64);
                 rs[q] = cs >= 0 ? rr : -1;
                 if (rs[q] >= 0 && col_ok) {
-                    const float4 w4 = *reinterpret_cast<const float4*>(xbase + (int64_t)cs * a.ldx);
+                    const float4 w4 = *reinterpret_cast<const float4*>(at_row(xbase, (uint32_t)cs, (uint32_t)a.ldx * 4u));
                     x[q][0] = w4.x; x[q][1] = w4.y; x[q][2] = w4.z; x[q][3] = w4.w;
                 } else {
                     x[q][0] = x[q][1] = x[q][2] = x[q][3] = 0.f;
