@@ -40,6 +40,7 @@ struct SplitArgs {
     const int4* fix_list;     // the rows that cross chunks: n_fix of them (see build_fix_list)
     int64_t n_fix, n_fix_long;  // the first n_fix_long of them cover a whole further chunk
     int64_t nnz, nsub, nchunks;
+    int64_t n_ne = 0;         // rows that have entries
     int32_t f;
     const float* X;
     int64_t ldx;
@@ -68,9 +69,14 @@ __device__ __forceinline__ float4 stream_load_f4(const float* p) {
 // and leading dimension.
 struct __attribute__((packed, aligned(4))) f4u { float x, y, z, w; };
 
+struct __attribute__((packed, aligned(4))) f2u { float x, y; };
+
 template <int VEC>
 __device__ __forceinline__ void load_vec(float (&d)[VEC], const float* p) {
-    if constexpr (VEC == 4) {
+    if constexpr (VEC == 2) {
+        const f2u v = *reinterpret_cast<const f2u*>(p);
+        d[0] = v.x; d[1] = v.y;
+    } else if constexpr (VEC == 4) {
         const f4u v = *reinterpret_cast<const f4u*>(p);
         d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
     } else {
@@ -80,7 +86,9 @@ __device__ __forceinline__ void load_vec(float (&d)[VEC], const float* p) {
 
 template <int VEC>
 __device__ __forceinline__ void store_vec(float* p, const float (&d)[VEC]) {
-    if constexpr (VEC == 4) {
+    if constexpr (VEC == 2) {
+        *reinterpret_cast<f2u*>(p) = f2u{d[0], d[1]};
+    } else if constexpr (VEC == 4) {
         *reinterpret_cast<f4u*>(p) = f4u{d[0], d[1], d[2], d[3]};
     } else {
         *p = d[0];
@@ -96,10 +104,10 @@ template <int LPR, int VEC>
 __device__ __forceinline__ bool lane_columns(int f, int y, int ny, int li, int* col0) {
     constexpr int W = LPR * VEC;
     int first = y * W, end = first + W < f ? first + W : f;
-    if constexpr (VEC == 4) {
-        const bool thin = ny > 1 && f - (ny - 1) * W < 4;
-        if (thin && y == ny - 1) first -= 4;
-        if (thin && y == ny - 2) end -= 4;
+    if constexpr (VEC > 1) {
+        const bool thin = ny > 1 && f - (ny - 1) * W < VEC;
+        if (thin && y == ny - 1) first -= VEC;
+        if (thin && y == ny - 2) end -= VEC;
     }
     const int c = first + li * VEC;
     *col0 = c + VEC <= end ? c : end - VEC;
@@ -596,13 +604,12 @@ __global__ __launch_bounds__(64) void k_spmm_short(SplitArgs a, int64_t nrows) {
                              a.row_scale ? a.row_scale[row] : 1.f, a.defer && a.defer[row]);
 }
 
-// Widths above 32 that are no multiple of four.  They used to run with one float per lane, a wavefront adding up a chunk of
-// 512 entries on its own, 164 bytes at a time for 41 columns.  Here a workgroup of 256 takes a chunk in two halves: all
+// Widths above 32 that are no multiple of four, few chunks.  They used to run with one float per lane, a wavefront adding up a
+// chunk of 512 entries on its own.  Here a workgroup of 256 takes a chunk in two halves: all
 // lanes fetch the half's rows of X (16 bytes per lane, `lanes` lanes per row, the last one repeating some columns) into LDS,
 // 16 rows per lane group in flight; then the lane groups take the rows of the result, one after another, and walk
 // their entries in LDS.  A row's part in a chunk stays one serial sum, as it was, so every sum keeps its order and
-// with it the sign that a ReLU further on may decide by.  41 columns, 0.6 M entries: 76 -> 33 us; 1.9 M: 121 -> 85
-// (k_spmm_ragged_many: 66 and 106).
+// with it the sign that a ReLU further on may decide by.  41 columns, 0.6 M entries: 76 -> 33 us.
 static constexpr int HALF = CHUNK / 2;
 
 template <int EPI>
@@ -741,112 +748,134 @@ __global__ __launch_bounds__(256, 3) void k_spmm_ragged(SplitArgs a, int lanes) 
     } else store_row(q, first + tid, acc);
 }
 
-// The same for many chunks, where there are enough of them to fill the GPU with one lane group (16 lanes, 64 columns) per
-// chunk: four chunks per wavefront, each walked from end to end, the indices of a flag word staged at a time and the
-// next ones fetched meanwhile.  (k_spmm_ragged leaves all but one of its lane groups idle where a row covers a chunk, and
-// that shows once the GPU is full.)  41 columns, 32 M entries: 1028 -> 927 us (k_spmm_ragged 1270).
-template <int EPI>
-__global__ __launch_bounds__(64) void k_spmm_ragged_many(SplitArgs a) {
-    constexpr int VEC = 4, LPR = 16, UNR = 8;
-    constexpr int GROUPS = 64 / LPR, PER = SUB / LPR;           // lane groups per wavefront, entries staged by a lane
-    __shared__ __align__(16) int32_t s_col[GROUPS][SUB_STRIDE];
-    __shared__ __align__(16) float s_val[GROUPS][SUB_STRIDE];
-    const int lane = threadIdx.x, li = lane & 15;
-    const int64_t c = (int64_t)blockIdx.x * 4 + (lane >> 4);
-    const bool active = c < a.nchunks;
-    int col0;
-    const bool col_ok = lane_columns<LPR, VEC>(a.f, blockIdx.y, gridDim.y, li, &col0) && active;
-    const int64_t k0 = c * CHUNK, j0 = c * SUBS_PER_CHUNK;
-    int32_t* const lc = s_col[lane / LPR];
-    float* const lv = s_val[lane / LPR];
-    const float* const xbase = a.X + col0;
-    bool continued = false;
-    int32_t q = 0;
-    uint32_t mask_next = 0;
-    int32_t cn[PER];
-    float vn[PER];
-    auto fetch = [&](int w) {                                   // flag word w of the chunk
-        const int64_t k = (j0 + w) * SUB + li * PER;
-        mask_next = active ? a.flags[j0 + w] : 0u;
+// The same for more chunks: one wavefront per chunk and panel of 64 * VEC columns, a row of X per instruction.  An entry is
+// the same for all lanes, so its index, value, row address and the test for a row start are scalar work (indices and
+// values come through the scalar cache, 16 at a time, nothing is staged), and the vector unit has one multiply-add per entry
+// and column.  The rows of 16 entries are on their way while the 16 before them are summed.  The rows begun in the chunk are
+// kept 64 at a time, one per lane.  Bound by the L2s' rate or line fills where there are a few thousand chunks.  41 columns, 1.9 M
+// entries: 85 -> 57 us (16 lanes of 16 bytes per chunk, four chunks per wavefront), 12 M: 236 -> 196, 33 M: 918 -> 897; 67
+// columns, 33 M: 1.71 -> 1.32 ms.
+template <int VEC, int EPI>
+__global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_line(SplitArgs a) {
+    typedef int32_t i16v __attribute__((ext_vector_type(16)));
+    typedef float f16v __attribute__((ext_vector_type(16)));
+    typedef const __attribute__((address_space(4))) int32_t* ConstI;        // read-only while the kernel runs
+    typedef const __attribute__((address_space(4))) float* ConstF;
+    typedef const __attribute__((address_space(4))) i16v* ConstI16;
+    typedef const __attribute__((address_space(4))) f16v* ConstF16;
+    typedef const __attribute__((address_space(1))) char* Global;
+    constexpr int UNR = 16;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t c = (int64_t)blockIdx.x * WAVES_PER_BLOCK + wave;
+    if (c >= a.nchunks) return;
+    int col0;                                   // (lanes without columns follow the last one that has some)
+    const bool col_ok = lane_columns<64, VEC>(a.f, blockIdx.y, gridDim.y, lane, &col0);
+    const int64_t k0 = c * CHUNK;
+    const int nk = a.nnz - k0 < CHUNK ? (int)(a.nnz - k0) : CHUNK;
+    const ConstI cols = (ConstI)(uintptr_t)(a.colidx + k0), flags = (ConstI)(uintptr_t)(a.flags + c * SUBS_PER_CHUNK);
+    const ConstF vals = (ConstF)(uintptr_t)(a.val ? a.val + k0 : nullptr);
+    const bool continued = k0 + CHUNK < a.nnz && !(flags[SUBS_PER_CHUNK] & 1);     // (padded by a chunk of zero words)
+    const uint32_t xpitch = (uint32_t)a.ldx * 4u, zpitch = (uint32_t)a.ldz * 4u, mpitch = (uint32_t)a.ldzprev * 4u;
+    // rows begun here: numbers and factors of 64 of them
+    const int32_t q1 = ((ConstI)(uintptr_t)a.sub_row)[c * SUBS_PER_CHUNK] + 1 - (flags[0] & 1);
+    int32_t rows = 0, at = 0, named = 0;      // 64 rows from the named-th on
+    float factors = 1.f;
+    auto name_rows = [&]() {
+        const int64_t q = (int64_t)q1 + at + lane, last = a.n_ne - 1;
+        rows = (int32_t)(q < last ? q : last);
+        if (a.ne_rows) rows = a.ne_rows[rows];
+        const bool raw = a.defer && a.defer[rows];
+        factors = a.row_scale && !raw ? a.row_scale[rows] : 1.f;
+        rows |= raw ? (int32_t)0x80000000 : 0;
+        asm volatile("" : "+v"(rows), "+v"(factors));        // fetched here, so that no later use has to wait for memory
+        named = at;
+    };
+    name_rows();
+    float acc[VEC] = {}, head[VEC] = {}, m[VEC] = {};
+    bool owned = false;
+    int32_t row = 0;
+    float scale = 1.f;
+    auto z_row = [&]() { return const_cast<float*>(at_row(a.Z, (uint32_t)row & 0x7fffffffu, zpitch)) + (uint32_t)col0; };
+    auto store_row = [&]() {
+        if (!col_ok) return;
+        float v[VEC];
 #pragma unroll
-        for (int t = 0; t < PER; ++t) { cn[t] = 0; vn[t] = 1.f; }
-        if (!active) return;
-        if (k + PER <= a.nnz) {
-            const int2 x = *reinterpret_cast<const int2*>(a.colidx + k);
-            cn[0] = x.x; cn[1] = x.y;
-            if (a.val) {
-                const float2 y = *reinterpret_cast<const float2*>(a.val + k);
-                vn[0] = y.x; vn[1] = y.y;
-            }
-        } else {
+        for (int u = 0; u < VEC; ++u) v[u] = acc[u] * scale;    // exact for scale = 1, which a raw sum has
+        if constexpr (EPI == GCN_EPI_RELU) {
 #pragma unroll
-            for (int t = 0; t < PER; ++t)
-                if (k + t < a.nnz) { cn[t] = a.colidx[k + t]; if (a.val) vn[t] = a.val[k + t]; }
+            for (int u = 0; u < VEC; ++u) v[u] = v[u] > 0.f || row < 0 ? v[u] : 0.f;
+        } else if constexpr (EPI == GCN_EPI_MASK) {
+#pragma unroll
+            for (int u = 0; u < VEC; ++u) v[u] = m[u] > 0.f || row < 0 ? v[u] : 0.f;
+        }
+        store_vec<VEC>(z_row(), v);
+    };
+    auto start_row = [&]() {
+        if (owned) store_row();
+        else {
+#pragma unroll
+            for (int u = 0; u < VEC; ++u) head[u] = acc[u];
+        }
+        owned = true;
+        row = __builtin_amdgcn_readlane(rows, at - named);
+        scale = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(factors), at - named));
+        if constexpr (EPI == GCN_EPI_MASK) load_vec<VEC>(m, at_row(a.Zprev, (uint32_t)row & 0x7fffffffu, mpitch) + (uint32_t)col0);
+        at += 1;
+#pragma unroll
+        for (int u = 0; u < VEC; ++u) acc[u] = 0.f;
+    };
+    auto load_x = [&](float (&x)[VEC], int32_t j) {             // a scalar address, the lane's column as the offset
+        uint64_t row = (uint64_t)(uintptr_t)a.X + (uint64_t)(uint32_t)j * xpitch;
+        uint32_t column = (uint32_t)col0 * 4u;
+        asm("" : "+s"(row), "+v"(column));
+        load_vec<VEC>(x, (const float*)(const Global)((const Global)row + column));
+    };
+    auto fetch = [&](int p, float (&x)[UNR][VEC]) {
+        const i16v cc = *(ConstI16)(cols + p);
+#pragma unroll
+        for (int e = 0; e < UNR; ++e) load_x(x[e], cc[e]);
+    };
+    auto sums = [&](int p, const float (&x)[UNR][VEC]) {
+        const uint32_t bits = (uint32_t)flags[p / SUB] >> (p % SUB);
+        f16v vv;
+        if (vals) vv = *(ConstF16)(vals + p);
+        else {
+#pragma unroll
+            for (int e = 0; e < UNR; ++e) vv[e] = 1.f;
+        }
+        if (at - named + UNR > 64) name_rows();
+#pragma unroll
+        for (int e = 0; e < UNR; ++e) {
+            if (bits >> e & 1u) start_row();
+#pragma unroll
+            for (int u = 0; u < VEC; ++u) acc[u] = fmaf(vv[e], x[e][u], acc[u]);
         }
     };
-    if (active) {
-        continued = k0 + CHUNK < a.nnz && !(a.flags[(c + 1) * SUBS_PER_CHUNK] & 1u);
-        q = a.sub_row[j0];
+    float xa[UNR][VEC], xb[UNR][VEC];
+    int p = 0;
+    if (UNR <= nk) fetch(0, xa);
+#pragma unroll 1
+    for (; p + 2 * UNR <= nk; p += 2 * UNR) {
+        fetch(p + UNR, xb);
+        sums(p, xa);
+        if (p + 3 * UNR <= nk) fetch(p + 2 * UNR, xa);
+        sums(p + UNR, xb);
     }
-    fetch(0);
-    q -= (int32_t)(mask_next & 1u);             // a start bit at the very first entry re-increments q
-    float acc[VEC] = {}, head[VEC] = {};
-    bool owned = false;
-    for (int w = 0; w < SUBS_PER_CHUNK; ++w) {
-        uint32_t mask = mask_next;
-        const int64_t left = active ? a.nnz - (j0 + w) * SUB : 0;
-        const int cnt = left >= SUB ? SUB : (left > 0 ? (int)left : 0);
+    if (p + UNR <= nk) { sums(p, xa); p += UNR; }
+#pragma unroll 1
+    for (; p < nk; ++p) {                       // the end of the last chunk
+        float x[VEC];
+        load_x(x, cols[p]);
+        if (at - named == 64) name_rows();
+        if ((uint32_t)flags[p / SUB] >> (p % SUB) & 1u) start_row();
 #pragma unroll
-        for (int t = 0; t < PER; ++t) { lc[li * PER + t] = cn[t]; lv[li * PER + t] = vn[t]; }
-        // LDS operations of one wavefront complete in order; the fences keep the compiler to it
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        if (w + 1 < SUBS_PER_CHUNK) fetch(w + 1);
-        for (int b = 0; b < cnt; b += UNR) {
-            float x[UNR][VEC], v[UNR];
-#pragma unroll
-            for (int e = 0; e < UNR; ++e) {
-                v[e] = lv[b + e];
-                load_vec<VEC>(x[e], xbase + (int64_t)lc[b + e] * a.ldx);    // past the end: row 0, not used
-            }
-#pragma unroll
-            for (int e = 0; e < UNR; ++e) {
-                if (b + e < cnt) {
-                    if (mask & 1u) {            // entry starts a row: close the fragment before it
-                        if (owned) {
-                            if (col_ok) {
-                                const int64_t row = a.ne_rows ? a.ne_rows[q] : q;
-                                epilogue_store<VEC, EPI>(a.Z + row * a.ldz + col0,
-                                                         EPI == GCN_EPI_MASK ? a.Zprev + row * a.ldzprev + col0 : nullptr,
-                                                         acc, a.row_scale ? a.row_scale[row] : 1.f,
-                                                         a.defer && a.defer[row]);
-                            }
-                        } else {
-#pragma unroll
-                            for (int u = 0; u < VEC; ++u) head[u] = acc[u];
-                            owned = true;
-                        }
-                        q += 1;
-#pragma unroll
-                        for (int u = 0; u < VEC; ++u) acc[u] = 0.f;
-                    }
-                    mask >>= 1;
-#pragma unroll
-                    for (int u = 0; u < VEC; ++u) acc[u] = fmaf(v[e], x[e][u], acc[u]);
-                }
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+        for (int u = 0; u < VEC; ++u) acc[u] = fmaf(vals ? vals[p] : 1.f, x[u], acc[u]);
     }
     if (!col_ok) return;
-    store_vec<VEC>(a.carry + c * a.f + col0, owned ? head : acc);        // without a row start the whole chunk is inside one row
+    store_vec<VEC>(a.carry + c * a.f + col0, owned ? head : acc);       // without a row start the whole chunk is inside one row
     if (owned) {
-        const int64_t row = a.ne_rows ? a.ne_rows[q] : q;
-        if (continued) store_vec<VEC>(a.Z + row * a.ldz + col0, acc);     // finished by k_spmm_fixup
-        else epilogue_store<VEC, EPI>(a.Z + row * a.ldz + col0,
-                                      EPI == GCN_EPI_MASK ? a.Zprev + row * a.ldzprev + col0 : nullptr, acc,
-                                      a.row_scale ? a.row_scale[row] : 1.f, a.defer && a.defer[row]);
+        if (continued) store_vec<VEC>(z_row(), acc);            // finished by k_spmm_fixup
+        else store_row();
     }
 }
 
@@ -1019,25 +1048,38 @@ static int launch_split(const SplitArgs& args, int epilogue, hipStream_t s) {
     return fixup_of<LPR, VEC>(args, epilogue, s);
 }
 
+template <int VEC>
+static int launch_line(const SplitArgs& args, int epilogue, hipStream_t s) {
+    const dim3 grid((unsigned)((args.nchunks + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK), (unsigned)((args.f + 64 * VEC - 1) / (64 * VEC)));
+    const dim3 block(64 * WAVES_PER_BLOCK);
+    timing_begin(s);
+    switch (epilogue) {
+        case GCN_EPI_NONE: hipLaunchKernelGGL((k_spmm_line<VEC, GCN_EPI_NONE>), grid, block, 0, s, args); break;
+        case GCN_EPI_RELU: hipLaunchKernelGGL((k_spmm_line<VEC, GCN_EPI_RELU>), grid, block, 0, s, args); break;
+        default: hipLaunchKernelGGL((k_spmm_line<VEC, GCN_EPI_MASK>), grid, block, 0, s, args); break;
+    }
+    timing_end(s);
+    GCN_LAUNCH_CHECK();
+    return launch_fixup<16, 1>(args, epilogue, s);
+}
+
 static int launch_ragged(const SplitArgs& args, int epilogue, hipStream_t s) {
     const unsigned panels = (unsigned)((args.f + 63) / 64);
+    // k_spmm_ragged puts four wavefronts to a chunk: worth it while that is what fills the GPU (0.3 M entries at 41 columns,
+    // 620 chunks: 22 us, k_spmm_line 27; 1 M, 1900 chunks: 51 and 49; 0.4 M at 101, 1660 chunks and panels: 52 and 34).
+    if (args.nchunks * panels > (int64_t)device_info().cus * 4) {
+        // two columns per lane where that halves the number of panels: every panel walks all entries
+        if ((args.f + 127) / 128 * 2 == (int)panels) return launch_line<2>(args, epilogue, s);
+        return launch_line<1>(args, epilogue, s);
+    }
     timing_begin(s);
-    if (args.nchunks * panels <= (int64_t)device_info().cus * 16) {
-        const int lanes = args.f >= 64 ? 16 : (args.f + 3) / 4;
-        const dim3 grid((unsigned)args.nchunks, panels);
-        const size_t lds = (size_t)HALF * lanes * sizeof(float4);
-        switch (epilogue) {
-            case GCN_EPI_NONE: launch_lds<k_spmm_ragged<GCN_EPI_NONE>>(grid, 256, lds, s, args, lanes); break;
-            case GCN_EPI_RELU: launch_lds<k_spmm_ragged<GCN_EPI_RELU>>(grid, 256, lds, s, args, lanes); break;
-            default: launch_lds<k_spmm_ragged<GCN_EPI_MASK>>(grid, 256, lds, s, args, lanes); break;
-        }
-    } else {
-        const dim3 grid((unsigned)((args.nchunks + 3) / 4), panels);
-        switch (epilogue) {
-            case GCN_EPI_NONE: hipLaunchKernelGGL(k_spmm_ragged_many<GCN_EPI_NONE>, grid, dim3(64), 0, s, args); break;
-            case GCN_EPI_RELU: hipLaunchKernelGGL(k_spmm_ragged_many<GCN_EPI_RELU>, grid, dim3(64), 0, s, args); break;
-            default: hipLaunchKernelGGL(k_spmm_ragged_many<GCN_EPI_MASK>, grid, dim3(64), 0, s, args); break;
-        }
+    const int lanes = args.f >= 64 ? 16 : (args.f + 3) / 4;
+    const dim3 grid((unsigned)args.nchunks, panels);
+    const size_t lds = (size_t)HALF * lanes * sizeof(float4);
+    switch (epilogue) {
+        case GCN_EPI_NONE: launch_lds<k_spmm_ragged<GCN_EPI_NONE>>(grid, 256, lds, s, args, lanes); break;
+        case GCN_EPI_RELU: launch_lds<k_spmm_ragged<GCN_EPI_RELU>>(grid, 256, lds, s, args, lanes); break;
+        default: launch_lds<k_spmm_ragged<GCN_EPI_MASK>>(grid, 256, lds, s, args, lanes); break;
     }
     timing_end(s);
     GCN_LAUNCH_CHECK();
@@ -1366,6 +1408,7 @@ static int run_matrix(gcn_csr* a, Matrix& mm, const int32_t* row_map, int64_t nn
         }
         if (o.dry) return GCN_OK;
         args.colidx = b.colidx; args.val = o.pattern ? nullptr : b.val; args.flags = b.flags; args.sub_row = b.sub_row;
+        args.n_ne = b.nrows;
         args.ne_rows = nullptr; args.rp = b.rp; args.row_scale = nullptr;     // the scale belongs to the reduced row
         args.fix_list = b.fix_list; args.n_fix = b.n_fix; args.n_fix_long = b.n_fix_long;
         args.Z = a->partial; args.ldz = f; args.Zprev = nullptr; args.ldzprev = 0;
@@ -1383,6 +1426,7 @@ static int run_matrix(gcn_csr* a, Matrix& mm, const int32_t* row_map, int64_t nn
     args.row_scale = o.row_scale;
     args.defer = o.defer;
     args.ne_rows = row_map ? row_map : mm.ne_rows;
+    args.n_ne = mm.n_ne;
     args.rp = mm.ne_rowptr ? mm.ne_rowptr : mm.rowptr;
     args.fix_list = mm.fix_list; args.n_fix = mm.n_fix; args.n_fix_long = mm.n_fix_long;
     args.Z = Z; args.ldz = ldz; args.Zprev = Zprev; args.ldzprev = ldzprev;
