@@ -163,13 +163,19 @@ __device__ __forceinline__ void stage_chunk(const SplitArgs& a, int64_t k0, int 
 }
 
 // What a wavefront keeps in LDS for its chunk.
-template <int VEC>
+template <int LPR, int VEC, int EPI>
 struct __attribute__((aligned(16))) WaveLds {
+    // A bit per column for as many of the rows begun here as leave five workgroups to a compute unit; the rows after them are
+    // looked up one by one (all 512 rows a chunk can begin: 12 M entries in rows of 236, 16 columns: 72 -> 78 us).
+    static constexpr int MASK_BYTES = VEC == 4 ? LPR / 2 : 4;
+    static constexpr int WITHOUT_MASK = 2 * LDS_PER_WAVE * 4 + CHUNK * 4 + (SUBS_PER_CHUNK + 4) * 4 + 64 * VEC * 4;
+    static constexpr int MASK_ROWS = EPI != GCN_EPI_MASK ? 0 : (8192 - WITHOUT_MASK) / MASK_BYTES;
     int32_t col[LDS_PER_WAVE];
     float val[LDS_PER_WAVE];                    // values; of a value-free product the factors of the rows begun here
     int32_t row[CHUNK];                         // the rows begun here; the sign bit says that their sum is stored raw
     uint32_t flag[SUBS_PER_CHUNK + 4];
     float head[64 * VEC];
+    uint8_t mask[MASK_ROWS * MASK_BYTES];       // whether the derivative mask lets the sums of the first rows through
 };
 
 // The work of one workgroup: the four chunks 4*grp .. 4*grp+3 of the matrix described by `a`.
@@ -184,8 +190,8 @@ struct __attribute__((aligned(16))) WaveLds {
 // them are slower (119 M entries over column blocks: 611 us, 620 with two sets).  12 M entries in rows of 236 at 64 columns, operand
 // in the L2s: 187 -> 168 us; 2 M at 32: 34 -> 27; 33 M, packed hub and rest at 16: 318 -> 293; 9 M in rows of 9 at
 // 32: 203 -> 200 (line fills).
-template <int LPR, int VEC, int EPI>
-__device__ __forceinline__ void split_body(const SplitArgs& a, int64_t grp, WaveLds<VEC>* lds) {
+template <int LPR, int VEC, int EPI, class Lds>
+__device__ __forceinline__ void split_body(const SplitArgs& a, int64_t grp, Lds* lds) {
     constexpr int G = 64 / LPR;                 // lane groups per wavefront
     constexpr int LEN = CHUNK / G, NW = LEN / SUB;              // entries and flag words per group
     constexpr int UNR = 4;                      // entries fetched together
@@ -199,7 +205,7 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int64_t grp, Wave
     const bool col_ok = lane_columns<LPR, VEC>(a.f, blockIdx.y, gridDim.y, li, &col0);
     const int64_t k0 = c * CHUNK, j0 = c * SUBS_PER_CHUNK;
     const int nk = a.nnz - k0 < CHUNK ? (int)(a.nnz - k0) : CHUNK;
-    WaveLds<VEC>& L = lds[wave];
+    Lds& L = lds[wave];
 
     // ---- stage the chunk: indices, values, flags, the rows begun here ----
     uint32_t word = 0;
@@ -226,14 +232,48 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int64_t grp, Wave
     const bool continued = k0 + CHUNK < a.nnz && !(L.flag[SUBS_PER_CHUNK] & 1u);
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     __builtin_amdgcn_wave_barrier();
+    // The mask of those rows, as bits: fetched when a row starts or ends, it drained the gathers in flight (hub schedule,
+    // 33 M entries at 16 columns: 375 -> 333 us; 1.9 M at 64: 75 -> 64; 1.9 M at 41, k_spmm_line: 87 -> 71).  Where all wavefronts
+    // start together and rows are even it costs a burst at the beginning (1 M in rows of 21, 64 columns: 39 -> 44).
+    if constexpr (EPI == GCN_EPI_MASK) {
+        constexpr int AT_ONCE = 4, MB = Lds::MASK_BYTES;
+        const uint32_t mpitch = (uint32_t)a.ldzprev * 4u;
+        const int staged = begun < Lds::MASK_ROWS ? begun : Lds::MASK_ROWS;
+        for (int i0 = g; i0 < staged; i0 += AT_ONCE * G) {
+            float m[AT_ONCE][VEC];
+#pragma unroll
+            for (int t = 0; t < AT_ONCE; ++t) {
+                const int i = i0 + t * G < staged ? i0 + t * G : i0;
+                load_vec<VEC>(m[t], at_row(a.Zprev + col0, (uint32_t)L.row[i] & 0x7fffffffu, mpitch));
+            }
+#pragma unroll
+            for (int t = 0; t < AT_ONCE; ++t) {
+                const int i = i0 + t * G < staged ? i0 + t * G : i0;     // (the first again, with the same bits)
+                if (t > 0 && i == i0) continue;
+                if constexpr (VEC == 4) {
+                    int bits = 0;
+#pragma unroll
+                    for (int u = 0; u < VEC; ++u) bits |= m[t][u] > 0.f ? 1 << u : 0;
+                    bits |= __builtin_amdgcn_mov_dpp(bits, 0xf5, 0xf, 0xf, true) << 4;         // of the lane to the right
+                    if (li % 2 == 0) L.mask[i * MB + li / 2] = (uint8_t)bits;
+                } else {
+                    const unsigned long long bits = __ballot(m[t][0] > 0.f);
+                    if (li == 0) *reinterpret_cast<uint32_t*>(L.mask + i * MB) = (uint32_t)(bits >> (g * LPR));
+                }
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
 
     // ---- walk this group's slice ----
-    float acc[VEC] = {}, m[VEC] = {};
+    float acc[VEC] = {};
+    int through = 0;                            // the mask's bits of this lane's columns
     bool owned = false;                         // has this group seen a row start yet?
     int32_t row = 0;
     float scale = 1.f;
     const float* const xbase = a.X + col0;
-    const uint32_t xpitch = (uint32_t)a.ldx * 4u, zpitch = (uint32_t)a.ldz * 4u, mpitch = (uint32_t)a.ldzprev * 4u;
+    const uint32_t xpitch = (uint32_t)a.ldx * 4u, zpitch = (uint32_t)a.ldz * 4u;
     auto z_row = [&]() { return const_cast<float*>(at_row(a.Z + col0, (uint32_t)row & 0x7fffffffu, zpitch)); };
     auto store_row = [&]() {
         float v[VEC];
@@ -244,7 +284,7 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int64_t grp, Wave
             for (int u = 0; u < VEC; ++u) v[u] = v[u] > 0.f || row < 0 ? v[u] : 0.f;
         } else if constexpr (EPI == GCN_EPI_MASK) {
 #pragma unroll
-            for (int u = 0; u < VEC; ++u) v[u] = m[u] > 0.f || row < 0 ? v[u] : 0.f;
+            for (int u = 0; u < VEC; ++u) v[u] = through >> u & 1 || row < 0 ? v[u] : 0.f;
         }
         store_vec<VEC>(z_row(), v);
     };
@@ -257,7 +297,16 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int64_t grp, Wave
         owned = true;
         row = L.row[at];
         if (!a.val) scale = L.val[at];
-        if constexpr (EPI == GCN_EPI_MASK) load_vec<VEC>(m, at_row(a.Zprev + col0, (uint32_t)row & 0x7fffffffu, mpitch));
+        if constexpr (EPI == GCN_EPI_MASK) {
+            if (at >= Lds::MASK_ROWS) {
+                float m[VEC];
+                load_vec<VEC>(m, at_row(a.Zprev + col0, (uint32_t)row & 0x7fffffffu, (uint32_t)a.ldzprev * 4u));
+                through = 0;
+#pragma unroll
+                for (int u = 0; u < VEC; ++u) through |= m[u] > 0.f ? 1 << u : 0;
+            } else if constexpr (VEC == 4) through = L.mask[at * Lds::MASK_BYTES + li / 2] >> (li % 2 * 4);
+            else through = (int)(*reinterpret_cast<const uint32_t*>(L.mask + at * Lds::MASK_BYTES) >> li);
+        }
         at += 1;
 #pragma unroll
         for (int u = 0; u < VEC; ++u) acc[u] = 0.f;
@@ -348,7 +397,7 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int64_t grp, Wave
 
 template <int LPR, int VEC, int EPI>
 __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_split(SplitArgs a) {
-    __shared__ WaveLds<VEC> lds[WAVES_PER_BLOCK];
+    __shared__ WaveLds<LPR, VEC, EPI> lds[WAVES_PER_BLOCK];
     split_body<LPR, VEC, EPI>(a, blockIdx.x, lds);
 }
 
@@ -776,14 +825,39 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_line(SplitArgs a)
     const ConstF vals = (ConstF)(uintptr_t)(a.val ? a.val + k0 : nullptr);
     const bool continued = k0 + CHUNK < a.nnz && !(flags[SUBS_PER_CHUNK] & 1);     // (padded by a chunk of zero words)
     const uint32_t xpitch = (uint32_t)a.ldx * 4u, zpitch = (uint32_t)a.ldz * 4u, mpitch = (uint32_t)a.ldzprev * 4u;
-    // rows begun here: numbers and factors of 64 of them
+    // rows begun here: numbers, factors and mask bits of 64 of them
     const int32_t q1 = ((ConstI)(uintptr_t)a.sub_row)[c * SUBS_PER_CHUNK] + 1 - (flags[0] & 1);
-    int32_t rows = 0, at = 0, named = 0;      // 64 rows from the named-th on
+    int begun = 0;
+    if constexpr (EPI == GCN_EPI_MASK) {
+        const i16v all = *(ConstI16)flags;
+#pragma unroll
+        for (int w = 0; w < SUBS_PER_CHUNK; ++w) begun += __popc((uint32_t)all[w]);
+    }
+    int32_t rows = 0, at = 0, named = 0;        // 64 rows from the named-th on
     float factors = 1.f;
+    int32_t low[VEC] = {}, high[VEC] = {};
     auto name_rows = [&]() {
         const int64_t q = (int64_t)q1 + at + lane, last = a.n_ne - 1;
         rows = (int32_t)(q < last ? q : last);
         if (a.ne_rows) rows = a.ne_rows[rows];
+        if constexpr (EPI == GCN_EPI_MASK) {    // a lane keeps its row's bits of all lanes
+            constexpr int AT_ONCE = 8;
+            const int count = begun - at < 64 ? begun - at : 64;
+            for (int i = 0; i < count; i += AT_ONCE) {
+                float t[AT_ONCE][VEC];
+#pragma unroll
+                for (int j = 0; j < AT_ONCE; ++j)
+                    load_vec<VEC>(t[j], at_row(a.Zprev, (uint32_t)__builtin_amdgcn_readlane(rows, i + j), mpitch) + (uint32_t)col0);
+#pragma unroll
+                for (int j = 0; j < AT_ONCE; ++j)
+#pragma unroll
+                    for (int u = 0; u < VEC; ++u) {
+                        const unsigned long long bits = __ballot(t[j][u] > 0.f);
+                        low[u] = lane == i + j ? (int32_t)bits : low[u];
+                        high[u] = lane == i + j ? (int32_t)(bits >> 32) : high[u];
+                    }
+            }
+        }
         const bool raw = a.defer && a.defer[rows];
         factors = a.row_scale && !raw ? a.row_scale[rows] : 1.f;
         rows |= raw ? (int32_t)0x80000000 : 0;
@@ -791,7 +865,8 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_line(SplitArgs a)
         named = at;
     };
     name_rows();
-    float acc[VEC] = {}, head[VEC] = {}, m[VEC] = {};
+    float acc[VEC] = {}, head[VEC] = {};
+    unsigned long long through[VEC] = {};
     bool owned = false;
     int32_t row = 0;
     float scale = 1.f;
@@ -806,7 +881,7 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_line(SplitArgs a)
             for (int u = 0; u < VEC; ++u) v[u] = v[u] > 0.f || row < 0 ? v[u] : 0.f;
         } else if constexpr (EPI == GCN_EPI_MASK) {
 #pragma unroll
-            for (int u = 0; u < VEC; ++u) v[u] = m[u] > 0.f || row < 0 ? v[u] : 0.f;
+            for (int u = 0; u < VEC; ++u) v[u] = through[u] >> lane & 1 || row < 0 ? v[u] : 0.f;
         }
         store_vec<VEC>(z_row(), v);
     };
@@ -819,7 +894,12 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_line(SplitArgs a)
         owned = true;
         row = __builtin_amdgcn_readlane(rows, at - named);
         scale = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(factors), at - named));
-        if constexpr (EPI == GCN_EPI_MASK) load_vec<VEC>(m, at_row(a.Zprev, (uint32_t)row & 0x7fffffffu, mpitch) + (uint32_t)col0);
+        if constexpr (EPI == GCN_EPI_MASK) {
+#pragma unroll
+            for (int u = 0; u < VEC; ++u)
+                through[u] = (unsigned long long)(uint32_t)__builtin_amdgcn_readlane(high[u], at - named) << 32 |
+                             (uint32_t)__builtin_amdgcn_readlane(low[u], at - named);
+        }
         at += 1;
 #pragma unroll
         for (int u = 0; u < VEC; ++u) acc[u] = 0.f;
@@ -886,7 +966,7 @@ template <int LPR, int VEC, int EPI>
 __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_split_pair(SplitArgs a, SplitArgs b, int ra, int rb) {
     // ra + rb == 8.  Workgroups go to the eight XCDs round-robin; the rotation by q lets every XCD see
     // both kinds of work in turn.
-    __shared__ WaveLds<VEC> lds[WAVES_PER_BLOCK];
+    __shared__ WaveLds<LPR, VEC, EPI> lds[WAVES_PER_BLOCK];
     const unsigned q = blockIdx.x / 8, r = (blockIdx.x + q) % 8;
     if ((int)r < ra) split_body<LPR, VEC, EPI>(a, (int64_t)q * ra + r, lds);
     else split_body<LPR, VEC, GCN_EPI_NONE>(b, (int64_t)q * rb + (r - ra), lds);
@@ -984,12 +1064,13 @@ __global__ void k_spmm_rowwise(int64_t n, const int64_t* __restrict__ rowptr, co
 // Dynamic LDS on top of the kernel's own, to lower the number of resident workgroups.  The kernels with 16 lane groups
 // per wavefront (rows of up to 64 bytes) keep 64 gathers in flight per wavefront and run slower with eight workgroups
 // per compute unit than with five (119 M entries at 16 columns: 0.64 -> 0.62 ms), which the 31 KB of the 16-byte kernel
-// leave by themselves; the one-float kernel takes four (102 M entries at one column: 612 -> 588 us).
+// leave by themselves; the one-float kernel takes four (102 M entries at one column: 612 -> 576 us).
 template <int LPR, int VEC>
-static size_t occupancy_pad(int lds_kb) {
+static size_t occupancy_pad(int lds_kb, int epilogue) {
     if (LPR != 4) return 0;
-    const size_t own = VEC == 1 ? (size_t)18 << 10 : WAVES_PER_BLOCK * sizeof(WaveLds<VEC>), want = (size_t)lds_kb << 10;
-    return want > own ? want - own : 0;
+    const size_t own = epilogue == GCN_EPI_MASK ? sizeof(WaveLds<LPR, VEC, GCN_EPI_MASK>) : sizeof(WaveLds<LPR, VEC, GCN_EPI_NONE>);
+    const size_t want = (size_t)(VEC == 1 ? lds_kb + 10 : lds_kb) << 10;
+    return want > WAVES_PER_BLOCK * own ? want - WAVES_PER_BLOCK * own : 0;
 }
 
 template <int LPR, int VEC>
@@ -1036,7 +1117,7 @@ static int launch_split(const SplitArgs& args, int epilogue, hipStream_t s) {
     const int tile = LPR * VEC;
     const dim3 grid((unsigned)((args.nchunks + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK), (unsigned)((args.f + tile - 1) / tile));
     const dim3 block(64 * WAVES_PER_BLOCK);
-    const size_t pad = (occupancy_pad<LPR, VEC>(args.lds_kb));
+    const size_t pad = (occupancy_pad<LPR, VEC>(args.lds_kb, epilogue));
     timing_begin(s);
     switch (epilogue) {
         case GCN_EPI_NONE: hipLaunchKernelGGL((k_spmm_split<LPR, VEC, GCN_EPI_NONE>), grid, block, pad, s, args); break;
@@ -1336,8 +1417,7 @@ static int run_split(const SplitArgs& args, int epilogue, hipStream_t s, bool an
     // the index/value stream and half the requests (config 3 at f = 128: 3.55 -> 3.27 ms; config 2, bound by line
     // fills: 1.46 -> 1.69 ms, so not there).
     // Rows that are not whole 16-byte pieces (only without an order to keep) straddle lines wherever they are cut: one
-    // panel up to 64 columns (41 columns, 1 M rows: 1.20 ms in two panels, 0.89 in one; k_spmm_ragged_many 0.92; with
-    // 200 K rows 0.073 against its 0.122).
+    // panel up to 64 columns (41 columns, 1 M rows: 1.20 ms in two panels, 0.89 in one).
     if ((f >= 64 && l2_resident) || (f % 4 != 0 && f <= 64)) return launch_split<16, 4>(args, epilogue, s);
     return launch_split<8, 4>(args, epilogue, s);
 }

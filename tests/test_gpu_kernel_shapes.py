@@ -215,6 +215,31 @@ def test_spmm_few_chunks_and_many_chunks_add_alike(f):
         a.close()
 
 
+@pytest.mark.parametrize("f", [1, 7, 16, 21, 32, 41, 64, 130])
+@pytest.mark.parametrize("longest", [1, 4, 900])
+def test_spmm_mask_of_many_rows_per_chunk(f, longest):
+    """Chunks that begin anything between no row and 512 rows, more than the kernels keep the derivative mask of: the masked
+    product is the plain one with the masked places set to zero, bit by bit."""
+    g = G()
+    rs = np.random.default_rng(87)
+    lengths = rs.integers(1, longest + 1, 1_200_000 // (longest + 1))
+    n, nc = lengths.size, 3000
+    rowptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    within = np.arange(rowptr[-1]) - np.repeat(rowptr[:-1], lengths)
+    colidx = (np.repeat(rs.integers(0, nc - longest, n), lengths) + within).astype(np.int32)
+    val = rs.standard_normal(colidx.size).astype(np.float32)
+    a = g.gcn_csr_create_from_csr_rect(n, nc, dev(rowptr), dev(colidx), dev(val), 0)
+    g.gcn_csr_config(a, g.CFG_SPMM_BLOCKS, 1)
+    X, Zp = dev(synth.normal_features(nc, f, 88)), dev(synth.normal_features(n, f, 89))
+    plain, masked = torch.empty(n, f, device="cuda"), torch.full((n, f), float("nan"), device="cuda")
+    g.gcn_spmm(a, 0, X, plain)
+    g.gcn_spmm(a, 0, X, masked, g.EPI_MASK, Zp)
+    want = np.add.reduceat(dev(val)[:, None].mul(X[dev(colidx).long()]).cpu().numpy(), rowptr[:-1], axis=0, dtype=np.float64)
+    assert_close(host(plain), want, f"rows of 1 to {longest}, f={f}")
+    np.testing.assert_array_equal(host(masked), np.where(host(Zp) > 0, host(plain), 0))
+    a.close()
+
+
 @pytest.mark.parametrize("f", [1, 3, 5, 7, 9, 17, 31, 33, 41, 63, 65, 130])
 @pytest.mark.parametrize("edges,blocks", [(3000, 1), (90_000, 1), (900_000, 1), (90_000, 3)])
 def test_layer_products_of_ragged_width(f, edges, blocks):
