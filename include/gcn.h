@@ -166,8 +166,8 @@ int gcn_spmm_describe(gcn_csr* a, int trans, int32_t f, char* out, size_t out_by
 /* -------------------------------------------------------------------------------------------
  * gcn_spmm for callers that cannot allocate device memory: code under HIP graph capture from its
  * first call on, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, result and
- * errors as gcn_spmm, always through the nonzero-split kernel over the stored order (so the result is
- * bit-identical to gcn_spmm with GCN_CFG_SPMM_ALGO = 2 and GCN_CFG_SPMM_BLOCKS = 1), but the partial rows of
+ * errors as gcn_spmm, always through the nonzero-split kernel over the stored order (the row-wise kernel for rows 4 GB
+ * and more apart), so the result is bit-identical to gcn_spmm with GCN_CFG_SPMM_ALGO = 2 and GCN_CFG_SPMM_BLOCKS = 1, but the partial rows of
  * rows that cross wavefronts (f floats per 512 stored entries) live in a fixed array of
  * GCN_SPMM_STATIC_SCRATCH_BYTES inside the library's device image instead of a buffer the handle grows.
  * The call makes no hipMalloc / hipFree and no allocating library call; it only queues kernels on `stream`.

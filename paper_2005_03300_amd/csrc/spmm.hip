@@ -135,7 +135,8 @@ __device__ __forceinline__ void epilogue_store(float* z, const float* zprev, flo
     store_vec<VEC>(z, v);
 }
 
-// Row `row` of a matrix whose rows are `pitch` bytes apart: one multiply-add of 32 by 32 bits.
+// Row `row` of a matrix whose rows are `pitch` bytes apart: one multiply-add of 32 by 32 bits.  Pitches of 4 GB and more
+// do not come here (far_rows).
 __device__ __forceinline__ const float* at_row(const float* base, uint32_t row, uint32_t pitch) {
     return reinterpret_cast<const float*>(reinterpret_cast<const char*>(base) + (uint64_t)row * pitch);
 }
@@ -1042,7 +1043,8 @@ __global__ __launch_bounds__(256) void k_zero_listed_rows(int64_t count, uint32_
 }
 
 // Reference-shaped kernel: one thread per output element walks its row.  Kept as a selectable
-// second implementation (GCN_CFG_SPMM_ALGO = 1) for cross-checks; never chosen automatically.
+// second implementation (GCN_CFG_SPMM_ALGO = 1) for cross-checks; chosen automatically only for operands that the
+// other kernels cannot address (see far_rows).
 template <int EPI>
 __global__ void k_spmm_rowwise(int64_t n, const int64_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
                                const float* __restrict__ val, const float* __restrict__ row_scale, int32_t f,
@@ -1680,6 +1682,29 @@ static int want_hub(Matrix& m, const Config& cfg, int64_t nnz, int64_t H, int64_
     return GCN_OK;
 }
 
+// Rows 4 GB and more apart: only the row-wise kernel, which computes its addresses in 64 bits, takes such operands; the
+// others multiply a row's number by its pitch in bytes, both 32 bits wide (see at_row).
+static bool far_rows(int64_t ldx, int64_t ldz, int epilogue, int64_t ldzprev) {
+    constexpr int64_t LIMIT = 1ll << 30;                        // floats
+    return ldx >= LIMIT || ldz >= LIMIT || (epilogue == GCN_EPI_MASK && ldzprev >= LIMIT);
+}
+
+static int launch_rowwise(const Matrix& m, int32_t f, const float* X, int64_t ldx, float* Z, int64_t ldz, int epilogue,
+                          const float* Zprev, int64_t ldzprev, const SpmmOpt& o, hipStream_t s) {
+    const int64_t n = m.nrows, work = n * f;
+    const dim3 grid((unsigned)((work + 255) / 256));
+    if (work / 256 >= (1ll << 31)) return fail(GCN_ERR_RANGE, "gcn_spmm: n*f too large for the row-wise kernel");
+    timing_begin(s);
+    switch (epilogue) {
+        case GCN_EPI_NONE: hipLaunchKernelGGL(k_spmm_rowwise<GCN_EPI_NONE>, grid, dim3(256), 0, s, n, m.rowptr, m.colidx, o.pattern ? nullptr : m.val, o.row_scale, f, X, ldx, Z, ldz, Zprev, ldzprev); break;
+        case GCN_EPI_RELU: hipLaunchKernelGGL(k_spmm_rowwise<GCN_EPI_RELU>, grid, dim3(256), 0, s, n, m.rowptr, m.colidx, o.pattern ? nullptr : m.val, o.row_scale, f, X, ldx, Z, ldz, Zprev, ldzprev); break;
+        default: hipLaunchKernelGGL(k_spmm_rowwise<GCN_EPI_MASK>, grid, dim3(256), 0, s, n, m.rowptr, m.colidx, o.pattern ? nullptr : m.val, o.row_scale, f, X, ldx, Z, ldz, Zprev, ldzprev); break;
+    }
+    timing_end(s);
+    GCN_LAUNCH_CHECK();
+    return GCN_OK;
+}
+
 static void took(gcn_csr* a, int sched) {
     g_last_schedule = sched;
     a->last_schedule = sched;
@@ -1698,7 +1723,6 @@ int spmm_launch(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx, f
         return GCN_OK;
     }
     int algo = cfg.spmm_algo;
-    const bool far_rows = ldx >= (1ll << 30) || ldz >= (1ll << 30) || ldzprev >= (1ll << 30);
     const bool vec4_all = (f % 4 == 0) && (ldx % 4 == 0) && (ldz % 4 == 0) && aligned16(X) && aligned16(Z) &&
                           (epilogue != GCN_EPI_MASK || ((ldzprev % 4 == 0) && aligned16(Zprev)));
     const int64_t nblocks = choose_blocks(cfg, n, ncols, nnz, f, 24);
@@ -1714,7 +1738,7 @@ int spmm_launch(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx, f
         algo = (huge && vec4_all && nblocks < 2 && narrow_steps) ? 3 : 2;
     }
     if (algo == 3 && !vec4_all) algo = 2;
-    if (far_rows) algo = 1;              // rows 4 GB and more apart: the others compute row addresses by 32-bit factors
+    if (far_rows(ldx, ldz, epilogue, ldzprev)) algo = 1;
     if ((algo == 2 && cfg.spmm_algo == 0) || algo == 4) {
         // Hub schedule: for operands beyond the L2s when most entries sit in long rows and hot columns
         // (decided from the matrix itself when the copy is built; a rejected shape is remembered).
@@ -1773,18 +1797,7 @@ int spmm_launch(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx, f
         took(a, GCN_SCHED_ROWWISE);
         if (o.describe) *o.describe += "rowwise";
         if (o.dry) return GCN_OK;
-        const int64_t work = n * f;
-        const dim3 grid((unsigned)((work + 255) / 256));
-        if (work / 256 >= (1ll << 31)) return fail(GCN_ERR_RANGE, "gcn_spmm: n*f too large for the row-wise kernel");
-        timing_begin(s);
-        switch (epilogue) {
-            case GCN_EPI_NONE: hipLaunchKernelGGL(k_spmm_rowwise<GCN_EPI_NONE>, grid, dim3(256), 0, s, n, m.rowptr, m.colidx, o.pattern ? nullptr : m.val, o.row_scale, f, X, ldx, Z, ldz, Zprev, ldzprev); break;
-            case GCN_EPI_RELU: hipLaunchKernelGGL(k_spmm_rowwise<GCN_EPI_RELU>, grid, dim3(256), 0, s, n, m.rowptr, m.colidx, o.pattern ? nullptr : m.val, o.row_scale, f, X, ldx, Z, ldz, Zprev, ldzprev); break;
-            default: hipLaunchKernelGGL(k_spmm_rowwise<GCN_EPI_MASK>, grid, dim3(256), 0, s, n, m.rowptr, m.colidx, o.pattern ? nullptr : m.val, o.row_scale, f, X, ldx, Z, ldz, Zprev, ldzprev); break;
-        }
-        timing_end(s);
-        GCN_LAUNCH_CHECK();
-        return GCN_OK;
+        return launch_rowwise(m, f, X, ldx, Z, ldz, epilogue, Zprev, ldzprev, o, s);
     }
     took(a, nblocks >= 2 ? GCN_SCHED_BLOCKED : GCN_SCHED_SPLIT);
     return run_matrix(a, m, nullptr, nnz, nblocks, f, X, ldx, Z, ldz, epilogue, Zprev, ldzprev, o, s);
@@ -1903,6 +1916,10 @@ extern "C" int gcn_spmm_static(gcn_csr* a, int trans, int32_t f, const float* X,
                     "array holds %zu; use gcn_spmm", need, (long long)a->nnz, (int)f, STATIC_SCRATCH_BYTES);
     hipStream_t s = (hipStream_t)stream;
     if (a->nnz == 0) return zero_empty_rows(m, f, Z, ldz, s);
+    if (far_rows(ldx, ldz, epilogue, ldzprev)) {
+        took(a, GCN_SCHED_ROWWISE);
+        return launch_rowwise(m, f, X, ldx, Z, ldz, epilogue, Zprev, ldzprev, SpmmOpt(), s);
+    }
     float* carry = nullptr;
     GCN_TRY(static_scratch(&carry));
     took(a, GCN_SCHED_SPLIT);

@@ -285,3 +285,46 @@ def test_layer_products_of_ragged_width(f, edges, blocks):
     assert_close(host(Y), Yref, "Y, sparse product first")
     assert_close(host(Gp), Gpref, "Gprev, sparse product first")
     a.close()
+
+
+def _far(rows, cols, pitch):
+    """A rows x cols matrix in device memory whose rows are `pitch` floats apart (4 GB and more)."""
+    return torch.empty((rows - 1) * pitch + cols, device="cuda").as_strided((rows, cols), (pitch, 1))
+
+
+@pytest.mark.parametrize("which,trans", [("X", 1), ("Z", 0), ("Zprev", 0)])
+@pytest.mark.parametrize("f", [5, 16, 41])
+def test_spmm_rows_four_gigabytes_apart(which, trans, f):
+    """Leading dimensions from 2^30 floats on, where a row's pitch in bytes no longer fits 32 bits, in each operand of each
+    entry point of the product; the matrix has three rows of chunks enough for every nonzero-split kernel."""
+    g = G()
+    nc, pitch = 250_000, (1 << 30) + 4
+    rs = np.random.default_rng(101)
+    rowptr = np.array([0, 200_000, 370_000, 570_000])
+    colidx = np.concatenate([np.sort(rs.choice(nc, k, replace=False)) for k in np.diff(rowptr)]).astype(np.int32)
+    val = rs.standard_normal(colidx.size).astype(np.float32)
+    a = g.gcn_csr_create_from_csr_rect(3, nc, dev(rowptr), dev(colidx), dev(val), g.BUILD_TRANSPOSE)
+    xrows, zrows = (3, nc) if trans else (nc, 3)
+    X, Zp = synth.normal_features(xrows, f, 102), synth.normal_features(zrows, f, 103)
+    Xd, Zd, Pd = [_far(r, f, pitch) if which == k else torch.empty(r, f, device="cuda")
+                  for k, r in (("X", xrows), ("Z", zrows), ("Zprev", zrows))]
+    Xd.copy_(dev(X)), Pd.copy_(dev(Zp))
+    row = np.repeat(np.arange(3), np.diff(rowptr))
+
+    def product(v):
+        out = np.zeros((zrows, f))
+        for i in range(3):
+            k = row == i
+            if trans:
+                out[colidx[k]] += v[k, None] * X[i].astype(np.float64)
+            else:
+                out[i] = v[k].astype(np.float64) @ X[colidx[k]].astype(np.float64)
+        return np.where(Zp > 0, out, 0)
+    for call in (g.gcn_spmm, g.gcn_spmm_static):
+        Zd.fill_(float("nan"))
+        call(a, trans, Xd, Zd, g.EPI_MASK, Pd)
+        assert_close(host(Zd.contiguous()), product(val), call.__name__)
+    Zd.fill_(float("nan"))
+    g.gcn_spmm_pattern(a, trans, Xd, Zd, None, g.EPI_MASK, Pd)
+    assert_close(host(Zd.contiguous()), product(np.ones_like(val)), "gcn_spmm_pattern")
+    a.close()
