@@ -140,7 +140,9 @@ int gcn_csr_export(const gcn_csr* a, int transposed, int64_t* rowptr, int32_t* c
  * val[k] * X[col[k],:], op(A) = A (trans=0) or A^T (trans=1).
  * X: device n x f, ld ldx >= f.  Z: device n x f, ld ldz >= f, must not overlap X (for a rectangular
  * matrix X has as many rows as op(A) has columns and Z as many as op(A) has rows).
- * epilogue GCN_EPI_MASK reads Zprev (device n x f, ld ldzprev); otherwise Zprev is ignored.
+ * epilogue GCN_EPI_MASK reads Zprev (device n x f, ld ldzprev); otherwise Zprev is ignored.  Zprev may be Z itself (same
+ * address and leading dimension; correct, but such a product takes the row-wise kernel, which is slow on long rows); no
+ * other element of Zprev may be one of Z.
  * Sums are fp32 and run-to-run reproducible (no floating-point atomics).  The first call at a
  * given width may build and cache a column-blocked copy of the matrix inside `a` (it allocates
  * and synchronises once); later calls only queue kernels.
@@ -167,7 +169,7 @@ int gcn_spmm_describe(gcn_csr* a, int trans, int32_t f, char* out, size_t out_by
  * gcn_spmm for callers that cannot allocate device memory: code under HIP graph capture from its
  * first call on, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, result and
  * errors as gcn_spmm, always through the nonzero-split kernel over the stored order (the row-wise kernel for rows 4 GB
- * and more apart), so the result is bit-identical to gcn_spmm with GCN_CFG_SPMM_ALGO = 2 and GCN_CFG_SPMM_BLOCKS = 1, but the partial rows of
+ * and more apart and for a mask that is Z itself), so the result is bit-identical to gcn_spmm with GCN_CFG_SPMM_ALGO = 2 and GCN_CFG_SPMM_BLOCKS = 1, but the partial rows of
  * rows that cross wavefronts (f floats per 512 stored entries) live in a fixed array of
  * GCN_SPMM_STATIC_SCRATCH_BYTES inside the library's device image instead of a buffer the handle grows.
  * The call makes no hipMalloc / hipFree and no allocating library call; it only queues kernels on `stream`.

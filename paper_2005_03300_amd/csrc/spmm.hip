@@ -98,8 +98,7 @@ __device__ __forceinline__ void store_vec(float* p, const float (&d)[VEC]) {
 // The columns of one lane in panel `y` of an operand of width f: VEC of them from `col0` (false: none).  A width that is
 // no multiple of 4 ends with a lane that repeats columns of its left neighbour, so that its 16 bytes stay inside
 // the row; both compute and store the same values.  When fewer than four columns are left for the last panel it
-// takes four more from the panel before, so that the repetition stays inside one wavefront (and a matrix with
-// a mask that is the output itself works).
+// takes four more from the panel before, so that the repetition stays inside one panel.
 template <int LPR, int VEC>
 __device__ __forceinline__ bool lane_columns(int f, int y, int ny, int li, int* col0) {
     constexpr int W = LPR * VEC;
@@ -136,7 +135,7 @@ __device__ __forceinline__ void epilogue_store(float* z, const float* zprev, flo
 }
 
 // Row `row` of a matrix whose rows are `pitch` bytes apart: one multiply-add of 32 by 32 bits.  Pitches of 4 GB and more
-// do not come here (far_rows).
+// do not come here (see rowwise_only).
 __device__ __forceinline__ const float* at_row(const float* base, uint32_t row, uint32_t pitch) {
     return reinterpret_cast<const float*>(reinterpret_cast<const char*>(base) + (uint64_t)row * pitch);
 }
@@ -1044,7 +1043,7 @@ __global__ __launch_bounds__(256) void k_zero_listed_rows(int64_t count, uint32_
 
 // Reference-shaped kernel: one thread per output element walks its row.  Kept as a selectable
 // second implementation (GCN_CFG_SPMM_ALGO = 1) for cross-checks; chosen automatically only for operands that the
-// other kernels cannot address (see far_rows).
+// other kernels do not take (see rowwise_only).
 template <int EPI>
 __global__ void k_spmm_rowwise(int64_t n, const int64_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
                                const float* __restrict__ val, const float* __restrict__ row_scale, int32_t f,
@@ -1682,11 +1681,18 @@ static int want_hub(Matrix& m, const Config& cfg, int64_t nnz, int64_t H, int64_
     return GCN_OK;
 }
 
-// Rows 4 GB and more apart: only the row-wise kernel, which computes its addresses in 64 bits, takes such operands; the
-// others multiply a row's number by its pitch in bytes, both 32 bits wide (see at_row).
-static bool far_rows(int64_t ldx, int64_t ldz, int epilogue, int64_t ldzprev) {
-    constexpr int64_t LIMIT = 1ll << 30;                        // floats
-    return ldx >= LIMIT || ldz >= LIMIT || (epilogue == GCN_EPI_MASK && ldzprev >= LIMIT);
+// Operands that only the row-wise kernel takes:
+//   * rows 4 GB and more apart: it computes its addresses in 64 bits, the others multiply a row's number by its pitch in
+//     bytes, both 32 bits wide (see at_row);
+//   * a mask that is the output itself: its threads read their element of the mask and then store that element, while the
+//     others store a row that crosses chunks, or that the hub schedule defers, before they finish it, and read
+//     the mask when they finish it (and two lanes of different wavefronts may compute the last columns of a ragged row).
+static bool rowwise_only(const Matrix& m, int64_t ldx, const float* Z, int64_t ldz, int epilogue, const float* Zprev,
+                         int64_t ldzprev) {
+    constexpr int64_t FAR = 1ll << 30;                          // floats
+    if (ldx >= FAR || ldz >= FAR) return true;
+    if (epilogue != GCN_EPI_MASK) return false;
+    return ldzprev >= FAR || (Zprev == Z && (ldzprev == ldz || m.nrows == 1));
 }
 
 static int launch_rowwise(const Matrix& m, int32_t f, const float* X, int64_t ldx, float* Z, int64_t ldz, int epilogue,
@@ -1738,7 +1744,7 @@ int spmm_launch(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx, f
         algo = (huge && vec4_all && nblocks < 2 && narrow_steps) ? 3 : 2;
     }
     if (algo == 3 && !vec4_all) algo = 2;
-    if (far_rows(ldx, ldz, epilogue, ldzprev)) algo = 1;
+    if (rowwise_only(m, ldx, Z, ldz, epilogue, Zprev, ldzprev)) algo = 1;
     if ((algo == 2 && cfg.spmm_algo == 0) || algo == 4) {
         // Hub schedule: for operands beyond the L2s when most entries sit in long rows and hot columns
         // (decided from the matrix itself when the copy is built; a rejected shape is remembered).
@@ -1916,7 +1922,7 @@ extern "C" int gcn_spmm_static(gcn_csr* a, int trans, int32_t f, const float* X,
                     "array holds %zu; use gcn_spmm", need, (long long)a->nnz, (int)f, STATIC_SCRATCH_BYTES);
     hipStream_t s = (hipStream_t)stream;
     if (a->nnz == 0) return zero_empty_rows(m, f, Z, ldz, s);
-    if (far_rows(ldx, ldz, epilogue, ldzprev)) {
+    if (rowwise_only(m, ldx, Z, ldz, epilogue, Zprev, ldzprev)) {
         took(a, GCN_SCHED_ROWWISE);
         return launch_rowwise(m, f, X, ldx, Z, ldz, epilogue, Zprev, ldzprev, SpmmOpt(), s);
     }

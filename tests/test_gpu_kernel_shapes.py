@@ -328,3 +328,38 @@ def test_spmm_rows_four_gigabytes_apart(which, trans, f):
     g.gcn_spmm_pattern(a, trans, Xd, Zd, None, g.EPI_MASK, Pd)
     assert_close(host(Zd.contiguous()), product(np.ones_like(val)), "gcn_spmm_pattern")
     a.close()
+
+
+@pytest.mark.parametrize("algo,blocks", [(0, 0), (2, 1), (2, 3), (3, 0), (4, 0)])
+@pytest.mark.parametrize("f", [3, 16, 41, 51])
+def test_spmm_mask_that_is_the_output(f, algo, blocks):
+    """Zprev == Z, with rows inside a chunk, over several chunks, over column blocks, deferred by the hub schedule, and at widths
+    whose last lane repeats columns: the result is that of the same call with the mask in a buffer of its own."""
+    g = G()
+    n = 3000
+    rs = np.random.default_rng(104)
+    src = rs.integers(0, n, 200_000).astype(np.int32)
+    dst = (n * rs.random(200_000) ** 4).astype(np.int32)
+    a = g.gcn_csr_create(n, dev(src), dev(dst), g.SYMMETRISE | g.ADD_SELF_LOOPS | g.NORM_SYM | g.BUILD_TRANSPOSE)
+    for key, value in ((g.CFG_SPMM_ALGO, algo), (g.CFG_SPMM_BLOCKS, blocks), (g.CFG_SWEEP_HEAVY, 64), (g.CFG_HUB_DMIN, 16),
+                       (g.CFG_HUB_BLOCK_COLS, 64)):
+        g.gcn_csr_config(a, key, value)
+    X, M = dev(synth.normal_features(n, f, 105)), dev(synth.normal_features(n, f, 106))
+    pitched = torch.full((n, f + 3), float("nan"), device="cuda")
+    ones = torch.ones(n, device="cuda")
+    calls = [lambda Z, P: g.gcn_spmm(a, 1, X, Z, g.EPI_MASK, P), lambda Z, P: g.gcn_spmm_static(a, 0, X, Z, g.EPI_MASK, P),
+             lambda Z, P: g.gcn_spmm_pattern(a, 0, X, Z, ones, g.EPI_MASK, P)]
+    for k, call in enumerate(calls):
+        apart = torch.empty(n, f, device="cuda")
+        call(apart, M)
+        for Z in (M.clone(), pitched[:, :f].copy_(M)):
+            call(Z, Z)
+            assert_close(host(Z), host(apart), f"call {k}")
+    assert torch.isnan(pitched[:, f:]).all()
+    # the backward call of a layer in sparse-product-first order
+    W, Gl, Y = dev(synth.glorot_weights((f, 20), 107)[0]), dev(synth.normal_features(n, 20, 108)), torch.empty(f, 20, device="cuda")
+    apart, S, Gp = torch.empty(n, f, device="cuda"), torch.empty(n, f, device="cuda"), M.clone()
+    g.gcn_layer_backward(a, X, M, W, Gl, X, S, Y, apart, g.ORDER_SPMM_FIRST)
+    g.gcn_layer_backward(a, X, Gp, W, Gl, X, S, Y, Gp, g.ORDER_SPMM_FIRST)
+    assert_close(host(Gp), host(apart), "Gprev")
+    a.close()
