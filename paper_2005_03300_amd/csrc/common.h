@@ -5,11 +5,11 @@
 #include <stdint.h>
 #include <stdio.h>
 
-#include <atomic>
 #include <string>
 #include <vector>
 
 #include "gcn.h"
+#include "largest_asked.h"
 
 namespace gcn {
 
@@ -260,17 +260,17 @@ struct PhaseTimer {
 };
 
 // Launches a kernel with dynamic LDS.  More than 64 KB per workgroup (static part included) has to be asked for, once
-// per kernel, device and size (two threads may both ask, which is harmless).
+// per kernel, device and larger size.  A request that fails is made again by the next launch, and reported by the
+// launch check.
 template <auto Kernel, typename... Args>
 void launch_lds(dim3 grid, int threads, size_t lds, hipStream_t s, const Args&... args) {
     if (lds > 44 * 1024) {
-        static std::atomic<size_t> asked[64];
+        static LargestAsked asked[64];
         int dev = 0;
         (void)hipGetDevice(&dev);
-        if (asked[dev & 63].load(std::memory_order_relaxed) < lds) {
-            (void)hipFuncSetAttribute((const void*)Kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            asked[dev & 63].store(lds, std::memory_order_relaxed);
-        }
+        asked[dev & 63].reach(lds, [](size_t bytes) {
+            return hipFuncSetAttribute((const void*)Kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess;
+        });
     }
     hipLaunchKernelGGL(Kernel, grid, dim3(threads), lds, s, args...);
 }
