@@ -359,8 +359,10 @@ int gcn_unique_u64(int64_t n, const uint64_t* keys_in, uint64_t* keys_out, int64
 #define GCN_SCHED_BLOCKED 5  /* nonzero-split over the column-blocked copy */
 int gcn_last_spmm_schedule(void);
 int gcn_csr_last_spmm_schedule(const gcn_csr* a);   /* the same per matrix (0 before its first product) */
-/* Number of stored orders of matrices (column-blocked, sweep, hub copies) this process has built so far: a
- * caller can check that a steady-state loop builds nothing. */
+/* Number of stored orders of matrices that this process has built so far beyond the compressed rows of A and A^T, each
+ * counted by itself: a column-blocked order; the tasks of a sweep copy, and the compressed rows of its long rows if it has
+ * any; the two parts of a hub copy.  A matrix that equals its transpose has one of each for both directions.  A caller can
+ * check that a steady-state loop builds nothing. */
 int64_t gcn_build_count(void);
 
 const char* gcn_last_error(void);

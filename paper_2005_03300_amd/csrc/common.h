@@ -129,7 +129,6 @@ struct Matrix {
     int64_t n_fix = 0, n_fix_long = 0;   // the first n_fix_long of them cover a whole further chunk
     int64_t nsub = 0, nchunks = 0;
     int32_t max_degree = 0;
-    bool both = false;           // this matrix is A and A^T (gcn_csr::symmetric): its other orders count for both
     // Other stored orders of the matrix, built on first use (or by a prepare call) and kept until the
     // matrix is destroyed.  blk / swp / hub are the copies the latest product used; a product that needs
     // another key (block width; lane groups, task height and long-row threshold; hub settings) parks the
@@ -246,7 +245,7 @@ Config& config();                               // the process-wide settings (gc
 inline const Config& cfg_of(const gcn_csr* a) { return a->own_cfg ? a->cfg : config(); }
 // schedule taken by the most recent sparse product of this process (GCN_SCHED_*), for tests and reports
 extern int g_last_schedule;
-void count_build(const Matrix& m);
+void count_build();                             // one stored order has been built (gcn_build_count)
 
 // event bracketing of the dominant kernel (GCN_CFG_TIMING)
 void timing_begin(hipStream_t s, int phase = GCN_PHASE_SPMM_KERNEL);

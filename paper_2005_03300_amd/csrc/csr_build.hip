@@ -336,7 +336,6 @@ static int create_impl(gcn_csr* a, int64_t n, int64_t m, const int32_t* src, con
         // Both directions of every pair are stored and the value formula (1, or 1/sqrt(d_i d_j)) is symmetric: A^T is A,
         // bit by bit, and one set of arrays and schedules serves both.
         a->symmetric = sym && !(flags & GCN_NORM_ROW);
-        a->A.both = a->symmetric;
         if (a->symmetric) a->has_t = true;
         else GCN_TRY(build_transpose(a, keys, cbits, k1.as<uint64_t>(), s));
     }

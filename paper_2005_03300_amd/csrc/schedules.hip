@@ -80,7 +80,6 @@ __global__ void k_set_i64(int64_t* p, int64_t v) { *p = v; }
 void free_blocked(Blocked& b);
 
 int build_blocked(Matrix& m, int64_t nnz, int64_t cpb, hipStream_t s) {
-    count_build(m);
     free_blocked(m.blk);
     Blocked& b = m.blk;
     if (nnz <= 0 || cpb <= 0) return fail(GCN_ERR_BADARG, "build_blocked: empty matrix or bad block width");
@@ -144,6 +143,7 @@ int build_blocked(Matrix& m, int64_t nnz, int64_t cpb, hipStream_t s) {
     b.nblocks = (int32_t)nblocks;
     b.nrows = R;
     GCN_TRY(build_fix_list(b.flags, b.sub_row, b.rp, nnz, &b.fix_list, &b.n_fix, &b.n_fix_long, s));
+    count_build();
     return GCN_OK;
 }
 
@@ -284,7 +284,6 @@ __global__ void k_heavy_len(int64_t nh, const int32_t* __restrict__ rows, const 
 }
 
 int build_sweep(Matrix& m, int64_t nnz, int32_t groups, int32_t rb, int32_t heavy_th, hipStream_t s) {
-    count_build(m);
     free_sweep(m.swp);
     Sweep& w = m.swp;
     if (nnz <= 0 || rb <= 0 || rb > 256 || (groups != 8 && groups != 16))
@@ -399,6 +398,7 @@ int build_sweep(Matrix& m, int64_t nnz, int32_t groups, int32_t rb, int32_t heav
         GCN_LAUNCH_CHECK();
         GCN_HIP_TRY(hipStreamSynchronize(s));
         GCN_TRY(build_fix_list(h->flags, h->sub_row, h->ne_rowptr, nnz_heavy, &h->fix_list, &h->n_fix, &h->n_fix_long, s));
+        count_build();
     }
     GCN_HIP_TRY(hipStreamSynchronize(s));
     w.groups = groups;
@@ -408,6 +408,7 @@ int build_sweep(Matrix& m, int64_t nnz, int32_t groups, int32_t rb, int32_t heav
     w.nnz_light = nnz_light;
     w.nnz_heavy = nnz_heavy;
     w.n_heavy = w.heavy ? w.heavy->n_ne : 0;
+    count_build();
     return GCN_OK;
 }
 
@@ -477,7 +478,6 @@ __global__ void k_hub_hot_rowptr(int64_t nh, int64_t nnz_hot, const int32_t* __r
 void free_hub(Hub& h);
 
 int build_hub(Matrix& m, int64_t nnz, int64_t H, int64_t cpb, int32_t dmin, hipStream_t s) {
-    count_build(m);
     free_hub(m.hub);
     Hub& h = m.hub;
     h.state = -1;                                            // until everything below has succeeded
@@ -569,6 +569,7 @@ int build_hub(Matrix& m, int64_t nnz, int64_t H, int64_t cpb, int32_t dmin, hipS
     GCN_HIP_TRY(hipMemcpyAsync(h.defer, defer.p, (size_t)n, hipMemcpyDeviceToDevice, s));
     GCN_HIP_TRY(hipStreamSynchronize(s));
     h.state = 1;
+    count_build();                                           // A_rest; A_hot's column-blocked order has been counted
     return GCN_OK;
 }
 

@@ -363,3 +363,36 @@ def test_spmm_mask_that_is_the_output(f, algo, blocks):
     g.gcn_layer_backward(a, X, Gp, W, Gl, X, S, Y, Gp, g.ORDER_SPMM_FIRST)
     assert_close(host(Gp), host(apart), "Gprev")
     a.close()
+
+
+def test_build_count_is_what_was_built():
+    """Each stored order counts once, when it is there: a matrix that equals its transpose builds one for both directions, a
+    directed one builds two; a matrix that the hub schedule rejects builds none."""
+    g = G()
+    n = 5000
+    rs = np.random.default_rng(109)
+    src = dev(rs.integers(0, n, 120_000).astype(np.int32))
+    dst = dev((n * rs.random(120_000) ** 4).astype(np.int32))
+
+    def built(a, trans):
+        before = g.gcn_build_count()
+        g.gcn_spmm_prepare(a, trans, 16)
+        return g.gcn_build_count() - before
+    sym = g.SYMMETRISE | g.ADD_SELF_LOOPS | g.NORM_SYM | g.BUILD_TRANSPOSE
+    for flags, again in ((sym, 0), (g.ADD_SELF_LOOPS | g.NORM_ROW | g.BUILD_TRANSPOSE, 1)):
+        for settings, count in (((g.CFG_SPMM_ALGO, 2, g.CFG_SPMM_BLOCKS, 4), 1),                   # the column-blocked order
+                                ((g.CFG_SPMM_ALGO, 3, g.CFG_SPMM_BLOCKS, 1, g.CFG_SWEEP_HEAVY, 1 << 20), 1),    # no long rows
+                                ((g.CFG_SPMM_ALGO, 3, g.CFG_SPMM_BLOCKS, 1, g.CFG_SWEEP_HEAVY, 30), 2),
+                                ((g.CFG_SPMM_ALGO, 3, g.CFG_SPMM_BLOCKS, 4, g.CFG_SWEEP_HEAVY, 30), 3)):
+            a = g.gcn_csr_create(n, src, dst, flags)
+            for key, value in zip(settings[::2], settings[1::2]):
+                g.gcn_csr_config(a, key, value)
+            assert [built(a, 0), built(a, 1), built(a, 0), built(a, 1)] == [count, again * count, 0, 0], (flags, settings)
+            a.close()
+    a = g.gcn_csr_create(n, src, dst, sym)
+    for key, value in ((g.CFG_SPMM_ALGO, 4), (g.CFG_HUB_DMIN, 16), (g.CFG_HUB_BLOCK_COLS, 64)):
+        g.gcn_csr_config(a, key, value)
+    assert [built(a, 0), built(a, 1)] == [2, 0] and g.gcn_spmm_describe(a, 0, 16).startswith("hub(")
+    g.gcn_csr_config(a, g.CFG_HUB_DMIN, 4900)                       # longer than any row: rejected
+    assert built(a, 0) == 0 and g.gcn_spmm_describe(a, 0, 16).startswith("split(")
+    a.close()
