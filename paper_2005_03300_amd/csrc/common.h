@@ -13,6 +13,10 @@
 
 namespace gcn {
 
+// 16 bytes at any 4-byte aligned address: the same instruction as for an aligned one, so one kernel serves every width
+// and leading dimension.
+struct __attribute__((packed, aligned(4))) f4u { float x, y, z, w; };
+
 // Thread-local error text returned by gcn_last_error().
 void set_error(const char* fmt, ...);
 int fail(int code, const char* fmt, ...);

@@ -16,18 +16,17 @@ namespace gcn {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-struct __attribute__((packed, aligned(4))) f4u { float x, y, z, w; };   // 16 bytes at 4-byte alignment
-
 // 16-byte load of data that is read once: the non-temporal hint keeps the stream from displacing what other
 // wavefronts still need in the caches.  Measured on 14 M rows: +10 % on the A^T B kernel when every row of A is
 // whole 128-byte lines (256 floats: 2.67 -> 2.39 ms, 128 floats: 1.62 -> 1.42 ms), +2 % on the strip kernel; a loss
 // where neighbouring wavefronts share lines (A^T B at 300 floats per row: 4.13 -> 4.22 ms), so the callers decide.
+// The address need only be 4-byte aligned: the last columns of a padded row start anywhere.
+typedef floatx4 floatx4u __attribute__((aligned(4)));
 __device__ __forceinline__ float4 stream4(const float* p) {
-    const floatx4 v = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(p));
+    const floatx4 v = __builtin_nontemporal_load(reinterpret_cast<const floatx4u*>(p));
     return make_float4(v[0], v[1], v[2], v[3]);
 }
 
-// 16 bytes at any 4-byte aligned address (the same instruction as for an aligned one).
 __device__ __forceinline__ float4 load4(const float* p) {
     const f4u v = *reinterpret_cast<const f4u*>(p);
     return make_float4(v.x, v.y, v.z, v.w);

@@ -65,10 +65,6 @@ __device__ __forceinline__ float4 stream_load_f4(const float* p) {
     return make_float4(v.x, v.y, v.z, v.w);
 }
 
-// 16 bytes at any 4-byte aligned address: the same instruction as for an aligned one, so one kernel serves every width
-// and leading dimension.
-struct __attribute__((packed, aligned(4))) f4u { float x, y, z, w; };
-
 struct __attribute__((packed, aligned(4))) f2u { float x, y; };
 
 template <int VEC>

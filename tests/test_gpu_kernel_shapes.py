@@ -62,6 +62,20 @@ def test_gemm_tn_epilogues_and_pitch():
     assert_close(host(Cd)[:, :N], np.where(Zp > 0, want, 0), "TN + mask")
 
 
+@pytest.mark.parametrize("M,N,lda", [(33, 16, 64), (70, 16, 96), (129, 41, 160), (301, 16, 320), (302, 64, 352)])
+def test_gemm_tn_of_padded_rows(M, N, lda):
+    """Rows of A that are whole 128-byte lines but whose last four columns start at any multiple of 4 bytes (the loads of these
+    rows carry the non-temporal hint)."""
+    g = G()
+    K = 2500
+    H, S = synth.normal_features(K, M, 47), synth.normal_features(K, N, 48)
+    Hd = torch.full((K, lda), float("nan"), device="cuda")[:, :M].copy_(dev(H))
+    assert Hd.data_ptr() % 128 == 0
+    Cd = torch.full((M, N), float("nan"), device="cuda")
+    g.gcn_gemm(1, 0, Hd, dev(S), Cd)
+    assert_close(host(Cd), H.astype(np.float64).T @ S.astype(np.float64), f"TN {M}x{N}, pitch {lda}")
+
+
 @pytest.mark.parametrize("M,K,N", [(4100, 256, 64), (2049, 602, 64), (1000, 602, 256), (130, 1000, 48), (70, 1900, 20),
                                    (65, 2300, 17), (300, 240, 41), (1025, 512, 32)])
 def test_gemm_nn_wide_second_operand(M, K, N):
