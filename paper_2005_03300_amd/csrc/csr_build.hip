@@ -262,8 +262,7 @@ static int build_transpose(gcn_csr* a, const uint64_t* keys, unsigned cbits, uin
     const int64_t nnz = a->nnz, n = a->ncols;            // A^T has ncols rows
     GCN_TRY(device_alloc_t(&a->At.val, (size_t)nnz));
     if (nnz > 0)
-        GCN_TRY((prims::radix_sort<uint64_t, float>(keys, scratch_keys, a->A.val, a->At.val, (size_t)nnz, cbits, false, s, 0,
-                                                    false)));
+        GCN_TRY((prims::radix_sort<uint64_t, float>(keys, scratch_keys, a->A.val, a->At.val, (size_t)nnz, cbits, false, s, false)));
     a->At.nrows = n;
     a->At.ncols = a->n;
     GCN_TRY(compress_keys(a->At, n, nnz, scratch_keys, cbits, true, s));
@@ -300,7 +299,7 @@ static int create_impl(gcn_csr* a, int64_t n, int64_t m, const int32_t* src, con
                            (int)sym, (int)loops, cbits, k0.as<uint64_t>());
         GCN_LAUNCH_CHECK();
         GCN_TRY((prims::radix_sort<uint64_t, prims::NoValue>(k0.as<uint64_t>(), k1.as<uint64_t>(), nullptr, nullptr,
-                                                             (size_t)cap, loops ? cbits + bits_for(n) : kbits, false, s, 0, false)));
+                                                             (size_t)cap, loops ? cbits + bits_for(n) : kbits, false, s, false)));
         int64_t hcnt = 0;
         uint64_t last = 0;
         GCN_TRY(prims::unique_keys(k1.as<uint64_t>(), k0.as<uint64_t>(), cap, &hcnt, s));

@@ -437,11 +437,11 @@ int radix_passes(const K* kin, K* kout, const V* vin, V* vout, size_t n, const u
 // Stable sort of n keys by their bits [0, end_bit), ascending or descending; the payload (if V is
 // not NoValue) moves with its key.  The inputs are left as they were; outputs must not overlap them.
 // Digit positions at which every key holds the same byte are skipped.
-// first_bit > 0: the bits below it are known to be in order already (or not to matter).  probe == false: every digit
-// position is taken to vary (the caller packed its keys), which saves a pass over them and a wait for the stream.
+// probe == false: every digit position is taken to vary (the caller packed its keys), which saves a pass over them and a
+// wait for the stream.
 template <typename K, typename V>
 int radix_sort(const K* kin, K* kout, const V* vin, V* vout, size_t n, unsigned end_bit, bool descending, hipStream_t s,
-               unsigned first_bit = 0, bool probe = true) {
+               bool probe = true) {
     constexpr bool HAS_V = !std::is_same<V, NoValue>::value;
     constexpr int NB = sizeof(K);
     if (n == 0) return GCN_OK;
@@ -451,7 +451,7 @@ int radix_sort(const K* kin, K* kout, const V* vin, V* vout, size_t n, unsigned 
     unsigned shifts[NB], masks[NB];
     int npass = 0;
     if (!probe) {
-        for (unsigned lo = first_bit; lo < end_bit; lo += 8) {
+        for (unsigned lo = 0; lo < end_bit; lo += 8) {
             shifts[npass] = lo;
             masks[npass] = (1u << (end_bit - lo < 8 ? end_bit - lo : 8)) - 1u;
             ++npass;
