@@ -80,7 +80,7 @@ extern "C" {
 #define GCN_CFG_HUB_MB 7   /* hub schedule: size in MB of the packed buffer that holds the rows of X selected by the columns with the most entries (default 32) */
 #define GCN_CFG_HUB_DMIN 8 /* hub schedule: rows with at least this many entries are treated as long rows (default 64) */
 #define GCN_CFG_HUB_BLOCK_COLS 9 /* hub schedule: columns per block of the packed buffer (0, default: about 2 MB of the gathered panel; a multiple of 64) */
-#define GCN_CFG_SPLIT_LDS_KB 10 /* nonzero-split kernel for operands of up to 16 floats: LDS per workgroup in KB, padding included (18..64, default 28; 18 = no padding, and up to what the kernel itself uses none either).  Padding lowers the number of resident wavefronts, which keep 64 gathers in flight each */
+#define GCN_CFG_SPLIT_LDS_KB 10 /* nonzero-split kernels with 16 lane groups per wavefront (operands of 1 to 3 and of 4 to 16 floats): LDS per workgroup in KB, padding included, which lowers the number of resident workgroups (160 KB per compute unit).  18..64, without effect up to what the kernel uses itself (28 KB for 1 to 3 floats, 31 KB beyond); 0 (default): 38 KB for 1 to 3 floats, no padding beyond */
 
 #define GCN_CFG_FUSED_LAST_LAYER 11 /* gcn_epoch*: when the last layer runs SpMM-first at f_in = 16 with at most 256 classes, one kernel per 16-row strip of A^T H computes the logits, the loss, G^L, the weight gradient and G^L W^T, and the n x C matrices Z^L and G^L are not written to memory.  1 (default): fused, gcn_epoch_view of the last layer then points at memory the epoch did not write; 2: fused and Z^L, G^L stored for inspection; 0: separate kernels (stored) */
 

@@ -384,7 +384,7 @@ static int set_config(Config& c, int key, int value) {
             c.spmm_blocks = value;
             return GCN_OK;
         case GCN_CFG_SPLIT_LDS_KB:
-            if (value < 18 || value > 64) return fail(GCN_ERR_BADARG, "GCN_CFG_SPLIT_LDS_KB must be in [18, 64]");
+            if (value != 0 && (value < 18 || value > 64)) return fail(GCN_ERR_BADARG, "GCN_CFG_SPLIT_LDS_KB must be 0 or in [18, 64]");
             c.split_lds_kb = value;
             return GCN_OK;
         case GCN_CFG_SWEEP_WAVES:

@@ -150,7 +150,7 @@ struct Config {
     int spmm_algo = 0;
     int spmm_blocks = 0;
     int sweep_heavy = 1024;
-    int split_lds_kb = 28;       // nonzero-split kernels for rows of up to 64 bytes: LDS per workgroup incl. padding (18: none)
+    int split_lds_kb = 0;        // nonzero-split kernels with 16 lane groups: LDS per workgroup incl. padding (0: see occupancy_pad)
     int sweep_waves = 9;
     int hub_mb = 32;             // hub schedule: size of the packed buffer of hot rows of X, MB
     int hub_block_cols = 0;      // hub schedule: columns per block (0: about 2 MB of the gathered panel)

@@ -49,7 +49,7 @@ struct SplitArgs {
     const float* Zprev;
     int64_t ldzprev;
     float* carry;             // [nchunks][f]
-    int lds_kb;               // host side: LDS per workgroup of the narrow kernel, padding included (settings)
+    int lds_kb = 0;           // host side: GCN_CFG_SPLIT_LDS_KB
 };
 
 // The index/value stream is read exactly once per product: load it with the non-temporal hint so
@@ -1061,12 +1061,13 @@ __global__ void k_spmm_rowwise(int64_t n, const int64_t* __restrict__ rowptr, co
 // Dynamic LDS on top of the kernel's own, to lower the number of resident workgroups.  The kernels with 16 lane groups
 // per wavefront (rows of up to 64 bytes) keep 64 gathers in flight per wavefront and run slower with eight workgroups
 // per compute unit than with five (119 M entries at 16 columns: 0.64 -> 0.62 ms), which the 31 KB of the 16-byte kernel
-// leave by themselves; the one-float kernel takes four (102 M entries at one column: 612 -> 576 us).
+// leave by themselves; the one-float kernel, with 28 KB of its own, takes four (102 M entries at one column: 612 -> 576
+// us) and is padded to 38 KB.  A setting takes the place of both rules.
 template <int LPR, int VEC>
 static size_t occupancy_pad(int lds_kb, int epilogue) {
     if (LPR != 4) return 0;
     const size_t own = epilogue == GCN_EPI_MASK ? sizeof(WaveLds<LPR, VEC, GCN_EPI_MASK>) : sizeof(WaveLds<LPR, VEC, GCN_EPI_NONE>);
-    const size_t want = (size_t)(VEC == 1 ? lds_kb + 10 : lds_kb) << 10;
+    const size_t want = (size_t)(lds_kb > 0 ? lds_kb : (VEC == 1 ? 38 : 0)) << 10;
     return want > WAVES_PER_BLOCK * own ? want - WAVES_PER_BLOCK * own : 0;
 }
 
@@ -1114,7 +1115,7 @@ static int launch_split(const SplitArgs& args, int epilogue, hipStream_t s) {
     const int tile = LPR * VEC;
     const dim3 grid((unsigned)((args.nchunks + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK), (unsigned)((args.f + tile - 1) / tile));
     const dim3 block(64 * WAVES_PER_BLOCK);
-    const size_t pad = (occupancy_pad<LPR, VEC>(args.lds_kb, epilogue));
+    const size_t pad = occupancy_pad<LPR, VEC>(args.lds_kb, epilogue);
     timing_begin(s);
     switch (epilogue) {
         case GCN_EPI_NONE: hipLaunchKernelGGL((k_spmm_split<LPR, VEC, GCN_EPI_NONE>), grid, block, pad, s, args); break;
@@ -1591,7 +1592,6 @@ static int run_hub(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx
     if (rest.n_ne < rest.nrows) GCN_TRY(zero_empty_rows(rest, f, Z, ldz, s));
 
     SplitArgs ar;                                  // A_rest over X, into Z
-    ar.lds_kb = cfg_of(a).split_lds_kb;
     ar.colidx = rest.colidx; ar.val = o.pattern ? nullptr : rest.val; ar.flags = rest.flags; ar.sub_row = rest.sub_row;
     ar.row_scale = o.row_scale; ar.defer = h.defer;
     ar.ne_rows = rest.ne_rows; ar.rp = rest.ne_rowptr ? rest.ne_rowptr : rest.rowptr;
@@ -1599,7 +1599,6 @@ static int run_hub(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx
     ar.nnz = h.nnz_rest; ar.nsub = rest.nsub; ar.nchunks = rest.nchunks; ar.f = f;
     ar.X = X; ar.ldx = ldx; ar.Z = Z; ar.ldz = ldz; ar.Zprev = Zprev; ar.ldzprev = ldzprev; ar.carry = a->carry;
     SplitArgs ah;                                  // A_hot over the packed rows, into the partial rows
-    ah.lds_kb = ar.lds_kb;
     ah.colidx = b.colidx; ah.val = o.pattern ? nullptr : b.val; ah.flags = b.flags; ah.sub_row = b.sub_row;
     ah.row_scale = nullptr; ah.defer = nullptr; ah.ne_rows = nullptr; ah.rp = b.rp;
     ah.fix_list = b.fix_list; ah.n_fix = b.n_fix; ah.n_fix_long = b.n_fix_long;

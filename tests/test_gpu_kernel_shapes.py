@@ -410,3 +410,28 @@ def test_build_count_is_what_was_built():
     g.gcn_csr_config(a, g.CFG_HUB_DMIN, 4900)                       # longer than any row: rejected
     assert built(a, 0) == 0 and g.gcn_spmm_describe(a, 0, 16).startswith("split(")
     a.close()
+
+
+def test_split_lds_setting():
+    """The LDS padding of the narrow nonzero-split kernels: 0 is the default, a value holds as it is, and no value changes a
+    result; what is out of range is refused."""
+    g = G()
+    n = 40_000
+    rs = np.random.default_rng(110)
+    src, dst = [rs.integers(0, n, 600_000).astype(np.int32) for _ in range(2)]
+    a = g.gcn_csr_create(n, dev(src), dev(dst), g.SYMMETRISE | g.ADD_SELF_LOOPS | g.NORM_SYM)
+    g.gcn_csr_config(a, g.CFG_SPMM_BLOCKS, 1)
+    for f in (3, 16):
+        X, Zp = dev(synth.normal_features(n, f, 111)), dev(synth.normal_features(n, f, 112))
+        first = None
+        for kb in (0, 18, 28, 38, 64):
+            g.gcn_csr_config(a, g.CFG_SPLIT_LDS_KB, kb)
+            for epi in (g.EPI_NONE, g.EPI_MASK):
+                Z = torch.full((n, f), float("nan"), device="cuda")
+                g.gcn_spmm(a, 0, X, Z, epi, Zp)
+                first = Z if first is None else first
+                assert torch.equal(Z, first if epi == g.EPI_NONE else torch.where(Zp > 0, first, 0.0)), (f, kb, epi)
+    for kb in (-1, 17, 65):
+        with pytest.raises(g.GcnError):
+            g.gcn_csr_config(a, g.CFG_SPLIT_LDS_KB, kb)
+    a.close()
