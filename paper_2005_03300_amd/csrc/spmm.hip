@@ -159,13 +159,13 @@ __device__ __forceinline__ void stage_chunk(const SplitArgs& a, int64_t k0, int 
 }
 
 // What a wavefront keeps in LDS for its chunk.
-template <int LPR, int VEC, int EPI>
+template <int LPR, int VEC, bool MASK>
 struct __attribute__((aligned(16))) WaveLds {
     // A bit per column for as many of the rows begun here as leave five workgroups to a compute unit; the rows after them are
     // looked up one by one (all 512 rows a chunk can begin: 12 M entries in rows of 236, 16 columns: 72 -> 78 us).
     static constexpr int MASK_BYTES = VEC == 4 ? LPR / 2 : 4;
     static constexpr int WITHOUT_MASK = 2 * LDS_PER_WAVE * 4 + CHUNK * 4 + (SUBS_PER_CHUNK + 4) * 4 + 64 * VEC * 4;
-    static constexpr int MASK_ROWS = EPI != GCN_EPI_MASK ? 0 : (8192 - WITHOUT_MASK) / MASK_BYTES;
+    static constexpr int MASK_ROWS = MASK ? (8192 - WITHOUT_MASK) / MASK_BYTES : 0;
     int32_t col[LDS_PER_WAVE];
     float val[LDS_PER_WAVE];                    // values; of a value-free product the factors of the rows begun here
     int32_t row[CHUNK];                         // the rows begun here; the sign bit says that their sum is stored raw
@@ -186,7 +186,7 @@ struct __attribute__((aligned(16))) WaveLds {
 // them are slower (119 M entries over column blocks: 611 us, 620 with two sets).  12 M entries in rows of 236 at 64 columns, operand
 // in the L2s: 187 -> 168 us; 2 M at 32: 34 -> 27; 33 M, packed hub and rest at 16: 318 -> 293; 9 M in rows of 9 at
 // 32: 203 -> 200 (line fills).
-template <int LPR, int VEC, int EPI, class Lds>
+template <int LPR, int VEC, int EPI, bool AHEAD, class Lds>
 __device__ __forceinline__ void split_body(const SplitArgs& a, int64_t grp, Lds* lds) {
     constexpr int G = 64 / LPR;                 // lane groups per wavefront
     constexpr int LEN = CHUNK / G, NW = LEN / SUB;              // entries and flag words per group
@@ -229,11 +229,11 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int64_t grp, Lds*
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     __builtin_amdgcn_wave_barrier();
     // The mask of those rows, as bits: fetched when a row starts or ends, it drained the gathers in flight (hub schedule,
-    // 33 M entries at 16 columns: 375 -> 333 us; 1.9 M at 64: 75 -> 64; 1.9 M at 41, k_spmm_line: 87 -> 71).  Where all wavefronts
-    // start together and rows are even it costs a burst at the beginning (1 M in rows of 21, 64 columns: 39 -> 44).
-    if constexpr (EPI == GCN_EPI_MASK) {
+    // 33 M entries at 16 columns: 375 -> 333 us; 1.9 M at 64: 75 -> 64; 1.9 M at 41, k_spmm_line: 87 -> 71).  Not AHEAD: see
+    // many_row_starts.
+    const uint32_t mpitch = (uint32_t)a.ldzprev * 4u;
+    if constexpr (EPI == GCN_EPI_MASK && AHEAD) {
         constexpr int AT_ONCE = 4, MB = Lds::MASK_BYTES;
-        const uint32_t mpitch = (uint32_t)a.ldzprev * 4u;
         const int staged = begun < Lds::MASK_ROWS ? begun : Lds::MASK_ROWS;
         for (int i0 = g; i0 < staged; i0 += AT_ONCE * G) {
             float m[AT_ONCE][VEC];
@@ -278,6 +278,11 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int64_t grp, Lds*
         if constexpr (EPI == GCN_EPI_RELU) {
 #pragma unroll
             for (int u = 0; u < VEC; ++u) v[u] = v[u] > 0.f || row < 0 ? v[u] : 0.f;
+        } else if constexpr (EPI == GCN_EPI_MASK && !AHEAD) {
+            float m[VEC];
+            load_vec<VEC>(m, at_row(a.Zprev + col0, (uint32_t)row & 0x7fffffffu, mpitch));
+#pragma unroll
+            for (int u = 0; u < VEC; ++u) v[u] = m[u] > 0.f || row < 0 ? v[u] : 0.f;
         } else if constexpr (EPI == GCN_EPI_MASK) {
 #pragma unroll
             for (int u = 0; u < VEC; ++u) v[u] = through >> u & 1 || row < 0 ? v[u] : 0.f;
@@ -293,10 +298,10 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int64_t grp, Lds*
         owned = true;
         row = L.row[at];
         if (!a.val) scale = L.val[at];
-        if constexpr (EPI == GCN_EPI_MASK) {
+        if constexpr (EPI == GCN_EPI_MASK && AHEAD) {
             if (at >= Lds::MASK_ROWS) {
                 float m[VEC];
-                load_vec<VEC>(m, at_row(a.Zprev + col0, (uint32_t)row & 0x7fffffffu, (uint32_t)a.ldzprev * 4u));
+                load_vec<VEC>(m, at_row(a.Zprev + col0, (uint32_t)row & 0x7fffffffu, mpitch));
                 through = 0;
 #pragma unroll
                 for (int u = 0; u < VEC; ++u) through |= m[u] > 0.f ? 1 << u : 0;
@@ -391,10 +396,10 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int64_t grp, Lds*
     }
 }
 
-template <int LPR, int VEC, int EPI>
+template <int LPR, int VEC, int EPI, bool AHEAD = true>
 __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_split(SplitArgs a) {
-    __shared__ WaveLds<LPR, VEC, EPI> lds[WAVES_PER_BLOCK];
-    split_body<LPR, VEC, EPI>(a, blockIdx.x, lds);
+    __shared__ WaveLds<LPR, VEC, EPI == GCN_EPI_MASK && AHEAD> lds[WAVES_PER_BLOCK];
+    split_body<LPR, VEC, EPI, AHEAD>(a, blockIdx.x, lds);
 }
 
 // The same product for matrices of few chunks, which is a chain of memory latencies, launches and first executions of
@@ -962,10 +967,10 @@ template <int LPR, int VEC, int EPI>
 __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_split_pair(SplitArgs a, SplitArgs b, int ra, int rb) {
     // ra + rb == 8.  Workgroups go to the eight XCDs round-robin; the rotation by q lets every XCD see
     // both kinds of work in turn.
-    __shared__ WaveLds<LPR, VEC, EPI> lds[WAVES_PER_BLOCK];
+    __shared__ WaveLds<LPR, VEC, EPI == GCN_EPI_MASK> lds[WAVES_PER_BLOCK];
     const unsigned q = blockIdx.x / 8, r = (blockIdx.x + q) % 8;
-    if ((int)r < ra) split_body<LPR, VEC, EPI>(a, (int64_t)q * ra + r, lds);
-    else split_body<LPR, VEC, GCN_EPI_NONE>(b, (int64_t)q * rb + (r - ra), lds);
+    if ((int)r < ra) split_body<LPR, VEC, EPI, true>(a, (int64_t)q * ra + r, lds);
+    else split_body<LPR, VEC, GCN_EPI_NONE, true>(b, (int64_t)q * rb + (r - ra), lds);
 }
 
 // Adds, in ascending chunk order, the carries of the chunks a row runs on into, then applies the epilogue.  One LPR-lane
@@ -1066,7 +1071,7 @@ __global__ void k_spmm_rowwise(int64_t n, const int64_t* __restrict__ rowptr, co
 template <int LPR, int VEC>
 static size_t occupancy_pad(int lds_kb, int epilogue) {
     if (LPR != 4) return 0;
-    const size_t own = epilogue == GCN_EPI_MASK ? sizeof(WaveLds<LPR, VEC, GCN_EPI_MASK>) : sizeof(WaveLds<LPR, VEC, GCN_EPI_NONE>);
+    const size_t own = epilogue == GCN_EPI_MASK ? sizeof(WaveLds<LPR, VEC, true>) : sizeof(WaveLds<LPR, VEC, false>);
     const size_t want = (size_t)(lds_kb > 0 ? lds_kb : (VEC == 1 ? 38 : 0)) << 10;
     return want > WAVES_PER_BLOCK * own ? want - WAVES_PER_BLOCK * own : 0;
 }
@@ -1090,6 +1095,12 @@ static int fixup_of(const SplitArgs& args, int epilogue, hipStream_t s) {
     if (VEC == 4 && args.f % 4 != 0) return launch_fixup<16, 1>(args, epilogue, s);
     return launch_fixup<LPR, VEC>(args, epilogue, s);
 }
+
+// Whether a masked product over 17 columns and more looks its mask up when a row ends instead of keeping bits: chunks that
+// begin more rows than there is room for bits read the rest one by one in any case, and the burst for those that fit
+// costs more than it saves.  Rows of up to 3.5 entries on average: in rows of 3 at 32 columns 1 M entries take 50 us with
+// bits and 41 without, 20 M 686 and 575; in rows of 5 20 M take 347 and 479.  At 16 columns the bits of all rows fit and win.
+static bool many_row_starts(const SplitArgs& a) { return 2 * a.nnz <= 7 * a.n_ne; }
 
 template <int LPR, int VEC>
 static int launch_split(const SplitArgs& args, int epilogue, hipStream_t s) {
@@ -1120,7 +1131,15 @@ static int launch_split(const SplitArgs& args, int epilogue, hipStream_t s) {
     switch (epilogue) {
         case GCN_EPI_NONE: hipLaunchKernelGGL((k_spmm_split<LPR, VEC, GCN_EPI_NONE>), grid, block, pad, s, args); break;
         case GCN_EPI_RELU: hipLaunchKernelGGL((k_spmm_split<LPR, VEC, GCN_EPI_RELU>), grid, block, pad, s, args); break;
-        default: hipLaunchKernelGGL((k_spmm_split<LPR, VEC, GCN_EPI_MASK>), grid, block, pad, s, args); break;
+        default:
+            if constexpr (VEC == 4 && LPR == 8) {
+                if (many_row_starts(args)) {
+                    hipLaunchKernelGGL((k_spmm_split<LPR, VEC, GCN_EPI_MASK, false>), grid, block, pad, s, args);
+                    break;
+                }
+            }
+            hipLaunchKernelGGL((k_spmm_split<LPR, VEC, GCN_EPI_MASK>), grid, block, pad, s, args);
+            break;
     }
     timing_end(s);
     GCN_LAUNCH_CHECK();

@@ -435,3 +435,29 @@ def test_split_lds_setting():
         with pytest.raises(g.GcnError):
             g.gcn_csr_config(a, g.CFG_SPLIT_LDS_KB, kb)
     a.close()
+
+
+@pytest.mark.parametrize("f", [17, 20, 32, 33, 64, 128])
+@pytest.mark.parametrize("lengths", [[3, 4], [4], [1], [1, 1, 1, 0, 900] + [1] * 500, [2, 0, 3]])
+def test_spmm_mask_on_both_sides_of_its_rule(f, lengths):
+    """Matrices whose mean row is just up to, and just beyond, the length below which the mask is looked up when a row ends, with
+    rows that cross chunks and empty rows among them; value-free with row factors too: the masked product is the plain
+    one with the masked places set to zero, bit by bit."""
+    g = G()
+    nc = 2000
+    lens = np.tile(lengths, 500_000 // sum(lengths))
+    rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    within = np.arange(rowptr[-1]) - np.repeat(rowptr[:-1], lens)
+    colidx = (np.repeat(np.random.default_rng(113).integers(0, nc - 900, lens.size), lens) + within).astype(np.int32)
+    n = lens.size
+    val = np.random.default_rng(114).standard_normal(colidx.size).astype(np.float32)
+    a = g.gcn_csr_create_from_csr_rect(n, nc, dev(rowptr), dev(colidx), dev(val), 0)
+    g.gcn_csr_config(a, g.CFG_SPMM_BLOCKS, 1)
+    X, M = dev(synth.normal_features(nc, f, 115)), dev(synth.normal_features(n, f, 116))
+    scale = dev(synth.normal_features(n, 1, 117)[:, 0])
+    for call in (lambda Z, *m: g.gcn_spmm(a, 0, X, Z, *m), lambda Z, *m: g.gcn_spmm_pattern(a, 0, X, Z, scale, *m)):
+        plain, masked = torch.empty(n, f, device="cuda"), torch.full((n, f), float("nan"), device="cuda")
+        call(plain)
+        call(masked, g.EPI_MASK, M)
+        assert torch.equal(masked, torch.where(M > 0, plain, 0.0))
+    a.close()
