@@ -39,30 +39,31 @@ MEASURED_TRAFFIC = {
     ("rmat20_spmm_f128", 128): {
         "bytes": 10045335483,
         "kernels": "k_spmm_split<8,4> over 4 panels of 32 columns + k_spmm_fixup",
-        "schedule": "split(chunks=63376)",
+        "schedule": "split(chunks=63376,kernel=k_spmm_split<8,4>)",
         "profile": "profiles/spmm_split_rmat20_f128.txt"},
     ("chunglu_reddit_gcn_602_16_16_41", 16): {
         "bytes": 1033356854,
         "kernels": "k_scale_rows + k_spmm_split<4,4> over the column-blocked copy + k_spmm_fixup + k_block_reduce",
-        "schedule": "blocked(blocks=8,cols_per_block=29696,partial_rows=1863720,chunks=224269)"
+        "schedule": "blocked(blocks=8,cols_per_block=29696,partial_rows=1863720,chunks=224269,kernel=k_spmm_split<4,4>)"
                     "; value-free (operand rows pre-scaled by d^-1/2, output rows scaled)",
         "profile": "profiles/spmm_blocked_chunglu_reddit_f16.txt"},
     ("rmat_amazon_gcn_300_16_16_24", 16): {
         "bytes": 20042035304,
         "kernels": "k_pack_rows + k_spmm_split_pair<4,4> (paired launch of the hub schedule) + 2 x k_spmm_fixup + k_block_reduce",
-        "schedule": "hub(hot_cols=524288,cols_per_block=32768,long_row>=64,nnz_hot=148858651,nnz_rest=96949372,partial_rows=7701691)",
+        "schedule": "hub(hot_cols=524288,cols_per_block=32768,long_row>=64,nnz_hot=148858651,nnz_rest=96949372,partial_rows=7701691,"
+                    "kernel=k_spmm_split_pair<4,4>)",
         "profile": "profiles/spmm_hub_rmat_amazon_f16.txt"},
     ("chunglu_protein_gcn_128_16_16_256", 16): {
         "bytes": 82950924194,
         "kernels": "k_scale_rows + 15 x k_spmm_sweep<4> + k_spmm_split<4,4> (column-blocked, long rows) + k_spmm_fixup + k_block_reduce",
-        "schedule": "sweep(entries_per_step=16,rows_per_task=256,long_row>1024,tasks=34163,launches=15,stored=936862448)"
-                    "+long_rows:blocked(blocks=101,cols_per_block=87040,partial_rows=12649811,chunks=745738)"
+        "schedule": "sweep(entries_per_step=16,rows_per_task=256,long_row>1024,tasks=34163,launches=15,stored=936862448,kernel=k_spmm_sweep<4>)"
+                    "+long_rows:blocked(blocks=101,cols_per_block=87040,partial_rows=12649811,chunks=745738,kernel=k_spmm_split<4,4>)"
                     "; value-free (operand rows pre-scaled by d^-1/2, output rows scaled)",
         "profile": "profiles/spmm_sweep_chunglu_protein_f16_default_command.txt"},
 }
 
 # kernels inside the library's event bracket of one product, by the schedule the library reports
-SCHEDULE_KERNELS = {1: "k_spmm_rowwise", 2: "k_spmm_split + k_spmm_fixup",
+SCHEDULE_KERNELS = {1: "k_spmm_rowwise", 2: "the nonzero-split kernel that extra.schedule names + k_spmm_fixup",
                     3: "k_spmm_sweep (rows <= 1024 entries) + k_spmm_split, k_spmm_fixup, k_block_reduce (column-blocked, longer rows)",
                     4: "k_pack_rows + k_spmm_split_pair (hub schedule: long rows x hot columns over packed rows + the rest) + k_spmm_fixup + k_block_reduce",
                     5: "k_spmm_split (column-blocked) + k_spmm_fixup + k_block_reduce"}

@@ -159,7 +159,7 @@ int gcn_spmm(gcn_csr* a, int trans, int32_t f, const float* X, int64_t ldx, floa
  * gcn_spmm / gcn_spmm_pattern would build or grow on their first call at that width -- the stored order the
  * schedule needs and the handle's buffers -- without running a product.  Synchronises `stream`.  Copies for
  * several widths are kept side by side, so a model whose products alternate between widths never rebuilds.
- * gcn_spmm_describe writes the schedule such a product takes and its launch shape as text into `out`
+ * gcn_spmm_describe writes the schedule such a product takes, its launch shape and its main kernel as text into `out`
  * (host, out_bytes including the terminator; truncated if too small), building it like gcn_spmm_prepare if
  * needed; reports and tests use it to tie a measurement to the schedule it was taken on. */
 int gcn_spmm_prepare(gcn_csr* a, int trans, int32_t f, void* stream);

@@ -1102,27 +1102,26 @@ static int fixup_of(const SplitArgs& args, int epilogue, hipStream_t s) {
 // bits and 41 without, 20 M 686 and 575; in rows of 5 20 M take 347 and 479.  At 16 columns the bits of all rows fit and win.
 static bool many_row_starts(const SplitArgs& a) { return 2 * a.nnz <= 7 * a.n_ne; }
 
+template <int LPR>
+static int launch_few(const SplitArgs& args, int epilogue, hipStream_t s) {
+    const int64_t panels = (args.f + LPR * 4 - 1) / (LPR * 4);
+    const dim3 grid((unsigned)((args.nchunks + WAVES_PER_BLOCK - 2) / (WAVES_PER_BLOCK - 1)), (unsigned)panels);
+    constexpr size_t lds = WAVES_PER_BLOCK * SUB * 64 * sizeof(float4);
+    SplitArgs few = args;
+    few.n_fix = args.n_fix_long;                  // they come first in the list
+    timing_begin(s);
+    switch (epilogue) {
+        case GCN_EPI_NONE: launch_lds<k_spmm_few<LPR, GCN_EPI_NONE>>(grid, 64 * WAVES_PER_BLOCK, lds, s, few); break;
+        case GCN_EPI_RELU: launch_lds<k_spmm_few<LPR, GCN_EPI_RELU>>(grid, 64 * WAVES_PER_BLOCK, lds, s, few); break;
+        default: launch_lds<k_spmm_few<LPR, GCN_EPI_MASK>>(grid, 64 * WAVES_PER_BLOCK, lds, s, few); break;
+    }
+    timing_end(s);
+    GCN_LAUNCH_CHECK();
+    return fixup_of<LPR, 4>(few, epilogue, s);
+}
+
 template <int LPR, int VEC>
 static int launch_split(const SplitArgs& args, int epilogue, hipStream_t s) {
-    const int64_t panels = (args.f + LPR * VEC - 1) / (LPR * VEC), waves = args.nchunks * panels;
-    if constexpr (VEC == 4) {
-        // as long as the workgroups of three chunks run side by side (their LDS allows one per compute unit)
-        if (waves <= (int64_t)device_info().cus * (WAVES_PER_BLOCK - 1)) {
-            const dim3 grid((unsigned)((args.nchunks + WAVES_PER_BLOCK - 2) / (WAVES_PER_BLOCK - 1)), (unsigned)panels);
-            constexpr size_t lds = WAVES_PER_BLOCK * SUB * 64 * sizeof(float4);
-            SplitArgs few = args;
-            few.n_fix = args.n_fix_long;                  // they come first in the list
-            timing_begin(s);
-            switch (epilogue) {
-                case GCN_EPI_NONE: launch_lds<k_spmm_few<LPR, GCN_EPI_NONE>>(grid, 64 * WAVES_PER_BLOCK, lds, s, few); break;
-                case GCN_EPI_RELU: launch_lds<k_spmm_few<LPR, GCN_EPI_RELU>>(grid, 64 * WAVES_PER_BLOCK, lds, s, few); break;
-                default: launch_lds<k_spmm_few<LPR, GCN_EPI_MASK>>(grid, 64 * WAVES_PER_BLOCK, lds, s, few); break;
-            }
-            timing_end(s);
-            GCN_LAUNCH_CHECK();
-            return fixup_of<LPR, VEC>(few, epilogue, s);
-        }
-    }
     const int tile = LPR * VEC;
     const dim3 grid((unsigned)((args.nchunks + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK), (unsigned)((args.f + tile - 1) / tile));
     const dim3 block(64 * WAVES_PER_BLOCK);
@@ -1163,13 +1162,6 @@ static int launch_line(const SplitArgs& args, int epilogue, hipStream_t s) {
 
 static int launch_ragged(const SplitArgs& args, int epilogue, hipStream_t s) {
     const unsigned panels = (unsigned)((args.f + 63) / 64);
-    // k_spmm_ragged puts four wavefronts to a chunk: worth it while that is what fills the GPU (0.3 M entries at 41 columns,
-    // 620 chunks: 22 us, k_spmm_line 27; 1 M, 1900 chunks: 51 and 49; 0.4 M at 101, 1660 chunks and panels: 52 and 34).
-    if (args.nchunks * panels > (int64_t)device_info().cus * 4) {
-        // two columns per lane where that halves the number of panels: every panel walks all entries
-        if ((args.f + 127) / 128 * 2 == (int)panels) return launch_line<2>(args, epilogue, s);
-        return launch_line<1>(args, epilogue, s);
-    }
     timing_begin(s);
     const int lanes = args.f >= 64 ? 16 : (args.f + 3) / 4;
     const dim3 grid((unsigned)args.nchunks, panels);
@@ -1188,8 +1180,11 @@ static int launch_ragged(const SplitArgs& args, int epilogue, hipStream_t s) {
 // Whether a matrix goes through k_spmm_short: its rows are all short, and all wavefronts are resident at once (eight per
 // compute unit at this kernel's registers).  With more rows the even chunks of k_spmm_split win (rows of 21 entries at 16
 // columns: 20 K rows 9.7 against 11.0 us, 50 K rows 17.7 against 14.2).
+static int short_lanes(int32_t f) {                // as in choose_split: the pieces of a row follow from them
+    return f % 4 == 0 ? (f <= 16 ? 4 : 8) : (f <= 8 ? 2 : (f <= 16 ? 4 : (f <= 32 ? 8 : 16)));
+}
 static bool short_rows(const Matrix& m, int32_t f) {
-    const int lpr = f % 4 == 0 ? (f <= 16 ? 4 : 8) : (f <= 8 ? 2 : (f <= 16 ? 4 : (f <= 32 ? 8 : 16)));
+    const int lpr = short_lanes(f);
     return f >= 4 && m.max_degree <= SHORT_ROW && m.nrows * lpr * ((f + 4 * lpr - 1) / (4 * lpr)) <= (int64_t)device_info().cus * 8 * 64;
 }
 
@@ -1204,7 +1199,7 @@ static int launch_short(const SplitArgs& args, int64_t nrows, int epilogue, hipS
         }
     };
     timing_begin(s);
-    // lanes per row and slices as in run_split: the pieces of a row follow from them
+    // lanes per row as in short_lanes, slices as the nonzero-split kernels cut them at this width
     if (args.f % 4 == 0) {
         if (args.f <= 16) go(std::integral_constant<int, 4>(), std::integral_constant<int, 32>());
         else go(std::integral_constant<int, 8>(), std::integral_constant<int, 64>());
@@ -1415,18 +1410,26 @@ static int launch_sweep(const SweepArgs& args, int64_t ntasks, int sweep_waves, 
     return GCN_OK;
 }
 
-// Chooses the lane layout for one nonzero-split product and launches it.
-static int run_split(const SplitArgs& args, int epilogue, hipStream_t s, bool any_order, bool l2_resident = false) {
-    const int32_t f = args.f;
-    if (f < 4) return launch_split<4, 1>(args, epilogue, s);
+// The kernel and lane layout of one nonzero-split product.
+struct SplitChoice {
+    enum Kernel { SPLIT, FEW, RAGGED, LINE } kernel;
+    int lpr, vec;                                 // lanes per row of X (RAGGED: from the width), floats per lane
+};
+
+static SplitChoice choose_split(int32_t f, int64_t nchunks, bool any_order, bool l2_resident) {
+    const int64_t cus = device_info().cus;
+    if (f < 4) return {SplitChoice::SPLIT, 4, 1};
     if (f % 4 != 0 && !any_order) {
-        if (f <= 8) return launch_split<8, 1>(args, epilogue, s);
-        if (f <= 16) return launch_split<16, 1>(args, epilogue, s);
-        if (f <= 32) return launch_split<32, 1>(args, epilogue, s);
-        return launch_ragged(args, epilogue, s);
+        if (f <= 8) return {SplitChoice::SPLIT, 8, 1};
+        if (f <= 16) return {SplitChoice::SPLIT, 16, 1};
+        if (f <= 32) return {SplitChoice::SPLIT, 32, 1};
+        // k_spmm_ragged puts four wavefronts to a chunk: worth it while that is what fills the GPU (0.3 M entries at 41 columns,
+        // 620 chunks: 22 us, k_spmm_line 27; 1 M, 1900 chunks: 51 and 49; 0.4 M at 101, 1660 chunks and panels: 52 and 34).
+        const int panels = (f + 63) / 64;
+        if (nchunks * panels <= cus * 4) return {SplitChoice::RAGGED, 0, 4};
+        // two columns per lane where that halves the number of panels: every panel walks all entries
+        return {SplitChoice::LINE, 64, (f + 127) / 128 * 2 == panels ? 2 : 1};
     }
-    if (f <= 16) return launch_split<4, 4>(args, epilogue, s);
-    if (f <= 32) return launch_split<8, 4>(args, epilogue, s);
     // Wider operands are processed in panels of 32 columns (one 128-byte line per gathered row): the panel of X that the
     // gathers touch is 4x smaller than at f = 128, so far more of it stays in L2, at the price of re-reading the
     // index/value stream once per panel.
@@ -1435,8 +1438,42 @@ static int run_split(const SplitArgs& args, int epilogue, hipStream_t s, bool an
     // fills: 1.46 -> 1.69 ms, so not there).
     // Rows that are not whole 16-byte pieces (only without an order to keep) straddle lines wherever they are cut: one
     // panel up to 64 columns (41 columns, 1 M rows: 1.20 ms in two panels, 0.89 in one).
-    if ((f >= 64 && l2_resident) || (f % 4 != 0 && f <= 64)) return launch_split<16, 4>(args, epilogue, s);
-    return launch_split<8, 4>(args, epilogue, s);
+    int lpr = 8;
+    if (f <= 16) lpr = 4;
+    else if (f > 32 && ((f >= 64 && l2_resident) || (f % 4 != 0 && f <= 64))) lpr = 16;
+    // k_spmm_few as long as its workgroups of three chunks run side by side (their LDS allows one per compute unit)
+    const int64_t panels = (f + 4 * lpr - 1) / (4 * lpr);
+    return {nchunks * panels <= cus * (WAVES_PER_BLOCK - 1) ? SplitChoice::FEW : SplitChoice::SPLIT, lpr, 4};
+}
+
+static std::string kernel_name(const SplitChoice& c) {
+    switch (c.kernel) {
+        case SplitChoice::FEW: return "k_spmm_few<" + std::to_string(c.lpr) + ">";
+        case SplitChoice::RAGGED: return "k_spmm_ragged";
+        case SplitChoice::LINE: return "k_spmm_line<" + std::to_string(c.vec) + ">";
+        default: return "k_spmm_split<" + std::to_string(c.lpr) + "," + std::to_string(c.vec) + ">";
+    }
+}
+
+static int run_split(const SplitArgs& args, int epilogue, hipStream_t s, const SplitChoice& c) {
+    switch (c.kernel) {
+        case SplitChoice::RAGGED: return launch_ragged(args, epilogue, s);
+        case SplitChoice::LINE: return c.vec == 2 ? launch_line<2>(args, epilogue, s) : launch_line<1>(args, epilogue, s);
+        case SplitChoice::FEW:
+            if (c.lpr == 4) return launch_few<4>(args, epilogue, s);
+            if (c.lpr == 8) return launch_few<8>(args, epilogue, s);
+            return launch_few<16>(args, epilogue, s);
+        default: break;
+    }
+    if (c.vec == 4) {
+        if (c.lpr == 4) return launch_split<4, 4>(args, epilogue, s);
+        if (c.lpr == 8) return launch_split<8, 4>(args, epilogue, s);
+        return launch_split<16, 4>(args, epilogue, s);
+    }
+    if (c.lpr == 4) return launch_split<4, 1>(args, epilogue, s);
+    if (c.lpr == 8) return launch_split<8, 1>(args, epilogue, s);
+    if (c.lpr == 16) return launch_split<16, 1>(args, epilogue, s);
+    return launch_split<32, 1>(args, epilogue, s);
 }
 
 // How many column blocks to cut X into so that one block of the gathered panel stays in one L2
@@ -1497,10 +1534,11 @@ static int run_matrix(gcn_csr* a, Matrix& mm, const int32_t* row_map, int64_t nn
         GCN_TRY(want_blocked(mm, nnz, cpb, s));
         const Blocked& b = mm.blk;
         GCN_TRY(grow_retire(a, &a->partial, &a->partial_bytes, (size_t)b.nrows * (size_t)f * sizeof(float)));
+        const SplitChoice choice = choose_split(f, mm.nchunks, o.any_order, true);
         if (o.describe) {
-            char t[160];
-            snprintf(t, sizeof t, "blocked(blocks=%d,cols_per_block=%lld,partial_rows=%lld,chunks=%lld)", (int)b.nblocks,
-                     (long long)b.cols_per_block, (long long)b.nrows, (long long)mm.nchunks);
+            char t[200];
+            snprintf(t, sizeof t, "blocked(blocks=%d,cols_per_block=%lld,partial_rows=%lld,chunks=%lld,kernel=%s)", (int)b.nblocks,
+                     (long long)b.cols_per_block, (long long)b.nrows, (long long)mm.nchunks, kernel_name(choice).c_str());
             *o.describe += t;
         }
         if (o.dry) return GCN_OK;
@@ -1509,13 +1547,16 @@ static int run_matrix(gcn_csr* a, Matrix& mm, const int32_t* row_map, int64_t nn
         args.ne_rows = nullptr; args.rp = b.rp; args.row_scale = nullptr;     // the scale belongs to the reduced row
         args.fix_list = b.fix_list; args.n_fix = b.n_fix; args.n_fix_long = b.n_fix_long;
         args.Z = a->partial; args.ldz = f; args.Zprev = nullptr; args.ldzprev = 0;
-        GCN_TRY(run_split(args, GCN_EPI_NONE, s, o.any_order, true));
+        GCN_TRY(run_split(args, GCN_EPI_NONE, s, choice));
         if (f >= 4) return launch_block_reduce<4>(mm.nrows, f, b, row_map, o.row_scale, o.accumulate ? 1 : 0, a->partial, Z, ldz, epilogue, Zprev, ldzprev, s);
         return launch_block_reduce<1>(mm.nrows, f, b, row_map, o.row_scale, o.accumulate ? 1 : 0, a->partial, Z, ldz, epilogue, Zprev, ldzprev, s);
     }
+    const SplitChoice choice = choose_split(f, mm.nchunks, o.any_order, false);
+    const bool short_kernel = !row_map && short_rows(mm, f);
     if (o.describe) {
-        char t[96];
-        snprintf(t, sizeof t, "split(chunks=%lld)", (long long)mm.nchunks);
+        char t[120];
+        snprintf(t, sizeof t, "split(chunks=%lld,kernel=%s)", (long long)mm.nchunks,
+                 short_kernel ? ("k_spmm_short<" + std::to_string(short_lanes(f)) + ">").c_str() : kernel_name(choice).c_str());
         *o.describe += t;
     }
     if (o.dry) return GCN_OK;
@@ -1527,12 +1568,12 @@ static int run_matrix(gcn_csr* a, Matrix& mm, const int32_t* row_map, int64_t nn
     args.rp = mm.ne_rowptr ? mm.ne_rowptr : mm.rowptr;
     args.fix_list = mm.fix_list; args.n_fix = mm.n_fix; args.n_fix_long = mm.n_fix_long;
     args.Z = Z; args.ldz = ldz; args.Zprev = Zprev; args.ldzprev = ldzprev;
-    if (!row_map && short_rows(mm, f)) {
+    if (short_kernel) {
         args.rp = mm.rowptr;
         return launch_short(args, mm.nrows, epilogue, s);
     }
     if (!row_map && mm.n_ne < mm.nrows) GCN_TRY(zero_empty_rows(mm, f, Z, ldz, s));
-    return run_split(args, epilogue, s, o.any_order);
+    return run_split(args, epilogue, s, choice);
 }
 
 // ---- hub schedule -----------------------------------------------------------------------------------------
@@ -1598,9 +1639,9 @@ static int run_hub(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx
     GCN_TRY(grow_retire(a, &a->carry2, &a->carry2_bytes, (size_t)hot.nchunks * (size_t)f * sizeof(float)));
     GCN_TRY(grow_retire(a, &a->partial, &a->partial_bytes, (size_t)b.nrows * (size_t)f * sizeof(float)));
     if (o.describe) {
-        char t[200];
-        snprintf(t, sizeof t, "hub(hot_cols=%lld,cols_per_block=%lld,long_row>=%d,nnz_hot=%lld,nnz_rest=%lld,partial_rows=%lld)",
-                 (long long)h.H, (long long)h.cpb, (int)h.dmin, (long long)h.nnz_hot, (long long)h.nnz_rest, (long long)b.nrows);
+        char t[240];
+        snprintf(t, sizeof t, "hub(hot_cols=%lld,cols_per_block=%lld,long_row>=%d,nnz_hot=%lld,nnz_rest=%lld,partial_rows=%lld,kernel=k_spmm_split_pair<%d,4>)",
+                 (long long)h.H, (long long)h.cpb, (int)h.dmin, (long long)h.nnz_hot, (long long)h.nnz_rest, (long long)b.nrows, f > 16 ? 8 : 4);
         *o.describe += t;
     }
     if (o.dry) return GCN_OK;
@@ -1790,10 +1831,10 @@ int spmm_launch(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx, f
         const Sweep& w = m.swp;
         if (o.describe) {
             const int64_t cap = (int64_t)device_info().cus * cfg.sweep_waves;
-            char t[200];
-            snprintf(t, sizeof t, "sweep(entries_per_step=%d,rows_per_task=%d,long_row>%d,tasks=%lld,launches=%lld,stored=%lld)",
+            char t[240];
+            snprintf(t, sizeof t, "sweep(entries_per_step=%d,rows_per_task=%d,long_row>%d,tasks=%lld,launches=%lld,stored=%lld,kernel=k_spmm_sweep<%d>)",
                      64 / LPRs, (int)rb, (int)cfg.sweep_heavy, (long long)w.ntasks,
-                     (long long)(((w.ntasks + cap - 1) / cap) * ((f + W - 1) / W)), (long long)w.padded);
+                     (long long)(((w.ntasks + cap - 1) / cap) * ((f + W - 1) / W)), (long long)w.padded, LPRs);
             *o.describe += t;
         }
         if (!o.dry) {

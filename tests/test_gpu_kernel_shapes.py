@@ -461,3 +461,30 @@ def test_spmm_mask_on_both_sides_of_its_rule(f, lengths):
         call(masked, g.EPI_MASK, M)
         assert torch.equal(masked, torch.where(M > 0, plain, 0.0))
     a.close()
+
+
+@pytest.mark.parametrize("rows,length,f,blocks,want", [
+    (1000, 17, 16, 0, "split(chunks=34,kernel=k_spmm_short<4>)"), (1000, 17, 41, 0, "split(chunks=34,kernel=k_spmm_short<16>)"),
+    (1000, 65, 16, 0, "split(chunks=127,kernel=k_spmm_few<4>)"), (1000, 65, 64, 0, "split(chunks=127,kernel=k_spmm_few<8>)"),
+    (1000, 65, 3, 0, "split(chunks=127,kernel=k_spmm_split<4,1>)"), (1000, 65, 21, 0, "split(chunks=127,kernel=k_spmm_split<32,1>)"),
+    (1000, 65, 41, 0, "split(chunks=127,kernel=k_spmm_ragged)"), (9000, 65, 41, 0, "split(chunks=1143,kernel=k_spmm_line<1>)"),
+    (9000, 65, 67, 0, "split(chunks=1143,kernel=k_spmm_line<2>)"), (9000, 65, 16, 0, "split(chunks=1143,kernel=k_spmm_split<4,4>)"),
+    (9000, 65, 32, 0, "split(chunks=1143,kernel=k_spmm_split<8,4>)"),
+    (9000, 65, 64, 2, "blocked(blocks=2,cols_per_block=1024,partial_rows=18000,chunks=1143,kernel=k_spmm_split<16,4>)")])
+def test_describe_names_the_kernel(rows, length, f, blocks, want):
+    """Which kernel a product goes through is part of its description (a stored measurement is tied to it); the product runs
+    and is right."""
+    g = G()
+    nc = 2000
+    rowptr = np.arange(rows + 1, dtype=np.int64) * length
+    step = nc // length                                             # entries on both sides of the middle column
+    colidx = np.tile(np.arange(length) * step, rows).astype(np.int32)
+    val = np.random.default_rng(118).standard_normal(colidx.size).astype(np.float32)
+    a = g.gcn_csr_create_from_csr_rect(rows, nc, dev(rowptr), dev(colidx), dev(val), 0)
+    g.gcn_csr_config(a, g.CFG_SPMM_BLOCKS, blocks)
+    assert g.gcn_spmm_describe(a, 0, f) == want
+    X = synth.normal_features(nc, f, 119)
+    Z = torch.full((rows, f), float("nan"), device="cuda")
+    g.gcn_spmm(a, 0, dev(X), Z)
+    assert_close(host(Z), val.reshape(rows, length).astype(np.float64) @ X[:step * length:step].astype(np.float64), want)
+    a.close()
