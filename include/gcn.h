@@ -116,6 +116,8 @@ int gcn_csr_create_from_csr(gcn_csr** out, int64_t n, const int64_t* rowptr, con
 int gcn_csr_create_from_csr_rect(gcn_csr** out, int64_t n_rows, int64_t n_cols, const int64_t* rowptr,
                                  const int32_t* colidx, const float* val, uint32_t flags, void* stream);
 
+/* Waits for the matrix's device.  What the matrix owned may be kept by the library for the next one; other allocators of
+ * the process get that memory only after gcn_scratch_release, which says how much it can be. */
 int gcn_csr_destroy(gcn_csr* a);
 
 /* Sizes; any output pointer may be NULL. */
@@ -311,7 +313,8 @@ int gcn_epoch_view(int64_t n, int32_t L_w, const int32_t* dims, int order, void*
 int gcn_config(int key, int value);
 int gcn_csr_config(gcn_csr* a, int key, int value);
 
-/* Frees the library-owned per-stream scratch (after waiting for the device); later calls allocate it again.  Also gives
+/* Frees the library-owned per-stream scratch (after waiting for the device); later calls allocate it again.  No call that
+ * uses this scratch may run on another thread meanwhile (constructions, products and epochs may).  Also gives
  * back what the library keeps of destroyed matrices and of graph construction to build the next matrix from: at most 1/64
  * of the device's memory, which an allocation of this library that would fail otherwise takes too. */
 int gcn_scratch_release(void);
@@ -334,8 +337,8 @@ int gcn_timing_read(int64_t* launches, double* total_ms);
 int gcn_timing_read_phases(int64_t* spans, double* total_ms);
 
 /* Building blocks of graph construction (section "Graph Neural Networks": the modified adjacency matrix
- * is assembled from an edge list; gcn_csr_create sorts 64-bit keys row<<32|col, drops equal neighbours and
- * takes prefix sums with exactly these routines).  Exported so that they can be checked on their own.  All
+ * is assembled from an edge list; gcn_csr_create packs each entry into one 64-bit key, row above
+ * column, sorts the keys, drops equal neighbours and takes prefix sums with exactly these routines).  Exported so that they can be checked on their own.  All
  * pointers are DEVICE pointers, inputs are left unchanged, outputs must not overlap inputs (gcn_exclusive_scan_i64
  * allows in == out); the calls allocate temporaries on the device and return after the stream has finished.
  *

@@ -148,8 +148,8 @@ def test_csr_create_at_powers_of_two_of_n(n, loops):
 
 
 def test_matrices_of_changing_size_reuse_memory_safely():
-    """Matrices come and go on two streams while products on others are still checked: blocks given back by one are taken
-    by the next."""
+    """Matrices of changing size come and go, on two streams in turn, and their products are checked: blocks given back by one
+    are taken by the next (two threads at the same time: see below)."""
     g = G()
     streams = [torch.cuda.Stream(), torch.cuda.Stream()]
     for k in range(6):
@@ -488,3 +488,85 @@ def test_describe_names_the_kernel(rows, length, f, blocks, want):
     g.gcn_spmm(a, 0, dev(X), Z)
     assert_close(host(Z), val.reshape(rows, length).astype(np.float64) @ X[:step * length:step].astype(np.float64), want)
     a.close()
+
+
+def test_two_threads_build_use_and_destroy_matrices_at_the_same_time():
+    """Two host threads, each with matrices and a stream of its own, whose constructions, products and destructions overlap (the
+    library's calls run outside the interpreter's lock): memory that one gives back is taken by the other while its
+    work is still running, and every array and result is the oracle's.  A third thread gives kept memory back to the
+    device now and then."""
+    import threading
+    g = G()
+    g.lib()
+    cases = []
+    for k, (n, edges) in enumerate([(3000, 30_000), (700, 60_000), (20_000, 90_000), (9000, 200_000)]):
+        rs = np.random.default_rng(120 + k)
+        src, dst = rs.integers(0, n, edges).astype(np.int32), (n * rs.random(edges) ** 2).astype(np.int32)
+        A = oracle.build_csr(n, src, dst)
+        X = synth.normal_features(n, 16, 130 + k)
+        cases.append((n, dev(src), dev(dst), A, dev(X), oracle.spmm(A, X)))
+    flags = g.SYMMETRISE | g.ADD_SELF_LOOPS | g.NORM_SYM | g.BUILD_TRANSPOSE
+    start, failed, done = threading.Barrier(2), [], threading.Event()
+    torch.cuda.synchronize()
+
+    def work(first):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                start.wait(60)
+                for turn in range(24):
+                    n, src, dst, A, X, want = cases[(first + turn) % len(cases)]
+                    a = g.gcn_csr_create(n, src, dst, flags)
+                    g.gcn_csr_config(a, g.CFG_SPMM_BLOCKS, [1, 3][turn % 2])       # with and without another stored order
+                    Z = torch.full((n, 16), float("nan"), device="cuda")
+                    g.gcn_spmm(a, turn % 2, X, Z)
+                    rowptr, colidx, val, deg = a.arrays(bool(turn % 2))
+                    a.close()
+                    torch.cuda.current_stream().synchronize()
+                    assert np.array_equal(host(rowptr), A.rowptr) and np.array_equal(host(colidx), A.colidx), turn
+                    assert np.array_equal(host(val).view(np.uint32), A.val.view(np.uint32)), turn
+                    assert_close(host(Z), want, f"turn {turn}")
+        except BaseException as e:
+            failed.append(e)
+            start.abort()
+
+    def release():
+        while not done.wait(0.02):
+            g.gcn_scratch_release()
+    threads = [threading.Thread(target=work, args=(i,)) for i in (0, 1)]
+    third = threading.Thread(target=release)
+    for t in threads + [third]:
+        t.start()
+    for t in threads:
+        t.join(100)
+    done.set()
+    third.join(20)
+    assert not failed, failed
+    assert not any(t.is_alive() for t in threads + [third])
+
+
+@pytest.mark.parametrize("f", [4, 7, 8, 13, 16, 21, 32, 33, 41, 64, 66, 130])
+def test_spmm_short_rows_add_alike_in_every_kernel(f):
+    """The kernel for few and short rows keeps the order of additions of the others: the same rows give the same bits on their
+    own, with one longer row behind them, and in a matrix of many chunks."""
+    g = G()
+    lengths = np.random.default_rng(140).integers(0, 65, 1000)
+    rowptr, colidx, val = _rows_matrix(lengths, 3000, 141)
+    longer = _rows_matrix([65], 3000, 142)
+    X = dev(synth.normal_features(3000, f, 143))
+    results, kernels = [], []
+    for kind in ("alone", "longer", "repeated"):
+        if kind == "alone":
+            m = (rowptr, colidx, val)
+        elif kind == "longer":
+            m = (np.append(rowptr, rowptr[-1] + 65), np.concatenate([colidx, longer[1]]), np.concatenate([val, longer[2]]))
+        else:
+            m = (np.concatenate([[0]] + [rowptr[1:] + k * rowptr[-1] for k in range(80)]), np.tile(colidx, 80), np.tile(val, 80))
+        a = g.gcn_csr_create_from_csr_rect(m[0].size - 1, 3000, dev(m[0]), dev(m[1]), dev(m[2]), 0)
+        g.gcn_csr_config(a, g.CFG_SPMM_BLOCKS, 1)
+        kernels.append(g.gcn_spmm_describe(a, 0, f).split("kernel=")[1].split("<")[0].rstrip(")"))
+        Z = torch.full((m[0].size - 1, f), float("nan"), device="cuda")
+        g.gcn_spmm(a, 0, X, Z)
+        results.append(Z[:1000].clone())
+        a.close()
+    assert kernels[0] == "k_spmm_short" and "k_spmm_short" not in kernels[1:]
+    assert torch.equal(results[0], results[1]) and torch.equal(results[0], results[2]), kernels
