@@ -1412,8 +1412,8 @@ static int launch_sweep(const SweepArgs& args, int64_t ntasks, int sweep_waves, 
 
 // The kernel and lane layout of one nonzero-split product.
 struct SplitChoice {
-    enum Kernel { SPLIT, FEW, RAGGED, LINE } kernel;
-    int lpr, vec;                                 // lanes per row of X (RAGGED: from the width), floats per lane
+    enum Kernel { SPLIT, FEW, RAGGED, LINE } kernel = SPLIT;
+    int lpr = 0, vec = 0;                         // lanes per row of X (RAGGED: from the width), floats per lane
 };
 
 static SplitChoice choose_split(int32_t f, int64_t nchunks, bool any_order, bool l2_resident) {
@@ -1551,8 +1551,8 @@ static int run_matrix(gcn_csr* a, Matrix& mm, const int32_t* row_map, int64_t nn
         if (f >= 4) return launch_block_reduce<4>(mm.nrows, f, b, row_map, o.row_scale, o.accumulate ? 1 : 0, a->partial, Z, ldz, epilogue, Zprev, ldzprev, s);
         return launch_block_reduce<1>(mm.nrows, f, b, row_map, o.row_scale, o.accumulate ? 1 : 0, a->partial, Z, ldz, epilogue, Zprev, ldzprev, s);
     }
-    const SplitChoice choice = choose_split(f, mm.nchunks, o.any_order, false);
     const bool short_kernel = !row_map && short_rows(mm, f);
+    const SplitChoice choice = short_kernel ? SplitChoice() : choose_split(f, mm.nchunks, o.any_order, false);
     if (o.describe) {
         char t[120];
         snprintf(t, sizeof t, "split(chunks=%lld,kernel=%s)", (long long)mm.nchunks,
