@@ -33,34 +33,61 @@ HBM_PEAK_GBPS = 8000.0
 # reads for a plain device copy of known size: FETCH_SIZE x 2.0, WRITE_SIZE x 1.0) and summed over the
 # kernels of a product; from the profiles/spmm_*.txt summaries.  They are fills of the eight L2s: reads that
 # the memory-side Infinity Cache served are included, so this is an upper bound of the HBM bytes.  Each entry
-# names the schedule it was measured on (what gcn_spmm_describe returned in that run): a line whose library
-# reports another schedule carries traffic = null instead of a stale figure.
+# names the schedule and kernel it was measured on (what gcn_spmm_describe returned in that run) and the code of the
+# sparse product at that time (sparse_code_digest): a line whose library reports another schedule, or whose tree holds
+# other code, carries traffic = null instead of a stale figure.
 MEASURED_TRAFFIC = {
     ("rmat20_spmm_f128", 128): {
-        "bytes": 10045335483,
+        "bytes": 9912864465,
         "kernels": "k_spmm_split<8,4> over 4 panels of 32 columns + k_spmm_fixup",
         "schedule": "split(chunks=63376,kernel=k_spmm_split<8,4>)",
         "profile": "profiles/spmm_split_rmat20_f128.txt"},
     ("chunglu_reddit_gcn_602_16_16_41", 16): {
-        "bytes": 1033356854,
+        "bytes": 1000021404,
         "kernels": "k_scale_rows + k_spmm_split<4,4> over the column-blocked copy + k_spmm_fixup + k_block_reduce",
         "schedule": "blocked(blocks=8,cols_per_block=29696,partial_rows=1863720,chunks=224269,kernel=k_spmm_split<4,4>)"
                     "; value-free (operand rows pre-scaled by d^-1/2, output rows scaled)",
         "profile": "profiles/spmm_blocked_chunglu_reddit_f16.txt"},
     ("rmat_amazon_gcn_300_16_16_24", 16): {
-        "bytes": 20042035304,
+        "bytes": 19360562564,
         "kernels": "k_pack_rows + k_spmm_split_pair<4,4> (paired launch of the hub schedule) + 2 x k_spmm_fixup + k_block_reduce",
         "schedule": "hub(hot_cols=524288,cols_per_block=32768,long_row>=64,nnz_hot=148858651,nnz_rest=96949372,partial_rows=7701691,"
                     "kernel=k_spmm_split_pair<4,4>)",
         "profile": "profiles/spmm_hub_rmat_amazon_f16.txt"},
     ("chunglu_protein_gcn_128_16_16_256", 16): {
-        "bytes": 82950924194,
+        "bytes": 81680497980,
         "kernels": "k_scale_rows + 15 x k_spmm_sweep<4> + k_spmm_split<4,4> (column-blocked, long rows) + k_spmm_fixup + k_block_reduce",
         "schedule": "sweep(entries_per_step=16,rows_per_task=256,long_row>1024,tasks=34163,launches=15,stored=936862448,kernel=k_spmm_sweep<4>)"
                     "+long_rows:blocked(blocks=101,cols_per_block=87040,partial_rows=12649811,chunks=745738,kernel=k_spmm_split<4,4>)"
                     "; value-free (operand rows pre-scaled by d^-1/2, output rows scaled)",
         "profile": "profiles/spmm_sweep_chunglu_protein_f16_default_command.txt"},
 }
+
+MEASURED_ON_CODE = "70951398a93870f0"
+
+
+def sparse_code_digest() -> str:
+    """Identifies the code of the sparse product and of its stored orders: the sources without comments and spacing."""
+    import hashlib
+    import re
+    h = hashlib.sha256()
+    for name in ("spmm.hip", "schedules.hip"):
+        with open(os.path.join(ROOT, "paper_2005_03300_amd", "csrc", name)) as fh:
+            h.update(re.sub(r"\s+", "", re.sub(r"/\*.*?\*/|//[^\n]*", "", fh.read(), flags=re.S)).encode())
+    return h.hexdigest()[:16]
+
+
+def stored_traffic(workload: str, f: int, schedule: str, code: str):
+    """The stored byte figure for this workload, or None and the reason why it does not apply (None: there is none)."""
+    meas = MEASURED_TRAFFIC.get((workload, f))
+    if meas is None:
+        return None, None
+    if meas["schedule"] != schedule:
+        return None, f"the stored counter figure was measured on schedule {meas['schedule']!r}, this run took {schedule!r}"
+    if code != MEASURED_ON_CODE:
+        return None, f"the stored counter figure was measured on code {MEASURED_ON_CODE}, this tree holds {code}"
+    return meas, None
+
 
 # kernels inside the library's event bracket of one product, by the schedule the library reports
 SCHEDULE_KERNELS = {1: "k_spmm_rowwise", 2: "the nonzero-split kernel that extra.schedule names + k_spmm_fixup",
@@ -317,15 +344,14 @@ def main() -> int:
                      spmm_products_timed=2 * args.steps, event_brackets=products,
                      main_kernel_ms_per_product=round(main_ms / max(products, 1), 4),
                      main_kernel_brackets=main_launches)
-        meas = MEASURED_TRAFFIC.get((w.name, f)) if not (args.slice > 1 or args.directed or args.no_permute or args.algo) else None
         traffic = None
-        if meas is not None:
-            if meas["schedule"] is None or meas["schedule"] == schedule_text:
+        if not (args.slice > 1 or args.directed or args.no_permute or args.algo):
+            meas, why_not = stored_traffic(w.name, f, schedule_text, sparse_code_digest())
+            if meas is not None:
                 traffic = meas["bytes"]
                 extra["traffic_measured_on"] = {k: meas[k] for k in ("kernels", "profile")}
-            else:
-                extra["traffic_withheld"] = (f"the stored counter figure was measured on schedule {meas['schedule']!r}, "
-                                             f"this run took {schedule_text!r}")
+            elif why_not:
+                extra["traffic_withheld"] = why_not
         value_free = "value-free" in schedule_text
         if value_free:
             # the library took the form that skips the stored values (4 B per entry instead of 8, one pre-scaling pass
