@@ -5,7 +5,8 @@
 
 Default workload: the stand-alone SpMM on the config 5 graph (the largest one: Protein-shaped Chung-Lu,
 8.7 M vertices, 1.32 G stored entries) at the hidden width f = 16.  One step is the pair Z = A X and
-Z = A^T X (the transposed product runs on its own stored arrays).  `value` is algorithmic GB/s:
+Z = A^T X (the graph is symmetric and stored once, so both products read the same arrays; with --directed the transposed
+product has its own).  `value` is algorithmic GB/s:
 (8 nnz + 8 (n+1) + 4 n f read + 4 n f written) per product over wall time, inputs resident in HBM before
 the timed region.  `--config 2` is the same on the R-MAT scale-20 graph at f = 128; `--config N --epoch`
 times one full-batch epoch (forward + loss + backward, lr = 0) of config N instead and reports milliseconds.
