@@ -72,13 +72,18 @@ struct Blocked {
 
 struct Matrix;
 
+// The sweep kernel: tasks (wavefronts) of a workgroup, which takes a compute unit, and the steps that a lane group works through in
+// one trip.  The entries of a trip lie group by group, so that neighbouring lanes fetch a group's entries.
+constexpr int SWEEP_TASKS = 5;
+constexpr int SWEEP_STEPS = 8;
+
 // Sweep copy of a matrix for operands far larger than the caches.  Rows are cut into tasks of
 // `rb` consecutive rows; a wavefront owns a task, accumulates its rows in LDS and walks the task's
 // entries in ascending column order, so all wavefronts of a launch (started together, equal length)
 // gather from one narrow band of X at a time and that band stays in L2.  The entries of a task are
-// stored in steps of `groups` entries whose rows all differ (packed that way when the copy is built,
-// an entry whose row is already in the step moving to one of the next steps), so the lane groups of
-// one step add to LDS without any conflict; padding entries have column -1.  Rows longer than
+// stored in steps of `groups` entries, those of two steps all of different rows (packed that way when the copy is
+// built, an entry whose row is already there moving to one of the next pairs), so the lane groups of
+// two steps add to LDS without any conflict.  Padding entries name the row behind the task's last.  Rows longer than
 // `heavy_threshold` are kept apart and go through the nonzero-split kernel.
 struct Sweep {
     int32_t groups = 0;
@@ -86,11 +91,11 @@ struct Sweep {
     int32_t heavy_threshold = 0;
     int64_t ntasks = 0, nnz_light = 0, nnz_heavy = 0, n_heavy = 0;
     int64_t padded = 0;           // entries stored, padding included
-    int32_t* colidx = nullptr;    // [padded] column, or -1 for a padding entry
+    int32_t* colidx = nullptr;    // [padded] column
     float* val = nullptr;         // [padded]
-    uint8_t* lrow = nullptr;      // [padded] row inside the task
-    int64_t* task_base = nullptr; // [ntasks] first stored entry of the task (multiple of 16)
-    int32_t* task_len = nullptr;  // [ntasks] stored entries of the task (multiple of groups)
+    uint16_t* lrow = nullptr;     // [padded] row inside the task, rb for a padding entry
+    int64_t* task_base = nullptr; // [ntasks] first stored entry of the task (a multiple of SWEEP_STEPS * groups)
+    int32_t* task_len = nullptr;  // [ntasks] stored entries of the task (as above)
     int32_t* task_order = nullptr;// [ntasks] task ids, longest first
     Matrix* heavy = nullptr;      // the heavy rows as a row-subset matrix (ne_rows = their ids)
 };

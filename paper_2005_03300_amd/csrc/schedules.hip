@@ -151,73 +151,107 @@ int build_blocked(Matrix& m, int64_t nnz, int64_t cpb, hipStream_t s) {
 
 struct SweepPayload { int32_t col; float val; int32_t row; };
 
-// One thread per task walks the task's entries in ascending column order and packs them into steps
-// of `groups` entries whose rows are all different (the lane groups of a step then add to different
-// rows in LDS).  An entry whose row is already in the step waits in a short list and opens one of the
-// next steps, so the stored order stays within a few steps of the column order.  With out == NULL
-// only the number of steps is counted (task_len, sort_key, padded_len); otherwise the entries are
-// written to task_base[t] + step*groups + slot.
-__global__ void k_sweep_pack(int64_t ntasks, int32_t rb, int32_t groups, const int64_t* __restrict__ task_ptr,
-                             const SweepPayload* __restrict__ payload, const int64_t* __restrict__ task_base,
-                             int32_t* __restrict__ colidx, float* __restrict__ val, uint8_t* __restrict__ lrow,
-                             int32_t* __restrict__ task_len, uint32_t* __restrict__ sort_key,
-                             int64_t* __restrict__ padded_len) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= ntasks) return;
-    constexpr int D = 24;                       // entries that may wait at one time
-    const int64_t lo = task_ptr[t], hi = task_ptr[t + 1];
+// One wavefront per task packs the task's entries, which come in ascending column order, into sets of `set` entries whose
+// rows are all different (what the sweep kernel adds to LDS without a look at the rows).  The wavefront keeps a window of
+// the next 64 entries, one per lane; of every row in it the first entry is a candidate, and the first `set` candidates
+// make the next set, so the stored order stays within a window of the column order.  Places of a set that no entry takes hold
+// padding: the column of the set's first entry and the row behind the task's last.  The sets of a trip are stored
+// slot by slot (see Sweep).  With colidx == NULL only the length is counted.
+__global__ __launch_bounds__(64) void k_sweep_pack(int32_t rb, int32_t groups, int32_t set, const int64_t* __restrict__ task_ptr,
+                                                   const SweepPayload* __restrict__ payload, const int64_t* __restrict__ task_base,
+                                                   int32_t* __restrict__ colidx, float* __restrict__ val, uint16_t* __restrict__ lrow,
+                                                   int32_t* __restrict__ task_len, uint32_t* __restrict__ sort_key,
+                                                   int64_t* __restrict__ padded_len) {
+    extern __shared__ int32_t first[];           // [rb] the lane that holds a row's first entry of the window
+    const int64_t t = blockIdx.x;
+    const int lane = threadIdx.x;
+    const int64_t lo = task_ptr[t], hi = task_ptr[t + 1], row0 = t * rb;
+    for (int i = lane; i < rb; i += 64) first[i] = 64;
+    auto settle = [] {                           // LDS operations of one wavefront complete in order
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+    struct Entry { int32_t col; int32_t val; int32_t row; };
+    auto fetch = [&](int64_t k) {
+        Entry e = {0, 0, 0};
+        if (k < hi) {
+            const SweepPayload p = payload[k];
+            e = {p.col, __float_as_int(p.val), (int32_t)(p.row - row0)};
+        }
+        return e;
+    };
+    auto pick = [](int32_t a, int32_t b, int from) {            // lane `from` of the 128 that a and b make
+        const int32_t x = __shfl(a, from & 63, 64), y = __shfl(b, from & 63, 64);
+        return from < 64 ? x : y;
+    };
+    Entry w = fetch(lo + lane), b0 = fetch(lo + 64 + lane), b1 = fetch(lo + 128 + lane);
+    int used = 0;                                // of b0's entries
+    int64_t ahead = lo + 192;                    // first entry not fetched yet
+    int64_t left = hi - lo;                      // entries not placed yet
     const int64_t base = task_base ? task_base[t] : 0;
-    int64_t wait[D];
-    int nw = 0;
-    int64_t i = lo, step = 0;
-    while (i < hi || nw > 0) {
-        uint64_t m0 = 0, m1 = 0, m2 = 0, m3 = 0;                    // rows (0..255) present in this step
-        int cnt = 0;
-        auto taken = [&](int r) {
-            const uint64_t bit = 1ull << (r & 63);
-            const int q = r >> 6;
-            return ((q == 0 ? m0 : q == 1 ? m1 : q == 2 ? m2 : m3) & bit) != 0;
-        };
-        auto take = [&](int r) {
-            const uint64_t bit = 1ull << (r & 63);
-            const int q = r >> 6;
-            if (q == 0) m0 |= bit; else if (q == 1) m1 |= bit; else if (q == 2) m2 |= bit; else m3 |= bit;
-        };
-        auto emit = [&](int64_t pos, int r) {
-            if (colidx) {
-                const SweepPayload pl = payload[pos];
-                const int64_t dst = base + step * groups + cnt;
-                colidx[dst] = pl.col;
-                val[dst] = pl.val;
-                lrow[dst] = (uint8_t)r;
+    const int trip = SWEEP_STEPS * groups, per_trip = trip / set;
+    settle();
+    int64_t done = 0;                            // sets
+    while (left > 0) {
+        const bool valid = lane < left;
+        if (valid) atomicMin(&first[w.row], lane);
+        settle();
+        const bool leads = valid && first[w.row] == lane;
+        settle();
+        if (leads) first[w.row] = 64;
+        settle();
+        const unsigned long long below = (1ull << lane) - 1ull;
+        const unsigned long long leaders = __ballot(leads);
+        const int slot = __popcll(leaders & below);
+        const bool taken = leads && slot < set;
+        const unsigned long long gone = __ballot(taken);
+        const int n = __popcll(gone);            // at least one
+        if (colidx) {
+            const int32_t c0 = __builtin_amdgcn_readfirstlane(w.col);      // (the first of the window always goes)
+            auto at = [&](int q) {               // place q of the set: step q / groups, slot q % groups
+                const int step = (int)(done % per_trip) * (set / groups) + q / groups;
+                return base + done / per_trip * trip + (q % groups) * SWEEP_STEPS + step;
+            };
+            if (taken) {
+                const int64_t d = at(slot);
+                colidx[d] = w.col; val[d] = __int_as_float(w.val); lrow[d] = (uint16_t)w.row;
             }
-            ++cnt;
-        };
-        int keep = 0;
-        for (int d = 0; d < nw; ++d) {                              // waiting entries first, oldest first
-            const int64_t pos = wait[d];
-            const int r = payload[pos].row % rb;
-            if (cnt < groups && !taken(r)) { take(r); emit(pos, r); }
-            else wait[keep++] = pos;
-        }
-        nw = keep;
-        while (cnt < groups && i < hi) {
-            const int r = payload[i].row % rb;
-            if (taken(r)) {
-                if (nw == D) break;                                 // close the step short rather than reorder further
-                wait[nw++] = i++;
-            } else {
-                take(r);
-                emit(i++, r);
+            if (lane >= n && lane < set) {
+                const int64_t d = at(lane);
+                colidx[d] = c0; val[d] = 0.f; lrow[d] = (uint16_t)rb;
             }
         }
-        ++step;                                                     // every step places at least one entry
+        // the entries that stay move up in order, the next ones follow
+        const int stay = 64 - n;
+        const int to = taken ? 64 - n + __popcll(gone & below) : lane - __popcll(gone & below);   // a permutation
+        w.col = __builtin_amdgcn_ds_permute(to * 4, w.col);
+        w.val = __builtin_amdgcn_ds_permute(to * 4, w.val);
+        w.row = __builtin_amdgcn_ds_permute(to * 4, w.row);
+        const int from = used + (lane >= stay ? lane - stay : 0);
+        const Entry e = {pick(b0.col, b1.col, from), pick(b0.val, b1.val, from), pick(b0.row, b1.row, from)};
+        if (lane >= stay) w = e;
+        used += n;
+        if (used >= 64) {
+            used -= 64;
+            b0 = b1;
+            b1 = fetch(ahead + lane);
+            ahead += 64;
+        }
+        left -= n;
+        ++done;
     }
-    if (!colidx) {
-        const int64_t len = step * groups;
-        task_len[t] = (int32_t)len;
-        sort_key[t] = (uint32_t)len;
-        padded_len[t] = (len + 15) & ~15ll;
+    const int64_t trips = (done + per_trip - 1) / per_trip;
+    if (colidx) {                                // padding up to a whole trip
+        for (int64_t d = done; d < trips * per_trip; ++d)
+            if (lane < set) {
+                const int step = (int)(d % per_trip) * (set / groups) + lane / groups;
+                const int64_t q = base + d / per_trip * trip + (lane % groups) * SWEEP_STEPS + step;
+                colidx[q] = 0; val[q] = 0.f; lrow[q] = (uint16_t)rb;
+            }
+    } else if (lane == 0) {
+        task_len[t] = (int32_t)(trips * trip);
+        sort_key[t] = (uint32_t)(trips * trip);
+        padded_len[t] = trips * trip;
     }
 }
 
@@ -283,10 +317,13 @@ __global__ void k_heavy_len(int64_t nh, const int32_t* __restrict__ rows, const 
     if (q == nh) len[q] = 0;
 }
 
-int build_sweep(Matrix& m, int64_t nnz, int32_t groups, int32_t rb, int32_t heavy_th, hipStream_t s) {
+int build_sweep(Matrix& m, int64_t nnz, int32_t groups, int32_t rb, int32_t asked_th, hipStream_t s) {
     free_sweep(m.swp);
     Sweep& w = m.swp;
-    if (nnz <= 0 || rb <= 0 || rb > 256 || (groups != 8 && groups != 16))
+    const int32_t set = 2 * groups;
+    // a row takes one set per entry at the least: with this bound task_len stays below 2^31 whatever the setting
+    const int32_t heavy_th = asked_th < 1 << 20 ? asked_th : 1 << 20;
+    if (nnz <= 0 || rb <= 0 || rb > 4096 || (groups != 8 && groups != 16))
         return fail(GCN_ERR_BADARG, "build_sweep: bad parameters");
     const int64_t n = m.nrows;
     const int64_t ntasks = (n + rb - 1) / rb;
@@ -324,9 +361,9 @@ int build_sweep(Matrix& m, int64_t nnz, int32_t groups, int32_t rb, int32_t heav
     GCN_TRY(len.alloc((size_t)ntasks * 4));
     GCN_TRY(len_sorted.alloc((size_t)ntasks * 4));
     GCN_TRY(plen.alloc((size_t)ntasks * 8));
-    hipLaunchKernelGGL(k_sweep_pack, dim3(blocks_for(ntasks, 64)), dim3(64), 0, s, ntasks, rb, groups, seg.as<int64_t>(),
+    hipLaunchKernelGGL(k_sweep_pack, dim3((unsigned)ntasks), dim3(64), (size_t)rb * 4, s, rb, groups, set, seg.as<int64_t>(),
                        p1.as<SweepPayload>(), (const int64_t*)nullptr, (int32_t*)nullptr, (float*)nullptr,
-                       (uint8_t*)nullptr, w.task_len, len.as<uint32_t>(), plen.as<int64_t>());
+                       (uint16_t*)nullptr, w.task_len, len.as<uint32_t>(), plen.as<int64_t>());
     GCN_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_iota_i32, dim3(blocks_for(ntasks)), dim3(TPB), 0, s, ntasks, ids.as<int32_t>());
     GCN_LAUNCH_CHECK();
@@ -345,14 +382,9 @@ int build_sweep(Matrix& m, int64_t nnz, int32_t groups, int32_t rb, int32_t heav
     GCN_TRY(device_alloc_t(&w.colidx, (size_t)padded));
     GCN_TRY(device_alloc_t(&w.val, (size_t)padded));
     GCN_TRY(device_alloc_t(&w.lrow, (size_t)padded));
-    if (padded > 0) {
-        GCN_HIP_TRY(hipMemsetAsync(w.colidx, 0xff, (size_t)padded * 4, s));  // column -1: padding until written
-        GCN_HIP_TRY(hipMemsetAsync(w.val, 0, (size_t)padded * 4, s));
-        GCN_HIP_TRY(hipMemsetAsync(w.lrow, 0, (size_t)padded, s));
-    }
     if (nnz_light > 0) {
         // pass 2: the same walk, now writing the entries
-        hipLaunchKernelGGL(k_sweep_pack, dim3(blocks_for(ntasks, 64)), dim3(64), 0, s, ntasks, rb, groups, seg.as<int64_t>(),
+        hipLaunchKernelGGL(k_sweep_pack, dim3((unsigned)ntasks), dim3(64), (size_t)rb * 4, s, rb, groups, set, seg.as<int64_t>(),
                            p1.as<SweepPayload>(), w.task_base, w.colidx, w.val, w.lrow, (int32_t*)nullptr,
                            (uint32_t*)nullptr, (int64_t*)nullptr);
         GCN_LAUNCH_CHECK();
@@ -403,7 +435,7 @@ int build_sweep(Matrix& m, int64_t nnz, int32_t groups, int32_t rb, int32_t heav
     GCN_HIP_TRY(hipStreamSynchronize(s));
     w.groups = groups;
     w.rb = rb;
-    w.heavy_threshold = heavy_th;
+    w.heavy_threshold = asked_th;
     w.ntasks = ntasks;
     w.nnz_light = nnz_light;
     w.nnz_heavy = nnz_heavy;

@@ -54,6 +54,7 @@ struct SplitArgs {
 
 // The index/value stream is read exactly once per product: load it with the non-temporal hint so
 // it does not push the gathered rows of X out of L2.
+typedef int intx2 __attribute__((ext_vector_type(2)));
 typedef int intx4 __attribute__((ext_vector_type(4)));
 typedef float fltx4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ int4 stream_load_i4(const int32_t* p) {
@@ -1260,20 +1261,32 @@ static int launch_block_reduce(int64_t n, int32_t f, const Blocked& b, const int
 }
 
 // ---- column sweep ---------------------------------------------------------------------------------------
-// One wavefront owns a task: `rb` consecutive rows whose results live in LDS (rb x W floats, W = 16
+// One wavefront owns a task: `rb` consecutive rows whose results live in LDS ((rb + 1) x W floats, W = 16
 // or 32) for the whole launch.  Its entries come in ascending column order, so it walks X left to
 // right; all wavefronts of a launch start together and have about the same length, so at any moment
 // the whole GPU gathers from a narrow band of X, which therefore stays in L2 even when X is far
-// larger than every cache.  The stored order puts G entries of different rows into every step (see
-// Sweep), so the G lane groups of one step always hold different rows: each multiplies its gathered row by the
+// larger than every cache.  The stored order puts 2 G entries of different rows into every two steps (see
+// Sweep), so the G lane groups of two steps always hold different rows: each multiplies its gathered row by the
 // value and adds it to the task's row in LDS with a plain read-modify-write.  Only this wavefront
 // touches these accumulators and its LDS operations complete in program order, so the sum order is
 // fixed and the result reproducible.
+//
+// Every launch reads X once per XCD at the least, so few launches (all of the LDS holds accumulators) and wavefronts that stay
+// together decide, not the speed of the walk: an L2 turns over in about 5 us, and a task that falls behind the others by more
+// than that finds none of their lines.  Hence a workgroup takes a whole compute unit, its wavefronts starting together;
+// and a wavefront waits for all it has asked for before it asks for more, which keeps the fast ones from running ahead,
+// and adds the trip before while it waits.  Indices are handed round in registers.
+// 0.47 G entries over 4.4 M rows of 64 bytes, sweep of one product (and its misses): a wavefront of 256 rows per workgroup, nine per
+// compute unit, indices handed round through the LDS: 4.2 ms (176 M); in registers 4.9 (247 M); two trips asked
+// for at once 5.5.  Workgroups of 5 x 511 rows, two trips at once: 3.4 to 4.3 (200 to 229 M), depending on where the compiler
+// put its waits; this kernel 3.4 (132 M: 138 G entries/s, 39 G misses/s, both ceilings together), and the same with four,
+// six or seven tasks in the same LDS.  With eight 4.3.  Product: 5.56 -> 4.75 ms; 1.32 G entries, 8.7 M rows 12.1 -> 10.2; 0.12
+// G, 1.2 M rows 1.30 -> 0.91, at 32 columns 1.65 -> 1.22.
 struct SweepArgs {
     const int32_t* colidx;
     const float* val;            // NULL: value-free product
     const float* row_scale;      // NULL, or one factor per output row
-    const uint8_t* lrow;
+    const uint16_t* lrow;
     const int64_t* task_base;
     const int32_t* task_len;
     const int32_t* task_order;
@@ -1284,84 +1297,111 @@ struct SweepArgs {
     const float* Zprev; int64_t ldzprev;
 };
 
-template <int LPR, int EPI>
-__global__ __launch_bounds__(64) void k_spmm_sweep(SweepArgs a, int64_t first_task) {
-    constexpr int G = 64 / LPR;                  // entries per step (16 or 8), all of different rows
+// Entry `q` of the eight that a lane group works through in a trip, of which each of its first four lanes holds two (q a constant
+// once the loop around is unrolled).
+__device__ __forceinline__ int trip_entry(const int (&x)[2], int q) {
+    const int v = x[q & 1];
+    switch (q >> 1) {
+        case 0: return __builtin_amdgcn_mov_dpp(v, 0x00, 0xf, 0xf, true);
+        case 1: return __builtin_amdgcn_mov_dpp(v, 0x55, 0xf, 0xf, true);
+        case 2: return __builtin_amdgcn_mov_dpp(v, 0xaa, 0xf, 0xf, true);
+        default: return __builtin_amdgcn_mov_dpp(v, 0xff, 0xf, 0xf, true);
+    }
+}
+
+template <int LPR, int EPI, bool VALUES>
+__global__ __launch_bounds__(64 * SWEEP_TASKS) void k_spmm_sweep(SweepArgs a, int64_t first_task, int32_t count) {
+    constexpr int G = 64 / LPR;                  // entries per step (16 or 8)
     constexpr int W = LPR * 4;                   // panel width in floats
-    constexpr int SPT = 64 / G;                  // steps per 64 entries
-    constexpr int U = 2;                         // 64-entry loads per trip
-    constexpr int STEPS = SPT * U;
-    extern __shared__ float acc[];               // [rb][W]
-    const int lane = threadIdx.x;
+    constexpr int STEPS = SWEEP_STEPS, TRIP = STEPS * G;
+    static_assert(STEPS == 8, "four lanes hold two entries each");
+    extern __shared__ float s_acc[];             // per wavefront [rb + 1][W]: the last row takes what padding entries add
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int32_t idx = (int32_t)(blockIdx.x * (blockDim.x >> 6)) + wave;
+    if (idx >= count) return;                    // whole wavefront leaves; no block-wide barrier below
+    float* const acc = s_acc + wave * ((a.rb + 1) * W);
     const int g = lane / LPR, li = lane % LPR;
     const int col0 = li * 4;
     const bool col_ok = col0 < a.f;
-    const int64_t task = a.task_order[first_task + blockIdx.x];
-    for (int i = lane * 4; i < a.rb * W; i += 256) *reinterpret_cast<float4*>(acc + i) = make_float4(0.f, 0.f, 0.f, 0.f);
+    const int64_t task = a.task_order[first_task + idx];
+    for (int i = lane * 4; i < (a.rb + 1) * W; i += 256) *reinterpret_cast<float4*>(acc + i) = make_float4(0.f, 0.f, 0.f, 0.f);
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     __builtin_amdgcn_wave_barrier();
 
-    const int64_t e0 = a.task_base[task];        // multiple of 16
-    const int len = a.task_len[task];            // multiple of G; padding entries have column -1
-    const float* xbase = a.X + col0;
-    // the entries of the next trip are fetched while the current one is gathered and added
-    int32_t c[U]; float v[U]; int r[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const int k = 64 * u + lane;
-        c[u] = -1; v[u] = 0.f; r[u] = 0;
-        if (k < len) {
-            c[u] = __builtin_nontemporal_load(a.colidx + e0 + k);
-            v[u] = a.val ? __builtin_nontemporal_load(a.val + e0 + k) : 1.f;
-            r[u] = (int)__builtin_nontemporal_load(a.lrow + e0 + k);
+    const int trips = a.task_len[task] / TRIP;
+    const int64_t mine = a.task_base[task] + g * STEPS + (lane & 3) * 2;       // this lane's two entries of the first trip
+    const float* const xbase = a.X + (col_ok ? col0 : 0);
+    const uint32_t xpitch = (uint32_t)a.ldx * 4u;
+    struct Index { int c[2], v[2]; uint32_t r; };
+    struct Rows { float x[STEPS][4]; int off[STEPS], v[2]; };
+    auto load = [&](int t, Index& n) {           // (past the end: the last trip again, not used)
+        const int64_t k = mine + (int64_t)(t < trips ? t : trips - 1) * TRIP;
+        const intx2 c = __builtin_nontemporal_load(reinterpret_cast<const intx2*>(a.colidx + k));
+        n.c[0] = c.x; n.c[1] = c.y;
+        n.r = __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(a.lrow + k));
+        if constexpr (VALUES) {
+            const intx2 v = __builtin_nontemporal_load(reinterpret_cast<const intx2*>(a.val + k));
+            n.v[0] = v.x; n.v[1] = v.y;
         }
-    }
-    for (int base = 0; base < len; base += 64 * U) {
-        int32_t nc[U]; float nv[U]; int nr[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int k = base + 64 * U + 64 * u + lane;
-            nc[u] = -1; nv[u] = 0.f; nr[u] = 0;
-            if (k < len) {
-                nc[u] = __builtin_nontemporal_load(a.colidx + e0 + k);
-                nv[u] = a.val ? __builtin_nontemporal_load(a.val + e0 + k) : 1.f;
-                nr[u] = (int)__builtin_nontemporal_load(a.lrow + e0 + k);
-            }
-        }
-        float x[STEPS][4];
-        float vs[STEPS];
-        int rs[STEPS];                           // row inside the task, or -1 for a padding entry
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int t = 0; t < SPT; ++t) {      // every gather of the trip is issued before any add
-                const int q = u * SPT + t;
-                const int src = t * G + g;
-                const int32_t cs = __shfl(c[u], src, 64);
-                vs[q] = __shfl(v[u], src, 64);
-                const int rr = __shfl(r[u], src, 64);
-                rs[q] = cs >= 0 ? rr : -1;
-                if (rs[q] >= 0 && col_ok) {
-                    const float4 w4 = *reinterpret_cast<const float4*>(at_row(xbase, (uint32_t)cs, (uint32_t)a.ldx * 4u));
-                    x[q][0] = w4.x; x[q][1] = w4.y; x[q][2] = w4.z; x[q][3] = w4.w;
-                } else {
-                    x[q][0] = x[q][1] = x[q][2] = x[q][3] = 0.f;
-                }
-            }
+    };
+    // Waits for everything on its way, then sends out the gathers of the trip in `n` and loads the indices of trip `next`.
+    auto gather = [&](Index& n, int next, Rows& m) {
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0x0f70);      // vmcnt(0)
+        __builtin_amdgcn_sched_barrier(0);
+        const float* at[STEPS];
+        const int off[2] = {(int)(n.r & 0xffffu) * W, (int)(n.r >> 16) * W};
 #pragma unroll
         for (int q = 0; q < STEPS; ++q) {
-            if (rs[q] >= 0 && col_ok) {          // the groups of a step hold different rows
-                float4* dst = reinterpret_cast<float4*>(acc + rs[q] * W + col0);
-                float4 cur = *dst;
-                cur.x = fmaf(vs[q], x[q][0], cur.x);
-                cur.y = fmaf(vs[q], x[q][1], cur.y);
-                cur.z = fmaf(vs[q], x[q][2], cur.z);
-                cur.w = fmaf(vs[q], x[q][3], cur.w);
-                *dst = cur;
+            at[q] = at_row(xbase, (uint32_t)trip_entry(n.c, q), xpitch);
+            m.off[q] = trip_entry(off, q) + col0;
+        }
+        if constexpr (VALUES) { m.v[0] = n.v[0]; m.v[1] = n.v[1]; }
+        __builtin_amdgcn_sched_barrier(0);
+        load(next, n);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < STEPS; ++q) {
+            const float4 w4 = *reinterpret_cast<const float4*>(at[q]);
+            m.x[q][0] = w4.x; m.x[q][1] = w4.y; m.x[q][2] = w4.z; m.x[q][3] = w4.w;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto add = [&](const Rows& m) {
+        constexpr int P = 2;                     // the entries of two steps hold different rows
+#pragma unroll
+        for (int q0 = 0; q0 < STEPS; q0 += P) {
+            float4 cur[P];
+#pragma unroll
+            for (int e = 0; e < P; ++e) cur[e] = *reinterpret_cast<const float4*>(acc + m.off[q0 + e]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int e = 0; e < P; ++e) {
+                const int q = q0 + e;
+                const float v = VALUES ? __int_as_float(trip_entry(m.v, q)) : 1.f;
+                cur[e].x = fmaf(v, m.x[q][0], cur[e].x);
+                cur[e].y = fmaf(v, m.x[q][1], cur[e].y);
+                cur[e].z = fmaf(v, m.x[q][2], cur[e].z);
+                cur[e].w = fmaf(v, m.x[q][3], cur[e].w);
+                *reinterpret_cast<float4*>(acc + m.off[q]) = cur[e];
             }
         }
-#pragma unroll
-        for (int u = 0; u < U; ++u) { c[u] = nc[u]; v[u] = nv[u]; r[u] = nr[u]; }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    if (trips > 0) {
+        Index n = {};
+        Rows xa, xb;
+        load(0, n);
+        gather(n, 1, xa);
+#pragma unroll 1
+        for (int t = 0;; t += 2) {
+            gather(n, t + 2, xb);                // trip t + 1
+            add(xa);
+            if (t + 1 >= trips) break;
+            gather(n, t + 3, xa);                // trip t + 2
+            add(xb);
+            if (t + 2 >= trips) break;
+        }
     }
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -1378,20 +1418,27 @@ __global__ __launch_bounds__(64) void k_spmm_sweep(SweepArgs a, int64_t first_ta
     }
 }
 
-template <int LPR>
-static int launch_sweep(const SweepArgs& args, int64_t ntasks, int sweep_waves, int epilogue, hipStream_t s) {
+// Rows of a task: what is left of a compute unit's LDS for each of SWEEP_TASKS, less the row of the padding entries.
+static int32_t sweep_rows(int panel) { return (160 << 10) / (SWEEP_TASKS * panel * 4) - 1; }
+// Tasks that a compute unit works on at once: GCN_CFG_SWEEP_WAVES, as many as there is room for.
+static int64_t sweep_tasks(const Config& cfg) { return cfg.sweep_waves < SWEEP_TASKS ? cfg.sweep_waves : SWEEP_TASKS; }
+
+template <int LPR, bool VALUES>
+static int launch_sweep(const SweepArgs& args, int64_t ntasks, int64_t per_cu, int epilogue, hipStream_t s) {
     constexpr int W = LPR * 4;
-    const size_t lds = (size_t)args.rb * W * sizeof(float);
     const unsigned ytiles = (unsigned)((args.f + W - 1) / W);
     // tasks that are resident at once; the launches get equal shares so that the last one is not a stub
-    const int64_t cap = (int64_t)device_info().cus * sweep_waves;
+    const int64_t cus = device_info().cus, cap = cus * per_cu;
     const int64_t nlaunch = (ntasks + cap - 1) / cap;
     const int64_t gen = (ntasks + nlaunch - 1) / nlaunch;
+    const int64_t waves = (gen + cus - 1) / cus;
+    const size_t lds = (size_t)waves * (args.rb + 1) * W * sizeof(float);
     timing_begin(s);
     for (unsigned y = 0; y < ytiles; ++y) {
         for (int64_t first = 0; first < ntasks; first += gen) {
-            const int64_t count = ntasks - first < gen ? ntasks - first : gen;
-            const dim3 grid((unsigned)count, 1);
+            const int32_t count = (int32_t)(ntasks - first < gen ? ntasks - first : gen);
+            const dim3 grid((unsigned)((count + waves - 1) / waves));
+            const int threads = (int)waves * 64;
             SweepArgs a = args;
             // one panel per launch: shift the column origin instead of using blockIdx.y
             a.X = args.X + (size_t)y * W;
@@ -1399,9 +1446,9 @@ static int launch_sweep(const SweepArgs& args, int64_t ntasks, int sweep_waves, 
             a.Zprev = args.Zprev ? args.Zprev + (size_t)y * W : nullptr;
             a.f = args.f - (int32_t)(y * W) < W ? args.f - (int32_t)(y * W) : W;
             switch (epilogue) {
-                case GCN_EPI_NONE: hipLaunchKernelGGL((k_spmm_sweep<LPR, GCN_EPI_NONE>), grid, dim3(64), lds, s, a, first); break;
-                case GCN_EPI_RELU: hipLaunchKernelGGL((k_spmm_sweep<LPR, GCN_EPI_RELU>), grid, dim3(64), lds, s, a, first); break;
-                default: hipLaunchKernelGGL((k_spmm_sweep<LPR, GCN_EPI_MASK>), grid, dim3(64), lds, s, a, first); break;
+                case GCN_EPI_NONE: launch_lds<k_spmm_sweep<LPR, GCN_EPI_NONE, VALUES>>(grid, threads, lds, s, a, first, count); break;
+                case GCN_EPI_RELU: launch_lds<k_spmm_sweep<LPR, GCN_EPI_RELU, VALUES>>(grid, threads, lds, s, a, first, count); break;
+                default: launch_lds<k_spmm_sweep<LPR, GCN_EPI_MASK, VALUES>>(grid, threads, lds, s, a, first, count); break;
             }
         }
     }
@@ -1826,11 +1873,11 @@ int spmm_launch(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx, f
         took(a, GCN_SCHED_SWEEP);
         const int LPRs = f <= 16 ? 4 : 8;
         const int W = LPRs * 4;
-        const int32_t rb = 4096 / W;                       // 16 KB of accumulators per wavefront
+        const int32_t rb = sweep_rows(W);
         GCN_TRY(want_sweep(m, nnz, 64 / LPRs, rb, cfg.sweep_heavy, s));
         const Sweep& w = m.swp;
         if (o.describe) {
-            const int64_t cap = (int64_t)device_info().cus * cfg.sweep_waves;
+            const int64_t cap = (int64_t)device_info().cus * sweep_tasks(cfg);
             char t[240];
             snprintf(t, sizeof t, "sweep(entries_per_step=%d,rows_per_task=%d,long_row>%d,tasks=%lld,launches=%lld,stored=%lld,kernel=k_spmm_sweep<%d>)",
                      64 / LPRs, (int)rb, (int)cfg.sweep_heavy, (long long)w.ntasks,
@@ -1841,8 +1888,9 @@ int spmm_launch(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx, f
             SweepArgs sa;
             sa.colidx = w.colidx; sa.val = o.pattern ? nullptr : w.val; sa.row_scale = o.row_scale; sa.lrow = w.lrow; sa.task_base = w.task_base; sa.task_len = w.task_len; sa.task_order = w.task_order;
             sa.n = n; sa.f = f; sa.rb = rb; sa.X = X; sa.ldx = ldx; sa.Z = Z; sa.ldz = ldz; sa.Zprev = Zprev; sa.ldzprev = ldzprev;
-            if (LPRs == 4) GCN_TRY(launch_sweep<4>(sa, w.ntasks, cfg.sweep_waves, epilogue, s));
-            else GCN_TRY(launch_sweep<8>(sa, w.ntasks, cfg.sweep_waves, epilogue, s));
+            const auto launch = LPRs == 4 ? (o.pattern ? launch_sweep<4, false> : launch_sweep<4, true>)
+                                          : (o.pattern ? launch_sweep<8, false> : launch_sweep<8, true>);
+            GCN_TRY(launch(sa, w.ntasks, sweep_tasks(cfg), epilogue, s));
         }
         if (w.heavy) {
             // long rows: nonzero-split kernel over the row subset; their rows are long enough for the

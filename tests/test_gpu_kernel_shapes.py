@@ -570,3 +570,40 @@ def test_spmm_short_rows_add_alike_in_every_kernel(f):
         a.close()
     assert kernels[0] == "k_spmm_short" and "k_spmm_short" not in kernels[1:]
     assert torch.equal(results[0], results[1]) and torch.equal(results[0], results[2]), kernels
+
+
+@pytest.mark.parametrize("f", [4, 16, 20, 32, 36])
+@pytest.mark.parametrize("shape", ["one_row", "task_of_rows", "two_tasks", "trips", "few_long", "gaps", "six_tasks"])
+def test_sweep_tasks_trips_and_padding(f, shape):
+    """The column sweep at the edges of its tasks (511 rows at up to 16 columns, 255 beyond), trips (128 and 64 entries) and pairs
+    of steps: rows that fill a window of 64 entries by themselves, tasks without entries, every epilogue, with and
+    without stored values.  What padding entries add must not reach a row of the result: row 0 of X holds an infinity."""
+    g = G()
+    rs = np.random.default_rng(120)
+    lengths = {"one_row": [700], "task_of_rows": [1] * 511, "two_tasks": [2] * 255 + [0, 3],
+               "trips": [1] * 64 + [63] + [1] * 2 + [0] * 444 + [128] + [0] * 511 + [129],
+               "few_long": [600, 0, 590, 1, 580] + [1] * 300, "gaps": [0] * 1100 + [5, 0, 40] + [0] * 600,
+               "six_tasks": list(rs.integers(0, 60, 511 * 5 + 9))}[shape]
+    n, nc = len(lengths), 900
+    rowptr, colidx, val = _rows_matrix(lengths, nc - 1, 121)
+    colidx += 1                                                     # column 0 is nobody's
+    a = g.gcn_csr_create_from_csr_rect(n, nc, dev(rowptr), dev(colidx), dev(val), 0)
+    g.gcn_csr_config(a, g.CFG_SPMM_ALGO, 3)
+    g.gcn_csr_config(a, g.CFG_SWEEP_HEAVY, 1 << 30)
+    rows = np.repeat(np.arange(n), lengths)
+    X, Zp = synth.normal_features(nc, f, 122), synth.normal_features(n, f, 123)
+    want, plain = np.zeros((n, f)), np.zeros((n, f))
+    np.add.at(want, rows, val[:, None].astype(np.float64) * X[colidx])
+    np.add.at(plain, rows, X[colidx].astype(np.float64))
+    X[0] = np.inf
+    Xd, Zpd = dev(X), dev(Zp)
+    assert g.gcn_spmm_describe(a, 0, f).startswith("sweep(")
+    for epi, of in ((g.EPI_NONE, lambda z: z), (g.EPI_RELU, lambda z: np.maximum(z, 0)), (g.EPI_MASK, lambda z: np.where(Zp > 0, z, 0))):
+        for waves in (9, 2):
+            g.gcn_csr_config(a, g.CFG_SWEEP_WAVES, waves)
+            Zd = torch.full((n, f), float("nan"), device="cuda")
+            g.gcn_spmm(a, 0, Xd, Zd, epi, Zpd)
+            assert_close(host(Zd), of(want), f"{shape} f={f} epilogue {epi}")
+            g.gcn_spmm_pattern(a, 0, Xd, Zd, None, epi, Zpd)
+            assert_close(host(Zd), of(plain), f"{shape} f={f} epilogue {epi}, value-free")
+    a.close()
