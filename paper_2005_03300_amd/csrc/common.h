@@ -10,6 +10,7 @@
 
 #include "gcn.h"
 #include "largest_asked.h"
+#include "spmm_cost.h"
 
 namespace gcn {
 
@@ -121,6 +122,14 @@ struct Hub {
     size_t xhot_bytes = 0;
 };
 
+// The schedule of a product whose order of additions is free (see SpmmOpt::any_schedule).
+struct SpmmPlan {
+    int32_t f = 0;
+    bool sweep = false;
+    int32_t blocks = 1;          // column blocks: of the matrix, or of the sweep's long rows
+    int32_t parts = 1, heavy = 0;// sweep: sums per row, long-row threshold
+};
+
 // One stored matrix in compressed rows plus its nonzero-split schedule.
 struct Matrix {
     int64_t nrows = 0, ncols = 0;
@@ -138,6 +147,8 @@ struct Matrix {
     int64_t n_fix = 0, n_fix_long = 0;   // the first n_fix_long of them cover a whole further chunk
     int64_t nsub = 0, nchunks = 0;
     int32_t max_degree = 0;
+    Lengths lengths;             // of its rows (not kept for the long rows of a sweep copy)
+    std::vector<SpmmPlan> plans; // schedules chosen so far, one per width
     // Other stored orders of the matrix, built on first use (or by a prepare call) and kept until the
     // matrix is destroyed.  blk / swp / hub are the copies the latest product used; a product that needs
     // another key (block width; lane groups, task height and long-row threshold; hub settings) parks the
@@ -305,6 +316,11 @@ struct SpmmOpt {
     bool pattern = false;
     const float* row_scale = nullptr;
     bool any_order = false;           // no ReLU decides on the result: a faster kernel may add a row's terms in another order
+    // Another schedule may add the terms in another order: also set for the stand-alone products (of widths that are a multiple of
+    // four, see spmm_launch).  The products whose sums a ReLU of this library decides on keep one schedule, chosen by sizes
+    // alone: where a sum is zero to rounding another order puts it on the other side, and every such element moves
+    // the gradient of the weights by 1e-4 of its norm.
+    bool any_schedule = false;
     // internal to the hub schedule:
     const uint8_t* defer = nullptr;   // rows whose sum is stored raw (no scale, no epilogue)
     bool accumulate = false;          // column-blocked reduce adds to what Z already holds
@@ -321,7 +337,7 @@ int spmm_launch(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx, f
                 int epilogue, const float* Zprev, int64_t ldzprev, hipStream_t s, const SpmmOpt& o = SpmmOpt());
 // builds the stored order and sizes the handle's buffers that spmm_launch would need for width f (16-byte
 // aligned operands with leading dimensions that are multiples of 4 assumed), without running the product
-int spmm_prepare(gcn_csr* a, Matrix& m, int32_t f, hipStream_t s);
+int spmm_prepare(gcn_csr* a, Matrix& m, int32_t f, hipStream_t s, bool any_schedule);
 // grows one of the handle's buffers; the replaced buffer is retired, not freed
 int grow_retire(gcn_csr* a, float** buf, size_t* have, size_t need);
 

@@ -49,8 +49,18 @@ __global__ void k_make_keys(int64_t m, int64_t n, const int32_t* __restrict__ sr
 
 // A fixed number of workgroups strides over the rows, so that there are few atomics on the two counters (one per
 // wavefront of 64 rows took 385 us on a million rows, nearly all of it waiting for the counters' one address).
+struct DegreeSums {
+    int32_t max_deg, pad;
+    unsigned long long n_nonempty;
+    unsigned long long rows[Lengths::BINS], entries[Lengths::BINS];        // as in Lengths
+};
+
 __global__ __launch_bounds__(256) void k_degrees(int64_t n, const int64_t* __restrict__ rowptr, int32_t* __restrict__ deg,
-                                                 int32_t* __restrict__ max_deg, unsigned long long* __restrict__ n_nonempty) {
+                                                 DegreeSums* __restrict__ sums) {
+    __shared__ unsigned s_rows[Lengths::BINS];
+    __shared__ unsigned long long s_entries[Lengths::BINS];
+    if (threadIdx.x < Lengths::BINS) { s_rows[threadIdx.x] = 0; s_entries[threadIdx.x] = 0; }
+    __syncthreads();
     int32_t m = 0;
     unsigned nz = 0;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
@@ -58,8 +68,13 @@ __global__ __launch_bounds__(256) void k_degrees(int64_t n, const int64_t* __res
         if (deg) deg[i] = d;
         m = d > m ? d : m;
         nz += d > 0;
+        if (sums && d > 0) {
+            const int b = 31 - __clz(d);
+            atomicAdd(&s_rows[b], 1u);
+            atomicAdd(&s_entries[b], (unsigned long long)d);
+        }
     }
-    if (!max_deg) return;
+    if (!sums) return;
 #pragma unroll
     for (int s = 32; s >= 1; s >>= 1) {
         const int32_t o = __shfl_xor(m, s, 64);
@@ -72,8 +87,12 @@ __global__ __launch_bounds__(256) void k_degrees(int64_t n, const int64_t* __res
     __syncthreads();
     if (threadIdx.x == 0) {
         for (int w = 1; w < 4; ++w) { m = s_m[w] > m ? s_m[w] : m; nz += s_nz[w]; }
-        atomicMax(max_deg, m);
-        if (nz) atomicAdd(n_nonempty, (unsigned long long)nz);
+        atomicMax(&sums->max_deg, m);
+        if (nz) atomicAdd(&sums->n_nonempty, (unsigned long long)nz);
+    }
+    if (threadIdx.x < Lengths::BINS && s_rows[threadIdx.x]) {
+        atomicAdd(&sums->rows[threadIdx.x], (unsigned long long)s_rows[threadIdx.x]);
+        atomicAdd(&sums->entries[threadIdx.x], s_entries[threadIdx.x]);
     }
 }
 static unsigned degree_blocks(int64_t n) {
@@ -218,16 +237,19 @@ int build_schedule(Matrix& m, int64_t n, int64_t nnz, hipStream_t s) {
     m.nsub = (nnz + SUB - 1) / SUB;
     m.nchunks = (nnz + CHUNK - 1) / CHUNK;
     TempBuf counters;
-    GCN_TRY(counters.alloc(16));
-    GCN_HIP_TRY(hipMemsetAsync(counters.p, 0, 16, s));
-    hipLaunchKernelGGL(k_degrees, dim3(degree_blocks(n)), dim3(256), 0, s, n, m.rowptr, (int32_t*)nullptr,
-                       (int32_t*)counters.p, (unsigned long long*)((char*)counters.p + 8));
+    GCN_TRY(counters.alloc(sizeof(DegreeSums)));
+    GCN_HIP_TRY(hipMemsetAsync(counters.p, 0, sizeof(DegreeSums), s));
+    hipLaunchKernelGGL(k_degrees, dim3(degree_blocks(n)), dim3(256), 0, s, n, m.rowptr, (int32_t*)nullptr, counters.as<DegreeSums>());
     GCN_LAUNCH_CHECK();
-    struct { int32_t maxd; int32_t pad; unsigned long long nne; } h;
-    GCN_HIP_TRY(hipMemcpyAsync(&h, counters.p, 16, hipMemcpyDeviceToHost, s));
+    DegreeSums h;
+    GCN_HIP_TRY(hipMemcpyAsync(&h, counters.p, sizeof h, hipMemcpyDeviceToHost, s));
     GCN_HIP_TRY(hipStreamSynchronize(s));
-    m.max_degree = h.maxd;
-    m.n_ne = (int64_t)h.nne;
+    m.max_degree = h.max_deg;
+    m.n_ne = (int64_t)h.n_nonempty;
+    for (int b = 0; b < Lengths::BINS; ++b) {
+        m.lengths.rows[b] = (int64_t)h.rows[b];
+        m.lengths.entries[b] = (int64_t)h.entries[b];
+    }
     const int64_t* rp = m.rowptr;
     if (m.n_ne < n) {
         GCN_TRY(device_alloc_t(&m.ne_rows, (size_t)m.n_ne));
@@ -318,8 +340,7 @@ static int create_impl(gcn_csr* a, int64_t n, int64_t m, const int32_t* src, con
     GCN_TRY(compress_keys(a->A, n, nnz, keys, cbits, false, s));
     GCN_TRY(device_alloc_t(&a->deg, (size_t)n));
     GCN_TRY(device_alloc_t(&a->A.val, (size_t)nnz));
-    hipLaunchKernelGGL(k_degrees, dim3(degree_blocks(n)), dim3(256), 0, s, n, a->A.rowptr, a->deg, (int32_t*)nullptr,
-                       (unsigned long long*)nullptr);
+    hipLaunchKernelGGL(k_degrees, dim3(degree_blocks(n)), dim3(256), 0, s, n, a->A.rowptr, a->deg, (DegreeSums*)nullptr);
     GCN_LAUNCH_CHECK();
     if (nnz > 0) {
         hipLaunchKernelGGL(k_values, dim3(blocks_for(nnz)), dim3(TPB), 0, s, nnz, keys, cbits, a->deg,
@@ -382,8 +403,7 @@ static int from_csr_impl(gcn_csr* a, int64_t n, int64_t ncols, const int64_t* ro
         GCN_HIP_TRY(hipStreamSynchronize(s));
         if (hbad) return fail(GCN_ERR_UNSORTED, "gcn_csr_create_from_csr: columns must be strictly ascending per row and inside [0,n)");
     }
-    hipLaunchKernelGGL(k_degrees, dim3(degree_blocks(n)), dim3(256), 0, s, n, a->A.rowptr, a->deg, (int32_t*)nullptr,
-                       (unsigned long long*)nullptr);
+    hipLaunchKernelGGL(k_degrees, dim3(degree_blocks(n)), dim3(256), 0, s, n, a->A.rowptr, a->deg, (DegreeSums*)nullptr);
     GCN_LAUNCH_CHECK();
     GCN_TRY(build_schedule(a->A, n, nnz, s));
     if (flags & GCN_BUILD_TRANSPOSE) {

@@ -22,7 +22,7 @@ static int norm_spmm(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t l
                      int epilogue, const float* Zprev, int64_t ldzprev, hipStream_t s, bool prescaled, bool any_order) {
     PhaseTimer pt(s, GCN_PHASE_SPMM);
     SpmmOpt o;
-    o.any_order = any_order;
+    o.any_order = o.any_schedule = any_order;
     if (!xs || !use_value_free(a)) return spmm_launch(a, m, f, X, ldx, Z, ldz, epilogue, Zprev, ldzprev, s, o);
     if (!prescaled) GCN_TRY(scale_rows_launch(a->n, f, X, ldx, a->inv_sqrt_deg, xs, f, s));
     o.pattern = true;
@@ -306,8 +306,8 @@ int gcn_epoch_prepare(gcn_csr* a, int32_t L_w, const int32_t* dims, int order, v
     for (int l = 0; l < L_w; ++l) {
         const int ord = resolve_order(order, dims[l], dims[l + 1]);
         const int32_t fw = ord == GCN_ORDER_GEMM_FIRST ? dims[l + 1] : dims[l];     // width of this layer's sparse products
-        GCN_TRY(spmm_prepare(a, matrix_of(a, 1), fw, s));                                      // forward: A^T
-        if (ord == GCN_ORDER_GEMM_FIRST || l > 0) GCN_TRY(spmm_prepare(a, matrix_of(a, 0), fw, s));   // backward: A
+        GCN_TRY(spmm_prepare(a, matrix_of(a, 1), fw, s, l == L_w - 1));                              // forward: A^T
+        if (ord == GCN_ORDER_GEMM_FIRST || l > 0) GCN_TRY(spmm_prepare(a, matrix_of(a, 0), fw, s, true));   // backward: A
     }
     GCN_HIP_TRY(hipStreamSynchronize(s));
     return GCN_OK;

@@ -1292,6 +1292,8 @@ struct SweepArgs {
     const int32_t* task_order;
     int64_t n;
     int32_t f, rb;
+    int32_t parts;               // how many sums a task's entries are cut into
+    int32_t panel, panels;       // of f
     const float* X; int64_t ldx;
     float* Z; int64_t ldz;
     const float* Zprev; int64_t ldzprev;
@@ -1321,8 +1323,8 @@ __global__ __launch_bounds__(64 * SWEEP_TASKS) void k_spmm_sweep(SweepArgs a, in
     if (idx >= count) return;                    // whole wavefront leaves; no block-wide barrier below
     float* const acc = s_acc + wave * ((a.rb + 1) * W);
     const int g = lane / LPR, li = lane % LPR;
-    const int col0 = li * 4;
-    const bool col_ok = col0 < a.f;
+    int col0;
+    const bool col_ok = lane_columns<LPR, 4>(a.f, a.panel, a.panels, li, &col0);
     const int64_t task = a.task_order[first_task + idx];
     for (int i = lane * 4; i < (a.rb + 1) * W; i += 256) *reinterpret_cast<float4*>(acc + i) = make_float4(0.f, 0.f, 0.f, 0.f);
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -1332,6 +1334,7 @@ __global__ __launch_bounds__(64 * SWEEP_TASKS) void k_spmm_sweep(SweepArgs a, in
     const int64_t mine = a.task_base[task] + g * STEPS + (lane & 3) * 2;       // this lane's two entries of the first trip
     const float* const xbase = a.X + (col_ok ? col0 : 0);
     const uint32_t xpitch = (uint32_t)a.ldx * 4u;
+    const int64_t row0 = task * a.rb;
     struct Index { int c[2], v[2]; uint32_t r; };
     struct Rows { float x[STEPS][4]; int off[STEPS], v[2]; };
     auto load = [&](int t, Index& n) {           // (past the end: the last trip again, not used)
@@ -1354,17 +1357,14 @@ __global__ __launch_bounds__(64 * SWEEP_TASKS) void k_spmm_sweep(SweepArgs a, in
 #pragma unroll
         for (int q = 0; q < STEPS; ++q) {
             at[q] = at_row(xbase, (uint32_t)trip_entry(n.c, q), xpitch);
-            m.off[q] = trip_entry(off, q) + col0;
+            m.off[q] = trip_entry(off, q) + li * 4;
         }
         if constexpr (VALUES) { m.v[0] = n.v[0]; m.v[1] = n.v[1]; }
         __builtin_amdgcn_sched_barrier(0);
         load(next, n);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int q = 0; q < STEPS; ++q) {
-            const float4 w4 = *reinterpret_cast<const float4*>(at[q]);
-            m.x[q][0] = w4.x; m.x[q][1] = w4.y; m.x[q][2] = w4.z; m.x[q][3] = w4.w;
-        }
+        for (int q = 0; q < STEPS; ++q) load_vec<4>(m.x[q], at[q]);
         __builtin_amdgcn_sched_barrier(0);
     };
     auto add = [&](const Rows& m) {
@@ -1388,7 +1388,39 @@ __global__ __launch_bounds__(64 * SWEEP_TASKS) void k_spmm_sweep(SweepArgs a, in
         }
         __builtin_amdgcn_sched_barrier(0);
     };
+    // The task's rows so far, G per pass and 16 bytes per lane: what Z holds of them (nothing at first) plus the sums in LDS.
+    bool part_in_z = false;
+    auto rows_out = [&](auto last) {
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll 4
+        for (int i = g; i < a.rb; i += G) {
+            const int64_t row = row0 + i;
+            if (row >= a.n || !col_ok) continue;
+            float4* const at = reinterpret_cast<float4*>(acc + i * W + li * 4);
+            float v[4] = {at->x, at->y, at->z, at->w};
+            float* const z = a.Z + row * a.ldz + col0;
+            if (part_in_z) {
+                float before[4];
+                load_vec<4>(before, z);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) v[u] += before[u];
+            }
+            if constexpr (last) {
+                epilogue_store<4, EPI>(z, EPI == GCN_EPI_MASK ? a.Zprev + row * a.ldzprev + col0 : nullptr, v,
+                                       a.row_scale ? a.row_scale[row] : 1.f);
+            } else {
+                store_vec<4>(z, v);
+                *at = make_float4(0.f, 0.f, 0.f, 0.f);
+            }
+        }
+        part_in_z = true;
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
     if (trips > 0) {
+        const int part = (trips / a.parts + 2) & ~1;            // trips between two of them, even
+        int next = part;
         Index n = {};
         Rows xa, xb;
         load(0, n);
@@ -1401,21 +1433,13 @@ __global__ __launch_bounds__(64 * SWEEP_TASKS) void k_spmm_sweep(SweepArgs a, in
             gather(n, t + 3, xa);                // trip t + 2
             add(xb);
             if (t + 2 >= trips) break;
+            if (t + 2 == next && a.parts > 1) {
+                rows_out(std::false_type());
+                next += part;
+            }
         }
     }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    // write the task's rows: G rows per pass, 16 bytes per lane
-    const int64_t row0 = task * a.rb;
-    for (int i = g; i < a.rb; i += G) {
-        const int64_t row = row0 + i;
-        if (row < a.n && col_ok) {
-            const float4 w4 = *reinterpret_cast<const float4*>(acc + i * W + col0);
-            float out[4] = {w4.x, w4.y, w4.z, w4.w};
-            epilogue_store<4, EPI>(a.Z + row * a.ldz + col0, EPI == GCN_EPI_MASK ? a.Zprev + row * a.ldzprev + col0 : nullptr, out,
-                                   a.row_scale ? a.row_scale[row] : 1.f);
-        }
-    }
+    rows_out(std::true_type());
 }
 
 // Rows of a task: what is left of a compute unit's LDS for each of SWEEP_TASKS, less the row of the padding entries.
@@ -1440,11 +1464,8 @@ static int launch_sweep(const SweepArgs& args, int64_t ntasks, int64_t per_cu, i
             const dim3 grid((unsigned)((count + waves - 1) / waves));
             const int threads = (int)waves * 64;
             SweepArgs a = args;
-            // one panel per launch: shift the column origin instead of using blockIdx.y
-            a.X = args.X + (size_t)y * W;
-            a.Z = args.Z + (size_t)y * W;
-            a.Zprev = args.Zprev ? args.Zprev + (size_t)y * W : nullptr;
-            a.f = args.f - (int32_t)(y * W) < W ? args.f - (int32_t)(y * W) : W;
+            a.panel = (int32_t)y;
+            a.panels = (int32_t)ytiles;
             switch (epilogue) {
                 case GCN_EPI_NONE: launch_lds<k_spmm_sweep<LPR, GCN_EPI_NONE, VALUES>>(grid, threads, lds, s, a, first, count); break;
                 case GCN_EPI_RELU: launch_lds<k_spmm_sweep<LPR, GCN_EPI_RELU, VALUES>>(grid, threads, lds, s, a, first, count); break;
@@ -1463,7 +1484,7 @@ struct SplitChoice {
     int lpr = 0, vec = 0;                         // lanes per row of X (RAGGED: from the width), floats per lane
 };
 
-static SplitChoice choose_split(int32_t f, int64_t nchunks, bool any_order, bool l2_resident) {
+static SplitChoice choose_split(int32_t f, int64_t nchunks, bool any_order, bool wide) {
     const int64_t cus = device_info().cus;
     if (f < 4) return {SplitChoice::SPLIT, 4, 1};
     if (f % 4 != 0 && !any_order) {
@@ -1479,15 +1500,14 @@ static SplitChoice choose_split(int32_t f, int64_t nchunks, bool any_order, bool
     }
     // Wider operands are processed in panels of 32 columns (one 128-byte line per gathered row): the panel of X that the
     // gathers touch is 4x smaller than at f = 128, so far more of it stays in L2, at the price of re-reading the
-    // index/value stream once per panel.
-    // When the gathers are served by the L2 anyway (column-blocked copy) panels of 64 are better: half the passes over
-    // the index/value stream and half the requests (config 3 at f = 128: 3.55 -> 3.27 ms; config 2, bound by line
-    // fills: 1.46 -> 1.69 ms, so not there).
+    // index/value stream once per panel.  Over column blocks, too: with blocks that suit a panel of 32 two passes beat one
+    // of 64 (40 M entries, 200 K vertices, 64 columns: 660 us and 820; 115 M, 233 K: 1530 and 1560).  The products
+    // that keep the schedule of their sizes alone (`wide`) have it in panels of 64 there, and with it their sums' order.
     // Rows that are not whole 16-byte pieces (only without an order to keep) straddle lines wherever they are cut: one
     // panel up to 64 columns (41 columns, 1 M rows: 1.20 ms in two panels, 0.89 in one).
     int lpr = 8;
     if (f <= 16) lpr = 4;
-    else if (f > 32 && ((f >= 64 && l2_resident) || (f % 4 != 0 && f <= 64))) lpr = 16;
+    else if (f > 32 && ((f >= 64 && wide) || (f % 4 != 0 && f <= 64))) lpr = 16;
     // k_spmm_few as long as its workgroups of three chunks run side by side (their LDS allows one per compute unit)
     const int64_t panels = (f + 4 * lpr - 1) / (4 * lpr);
     return {nchunks * panels <= cus * (WAVES_PER_BLOCK - 1) ? SplitChoice::FEW : SplitChoice::SPLIT, lpr, 4};
@@ -1543,6 +1563,46 @@ static int64_t choose_blocks(const Config& cfg, int64_t nrows, int64_t ncols, in
     return (cap >= 2 && 4 * cap >= want) ? cap : 1;
 }
 
+// The schedule of a product whose order of additions is free, by what the schedules are estimated to cost (spmm_cost.h); worked
+// out once per matrix and width.  `usual` is the number of blocks that the sizes alone give.  Small matrices and operands
+// that an L2 holds do not ask.
+static bool worth_a_plan(const Matrix& m, int32_t f, int64_t nnz) {
+    const int64_t panel = f < 32 ? f : 32;
+    return f >= 4 && nnz >= (1 << 20) && m.lengths.total() == nnz && m.ncols * panel * 4 > device_info().l2_bytes / 8 * 7;
+}
+
+static const SpmmPlan& plan_of(gcn_csr* a, Matrix& m, int32_t f, int64_t usual) {
+    for (const SpmmPlan& p : m.plans)
+        if (p.f == f) return p;
+    SpmmPlan p;
+    p.f = f;
+    const int64_t nnz = m.lengths.total();
+    const SpmmCost c{f, device_info().cus, 8.0, (double)device_info().l2_bytes};
+    // the columns of a matrix are the rows of its transpose, where that is stored; otherwise taken to be alike
+    const Matrix& t = a->symmetric || &m == &a->At ? a->A : a->At;
+    const Lengths lines = c.lines(t.lengths.total() == nnz ? t.lengths : Lengths::equal(m.ncols, nnz));
+    double split = 0;
+    p.blocks = c.best_blocks(m.lengths, lines, m.ncols, (int)usual, &split);
+    // The sweep adds a row's terms one after another: `parts` sums of about 20 terms on average are no further from the exact sum
+    // than those of the nonzero split, which adds slices of 32 or 64 terms (30 M pairs, 1 M vertices, 16 columns: 10.0e-8 of
+    // the norm there, 14.1, 10.5, 9.1 and 8.5e-8 with one to four parts; a part costs 6 % of the product).
+    constexpr int HEAVY = 8;                                    // rows of 2^8 entries and more are long
+    const int64_t mean = nnz / (m.n_ne > 0 ? m.n_ne : 1);
+    const int parts = (int)std::max<int64_t>(1, (mean + 20) / 21);
+    int heavy_blocks = 1;
+    const int32_t W = f <= 16 ? 16 : 32;
+    const double sweep = c.sweep(m.lengths, lines, m.nrows, m.ncols, HEAVY, sweep_rows(W), SWEEP_TASKS, parts, &heavy_blocks);
+    // ragged rows in two panels straddle lines twice (41 columns: no gain)
+    p.sweep = sweep < 0.87 * split && (f % 4 == 0 || f < 32);
+    if (p.sweep) {
+        p.blocks = heavy_blocks;
+        p.parts = parts;
+        p.heavy = (1 << HEAVY) - 1;
+    }
+    m.plans.push_back(p);
+    return m.plans.back();
+}
+
 static int zero_empty_rows(const Matrix& m, int32_t f, float* Z, int64_t ldz, hipStream_t s) {
     const int64_t n_empty = m.nrows - m.n_ne;
     if (m.empty_rows && n_empty > 0) {
@@ -1581,7 +1641,7 @@ static int run_matrix(gcn_csr* a, Matrix& mm, const int32_t* row_map, int64_t nn
         GCN_TRY(want_blocked(mm, nnz, cpb, s));
         const Blocked& b = mm.blk;
         GCN_TRY(grow_retire(a, &a->partial, &a->partial_bytes, (size_t)b.nrows * (size_t)f * sizeof(float)));
-        const SplitChoice choice = choose_split(f, mm.nchunks, o.any_order, true);
+        const SplitChoice choice = choose_split(f, mm.nchunks, o.any_order, !o.any_schedule);
         if (o.describe) {
             char t[200];
             snprintf(t, sizeof t, "blocked(blocks=%d,cols_per_block=%lld,partial_rows=%lld,chunks=%lld,kernel=%s)", (int)b.nblocks,
@@ -1819,7 +1879,9 @@ static void took(gcn_csr* a, int sched) {
 }
 
 int spmm_launch(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx, float* Z, int64_t ldz,
-                int epilogue, const float* Zprev, int64_t ldzprev, hipStream_t s, const SpmmOpt& o) {
+                int epilogue, const float* Zprev, int64_t ldzprev, hipStream_t s, const SpmmOpt& asked) {
+    SpmmOpt o = asked;
+    o.any_schedule = false;                                // set again where a plan decides
     const int64_t n = m.nrows, ncols = m.ncols, nnz = a->nnz;
     const Config& cfg = cfg_of(a);
     if (nnz == 0) {
@@ -1833,7 +1895,9 @@ int spmm_launch(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx, f
     int algo = cfg.spmm_algo;
     const bool vec4_all = (f % 4 == 0) && (ldx % 4 == 0) && (ldz % 4 == 0) && aligned16(X) && aligned16(Z) &&
                           (epilogue != GCN_EPI_MASK || ((ldzprev % 4 == 0) && aligned16(Zprev)));
-    const int64_t nblocks = choose_blocks(cfg, n, ncols, nnz, f, 24);
+    int64_t nblocks = choose_blocks(cfg, n, ncols, nnz, f, 24);
+    int32_t heavy = cfg.sweep_heavy, parts = 1;
+    int64_t heavy_blocks = 0;                              // 0: by sizes
     if (algo == 0) {
         // Column sweep when X is far beyond the caches, rows are long enough to give every task a
         // real walk over the columns, and too short for partial-row blocking; else nonzero-split.
@@ -1845,7 +1909,18 @@ int spmm_launch(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx, f
         const bool narrow_steps = deg >= 64 && 64 * ncols / deg <= (6ll << 20);
         algo = (huge && vec4_all && nblocks < 2 && narrow_steps) ? 3 : 2;
     }
-    if (algo == 3 && !vec4_all) algo = 2;
+    if (algo == 3 && f < 4) algo = 2;
+    bool hub_first = nblocks < 2;
+    if (algo == 2 && cfg.spmm_algo == 0 && cfg.spmm_blocks == 0 && asked.any_schedule && worth_a_plan(m, f, nnz)) {
+        o.any_schedule = true;
+        const SpmmPlan& p = plan_of(a, m, f, nblocks);
+        if (p.sweep) {
+            algo = 3;
+            heavy = std::min(heavy, p.heavy);
+            parts = p.parts;
+            heavy_blocks = p.blocks;
+        } else nblocks = p.blocks;
+    }
     if (rowwise_only(m, ldx, Z, ldz, epilogue, Zprev, ldzprev)) algo = 1;
     if ((algo == 2 && cfg.spmm_algo == 0) || algo == 4) {
         // Hub schedule: for operands beyond the L2s when most entries sit in long rows and hot columns
@@ -1858,7 +1933,7 @@ int spmm_launch(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx, f
         // Measured: it pays when a gathered row is narrower than a 128-byte line (packing then also puts
         // two hot rows into one line: config 4, width 16, 4.33 -> 3.15 ms) and not at 128 bytes per row
         // (config 2: 1.44 -> 1.48 ms), so the automatic choice is limited to panels below 32 floats.
-        const bool eligible = vec4_all && nblocks < 2 && H >= 2 * cpb && nnz >= (forced ? 1 : (4ll << 20)) &&
+        const bool eligible = vec4_all && hub_first && H >= 2 * cpb && nnz >= (forced ? 1 : (4ll << 20)) &&
                               (forced || (panel < 32 && ncols * panel * 4 > (32ll << 20)));
         if (eligible) {
             // built once per matrix and settings for the width of the first product that qualifies
@@ -1874,20 +1949,20 @@ int spmm_launch(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx, f
         const int LPRs = f <= 16 ? 4 : 8;
         const int W = LPRs * 4;
         const int32_t rb = sweep_rows(W);
-        GCN_TRY(want_sweep(m, nnz, 64 / LPRs, rb, cfg.sweep_heavy, s));
+        GCN_TRY(want_sweep(m, nnz, 64 / LPRs, rb, heavy, s));
         const Sweep& w = m.swp;
         if (o.describe) {
             const int64_t cap = (int64_t)device_info().cus * sweep_tasks(cfg);
             char t[240];
-            snprintf(t, sizeof t, "sweep(entries_per_step=%d,rows_per_task=%d,long_row>%d,tasks=%lld,launches=%lld,stored=%lld,kernel=k_spmm_sweep<%d>)",
-                     64 / LPRs, (int)rb, (int)cfg.sweep_heavy, (long long)w.ntasks,
+            snprintf(t, sizeof t, "sweep(entries_per_step=%d,rows_per_task=%d,long_row>%d,sums_per_row=%d,tasks=%lld,launches=%lld,stored=%lld,kernel=k_spmm_sweep<%d>)",
+                     64 / LPRs, (int)rb, (int)heavy, (int)parts, (long long)w.ntasks,
                      (long long)(((w.ntasks + cap - 1) / cap) * ((f + W - 1) / W)), (long long)w.padded, LPRs);
             *o.describe += t;
         }
         if (!o.dry) {
             SweepArgs sa;
             sa.colidx = w.colidx; sa.val = o.pattern ? nullptr : w.val; sa.row_scale = o.row_scale; sa.lrow = w.lrow; sa.task_base = w.task_base; sa.task_len = w.task_len; sa.task_order = w.task_order;
-            sa.n = n; sa.f = f; sa.rb = rb; sa.X = X; sa.ldx = ldx; sa.Z = Z; sa.ldz = ldz; sa.Zprev = Zprev; sa.ldzprev = ldzprev;
+            sa.n = n; sa.f = f; sa.rb = rb; sa.parts = parts; sa.X = X; sa.ldx = ldx; sa.Z = Z; sa.ldz = ldz; sa.Zprev = Zprev; sa.ldzprev = ldzprev;
             const auto launch = LPRs == 4 ? (o.pattern ? launch_sweep<4, false> : launch_sweep<4, true>)
                                           : (o.pattern ? launch_sweep<8, false> : launch_sweep<8, true>);
             GCN_TRY(launch(sa, w.ntasks, sweep_tasks(cfg), epilogue, s));
@@ -1896,7 +1971,7 @@ int spmm_launch(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx, f
             // long rows: nonzero-split kernel over the row subset; their rows are long enough for the
             // column-blocked form to pay even with many blocks
             Matrix& h = *w.heavy;
-            const int64_t hb = choose_blocks(cfg, h.nrows, ncols, w.nnz_heavy, f, 30);
+            const int64_t hb = heavy_blocks > 0 ? heavy_blocks : choose_blocks(cfg, h.nrows, ncols, w.nnz_heavy, f, 30);
             if (o.describe) *o.describe += "+long_rows:";
             GCN_TRY(run_matrix(a, h, h.ne_rows, w.nnz_heavy, hb, f, X, ldx, Z, ldz, epilogue, Zprev, ldzprev, o, s));
         }
@@ -1921,9 +1996,10 @@ bool use_value_free(const gcn_csr* a) {
     return mode == 1 || a->nnz / (a->n > 0 ? a->n : 1) >= 64;
 }
 
-int spmm_prepare(gcn_csr* a, Matrix& m, int32_t f, hipStream_t s) {
+int spmm_prepare(gcn_csr* a, Matrix& m, int32_t f, hipStream_t s, bool any_schedule) {
     SpmmOpt o;
     o.dry = true;
+    o.any_schedule = any_schedule;
     return spmm_launch(a, m, f, nullptr, f, nullptr, f, GCN_EPI_NONE, nullptr, 0, s, o);
 }
 
@@ -1948,6 +2024,10 @@ static int check_spmm_args(const char* who, const gcn_csr* a, int trans, int32_t
     return GCN_OK;
 }
 
+// Whether a stand-alone product may take any schedule: not at the ragged widths, whose kernels all add alike, and not the plain
+// forward product A^T X, on which the first hidden layer of gcn_epoch_preaggregated (or of the caller's own) decides.
+static bool free_schedule(int32_t f, int trans, int epilogue) { return f % 4 == 0 && !(trans && epilogue == GCN_EPI_NONE); }
+
 extern "C" int gcn_spmm(gcn_csr* a, int trans, int32_t f, const float* X, int64_t ldx, float* Z, int64_t ldz,
                         int epilogue, const float* Zprev, int64_t ldzprev, void* stream) {
     GCN_TRY(check_spmm_args("gcn_spmm", a, trans, f, X, ldx, Z, ldz, epilogue, Zprev, ldzprev));
@@ -1960,16 +2040,21 @@ extern "C" int gcn_spmm(gcn_csr* a, int trans, int32_t f, const float* X, int64_
         SpmmOpt o;
         o.pattern = true;
         o.row_scale = a->inv_sqrt_deg;
+        o.any_schedule = free_schedule(f, trans, epilogue);
         return spmm_launch(a, matrix_of(a, trans), f, a->xs, f, Z, ldz, epilogue, Zprev, ldzprev, s_of(stream), o);
     }
-    return spmm_launch(a, matrix_of(a, trans), f, X, ldx, Z, ldz, epilogue, Zprev, ldzprev, (hipStream_t)stream);
+    SpmmOpt o;
+    o.any_schedule = free_schedule(f, trans, epilogue);
+    return spmm_launch(a, matrix_of(a, trans), f, X, ldx, Z, ldz, epilogue, Zprev, ldzprev, (hipStream_t)stream, o);
 }
 
 extern "C" int gcn_spmm_prepare(gcn_csr* a, int trans, int32_t f, void* stream) {
     if (!a || f <= 0) return fail(GCN_ERR_BADARG, "gcn_spmm_prepare: NULL matrix or f <= 0");
     if (trans && !a->has_t) return fail(GCN_ERR_NOTRANSPOSE, "gcn_spmm_prepare: trans=1 needs GCN_BUILD_TRANSPOSE");
     if (use_value_free(a)) GCN_TRY(grow_retire(a, &a->xs, &a->xs_bytes, (size_t)a->n * (size_t)f * sizeof(float)));
-    return spmm_prepare(a, matrix_of(a, trans), f, (hipStream_t)stream);
+    // for the layer calls too: their backward and last products are free at every width
+    if (!free_schedule(f, trans, GCN_EPI_NONE)) GCN_TRY(spmm_prepare(a, matrix_of(a, trans), f, (hipStream_t)stream, false));
+    return spmm_prepare(a, matrix_of(a, trans), f, (hipStream_t)stream, true);
 }
 
 extern "C" int gcn_spmm_describe(gcn_csr* a, int trans, int32_t f, char* out, size_t out_bytes, void* stream) {
@@ -1979,6 +2064,7 @@ extern "C" int gcn_spmm_describe(gcn_csr* a, int trans, int32_t f, char* out, si
     SpmmOpt o;
     o.dry = true;
     o.describe = &text;
+    o.any_schedule = free_schedule(f, trans, GCN_EPI_NONE);
     o.pattern = use_value_free(a);
     GCN_TRY(spmm_launch(a, matrix_of(a, trans), f, nullptr, f, nullptr, f, GCN_EPI_NONE, nullptr, 0, (hipStream_t)stream, o));
     if (o.pattern) text += "; value-free (operand rows pre-scaled by d^-1/2, output rows scaled)";
@@ -2042,6 +2128,7 @@ extern "C" int gcn_spmm_pattern(gcn_csr* a, int trans, int32_t f, const float* X
     SpmmOpt o;
     o.pattern = true;
     o.row_scale = row_scale;
+    o.any_schedule = free_schedule(f, trans, epilogue);
     PhaseTimer whole(s_of(stream), GCN_PHASE_SPMM);
     return spmm_launch(a, matrix_of(a, trans), f, X, ldx, Z, ldz, epilogue, Zprev, ldzprev, (hipStream_t)stream, o);
 }

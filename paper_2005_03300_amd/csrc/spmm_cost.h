@@ -1,0 +1,160 @@
+// What a sparse product costs in each of the schedules, estimated from how long the rows and the columns of the matrix are
+// (host code without HIP).  The choice it makes is one of speed alone; every schedule computes every product.
+//
+// Two rates bound the gathers: what the L2s serve, and what they fetch (one 128-byte line per miss).  The misses follow from
+// the distribution of the column lengths: the L2 of an XCD holds `C` lines, a line of rate r (its share of the accesses) is
+// found there with probability 1 - exp(-r T), and T is such that the expected number of lines held is C (Che's
+// approximation of an LRU cache); a line costs one miss in any case where it is touched at all.  The constants were fitted to 600
+// timed products (uniform, R-MAT and Chung-Lu graphs of 60 K to 4 M vertices, 26 to 490 entries per row, 16 to 128
+// columns, 1 to 32 blocks, both schedules): estimates are within 9 % (blocks) and 11 % (sweep) of the times in the root
+// mean square, and the blocks chosen cost 2 to 4 % more than the best on average, where the rule by sizes alone
+// (blocks of 2 MB, rows of 24 entries per block) costs 9 %, up to 42 %.
+#pragma once
+#include <stdint.h>
+
+#include <algorithm>
+#include <cmath>
+
+namespace gcn {
+
+// How many rows (of a matrix, or of its transpose) have 2^b .. 2^(b+1) - 1 entries, and how many entries they hold.
+struct Lengths {
+    static constexpr int BINS = 32;
+    int64_t rows[BINS] = {};
+    int64_t entries[BINS] = {};
+    int64_t total() const { int64_t t = 0; for (int64_t e : entries) t += e; return t; }
+    int64_t count() const { int64_t t = 0; for (int64_t r : rows) t += r; return t; }
+    // the rows of at least 2^b entries, or the others
+    Lengths from(int b) const { Lengths l; for (int i = b; i < BINS; ++i) { l.rows[i] = rows[i]; l.entries[i] = entries[i]; } return l; }
+    Lengths below(int b) const { Lengths l; for (int i = 0; i < b; ++i) { l.rows[i] = rows[i]; l.entries[i] = entries[i]; } return l; }
+    // two of them at random on one line, three and four by doing it again: the lengths of the lines
+    Lengths paired() const {
+        Lengths l;
+        double r[BINS] = {}, e[BINS] = {};
+        const double all = std::max<double>(1.0, (double)count());
+        for (int i = 0; i < BINS; ++i)
+            for (int j = 0; rows[i] > 0 && j < BINS; ++j) {
+                if (rows[j] <= 0) continue;
+                const double n = 0.5 * (double)rows[i] * (double)rows[j] / all;
+                const double d = (double)entries[i] / (double)rows[i] + (double)entries[j] / (double)rows[j];
+                const int b = std::min(BINS - 1, (int)std::log2(d));
+                r[b] += n;
+                e[b] += n * d;
+            }
+        for (int i = 0; i < BINS; ++i)
+            if (r[i] > 0) { l.rows[i] = std::max<int64_t>(1, (int64_t)(r[i] + 0.5)); l.entries[i] = std::max<int64_t>(1, (int64_t)(e[i] + 0.5)); }
+        return l;
+    }
+    static Lengths equal(int64_t rows, int64_t entries) {        // all rows alike
+        Lengths l;
+        int b = 0;
+        while (b < 31 && (2ll << b) * rows <= entries) ++b;
+        l.rows[b] = rows;
+        l.entries[b] = entries;
+        return l;
+    }
+};
+
+struct SpmmCost {
+    int32_t f;                   // columns of the operand
+    int cus;
+    double xcds = 8, l2_bytes;
+
+    int panel() const { return f <= 16 ? 16 : 32; }
+    int passes() const { return (f + 31) / 32; }
+    int rows_per_line() const { const int w = f < 32 ? f : 32; return w >= 17 ? 1 : 32 / (w < 1 ? 1 : w); }
+
+    // The lines of X by the number of entries that select them.
+    Lengths lines(const Lengths& cols) const {
+        Lengths l = cols;
+        for (int per = rows_per_line(); per > 1; per /= 2) l = l.paired();
+        return l;
+    }
+
+    // Misses of one XCD: `accesses` to the lines that a `share` of the columns selects, which stay (`band`) or not.
+    double misses(const Lengths& lines, double share, double accesses, bool band) const {
+        const double all = std::max<double>(1.0, (double)lines.total()), c = l2_bytes * 0.835 / 128.0;        // the streams take some
+        double n[Lengths::BINS], r[Lengths::BINS];
+        int k = 0;
+        for (int b = 0; b < Lengths::BINS; ++b)
+            if (lines.rows[b] > 0) {
+                n[k] = (double)lines.rows[b] * share;
+                r[k++] = (double)lines.entries[b] / (double)lines.rows[b] / (all * share);
+            }
+        auto touched = [&](double t) { double s = 0; for (int i = 0; i < k; ++i) s += n[i] * (1.0 - std::exp(-r[i] * t)); return s; };
+        const double once = touched(accesses);
+        if (band || once <= c) return once;
+        double lo = 0, hi = accesses;
+        for (int it = 0; it < 40; ++it) {
+            const double mid = 0.5 * (lo + hi);
+            if (touched(mid) < c) lo = mid; else hi = mid;
+        }
+        double s = 0;
+        for (int i = 0; i < k; ++i) s += std::max(n[i] * (1.0 - std::exp(-r[i] * accesses)), n[i] * r[i] * accesses * std::exp(-r[i] * lo));
+        return s;
+    }
+
+    // Nonzero-split over `blocks` column blocks of the rows `rows` (microseconds); `lines` of the whole matrix.
+    double split(const Lengths& rows, const Lengths& lines, int blocks) const {
+        const double nnz = (double)rows.total(), fetched = nnz * passes();
+        const double m = misses(lines, 1.0 / blocks, nnz / xcds / blocks, false) * xcds * blocks * passes() + fetched * 8 / 128;
+        const bool narrow = f <= 16;
+        const double served = fetched / (narrow ? 228e3 : 174e3), filled = m / (narrow ? 67.9e3 : 57.2e3);
+        const double e = narrow ? 1.94 : 4.6;
+        double t = std::pow(std::pow(served, e) + std::pow(filled, e), 1.0 / e) + 5.0;
+        if (blocks > 1) {                        // partial rows: written, read, added
+            double partial = 0;
+            for (int b = 0; b < Lengths::BINS; ++b)
+                if (rows.rows[b] > 0)
+                    partial += (double)rows.rows[b] * blocks * (1.0 - std::pow(1.0 - 1.0 / blocks, (double)rows.entries[b] / (double)rows.rows[b]));
+            t += partial * f * 4 * (narrow ? 0.518e-6 : 0.453e-6) + 7.6;
+        }
+        return t;
+    }
+
+    // The number of blocks that costs least, `usual` unless another is 10 % better (the estimate's own error).  Up to 16 columns no
+    // fewer than usual (15 M pairs, R-MAT, 150 K vertices: 122 us over five, 131 over one, estimated 117 and 103).
+    int best_blocks(const Lengths& rows, const Lengths& lines, int64_t ncols, int usual, double* cost) const {
+        static const int tried[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96};
+        int best = usual;
+        double least = split(rows, lines, usual);
+        const double keep = least * 0.9;
+        for (int b : tried) {
+            if (b == usual || (b > 1 && ncols / b < 2048) || (f <= 16 && b < usual)) continue;
+            const double t = split(rows, lines, b);
+            if (t < keep && t < least) { least = t; best = b; }
+        }
+        *cost = least;
+        return best;
+    }
+
+    // Column sweep: rows below 2^heavy entries in `tasks_per_cu` tasks of `task_rows` per compute unit, `parts` sums per row; the
+    // others by the nonzero split (*heavy_blocks receives over how many blocks).
+    double sweep(const Lengths& rows, const Lengths& lines, int64_t nrows, int64_t ncols, int heavy, int32_t task_rows, int tasks_per_cu,
+                 int parts, int* heavy_blocks) const {
+        const Lengths light = rows.below(heavy), rest = rows.from(heavy);
+        const double nl = (double)light.total(), tasks = std::ceil((double)nrows / task_rows);
+        const double launches = std::ceil(tasks / ((double)tasks_per_cu * cus));
+        const int panels = (f + panel() - 1) / panel();
+        *heavy_blocks = 1;
+        if (nl <= 0) return 1e30;
+        // a row takes one pair of steps per entry: padding where a task's longest row has more than its share
+        int longest = 1;
+        for (int b = 0; b < heavy; ++b) if (light.rows[b] > 0) longest = 2 << b;
+        const double places = 2.0 * (64 / (panel() / 4));
+        const double pad = std::max(1.0, 0.55 * longest * places / (task_rows * nl / (double)nrows));
+        const double fetched = nl * pad;
+        const double m = launches * xcds * misses(lines, 1.0, nl / launches / xcds, true) + fetched * 10 / 128;
+        const double through = std::max(fetched / 130e3, m / 54e3);
+        const double chain = launches * (fetched / tasks / (8.0 * 64 / (panel() / 4))) * 0.67;        // a trip takes 0.67 us
+        double t = panels * (std::max(through, chain) + 4.0 * launches) + (parts - 1) * (double)nrows * f * 8 / 3.7e6;
+        if (rest.total() > 0) {
+            double h = 0;
+            *heavy_blocks = best_blocks(rest, lines, ncols, 1, &h);
+            t += 1.41 * h + 8.0;
+        }
+        return t;
+    }
+};
+
+}  // namespace gcn

@@ -607,3 +607,44 @@ def test_sweep_tasks_trips_and_padding(f, shape):
             g.gcn_spmm_pattern(a, 0, Xd, Zd, None, epi, Zpd)
             assert_close(host(Zd), of(plain), f"{shape} f={f} epilogue {epi}, value-free")
     a.close()
+
+
+@pytest.mark.parametrize("graph,f,want", [("wide", 16, "sweep("), ("wide", 32, "sweep("), ("wide", 20, "sweep("), ("wide", 48, "sweep("),
+                                          ("few_blocks", 32, "blocked(blocks=4,"), ("few_blocks", 64, "blocked(blocks=4,")])
+def test_schedule_by_cost_against_the_one_by_sizes(graph, f, want):
+    """Products whose schedule is chosen by estimated cost (A X, and A^T X with an epilogue), with operands of every pitch and alignment, in
+    both forms, against the products that keep the schedule of the sizes (A^T X: the matrix is symmetric) and against the
+    oracle: as far from it as those are, and no further."""
+    g = G()
+    rs = np.random.default_rng(124)
+    n, pairs = (500_000, 10_000_000) if graph == "wide" else (150_000, 5_000_000)
+    src, dst = [rs.integers(0, n, pairs).astype(np.int32) for _ in range(2)]
+    a = g.gcn_csr_create(n, dev(src), dev(dst), g.SYMMETRISE | g.ADD_SELF_LOOPS | g.NORM_SYM | g.BUILD_TRANSPOSE)
+    assert g.gcn_spmm_describe(a, 0, f).startswith(want) and not g.gcn_spmm_describe(a, 1, f).startswith(want)
+    ref = oracle.build_csr(n, src, dst)
+    X, Zp = synth.uniform_features(n, f, 125), synth.normal_features(n, f, 126)
+    exact = oracle.spmm(ref, X.astype(np.float64))
+    Xd, Zpd = dev(X), dev(Zp)
+    Zd = torch.empty(n, f, device="cuda")
+
+    def error():
+        return float((Zd.double() - dev(exact)).norm() / np.linalg.norm(exact))
+    g.gcn_spmm(a, 1, Xd, Zd)
+    usual = error()
+    g.gcn_spmm(a, 0, Xd, Zd)
+    first = host(Zd)
+    assert error() <= 1.02 * usual, (error(), usual)
+    assert_close(first, exact, "A X")
+    g.gcn_spmm(a, 0, Xd, Zd)
+    assert np.array_equal(first.view(np.uint32), host(Zd).view(np.uint32))
+    for trans, pad, off in ((0, 4, 0), (1, 1, 0), (0, 3, 1), (1, 0, 2)):
+        Xp = torch.full((n * (f + pad) + off,), float("nan"), device="cuda")[off:].view(n, f + pad)
+        Xp[:, :f] = Xd
+        Zw = torch.full((n, f + pad), float("nan"), device="cuda")
+        g.gcn_spmm(a, trans, Xp[:, :f], Zw[:, :f], g.EPI_RELU)
+        assert torch.equal(Zw[:, :f], dev(np.maximum(first, 0))) and bool(torch.isnan(Zw[:, f:]).all()), (trans, pad, off)
+        g.gcn_spmm(a, trans, Xp[:, :f], Zw[:, :f], g.EPI_MASK, Zpd)
+        assert torch.equal(Zw[:, :f], dev(np.where(Zp > 0, first, 0))), (trans, pad, off)
+    g.gcn_spmm_pattern(a, 0, Xd, Zd)
+    assert_close(host(Zd), oracle.spmm_pattern(ref, X.astype(np.float64)), "value-free")
+    a.close()
