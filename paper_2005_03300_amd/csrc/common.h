@@ -294,7 +294,7 @@ void launch_lds(dim3 grid, int threads, size_t lds, hipStream_t s, const Args&..
     hipLaunchKernelGGL(Kernel, grid, dim3(threads), lds, s, args...);
 }
 
-int build_schedule(Matrix& m, int64_t n, int64_t nnz, hipStream_t s);
+int build_schedule(Matrix& m, int64_t n, int64_t nnz, hipStream_t s, int32_t* deg = nullptr);   // deg: also receives the row lengths
 // One record per row whose entries run on into further chunks: x, y = the first and the last of them, z = the row (its
 // index among the non-empty rows).  Rows that leave no row start in chunk x come first (n_long of them).
 int build_fix_list(const uint32_t* flags, const int32_t* sub_row, const int64_t* rp, int64_t nnz, int4** list,

@@ -19,32 +19,70 @@ namespace gcn {
 
 // ---- kernels ---------------------------------------------------------------------------------
 
-__global__ void k_check_ids(int64_t m, int64_t n, const int32_t* __restrict__ src,
-                            const int32_t* __restrict__ dst, int* __restrict__ bad) {
-    int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= m) return;
-    int32_t u = src[e], v = dst[e];
-    if (u < 0 || v < 0 || u >= n || v >= n) *bad = 1;
+// The keys of the sort: one per stored direction of each input pair, then the diagonal.  A pair with u == v is dropped: with
+// self loops its key is that of the diagonal entry, which exists anyway; without, it becomes the key n<<cbits, which sorts
+// behind every real one.  The first pass of the sort reads the pairs themselves: a kernel that wrote the keys and one that checked
+// the ids took 104 us for 16.8 M pairs, the pass takes 65 us longer than over written keys.  *bad is set where an id
+// is outside [0, n), and nothing may be indexed by the keys then.
+struct PairKeys {
+    typedef uint64_t Key;
+    const int32_t* src;
+    const int32_t* dst;
+    int64_t m, n;
+    bool symmetrise, self_loops;
+    unsigned cbits;
+    int* bad;
+    __device__ uint64_t operator()(size_t i, bool& wrong) const {
+        const int64_t pairs = symmetrise ? 2 * m : m;
+        if ((int64_t)i >= pairs) {
+            const uint64_t v = (uint64_t)((int64_t)i - pairs);
+            return v << cbits | v;
+        }
+        const int64_t t = symmetrise ? (int64_t)(i >> 1) : (int64_t)i;
+        const uint64_t u = (uint32_t)src[t], v = (uint32_t)dst[t];
+        wrong |= u >= (uint64_t)n || v >= (uint64_t)n;
+        if (u == v && !self_loops) return (uint64_t)n << cbits;
+        return symmetrise && (i & 1) ? (v << cbits | u) : (u << cbits | v);
+    }
+    __device__ void report() const { *bad = 1; }
+};
+
+// The first key of every run of equal ones becomes an entry: its column, the row pointers of the rows it opens (all those after
+// the row of the key before it) and, where they are wanted, the key itself.  Keys of row n (dropped pairs) open the rows
+// that are left and are no entry.
+struct EmitEntry {
+    const uint64_t* in;
+    int64_t n;                   // rows
+    unsigned cbits;
+    int64_t* rowptr;
+    int32_t* colidx;
+    uint64_t* keys;              // or NULL
+    __device__ void operator()(int64_t i, int64_t pos) const {
+        const uint64_t key = in[i];
+        const int64_t r = (int64_t)(key >> cbits);
+        for (int64_t q = i > 0 ? (int64_t)(in[i - 1] >> cbits) + 1 : 0; q <= r; ++q) rowptr[q] = pos;
+        if (r >= n) return;
+        colidx[pos] = (int32_t)(key & ((1ull << cbits) - 1));
+        if (keys) keys[pos] = key;
+    }
+};
+
+// What the host has to know after the sort, in one copy (three copies that each wait for the stream took 60 us).
+struct SortResult {
+    int64_t kept;
+    uint64_t last;
+    int32_t bad;
+};
+__global__ void k_sort_result(const int64_t* __restrict__ kept, const uint64_t* __restrict__ last, const int* __restrict__ bad,
+                              SortResult* __restrict__ out) {
+    *out = SortResult{*kept, *last, *bad};
 }
 
-// One key per stored direction of each input pair.  A pair with u == v is dropped: with self loops its key is that of
-// the diagonal entry, which exists anyway; without, it becomes the key n<<cbits, which sorts behind every real one.
-// The diagonal is appended after the 'mult*m' keys of the pairs.
-__global__ void k_make_keys(int64_t m, int64_t n, const int32_t* __restrict__ src,
-                            const int32_t* __restrict__ dst, int symmetrise, int self_loops, unsigned cbits,
-                            uint64_t* __restrict__ keys) {
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int mult = symmetrise ? 2 : 1;
-    if (t < m) {
-        const uint64_t u = (uint32_t)src[t], v = (uint32_t)dst[t];
-        const bool drop = u == v && !self_loops;
-        const uint64_t none = (uint64_t)n << cbits;
-        keys[t * mult] = drop ? none : (u << cbits | v);
-        if (symmetrise) keys[t * mult + 1] = drop ? none : (v << cbits | u);
-    } else if (self_loops && t < m + n) {
-        uint64_t i = (uint64_t)(t - m);
-        keys[m * mult + (t - m)] = i << cbits | i;
-    }
+// Closes the rows behind the last key's.
+__global__ __launch_bounds__(256) void k_close_rows(int64_t n, int64_t nnz, const uint64_t* __restrict__ last, unsigned cbits,
+                                                    int64_t* __restrict__ rowptr) {
+    const int64_t from = last ? (int64_t)(*last >> cbits) + 1 : 0;
+    for (int64_t q = from + (int64_t)blockIdx.x * 256 + threadIdx.x; q <= n; q += (int64_t)gridDim.x * 256) rowptr[q] = nnz;
 }
 
 // A fixed number of workgroups strides over the rows, so that there are few atomics on the two counters (one per
@@ -68,13 +106,12 @@ __global__ __launch_bounds__(256) void k_degrees(int64_t n, const int64_t* __res
         if (deg) deg[i] = d;
         m = d > m ? d : m;
         nz += d > 0;
-        if (sums && d > 0) {
+        if (d > 0) {
             const int b = 31 - __clz(d);
             atomicAdd(&s_rows[b], 1u);
             atomicAdd(&s_entries[b], (unsigned long long)d);
         }
     }
-    if (!sums) return;
 #pragma unroll
     for (int s = 32; s >= 1; s >>= 1) {
         const int32_t o = __shfl_xor(m, s, 64);
@@ -103,23 +140,45 @@ static unsigned degree_blocks(int64_t n) {
 // val(i,j) = (float)(1 / sqrt(d_i d_j)): exact integer product in double, correctly rounded
 // square root and division, one rounding to float -- the same value on any IEEE machine.
 // norm 2 is the row normalisation D^-1 (A+I): val(i,j) = (float)(1 / d_i).
-__global__ void k_values(int64_t nnz, const uint64_t* __restrict__ keys, unsigned cbits, const int32_t* __restrict__ deg,
-                         int norm, float* __restrict__ val) {
-    int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= nnz) return;
-    if (norm == 0) {
-        val[k] = 1.0f;
-        return;
+// Four entries per thread; their rows follow from the schedule (the row of every 32nd entry and the flag of every row start), so
+// that only the columns are read.  Bound by the gathers of the columns' degrees: 16 bits where the longest row allows it, so that an
+// L2 holds the table.  34.3 M entries, 1 M rows: 231 us with an entry per thread and 8-byte keys, 204 this way with 32 bits, 179 with 16.
+template <typename Degree>
+__global__ __launch_bounds__(256) void k_values(int64_t nnz, const int32_t* __restrict__ colidx, const uint32_t* __restrict__ flags,
+                                                const int32_t* __restrict__ sub_row, const int32_t* __restrict__ ne_rows,
+                                                const Degree* __restrict__ deg, int norm, float* __restrict__ val) {
+    const int64_t k0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
+    if (k0 >= nnz) return;
+    const uint32_t word = flags[k0 / SUB] & ~1u;
+    const int32_t first = sub_row[k0 / SUB];
+    const int b0 = (int)(k0 % SUB), here = nnz - k0 < 4 ? (int)(nnz - k0) : 4;
+    int32_t c[4], di[4], dj[4];
+    if (here == 4) {
+        const int4 cc = *reinterpret_cast<const int4*>(colidx + k0);
+        c[0] = cc.x; c[1] = cc.y; c[2] = cc.z; c[3] = cc.w;
+    } else {
+        for (int e = 0; e < 4; ++e) c[e] = e < here ? colidx[k0 + e] : 0;
     }
-    uint64_t key = keys[k];
-    double di = (double)deg[key >> cbits], dj = (double)deg[key & ((1ull << cbits) - 1)];
-    if (norm == 2) val[k] = (float)__ddiv_rn(1.0, di);
-    else {
-        // a vertex whose row is empty (no self loops, no outgoing edge) scales by 0: D^-1/2 as a pseudo-inverse,
-        // the same convention as the per-vertex factors of the value-free product
-        const double dd = __dmul_rn(di, dj);
-        val[k] = dd > 0.0 ? (float)__ddiv_rn(1.0, __dsqrt_rn(dd)) : 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int32_t q = first + __popc(e < here ? word & (0xffffffffu >> (31 - b0 - e)) : 0u);
+        di[e] = deg[ne_rows ? ne_rows[q] : q];
+        dj[e] = norm == 1 ? deg[c[e]] : 0;
     }
+    float v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        if (norm == 2) v[e] = (float)__ddiv_rn(1.0, (double)di[e]);
+        else {
+            // a vertex whose row is empty (no self loops, no outgoing edge) scales by 0: D^-1/2 as a pseudo-inverse,
+            // the same convention as the per-vertex factors of the value-free product
+            const double dd = __dmul_rn((double)di[e], (double)dj[e]);
+            v[e] = dd > 0.0 ? (float)__ddiv_rn(1.0, __dsqrt_rn(dd)) : 0.f;
+        }
+    }
+    if (here == 4) *reinterpret_cast<float4*>(val + k0) = make_float4(v[0], v[1], v[2], v[3]);
+    else
+        for (int e = 0; e < here; ++e) val[k0 + e] = v[e];
 }
 
 // keys row<<cbits|col from compressed rows: thread k finds its row by bisection on rowptr.  *bad is set unless the columns
@@ -137,6 +196,11 @@ __global__ void k_keys_from_csr(int64_t nnz, int64_t n, int64_t ncols, const int
     const int32_t c = colidx[k];
     if (c < 0 || c >= ncols || (k > rowptr[lo] && colidx[k - 1] >= c)) *bad = 1;
     keys[k] = ((uint64_t)lo << cbits) | (uint32_t)c;
+}
+
+__global__ __launch_bounds__(256) void k_narrow(int64_t n, const int32_t* __restrict__ in, uint16_t* __restrict__ out) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n) out[i] = (uint16_t)in[i];
 }
 
 __global__ void k_validate_rowptr(int64_t n, const int64_t* __restrict__ rowptr, int* __restrict__ bad) {
@@ -203,6 +267,11 @@ struct LeadsCarry {
     }
 };
 
+__global__ void k_two_totals(const int64_t* __restrict__ a, const int64_t* __restrict__ b, int64_t* __restrict__ out) {
+    out[0] = *a;
+    out[1] = *b;
+}
+
 __global__ void k_fix_records(int64_t count, const int32_t* __restrict__ sel, const int32_t* __restrict__ sub_row,
                               const int64_t* __restrict__ rp, int4* __restrict__ list) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -218,13 +287,24 @@ int build_fix_list(const uint32_t* flags, const int32_t* sub_row, const int64_t*
     const int64_t nchunks = (nnz + CHUNK - 1) / CHUNK;
     if (nchunks <= 1) return GCN_OK;
     if (nchunks >= (1ll << 31)) return fail(GCN_ERR_RANGE, "schedule: too many chunks");
-    TempBuf sel;
-    GCN_TRY(sel.alloc((size_t)(nchunks - 1) * 4));
-    int64_t n_short = 0;
-    GCN_TRY(prims::select_indices(nchunks - 1, LeadsCarry{flags, sub_row, rp, nnz, true}, sel.as<int32_t>(), n_long, s));
-    GCN_TRY(prims::select_indices(nchunks - 1, LeadsCarry{flags, sub_row, rp, nnz, false}, sel.as<int32_t>() + *n_long, &n_short, s));
-    const int64_t nsel = *n_long + n_short;
+    // both kinds are positioned before the host waits for their numbers, once
+    const LeadsCarry longs{flags, sub_row, rp, nnz, true}, shorts{flags, sub_row, rp, nnz, false};
+    TempBuf sel, off_long, off_short, totals;
+    GCN_TRY(prims::select_positions(nchunks - 1, longs, off_long, s));
+    GCN_TRY(prims::select_positions(nchunks - 1, shorts, off_short, s));
+    GCN_TRY(totals.alloc(16));
+    hipLaunchKernelGGL(k_two_totals, dim3(1), dim3(1), 0, s, prims::select_total(nchunks - 1, off_long), prims::select_total(nchunks - 1, off_short),
+                       totals.as<int64_t>());
+    GCN_LAUNCH_CHECK();
+    int64_t h[2] = {0, 0};
+    GCN_HIP_TRY(hipMemcpyAsync(h, totals.p, 16, hipMemcpyDeviceToHost, s));
+    GCN_HIP_TRY(hipStreamSynchronize(s));
+    *n_long = h[0];
+    const int64_t nsel = h[0] + h[1];
     if (nsel > 0) {
+        GCN_TRY(sel.alloc((size_t)nsel * 4));
+        GCN_TRY(prims::select_store(nchunks - 1, longs, prims::EmitIndex32{sel.as<int32_t>()}, off_long, s));
+        GCN_TRY(prims::select_store(nchunks - 1, shorts, prims::EmitIndex32{sel.as<int32_t>() + h[0]}, off_short, s));
         GCN_TRY(device_alloc_t(list, (size_t)nsel));
         hipLaunchKernelGGL(k_fix_records, dim3(blocks_for(nsel)), dim3(TPB), 0, s, nsel, sel.as<int32_t>(), sub_row, rp, *list);
         GCN_LAUNCH_CHECK();
@@ -233,13 +313,13 @@ int build_fix_list(const uint32_t* flags, const int32_t* sub_row, const int64_t*
     return GCN_OK;
 }
 
-int build_schedule(Matrix& m, int64_t n, int64_t nnz, hipStream_t s) {
+int build_schedule(Matrix& m, int64_t n, int64_t nnz, hipStream_t s, int32_t* deg) {
     m.nsub = (nnz + SUB - 1) / SUB;
     m.nchunks = (nnz + CHUNK - 1) / CHUNK;
     TempBuf counters;
     GCN_TRY(counters.alloc(sizeof(DegreeSums)));
     GCN_HIP_TRY(hipMemsetAsync(counters.p, 0, sizeof(DegreeSums), s));
-    hipLaunchKernelGGL(k_degrees, dim3(degree_blocks(n)), dim3(256), 0, s, n, m.rowptr, (int32_t*)nullptr, counters.as<DegreeSums>());
+    hipLaunchKernelGGL(k_degrees, dim3(degree_blocks(n)), dim3(256), 0, s, n, m.rowptr, deg, counters.as<DegreeSums>());
     GCN_LAUNCH_CHECK();
     DegreeSums h;
     GCN_HIP_TRY(hipMemcpyAsync(&h, counters.p, sizeof h, hipMemcpyDeviceToHost, s));
@@ -300,65 +380,68 @@ static int create_impl(gcn_csr* a, int64_t n, int64_t m, const int32_t* src, con
     const int64_t cap = m * mult + (loops ? n : 0);
     const unsigned cbits = bits_for(n), kbits = cbits + bits_for(n + 1);
 
-    TempBuf bad;
+    const bool transpose = flags & GCN_BUILD_TRANSPOSE;
+    // Both directions of every pair are stored and the value formula (1, or 1/sqrt(d_i d_j)) is symmetric: A^T is A,
+    // bit by bit, and one set of arrays and schedules serves both.
+    a->symmetric = transpose && sym && !(flags & GCN_NORM_ROW);
+
+    TempBuf bad, k0, k1, off;
     GCN_TRY(bad.alloc(sizeof(int)));
     GCN_HIP_TRY(hipMemsetAsync(bad.p, 0, sizeof(int), s));
-    if (m > 0) {
-        hipLaunchKernelGGL(k_check_ids, dim3(blocks_for(m)), dim3(TPB), 0, s, m, n, src, dst, bad.as<int>());
-        GCN_LAUNCH_CHECK();
-    }
-    int hbad = 0;
-    GCN_HIP_TRY(hipMemcpyAsync(&hbad, bad.p, sizeof(int), hipMemcpyDeviceToHost, s));
-    GCN_HIP_TRY(hipStreamSynchronize(s));
-    if (hbad) return fail(GCN_ERR_RANGE, "gcn_csr_create: a vertex id is outside [0, %lld)", (long long)n);
-
-    TempBuf k0, k1;
-    GCN_TRY(k0.alloc((size_t)cap * 8));
-    GCN_TRY(k1.alloc((size_t)cap * 8));
     int64_t nnz = 0;
+    const uint64_t none = (uint64_t)n << cbits;
     if (cap > 0) {
-        hipLaunchKernelGGL(k_make_keys, dim3(blocks_for(m + (loops ? n : 0))), dim3(TPB), 0, s, m, n, src, dst,
-                           (int)sym, (int)loops, cbits, k0.as<uint64_t>());
+        GCN_TRY(k1.alloc((size_t)cap * 8));
+        GCN_TRY(prims::radix_sort_from(PairKeys{src, dst, m, n, sym, loops, cbits, bad.as<int>()}, k1.as<uint64_t>(), (size_t)cap,
+                                       loops ? cbits + bits_for(n) : kbits, s));
+        GCN_TRY(prims::select_positions(cap, prims::FirstOfRun{k1.as<uint64_t>()}, off, s));
+        TempBuf result;
+        GCN_TRY(result.alloc(sizeof(SortResult)));
+        hipLaunchKernelGGL(k_sort_result, dim3(1), dim3(1), 0, s, prims::select_total(cap, off), k1.as<uint64_t>() + (cap - 1), bad.as<int>(),
+                           result.as<SortResult>());
         GCN_LAUNCH_CHECK();
-        GCN_TRY((prims::radix_sort<uint64_t, prims::NoValue>(k0.as<uint64_t>(), k1.as<uint64_t>(), nullptr, nullptr,
-                                                             (size_t)cap, loops ? cbits + bits_for(n) : kbits, false, s, false)));
-        int64_t hcnt = 0;
-        uint64_t last = 0;
-        GCN_TRY(prims::unique_keys(k1.as<uint64_t>(), k0.as<uint64_t>(), cap, &hcnt, s));
-        if (hcnt > 0 && !loops) {
-            GCN_HIP_TRY(hipMemcpyAsync(&last, k0.as<uint64_t>() + (hcnt - 1), 8, hipMemcpyDeviceToHost, s));
-            GCN_HIP_TRY(hipStreamSynchronize(s));
-            if (last == ((uint64_t)n << cbits)) hcnt -= 1;
-        }
-        nnz = hcnt;
+        SortResult h;
+        GCN_HIP_TRY(hipMemcpyAsync(&h, result.p, sizeof h, hipMemcpyDeviceToHost, s));
+        GCN_HIP_TRY(hipStreamSynchronize(s));
+        if (h.bad) return fail(GCN_ERR_RANGE, "gcn_csr_create: a vertex id is outside [0, %lld)", (long long)n);
+        nnz = h.kept - (!loops && h.last == none ? 1 : 0);
     }
-    const uint64_t* keys = k0.as<uint64_t>();   // sorted, distinct, nnz of them
     a->n = n;
     a->ncols = n;
     a->nnz = nnz;
     a->A.nrows = a->A.ncols = n;
-    GCN_TRY(compress_keys(a->A, n, nnz, keys, cbits, false, s));
+    GCN_TRY(device_alloc_t(&a->A.rowptr, (size_t)n + 1));
+    GCN_TRY(device_alloc_t(&a->A.colidx, (size_t)nnz));
+    if (cap > 0) {
+        if (transpose && !a->symmetric) GCN_TRY(k0.alloc((size_t)nnz * 8));
+        GCN_TRY(prims::select_store(cap, prims::FirstOfRun{k1.as<uint64_t>()},
+                                    EmitEntry{k1.as<uint64_t>(), n, cbits, a->A.rowptr, a->A.colidx, k0.as<uint64_t>()}, off, s));
+    }
+    hipLaunchKernelGGL(k_close_rows, dim3(degree_blocks(n)), dim3(256), 0, s, n, nnz, cap > 0 ? k1.as<uint64_t>() + (cap - 1) : nullptr,
+                       cbits, a->A.rowptr);
+    GCN_LAUNCH_CHECK();
     GCN_TRY(device_alloc_t(&a->deg, (size_t)n));
     GCN_TRY(device_alloc_t(&a->A.val, (size_t)nnz));
-    hipLaunchKernelGGL(k_degrees, dim3(degree_blocks(n)), dim3(256), 0, s, n, a->A.rowptr, a->deg, (DegreeSums*)nullptr);
-    GCN_LAUNCH_CHECK();
+    GCN_TRY(build_schedule(a->A, n, nnz, s, a->deg));
     if (nnz > 0) {
-        hipLaunchKernelGGL(k_values, dim3(blocks_for(nnz)), dim3(TPB), 0, s, nnz, keys, cbits, a->deg,
-                           (flags & GCN_NORM_ROW) ? 2 : ((flags & GCN_NORM_SYM) ? 1 : 0), a->A.val);
+        const dim3 grid(blocks_for((nnz + 3) / 4));
+        if ((flags & GCN_NORM_SYM) && a->A.max_degree < (1 << 16)) {
+            TempBuf deg16;
+            GCN_TRY(deg16.alloc((size_t)n * 2));
+            hipLaunchKernelGGL(k_narrow, dim3(blocks_for(n)), dim3(TPB), 0, s, n, a->deg, deg16.as<uint16_t>());
+            GCN_LAUNCH_CHECK();
+            hipLaunchKernelGGL(k_values<uint16_t>, grid, dim3(TPB), 0, s, nnz, a->A.colidx, a->A.flags, a->A.sub_row, a->A.ne_rows, deg16.as<uint16_t>(), 1, a->A.val);
+        } else if (flags & (GCN_NORM_ROW | GCN_NORM_SYM))
+            hipLaunchKernelGGL(k_values<int32_t>, grid, dim3(TPB), 0, s, nnz, a->A.colidx, a->A.flags, a->A.sub_row, a->A.ne_rows, a->deg, (flags & GCN_NORM_ROW) ? 2 : 1, a->A.val);
+        else hipLaunchKernelGGL(k_fill_f32, dim3(blocks_for(nnz)), dim3(TPB), 0, s, nnz, 1.0f, a->A.val);
         GCN_LAUNCH_CHECK();
     }
     if ((flags & GCN_NORM_SYM) && n > 0) {
         GCN_TRY(device_alloc_t(&a->inv_sqrt_deg, (size_t)n));
         GCN_TRY(inv_sqrt_deg_launch(n, a->deg, a->inv_sqrt_deg, s));
     }
-    GCN_TRY(build_schedule(a->A, n, nnz, s));
-    if (flags & GCN_BUILD_TRANSPOSE) {
-        // Both directions of every pair are stored and the value formula (1, or 1/sqrt(d_i d_j)) is symmetric: A^T is A,
-        // bit by bit, and one set of arrays and schedules serves both.
-        a->symmetric = sym && !(flags & GCN_NORM_ROW);
-        if (a->symmetric) a->has_t = true;
-        else GCN_TRY(build_transpose(a, keys, cbits, k1.as<uint64_t>(), s));
-    }
+    if (a->symmetric) a->has_t = true;
+    else if (transpose) GCN_TRY(build_transpose(a, k0.as<uint64_t>(), cbits, k1.as<uint64_t>(), s));
     return GCN_OK;
 }
 
@@ -403,9 +486,7 @@ static int from_csr_impl(gcn_csr* a, int64_t n, int64_t ncols, const int64_t* ro
         GCN_HIP_TRY(hipStreamSynchronize(s));
         if (hbad) return fail(GCN_ERR_UNSORTED, "gcn_csr_create_from_csr: columns must be strictly ascending per row and inside [0,n)");
     }
-    hipLaunchKernelGGL(k_degrees, dim3(degree_blocks(n)), dim3(256), 0, s, n, a->A.rowptr, a->deg, (DegreeSums*)nullptr);
-    GCN_LAUNCH_CHECK();
-    GCN_TRY(build_schedule(a->A, n, nnz, s));
+    GCN_TRY(build_schedule(a->A, n, nnz, s, a->deg));
     if (flags & GCN_BUILD_TRANSPOSE) {
         GCN_TRY(k1.alloc((size_t)nnz * 8));
         GCN_TRY(build_transpose(a, keys.as<uint64_t>(), cbits, k1.as<uint64_t>(), s));

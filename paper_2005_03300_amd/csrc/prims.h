@@ -172,22 +172,35 @@ __global__ __launch_bounds__(P_TPB) void k_select_emit(int64_t n, Pred pred, Emi
             emit(base + (int64_t)k * P_TPB, off + cnt[k * P_WAVES + w] + __popcll(kept[k] & ((1ull << lane) - 1ull)));
 }
 
+// The first pass: tile_off receives the position of each tile's first kept index and, behind them, the number of kept ones.
+template <typename Pred> int select_positions(int64_t n, Pred pred, Scratch& tile_off, hipStream_t s) {
+    const int64_t ntiles = (n + SEL_TILE - 1) / SEL_TILE;
+    if (ntiles >= (1ll << 31)) return fail(GCN_ERR_RANGE, "select: %lld candidates are too many", (long long)n);
+    GCN_TRY(tile_off.alloc((size_t)(ntiles + 1) * 8));
+    int64_t* const cnt = tile_off.as<int64_t>();
+    GCN_HIP_TRY(hipMemsetAsync(cnt + ntiles, 0, 8, s));
+    hipLaunchKernelGGL(k_select_count<Pred>, dim3((unsigned)ntiles), dim3(P_TPB), 0, s, n, pred, cnt);
+    GCN_LAUNCH_CHECK();
+    return exclusive_scan<int64_t>(cnt, cnt, (size_t)ntiles + 1, s);
+}
+inline const int64_t* select_total(int64_t n, const Scratch& tile_off) { return tile_off.as<int64_t>() + (n + SEL_TILE - 1) / SEL_TILE; }
+
+// The second.
+template <typename Pred, typename Emit> int select_store(int64_t n, Pred pred, Emit emit, const Scratch& tile_off, hipStream_t s) {
+    hipLaunchKernelGGL((k_select_emit<Pred, Emit>), dim3((unsigned)((n + SEL_TILE - 1) / SEL_TILE)), dim3(P_TPB), 0, s, n, pred, emit,
+                       (const int64_t*)tile_off.as<int64_t>());
+    GCN_LAUNCH_CHECK();
+    return GCN_OK;
+}
+
 template <typename Pred, typename Emit> int select(int64_t n, Pred pred, Emit emit, int64_t* count, hipStream_t s) {
     if (count) *count = 0;
     if (n <= 0) return GCN_OK;
-    const int64_t ntiles = (n + SEL_TILE - 1) / SEL_TILE;
-    if (ntiles >= (1ll << 31)) return fail(GCN_ERR_RANGE, "select: %lld candidates are too many", (long long)n);
-    Scratch cnt;
-    GCN_TRY(cnt.alloc((size_t)(ntiles + 1) * 8));
-    GCN_HIP_TRY(hipMemsetAsync(cnt.as<int64_t>() + ntiles, 0, 8, s));
-    hipLaunchKernelGGL(k_select_count<Pred>, dim3((unsigned)ntiles), dim3(P_TPB), 0, s, n, pred, cnt.as<int64_t>());
-    GCN_LAUNCH_CHECK();
-    GCN_TRY(exclusive_scan<int64_t>(cnt.as<int64_t>(), cnt.as<int64_t>(), (size_t)ntiles + 1, s));
-    hipLaunchKernelGGL((k_select_emit<Pred, Emit>), dim3((unsigned)ntiles), dim3(P_TPB), 0, s, n, pred, emit,
-                       (const int64_t*)cnt.as<int64_t>());
-    GCN_LAUNCH_CHECK();
+    Scratch off;
+    GCN_TRY(select_positions(n, pred, off, s));
+    GCN_TRY(select_store(n, pred, emit, off, s));
     if (!count) return GCN_OK;
-    GCN_HIP_TRY(hipMemcpyAsync(count, cnt.as<int64_t>() + ntiles, 8, hipMemcpyDeviceToHost, s));
+    GCN_HIP_TRY(hipMemcpyAsync(count, select_total(n, off), 8, hipMemcpyDeviceToHost, s));
     GCN_HIP_TRY(hipStreamSynchronize(s));
     return GCN_OK;
 }
@@ -234,6 +247,15 @@ template <typename K> __device__ inline unsigned digit_of(K key, unsigned shift,
     return ((unsigned)(key >> shift) & mask) ^ flip;
 }
 
+// Where the keys of a pass come from: an array, or (first pass) whatever computes the i-th key and may find it wrong, which the
+// counting kernel reports once per thread.
+template <typename K> struct KeyArray {
+    typedef K Key;
+    const K* keys;
+    __device__ K operator()(size_t i, bool&) const { return keys[i]; }
+    __device__ void report() const {}
+};
+
 // Whole-key histograms of every digit position at once: hist[p*256 + d] = keys whose p-th byte is d.
 template <typename K>
 __global__ __launch_bounds__(P_TPB) void k_radix_byte_hist(const K* __restrict__ keys, size_t n,
@@ -269,25 +291,37 @@ __global__ __launch_bounds__(P_TPB) void k_radix_byte_hist(const K* __restrict__
         if (h[i]) atomicAdd(&hist[i], (unsigned long long)h[i]);
 }
 
-template <typename K, typename Off>
-__global__ __launch_bounds__(P_TPB) void k_radix_tile_hist(const K* __restrict__ keys, size_t n, unsigned shift,
+// Bound by memory: eight keys of a thread are on their way at a time (34.6 M 8-byte keys: 96 us with one, 66 with eight).
+template <typename Source, typename Off>
+__global__ __launch_bounds__(P_TPB) void k_radix_tile_hist(Source key_at, size_t n, unsigned shift,
                                                           unsigned mask, unsigned flip, size_t ntiles,
                                                           Off* __restrict__ hist) {
+    constexpr int AT_ONCE = 8;
+    typedef typename Source::Key K;
     __shared__ unsigned h[RS_RADIX];
     h[threadIdx.x] = 0;
     __syncthreads();
     const size_t base = (size_t)blockIdx.x * RS_TILE;
     unsigned last = 0, run = 0;
-    for (int r = 0; r < RS_ROUNDS; ++r) {
-        const size_t i = base + (size_t)r * P_TPB + threadIdx.x;
-        if (i < n) {
-            const unsigned d = digit_of(keys[i], shift, mask, flip);
+    bool wrong = false;
+    for (int r = 0; r < RS_ROUNDS; r += AT_ONCE) {
+        K key[AT_ONCE];
+#pragma unroll
+        for (int e = 0; e < AT_ONCE; ++e) {
+            const size_t i = base + (size_t)(r + e) * P_TPB + threadIdx.x;
+            key[e] = key_at(i < n ? i : n - 1, wrong);
+        }
+#pragma unroll
+        for (int e = 0; e < AT_ONCE; ++e) {
+            if (base + (size_t)(r + e) * P_TPB + threadIdx.x >= n) break;
+            const unsigned d = digit_of(key[e], shift, mask, flip);
             if (run && d != last) { atomicAdd(&h[last], run); run = 0; }
             last = d;
             ++run;
         }
     }
     if (run) atomicAdd(&h[last], run);
+    if (wrong) key_at.report();
     __syncthreads();
     hist[(size_t)threadIdx.x * ntiles + blockIdx.x] = (Off)h[threadIdx.x];
 }
@@ -301,11 +335,12 @@ template <typename K, typename V> constexpr size_t radix_lds_bytes() {
     return (size_t)RS_TILE * (sizeof(K) > v ? sizeof(K) : v);
 }
 
-template <typename K, typename V, typename Off>
-__global__ __launch_bounds__(RS_TPB) void k_radix_scatter(const K* __restrict__ kin, K* __restrict__ kout,
+template <typename Source, typename V, typename Off>
+__global__ __launch_bounds__(RS_TPB) void k_radix_scatter(Source key_at, typename Source::Key* __restrict__ kout,
                                                          const V* __restrict__ vin, V* __restrict__ vout, size_t n,
                                                          unsigned shift, unsigned mask, unsigned flip, size_t ntiles,
                                                          const Off* __restrict__ first) {
+    typedef typename Source::Key K;
     extern __shared__ __align__(16) unsigned char s_tile[];    // the tile's keys, then its payload, in output order
     __shared__ unsigned cnt[RS_WAVES][RS_RADIX];    // keys of each digit by wavefront; then their first place in the tile
     __shared__ Off place[RS_RADIX];                 // output position of a digit's keys less their place in the tile
@@ -316,10 +351,11 @@ __global__ __launch_bounds__(RS_TPB) void k_radix_scatter(const K* __restrict__ 
     for (int i = threadIdx.x; i < RS_WAVES * RS_RADIX; i += RS_TPB) (&cnt[0][0])[i] = 0;
     const int t0 = w * 64 * RS_ITEMS + lane;        // the thread's keys are t0 + 64 k
     K key[RS_ITEMS];
+    bool wrong = false;                             // (reported by the counting kernel)
 #pragma unroll
     for (int k = 0; k < RS_ITEMS; ++k) {
         key[k] = 0;
-        if (t0 + 64 * k < left) key[k] = kin[base + t0 + 64 * k];
+        if (t0 + 64 * k < left) key[k] = key_at(base + t0 + 64 * k, wrong);
     }
     __syncthreads();
     unsigned rank[RS_ITEMS];
@@ -400,9 +436,27 @@ __global__ __launch_bounds__(RS_TPB) void k_radix_scatter(const K* __restrict__ 
     }
 }
 
-template <typename K, typename V, typename Off>
-int radix_passes(const K* kin, K* kout, const V* vin, V* vout, size_t n, const unsigned* shifts, const unsigned* masks,
+template <typename Source, typename V, typename Off>
+int radix_pass(Source from, typename Source::Key* kdst, const V* vsrc, V* vdst, size_t n, unsigned shift, unsigned mask, unsigned flip,
+               Off* hist, hipStream_t s) {
+    typedef typename Source::Key K;
+    const size_t ntiles = (n + RS_TILE - 1) / RS_TILE;
+    constexpr size_t lds = radix_lds_bytes<K, V>();
+    if (lds > 48 * 1024)      // with the static part more than the 64 KB a workgroup gets without asking
+        GCN_HIP_TRY(hipFuncSetAttribute((const void*)k_radix_scatter<Source, V, Off>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    hipLaunchKernelGGL((k_radix_tile_hist<Source, Off>), dim3((unsigned)ntiles), dim3(P_TPB), 0, s, from, n, shift, mask, flip, ntiles, hist);
+    GCN_LAUNCH_CHECK();
+    GCN_TRY(exclusive_scan<Off>(hist, hist, ntiles * RS_RADIX, s));
+    hipLaunchKernelGGL((k_radix_scatter<Source, V, Off>), dim3((unsigned)ntiles), dim3(RS_TPB), lds, s, from, kdst, vsrc,
+                       vdst, n, shift, mask, flip, ntiles, (const Off*)hist);
+    GCN_LAUNCH_CHECK();
+    return GCN_OK;
+}
+
+template <typename Source, typename V, typename Off>
+int radix_passes(Source from, typename Source::Key* kout, const V* vin, V* vout, size_t n, const unsigned* shifts, const unsigned* masks,
                  int npass, bool descending, hipStream_t s) {
+    typedef typename Source::Key K;
     constexpr bool HAS_V = !std::is_same<V, NoValue>::value;
     const size_t ntiles = (n + RS_TILE - 1) / RS_TILE;
     Scratch hist, tk, tv;
@@ -411,27 +465,41 @@ int radix_passes(const K* kin, K* kout, const V* vin, V* vout, size_t n, const u
         GCN_TRY(tk.alloc(n * sizeof(K)));
         if (HAS_V) GCN_TRY(tv.alloc(n * sizeof(V)));
     }
-    const K* ksrc = kin;
+    const K* ksrc = nullptr;
     const V* vsrc = vin;
-    constexpr size_t lds = radix_lds_bytes<K, V>();
-    if (lds > 48 * 1024)      // with the static part more than the 64 KB a workgroup gets without asking
-        GCN_HIP_TRY(hipFuncSetAttribute((const void*)k_radix_scatter<K, V, Off>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     for (int p = 0; p < npass; ++p) {
         const bool to_out = ((npass - 1 - p) % 2) == 0;      // the last pass lands in the caller's output
         K* kdst = to_out ? kout : tk.as<K>();
         V* vdst = to_out ? vout : tv.as<V>();
         const unsigned flip = descending ? masks[p] : 0u;
-        hipLaunchKernelGGL((k_radix_tile_hist<K, Off>), dim3((unsigned)ntiles), dim3(P_TPB), 0, s, ksrc, n, shifts[p],
-                           masks[p], flip, ntiles, hist.as<Off>());
-        GCN_LAUNCH_CHECK();
-        GCN_TRY(exclusive_scan<Off>(hist.as<Off>(), hist.as<Off>(), ntiles * RS_RADIX, s));
-        hipLaunchKernelGGL((k_radix_scatter<K, V, Off>), dim3((unsigned)ntiles), dim3(RS_TPB), lds, s, ksrc, kdst, vsrc,
-                           vdst, n, shifts[p], masks[p], flip, ntiles, (const Off*)hist.as<Off>());
-        GCN_LAUNCH_CHECK();
+        if (p == 0) GCN_TRY((radix_pass<Source, V, Off>(from, kdst, vsrc, vdst, n, shifts[p], masks[p], flip, hist.as<Off>(), s)));
+        else GCN_TRY((radix_pass<KeyArray<K>, V, Off>(KeyArray<K>{ksrc}, kdst, vsrc, vdst, n, shifts[p], masks[p], flip, hist.as<Off>(), s)));
         ksrc = kdst;
         vsrc = vdst;
     }
     return GCN_OK;
+}
+
+// The passes over the bits [0, end_bit).
+inline int radix_digits(unsigned end_bit, unsigned* shifts, unsigned* masks) {
+    int npass = 0;
+    for (unsigned lo = 0; lo < end_bit; lo += 8) {
+        shifts[npass] = lo;
+        masks[npass] = (1u << (end_bit - lo < 8 ? end_bit - lo : 8)) - 1u;
+        ++npass;
+    }
+    return npass;
+}
+
+// Ascending sort of n keys that `from` computes (twice each), by their bits [0, end_bit), at least one of them.
+template <typename Source>
+int radix_sort_from(Source from, typename Source::Key* kout, size_t n, unsigned end_bit, hipStream_t s) {
+    typedef typename Source::Key K;
+    if (n == 0) return GCN_OK;
+    if ((n + RS_TILE - 1) / RS_TILE >= (1ull << 31)) return fail(GCN_ERR_RANGE, "radix_sort: %zu keys are too many", n);
+    unsigned shifts[sizeof(K)], masks[sizeof(K)];
+    const int npass = radix_digits(end_bit > 8 * sizeof(K) ? 8 * sizeof(K) : end_bit, shifts, masks);
+    return radix_passes<Source, NoValue, unsigned long long>(from, kout, nullptr, nullptr, n, shifts, masks, npass, false, s);
 }
 
 // Stable sort of n keys by their bits [0, end_bit), ascending or descending; the payload (if V is
@@ -451,11 +519,7 @@ int radix_sort(const K* kin, K* kout, const V* vin, V* vout, size_t n, unsigned 
     unsigned shifts[NB], masks[NB];
     int npass = 0;
     if (!probe) {
-        for (unsigned lo = 0; lo < end_bit; lo += 8) {
-            shifts[npass] = lo;
-            masks[npass] = (1u << (end_bit - lo < 8 ? end_bit - lo : 8)) - 1u;
-            ++npass;
-        }
+        npass = radix_digits(end_bit, shifts, masks);
     } else {
         Scratch bh;
         GCN_TRY(bh.alloc(NB * RS_RADIX * 8));
@@ -488,7 +552,7 @@ int radix_sort(const K* kin, K* kout, const V* vin, V* vout, size_t n, unsigned 
         return GCN_OK;
     }
     // positions are 64-bit whatever n is (their table is 1/32 of the keys' size): one code path at every size
-    return radix_passes<K, V, unsigned long long>(kin, kout, vin, vout, n, shifts, masks, npass, descending, s);
+    return radix_passes<KeyArray<K>, V, unsigned long long>(KeyArray<K>{kin}, kout, vin, vout, n, shifts, masks, npass, descending, s);
 }
 
 template <typename K> int sort_keys(const K* in, K* out, size_t n, unsigned end_bit, hipStream_t s) {

@@ -648,3 +648,35 @@ def test_schedule_by_cost_against_the_one_by_sizes(graph, f, want):
     g.gcn_spmm_pattern(a, 0, Xd, Zd)
     assert_close(host(Zd), oracle.spmm_pattern(ref, X.astype(np.float64)), "value-free")
     a.close()
+
+
+@pytest.mark.parametrize("n,m", [(1, 1), (2, 3), (300, 64), (300, 127), (5000, 4096), (5000, 4097), (70_000, 20_481)])
+@pytest.mark.parametrize("symmetrise", [False, True])
+@pytest.mark.parametrize("loops", [False, True])
+def test_csr_create_from_pairs_at_tile_edges(n, m, symmetrise, loops):
+    """The sort reads the pairs themselves, entries and row pointers come from the removal of equal keys: pair counts at the edges of the
+    sort's tiles, repeated pairs and pairs of equal ends, rows that stay empty at either end, both normalisations; an id outside
+    the range is refused wherever it stands."""
+    g = G()
+    rs = np.random.default_rng(127)
+    src = rs.integers(0, max(1, n // 3), m).astype(np.int32) + n // 3          # (the outer thirds stay empty without loops)
+    dst = rs.integers(0, max(1, n // 3), m).astype(np.int32) + n // 3
+    src[::5], dst[::7] = src[0], dst[0]
+    dst[::11] = src[::11]
+    src, dst = np.minimum(src, n - 1), np.minimum(dst, n - 1)
+    for norm, flag in (("none", 0), ("sym", g.NORM_SYM), ("row", g.NORM_ROW)):
+        flags = flag | (g.SYMMETRISE if symmetrise else 0) | (g.ADD_SELF_LOOPS if loops else 0) | g.BUILD_TRANSPOSE
+        a = g.gcn_csr_create(n, dev(src), dev(dst), flags)
+        for trans in (False, True):
+            ref = oracle.build_csr(n, src, dst, symmetrise=symmetrise, self_loops=loops, norm=norm)
+            ref = oracle.transpose(ref) if trans else ref
+            rowptr, colidx, val, _ = a.arrays(trans)
+            assert np.array_equal(host(rowptr), ref.rowptr) and np.array_equal(host(colidx), ref.colidx), (norm, trans)
+            assert np.array_equal(host(val).view(np.uint32), ref.val.view(np.uint32)), (norm, trans)
+        a.close()
+    for where, bad in ((0, -1), (m - 1, n), (m // 2, 2**31 - 1)):
+        for arr in (src, dst):
+            kept, arr[where] = arr[where], bad
+            with pytest.raises(g.GcnError):
+                g.gcn_csr_create(n, dev(src), dev(dst), g.SYMMETRISE if symmetrise else 0)
+            arr[where] = kept
