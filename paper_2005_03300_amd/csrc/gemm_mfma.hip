@@ -310,9 +310,9 @@ __global__ __launch_bounds__(512) void k_gemm_tall_flat(TallArgs a) {
 // and whose sums are added in LDS in a fixed order, so that a narrow product writes no more partial results than a
 // wide one.  Each trip consumes 16 rows (four per matrix instruction, one per lane quarter).  blockIdx.y takes 16 NT columns of B, blockIdx.z a share of the
 // column groups of A: any M and N.  The partial M x N results go to part[blockIdx.x][M][N].
-// Bound by the stream of A and B up to about 32 columns of B (128 x 16 over 4.4 M rows: 0.41 ms, 6.1 TB/s) and by the fp32
-// matrix rate and the stream together beyond (256 x 64 over 120 K rows 89 us, 44 TFLOP/s; one thread per output element
-// took 16.5 ms; 602 x 64 over 233 K rows: 0.27 ms, 66 TFLOP/s).
+// Bound by the stream of A and B up to about 32 columns of B (128 x 16 over 4.4 M rows: 0.36 ms, 6.9 TB/s; 300 x 16 over 14.2 M rows: 2.86 ms,
+// 6.4 TB/s) and by the fp32 matrix rate and the stream together beyond (256 x 64 over 120 K rows 52 us, 75 TFLOP/s; one
+// thread per output element took 16.5 ms).  Without the next trip on its way 3.3 ms, 0.41 ms and 61 us.
 struct TnArgs {
     int64_t K;
     int32_t M, N;
@@ -333,13 +333,26 @@ __global__ __launch_bounds__(512) void k_gemm_tn(TnArgs a) {
     const int64_t ke = kb + a.k_per_block < a.K ? kb + a.k_per_block : a.K;
     const int n0 = blockIdx.y * (16 * NT);
     const int m0 = blockIdx.z * (a.gw * MG * 64);
-    floatx4 acc[MG][4][NT];
+    floatx4 acc[MG][4][NT], sum[MG][4][NT];
 #pragma unroll
     for (int g = 0; g < MG; ++g)
 #pragma unroll
         for (int t = 0; t < 4; ++t)
 #pragma unroll
-            for (int u = 0; u < NT; ++u) acc[g][t][u] = (floatx4){0.f, 0.f, 0.f, 0.f};
+            for (int u = 0; u < NT; ++u) sum[g][t][u] = acc[g][t][u] = (floatx4){0.f, 0.f, 0.f, 0.f};
+    // after every 8 trips: a workgroup may take tens of thousands of rows, too many for one chain of additions (300 x 16 over
+    // 14.2 M rows: 29e-7 of the norm off without, 3.6e-7 with, and 7.5e-7 with 8192 workgroups of one chain each)
+    auto flush = [&]() {
+#pragma unroll
+        for (int g = 0; g < MG; ++g)
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int u = 0; u < NT; ++u) {
+                    sum[g][t][u] += acc[g][t][u];
+                    acc[g][t][u] = (floatx4){0.f, 0.f, 0.f, 0.f};
+                }
+    };
 
     // Lanes past the last column repeat the last four columns of A (the last column of B): no load needs a guard, and
     // an element that two lanes compute gets the same bits from both.
@@ -361,43 +374,27 @@ __global__ __launch_bounds__(512) void k_gemm_tn(TnArgs a) {
     const int kstep = 16 * a.rw;
     int64_t k0 = kfirst;
     // Wavefronts on neighbouring columns share the lines at their edges when rows are not whole lines: kept within four
-    // trips of each other they find them in the caches (300 x 16 over 14.2 M rows 4.20 -> 3.33 ms, 5.4 TB/s).  All
-    // of them take the same number of trips.  Products of 33 columns or more are bound by the matrix rate: no barrier
-    // there (602 x 64: 275 us without, 296 us with).
-    const bool in_step = NT <= 2 && a.rw == 1 && a.gw > 1;
-    int trip = 0;
-    for (; k0 < ke; k0 += kstep) {
-        if (in_step && (++trip & 3) == 0) __builtin_amdgcn_s_barrier();
-        float av[4][MG][4], bv[4][NT];
-        if (k0 + 16 <= ke) {
+    // trips of each other they find them in the caches (300 x 16 over 1.8 M rows 385 us without, 371 with; 500 x 64
+    // over 60 K rows 57 and 52).  All of them take the same number of trips.
+    const bool in_step = a.rw == 1 && a.gw > 1;
+    struct Trip { float a[4][MG][4], b[4][NT]; };
+    auto load = [&](Trip& x) {                          // 16 rows from ap, bp on, which move to the next trip
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
+        for (int s = 0; s < 4; ++s) {
 #pragma unroll
-                for (int u = 0; u < NT; ++u) bv[s][u] = bp[u][4 * s * a.ldb];
+            for (int u = 0; u < NT; ++u) x.b[s][u] = bp[u][4 * s * a.ldb];
 #pragma unroll
-                for (int g = 0; g < MG; ++g) {
-                    const float4 v = STREAM ? stream4(ap[g] + 4 * s * a.lda) : load4(ap[g] + 4 * s * a.lda);
-                    av[s][g][0] = v.x; av[s][g][1] = v.y; av[s][g][2] = v.z; av[s][g][3] = v.w;
-                }
-            }
-        } else {                                        // the last, short trip: rows past the end count as zero
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const bool kok = k0 + 4 * s + kq < ke;
-#pragma unroll
-                for (int u = 0; u < NT; ++u) bv[s][u] = kok ? bp[u][4 * s * a.ldb] : 0.f;
-#pragma unroll
-                for (int g = 0; g < MG; ++g) {
-                    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (kok) v = load4(ap[g] + 4 * s * a.lda);
-                    av[s][g][0] = v.x; av[s][g][1] = v.y; av[s][g][2] = v.z; av[s][g][3] = v.w;
-                }
+            for (int g = 0; g < MG; ++g) {
+                const float4 v = STREAM ? stream4(ap[g] + 4 * s * a.lda) : load4(ap[g] + 4 * s * a.lda);
+                x.a[s][g][0] = v.x; x.a[s][g][1] = v.y; x.a[s][g][2] = v.z; x.a[s][g][3] = v.w;
             }
         }
 #pragma unroll
         for (int g = 0; g < MG; ++g) ap[g] += (int64_t)kstep * a.lda;
 #pragma unroll
         for (int u = 0; u < NT; ++u) bp[u] += (int64_t)kstep * a.ldb;
+    };
+    auto multiply = [&](const Trip& x) {
 #pragma unroll
         for (int s = 0; s < 4; ++s)
 #pragma unroll
@@ -406,8 +403,52 @@ __global__ __launch_bounds__(512) void k_gemm_tn(TnArgs a) {
                 for (int t = 0; t < 4; ++t)
 #pragma unroll
                     for (int u = 0; u < NT; ++u)
-                        acc[g][t][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[s][g][t], bv[s][u], acc[g][t][u], 0, 0, 0);
+                        acc[g][t][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.a[s][g][t], x.b[s][u], acc[g][t][u], 0, 0, 0);
+    };
+    int trip = 0;
+    auto step = [&]() { if (in_step && (++trip & 3) == 0) __builtin_amdgcn_s_barrier(); };
+    const int64_t full = k0 + 16 <= ke ? (ke - 16 - k0) / kstep + 1 : 0;      // whole trips of this wavefront
+    const int64_t all = k0 < ke ? (ke - 1 - k0) / kstep + 1 : 0;        // with the short one
+    {                                                   // the next trip is on its way while this one is multiplied
+        Trip x, y;
+        int64_t t = 0;
+        if (full > 0) load(x);
+#pragma unroll 1
+        for (; t + 2 <= full; t += 2) {
+            load(y);
+            step();
+            multiply(x);
+            if (t + 2 < full) load(x);
+            step();
+            multiply(y);
+            if ((t & 6) == 6) flush();
+        }
+        if (t < full) { step(); multiply(x); }
     }
+    if (full < all) {                                   // the short trip: rows past the end count as zero
+        k0 += full * kstep;
+        step();
+        Trip x;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const bool kok = k0 + 4 * s + kq < ke;
+#pragma unroll
+            for (int u = 0; u < NT; ++u) x.b[s][u] = kok ? bp[u][4 * s * a.ldb] : 0.f;
+#pragma unroll
+            for (int g = 0; g < MG; ++g) {
+                float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (kok) v = load4(ap[g] + 4 * s * a.lda);
+                x.a[s][g][0] = v.x; x.a[s][g][1] = v.y; x.a[s][g][2] = v.z; x.a[s][g][3] = v.w;
+            }
+        }
+        multiply(x);
+    }
+#pragma unroll
+    for (int g = 0; g < MG; ++g)
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int u = 0; u < NT; ++u) acc[g][t][u] += sum[g][t][u];
     // the row sets hold partial sums of the same tiles: added in order 0, 1, 2, 3 in LDS
     for (int w = 1; w < a.rw; ++w) {
         float4* mine = reinterpret_cast<float4*>(s_part) + (size_t)gwave * (MG * 4 * NT) * 64 + lane;
@@ -459,16 +500,17 @@ __global__ __launch_bounds__(256) void k_gemm_tn_narrow(TnArgs a) {
     const int i = lane & 15, kq = lane >> 4;
     const int64_t kb = (int64_t)blockIdx.x * a.k_per_block;
     const int64_t ke = kb + a.k_per_block < a.K ? kb + a.k_per_block : a.K;
-    floatx4 acc[MG][NT];
+    floatx4 acc[MG][NT], total[MG][NT];
 #pragma unroll
     for (int g = 0; g < MG; ++g)
 #pragma unroll
-        for (int u = 0; u < NT; ++u) acc[g][u] = (floatx4){0.f, 0.f, 0.f, 0.f};
+        for (int u = 0; u < NT; ++u) total[g][u] = acc[g][u] = (floatx4){0.f, 0.f, 0.f, 0.f};
     bool mok[MG], nok[NT];
 #pragma unroll
     for (int g = 0; g < MG; ++g) mok[g] = 16 * g + i < a.M;
 #pragma unroll
     for (int u = 0; u < NT; ++u) nok[u] = 16 * u + i < a.N;
+    int trip = 0;
     for (int64_t k0 = kb + 16 * wave; k0 < ke; k0 += 64) {
         float av[4][MG], bv[4][NT];
 #pragma unroll
@@ -489,7 +531,17 @@ __global__ __launch_bounds__(256) void k_gemm_tn_narrow(TnArgs a) {
 #pragma unroll
                 for (int u = 0; u < NT; ++u)
                     acc[g][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[s][g], bv[s][u], acc[g][u], 0, 0, 0);
+        if ((++trip & 7) == 0) {                        // (as in k_gemm_tn)
+#pragma unroll
+            for (int g = 0; g < MG; ++g)
+#pragma unroll
+                for (int u = 0; u < NT; ++u) { total[g][u] += acc[g][u]; acc[g][u] = (floatx4){0.f, 0.f, 0.f, 0.f}; }
+        }
     }
+#pragma unroll
+    for (int g = 0; g < MG; ++g)
+#pragma unroll
+        for (int u = 0; u < NT; ++u) acc[g][u] += total[g][u];
     // the four wavefronts hold partial sums of the same tiles: add them in LDS, fixed order
     float* out = a.part + (int64_t)blockIdx.x * a.M * a.N;
     __shared__ float s_red[4][MG][NT][64][4];
@@ -642,8 +694,8 @@ static TnShape tn_shape(int64_t M, int64_t N, int64_t K) {
     if (g.narrow) {
         g.MG = (int)((g.Mw + 15) / 16);
     } else {
-        // column groups per wavefront: what the accumulators leave room for (up to 128 registers)
-        const int mg_max = g.NT >= 3 ? 2 : (g.NT == 2 ? 3 : 4);
+        // column groups per wavefront: what two sets of accumulators and two trips leave room for (250 registers)
+        const int mg_max = g.NT >= 2 ? 1 : 3;
         // wavefronts on different groups: one per group up to 8, else the count in 4..8 that leaves the fewest idle
         // slots (300 columns: 5 groups on 5 wavefronts instead of 2+1+1+1 on 4)
         g.gw = groups;
@@ -663,14 +715,19 @@ static TnShape tn_shape(int64_t M, int64_t N, int64_t K) {
     const int64_t rows = g.narrow ? 64 : 16 * g.rw;       // rows per trip of a workgroup
     const int64_t count = g.Mw * g.Nw;
     int64_t blocks = K / (2 * rows);
-    // measured: more, shorter workgroups pay when a workgroup has five or more wavefronts (300 columns:
-    // 4.13 ms with 2048 workgroups, 3.84 ms with 8192), fewer otherwise (256 columns: 2.69 vs 2.84 ms)
-    int64_t most = g.narrow ? 2048 : (g.gw >= 5 ? 8192 : (g.gw >= 4 ? 2048 : 4096));
-    // the partial results are written and read once more: keep them below an eighth of the operands' bytes, unless
-    // that leaves fewer than 64 workgroups over K (fewer still where the result alone is large)
-    const int64_t fair = K * (g.Mw + g.Nw) / (16 * count);
+    // but no more workgroups than run side by side: a workgroup loads its next trip while it multiplies, and the partial results
+    // are written and read once more.  One per compute unit, two where the partial results are below 1/40 of the operands
+    // (200 x 32 over 1 M rows 231 and 199 us; 256 x 64 over 120 K rows 52 and 64); four of the narrow kernel (16 x 16 over 4.4 M rows:
+    // 105 us, two 150, eight 112).  With up to 8192, and partial results below an eighth of the operands: 300 x 16 over 14.2 M
+    // rows 3.20 ms (now 2.86, 6.4 TB/s), 128 x 16 over 4.4 M 425 us (364), 256 x 64 over 120 K 89 (52), 602 x 64 over 100 K 255 (127).
+    const int64_t cus = device_info().cus, operands = K * (g.Mw + g.Nw);
+    int64_t most = (g.narrow ? 4 : (80 * cus * count <= operands ? 2 : 1)) * cus / ((int64_t)g.ny * g.nz);
+    // partial results below a third of the operands, unless that leaves fewer than 64 workgroups over K (fewer still where
+    // the result alone is large)
+    const int64_t fair = operands / (3 * count);
     const int64_t least = count >= (1ll << 26) ? 1 : (count > (1ll << 20) ? (1ll << 26) / count : 64);
-    if (most > fair) most = fair < least ? least : fair;
+    if (most > fair) most = fair;
+    if (most < least) most = least;
     if (blocks > most) blocks = most;
     if (blocks < 1) blocks = 1;
     int64_t kpb = (K + blocks - 1) / blocks;
@@ -799,9 +856,8 @@ int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const floa
         else hipLaunchKernelGGL((k_gemm_tn_narrow<2, 2>), grid, dim3(256), 0, s, args);
     }
 #define GCN_TN_CASE(mg, nt) else if (g.MG == mg && g.NT == nt) launch_tn<mg, nt>(args, stream, grid, s)
-    GCN_TN_CASE(1, 1); GCN_TN_CASE(2, 1); GCN_TN_CASE(3, 1); GCN_TN_CASE(4, 1);
-    GCN_TN_CASE(1, 2); GCN_TN_CASE(2, 2); GCN_TN_CASE(3, 2);
-    GCN_TN_CASE(1, 3); GCN_TN_CASE(2, 3); GCN_TN_CASE(1, 4); GCN_TN_CASE(2, 4);
+    GCN_TN_CASE(1, 1); GCN_TN_CASE(2, 1); GCN_TN_CASE(3, 1);
+    GCN_TN_CASE(1, 2); GCN_TN_CASE(1, 3); GCN_TN_CASE(1, 4);
 #undef GCN_TN_CASE
     GCN_LAUNCH_CHECK();
     const int64_t count = M * N;

@@ -680,3 +680,21 @@ def test_csr_create_from_pairs_at_tile_edges(n, m, symmetrise, loops):
             with pytest.raises(g.GcnError):
                 g.gcn_csr_create(n, dev(src), dev(dst), g.SYMMETRISE if symmetrise else 0)
             arr[where] = kept
+
+
+@pytest.mark.parametrize("M,N", [(16, 16), (64, 16), (300, 16), (602, 16), (130, 32), (200, 48), (100, 64), (700, 64)])
+@pytest.mark.parametrize("trips", [1, 2, 7, 8, 9, 16, 17])
+def test_gemm_tn_trips_and_sums(M, N, trips):
+    """Numbers of 16-row trips at which the pipeline of the A^T B kernel ends, its sums are put aside, or the last trip is short; wide and
+    narrow, one and several column groups per wavefront.  The error against 64 bits is what single precision gives: chains of at most 8
+    trips, 3.5e-7 of the norm was measured up to 14 M rows."""
+    g = G()
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    for K in (trips * 16, trips * 16 * cus + 5, trips * 64 * cus - 1):
+        if K * (M + N) > 4e7:
+            continue
+        H, S = synth.normal_features(K, M, 128), synth.normal_features(K, N, 129)
+        Y = torch.full((M, N), float("nan"), device="cuda")
+        g.gcn_gemm(1, 0, dev(H), dev(S), Y)
+        want = H.astype(np.float64).T @ S.astype(np.float64)
+        assert np.linalg.norm(host(Y) - want) <= 5e-7 * np.linalg.norm(want), (K, M, N)
