@@ -68,6 +68,33 @@ struct TallArgs {
     const float* row_scale;   // NULL, or one factor per row of C, applied after bias and epilogue (wide store path only)
 };
 
+// Columns n0 .. n0 + 16 NT of op(B) into LDS, zeros behind its end: 16 bytes per load, four loads of a thread on their way.
+template <int NT>
+__device__ __forceinline__ void stage_b(const TallArgs& a, int n0, float* Bs) {
+    constexpr int C = 16 * NT;
+    auto four = [](const float* p, int left) {          // the first `left` of four
+        if (left >= 4) return load4(p);
+        return make_float4(left > 0 ? p[0] : 0.f, left > 1 ? p[1] : 0.f, left > 2 ? p[2] : 0.f, 0.f);
+    };
+    if (!a.tb) {
+        const int count = a.Kpad * (C / 4);
+#pragma unroll 4
+        for (int i = threadIdx.x; i < count; i += blockDim.x) {
+            const int k = i / (C / 4), j = i % (C / 4) * 4;
+            *reinterpret_cast<float4*>(Bs + k * a.S + j) = four(a.B + (int64_t)k * a.ldb + n0 + j, k < a.K ? a.N - n0 - j : 0);
+        }
+    } else {
+        const int count = a.Kpad / 4 * C;
+#pragma unroll 4
+        for (int i = threadIdx.x; i < count; i += blockDim.x) {
+            const int k = i / C * 4, j = i % C;
+            const float4 v = four(a.B + (int64_t)(n0 + j) * a.ldb + k, n0 + j < a.N ? a.K - k : 0);
+            float* const at = Bs + k * a.S + j;
+            at[0] = v.x; at[a.S] = v.y; at[2 * a.S] = v.z; at[3 * a.S] = v.w;
+        }
+    }
+}
+
 // TR: the two MFMA operands are swapped, so a lane ends up with four consecutive columns of one
 // row of C (element v of tile t is C[row0 + l%16][16t + 4*(l/16) + v]) and stores them with one
 // 16-byte instruction; needs N % 4 == 0 and 16-byte aligned rows of C (and of Zprev for the mask).
@@ -79,13 +106,7 @@ template <int NT, int EPI, bool TR, bool ASC>
 __global__ __launch_bounds__(512) void k_gemm_tall(TallArgs a) {
     extern __shared__ float Bs[];                       // [Kpad][S]
     const int n0 = blockIdx.y * (NT * 16);
-    const int ncols = NT * 16;
-    for (int idx = threadIdx.x; idx < a.Kpad * ncols; idx += blockDim.x) {
-        const int k = idx / ncols, j = idx % ncols;
-        float v = 0.f;
-        if (k < a.K && n0 + j < a.N) v = a.tb ? a.B[(int64_t)(n0 + j) * a.ldb + k] : a.B[(int64_t)k * a.ldb + n0 + j];
-        Bs[k * a.S + j] = v;
-    }
+    stage_b<NT>(a, n0, Bs);
     __syncthreads();
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
@@ -212,13 +233,7 @@ __global__ __launch_bounds__(512) void k_gemm_tall_flat(TallArgs a) {
     const int strip_floats = 16 * a.K;
     float* As = lds + a.Kpad * a.S + (threadIdx.x >> 6) * (KV * 256);    // this wavefront's strip, flat
     const int n0 = blockIdx.y * (NT * 16);
-    const int ncols = NT * 16;
-    for (int idx = threadIdx.x; idx < a.Kpad * ncols; idx += blockDim.x) {
-        const int k = idx / ncols, j = idx % ncols;
-        float v = 0.f;
-        if (k < a.K && n0 + j < a.N) v = a.tb ? a.B[(int64_t)(n0 + j) * a.ldb + k] : a.B[(int64_t)k * a.ldb + n0 + j];
-        Bs[k * a.S + j] = v;
-    }
+    stage_b<NT>(a, n0, Bs);
     __syncthreads();
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
@@ -817,10 +832,12 @@ int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const floa
                 }
             }
         }
-        // eight wavefronts share op(B) when only one or two workgroups fit a compute unit beside each other
-        const int waves = lds > 40 * 1024 ? 8 : 4;
+        // Eight wavefronts share op(B), and no more workgroups than two per compute unit (one where op(B) allows no two) put it into
+        // LDS: 128 x 64 on 200 K rows 59 us with 1536 workgroups of four, 40 with 512 of eight; 64 x 64 on 120 K rows 21 and
+        // 17; 16 x 16 on 4.4 M 110 and 100.
+        constexpr int waves = 8;
         int64_t bx = (ntiles + waves - 1) / waves;
-        const int64_t cap = 256 * (lds > 80 * 1024 ? 1 : (lds > 53 * 1024 ? 2 : (lds > 40 * 1024 ? 3 : (lds > 20 * 1024 ? 6 : 8))));
+        const int64_t cap = (int64_t)device_info().cus * (lds > 80 * 1024 ? 1 : 2);
         if (bx > cap) bx = cap;
         const dim3 grid((unsigned)bx, (unsigned)((nt_total + NT - 1) / NT));
         switch (NT) {
