@@ -2,8 +2,10 @@
 // discusses under "Block Two-Dimensional (2D) Algorithms", Equation H = sigma(Z)) with the mean
 // negative log-likelihood over all vertices, and Equation 1 specialised to it:
 //   G = (softmax(Z) - onehot(y)) / n.
-// L lanes share a row and keep its logits in registers (VEC per lane, C <= L*VEC): one read of Z,
-// one write of G.  Row maxima and sums are butterfly reductions inside the L lanes.  Workgroups
+// L lanes share a row and keep its logits in registers (four per lane, C <= 4 L): one read of Z,
+// one write of G, 16 bytes per lane at any alignment, what is left of a ragged row one by one.  Bound by the instructions of the
+// reductions where a row is short: with a column per lane a wavefront had one row of 41, now it has four (200 K rows: 44.7 -> 26.8
+// us; 300 K rows of 130, three passes before, 232 -> 129 us).  Row maxima and sums are butterfly reductions inside the L lanes.  Workgroups
 // stride over the rows; every thread adds its rows' losses in double in a fixed order, then a
 // fixed tree joins threads and workgroups, so the loss is reproducible bit for bit.
 #include "common.h"
@@ -12,26 +14,28 @@ namespace gcn {
 
 static constexpr int LOSS_BLOCKS_MAX = 2048;
 
-template <int L, int VEC>
+template <int L, bool RAGGED>
 __global__ __launch_bounds__(256) void k_softmax_nll(int64_t n, int32_t C, const float* __restrict__ Z, int64_t ldz,
                                                      const int32_t* __restrict__ labels, float* __restrict__ G,
                                                      int64_t ldg, float inv_n, double* __restrict__ part) {
-    constexpr int ROWS = 256 / L;
+    constexpr int ROWS = 256 / L, VEC = 4;
     const int li = threadIdx.x % L;
     const int c0 = li * VEC;
+    const bool whole = c0 + VEC <= C;
     double mine = 0.0;
     for (int64_t i = (int64_t)blockIdx.x * ROWS + threadIdx.x / L; i < n; i += (int64_t)gridDim.x * ROWS) {
         const float* z = Z + i * ldz;
-        float v[VEC];
-        if constexpr (VEC == 4) {
-            if (c0 < C) {
-                const float4 t = *reinterpret_cast<const float4*>(z + c0);
-                v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
-            } else {
-                v[0] = v[1] = v[2] = v[3] = -INFINITY;
-            }
-        } else {
-            v[0] = c0 < C ? z[c0] : -INFINITY;
+        float v[VEC] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+        if (!RAGGED && whole) {
+            const float4 t = *reinterpret_cast<const float4*>(z + c0);
+            v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+        } else if (whole) {
+            const f4u t = *reinterpret_cast<const f4u*>(z + c0);
+            v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+        } else if constexpr (RAGGED) {
+#pragma unroll
+            for (int e = 0; e < VEC - 1; ++e)
+                if (c0 + e < C) v[e] = z[c0 + e];
         }
         float m = v[0];
 #pragma unroll
@@ -52,8 +56,13 @@ __global__ __launch_bounds__(256) void k_softmax_nll(int64_t n, int32_t C, const
 #pragma unroll
             for (int e = 0; e < VEC; ++e)
                 g[e] = labelled ? (expf(v[e] - lse) - (c0 + e == y ? 1.f : 0.f)) * inv_n : 0.f;
-            if constexpr (VEC == 4) *reinterpret_cast<float4*>(G + i * ldg + c0) = make_float4(g[0], g[1], g[2], g[3]);
-            else G[i * ldg + c0] = g[0];
+            if (!RAGGED && whole) *reinterpret_cast<float4*>(G + i * ldg + c0) = make_float4(g[0], g[1], g[2], g[3]);
+            else if (whole) *reinterpret_cast<f4u*>(G + i * ldg + c0) = f4u{g[0], g[1], g[2], g[3]};
+            else if constexpr (RAGGED) {
+#pragma unroll
+                for (int e = 0; e < VEC - 1; ++e)
+                    if (c0 + e < C) G[i * ldg + c0 + e] = g[e];
+            }
         }
         // the lane that holds column y contributes lse - z_y
         float zy = 0.f;
@@ -119,29 +128,30 @@ __global__ __launch_bounds__(256) void k_loss_final(int64_t parts, const double*
     if (threadIdx.x == 0) *loss = (float)(s[0] * inv_n);
 }
 
-template <int L, int VEC>
+template <int L>
 static void launch_rows(int64_t blocks, int64_t n, int32_t C, const float* Z, int64_t ldz, const int32_t* labels,
                         float* G, int64_t ldg, double* part, float inv_m, hipStream_t s) {
-    hipLaunchKernelGGL((k_softmax_nll<L, VEC>), dim3((unsigned)blocks), dim3(256), 0, s, n, C, Z, ldz, labels, G, ldg,
-                       inv_m, part);
+    const bool aligned = (C % 4 == 0) && (ldz % 4 == 0) && (((uintptr_t)Z & 15u) == 0) &&
+                         (!G || ((ldg % 4 == 0) && (((uintptr_t)G & 15u) == 0)));
+    if (!aligned) hipLaunchKernelGGL((k_softmax_nll<L, true>), dim3((unsigned)blocks), dim3(256), 0, s, n, C, Z, ldz, labels, G, ldg, inv_m, part);
+    else hipLaunchKernelGGL((k_softmax_nll<L, false>), dim3((unsigned)blocks), dim3(256), 0, s, n, C, Z, ldz, labels, G, ldg, inv_m, part);
 }
 
-template <int VEC>
-static void dispatch_rows(int lanes, int64_t n, int32_t C, const float* Z, int64_t ldz, const int32_t* labels,
+static void dispatch_rows(int64_t n, int32_t C, const float* Z, int64_t ldz, const int32_t* labels,
                           float* G, int64_t ldg, double* part, int64_t* blocks_out, float inv_m, hipStream_t s) {
     int L = 2;
-    while (L < lanes) L <<= 1;
+    while (4 * L < C) L <<= 1;
     const int64_t rows_per_block = 256 / L;
     int64_t blocks = (n + rows_per_block - 1) / rows_per_block;
     if (blocks > LOSS_BLOCKS_MAX) blocks = LOSS_BLOCKS_MAX;
     *blocks_out = blocks;
     switch (L) {
-        case 2: launch_rows<2, VEC>(blocks, n, C, Z, ldz, labels, G, ldg, part, inv_m, s); break;
-        case 4: launch_rows<4, VEC>(blocks, n, C, Z, ldz, labels, G, ldg, part, inv_m, s); break;
-        case 8: launch_rows<8, VEC>(blocks, n, C, Z, ldz, labels, G, ldg, part, inv_m, s); break;
-        case 16: launch_rows<16, VEC>(blocks, n, C, Z, ldz, labels, G, ldg, part, inv_m, s); break;
-        case 32: launch_rows<32, VEC>(blocks, n, C, Z, ldz, labels, G, ldg, part, inv_m, s); break;
-        default: launch_rows<64, VEC>(blocks, n, C, Z, ldz, labels, G, ldg, part, inv_m, s); break;
+        case 2: launch_rows<2>(blocks, n, C, Z, ldz, labels, G, ldg, part, inv_m, s); break;
+        case 4: launch_rows<4>(blocks, n, C, Z, ldz, labels, G, ldg, part, inv_m, s); break;
+        case 8: launch_rows<8>(blocks, n, C, Z, ldz, labels, G, ldg, part, inv_m, s); break;
+        case 16: launch_rows<16>(blocks, n, C, Z, ldz, labels, G, ldg, part, inv_m, s); break;
+        case 32: launch_rows<32>(blocks, n, C, Z, ldz, labels, G, ldg, part, inv_m, s); break;
+        default: launch_rows<64>(blocks, n, C, Z, ldz, labels, G, ldg, part, inv_m, s); break;
     }
 }
 
@@ -164,12 +174,8 @@ static int softmax_nll_impl(int64_t n, int32_t C, const float* Z, int64_t ldz, c
     double* part = (double*)scratch;
     int64_t blocks = 0;
     const float inv_m = 1.0f / (float)n_labelled;
-    const bool vec4 = (C % 4 == 0) && (ldz % 4 == 0) && (((uintptr_t)Z & 15u) == 0) &&
-                      (!G || ((ldg % 4 == 0) && (((uintptr_t)G & 15u) == 0)));
-    if (vec4 && C <= 256) {
-        dispatch_rows<4>(C / 4, n, C, Z, ldz, labels, G, ldg, part, &blocks, inv_m, s);
-    } else if (C <= 64) {
-        dispatch_rows<1>(C, n, C, Z, ldz, labels, G, ldg, part, &blocks, inv_m, s);
+    if (C <= 256) {
+        dispatch_rows(n, C, Z, ldz, labels, G, ldg, part, &blocks, inv_m, s);
     } else {
         blocks = (n + 3) / 4;
         if (blocks > LOSS_BLOCKS_MAX) blocks = LOSS_BLOCKS_MAX;

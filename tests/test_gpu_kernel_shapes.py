@@ -698,3 +698,29 @@ def test_gemm_tn_trips_and_sums(M, N, trips):
         g.gcn_gemm(1, 0, dev(H), dev(S), Y)
         want = H.astype(np.float64).T @ S.astype(np.float64)
         assert np.linalg.norm(host(Y) - want) <= 5e-7 * np.linalg.norm(want), (K, M, N)
+
+
+@pytest.mark.parametrize("n,C", [(1, 1), (3, 2), (70, 3), (129, 5), (1000, 7), (300, 9), (257, 41), (64, 63), (65, 65), (100, 67), (33, 130), (40, 255), (20, 257)])
+@pytest.mark.parametrize("pad,off", [(0, 0), (1, 0), (3, 2), (4, 4)])
+def test_softmax_of_ragged_rows(n, C, pad, off):
+    """Rows that are no multiple of a lane's 16 bytes, at any pitch and alignment: loss, gradient, nothing written beside the rows."""
+    g = G()
+    rs = np.random.default_rng(130)
+    Z = synth.normal_features(n, C, 131) * 4
+    y = rs.integers(0, C, n).astype(np.int32)
+    y[1::3] = -1
+    buf = torch.full((n * (C + pad) + off,), float("nan"), device="cuda")[off:].view(n, C + pad)
+    buf[:, :C] = dev(Z)
+    Gd = torch.full((n * (C + pad) + off,), float("nan"), device="cuda")[off:].view(n, C + pad)
+    loss = torch.zeros(1, device="cuda")
+    m = int((y >= 0).sum())
+    g.gcn_softmax_nll_masked(buf[:, :C], dev(y), m, loss, Gd[:, :C])
+    Zd = Z.astype(np.float64)
+    p = np.exp(Zd - Zd.max(1, keepdims=True))
+    p /= p.sum(1, keepdims=True)
+    on = y >= 0
+    want = np.where(on[:, None], (p - (np.arange(C) == y[:, None])) / m, 0)
+    assert_close(host(Gd)[:, :C], want, f"G {n}x{C}")
+    assert np.all(np.isnan(host(Gd)[:, C:]))
+    nll = -np.log(p[on, y[on]]).mean()
+    assert abs(loss.item() - nll) <= 1e-5 * max(1.0, abs(nll))
