@@ -50,7 +50,22 @@ struct SplitArgs {
     int64_t ldzprev;
     float* carry;             // [nchunks][f]
     int lds_kb = 0;           // host side: GCN_CFG_SPLIT_LDS_KB
+    uint32_t per_xcd = 0;     // 0, or how many consecutive groups of chunks an XCD takes (see chunk_group)
 };
+
+// The group of WAVES_PER_BLOCK chunks that this workgroup takes.  Workgroups go to the XCDs in turn.  Over column blocks,
+// whose chunks come block by block, every XCD takes one stretch of them instead: a block of X is then fetched into the
+// one or two L2s whose XCDs walk it and not into all eight, which counts as long as the blocks are short of entries (5 M entries,
+// 150 K columns, four blocks: 187 -> 140 us at 64 columns, 95 -> 74 at 32; 6 M, 120 K, two blocks at 64: 126 -> 117; 119 M,
+// 233 K, seven blocks: no difference).  The panels of a product follow each other: each of them to its own XCDs took longer
+// where X is beyond the L2s (33 M entries, 128 columns: 1.37 -> 1.55 ms).
+static constexpr uint32_t XCDS = 8;
+__device__ __forceinline__ int64_t chunk_group(const SplitArgs& a) {
+    return a.per_xcd ? (int64_t)(blockIdx.x % XCDS) * a.per_xcd + blockIdx.x / XCDS : (int64_t)blockIdx.x;
+}
+static inline unsigned chunk_groups(const SplitArgs& a) {          // workgroups per panel
+    return a.per_xcd ? XCDS * a.per_xcd : (unsigned)((a.nchunks + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK);
+}
 
 // The index/value stream is read exactly once per product: load it with the non-temporal hint so
 // it does not push the gathered rows of X out of L2.
@@ -400,7 +415,7 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int64_t grp, Lds*
 template <int LPR, int VEC, int EPI, bool AHEAD = true>
 __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_split(SplitArgs a) {
     __shared__ WaveLds<LPR, VEC, EPI == GCN_EPI_MASK && AHEAD> lds[WAVES_PER_BLOCK];
-    split_body<LPR, VEC, EPI, AHEAD>(a, blockIdx.x, lds);
+    split_body<LPR, VEC, EPI, AHEAD>(a, chunk_group(a), lds);
 }
 
 // The same product for matrices of few chunks, which is a chain of memory latencies, launches and first executions of
@@ -817,7 +832,7 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_line(SplitArgs a)
     typedef const __attribute__((address_space(1))) char* Global;
     constexpr int UNR = 16;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t c = (int64_t)blockIdx.x * WAVES_PER_BLOCK + wave;
+    const int64_t c = chunk_group(a) * WAVES_PER_BLOCK + wave;
     if (c >= a.nchunks) return;
     int col0;                                   // (lanes without columns follow the last one that has some)
     const bool col_ok = lane_columns<64, VEC>(a.f, blockIdx.y, gridDim.y, lane, &col0);
@@ -1124,7 +1139,7 @@ static int launch_few(const SplitArgs& args, int epilogue, hipStream_t s) {
 template <int LPR, int VEC>
 static int launch_split(const SplitArgs& args, int epilogue, hipStream_t s) {
     const int tile = LPR * VEC;
-    const dim3 grid((unsigned)((args.nchunks + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK), (unsigned)((args.f + tile - 1) / tile));
+    const dim3 grid(chunk_groups(args), (unsigned)((args.f + tile - 1) / tile));
     const dim3 block(64 * WAVES_PER_BLOCK);
     const size_t pad = occupancy_pad<LPR, VEC>(args.lds_kb, epilogue);
     timing_begin(s);
@@ -1148,7 +1163,7 @@ static int launch_split(const SplitArgs& args, int epilogue, hipStream_t s) {
 
 template <int VEC>
 static int launch_line(const SplitArgs& args, int epilogue, hipStream_t s) {
-    const dim3 grid((unsigned)((args.nchunks + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK), (unsigned)((args.f + 64 * VEC - 1) / (64 * VEC)));
+    const dim3 grid(chunk_groups(args), (unsigned)((args.f + 64 * VEC - 1) / (64 * VEC)));
     const dim3 block(64 * WAVES_PER_BLOCK);
     timing_begin(s);
     switch (epilogue) {
@@ -1592,8 +1607,10 @@ static const SpmmPlan& plan_of(gcn_csr* a, Matrix& m, int32_t f, int64_t usual) 
     int heavy_blocks = 1;
     const int32_t W = f <= 16 ? 16 : 32;
     const double sweep = c.sweep(m.lengths, lines, m.nrows, m.ncols, HEAVY, sweep_rows(W), SWEEP_TASKS, parts, &heavy_blocks);
-    // ragged rows in two panels straddle lines twice (41 columns: no gain)
-    p.sweep = sweep < 0.87 * split && (f % 4 == 0 || f < 32);
+    // Above 0.84 the hub schedule, which this does not estimate, may be as fast (246 M entries, 14 M vertices, R-MAT at 16 columns:
+    // 0.86, both 2.98 ms), and the sweep's copy takes longer to build.  Ragged rows in two panels straddle lines twice (41
+    // columns: no gain).
+    p.sweep = sweep < 0.84 * split && (f % 4 == 0 || f < 32);
     if (p.sweep) {
         p.blocks = heavy_blocks;
         p.parts = parts;
@@ -1654,6 +1671,7 @@ static int run_matrix(gcn_csr* a, Matrix& mm, const int32_t* row_map, int64_t nn
         args.ne_rows = nullptr; args.rp = b.rp; args.row_scale = nullptr;     // the scale belongs to the reduced row
         args.fix_list = b.fix_list; args.n_fix = b.n_fix; args.n_fix_long = b.n_fix_long;
         args.Z = a->partial; args.ldz = f; args.Zprev = nullptr; args.ldzprev = 0;
+        args.per_xcd = (uint32_t)((mm.nchunks + XCDS * WAVES_PER_BLOCK - 1) / (XCDS * WAVES_PER_BLOCK));
         GCN_TRY(run_split(args, GCN_EPI_NONE, s, choice));
         if (f >= 4) return launch_block_reduce<4>(mm.nrows, f, b, row_map, o.row_scale, o.accumulate ? 1 : 0, a->partial, Z, ldz, epilogue, Zprev, ldzprev, s);
         return launch_block_reduce<1>(mm.nrows, f, b, row_map, o.row_scale, o.accumulate ? 1 : 0, a->partial, Z, ldz, epilogue, Zprev, ldzprev, s);

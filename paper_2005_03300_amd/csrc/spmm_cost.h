@@ -8,7 +8,9 @@
 // timed products (uniform, R-MAT and Chung-Lu graphs of 60 K to 4 M vertices, 26 to 490 entries per row, 16 to 128
 // columns, 1 to 32 blocks, both schedules): estimates are within 9 % (blocks) and 11 % (sweep) of the times in the root
 // mean square, and the blocks chosen cost 2 to 4 % more than the best on average, where the rule by sizes alone
-// (blocks of 2 MB, rows of 24 entries per block) costs 9 %, up to 42 %.
+// (blocks of 2 MB, rows of 24 entries per block) costs 9 %, up to 42 %.  The cost of a partial row and the share of the blocks
+// that an XCD walks were set again when the XCDs took stretches of the blocks (see chunk_group): estimates over 2 to 16 blocks of
+// seven graphs within 12 % at 16, 32 and 64 columns.
 #pragma once
 #include <stdint.h>
 
@@ -97,7 +99,8 @@ struct SpmmCost {
     // Nonzero-split over `blocks` column blocks of the rows `rows` (microseconds); `lines` of the whole matrix.
     double split(const Lengths& rows, const Lengths& lines, int blocks) const {
         const double nnz = (double)rows.total(), fetched = nnz * passes();
-        const double m = misses(lines, 1.0 / blocks, nnz / xcds / blocks, false) * xcds * blocks * passes() + fetched * 8 / 128;
+        const double each = std::max(1.0, blocks / xcds);        // blocks that an XCD walks: each is in one of their L2s
+        const double m = misses(lines, 1.0 / blocks, nnz / xcds / each, false) * xcds * each * passes() + fetched * 8 / 128;
         const bool narrow = f <= 16;
         const double served = fetched / (narrow ? 228e3 : 174e3), filled = m / (narrow ? 67.9e3 : 57.2e3);
         const double e = narrow ? 1.94 : 4.6;
@@ -107,18 +110,18 @@ struct SpmmCost {
             for (int b = 0; b < Lengths::BINS; ++b)
                 if (rows.rows[b] > 0)
                     partial += (double)rows.rows[b] * blocks * (1.0 - std::pow(1.0 - 1.0 / blocks, (double)rows.entries[b] / (double)rows.rows[b]));
-            t += partial * f * 4 * (narrow ? 0.518e-6 : 0.453e-6) + 7.6;
+            t += partial * f * 4 * (narrow ? 0.47e-6 : 0.43e-6) + 7.6;
         }
         return t;
     }
 
-    // The number of blocks that costs least, `usual` unless another is 10 % better (the estimate's own error).  Up to 16 columns no
+    // The number of blocks that costs least, `usual` unless another is 6 % better.  Up to 16 columns no
     // fewer than usual (15 M pairs, R-MAT, 150 K vertices: 122 us over five, 131 over one, estimated 117 and 103).
     int best_blocks(const Lengths& rows, const Lengths& lines, int64_t ncols, int usual, double* cost) const {
         static const int tried[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96};
         int best = usual;
         double least = split(rows, lines, usual);
-        const double keep = least * 0.9;
+        const double keep = least * 0.94;
         for (int b : tried) {
             if (b == usual || (b > 1 && ncols / b < 2048) || (f <= 16 && b < usual)) continue;
             const double t = split(rows, lines, b);

@@ -724,3 +724,24 @@ def test_softmax_of_ragged_rows(n, C, pad, off):
     assert np.all(np.isnan(host(Gd)[:, C:]))
     nll = -np.log(p[on, y[on]]).mean()
     assert abs(loss.item() - nll) <= 1e-5 * max(1.0, abs(nll))
+
+
+@pytest.mark.parametrize("chunks", [769, 772, 799, 800, 801, 831, 833])
+@pytest.mark.parametrize("f", [16, 31, 41, 64])
+def test_column_blocks_walked_by_one_xcd_each(chunks, f):
+    """Over column blocks an XCD takes one stretch of the chunks: numbers of chunks that leave the last stretch short, or the last
+    workgroup without one, in both kernels that take so many chunks."""
+    g = G()
+    lengths = np.full(chunks, 512)
+    lengths[::9] -= 40
+    lengths[4::9] += 40
+    lengths[-1] = chunks * 512 - int(lengths[:-1].sum()) - 3
+    rowptr, colidx, val = _rows_matrix(lengths, 2500, 132)
+    X = synth.uniform_features(2500, f, 133)
+    a = g.gcn_csr_create_from_csr_rect(len(lengths), 2500, dev(rowptr), dev(colidx), dev(val), 0)
+    g.gcn_csr_config(a, g.CFG_SPMM_BLOCKS, 2)
+    Zd = torch.full((len(lengths), f), float("nan"), device="cuda")
+    g.gcn_spmm(a, 0, dev(X), Zd)
+    A = torch.sparse_csr_tensor(torch.from_numpy(rowptr), torch.from_numpy(colidx).long(), torch.from_numpy(val).double(), (len(lengths), 2500))
+    assert_close(host(Zd), (A @ torch.from_numpy(X).double()).numpy(), f"{chunks} chunks f={f}")
+    a.close()
