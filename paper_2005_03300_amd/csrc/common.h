@@ -352,7 +352,7 @@ int fused_last_launch(int64_t n, int32_t C, const float* T, const float* W, cons
                       float* loss, float* Y, float* S, const float* s_scale, float* Zout, float* Gout, void* scratch,
                       hipStream_t s);
 int colsum_launch(int64_t rows, int32_t cols, const float* G, int64_t ldg, float* out, hipStream_t s);
-int axpy_launch(int64_t count, float* W, const float* Y, float lr, hipStream_t s);
+int update_launch(int32_t L, const int32_t* dims, float* const* W, float* const* Y, float lr, hipStream_t s);
 int relu_launch(int64_t rows, int32_t cols, const float* Z, int64_t ldz, float* H, int64_t ldh, hipStream_t s);
 // Z (dense rows) += 1 bias^T, then max(Z, 0) in place (relu) or, when H is given, into H
 int bias_add_launch(int64_t rows, int32_t cols, float* Z, const float* bias, int relu, float* H, hipStream_t s);

@@ -140,9 +140,18 @@ __global__ void k_inv_sqrt_deg(int64_t n, const int32_t* __restrict__ deg, float
     if (i < n) out[i] = deg[i] > 0 ? (float)__ddiv_rn(1.0, __dsqrt_rn((double)deg[i])) : 0.f;
 }
 
-__global__ void k_axpy(int64_t count, float* __restrict__ W, const float* __restrict__ Y, float lr) {
+// W = W - lr Y of several layers, a layer per y.  The matrices are a few thousand numbers each, so a launch is what the update
+// costs (4.6 us between large kernels): one for all of them.
+struct UpdateArgs {
+    static constexpr int LAYERS = 16;
+    int64_t count[LAYERS];
+    float* W[LAYERS];
+    const float* Y[LAYERS];
+};
+__global__ void k_update(UpdateArgs a, float lr) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < count) W[t] = W[t] - lr * Y[t];
+    float* const W = a.W[blockIdx.y];
+    if (t < a.count[blockIdx.y]) W[t] = W[t] - lr * a.Y[blockIdx.y][t];
 }
 
 static inline unsigned nblocks(int64_t work) { return (unsigned)((work + 255) / 256 > 0 ? (work + 255) / 256 : 1); }
@@ -258,9 +267,27 @@ int inv_sqrt_deg_launch(int64_t n, const int32_t* deg, float* out, hipStream_t s
     return GCN_OK;
 }
 
-int axpy_launch(int64_t count, float* W, const float* Y, float lr, hipStream_t s) {
-    hipLaunchKernelGGL(k_axpy, dim3(nblocks(count)), dim3(256), 0, s, count, W, Y, lr);
-    GCN_LAUNCH_CHECK();
+// The layers in turn, those of a launch side by side: a layer whose W is also the W or the Y of another one in the launch (tied
+// weights) starts the next launch.
+int update_launch(int32_t L, const int32_t* dims, float* const* W, float* const* Y, float lr, hipStream_t s) {
+    auto meet = [](const float* p, int64_t np, const float* q, int64_t nq) { return p < q + nq && q < p + np; };
+    for (int l = 0; l < L;) {
+        UpdateArgs a;
+        int k = 0;
+        int64_t most = 0;
+        for (; l < L && k < UpdateArgs::LAYERS; ++l, ++k) {
+            const int64_t count = (int64_t)dims[l] * dims[l + 1];
+            bool apart = true;
+            for (int j = 0; j < k; ++j)
+                apart = apart && !meet(W[l], count, a.W[j], a.count[j]) && !meet(W[l], count, a.Y[j], a.count[j]) &&
+                        !meet(Y[l], count, a.W[j], a.count[j]);
+            if (!apart) break;
+            a.count[k] = count; a.W[k] = W[l]; a.Y[k] = Y[l];
+            most = count > most ? count : most;
+        }
+        hipLaunchKernelGGL(k_update, dim3(nblocks(most), (unsigned)k), dim3(256), 0, s, a, lr);
+        GCN_LAUNCH_CHECK();
+    }
     return GCN_OK;
 }
 

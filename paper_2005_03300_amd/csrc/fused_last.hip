@@ -18,7 +18,7 @@
 //   3. Y tiles += T^T G over the 16 rows of the strip: here the row index is the contraction index, which
 //      both operand layouts keep in l/16, so G goes through 16 x 16 transpositions in LDS, four tiles at a time.
 // Y accumulates in registers over all strips of a wavefront; the wavefronts of a workgroup are added in a fixed
-// order in LDS, the workgroups by two small kernels in a fixed order: bit-reproducible.
+// order in LDS, the workgroups by a small kernel in a fixed order: bit-reproducible.
 #include "common.h"
 
 namespace gcn {
@@ -26,7 +26,6 @@ namespace gcn {
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 static constexpr int FUSED_BLOCKS_MAX = 2048;
-static constexpr int FUSED_FOLD = 32;
 
 struct FusedArgs {
     int64_t n;
@@ -462,29 +461,52 @@ __global__ __launch_bounds__(256, 3) void k_fused_last_wide(FusedArgs a) {
     if (threadIdx.x == 0) a.lpart[blockIdx.x] = (s_w[0] + s_w[1]) + (s_w[2] + s_w[3]);
 }
 
-// folded[j][e] = sum over the workgroups b = j, j + FOLD, j + 2 FOLD, ... of part[b][e], in that order
-__global__ __launch_bounds__(256) void k_fused_fold(int count, int blocks, const float* __restrict__ part,
-                                                    float* __restrict__ folded) {
-    const int e = blockIdx.x * 256 + threadIdx.x;
-    const int j = blockIdx.y;
-    if (e >= count) return;
+// Y and the loss from the workgroups' partial results.  16 columns of a row of Y per workgroup, a partial result each for
+// its 64 groups of threads, eight of them in flight (one after another, as the compiler left them, 64 waits for memory made
+// 24 us of this); every group's sum, then the 64 of them in pairs.  One more workgroup adds the loss.  2048 partial results of 512
+// numbers: 8 us, 24 + 9 + 5 in three launches before.
+__global__ __launch_bounds__(1024) void k_fused_y(int C, int CP, int blocks, const float* __restrict__ part, float* __restrict__ Y,
+                                                  const double* __restrict__ lpart, double inv_m, float* __restrict__ loss) {
+    constexpr int GROUPS = 64, AHEAD = 8;
+    __shared__ float s_y[GROUPS][16];
+    __shared__ double s_l[256];
+    const int i = threadIdx.x % 16, j = threadIdx.x / 16;
+    if ((int)blockIdx.x == CP) {                                // the loss
+        double acc = 0.0;
+        if (threadIdx.x < 256) {
+            for (int b = threadIdx.x; b < blocks; b += 256) acc += lpart[b];
+            s_l[threadIdx.x] = acc;
+        }
+        __syncthreads();
+        for (int d = 128; d >= 1; d >>= 1) {
+            if ((int)threadIdx.x < d) s_l[threadIdx.x] += s_l[threadIdx.x + d];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) *loss = (float)(s_l[0] * inv_m);
+        return;
+    }
+    const int e = blockIdx.x * 16 + i;                          // of 16 CP numbers
+    const size_t count = (size_t)16 * CP;
+    const float* p = part + e;
     float acc = 0.f;
-    for (int b = j; b < blocks; b += FUSED_FOLD) acc += part[(size_t)b * count + e];
-    folded[(size_t)j * count + e] = acc;
+    int b = j;
+    for (; b + (AHEAD - 1) * GROUPS < blocks; b += AHEAD * GROUPS) {
+        float x[AHEAD];
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) x[u] = p[(size_t)(b + u * GROUPS) * count];
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) acc += x[u];
+    }
+    for (; b < blocks; b += GROUPS) acc += p[(size_t)b * count];
+    s_y[j][i] = acc;
+    __syncthreads();
+    for (int d = GROUPS / 2; d >= 1; d >>= 1) {
+        if (j < d) s_y[j][i] += s_y[j + d][i];
+        __syncthreads();
+    }
+    const int k = e / CP, c = e % CP;
+    if (j == 0 && c < C) Y[k * C + c] = s_y[0][i];
 }
-
-// Y[k][c] = sum over j of folded[j][k][c] for the C real columns
-__global__ __launch_bounds__(256) void k_fused_y(int C, int CP, int parts, const float* __restrict__ folded,
-                                                 float* __restrict__ Y) {
-    const int e = blockIdx.x * 256 + threadIdx.x;
-    if (e >= 16 * C) return;
-    const int k = e / C, c = e % C;
-    float acc = 0.f;
-    for (int j = 0; j < parts; ++j) acc += folded[(size_t)j * 16 * CP + k * CP + c];
-    Y[k * C + c] = acc;
-}
-
-int loss_final_launch(int64_t parts, const double* part, double inv_n, float* loss, hipStream_t s);
 
 static int fused_nt(int32_t C) {
     const int need = (C + 15) / 16;
@@ -505,7 +527,7 @@ size_t fused_last_scratch_bytes(int64_t n, int32_t C) {
     const int NT = fused_nt(C);
     if (!NT) return 0;
     const size_t per = (size_t)16 * 16 * NT * sizeof(float);
-    return (size_t)(fused_blocks(n) + FUSED_FOLD) * per + (size_t)FUSED_BLOCKS_MAX * sizeof(double);
+    return (size_t)fused_blocks(n) * per + (size_t)FUSED_BLOCKS_MAX * sizeof(double);
 }
 
 template <int NT>
@@ -537,8 +559,7 @@ int fused_last_launch(int64_t n, int32_t C, const float* T, const float* W, cons
     a.n = n; a.C = C; a.T = T; a.W = W; a.labels = labels; a.inv_m = 1.0f / (float)n_labelled;
     a.S = S; a.s_scale = s_scale; a.Zout = Zout; a.Gout = Gout;
     a.ypart = (float*)scratch;
-    float* folded = a.ypart + (size_t)blocks * count;
-    a.lpart = (double*)(folded + (size_t)FUSED_FOLD * count);
+    a.lpart = (double*)(a.ypart + (size_t)blocks * count);
     switch (NT) {
         case 1: launch_fused<1>(a, blocks, s); break;
         case 2: launch_fused<2>(a, blocks, s); break;
@@ -548,14 +569,10 @@ int fused_last_launch(int64_t n, int32_t C, const float* T, const float* W, cons
         default: launch_fused_wide<4>(a, blocks, s); break;
     }
     GCN_LAUNCH_CHECK();
-    const int parts = blocks < FUSED_FOLD ? (int)blocks : FUSED_FOLD;
-    hipLaunchKernelGGL(k_fused_fold, dim3((unsigned)((count + 255) / 256), (unsigned)parts), dim3(256), 0, s, count,
-                       (int)blocks, (const float*)a.ypart, folded);
+    hipLaunchKernelGGL(k_fused_y, dim3((unsigned)(16 * NT + 1)), dim3(1024), 0, s, (int)C, 16 * NT, (int)blocks,
+                       (const float*)a.ypart, Y, (const double*)a.lpart, 1.0 / (double)n_labelled, loss);
     GCN_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_fused_y, dim3((unsigned)((16 * C + 255) / 256)), dim3(256), 0, s, (int)C, 16 * NT, parts,
-                       (const float*)folded, Y);
-    GCN_LAUNCH_CHECK();
-    return loss_final_launch(blocks, a.lpart, 1.0 / (double)n_labelled, loss, s);
+    return GCN_OK;
 }
 
 }  // namespace gcn

@@ -291,8 +291,7 @@ static int epoch_impl(gcn_csr* a, int32_t L_w, const int32_t* dims, const float*
                                     layer_order(l), s, at(lay.XS), true));
     }
     PhaseTimer pt(s, GCN_PHASE_OTHER);
-    if (lr != 0.f)
-        for (int l = 0; l < L_w; ++l) GCN_TRY(axpy_launch((int64_t)dims[l] * dims[l + 1], W[l], Y[l], lr, s));
+    if (lr != 0.f) GCN_TRY(update_launch(L_w, dims, W, Y, lr, s));
     return GCN_OK;
 }
 

@@ -745,3 +745,53 @@ def test_column_blocks_walked_by_one_xcd_each(chunks, f):
     A = torch.sparse_csr_tensor(torch.from_numpy(rowptr), torch.from_numpy(colidx).long(), torch.from_numpy(val).double(), (len(lengths), 2500))
     assert_close(host(Zd), (A @ torch.from_numpy(X).double()).numpy(), f"{chunks} chunks f={f}")
     a.close()
+
+
+@pytest.mark.parametrize("strips", [1, 3, 4, 5, 252, 256, 257, 2044, 2052, 8192, 8199])
+@pytest.mark.parametrize("C", [3, 16, 41, 130])
+def test_last_layer_sums_of_workgroups(strips, C):
+    """The fused last layer's weight gradient and loss from 1 to 2048 workgroups' partial results: fewer than the 64 groups of threads that
+    add them, a multiple of eight times as many, and others; the last strip is short."""
+    g = G()
+    n = strips * 16 - 5
+    rs = np.random.default_rng(134)
+    P0, W = synth.normal_features(n, 16, 135), synth.normal_features(16, C, 136) * np.float32(0.3)
+    y = rs.integers(0, C, n).astype(np.int32)
+    y[2::5] = -1
+    a = g.gcn_csr_create(n, dev(np.zeros(1, np.int32)), dev(np.zeros(1, np.int32)), g.ADD_SELF_LOOPS | g.NORM_SYM | g.SYMMETRISE | g.BUILD_TRANSPOSE)
+    Y, loss = torch.full((16, C), float("nan"), device="cuda"), torch.zeros(1, device="cuda")
+    ws = torch.empty(g.gcn_epoch_workspace_bytes(n, [16, C]), dtype=torch.uint8, device="cuda")
+    m = int((y >= 0).sum())
+    g.gcn_epoch_preaggregated(a, [16, C], dev(P0), dev(y), m, [dev(W)], [Y], 0.0, loss, ws)
+    Z = P0.astype(np.float64) @ W
+    lse = np.log(np.exp(Z - Z.max(1, keepdims=True)).sum(1)) + Z.max(1)
+    Gd = np.where((y >= 0)[:, None], (np.exp(Z - lse[:, None]) - (np.arange(C) == y[:, None])) / m, 0)
+    assert_close(host(Y), P0.T.astype(np.float64) @ Gd, f"Y {strips} {C}")
+    nll = (lse - Z[np.arange(n), np.maximum(y, 0)])[y >= 0].mean()
+    assert abs(loss.item() - nll) <= 1e-5 * max(1.0, abs(nll))
+    a.close()
+
+
+@pytest.mark.parametrize("tied", [[], [(1, 2)], [(0, 1), (1, 2), (16, 17)], [(3, 18)]])
+def test_update_of_many_and_of_tied_layers(tied):
+    """All layers' W are updated side by side, more of them than a launch takes, and one after another where they share a matrix."""
+    g = G()
+    rs = np.random.default_rng(137)
+    n, L = 200, 20
+    dims = [6] * (L + 1)
+    a = g.gcn_csr_create(n, *[dev(rs.integers(0, n, 800).astype(np.int32)) for _ in range(2)], g.ADD_SELF_LOOPS | g.NORM_SYM | g.SYMMETRISE | g.BUILD_TRANSPOSE)
+    W = [dev(np.eye(6, dtype=np.float32) + synth.normal_features(6, 6, 138 + l) * np.float32(0.1)) for l in range(L)]
+    for l, k in tied:
+        W[k] = W[l]
+    Y = [torch.empty(6, 6, device="cuda") for _ in range(L)]
+    H0, y, loss = dev(np.abs(synth.normal_features(n, 6, 139))), dev(rs.integers(0, 6, n).astype(np.int32)), torch.zeros(1, device="cuda")
+    ws = torch.empty(g.gcn_epoch_workspace_bytes(n, dims), dtype=torch.uint8, device="cuda")
+    g.gcn_epoch(a, dims, H0, y, W, Y, 0.0, loss, ws)
+    want, gradients = {w.data_ptr(): host(w).copy() for w in W}, [host(v).copy() for v in Y]
+    for w, v in zip(W, gradients):
+        want[w.data_ptr()] -= np.float32(0.5) * v
+    g.gcn_epoch(a, dims, H0, y, W, Y, 0.5, loss, ws)
+    for w, v, k in zip(W, gradients, range(L)):
+        assert np.array_equal(host(Y[k]), v) and np.abs(v).max() > 0, k
+        assert np.allclose(host(w), want[w.data_ptr()], rtol=3e-7, atol=1e-9), k       # a rounding of the product may be fused away
+    a.close()
