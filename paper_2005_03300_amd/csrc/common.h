@@ -312,6 +312,15 @@ void free_matrix(Matrix& m);
 
 // Variants of the sparse product: `pattern` ignores the stored values (every entry counts as 1),
 // `row_scale` multiplies output row i by row_scale[i] before the epilogue.
+// What a layer does with its product: Z = product + bias, and ReLU in place or into H (rows as far apart as those of Z).  Some of the
+// schedules do it where they store a row and set `done`; behind the others it is a pass of its own.
+static constexpr int EPI_LAYER = 3;       // internal epilogue, beside GCN_EPI_*
+struct LayerEnd {
+    const float* bias = nullptr;
+    float* H = nullptr;
+    bool relu = false;                    // in place
+    bool done = false;
+};
 struct SpmmOpt {
     bool pattern = false;
     const float* row_scale = nullptr;
@@ -321,6 +330,7 @@ struct SpmmOpt {
     // alone: where a sum is zero to rounding another order puts it on the other side, and every such element moves
     // the gradient of the weights by 1e-4 of its norm.
     bool any_schedule = false;
+    LayerEnd* end = nullptr;          // only with the epilogue GCN_EPI_NONE
     // internal to the hub schedule:
     const uint8_t* defer = nullptr;   // rows whose sum is stored raw (no scale, no epilogue)
     bool accumulate = false;          // column-blocked reduce adds to what Z already holds

@@ -49,6 +49,9 @@ struct SplitArgs {
     const float* Zprev;
     int64_t ldzprev;
     float* carry;             // [nchunks][f]
+    const float* bias = nullptr;        // with EPI_LAYER (see LayerEnd)
+    float* H = nullptr;
+    int relu = 0;
     int lds_kb = 0;           // host side: GCN_CFG_SPLIT_LDS_KB
     uint32_t per_xcd = 0;     // 0, or how many consecutive groups of chunks an XCD takes (see chunk_group)
 };
@@ -144,6 +147,24 @@ __device__ __forceinline__ void epilogue_store(float* z, const float* zprev, flo
         for (int e = 0; e < VEC; ++e) v[e] = m[e] > 0.f ? v[e] : 0.f;
     }
     store_vec<VEC>(z, v);
+}
+
+// The end of a layer: the same roundings as a product and a pass of its own, so no multiply-add.
+template <int VEC>
+__device__ __forceinline__ void layer_store(float* z, float* h, const float* bias, int relu, float (&v)[VEC], float scale) {
+#pragma clang fp contract(off)
+    float b[VEC] = {};
+    if (bias) load_vec<VEC>(b, bias);
+    float r[VEC];
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+        v[e] = v[e] * scale;
+        if (bias) v[e] = v[e] + b[e];
+        r[e] = v[e] > 0.f ? v[e] : 0.f;
+        if (relu) v[e] = r[e];
+    }
+    store_vec<VEC>(z, v);
+    if (h) store_vec<VEC>(h, r);
 }
 
 // Row `row` of a matrix whose rows are `pitch` bytes apart: one multiply-add of 32 by 32 bits.  Pitches of 4 GB and more
@@ -287,7 +308,12 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int64_t grp, Lds*
     const float* const xbase = a.X + col0;
     const uint32_t xpitch = (uint32_t)a.ldx * 4u, zpitch = (uint32_t)a.ldz * 4u;
     auto z_row = [&]() { return const_cast<float*>(at_row(a.Z + col0, (uint32_t)row & 0x7fffffffu, zpitch)); };
+    float bias[VEC] = {};                       // in registers: a row's end must not wait for memory
+    if constexpr (EPI == EPI_LAYER) {
+        if (a.bias && col_ok) load_vec<VEC>(bias, a.bias + col0);
+    }
     auto store_row = [&]() {
+#pragma clang fp contract(off)                  // the bias is added to the rounded product (see layer_store)
         float v[VEC];
 #pragma unroll
         for (int u = 0; u < VEC; ++u) v[u] = acc[u] * scale;    // exact for scale = 1, which a raw sum has
@@ -302,6 +328,16 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int64_t grp, Lds*
         } else if constexpr (EPI == GCN_EPI_MASK) {
 #pragma unroll
             for (int u = 0; u < VEC; ++u) v[u] = through >> u & 1 || row < 0 ? v[u] : 0.f;
+        }
+        if constexpr (EPI == EPI_LAYER) {
+            float r[VEC];
+#pragma unroll
+            for (int u = 0; u < VEC; ++u) {
+                if (a.bias) v[u] = v[u] + bias[u];
+                r[u] = v[u] > 0.f ? v[u] : 0.f;
+                if (a.relu) v[u] = r[u];
+            }
+            if (a.H) store_vec<VEC>(const_cast<float*>(at_row(a.H + col0, (uint32_t)row & 0x7fffffffu, zpitch)), r);
         }
         store_vec<VEC>(z_row(), v);
     };
@@ -1028,8 +1064,10 @@ __global__ __launch_bounds__(256) void k_spmm_fixup(SplitArgs a) {
     }
 #pragma unroll
     for (int v = 0; v < VEC; ++v) cur[v] += sum[v];
-    epilogue_store<VEC, EPI>(z, EPI == GCN_EPI_MASK ? a.Zprev + row * a.ldzprev + col0 : nullptr, cur,
-                             a.row_scale ? a.row_scale[row] : 1.f, a.defer && a.defer[row]);
+    const float scale = a.row_scale ? a.row_scale[row] : 1.f;
+    if constexpr (EPI == EPI_LAYER)
+        layer_store<VEC>(z, a.H ? a.H + row * a.ldz + col0 : nullptr, a.bias ? a.bias + col0 : nullptr, a.relu, cur, scale);
+    else epilogue_store<VEC, EPI>(z, EPI == GCN_EPI_MASK ? a.Zprev + row * a.ldzprev + col0 : nullptr, cur, scale, a.defer && a.defer[row]);
 }
 
 // Rows without stored entries produce zeros (any epilogue maps 0 to 0).
@@ -1099,6 +1137,7 @@ static int launch_fixup(const SplitArgs& args, int epilogue, hipStream_t s) {
     switch (epilogue) {
         case GCN_EPI_NONE: hipLaunchKernelGGL((k_spmm_fixup<LPR, VEC, GCN_EPI_NONE>), grid, dim3(256), 0, s, args); break;
         case GCN_EPI_RELU: hipLaunchKernelGGL((k_spmm_fixup<LPR, VEC, GCN_EPI_RELU>), grid, dim3(256), 0, s, args); break;
+        case EPI_LAYER: hipLaunchKernelGGL((k_spmm_fixup<LPR, VEC, EPI_LAYER>), grid, dim3(256), 0, s, args); break;
         default: hipLaunchKernelGGL((k_spmm_fixup<LPR, VEC, GCN_EPI_MASK>), grid, dim3(256), 0, s, args); break;
     }
     GCN_LAUNCH_CHECK();
@@ -1146,6 +1185,9 @@ static int launch_split(const SplitArgs& args, int epilogue, hipStream_t s) {
     switch (epilogue) {
         case GCN_EPI_NONE: hipLaunchKernelGGL((k_spmm_split<LPR, VEC, GCN_EPI_NONE>), grid, block, pad, s, args); break;
         case GCN_EPI_RELU: hipLaunchKernelGGL((k_spmm_split<LPR, VEC, GCN_EPI_RELU>), grid, block, pad, s, args); break;
+        case EPI_LAYER:                         // (run_matrix)
+            if constexpr (VEC == 4) hipLaunchKernelGGL((k_spmm_split<LPR, VEC, EPI_LAYER>), grid, block, pad, s, args);
+            break;
         default:
             if constexpr (VEC == 4 && LPR == 8) {
                 if (many_row_starts(args)) {
@@ -1238,7 +1280,7 @@ __global__ __launch_bounds__(256) void k_block_reduce(int64_t n, int32_t f, int3
                                                       const int32_t* __restrict__ rq_idx, const int32_t* __restrict__ row_map,
                                                       const float* __restrict__ row_scale, const float* __restrict__ P,
                                                       float* __restrict__ Z, int64_t ldz, const float* __restrict__ Zprev,
-                                                      int64_t ldzprev, int accumulate) {
+                                                      int64_t ldzprev, int accumulate, LayerEnd end) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t i = t / lanes;
     int col0 = (int)(t % lanes) * VEC;
@@ -1255,21 +1297,26 @@ __global__ __launch_bounds__(256) void k_block_reduce(int64_t n, int32_t f, int3
 #pragma unroll
         for (int v = 0; v < VEC; ++v) acc[v] += part[v];
     }
-    epilogue_store<VEC, EPI>(Z + row * ldz + col0, EPI == GCN_EPI_MASK ? Zprev + row * ldzprev + col0 : nullptr, acc,
-                             row_scale ? row_scale[row] : 1.f);
+    const float scale = row_scale ? row_scale[row] : 1.f;
+    if constexpr (EPI == EPI_LAYER)
+        layer_store<VEC>(Z + row * ldz + col0, end.H ? end.H + row * ldz + col0 : nullptr, end.bias ? end.bias + col0 : nullptr, end.relu,
+                         acc, scale);
+    else epilogue_store<VEC, EPI>(Z + row * ldz + col0, EPI == GCN_EPI_MASK ? Zprev + row * ldzprev + col0 : nullptr, acc, scale);
 }
 
 template <int VEC>
 static int launch_block_reduce(int64_t n, int32_t f, const Blocked& b, const int32_t* row_map, const float* row_scale,
                                int accumulate, const float* P, float* Z,
-                               int64_t ldz, int epilogue, const float* Zprev, int64_t ldzprev, hipStream_t s) {
+                               int64_t ldz, int epilogue, const float* Zprev, int64_t ldzprev, hipStream_t s,
+                               const LayerEnd& end = LayerEnd()) {
     const int lanes = (f + VEC - 1) / VEC;
     const int64_t threads = n * lanes;
     const dim3 grid((unsigned)((threads + 255) / 256));
     switch (epilogue) {
-        case GCN_EPI_NONE: hipLaunchKernelGGL((k_block_reduce<VEC, GCN_EPI_NONE>), grid, dim3(256), 0, s, n, f, lanes, b.rq_ptr, b.rq_idx, row_map, row_scale, P, Z, ldz, Zprev, ldzprev, accumulate); break;
-        case GCN_EPI_RELU: hipLaunchKernelGGL((k_block_reduce<VEC, GCN_EPI_RELU>), grid, dim3(256), 0, s, n, f, lanes, b.rq_ptr, b.rq_idx, row_map, row_scale, P, Z, ldz, Zprev, ldzprev, accumulate); break;
-        default: hipLaunchKernelGGL((k_block_reduce<VEC, GCN_EPI_MASK>), grid, dim3(256), 0, s, n, f, lanes, b.rq_ptr, b.rq_idx, row_map, row_scale, P, Z, ldz, Zprev, ldzprev, accumulate); break;
+        case GCN_EPI_NONE: hipLaunchKernelGGL((k_block_reduce<VEC, GCN_EPI_NONE>), grid, dim3(256), 0, s, n, f, lanes, b.rq_ptr, b.rq_idx, row_map, row_scale, P, Z, ldz, Zprev, ldzprev, accumulate, end); break;
+        case GCN_EPI_RELU: hipLaunchKernelGGL((k_block_reduce<VEC, GCN_EPI_RELU>), grid, dim3(256), 0, s, n, f, lanes, b.rq_ptr, b.rq_idx, row_map, row_scale, P, Z, ldz, Zprev, ldzprev, accumulate, end); break;
+        case EPI_LAYER: hipLaunchKernelGGL((k_block_reduce<VEC, EPI_LAYER>), grid, dim3(256), 0, s, n, f, lanes, b.rq_ptr, b.rq_idx, row_map, row_scale, P, Z, ldz, Zprev, ldzprev, accumulate, end); break;
+        default: hipLaunchKernelGGL((k_block_reduce<VEC, GCN_EPI_MASK>), grid, dim3(256), 0, s, n, f, lanes, b.rq_ptr, b.rq_idx, row_map, row_scale, P, Z, ldz, Zprev, ldzprev, accumulate, end); break;
     }
     GCN_LAUNCH_CHECK();
     return GCN_OK;
@@ -1673,8 +1720,14 @@ static int run_matrix(gcn_csr* a, Matrix& mm, const int32_t* row_map, int64_t nn
         args.Z = a->partial; args.ldz = f; args.Zprev = nullptr; args.ldzprev = 0;
         args.per_xcd = (uint32_t)((mm.nchunks + XCDS * WAVES_PER_BLOCK - 1) / (XCDS * WAVES_PER_BLOCK));
         GCN_TRY(run_split(args, GCN_EPI_NONE, s, choice));
-        if (f >= 4) return launch_block_reduce<4>(mm.nrows, f, b, row_map, o.row_scale, o.accumulate ? 1 : 0, a->partial, Z, ldz, epilogue, Zprev, ldzprev, s);
-        return launch_block_reduce<1>(mm.nrows, f, b, row_map, o.row_scale, o.accumulate ? 1 : 0, a->partial, Z, ldz, epilogue, Zprev, ldzprev, s);
+        LayerEnd end;
+        if (o.end && !row_map) {
+            epilogue = EPI_LAYER;
+            end = *o.end;
+            o.end->done = true;
+        }
+        if (f >= 4) return launch_block_reduce<4>(mm.nrows, f, b, row_map, o.row_scale, o.accumulate ? 1 : 0, a->partial, Z, ldz, epilogue, Zprev, ldzprev, s, end);
+        return launch_block_reduce<1>(mm.nrows, f, b, row_map, o.row_scale, o.accumulate ? 1 : 0, a->partial, Z, ldz, epilogue, Zprev, ldzprev, s, end);
     }
     const bool short_kernel = !row_map && short_rows(mm, f);
     const SplitChoice choice = short_kernel ? SplitChoice() : choose_split(f, mm.nchunks, o.any_order, false);
@@ -1696,6 +1749,12 @@ static int run_matrix(gcn_csr* a, Matrix& mm, const int32_t* row_map, int64_t nn
     if (short_kernel) {
         args.rp = mm.rowptr;
         return launch_short(args, mm.nrows, epilogue, s);
+    }
+    if (o.end && !row_map && choice.kernel == SplitChoice::SPLIT && choice.vec == 4 && mm.n_ne == mm.nrows) {
+        // (rows without entries are their bias alone; the other kernels run where a pass more is a launch more, or on ragged widths)
+        epilogue = EPI_LAYER;
+        args.bias = o.end->bias; args.H = o.end->H; args.relu = o.end->relu;
+        o.end->done = true;
     }
     if (!row_map && mm.n_ne < mm.nrows) GCN_TRY(zero_empty_rows(mm, f, Z, ldz, s));
     return run_split(args, epilogue, s, choice);

@@ -795,3 +795,43 @@ def test_update_of_many_and_of_tied_layers(tied):
         assert np.array_equal(host(Y[k]), v) and np.abs(v).max() > 0, k
         assert np.allclose(host(w), want[w.data_ptr()], rtol=3e-7, atol=1e-9), k       # a rounding of the product may be fused away
     a.close()
+
+
+@pytest.mark.parametrize("f", [4, 7, 16, 20, 32, 41, 48, 64, 130])
+@pytest.mark.parametrize("pairs,loops,blocks", [(500, True, 0), (400_000, True, 1), (400_000, True, 3), (400_000, False, 1), (400_000, False, 3)])
+@pytest.mark.parametrize("values", [0, 1])
+def test_layer_end_in_the_product(f, pairs, loops, blocks, values):
+    """Bias and activation where the product stores its rows, or in a pass behind it (few chunks, ragged widths, rows without
+    entries): the same bits as the product, plus the bias, clamped; H beside Z, in place, over T; nothing but H and Z is written."""
+    g = G()
+    rs = np.random.default_rng(140)
+    n = 3001
+    src, dst = [np.concatenate([rs.integers(0, n - 5, pairs), np.full(1500, 7)]).astype(np.int32) for _ in range(2)]
+    dst[-1500:] = rs.integers(0, n - 5, 1500)                       # a row over several chunks
+    a = g.gcn_csr_create(n, dev(src), dev(dst), (g.ADD_SELF_LOOPS if loops else 0) | g.SYMMETRISE | g.NORM_SYM | g.BUILD_TRANSPOSE)
+    g.gcn_csr_config(a, g.CFG_SPMM_BLOCKS, blocks)
+    g.gcn_csr_config(a, g.CFG_PATTERN_SPMM, values)
+    X, W, b = dev(synth.normal_features(n, 24, 141)), dev(synth.normal_features(24, f, 142)), dev(synth.normal_features(1, f, 143)[0])
+    T, Z, want = [torch.full((n, f), float("nan"), device="cuda") for _ in range(3)]
+    room = torch.full((n + 2, f), float("nan"), device="cuda")
+    for bias in (b, None):
+        H = room[1:-1].fill_(float("nan"))
+        g.gcn_layer_forward(a, X, W, Z, H, T, g.ORDER_GEMM_FIRST, g.ACT_RELU, bias=bias)
+        g.gcn_gemm(0, 0, X, W, T)
+        xs = T
+        g.gcn_csr_config(a, g.CFG_PATTERN_SPMM, 0)                  # the layer calls have no room for a scaled operand
+        g.gcn_spmm(a, 1, xs, want)
+        g.gcn_csr_config(a, g.CFG_PATTERN_SPMM, values)
+        if bias is not None:
+            want += bias
+        assert torch.equal(Z, want) and torch.equal(H, want.clamp(min=0)), bias is None
+        assert bool(torch.isnan(room[0]).all() and torch.isnan(room[-1]).all())
+        g.gcn_layer_forward(a, X, W, Z, T, T, g.ORDER_GEMM_FIRST, g.ACT_RELU, bias=bias)           # H over T
+        assert torch.equal(Z, want) and torch.equal(T, want.clamp(min=0))
+        g.gcn_layer_forward(a, X, W, Z, Z, T, g.ORDER_GEMM_FIRST, g.ACT_RELU, bias=bias)           # in place
+        assert torch.equal(Z, want.clamp(min=0))
+        for Ho in (None, H):                                                                       # without an activation
+            g.gcn_layer_forward(a, X, W, Z, Ho, T, g.ORDER_GEMM_FIRST, g.ACT_NONE, bias=bias)
+            assert_close(host(Z), host(want).astype(np.float64), "no activation")
+            assert Ho is None or torch.equal(H, Z)
+    a.close()
