@@ -352,6 +352,8 @@ int spmm_prepare(gcn_csr* a, Matrix& m, int32_t f, hipStream_t s, bool any_sched
 int grow_retire(gcn_csr* a, float** buf, size_t* have, size_t need);
 
 // `row_scale` (optional): row i of C is multiplied by row_scale[i] after bias and epilogue
+int gemm_back_launch(int64_t n, int32_t f_in, int32_t f_out, const float* Hin, int64_t ldh, const float* S, const float* W,
+                     const float* Zprev, float* Y, float* Gprev, hipStream_t s, bool* handled);
 int gemm_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, const float* B,
                 int64_t ldb, float* C, int64_t ldc, const float* bias, int epilogue, const float* Zprev,
                 int64_t ldzprev, hipStream_t s, const float* row_scale = nullptr);

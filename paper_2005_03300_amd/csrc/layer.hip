@@ -102,6 +102,12 @@ static int layer_backward_impl(gcn_csr* a, int32_t f_in, int32_t f_out, const fl
     if (order == GCN_ORDER_GEMM_FIRST) {
         // S = A G;  Y = Hin^T S;  Gprev = (S W^T) (.) sigma'(Zprev)
         GCN_TRY(norm_spmm(a, matrix_of(a, 0), f_out, G, f_out, xs, S, f_out, GCN_EPI_NONE, nullptr, 0, s, false, true));
+        if (Gprev) {
+            PhaseTimer pt(s, GCN_PHASE_GEMM);
+            bool both = false;
+            GCN_TRY(gemm_back_launch(n, f_in, f_out, Hin, ldh, S, W, Zprev, Y, Gprev, s, &both));
+            if (both) return GCN_OK;
+        }
         GCN_TRY(timed_gemm(1, 0, f_in, f_out, n, Hin, ldh, S, f_out, Y, f_out, nullptr, GCN_EPI_NONE, nullptr, 0, s));
         if (Gprev)
             GCN_TRY(timed_gemm(0, 1, n, f_in, f_out, S, f_out, W, f_out, Gprev, f_in, nullptr, GCN_EPI_MASK, Zprev, f_in, s));

@@ -835,3 +835,34 @@ def test_layer_end_in_the_product(f, pairs, loops, blocks, values):
             assert_close(host(Z), host(want).astype(np.float64), "no activation")
             assert Ho is None or torch.equal(H, Z)
     a.close()
+
+
+@pytest.mark.parametrize("n", [63, 64, 65, 79, 128, 129, 1000, 8192, 70_001])
+@pytest.mark.parametrize("pad,own", [(0, True), (0, False), (4, False), (1, False)])
+def test_backward_products_of_width_16(n, pad, own):
+    """Y = H^T S and Gprev = (S W^T) masked, in one pass where rows are aligned (not: pitch 17, below 64 rows): last trips of every
+    length, the mask from H itself and from a matrix of its own, Gprev over H and over S."""
+    g = G()
+    rs = np.random.default_rng(144)
+    a = g.gcn_csr_create(n, *[dev(rs.integers(0, n, 3 * n).astype(np.int32)) for _ in range(2)], g.ADD_SELF_LOOPS | g.NORM_ROW | g.BUILD_TRANSPOSE)
+    H, Zp, W, Gm = [synth.normal_features(k, 16, 145 + i) for i, k in enumerate((n, n, 16, n))]
+    Hd = torch.full((n, 16 + pad), float("nan"), device="cuda")
+    Hd[:, :16] = dev(H)
+    Hd, Wd = Hd[:, :16], dev(W)
+    Zd = Hd if own else dev(Zp)
+    S, Y = torch.empty(n, 16, device="cuda"), torch.full((16, 16), float("nan"), device="cuda")
+    Gp = torch.full((n + 2, 16), float("nan"), device="cuda")
+    g.gcn_layer_backward(a, Hd, Zd, Wd, dev(Gm), None, S, Y, Gp[1:-1], g.ORDER_GEMM_FIRST)
+    Sx = host(S).astype(np.float64)
+    wantY, wantG = H.T.astype(np.float64) @ Sx, np.where((H if own else Zp) > 0, Sx @ W.T, 0)
+    assert np.linalg.norm(host(Y) - wantY) <= 5e-7 * np.linalg.norm(wantY)
+    assert_close(host(Gp)[1:-1], wantG, f"{n} {pad}")
+    assert bool(torch.isnan(Gp[0]).all() and torch.isnan(Gp[-1]).all())
+    plain = torch.empty(n, 16, device="cuda")
+    g.gcn_gemm(0, 1, S, Wd, plain, epilogue=g.EPI_MASK, Zprev=Zd)
+    assert torch.equal(Gp[1:-1], plain)
+    first = Y.clone()
+    for over in ([S] if pad else [S, Hd]):
+        g.gcn_layer_backward(a, Hd, Zd, Wd, dev(Gm), None, S, Y, over, g.ORDER_GEMM_FIRST)
+        assert torch.equal(over, plain) and torch.equal(Y, first)
+    a.close()
