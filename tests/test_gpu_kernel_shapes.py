@@ -747,7 +747,7 @@ def test_column_blocks_walked_by_one_xcd_each(chunks, f):
     a.close()
 
 
-@pytest.mark.parametrize("strips", [1, 3, 4, 5, 252, 256, 257, 2044, 2052, 8192, 8199])
+@pytest.mark.parametrize("strips", [1, 3, 4, 5, 16, 17, 252, 256, 257, 1008, 1024, 2052, 8192, 8199, 32_768, 33_001])
 @pytest.mark.parametrize("C", [3, 16, 41, 130])
 def test_last_layer_sums_of_workgroups(strips, C):
     """The fused last layer's weight gradient and loss from 1 to 2048 workgroups' partial results: fewer than the 64 groups of threads that
