@@ -163,7 +163,8 @@ int gcn_spmm(gcn_csr* a, int trans, int32_t f, const float* X, int64_t ldx, floa
  * several widths are kept side by side, so a model whose products alternate between widths never rebuilds.
  * gcn_spmm_describe writes the schedule such a product takes, its launch shape and its main kernel as text into `out`
  * (host, out_bytes including the terminator; truncated if too small), building it like gcn_spmm_prepare if
- * needed; reports and tests use it to tie a measurement to the schedule it was taken on. */
+ * needed; reports and tests use it to tie a measurement to the schedule it was taken on.  It describes the product without an
+ * epilogue: A X and products with an epilogue may take another schedule than A^T X, whose order of additions is kept. */
 int gcn_spmm_prepare(gcn_csr* a, int trans, int32_t f, void* stream);
 int gcn_spmm_describe(gcn_csr* a, int trans, int32_t f, char* out, size_t out_bytes, void* stream);
 
