@@ -63,7 +63,13 @@ struct SpmmCost {
     double xcds = 8, l2_bytes;
 
     int panel() const { return f <= 16 ? 16 : 32; }
-    int passes() const { return (f + 31) / 32; }
+    // Rows of 33 to 64 columns that are not whole 16-byte pieces are gathered in one panel, by as many lines as 4 f bytes at any
+    // address touch on average; they share the lines at their ends.  (Taken for two panels of whole lines, they were given blocks
+    // half as wide again as they should be: 41 columns, 6 M entries, 120 K vertices over two blocks 131 us, over three 122, estimated 132
+    // and 122; 10 M, 150 K over four 220, over six 211.)
+    bool ragged() const { return f % 4 != 0 && f > 32 && f <= 64; }
+    int passes() const { return ragged() ? 1 : (f + 31) / 32; }
+    double lines_per_row() const { return ragged() ? (4.0 * f + 124.0) / 128.0 : 1.0; }
     int rows_per_line() const { const int w = f < 32 ? f : 32; return w >= 17 ? 1 : 32 / (w < 1 ? 1 : w); }
 
     // The lines of X by the number of entries that select them.
@@ -75,7 +81,7 @@ struct SpmmCost {
 
     // Misses of one XCD: `accesses` to the lines that a `share` of the columns selects, which stay (`band`) or not.
     double misses(const Lengths& lines, double share, double accesses, bool band) const {
-        const double all = std::max<double>(1.0, (double)lines.total()), c = l2_bytes * 0.835 / 128.0;        // the streams take some
+        const double all = std::max<double>(1.0, (double)lines.total()), c = l2_bytes * 0.835 / 128.0 / (ragged() ? f / 32.0 : 1.0);        // the streams take some
         double n[Lengths::BINS], r[Lengths::BINS];
         int k = 0;
         for (int b = 0; b < Lengths::BINS; ++b)
@@ -98,9 +104,9 @@ struct SpmmCost {
 
     // Nonzero-split over `blocks` column blocks of the rows `rows` (microseconds); `lines` of the whole matrix.
     double split(const Lengths& rows, const Lengths& lines, int blocks) const {
-        const double nnz = (double)rows.total(), fetched = nnz * passes();
+        const double nnz = (double)rows.total(), w = lines_per_row(), fetched = nnz * passes() * w;
         const double each = std::max(1.0, blocks / xcds);        // blocks that an XCD walks: each is in one of their L2s
-        const double m = misses(lines, 1.0 / blocks, nnz / xcds / each, false) * xcds * each * passes() + fetched * 8 / 128;
+        const double m = misses(lines, 1.0 / blocks, nnz / xcds / each, false) * xcds * each * passes() * w + nnz * passes() * 8 / 128;
         const bool narrow = f <= 16;
         const double served = fetched / (narrow ? 228e3 : 174e3), filled = m / (narrow ? 67.9e3 : 57.2e3);
         const double e = narrow ? 1.94 : 4.6;

@@ -91,3 +91,31 @@ def test_estimated_costs_choose_as_timed(tmp_path):
         }
     """)
     assert r.returncode == 0 and r.stdout.split() == ["111"] * 8 + ["ok"], (r.returncode, r.stdout, r.stderr)
+
+
+def test_estimated_costs_of_ragged_rows(tmp_path):
+    """Blocks for rows of 33 to 64 columns that are no whole 16-byte pieces, on uniform matrices timed over 1 to 8 blocks: what is
+    chosen takes no more than 5 % longer than the fastest; the widths beside that range are estimated as before."""
+    r = run_cpp(tmp_path, """
+        #include <cstdio>
+        #include "spmm_cost.h"
+        using namespace gcn;
+        int main() {
+            struct { int64_t n, mean; int f, usual; double us[9]; } timed[] = {       // microseconds by number of blocks
+                {150000, 67, 41, 2, {0, 344, 299, 252, 220, 0, 211, 0, 227}}, {150000, 67, 47, 2, {0, 380, 340, 292, 256, 0, 240, 0, 253}},
+                {100000, 81, 41, 3, {0, 243, 188, 154, 152, 0, 148, 0, 158}}, {100000, 81, 47, 3, {0, 274, 219, 176, 168, 0, 163, 0, 169}}};
+            for (auto& t : timed) {
+                const SpmmCost c{t.f, 256, 8.0, 4.0 * (1 << 20)};
+                const Lengths rows = Lengths::equal(t.n, t.n * t.mean);
+                double cost = 0, least = 1e30;
+                const int b = c.best_blocks(rows, c.lines(rows), t.n, t.usual, &cost);
+                for (double us : t.us) if (us > 0) least = std::min(least, us);
+                std::printf("%d ", b <= 8 && t.us[b] > 0 && t.us[b] <= 1.05 * least);
+            }
+            for (int f : {31, 32, 33, 36, 63, 64, 65, 127}) {
+                const SpmmCost c{f, 256, 8.0, 4.0 * (1 << 20)};
+                std::printf("%d%d ", c.passes(), c.lines_per_row() == 1.0);
+            }
+        }
+    """)
+    assert r.returncode == 0 and r.stdout.split() == ["1"] * 4 + ["11", "11", "10", "21", "10", "21", "31", "41"], (r.returncode, r.stdout, r.stderr)
