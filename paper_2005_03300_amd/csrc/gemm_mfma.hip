@@ -961,11 +961,20 @@ int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const floa
     return GCN_OK;
 }
 
-// Gprev = (S W^T) masked by Zprev, Y = Hin^T S; all of them 16 wide and their rows 16-byte aligned, or *handled stays false.
+// Whether Gprev (n rows of 16 floats) shares no memory with a matrix of n rows of 16 floats, `ld` apart, that the same kernel
+// reads, or lies on it row by row: then a row is read and written by one wavefront, in that order.
+static bool row_by_row(int64_t n, const float* Gprev, const float* M, int64_t ld) {
+    return (M == Gprev && ld == 16) || M + (n - 1) * ld + 16 <= Gprev || Gprev + n * 16 <= M;
+}
+
+// Gprev = (S W^T) masked by Zprev, Y = Hin^T S; all of them 16 wide and their rows 16-byte aligned, or *handled stays false.  It also
+// stays false where Gprev lies across rows of an operand that another workgroup may not have read yet: the
+// two products one after the other read all of Hin before they write Gprev.
 int gemm_back_launch(int64_t n, int32_t f_in, int32_t f_out, const float* Hin, int64_t ldh, const float* S, const float* W,
                      const float* Zprev, float* Y, float* Gprev, hipStream_t s, bool* handled) {
     *handled = false;
     if (f_in != 16 || f_out != 16 || n < 64 || ldh % 4 != 0 || !al16(Hin) || !al16(S) || !al16(Zprev) || !al16(Gprev)) return GCN_OK;
+    if (!row_by_row(n, Gprev, Hin, ldh) || !row_by_row(n, Gprev, S, 16) || !row_by_row(n, Gprev, Zprev, 16)) return GCN_OK;
     const TnShape g = tn_shape(16, 16, n);
     void* scratch = nullptr;
     GCN_TRY(scratch_get(&scratch, g.scratch_bytes, s));

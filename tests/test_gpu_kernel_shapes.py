@@ -866,3 +866,25 @@ def test_backward_products_of_width_16(n, pad, own):
         g.gcn_layer_backward(a, Hd, Zd, Wd, dev(Gm), None, S, Y, over, g.ORDER_GEMM_FIRST)
         assert torch.equal(over, plain) and torch.equal(Y, first)
     a.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [64, 1000, 70_001])
+@pytest.mark.parametrize("ldh,first,over", [(20, 0, 0), (20, 0, 4), (16, 16, 0), (16, 0, 16), (24, 8, 0)])
+def test_backward_products_of_width_16_with_gprev_across_the_rows_of_h(n, ldh, first, over):
+    """Gprev in H's memory at another pitch or offset: row i of Gprev lies over other rows of H, all of which Y needs first."""
+    g = G()
+    rs = np.random.default_rng(146)
+    a = g.gcn_csr_create(n, *[dev(rs.integers(0, n, 3 * n).astype(np.int32)) for _ in range(2)], g.ADD_SELF_LOOPS | g.NORM_ROW | g.BUILD_TRANSPOSE)
+    H, Zp, W, Gm = [synth.normal_features(k, 16, 147 + i) for i, k in enumerate((n, n, 16, n))]
+    memory = torch.zeros(n * ldh + 64, device="cuda")
+    Hd = memory[first:first + n * ldh].view(n, ldh)[:, :16]
+    Hd.copy_(dev(H))
+    Gp = memory[over:over + n * 16].view(n, 16)
+    S, Y = torch.empty(n, 16, device="cuda"), torch.full((16, 16), float("nan"), device="cuda")
+    g.gcn_layer_backward(a, Hd, dev(Zp), dev(W), dev(Gm), None, S, Y, Gp, g.ORDER_GEMM_FIRST)
+    Sx = host(S).astype(np.float64)
+    wantY = H.T.astype(np.float64) @ Sx
+    assert np.linalg.norm(host(Y) - wantY) <= 5e-7 * np.linalg.norm(wantY)
+    assert_close(host(Gp), np.where(Zp > 0, Sx @ W.T, 0), f"{n} {ldh} {first} {over}")
+    a.close()
