@@ -42,19 +42,17 @@ struct FusedArgs {
     double* lpart;            // [gridDim.x]
 };
 
-// The largest of three, NaN left out like fmaxf (which the compiler precedes with an instruction per operand to quiet what no
-// matrix instruction gives).
-__device__ __forceinline__ float max3(float a, float b, float c) {
-    float m;
-    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(m) : "v"(a), "v"(b), "v"(c));
-    return m;
-}
+// The larger of two, NaN if either is: a row with a NaN among its logits has a NaN for its sum in any case.  (fmaxf, which leaves NaN
+// out, is preceded by an instruction per operand that quiets what no matrix instruction gives; two of these in a row
+// are one instruction.  From the compiler, not by inline assembly: it counts the cycles that a matrix result needs before
+// another instruction reads it.)
+__device__ __forceinline__ float larger(float a, float b) { return __builtin_elementwise_maximum(a, b); }
 
-// FULL: C == 16 NT, no padding columns (their tests are compiled out).  Bound by instructions: a strip's matrix and vector instructions
+// Bound by instructions: a strip's matrix and vector instructions
 // add up to its time (24 classes: 24 matrix instructions of 32 cycles and some 200 of 4).  At least four wavefronts per SIMD are
 // asked for, which also keeps the accumulators out of the second half of the registers, to and from which they were
 // copied: with that and the shorter maximum 1.8 M rows of 24 classes take 91 us (97 before), 14.2 M 625 (684).
-template <int NT, bool FULL>
+template <int NT>
 __global__ __launch_bounds__(256, NT <= 4 ? 4 : 1) void k_fused_last(FusedArgs a) {
     constexpr int CP = 16 * NT;            // padded class count
     constexpr int SW = CP + 4;             // row stride of Ws
@@ -130,7 +128,7 @@ __global__ __launch_bounds__(256, NT <= 4 ? 4 : 1) void k_fused_last(FusedArgs a
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const int c = 16 * t + 4 * g + v;
-                    if (FULL || c < a.C) a.Zout[row * a.C + c] = z[t][v];
+                    if (c < a.C) a.Zout[row * a.C + c] = z[t][v];
                 }
         }
         // row-wise log-softmax over the C real columns (padding columns: exp(-inf) = 0)
@@ -138,12 +136,12 @@ __global__ __launch_bounds__(256, NT <= 4 ? 4 : 1) void k_fused_last(FusedArgs a
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v)
-                if (!FULL) z[t][v] = 16 * t + 4 * g + v < a.C ? z[t][v] : -INFINITY;
-            m = max3(max3(m, z[t][0], z[t][1]), z[t][2], z[t][3]);
+            for (int v = 0; v < 4; ++v) z[t][v] = 16 * t + 4 * g + v < a.C ? z[t][v] : -INFINITY;
+            m = larger(larger(larger(larger(m, z[t][0]), z[t][1]), z[t][2]), z[t][3]);
         }
-        m = fmaxf(m, __shfl_xor(m, 16, 64));
-        m = fmaxf(m, __shfl_xor(m, 32, 64));
+        m = larger(m, __shfl_xor(m, 16, 64));
+        m = larger(m, __shfl_xor(m, 32, 64));
+        if (!labelled) m = INFINITY;               // exp = 0 times a scale of 0, also where another logit of the row is NaN
         // e = exp(z - max) is computed once per logit and reused: softmax = e / sum(e); the lane that holds
         // column y keeps z_y for the loss
         float ssum = 0.f, zy = 0.f;
@@ -178,7 +176,7 @@ __global__ __launch_bounds__(256, NT <= 4 ? 4 : 1) void k_fused_last(FusedArgs a
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const int c = 16 * t + 4 * g + v;
-                    if (FULL || c < a.C) a.Gout[row * a.C + c] = z[t][v];
+                    if (c < a.C) a.Gout[row * a.C + c] = z[t][v];
                 }
         }
         // 2. S = G W^T: the lane gets S[row r][4g + v]
@@ -549,8 +547,8 @@ template <int NT>
 static void launch_fused(const FusedArgs& a, int64_t blocks, hipStream_t s) {
     const int GT = NT < 4 ? NT : 4;
     const size_t lds = (size_t)(16 * (16 * NT + 4) + 16 * NT * 20 + 4 * (1 + GT) * 16 * 20) * sizeof(float);
-    // (a variant with the padding tests compiled out for C == 16 NT made the register allocator spill: not used)
-    hipLaunchKernelGGL((k_fused_last<NT, false>), dim3((unsigned)blocks), dim3(256), lds, s, a);
+    // (a variant with the padding tests compiled out for C == 16 NT made the register allocator spill)
+    hipLaunchKernelGGL((k_fused_last<NT>), dim3((unsigned)blocks), dim3(256), lds, s, a);
 }
 
 template <int TW>

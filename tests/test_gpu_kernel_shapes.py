@@ -772,6 +772,38 @@ def test_last_layer_sums_of_workgroups(strips, C):
     a.close()
 
 
+@pytest.mark.parametrize("C", [3, 16, 41, 64, 130])
+@pytest.mark.parametrize("labelled", [True, False])
+def test_last_layer_with_logits_at_the_ends_of_the_range(C, labelled):
+    """A logit of minus infinity counts for nothing; a NaN in a labelled row reaches the loss and all of Y, as the separate kernels do it."""
+    g = G()
+    n = 100
+    P0, W = synth.normal_features(n, 16, 151), synth.normal_features(16, C, 152) * np.float32(0.3)
+    P0[:, 15], W[15] = 0, 0
+    P0[7, :], P0[7, 15], W[15, 0] = 0, 1e30, -1e30                     # logits of row 7: -inf, 0, 0, ...
+    y = np.full(n, 1, np.int32)
+    y[50] = 1 if labelled else -1
+    a = g.gcn_csr_create(n, dev(np.zeros(1, np.int32)), dev(np.zeros(1, np.int32)), g.ADD_SELF_LOOPS | g.NORM_SYM | g.SYMMETRISE | g.BUILD_TRANSPOSE)
+    m = int((y >= 0).sum())
+    ws = torch.empty(g.gcn_epoch_workspace_bytes(n, [16, C]), dtype=torch.uint8, device="cuda")
+
+    def run(P):
+        Y, loss = torch.full((16, C), float("nan"), device="cuda"), torch.zeros(1, device="cuda")
+        g.gcn_epoch_preaggregated(a, [16, C], dev(P), dev(y), m, [dev(W)], [Y], 0.0, loss, ws)
+        return host(Y), loss.item()
+    Y, loss = run(P0)
+    Z = P0.astype(np.float64) @ W
+    Z[7, 0] = -np.inf
+    lse = np.log(np.exp(Z - Z.max(1, keepdims=True)).sum(1)) + Z.max(1)
+    Gd = np.where((y >= 0)[:, None], (np.exp(Z - lse[:, None]) - (np.arange(C) == y[:, None])) / m, 0)
+    assert_close(Y, P0.T.astype(np.float64) @ Gd, f"Y {C}")
+    assert abs(loss - (lse - Z[:, 1])[y >= 0].mean()) <= 1e-5 * abs(loss)
+    P0[50, 3] = np.nan
+    Y, loss = run(P0)
+    assert np.isnan(loss) == labelled and (np.isnan(Y).all() or not labelled)
+    a.close()
+
+
 @pytest.mark.parametrize("tied", [[], [(1, 2)], [(0, 1), (1, 2), (16, 17)], [(3, 18)]])
 def test_update_of_many_and_of_tied_layers(tied):
     """All layers' W are updated side by side, more of them than a launch takes, and one after another where they share a matrix."""
