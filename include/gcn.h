@@ -145,7 +145,11 @@ int gcn_csr_export(const gcn_csr* a, int transposed, int64_t* rowptr, int32_t* c
  * epilogue GCN_EPI_MASK reads Zprev (device n x f, ld ldzprev); otherwise Zprev is ignored.  Zprev may be Z itself (same
  * address and leading dimension; correct, but such a product takes the row-wise kernel, which is slow on long rows); no
  * other element of Zprev may be one of Z.
- * Sums are fp32 and run-to-run reproducible (no floating-point atomics).  The first call at a
+ * Sums are fp32 and run-to-run reproducible (no floating-point atomics).  The order of a sum's terms depends on the matrix, the
+ * width, the settings and the direction: A^T X, plain or with GCN_EPI_RELU, keeps an order that the sizes alone decide, the
+ * one of the layer and epoch calls' hidden layers; A X with any epilogue, and A^T X with GCN_EPI_MASK, may take another one that
+ * is faster.  So trans = 0 and trans = 1 on a matrix that equals its transpose, and A^T X with and without a mask, can differ
+ * by fp32 roundings; the product with GCN_EPI_RELU is the clamp of the plain product bit by bit.  The first call at a
  * given width may build and cache a column-blocked copy of the matrix inside `a` (it allocates
  * and synchronises once); later calls only queue kernels.
  * For a matrix that gcn_csr_create normalised symmetrically the same product is D^-1/2 ((A+I) (D^-1/2 X)); when
@@ -164,7 +168,7 @@ int gcn_spmm(gcn_csr* a, int trans, int32_t f, const float* X, int64_t ldx, floa
  * gcn_spmm_describe writes the schedule such a product takes, its launch shape and its main kernel as text into `out`
  * (host, out_bytes including the terminator; truncated if too small), building it like gcn_spmm_prepare if
  * needed; reports and tests use it to tie a measurement to the schedule it was taken on.  It describes the product without an
- * epilogue: A X and products with an epilogue may take another schedule than A^T X, whose order of additions is kept. */
+ * epilogue; A^T X with GCN_EPI_MASK may take the one that A X takes (see gcn_spmm). */
 int gcn_spmm_prepare(gcn_csr* a, int trans, int32_t f, void* stream);
 int gcn_spmm_describe(gcn_csr* a, int trans, int32_t f, char* out, size_t out_bytes, void* stream);
 

@@ -325,10 +325,10 @@ struct SpmmOpt {
     bool pattern = false;
     const float* row_scale = nullptr;
     bool any_order = false;           // no ReLU decides on the result: a faster kernel may add a row's terms in another order
-    // Another schedule may add the terms in another order: also set for the stand-alone products (of widths that are a multiple of
-    // four, see spmm_launch).  The products whose sums a ReLU of this library decides on keep one schedule, chosen by sizes
-    // alone: where a sum is zero to rounding another order puts it on the other side, and every such element moves
-    // the gradient of the weights by 1e-4 of its norm.
+    // Another schedule may add the terms in another order: also set for the stand-alone products A X, and A^T X with a mask (of
+    // widths that are a multiple of four, see free_schedule).  The forward products A^T X, on whose sums a ReLU decides, keep one
+    // schedule, chosen by sizes alone: where a sum is zero to rounding another order puts it on the other side, and every
+    // such element moves the gradient of the weights by 1e-4 of its norm.
     bool any_schedule = false;
     LayerEnd* end = nullptr;          // only with the epilogue GCN_EPI_NONE
     // internal to the hub schedule:

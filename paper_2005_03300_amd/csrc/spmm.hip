@@ -2101,9 +2101,10 @@ static int check_spmm_args(const char* who, const gcn_csr* a, int trans, int32_t
     return GCN_OK;
 }
 
-// Whether a stand-alone product may take any schedule: not at the ragged widths, whose kernels all add alike, and not the plain
-// forward product A^T X, on which the first hidden layer of gcn_epoch_preaggregated (or of the caller's own) decides.
-static bool free_schedule(int32_t f, int trans, int epilogue) { return f % 4 == 0 && !(trans && epilogue == GCN_EPI_NONE); }
+// Whether a stand-alone product may take any schedule: not at the ragged widths, whose kernels all add alike, and not the
+// forward product A^T X, plain or with a ReLU, on which the first hidden layer of gcn_epoch_preaggregated (or of the caller's
+// own) decides.  A ReLU never changes the sums: A X takes the same schedule with and without one, and so does A^T X.
+static bool free_schedule(int32_t f, int trans, int epilogue) { return f % 4 == 0 && !(trans && epilogue != GCN_EPI_MASK); }
 
 extern "C" int gcn_spmm(gcn_csr* a, int trans, int32_t f, const float* X, int64_t ldx, float* Z, int64_t ldz,
                         int epilogue, const float* Zprev, int64_t ldzprev, void* stream) {

@@ -612,7 +612,7 @@ def test_sweep_tasks_trips_and_padding(f, shape):
 @pytest.mark.parametrize("graph,f,want", [("wide", 16, "sweep("), ("wide", 32, "sweep("), ("wide", 20, "sweep("), ("wide", 48, "sweep("),
                                           ("few_blocks", 32, "blocked(blocks=4,"), ("few_blocks", 64, "blocked(blocks=4,")])
 def test_schedule_by_cost_against_the_one_by_sizes(graph, f, want):
-    """Products whose schedule is chosen by estimated cost (A X, and A^T X with an epilogue), with operands of every pitch and alignment, in
+    """Products whose schedule is chosen by estimated cost (A X, and A^T X with a mask), with operands of every pitch and alignment, in
     both forms, against the products that keep the schedule of the sizes (A^T X: the matrix is symmetric) and against the
     oracle: as far from it as those are, and no further."""
     g = G()
@@ -631,6 +631,7 @@ def test_schedule_by_cost_against_the_one_by_sizes(graph, f, want):
         return float((Zd.double() - dev(exact)).norm() / np.linalg.norm(exact))
     g.gcn_spmm(a, 1, Xd, Zd)
     usual = error()
+    kept = host(Zd)
     g.gcn_spmm(a, 0, Xd, Zd)
     first = host(Zd)
     assert error() <= 1.02 * usual, (error(), usual)
@@ -642,7 +643,7 @@ def test_schedule_by_cost_against_the_one_by_sizes(graph, f, want):
         Xp[:, :f] = Xd
         Zw = torch.full((n, f + pad), float("nan"), device="cuda")
         g.gcn_spmm(a, trans, Xp[:, :f], Zw[:, :f], g.EPI_RELU)
-        assert torch.equal(Zw[:, :f], dev(np.maximum(first, 0))) and bool(torch.isnan(Zw[:, f:]).all()), (trans, pad, off)
+        assert torch.equal(Zw[:, :f], dev(np.maximum(kept if trans else first, 0))) and bool(torch.isnan(Zw[:, f:]).all()), (trans, pad, off)
         g.gcn_spmm(a, trans, Xp[:, :f], Zw[:, :f], g.EPI_MASK, Zpd)
         assert torch.equal(Zw[:, :f], dev(np.where(Zp > 0, first, 0))), (trans, pad, off)
     g.gcn_spmm_pattern(a, 0, Xd, Zd)
@@ -919,4 +920,28 @@ def test_backward_products_of_width_16_with_gprev_across_the_rows_of_h(n, ldh, f
     wantY = H.T.astype(np.float64) @ Sx
     assert np.linalg.norm(host(Y) - wantY) <= 5e-7 * np.linalg.norm(wantY)
     assert_close(host(Gp), np.where(Zp > 0, Sx @ W.T, 0), f"{n} {ldh} {first} {over}")
+    a.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("f", [16, 32])
+def test_a_relu_does_not_change_the_sums(f):
+    """A X may take another order of additions than A^T X; with a ReLU each of them is the clamp of the plain product, bit by bit, and
+    A^T X that of the layer call."""
+    g = G()
+    n, pairs = 500_000, 10_000_000
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(161)
+    src, dst = [torch.randint(n, (pairs,), generator=gen, device="cuda", dtype=torch.int32) for _ in range(2)]
+    a = g.gcn_csr_create(n, src, dst, g.SYMMETRISE | g.ADD_SELF_LOOPS | g.NORM_SYM | g.BUILD_TRANSPOSE)
+    X = torch.rand(n, f, generator=gen, device="cuda") - 0.5
+    assert g.gcn_spmm_describe(a, 0, f) != g.gcn_spmm_describe(a, 1, f)
+    for trans in (0, 1):
+        plain, relu = torch.empty(n, f, device="cuda"), torch.empty(n, f, device="cuda")
+        g.gcn_spmm(a, trans, X, plain)
+        g.gcn_spmm(a, trans, X, relu, g.EPI_RELU)
+        assert torch.equal(relu, plain.clamp(min=0)), trans
+    T, Z = torch.empty(n, f, device="cuda"), torch.empty(n, f, device="cuda")
+    g.gcn_layer_forward(a, X, torch.eye(f, device="cuda"), Z, Z, T, g.ORDER_SPMM_FIRST)
+    assert torch.equal(T, plain) and torch.equal(Z, relu)
     a.close()
