@@ -122,14 +122,6 @@ struct Hub {
     size_t xhot_bytes = 0;
 };
 
-// The schedule of a product whose order of additions is free (see SpmmOpt::any_schedule).
-struct SpmmPlan {
-    int32_t f = 0;
-    bool sweep = false;
-    int32_t blocks = 1;          // column blocks: of the matrix, or of the sweep's long rows
-    int32_t parts = 1, heavy = 0;// sweep: sums per row, long-row threshold
-};
-
 // One stored matrix in compressed rows plus its nonzero-split schedule.
 struct Matrix {
     int64_t nrows = 0, ncols = 0;

@@ -1633,11 +1633,12 @@ static bool worth_a_plan(const Matrix& m, int32_t f, int64_t nnz) {
     return f >= 4 && nnz >= (1 << 20) && m.lengths.total() == nnz && m.ncols * panel * 4 > device_info().l2_bytes / 8 * 7;
 }
 
-static const SpmmPlan& plan_of(gcn_csr* a, Matrix& m, int32_t f, int64_t usual) {
-    for (const SpmmPlan& p : m.plans)
+static SpmmPlan& plan_of(gcn_csr* a, Matrix& m, int32_t f, int64_t usual) {
+    for (SpmmPlan& p : m.plans)
         if (p.f == f) return p;
     SpmmPlan p;
     p.f = f;
+    p.usual = (int32_t)usual;
     const int64_t nnz = m.lengths.total();
     const SpmmCost c{f, device_info().cus, 8.0, (double)device_info().l2_bytes};
     // the columns of a matrix are the rows of its transpose, where that is stored; otherwise taken to be alike
@@ -1868,7 +1869,12 @@ int want_blocked(Matrix& m, int64_t nnz, int64_t cpb, hipStream_t s) {
             return GCN_OK;
         }
     BuildScope scope(s);
-    return build_blocked(m, nnz, cpb, s);
+    const int rc = build_blocked(m, nnz, cpb, s);
+    if (rc != GCN_OK) {
+        (void)hipStreamSynchronize(s);
+        free_blocked(m.blk);
+    }
+    return rc;
 }
 
 int want_sweep(Matrix& m, int64_t nnz, int32_t groups, int32_t rb, int32_t th, hipStream_t s) {
@@ -1885,7 +1891,12 @@ int want_sweep(Matrix& m, int64_t nnz, int32_t groups, int32_t rb, int32_t th, h
             return GCN_OK;
         }
     BuildScope scope(s);
-    return build_sweep(m, nnz, groups, rb, th, s);
+    const int rc = build_sweep(m, nnz, groups, rb, th, s);
+    if (rc != GCN_OK) {
+        (void)hipStreamSynchronize(s);
+        free_sweep(m.swp);
+    }
+    return rc;
 }
 
 // The hub copy for the current settings: the one in use, a parked one, or a new attempt (state 1 built,
@@ -1955,8 +1966,8 @@ static void took(gcn_csr* a, int sched) {
     a->last_schedule = sched;
 }
 
-int spmm_launch(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx, float* Z, int64_t ldz,
-                int epilogue, const float* Zprev, int64_t ldzprev, hipStream_t s, const SpmmOpt& asked) {
+static int launch_product(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx, float* Z, int64_t ldz,
+                          int epilogue, const float* Zprev, int64_t ldzprev, hipStream_t s, const SpmmOpt& asked, SpmmPlan** plan) {
     SpmmOpt o = asked;
     o.any_schedule = false;                                // set again where a plan decides
     const int64_t n = m.nrows, ncols = m.ncols, nnz = a->nnz;
@@ -1990,7 +2001,8 @@ int spmm_launch(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx, f
     bool hub_first = nblocks < 2;
     if (algo == 2 && cfg.spmm_algo == 0 && cfg.spmm_blocks == 0 && asked.any_schedule && worth_a_plan(m, f, nnz)) {
         o.any_schedule = true;
-        const SpmmPlan& p = plan_of(a, m, f, nblocks);
+        SpmmPlan& p = plan_of(a, m, f, nblocks);
+        *plan = &p;
         if (p.sweep) {
             algo = 3;
             heavy = std::min(heavy, p.heavy);
@@ -2062,6 +2074,15 @@ int spmm_launch(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx, f
     }
     took(a, nblocks >= 2 ? GCN_SCHED_BLOCKED : GCN_SCHED_SPLIT);
     return run_matrix(a, m, nullptr, nnz, nblocks, f, X, ldx, Z, ldz, epilogue, Zprev, ldzprev, o, s);
+}
+
+int spmm_launch(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx, float* Z, int64_t ldz,
+                int epilogue, const float* Zprev, int64_t ldzprev, hipStream_t s, const SpmmOpt& asked) {
+    const size_t said = asked.describe ? asked.describe->size() : 0;
+    return run_or_by_sizes(GCN_ERR_OOM, [&](SpmmPlan** plan) {
+        if (asked.describe) asked.describe->resize(said);
+        return launch_product(a, m, f, X, ldx, Z, ldz, epilogue, Zprev, ldzprev, s, asked, plan);
+    });
 }
 
 // For a matrix this library normalised symmetrically, D^-1/2 (A+I) D^-1/2 X = D^-1/2 ((A+I) (D^-1/2 X))

@@ -166,4 +166,27 @@ struct SpmmCost {
     }
 };
 
+// The schedule of a product whose order of additions is free (see SpmmOpt::any_schedule).
+struct SpmmPlan {
+    int32_t f = 0;
+    bool sweep = false;
+    int32_t blocks = 1;          // column blocks: of the matrix, or of the sweep's long rows
+    int32_t parts = 1, heavy = 0;// sweep: sums per row, long-row threshold
+    int32_t usual = 1;           // blocks by the sizes alone
+    bool by_sizes() const { return !sweep && blocks == usual; }
+};
+
+// Runs a product (`run` leaves the plan it followed, if any, in its argument).  The stored order of a planned schedule is there for
+// speed: where there is no memory for it, this and later products of that width take the schedule of the sizes.
+template <class Run>
+int run_or_by_sizes(int out_of_memory, const Run& run) {
+    SpmmPlan* plan = nullptr;
+    const int rc = run(&plan);
+    if (rc != out_of_memory || !plan || plan->by_sizes()) return rc;
+    plan->sweep = false;
+    plan->blocks = plan->usual;
+    plan = nullptr;
+    return run(&plan);
+}
+
 }  // namespace gcn

@@ -119,3 +119,39 @@ def test_estimated_costs_of_ragged_rows(tmp_path):
         }
     """)
     assert r.returncode == 0 and r.stdout.split() == ["1"] * 4 + ["11", "11", "10", "21", "10", "21", "31", "41"], (r.returncode, r.stdout, r.stderr)
+
+
+def test_a_planned_schedule_without_memory_gives_way_to_the_one_by_sizes(tmp_path):
+    """A product whose planned stored order cannot be allocated runs by sizes, then and later; any other error, and no memory for the
+    schedule of the sizes itself, is the caller's."""
+    r = run_cpp(tmp_path, """
+        #include <cstdio>
+        #include "spmm_cost.h"
+        using namespace gcn;
+        int main() {
+            const int OK = 0, OOM = -4, HIP = -6;
+            for (int copy : {OK, OOM, HIP})
+                for (int plain : {OK, OOM})
+                    for (int kind = 0; kind < 4; ++kind) {          // no plan, sweep, other blocks, the blocks of the sizes
+                        SpmmPlan kept;
+                        kept.usual = 2;
+                        kept.sweep = kind == 1;
+                        kept.blocks = kind == 2 ? 8 : (kind == 1 ? 1 : 2);
+                        int runs = 0;
+                        auto product = [&](SpmmPlan** plan) {
+                            ++runs;
+                            if (kind) *plan = &kept;
+                            return kind && !kept.by_sizes() ? copy : plain;
+                        };
+                        const bool planned = kind == 1 || kind == 2;
+                        const int first = run_or_by_sizes(OOM, product), one = runs;
+                        const int again = run_or_by_sizes(OOM, product), two = runs - one;
+                        const int want = planned && copy != OOM ? copy : plain;
+                        const bool gave_way = planned && copy == OOM;
+                        if (first != want || again != want || one != 1 + gave_way || two != 1 || kept.by_sizes() != (!planned || gave_way))
+                            std::printf("%d/%d/%d: %d %d %d %d ", copy, plain, kind, first, again, one, two);
+                    }
+            std::printf("done");
+        }
+    """)
+    assert r.returncode == 0 and r.stdout == "done", (r.returncode, r.stdout, r.stderr)
