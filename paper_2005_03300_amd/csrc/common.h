@@ -51,6 +51,8 @@ int fail(int code, const char* fmt, ...);
 constexpr int SUB = 32;
 constexpr int CHUNK = 512;
 constexpr int SUBS_PER_CHUNK = CHUNK / SUB;
+// Matrices of fewer entries keep the schedule of the sizes.
+constexpr int64_t PLANNED_NNZ = 1 << 20;
 
 // Column-blocked copy of a matrix: the entries re-sorted by (column block, row, column).  Each
 // non-empty (block, row) pair is a row of a partial-result matrix P; the SpMM kernel runs over this
@@ -140,6 +142,7 @@ struct Matrix {
     int64_t nsub = 0, nchunks = 0;
     int32_t max_degree = 0;
     Lengths lengths;             // of its rows (not kept for the long rows of a sweep copy)
+    RowOrder order;              // how they lie (likewise)
     std::vector<SpmmPlan> plans; // schedules chosen so far, one per width
     // Other stored orders of the matrix, built on first use (or by a prepare call) and kept until the
     // matrix is destroyed.  blk / swp / hub are the copies the latest product used; a product that needs

@@ -91,7 +91,40 @@ struct DegreeSums {
     int32_t max_deg, pad;
     unsigned long long n_nonempty;
     unsigned long long rows[Lengths::BINS], entries[Lengths::BINS];        // as in Lengths
+    unsigned long long sum, squares;                                       // as in RowOrder
+    unsigned ones[RowOrder::WINDOWS];
 };
+
+// The columns of a window of entries (see RowOrder), each of them one bit of a table: how many bits get set.  A workgroup per window,
+// 2^18 bits for 2^15 entries, eight loads in flight.  nnz >= RowOrder::STRETCH.  (34 M entries: 9 us of 2.3 ms of construction.)
+__global__ __launch_bounds__(1024) void k_sample_columns(int64_t nnz, const int32_t* __restrict__ colidx, unsigned* __restrict__ ones) {
+    constexpr int WORDS = (1 << RowOrder::BITS) / 32, LOADS = RowOrder::WINDOW / 4 / 1024, AT_ONCE = 1024 * 4 / RowOrder::GROUP_ENTRIES;
+    __shared__ unsigned s_bits[WORDS];
+    __shared__ unsigned s_ones;
+    const int64_t first = ((nnz - RowOrder::STRETCH) / (RowOrder::WINDOWS - 1) * blockIdx.x) & ~3ll;
+    const int per = 1024 / AT_ONCE, group = (int)threadIdx.x / per, at = (int)threadIdx.x % per;
+    int4 c[LOADS];
+#pragma unroll
+    for (int p = 0; p < LOADS; ++p)
+        c[p] = *reinterpret_cast<const int4*>(colidx + first + (int64_t)(p * AT_ONCE + group) * (RowOrder::APART * RowOrder::GROUP_ENTRIES) + 4 * at);
+    for (int w = threadIdx.x; w < WORDS; w += 1024) s_bits[w] = 0;
+    if (threadIdx.x == 0) s_ones = 0;
+    __syncthreads();
+    auto set = [&](int32_t column) {
+        const uint32_t b = RowOrder::bit_of((uint32_t)column);
+        atomicOr(&s_bits[b / 32], 1u << b % 32);
+    };
+#pragma unroll
+    for (int p = 0; p < LOADS; ++p) { set(c[p].x); set(c[p].y); set(c[p].z); set(c[p].w); }
+    __syncthreads();
+    unsigned n = 0;
+    for (int w = threadIdx.x; w < WORDS; w += 1024) n += __popc(s_bits[w]);
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) n += __shfl_xor(n, d, 64);
+    if ((threadIdx.x & 63) == 0) atomicAdd(&s_ones, n);
+    __syncthreads();
+    if (threadIdx.x == 0) ones[blockIdx.x] = s_ones;
+}
 
 __global__ __launch_bounds__(256) void k_degrees(int64_t n, const int64_t* __restrict__ rowptr, int32_t* __restrict__ deg,
                                                  DegreeSums* __restrict__ sums) {
@@ -101,9 +134,14 @@ __global__ __launch_bounds__(256) void k_degrees(int64_t n, const int64_t* __res
     __syncthreads();
     int32_t m = 0;
     unsigned nz = 0;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-        const int32_t d = (int32_t)(rowptr[i + 1] - rowptr[i]);
-        if (deg) deg[i] = d;
+    unsigned long long sum = 0, squares = 0;
+    for (int64_t first = (int64_t)blockIdx.x * 256; first < n; first += (int64_t)gridDim.x * 256) {
+        const int64_t i = first + threadIdx.x;
+        int32_t d = 0;
+        if (i < n) {
+            d = (int32_t)(rowptr[i + 1] - rowptr[i]);
+            if (deg) deg[i] = d;
+        }
         m = d > m ? d : m;
         nz += d > 0;
         if (d > 0) {
@@ -111,7 +149,13 @@ __global__ __launch_bounds__(256) void k_degrees(int64_t n, const int64_t* __res
             atomicAdd(&s_rows[b], 1u);
             atomicAdd(&s_entries[b], (unsigned long long)d);
         }
+        unsigned group = d < RowOrder::LONG ? d : RowOrder::LONG;      // 64 rows: a wavefront's
+#pragma unroll
+        for (int s = 32; s >= 1; s >>= 1) group += __shfl_xor(group, s, 64);
+        sum += group;
+        squares += (unsigned long long)group * group;
     }
+    static_assert(RowOrder::GROUP == 64, "one wavefront");
 #pragma unroll
     for (int s = 32; s >= 1; s >>= 1) {
         const int32_t o = __shfl_xor(m, s, 64);
@@ -120,12 +164,20 @@ __global__ __launch_bounds__(256) void k_degrees(int64_t n, const int64_t* __res
     }
     __shared__ int32_t s_m[4];
     __shared__ unsigned s_nz[4];
-    if ((threadIdx.x & 63) == 0) { s_m[threadIdx.x >> 6] = m; s_nz[threadIdx.x >> 6] = nz; }
+    __shared__ unsigned long long s_sum[4], s_squares[4];
+    if ((threadIdx.x & 63) == 0) {
+        const int w = threadIdx.x >> 6;
+        s_m[w] = m; s_nz[w] = nz; s_sum[w] = sum; s_squares[w] = squares;
+    }
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int w = 1; w < 4; ++w) { m = s_m[w] > m ? s_m[w] : m; nz += s_nz[w]; }
+        for (int w = 1; w < 4; ++w) { m = s_m[w] > m ? s_m[w] : m; nz += s_nz[w]; sum += s_sum[w]; squares += s_squares[w]; }
         atomicMax(&sums->max_deg, m);
-        if (nz) atomicAdd(&sums->n_nonempty, (unsigned long long)nz);
+        if (nz) {
+            atomicAdd(&sums->n_nonempty, (unsigned long long)nz);
+            atomicAdd(&sums->sum, sum);
+            atomicAdd(&sums->squares, squares);
+        }
     }
     if (threadIdx.x < Lengths::BINS && s_rows[threadIdx.x]) {
         atomicAdd(&sums->rows[threadIdx.x], (unsigned long long)s_rows[threadIdx.x]);
@@ -321,6 +373,12 @@ int build_schedule(Matrix& m, int64_t n, int64_t nnz, hipStream_t s, int32_t* de
     GCN_HIP_TRY(hipMemsetAsync(counters.p, 0, sizeof(DegreeSums), s));
     hipLaunchKernelGGL(k_degrees, dim3(degree_blocks(n)), dim3(256), 0, s, n, m.rowptr, deg, counters.as<DegreeSums>());
     GCN_LAUNCH_CHECK();
+    const bool sampled = nnz >= PLANNED_NNZ;
+    static_assert(PLANNED_NNZ >= RowOrder::STRETCH, "windows lie inside the matrix");
+    if (sampled) {
+        hipLaunchKernelGGL(k_sample_columns, dim3(RowOrder::WINDOWS), dim3(1024), 0, s, nnz, m.colidx, counters.as<DegreeSums>()->ones);
+        GCN_LAUNCH_CHECK();
+    }
     DegreeSums h;
     GCN_HIP_TRY(hipMemcpyAsync(&h, counters.p, sizeof h, hipMemcpyDeviceToHost, s));
     GCN_HIP_TRY(hipStreamSynchronize(s));
@@ -330,6 +388,9 @@ int build_schedule(Matrix& m, int64_t n, int64_t nnz, hipStream_t s, int32_t* de
         m.lengths.rows[b] = (int64_t)h.rows[b];
         m.lengths.entries[b] = (int64_t)h.entries[b];
     }
+    m.order.sum = (double)h.sum;
+    m.order.squares = (double)h.squares;
+    m.order.distinct = sampled ? RowOrder::distinct_of(h.ones) : 0.0;
     const int64_t* rp = m.rowptr;
     if (m.n_ne < n) {
         GCN_TRY(device_alloc_t(&m.ne_rows, (size_t)m.n_ne));

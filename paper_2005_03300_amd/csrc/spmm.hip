@@ -1630,7 +1630,7 @@ static int64_t choose_blocks(const Config& cfg, int64_t nrows, int64_t ncols, in
 // that an L2 holds do not ask.
 static bool worth_a_plan(const Matrix& m, int32_t f, int64_t nnz) {
     const int64_t panel = f < 32 ? f : 32;
-    return f >= 4 && nnz >= (1 << 20) && m.lengths.total() == nnz && m.ncols * panel * 4 > device_info().l2_bytes / 8 * 7;
+    return f >= 4 && nnz >= PLANNED_NNZ && m.lengths.total() == nnz && m.ncols * panel * 4 > device_info().l2_bytes / 8 * 7;
 }
 
 static SpmmPlan& plan_of(gcn_csr* a, Matrix& m, int32_t f, int64_t usual) {
@@ -1643,7 +1643,13 @@ static SpmmPlan& plan_of(gcn_csr* a, Matrix& m, int32_t f, int64_t usual) {
     const SpmmCost c{f, device_info().cus, 8.0, (double)device_info().l2_bytes};
     // the columns of a matrix are the rows of its transpose, where that is stored; otherwise taken to be alike
     const Matrix& t = a->symmetric || &m == &a->At ? a->A : a->At;
-    const Lengths lines = c.lines(t.lengths.total() == nnz ? t.lengths : Lengths::equal(m.ncols, nnz));
+    const bool known = t.lengths.total() == nnz;
+    const Lengths cols = known ? t.lengths : Lengths::equal(m.ncols, nnz), lines = c.lines(cols);
+    if (!even_rows(m.lengths, m.nrows, m.order) || (known && !even_rows(cols, m.ncols, t.order)) || !drawn_columns(cols, m.order)) {
+        p.blocks = p.usual;
+        m.plans.push_back(p);
+        return m.plans.back();
+    }
     double split = 0;
     p.blocks = c.best_blocks(m.lengths, lines, m.ncols, (int)usual, &split);
     // The sweep adds a row's terms one after another: `parts` sums of about 20 terms on average are no further from the exact sum

@@ -945,3 +945,56 @@ def test_a_relu_does_not_change_the_sums(f):
     g.gcn_layer_forward(a, X, torch.eye(f, device="cuda"), Z, Z, T, g.ORDER_SPMM_FIRST)
     assert torch.equal(T, plain) and torch.equal(Z, relu)
     a.close()
+
+
+def drawn_graph(kind, n, pairs, seed):
+    """Endpoints on the GPU: uniform, by a power law with exponent 2.3 (heaviest first), within a band, or mostly inside communities that lie
+    one after another; the last three numbered so that the order of the vertices says something."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    u = lambda: torch.rand(pairs, generator=gen, device="cuda", dtype=torch.float64)
+    if kind == "power":
+        b, i0 = 1 - 1 / 1.3, 20.0
+        return [((u() * ((n + i0) ** b - i0 ** b) + i0 ** b) ** (1 / b) - i0).clamp(0, n - 1).int() for _ in range(2)], gen
+    src = (u() * n).int()
+    if kind == "band":
+        return [src, ((src + torch.randn(pairs, generator=gen, device="cuda") * 5000) % n).int().clamp(0, n - 1)], gen
+    dst = (u() * n).int()
+    if kind == "communities":
+        inside = u() < 0.8
+        dst = torch.where(inside, (src // 5000 * 5000 + (u() * 5000).int()).clamp(max=n - 1), dst)
+    return [src, dst], gen
+
+
+@pytest.mark.parametrize("kind", ["band", "communities", "power"])
+def test_ordered_matrices_keep_the_schedule_of_the_sizes(kind):
+    """The estimates take the vertices' order for random.  Vertices numbered along a band, by communities or by degree: A X runs as A^T X does, by
+    the sizes; the same graph renamed at random does not."""
+    g = G()
+    n, pairs = 500_000, 10_000_000
+    (src, dst), gen = drawn_graph(kind, n, pairs, 171)
+    rename = torch.randperm(n, generator=gen, device="cuda").int()
+    for ordered in (True, False):
+        s, d = (src, dst) if ordered else (rename[src], rename[dst])
+        a = g.gcn_csr_create(n, s, d, g.SYMMETRISE | g.ADD_SELF_LOOPS | g.NORM_SYM | g.BUILD_TRANSPOSE)
+        same = [g.gcn_spmm_describe(a, 0, f) == g.gcn_spmm_describe(a, 1, f) for f in (16, 32, 64)]
+        assert all(same) if ordered else not all(same), (kind, ordered, same)
+        a.close()
+
+
+@pytest.mark.parametrize("nnz", [(1 << 20) - 1, 1 << 20, (1 << 20) + 1, (1 << 20) + 3, (1 << 20) + 2049])
+def test_columns_are_sampled_inside_the_matrix(nnz):
+    """The smallest matrices that are sampled, entries not a multiple of the loads' width, transposes not stored: products as without."""
+    g = G()
+    rs = np.random.default_rng(172)
+    n, nc, f = 30_000, 200_000, 8
+    lengths = rs.multinomial(nnz, np.full(n, 1 / n))
+    rowptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    colidx = np.concatenate([np.sort(rs.choice(nc, k, replace=False)) for k in lengths]).astype(np.int32)
+    val = rs.standard_normal(nnz).astype(np.float32)
+    a = g.gcn_csr_create_from_csr_rect(n, nc, dev(rowptr), dev(colidx), dev(val), 0)
+    X = synth.normal_features(nc, f, 173)
+    want = np.zeros((n, f))
+    np.add.at(want, np.repeat(np.arange(n), lengths), val[:, None].astype(np.float64) * X[colidx])
+    assert_close(host(g.gcn_spmm(a, 0, dev(X), torch.empty(n, f, device="cuda"))), want, str(nnz))
+    a.close()

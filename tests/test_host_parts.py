@@ -155,3 +155,67 @@ def test_a_planned_schedule_without_memory_gives_way_to_the_one_by_sizes(tmp_pat
         }
     """)
     assert r.returncode == 0 and r.stdout == "done", (r.returncode, r.stdout, r.stderr)
+
+
+def test_an_order_of_the_vertices_that_is_not_random_is_told(tmp_path):
+    """Rows of all lengths and columns drawn at random pass; rows sorted by length, denser and sparser halves, and windows that select fewer
+    columns than draws would do not.  Rows that are all alike, empty ones and single ones divide by nothing."""
+    r = run_cpp(tmp_path, """
+        #include <cstdio>
+        #include <random>
+        #include <vector>
+        #include "spmm_cost.h"
+        using namespace gcn;
+        static Lengths lengths(const std::vector<int>& d) {
+            Lengths l;
+            for (int x : d) if (x > 0) { const int b = (int)std::log2((double)x); l.rows[b]++; l.entries[b] += x; }
+            return l;
+        }
+        static RowOrder order(const std::vector<int>& d) {
+            RowOrder o;
+            for (size_t i = 0; i < d.size(); i += RowOrder::GROUP) {
+                double g = 0;
+                for (size_t k = i; k < d.size() && k < i + RowOrder::GROUP; ++k) g += std::min(d[k], (int)RowOrder::LONG);
+                o.sum += g;
+                o.squares += g * g;
+            }
+            return o;
+        }
+        int main() {
+            std::mt19937 gen(7);
+            std::uniform_real_distribution<double> u(0, 1);
+            for (int n : {1, 63, 64, 65, 5000, 200000}) {
+                std::vector<int> poisson(n), power(n), alike(n, 40), none(n, 0), halves(n);
+                std::poisson_distribution<int> p(30), dense(60), thin(15);
+                for (int i = 0; i < n; ++i) {
+                    poisson[i] = p(gen);
+                    power[i] = std::min(20000, (int)(4 * std::pow(u(gen), -0.75)));
+                    halves[i] = i < n / 2 ? dense(gen) : thin(gen);
+                }
+                std::vector<int> sorted = power;
+                std::sort(sorted.begin(), sorted.end());
+                for (auto* d : {&poisson, &power, &alike, &none}) std::printf("%d", even_rows(lengths(*d), n, order(*d)));
+                if (n >= 5000) std::printf("%d%d", even_rows(lengths(sorted), n, order(sorted)), even_rows(lengths(halves), n, order(halves)));
+                std::printf(" ");
+            }
+            // windows of as many entries as drawn, by the table of bits; then of 0.85 times as many
+            const int n = 150000;
+            std::vector<int> d(n);
+            for (int& x : d) x = 1 + (int)(8 * std::pow(u(gen), -0.7));
+            std::vector<int> pick;
+            for (int i = 0; i < n; ++i) for (int k = 0; k < d[i]; ++k) pick.push_back(i);
+            for (double keep : {1.0, 0.85}) {
+                unsigned ones[RowOrder::WINDOWS] = {};
+                for (unsigned& o : ones) {
+                    std::vector<bool> bit(1 << RowOrder::BITS);
+                    for (int k = 0; k < RowOrder::WINDOW * keep; ++k) bit[RowOrder::bit_of((uint32_t)pick[(size_t)(u(gen) * pick.size())])] = true;
+                    for (bool b : bit) o += b;
+                }
+                RowOrder o;
+                std::printf("%d", drawn_columns(lengths(d), o));             // not sampled
+                o.distinct = RowOrder::distinct_of(ones);
+                std::printf("%d ", drawn_columns(lengths(d), o));
+            }
+        }
+    """)
+    assert r.returncode == 0 and r.stdout.split() == ["1111"] * 4 + ["111100"] * 2 + ["01", "00"], (r.returncode, r.stdout, r.stderr)
