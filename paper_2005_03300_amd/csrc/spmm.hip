@@ -1652,15 +1652,15 @@ static SpmmPlan& plan_of(gcn_csr* a, Matrix& m, int32_t f, int64_t usual) {
     }
     double split = 0;
     p.blocks = c.best_blocks(m.lengths, lines, m.ncols, (int)usual, &split);
-    // The sweep adds a row's terms one after another: `parts` sums of about 20 terms on average are no further from the exact sum
-    // than those of the nonzero split, which adds slices of 32 or 64 terms (30 M pairs, 1 M vertices, 16 columns: 10.0e-8 of
-    // the norm there, 14.1, 10.5, 9.1 and 8.5e-8 with one to four parts; a part costs 6 % of the product).
-    constexpr int HEAVY = 8;                                    // rows of 2^8 entries and more are long
-    const int64_t mean = nnz / (m.n_ne > 0 ? m.n_ne : 1);
-    const int parts = (int)std::max<int64_t>(1, (mean + 20) / 21);
+    constexpr int HEAVY = 8, MOST_PARTS = 8;                    // rows of 2^8 entries and more are long
     int heavy_blocks = 1;
     const int32_t W = f <= 16 ? 16 : 32;
-    const double sweep = c.sweep(m.lengths, lines, m.nrows, m.ncols, HEAVY, sweep_rows(W), SWEEP_TASKS, parts, &heavy_blocks);
+    double sweep = c.sweep(m.lengths, lines, m.nrows, m.ncols, HEAVY, sweep_rows(W), SWEEP_TASKS, 1, &heavy_blocks);
+    // As many sums per row as keep them as close to the exact ones as the nonzero split's (see as_exact; 30 M pairs, 1 M vertices, 16
+    // columns: 10.0e-8 of the norm there, 14.1, 10.5, 9.1 and 8.5e-8 with one to four; another costs 6 % of the product).
+    int parts = 1;
+    while (parts <= MOST_PARTS && !c.as_exact(m.lengths, p.usual, heavy_blocks, parts, HEAVY, a->inv_sqrt_deg != nullptr)) ++parts;
+    if (parts > 1) sweep = parts > MOST_PARTS ? 1e30 : c.sweep(m.lengths, lines, m.nrows, m.ncols, HEAVY, sweep_rows(W), SWEEP_TASKS, parts, &heavy_blocks);
     // Above 0.84 the hub schedule, which this does not estimate, may be as fast (246 M entries, 14 M vertices, R-MAT at 16 columns:
     // 0.86, both 2.98 ms), and the sweep's copy takes longer to build.  Ragged rows in two panels straddle lines twice (41
     // columns: no gain).

@@ -151,15 +151,15 @@ struct SpmmCost {
         return t;
     }
 
-    // The number of blocks that costs least, `usual` unless another is 6 % better.  Up to 16 columns no
-    // fewer than usual (15 M pairs, R-MAT, 150 K vertices: 122 us over five, 131 over one, estimated 117 and 103).
+    // The number of blocks that costs least, `usual` unless another is 6 % better.  No fewer than usual: the pieces of a sum would be
+    // longer, and its error larger.
     int best_blocks(const Lengths& rows, const Lengths& lines, int64_t ncols, int usual, double* cost) const {
         static const int tried[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96};
         int best = usual;
         double least = split(rows, lines, usual);
         const double keep = least * 0.94;
         for (int b : tried) {
-            if (b == usual || (b > 1 && ncols / b < 2048) || (f <= 16 && b < usual)) continue;
+            if (b == usual || (b > 1 && ncols / b < 2048) || b < usual) continue;
             const double t = split(rows, lines, b);
             if (t < keep && t < least) { least = t; best = b; }
         }
@@ -193,6 +193,58 @@ struct SpmmCost {
             t += 1.41 * h + 8.0;
         }
         return t;
+    }
+
+    // ---- rounding errors ----
+    // Every addition rounds in proportion to what has been added up; with terms alike in size the squares of these errors add up to
+    // the number of terms in each sum so far, over all additions.  One chain of k terms:
+    static double chain(double k) { return 0.5 * k * (k + 1); }
+    // A row of `length` entries in the nonzero split over `blocks` blocks: chains that end where a lane group's slice of `slice`
+    // entries does, wherever the row starts, joined in pairs; the blocks' sums are added one after another.
+    static double split_error(double length, int slice, int blocks) {
+        const double most = std::min(length, 2048.0);             // beyond that rows are alike: the slices bound the chains
+        const double b = std::max(1.0, std::min((double)blocks, std::floor(most)));
+        const int len = std::max(1, (int)(most / b + 0.5));
+        double sum = 0, p[2048 / 32 + 2];
+        const int step = slice / 16;
+        for (int o = 0; o < slice; o += step) {
+            int k = 0;
+            for (int at = 0, end = slice - o; at < len; at = end, end += slice) p[k++] = std::min(end, len) - at;
+            for (int i = 0; i < k; ++i) sum += chain(p[i]);
+            for (; k > 1; k = (k + 1) / 2)
+                for (int i = 0; i < k; i += 2) {
+                    if (i + 1 < k) sum += p[i] + p[i + 1];
+                    p[i / 2] = p[i] + (i + 1 < k ? p[i + 1] : 0);
+                }
+        }
+        return b * sum / 16 + (most / b) * (0.5 * b * (b + 1) - 1.0);
+    }
+    // In the sweep: `parts` chains, of which each entry is in one or another, added one after another.
+    static double sweep_error(double length, int parts) {
+        const double p = parts, pieces = p * (1.0 - std::pow(1.0 - 1.0 / p, length));
+        return 0.5 * (length * length / p + length * (1.0 - 1.0 / p) + length) +
+               (pieces > 1 ? (length / pieces) * (0.5 * pieces * (pieces + 1) - 1.0) : 0.0);
+    }
+    // Over all rows, whose terms are in proportion to length^(power/2).  parts = 0: the nonzero split over `blocks`; otherwise rows below
+    // 2^heavy entries in the sweep, the others over `blocks`.
+    double error(const Lengths& rows, int blocks, int parts, int heavy, int power) const {
+        double sum = 0;
+        for (int b = 0; b < Lengths::BINS; ++b) {
+            if (rows.rows[b] <= 0) continue;
+            const double l = (double)rows.entries[b] / (double)rows.rows[b];
+            sum += (double)rows.rows[b] * std::pow(l, power) *
+                   (parts > 0 && b < heavy ? sweep_error(l, parts) : split_error(l, f <= 16 ? 32 : 64, blocks));
+        }
+        return sum;
+    }
+    // Whether sums in that schedule are as close to the exact ones as in the nonzero split over `usual` blocks.  Values 1 / sqrt(d_i d_j)
+    // make the terms of a long row small (`normalised`); of others nothing is known: they may be alike, or 1 / d_i.
+    bool as_exact(const Lengths& rows, int usual, int blocks, int parts, int heavy, bool normalised) const {
+        for (int power : {0, -1, -2}) {
+            if ((power == -1) != normalised) continue;
+            if (error(rows, blocks, parts, heavy, power) > error(rows, usual, 0, heavy, power)) return false;
+        }
+        return true;
     }
 };
 

@@ -998,3 +998,34 @@ def test_columns_are_sampled_inside_the_matrix(nnz):
     np.add.at(want, np.repeat(np.arange(n), lengths), val[:, None].astype(np.float64) * X[colidx])
     assert_close(host(g.gcn_spmm(a, 0, dev(X), torch.empty(n, f, device="cuda"))), want, str(nnz))
     a.close()
+
+
+@pytest.mark.parametrize("kind,mean", [("uniform", 12), ("uniform", 17), ("uniform", 21), ("uniform", 41), ("power", 13), ("power", 20), ("power", 41)])
+@pytest.mark.parametrize("norm", ["sym", "row"])
+def test_schedules_by_cost_are_no_less_exact(kind, mean, norm):
+    """The error of A X against sums in 64 bits is no larger than that of the nonzero split, whatever schedule is taken, at mean rows where one sum
+    per row in the sweep would be a longer chain; values 1 / sqrt(d_i d_j), whose long rows are small, and 1 / d_i."""
+    g = G()
+    n = 800_000
+    (src, dst), gen = drawn_graph(kind, n, n * (mean - 1) // (2 if norm == "sym" else 1), 174)
+    rename = torch.randperm(n, generator=gen, device="cuda").int()
+    flags = g.SYMMETRISE | g.NORM_SYM if norm == "sym" else g.NORM_ROW
+    a = g.gcn_csr_create(n, rename[src], rename[dst], flags | g.ADD_SELF_LOOPS | g.BUILD_TRANSPOSE)
+    rowptr, colidx, val, _ = a.arrays(False)
+    rows = torch.repeat_interleave(torch.arange(n, device="cuda"), rowptr[1:] - rowptr[:-1])
+    for f in (16, 32):
+        X = torch.rand(n, f, generator=gen, device="cuda") * 2 - 1
+        exact = torch.zeros(n, f, dtype=torch.float64, device="cuda")
+        for k in range(0, a.nnz, 1 << 22):
+            part = slice(k, k + (1 << 22))
+            exact.index_add_(0, rows[part], val[part, None].double() * X[colidx[part].long()])
+        error = []
+        for algo in (0, 2):
+            g.gcn_csr_config(a, g.CFG_SPMM_ALGO, algo)
+            g.gcn_csr_config(a, g.CFG_SPMM_BLOCKS, 1 if algo else 0)
+            error.append(float((g.gcn_spmm(a, 0, X, torch.empty(n, f, device="cuda")).double() - exact).norm() / exact.norm()))
+        g.gcn_csr_config(a, g.CFG_SPMM_ALGO, 0)
+        g.gcn_csr_config(a, g.CFG_SPMM_BLOCKS, 0)
+        print(kind, mean, norm, f, g.gcn_spmm_describe(a, 0, f)[:90], error)
+        assert error[0] <= 1.005 * error[1], (kind, mean, norm, f, g.gcn_spmm_describe(a, 0, f), error)
+    a.close()

@@ -219,3 +219,70 @@ def test_an_order_of_the_vertices_that_is_not_random_is_told(tmp_path):
         }
     """)
     assert r.returncode == 0 and r.stdout.split() == ["1111"] * 4 + ["111100"] * 2 + ["01", "00"], (r.returncode, r.stdout, r.stderr)
+
+
+def test_estimated_rounding_errors(tmp_path):
+    """The squared error of a row's sum in either schedule, in units of one rounding of one term, against sums added up in single precision in that
+    very order; and the number of sums per row that follows is no less exact than the nonzero split for rows of 12 to 200 entries."""
+    r = run_cpp(tmp_path, """
+        #include <cstdio>
+        #include <random>
+        #include <vector>
+        #include "spmm_cost.h"
+        using namespace gcn;
+        int main() {
+            std::mt19937 gen(11);
+            std::uniform_real_distribution<double> value(-1, 1), u(0, 1);
+            const int rows = 6000;
+            double unit = 0;
+            for (int length : {16, 20, 41, 100})
+                for (int parts = 0; parts <= 3; ++parts) {
+                    double square = 0;
+                    for (int r = 0; r < rows; ++r) {
+                        std::vector<std::vector<double>> piece(1);
+                        double exact = 0;
+                        const int offset = (int)(u(gen) * 32);
+                        std::vector<int> in(length);
+                        for (int& p : in) p = (int)(u(gen) * std::max(1, parts));
+                        std::sort(in.begin(), in.end());
+                        for (int k = 0; k < length; ++k) {
+                            if (k > 0 && (parts ? in[k] != in[k - 1] : (k + offset) % 32 == 0)) piece.emplace_back();
+                            piece.back().push_back(value(gen) * 0.3);
+                            exact += piece.back().back();
+                        }
+                        std::vector<float> sum;
+                        for (auto& p : piece) {
+                            float s = 0;
+                            for (double x : p) s = (float)((double)s + x);
+                            sum.push_back(s);
+                        }
+                        if (parts) for (size_t i = 1; i < sum.size(); ++i) sum[0] = sum[0] + sum[i];
+                        else
+                            while (sum.size() > 1) {
+                                std::vector<float> next;
+                                for (size_t i = 0; i < sum.size(); i += 2) next.push_back(i + 1 < sum.size() ? sum[i] + sum[i + 1] : sum[i]);
+                                sum = next;
+                            }
+                        square += (sum[0] - exact) * (sum[0] - exact) / rows;
+                    }
+                    const double model = parts ? SpmmCost::sweep_error(length, parts) : SpmmCost::split_error(length, 32, 1);
+                    if (unit == 0) unit = square / model;
+                    const double ratio = std::sqrt(square / (model * unit));
+                    if (ratio < 0.9 || ratio > 1.1) std::printf("length %d parts %d: %.2f ", length, parts, ratio);
+                }
+            for (int mean : {12, 16, 20, 21, 25, 41, 61, 100, 200})
+                for (int f : {16, 32}) {
+                    const SpmmCost c{f, 256, 8.0, 4.0 * (1 << 20)};
+                    const Lengths l = Lengths::equal(1 << 20, (int64_t)mean << 20);
+                    for (bool normalised : {false, true}) {
+                        int parts = 1;
+                        while (parts < 20 && !c.as_exact(l, 1, 1, parts, 8, normalised)) ++parts;
+                        if (SpmmCost::sweep_error(mean, parts) > SpmmCost::split_error(mean, f <= 16 ? 32 : 64, 1) || parts < 2 || parts > 8)
+                            std::printf("mean %d f %d: %d sums ", mean, f, parts);
+                    }
+                    if (!c.as_exact(l, 4, 4, 0, 8, true) || c.as_exact(l, 4, 2, 0, 8, true)) std::printf("blocks %d %d ", mean, f);
+                }
+            std::printf("done");
+        }
+    """)
+    assert r.returncode == 0 and r.stdout == "done", (r.returncode, r.stdout, r.stderr)
