@@ -94,6 +94,8 @@ struct Sweep {
     int32_t heavy_threshold = 0;
     int64_t ntasks = 0, nnz_light = 0, nnz_heavy = 0, n_heavy = 0;
     int64_t padded = 0;           // entries stored, padding included
+    bool built = false;           // or counted only and found to be sparser than was asked for
+    bool sparser(double most) const { return most > 0 && (double)padded > most * (double)nnz_light; }
     int32_t* colidx = nullptr;    // [padded] column
     float* val = nullptr;         // [padded]
     uint16_t* lrow = nullptr;     // [padded] row inside the task, rb for a padding entry
@@ -297,9 +299,10 @@ int build_fix_list(const uint32_t* flags, const int32_t* sub_row, const int64_t*
 int build_blocked(Matrix& m, int64_t nnz, int64_t cols_per_block, hipStream_t s);
 // make m.blk / m.swp the copy with the given key: the current one, a parked one, or a newly built one
 int want_blocked(Matrix& m, int64_t nnz, int64_t cols_per_block, hipStream_t s);
-int want_sweep(Matrix& m, int64_t nnz, int32_t groups, int32_t rb, int32_t heavy_threshold, hipStream_t s);
+// most > 0: a copy that would store more than `most` places per entry (see Sweep::sparser) is not built
+int want_sweep(Matrix& m, int64_t nnz, int32_t groups, int32_t rb, int32_t heavy_threshold, double most, hipStream_t s);
 void free_blocked(Blocked& b);
-int build_sweep(Matrix& m, int64_t nnz, int32_t groups, int32_t rb, int32_t heavy_threshold, hipStream_t s);
+int build_sweep(Matrix& m, int64_t nnz, int32_t groups, int32_t rb, int32_t heavy_threshold, double most, hipStream_t s);
 void free_sweep(Sweep& w);
 int build_hub(Matrix& m, int64_t nnz, int64_t H, int64_t cpb, int32_t dmin, hipStream_t s);
 void free_hub(Hub& h);

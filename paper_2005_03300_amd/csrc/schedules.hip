@@ -317,7 +317,7 @@ __global__ void k_heavy_len(int64_t nh, const int32_t* __restrict__ rows, const 
     if (q == nh) len[q] = 0;
 }
 
-int build_sweep(Matrix& m, int64_t nnz, int32_t groups, int32_t rb, int32_t asked_th, hipStream_t s) {
+int build_sweep(Matrix& m, int64_t nnz, int32_t groups, int32_t rb, int32_t asked_th, double most, hipStream_t s) {
     free_sweep(m.swp);
     Sweep& w = m.swp;
     const int32_t set = 2 * groups;
@@ -377,7 +377,14 @@ int build_sweep(Matrix& m, int64_t nnz, int32_t groups, int32_t rb, int32_t aske
     GCN_HIP_TRY(hipStreamSynchronize(s));
     const int64_t nnz_heavy = nnz - nnz_light;
     const int64_t padded = last_base + last_plen;
+    w.groups = groups;
+    w.rb = rb;
+    w.heavy_threshold = asked_th;
+    w.ntasks = ntasks;
     w.padded = padded;
+    w.nnz_light = nnz_light;
+    w.nnz_heavy = nnz_heavy;
+    if (w.sparser(most)) return GCN_OK;
 
     GCN_TRY(device_alloc_t(&w.colidx, (size_t)padded));
     GCN_TRY(device_alloc_t(&w.val, (size_t)padded));
@@ -433,13 +440,8 @@ int build_sweep(Matrix& m, int64_t nnz, int32_t groups, int32_t rb, int32_t aske
         count_build();
     }
     GCN_HIP_TRY(hipStreamSynchronize(s));
-    w.groups = groups;
-    w.rb = rb;
-    w.heavy_threshold = asked_th;
-    w.ntasks = ntasks;
-    w.nnz_light = nnz_light;
-    w.nnz_heavy = nnz_heavy;
     w.n_heavy = w.heavy ? w.heavy->n_ne : 0;
+    w.built = true;
     count_build();
     return GCN_OK;
 }

@@ -1669,6 +1669,7 @@ static SpmmPlan& plan_of(gcn_csr* a, Matrix& m, int32_t f, int64_t usual) {
         p.blocks = heavy_blocks;
         p.parts = parts;
         p.heavy = (1 << HEAVY) - 1;
+        p.padding = c.padding(m.lengths.below(HEAVY), m.nrows, sweep_rows(W));
     }
     m.plans.push_back(p);
     return m.plans.back();
@@ -1883,8 +1884,10 @@ int want_blocked(Matrix& m, int64_t nnz, int64_t cpb, hipStream_t s) {
     return rc;
 }
 
-int want_sweep(Matrix& m, int64_t nnz, int32_t groups, int32_t rb, int32_t th, hipStream_t s) {
-    auto is = [&](const Sweep& w) { return w.groups == groups && w.rb == rb && w.heavy_threshold == th; };
+int want_sweep(Matrix& m, int64_t nnz, int32_t groups, int32_t rb, int32_t th, double most, hipStream_t s) {
+    auto is = [&](const Sweep& w) {
+        return w.groups == groups && w.rb == rb && w.heavy_threshold == th && (w.built || w.sparser(most));
+    };
     if (is(m.swp)) return GCN_OK;
     if (m.swp.groups != 0) {
         m.swp_parked.push_back(m.swp);
@@ -1897,7 +1900,7 @@ int want_sweep(Matrix& m, int64_t nnz, int32_t groups, int32_t rb, int32_t th, h
             return GCN_OK;
         }
     BuildScope scope(s);
-    const int rc = build_sweep(m, nnz, groups, rb, th, s);
+    const int rc = build_sweep(m, nnz, groups, rb, th, most, s);
     if (rc != GCN_OK) {
         (void)hipStreamSynchronize(s);
         free_sweep(m.swp);
@@ -2017,6 +2020,23 @@ static int launch_product(gcn_csr* a, Matrix& m, int32_t f, const float* X, int6
         } else nblocks = p.blocks;
     }
     if (rowwise_only(m, ldx, Z, ldz, epilogue, Zprev, ldzprev)) algo = 1;
+    const int sweep_lanes = f <= 16 ? 4 : 8;
+    const int32_t rb = sweep_rows(4 * sweep_lanes);
+    if (algo == 3) {
+        // How many places the copy takes shows when it is built, not in the lengths of the rows: where the rows of a task select runs of
+        // columns that its other rows do not, few of them fill a set (rows of 41 on columns 41 i on: 8 places per entry, 1834 us
+        // where the nonzero split takes 394).  Such a matrix goes on without it, by the sizes.  Planned copies of 700 renamed graphs
+        // took 1.03 at the most, those chosen by sizes (rows up to 1024 entries, R-MAT) 1.53; at 2.2 the walk is slower than the gathers it saves.
+        const double most = cfg.spmm_algo == 3 ? 0.0 : (*plan ? 1.25 * (*plan)->padding : 2.0);
+        GCN_TRY(want_sweep(m, nnz, 64 / sweep_lanes, rb, heavy, most, s));
+        if (m.swp.sparser(most)) {
+            algo = 2;
+            if (*plan) {
+                (*plan)->give_way();
+                nblocks = (*plan)->blocks;
+            }
+        }
+    }
     if ((algo == 2 && cfg.spmm_algo == 0) || algo == 4) {
         // Hub schedule: for operands beyond the L2s when most entries sit in long rows and hot columns
         // (decided from the matrix itself when the copy is built; a rejected shape is remembered).
@@ -2041,10 +2061,7 @@ static int launch_product(gcn_csr* a, Matrix& m, int32_t f, const float* X, int6
     }
     if (algo == 3) {
         took(a, GCN_SCHED_SWEEP);
-        const int LPRs = f <= 16 ? 4 : 8;
-        const int W = LPRs * 4;
-        const int32_t rb = sweep_rows(W);
-        GCN_TRY(want_sweep(m, nnz, 64 / LPRs, rb, heavy, s));
+        const int LPRs = sweep_lanes, W = LPRs * 4;
         const Sweep& w = m.swp;
         if (o.describe) {
             const int64_t cap = (int64_t)device_info().cus * sweep_tasks(cfg);

@@ -167,6 +167,15 @@ struct SpmmCost {
         return best;
     }
 
+    // Places that the sweep stores per entry: a row takes one pair of steps per entry, so there is padding where a task's longest row has
+    // more than its share.
+    double padding(const Lengths& light, int64_t nrows, int32_t task_rows) const {
+        int longest = 1;
+        for (int b = 0; b < Lengths::BINS; ++b) if (light.rows[b] > 0) longest = b < 30 ? 2 << b : longest;
+        const double places = 2.0 * (64 / (panel() / 4));
+        return std::max(1.0, 0.55 * longest * places / (task_rows * (double)light.total() / (double)nrows));
+    }
+
     // Column sweep: rows below 2^heavy entries in `tasks_per_cu` tasks of `task_rows` per compute unit, `parts` sums per row; the
     // others by the nonzero split (*heavy_blocks receives over how many blocks).
     double sweep(const Lengths& rows, const Lengths& lines, int64_t nrows, int64_t ncols, int heavy, int32_t task_rows, int tasks_per_cu,
@@ -177,11 +186,7 @@ struct SpmmCost {
         const int panels = (f + panel() - 1) / panel();
         *heavy_blocks = 1;
         if (nl <= 0) return 1e30;
-        // a row takes one pair of steps per entry: padding where a task's longest row has more than its share
-        int longest = 1;
-        for (int b = 0; b < heavy; ++b) if (light.rows[b] > 0) longest = 2 << b;
-        const double places = 2.0 * (64 / (panel() / 4));
-        const double pad = std::max(1.0, 0.55 * longest * places / (task_rows * nl / (double)nrows));
+        const double pad = padding(light, nrows, task_rows);
         const double fetched = nl * pad;
         const double m = launches * xcds * misses(lines, 1.0, nl / launches / xcds, true) + fetched * 10 / 128;
         const double through = std::max(fetched / 130e3, m / 54e3);
@@ -285,7 +290,9 @@ struct SpmmPlan {
     int32_t blocks = 1;          // column blocks: of the matrix, or of the sweep's long rows
     int32_t parts = 1, heavy = 0;// sweep: sums per row, long-row threshold
     int32_t usual = 1;           // blocks by the sizes alone
+    double padding = 1;          // sweep: places per entry, estimated
     bool by_sizes() const { return !sweep && blocks == usual; }
+    void give_way() { sweep = false; blocks = usual; }
 };
 
 // Runs a product (`run` leaves the plan it followed, if any, in its argument).  The stored order of a planned schedule is there for
@@ -295,8 +302,7 @@ int run_or_by_sizes(int out_of_memory, const Run& run) {
     SpmmPlan* plan = nullptr;
     const int rc = run(&plan);
     if (rc != out_of_memory || !plan || plan->by_sizes()) return rc;
-    plan->sweep = false;
-    plan->blocks = plan->usual;
+    plan->give_way();
     plan = nullptr;
     return run(&plan);
 }

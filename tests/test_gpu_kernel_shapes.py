@@ -1029,3 +1029,31 @@ def test_schedules_by_cost_are_no_less_exact(kind, mean, norm):
         print(kind, mean, norm, f, g.gcn_spmm_describe(a, 0, f)[:90], error)
         assert error[0] <= 1.005 * error[1], (kind, mean, norm, f, g.gcn_spmm_describe(a, 0, f), error)
     a.close()
+
+
+@pytest.mark.parametrize("n,k,f,usual", [(500_000, 41, 16, "split("), (500_000, 41, 32, "split("), (600_000, 100, 32, "split(")])
+def test_rows_that_fill_no_set_are_not_swept(n, k, f, usual):
+    """Row i selects the columns k i to k i + k - 1 (mod n): as long as the rows and columns of a uniform matrix, and as many different columns, but
+    a task's rows come one after the other and a sweep copy would be padding for the most part.  Neither the estimates nor (mean of 64
+    and more) the sizes take it, it is asked for once, and the product is right; asked for by the caller it is built."""
+    g = G()
+    rowptr = torch.arange(0, (n + 1) * k, k, device="cuda")
+    cols = (torch.arange(n, device="cuda")[:, None] * k + torch.arange(k, device="cuda")) % n
+    a = g.gcn_csr_create_from_csr(n, rowptr, cols.sort(1).values.int().reshape(-1), None, 0)
+    assert g.gcn_spmm_describe(a, 0, f).startswith(usual)
+    built = g.gcn_build_count()
+    X = torch.rand(n, f, device="cuda") * 2 - 1
+    Z = g.gcn_spmm(a, 0, X, torch.empty(n, f, device="cuda"))
+    g.gcn_spmm(a, 0, X, Z)
+    assert g.gcn_build_count() == built
+    want = torch.zeros(n, f, device="cuda", dtype=torch.float64)
+    for c in cols.unbind(1):
+        want += X[c]
+    assert_close(host(Z), host(want), f"{n} {k} {f}")
+    if n == 500_000 and f == 16:
+        g.gcn_csr_config(a, g.CFG_SPMM_ALGO, 3)
+        assert g.gcn_spmm_describe(a, 0, f).startswith("sweep(")
+        assert_close(host(g.gcn_spmm(a, 0, X, Z)), host(want), "asked for")
+        g.gcn_csr_config(a, g.CFG_SPMM_ALGO, 0)
+        assert g.gcn_spmm_describe(a, 0, f).startswith(usual)
+    a.close()
