@@ -321,10 +321,9 @@ int build_sweep(Matrix& m, int64_t nnz, int32_t groups, int32_t rb, int32_t aske
     free_sweep(m.swp);
     Sweep& w = m.swp;
     const int32_t set = 2 * groups;
-    // a row takes one set per entry at the least: with this bound task_len stays below 2^31 whatever the setting
-    const int32_t heavy_th = asked_th < 1 << 20 ? asked_th : 1 << 20;
     if (nnz <= 0 || rb <= 0 || rb > 4096 || (groups != 8 && groups != 16))
         return fail(GCN_ERR_BADARG, "build_sweep: bad parameters");
+    const int32_t heavy_th = asked_th < longest_swept(rb, set) ? asked_th : longest_swept(rb, set);
     const int64_t n = m.nrows;
     const int64_t ntasks = (n + rb - 1) / rb;
     const unsigned cbits = bits_for(m.ncols);

@@ -87,6 +87,10 @@ struct Lengths {
     }
 };
 
+// The longest row that may go into a sweep copy of tasks of `rb` rows, whose places are counted in 32 bits: at worst every entry of a task
+// makes a set of its own, and the last trip (at most 8 sets) is filled up.
+inline int32_t longest_swept(int32_t rb, int32_t set) { return (int32_t)((INT32_MAX / set - 8) / rb); }
+
 struct SpmmCost {
     int32_t f;                   // columns of the operand
     int cus;

@@ -121,6 +121,25 @@ def test_estimated_costs_of_ragged_rows(tmp_path):
     assert r.returncode == 0 and r.stdout.split() == ["1"] * 4 + ["11", "11", "10", "21", "10", "21", "31", "41"], (r.returncode, r.stdout, r.stderr)
 
 
+def test_places_of_a_sweep_task_fit_32_bits(tmp_path):
+    """A task whose rows are as long as the sweep takes them, every entry in a set of its own and the last trip filled up, has fewer than
+    2^31 places, at the task heights in use and at the least and the greatest; no such row is left out without need."""
+    r = run_cpp(tmp_path, """
+        #include <cstdio>
+        #include "spmm_cost.h"
+        using namespace gcn;
+        int main() {
+            for (int rb : {1, 255, 511, 4096})
+                for (int set : {16, 32}) {
+                    const int64_t trip = 4 * set, longest = longest_swept(rb, set);
+                    const int64_t places = (rb * longest * set + trip - 1) / trip * trip, more = rb * (longest + 1) * set + 8 * set;
+                    std::printf("%d ", longest > 1024 && places <= INT32_MAX && more > INT32_MAX);
+                }
+        }
+    """)
+    assert r.returncode == 0 and r.stdout.split() == ["1"] * 8, (r.returncode, r.stdout, r.stderr)
+
+
 def test_a_planned_schedule_without_memory_gives_way_to_the_one_by_sizes(tmp_path):
     """A product whose planned stored order cannot be allocated runs by sizes, then and later; any other error, and no memory for the
     schedule of the sizes itself, is the caller's."""
