@@ -727,11 +727,12 @@ def test_softmax_of_ragged_rows(n, C, pad, off):
     assert abs(loss.item() - nll) <= 1e-5 * max(1.0, abs(nll))
 
 
-@pytest.mark.parametrize("chunks", [769, 772, 799, 800, 801, 831, 833])
-@pytest.mark.parametrize("f", [16, 31, 41, 64])
-def test_column_blocks_walked_by_one_xcd_each(chunks, f):
+@pytest.mark.parametrize("f,kernel,chunks", [(f, kernel, least + more) for f, kernel, least in (
+    (16, "k_spmm_split<4,4>", 769), (31, "k_spmm_split<32,1>", 769), (64, "k_spmm_split<16,4>", 769),
+    (41, "k_spmm_line<1>", 1025), (67, "k_spmm_line<2>", 1025)) for more in (0, 3, 30, 31, 32, 62, 64)])
+def test_column_blocks_walked_by_one_xcd_each(f, kernel, chunks):
     """Over column blocks an XCD takes one stretch of the chunks: numbers of chunks that leave the last stretch short, or the last
-    workgroup without one, in both kernels that take so many chunks."""
+    workgroup without one, in both kernels that take so many chunks (fewer go to others, which do not deal them out)."""
     g = G()
     lengths = np.full(chunks, 512)
     lengths[::9] -= 40
@@ -741,6 +742,7 @@ def test_column_blocks_walked_by_one_xcd_each(chunks, f):
     X = synth.uniform_features(2500, f, 133)
     a = g.gcn_csr_create_from_csr_rect(len(lengths), 2500, dev(rowptr), dev(colidx), dev(val), 0)
     g.gcn_csr_config(a, g.CFG_SPMM_BLOCKS, 2)
+    assert f"chunks={chunks},kernel={kernel}" in g.gcn_spmm_describe(a, 0, f)
     Zd = torch.full((len(lengths), f), float("nan"), device="cuda")
     g.gcn_spmm(a, 0, dev(X), Zd)
     A = torch.sparse_csr_tensor(torch.from_numpy(rowptr), torch.from_numpy(colidx).long(), torch.from_numpy(val).double(), (len(lengths), 2500))
