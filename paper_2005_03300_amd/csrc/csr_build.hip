@@ -287,18 +287,6 @@ __global__ void k_ne_rowptr(int64_t n_ne, int64_t nnz, const int32_t* __restrict
 
 // ---- host helpers ---------------------------------------------------------------------------------
 
-// From sorted distinct keys (row<<cbits|col, ordered by row; or by column when `by_col`, then the roles change) fill
-// rowptr/colidx of `m` (allocates them).
-static int compress_keys(Matrix& m, int64_t n, int64_t nnz, const uint64_t* keys, unsigned cbits, bool by_col, hipStream_t s) {
-    GCN_TRY(device_alloc_t(&m.rowptr, (size_t)n + 1));
-    GCN_TRY(device_alloc_t(&m.colidx, (size_t)nnz));
-    const uint64_t cmask = (1ull << cbits) - 1;
-    if (by_col) hipLaunchKernelGGL(k_compress, dim3(blocks_for(nnz)), dim3(TPB), 0, s, nnz, n, keys, 0u, cmask, cbits, ~0ull, m.rowptr, m.colidx);
-    else hipLaunchKernelGGL(k_compress, dim3(blocks_for(nnz)), dim3(TPB), 0, s, nnz, n, keys, cbits, ~0ull, 0u, cmask, m.rowptr, m.colidx);
-    GCN_LAUNCH_CHECK();
-    return GCN_OK;
-}
-
 // The chunks c >= 1 whose first entry continues a row begun earlier and that are the first such chunk
 // of that row: exactly the chunks for which the fix-up kernel has work.  `covered`: only those in which no row starts,
 // otherwise only the others.
@@ -428,7 +416,11 @@ static int build_transpose(gcn_csr* a, const uint64_t* keys, unsigned cbits, uin
         GCN_TRY((prims::radix_sort<uint64_t, float>(keys, scratch_keys, a->A.val, a->At.val, (size_t)nnz, cbits, false, s, false)));
     a->At.nrows = n;
     a->At.ncols = a->n;
-    GCN_TRY(compress_keys(a->At, n, nnz, scratch_keys, cbits, true, s));
+    GCN_TRY(device_alloc_t(&a->At.rowptr, (size_t)n + 1));
+    GCN_TRY(device_alloc_t(&a->At.colidx, (size_t)nnz));
+    hipLaunchKernelGGL(k_compress, dim3(blocks_for(nnz)), dim3(TPB), 0, s, nnz, n, scratch_keys, 0u, (1ull << cbits) - 1, cbits, ~0ull,
+                       a->At.rowptr, a->At.colidx);
+    GCN_LAUNCH_CHECK();
     GCN_TRY(build_schedule(a->At, n, nnz, s));
     a->has_t = true;
     return GCN_OK;
