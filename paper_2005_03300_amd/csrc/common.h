@@ -329,6 +329,7 @@ struct SpmmOpt {
     // such element moves the gradient of the weights by 1e-4 of its norm.
     bool any_schedule = false;
     LayerEnd* end = nullptr;          // only with the epilogue GCN_EPI_NONE
+    bool narrow = false;              // internal, see SpmmPlan::narrow
     // internal to the hub schedule:
     const uint8_t* defer = nullptr;   // rows whose sum is stored raw (no scale, no epilogue)
     bool accumulate = false;          // column-blocked reduce adds to what Z already holds

@@ -1562,9 +1562,8 @@ static SplitChoice choose_split(int32_t f, int64_t nchunks, bool any_order, bool
     }
     // Wider operands are processed in panels of 32 columns (one 128-byte line per gathered row): the panel of X that the
     // gathers touch is 4x smaller than at f = 128, so far more of it stays in L2, at the price of re-reading the
-    // index/value stream once per panel.  Over column blocks, too: with blocks that suit a panel of 32 two passes beat one
-    // of 64 (40 M entries, 200 K vertices, 64 columns: 660 us and 820; 115 M, 233 K: 1530 and 1560).  The products
-    // that keep the schedule of their sizes alone (`wide`) have it in panels of 64 there, and with it their sums' order.
+    // index/value stream once per panel.  Over column blocks (`wide`) 64 unless a plan says otherwise (see SpmmCost::narrow_panels);
+    // the products that keep the schedule of their sizes alone have no plan, and with the panels they keep their sums' order.
     // Rows that are not whole 16-byte pieces (only without an order to keep) straddle lines wherever they are cut: one
     // panel up to 64 columns (41 columns, 1 M rows: 1.20 ms in two panels, 0.89 in one).
     int lpr = 8;
@@ -1651,7 +1650,11 @@ static SpmmPlan& plan_of(gcn_csr* a, Matrix& m, int32_t f, int64_t usual) {
         return m.plans.back();
     }
     double split = 0;
-    p.blocks = c.best_blocks(m.lengths, lines, m.ncols, (int)usual, &split);
+    p.narrow = c.narrow_panels(lines, (int)usual);
+    // (rows beyond 64 columns that are not whole 16-byte pieces: by the sizes, in panels of 64, which are not estimated)
+    const double must = f > 64 && f % 4 != 0 && usual >= 2 ? 0.0 : c.must_save((int)usual, p.narrow);
+    p.blocks = c.best_blocks(m.lengths, lines, m.ncols, (int)usual, must, &split);
+    p.narrow = p.narrow || p.blocks > usual;
     constexpr int HEAVY = 8, MOST_PARTS = 8;                    // rows of 2^8 entries and more are long
     int heavy_blocks = 1;
     const int32_t W = f <= 16 ? 16 : 32;
@@ -1661,12 +1664,11 @@ static SpmmPlan& plan_of(gcn_csr* a, Matrix& m, int32_t f, int64_t usual) {
     int parts = 1;
     while (parts <= MOST_PARTS && !c.as_exact(m.lengths, p.usual, heavy_blocks, parts, HEAVY, a->inv_sqrt_deg != nullptr)) ++parts;
     if (parts > 1) sweep = parts > MOST_PARTS ? 1e30 : c.sweep(m.lengths, lines, m.nrows, m.ncols, HEAVY, sweep_rows(W), SWEEP_TASKS, parts, &heavy_blocks);
-    // Above 0.84 the hub schedule, which this does not estimate, may be as fast (246 M entries, 14 M vertices, R-MAT at 16 columns:
-    // 0.86, both 2.98 ms), and the sweep's copy takes longer to build.  Ragged rows in two panels straddle lines twice (41
-    // columns: no gain).
-    p.sweep = sweep < 0.84 * split && (f % 4 == 0 || f < 32);
+    // Ragged rows in two panels straddle lines twice (41 columns: no gain).
+    p.sweep = sweep < c.sweep_must_save() * split && (f % 4 == 0 || f < 32);
     if (p.sweep) {
         p.blocks = heavy_blocks;
+        p.narrow = true;
         p.parts = parts;
         p.heavy = (1 << HEAVY) - 1;
         p.padding = c.padding(m.lengths.below(HEAVY), m.nrows, sweep_rows(W));
@@ -1713,7 +1715,7 @@ static int run_matrix(gcn_csr* a, Matrix& mm, const int32_t* row_map, int64_t nn
         GCN_TRY(want_blocked(mm, nnz, cpb, s));
         const Blocked& b = mm.blk;
         GCN_TRY(grow_retire(a, &a->partial, &a->partial_bytes, (size_t)b.nrows * (size_t)f * sizeof(float)));
-        const SplitChoice choice = choose_split(f, mm.nchunks, o.any_order, !o.any_schedule);
+        const SplitChoice choice = choose_split(f, mm.nchunks, o.any_order, !o.narrow);
         if (o.describe) {
             char t[200];
             snprintf(t, sizeof t, "blocked(blocks=%d,cols_per_block=%lld,partial_rows=%lld,chunks=%lld,kernel=%s)", (int)b.nblocks,
@@ -1978,7 +1980,6 @@ static void took(gcn_csr* a, int sched) {
 static int launch_product(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx, float* Z, int64_t ldz,
                           int epilogue, const float* Zprev, int64_t ldzprev, hipStream_t s, const SpmmOpt& asked, SpmmPlan** plan) {
     SpmmOpt o = asked;
-    o.any_schedule = false;                                // set again where a plan decides
     const int64_t n = m.nrows, ncols = m.ncols, nnz = a->nnz;
     const Config& cfg = cfg_of(a);
     if (nnz == 0) {
@@ -2009,7 +2010,6 @@ static int launch_product(gcn_csr* a, Matrix& m, int32_t f, const float* X, int6
     if (algo == 3 && f < 4) algo = 2;
     bool hub_first = nblocks < 2;
     if (algo == 2 && cfg.spmm_algo == 0 && cfg.spmm_blocks == 0 && asked.any_schedule && worth_a_plan(m, f, nnz)) {
-        o.any_schedule = true;
         SpmmPlan& p = plan_of(a, m, f, nblocks);
         *plan = &p;
         if (p.sweep) {
@@ -2018,6 +2018,7 @@ static int launch_product(gcn_csr* a, Matrix& m, int32_t f, const float* X, int6
             parts = p.parts;
             heavy_blocks = p.blocks;
         } else nblocks = p.blocks;
+        o.narrow = p.narrow;
     }
     if (rowwise_only(m, ldx, Z, ldz, epilogue, Zprev, ldzprev)) algo = 1;
     const int sweep_lanes = f <= 16 ? 4 : 8;
@@ -2034,6 +2035,7 @@ static int launch_product(gcn_csr* a, Matrix& m, int32_t f, const float* X, int6
             if (*plan) {
                 (*plan)->give_way();
                 nblocks = (*plan)->blocks;
+                o.narrow = (*plan)->narrow;
             }
         }
     }

@@ -7,11 +7,10 @@
 // approximation of an LRU cache); a line costs one miss in any case where it is touched at all.  That takes the vertices' order
 // for random: a matrix of another keeps the schedule of the sizes (see even_rows, drawn_columns).  The constants were fitted to 600
 // timed products (uniform, R-MAT and Chung-Lu graphs of 60 K to 4 M vertices, 26 to 490 entries per row, 16 to 128
-// columns, 1 to 32 blocks, both schedules): estimates are within 9 % (blocks) and 11 % (sweep) of the times in the root
-// mean square, and the blocks chosen cost 2 to 4 % more than the best on average, where the rule by sizes alone
-// (blocks of 2 MB, rows of 24 entries per block) costs 9 %, up to 42 %.  The cost of a partial row and the share of the blocks
-// that an XCD walks were set again when the XCDs took stretches of the blocks (see chunk_group): estimates over 2 to 16 blocks of
-// seven graphs at 16, 32 and 64 columns are within 12 % in the root mean square (0.68 to 1.28 of the time).
+// columns, 1 to 32 blocks, both schedules).  The cost of a partial row and the share of the blocks that an XCD walks were set again when the
+// XCDs took stretches of the blocks (see chunk_group).  Estimates are within 12 % of the times in the root mean square, worse on
+// R-MAT graphs and on narrow rows; a schedule other than that of the sizes is taken only where its estimated gain is beyond what they were
+// found to be wrong by (must_save, narrow_panels, sweep_must_save), at the price of gains below 10 to 20 %.
 #pragma once
 #include <stdint.h>
 
@@ -113,9 +112,10 @@ struct SpmmCost {
         return l;
     }
 
-    // Misses of one XCD: `accesses` to the lines that a `share` of the columns selects, which stay (`band`) or not.
-    double misses(const Lengths& lines, double share, double accesses, bool band) const {
-        const double all = std::max<double>(1.0, (double)lines.total()), c = l2_bytes * 0.835 / 128.0 / (ragged() ? f / 32.0 : 1.0);        // the streams take some
+    // Misses of one XCD: `accesses` to the lines that a `share` of the columns selects, which stay (`band`) or not.  A row of X
+    // is `lines_each` lines.
+    double misses(const Lengths& lines, double share, double accesses, bool band, double lines_each) const {
+        const double all = std::max<double>(1.0, (double)lines.total()), c = l2_bytes * 0.835 / 128.0 / lines_each;        // the streams take some
         double n[Lengths::BINS], r[Lengths::BINS];
         int k = 0;
         for (int b = 0; b < Lengths::BINS; ++b)
@@ -136,11 +136,23 @@ struct SpmmCost {
         return s;
     }
 
+    // Share of the gathers over `blocks` column blocks that miss.
+    double missed(const Lengths& lines, int blocks, double lines_each) const {
+        const double each = std::max(1.0, blocks / xcds), all = std::max<double>(1.0, (double)lines.total());        // blocks that an XCD walks: each is in one of their L2s
+        return misses(lines, 1.0 / blocks, all / xcds / each, false, lines_each) * xcds * each / all;
+    }
+    // Whether rows of 64 columns and more go over column blocks in panels of 32: half the panel misses less, but it takes two passes over the
+    // entries.  Where a third of the gathers in panels of 64 would miss, and more, it took 0.65 to 1.00 of the time (430 products over 2 to
+    // 16 blocks at 64 to 160 columns), where fewer would, 0.95 to 1.14; at 200 columns 0.92 to 1.06, at 67 and 101 1.02 to 1.25: not where
+    // the pieces of a row start in the middle of half a line.
+    bool narrow_panels(const Lengths& lines, int blocks) const {
+        return f >= 64 && f % 16 == 0 && blocks >= 2 && missed(lines, blocks, 2.0) >= 0.34;
+    }
+
     // Nonzero-split over `blocks` column blocks of the rows `rows` (microseconds); `lines` of the whole matrix.
     double split(const Lengths& rows, const Lengths& lines, int blocks) const {
         const double nnz = (double)rows.total(), w = lines_per_row(), fetched = nnz * passes() * w;
-        const double each = std::max(1.0, blocks / xcds);        // blocks that an XCD walks: each is in one of their L2s
-        const double m = misses(lines, 1.0 / blocks, nnz / xcds / each, false) * xcds * each * passes() * w + nnz * passes() * 8 / 128;
+        const double m = nnz * missed(lines, blocks, ragged() ? f / 32.0 : 1.0) * passes() * w + nnz * passes() * 8 / 128;
         const bool narrow = f <= 16;
         const double served = fetched / (narrow ? 228e3 : 174e3), filled = m / (narrow ? 67.9e3 : 57.2e3);
         const double e = narrow ? 1.94 : 4.6;
@@ -150,18 +162,32 @@ struct SpmmCost {
             for (int b = 0; b < Lengths::BINS; ++b)
                 if (rows.rows[b] > 0)
                     partial += (double)rows.rows[b] * blocks * (1.0 - std::pow(1.0 - 1.0 / blocks, (double)rows.entries[b] / (double)rows.rows[b]));
-            t += partial * f * 4 * (narrow ? 0.47e-6 : 0.43e-6) + 7.6;
+            t += partial * std::max(f, 16) * 4 * (narrow ? 0.47e-6 : 0.43e-6) + 7.6;
         }
         return t;
     }
 
-    // The number of blocks that costs least, `usual` unless another is 6 % better.  No fewer than usual: the pieces of a sum would be
-    // longer, and its error larger.
-    int best_blocks(const Lengths& rows, const Lengths& lines, int64_t ncols, int usual, double* cost) const {
+    // How much less than the blocks of the sizes others have to cost: more than the estimates were found to be wrong by.  Timed and estimated
+    // gain of 2500 products of 1 to 110 M entries over more blocks (uniform, Chung-Lu, R-MAT; 100 K to 3.2 M vertices; 4 to 200 columns): up to
+    // 1.25 of the estimate, on R-MAT; with several blocks to start from and up to 16 columns 1.35; where the rows are no whole lines 1.17. Against
+    // panels of 32 either way (`narrower`, see above; the sizes' panels of 64 take longer still) 1.05.  With these numbers 600 such products took
+    // 0.45 to 1.02 of the time of the sizes' blocks.
+    double must_save(int usual, bool narrower) const {
+        if (narrower) return 0.94;
+        if (f <= 16) return usual >= 2 ? 0.76 : 0.82;
+        return f % 32 == 0 ? 0.82 : 0.86;
+    }
+    // And how much less the sweep.  Nothing estimates the hub schedule, which the sizes may choose in place of one block; of 900 products 0.40 to
+    // 1.01 of the time of the sizes' schedule.  Beyond 0.7 below 8 columns up to 1.18, beyond 0.75 in two panels that are not whole lines 1.07.
+    double sweep_must_save() const { return f < 8 ? 0.70 : (f > 32 && f < 64 ? 0.75 : 0.84); }
+
+    // The number of blocks that costs least, `usual` unless another is as much better as `must` says.  No fewer than usual: the
+    // pieces of a sum would be longer, and its error larger.
+    int best_blocks(const Lengths& rows, const Lengths& lines, int64_t ncols, int usual, double must, double* cost) const {
         static const int tried[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96};
         int best = usual;
         double least = split(rows, lines, usual);
-        const double keep = least * 0.94;
+        const double keep = least * must;
         for (int b : tried) {
             if (b == usual || (b > 1 && ncols / b < 2048) || b < usual) continue;
             const double t = split(rows, lines, b);
@@ -192,13 +218,13 @@ struct SpmmCost {
         if (nl <= 0) return 1e30;
         const double pad = padding(light, nrows, task_rows);
         const double fetched = nl * pad;
-        const double m = launches * xcds * misses(lines, 1.0, nl / launches / xcds, true) + fetched * 10 / 128;
+        const double m = launches * xcds * misses(lines, 1.0, nl / launches / xcds, true, 1.0) + fetched * 10 / 128;
         const double through = std::max(fetched / 130e3, m / 54e3);
         const double chain = launches * (fetched / tasks / (8.0 * 64 / (panel() / 4))) * 0.67;        // a trip takes 0.67 us
         double t = panels * (std::max(through, chain) + 4.0 * launches) + (parts - 1) * (double)nrows * f * 8 / 3.7e6;
         if (rest.total() > 0) {
             double h = 0;
-            *heavy_blocks = best_blocks(rest, lines, ncols, 1, &h);
+            *heavy_blocks = best_blocks(rest, lines, ncols, 1, 0.94, &h);
             t += 1.41 * h + 8.0;
         }
         return t;
@@ -292,11 +318,12 @@ struct SpmmPlan {
     int32_t f = 0;
     bool sweep = false;
     int32_t blocks = 1;          // column blocks: of the matrix, or of the sweep's long rows
+    bool narrow = false;         // these in panels of 32
     int32_t parts = 1, heavy = 0;// sweep: sums per row, long-row threshold
     int32_t usual = 1;           // blocks by the sizes alone
     double padding = 1;          // sweep: places per entry, estimated
     bool by_sizes() const { return !sweep && blocks == usual; }
-    void give_way() { sweep = false; blocks = usual; }
+    void give_way() { sweep = narrow = false; blocks = usual; }
 };
 
 // Runs a product (`run` leaves the plan it followed, if any, in its argument).  The stored order of a planned schedule is there for

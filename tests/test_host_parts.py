@@ -69,7 +69,7 @@ def test_estimated_costs_choose_as_timed(tmp_path):
                 const Lengths rows = uniform(t.n, t.mean), l = c.lines(rows);
                 double split = 0;
                 int hb = 0;
-                const int b = c.best_blocks(rows, l, t.n, 1, &split);
+                const int b = c.best_blocks(rows, l, t.n, 1, c.must_save(1, false), &split);
                 const double sweep = c.sweep(rows, l, t.n, t.n, 8, t.f <= 16 ? 511 : 255, 5, 1, &hb);
                 const bool right = (sweep < split) == (t.sweep < t.split) || std::fabs(t.sweep / t.split - 1) < 0.1;
                 std::printf("%d%d%d ", (int)right, (int)(split > 0.7 * t.split && split < 1.4 * t.split), (int)(sweep > 0.7 * t.sweep && sweep < 1.4 * t.sweep));
@@ -83,14 +83,81 @@ def test_estimated_costs_choose_as_timed(tmp_path):
             longest.entries[30] = 1ll << 30;
             for (const Lengths& l : {one, longest})
                 for (int64_t n : {1ll, 1ll << 31}) {
-                    c.best_blocks(l, c.lines(l), n, 1, &x);
+                    c.best_blocks(l, c.lines(l), n, 1, 0.9, &x);
                     if (!std::isfinite(x) || !std::isfinite(c.sweep(l, c.lines(l), n, n, 8, 511, 5, 3, &hb)) || hb < 1) std::printf("bad ");
                 }
-            c.best_blocks(none, c.lines(none), 1, 1, &x);
+            c.best_blocks(none, c.lines(none), 1, 1, 0.9, &x);
             std::printf(std::isfinite(x) ? "ok" : "bad");
         }
     """)
     assert r.returncode == 0 and r.stdout.split() == ["111"] * 8 + ["ok"], (r.returncode, r.stdout, r.stderr)
+
+
+def test_schedules_of_skewed_matrices_are_not_changed_for_worse(tmp_path):
+    """Renamed power-law graphs whose products were timed by the sizes and in another schedule (column blocks, narrower panels, sweep): where the other one
+    took longer, by 7 to 35 %, the product keeps the schedule of the sizes; where it took at least a quarter less, it does not."""
+    r = run_cpp(tmp_path, """
+        #include <cstdio>
+        #include "spmm_cost.h"
+        using namespace gcn;
+        int main() {
+            struct { int f; int64_t n; int usual, other; double sizes, us; int64_t rows[20], entries[20]; } timed[] = {      // other: blocks, or -1 for the sweep
+                {16, 675186, 6, 12, 749, 826,      // Chung-Lu 2.3
+                 {0, 0, 0, 0, 5076, 300760, 223083, 87671, 35080, 14174, 5639, 2267, 894, 352, 131, 52, 7},
+                 {0, 0, 0, 0, 147971, 14702678, 19408359, 15313048, 12269416, 9929442, 7904851, 6343942, 5001566, 3946723, 2932200, 2319702, 509646}},
+                {64, 347117, 6, 8, 1468, 1069,      // Chung-Lu 3.0
+                 {0, 0, 0, 0, 0, 322, 199977, 110806, 27155, 6669, 1664, 409, 102, 13},
+                 {0, 0, 0, 0, 0, 19565, 19857316, 18824723, 9249552, 4549048, 2271359, 1116087, 554376, 118617}},
+                {64, 369072, 7, 7, 1587, 1166,      // Chung-Lu 3.0
+                 {0, 0, 0, 0, 0, 93, 196082, 130646, 31842, 7842, 1946, 481, 121, 19},
+                 {0, 0, 0, 0, 0, 5668, 20028805, 22195493, 10851746, 5352967, 2659340, 1310320, 656469, 179984}},
+                {64, 101762, 7, 7, 251, 284,      // R-MAT
+                 {7676, 10417, 11314, 12516, 16930, 4606, 16669, 9929, 2388, 6076, 2289, 118, 680, 136, 17, 1},
+                 {7676, 25454, 60455, 129704, 414250, 187899, 1348980, 2291067, 687169, 4293136, 4398163, 260204, 3330949, 1511809, 377989, 38586}},
+                {128, 112570, 6, 6, 458, 522,      // R-MAT
+                 {11161, 13637, 15287, 12088, 19584, 8365, 10915, 11874, 323, 6102, 2380, 21, 679, 136, 17, 1},
+                 {11161, 33023, 82466, 124766, 431292, 464708, 788156, 2358949, 99228, 3614149, 3911260, 48254, 2886741, 1342726, 346141, 36510}},
+                {8, 2766711, 1, 24, 530, 715,      // Chung-Lu 2.1
+                 {125892, 731512, 1122483, 478072, 175632, 73464, 32579, 14747, 6726, 3083, 1402, 628, 281, 125, 54, 24, 7},
+                 {125892, 1879539, 5784293, 4958765, 3760640, 3194307, 2857279, 2598683, 2373193, 2177934, 1979146, 1768976, 1580826, 1404822, 1210214, 1075229, 558663}},
+                {16, 486654, 1, 8, 404, 299,      // Chung-Lu 3.0
+                 {0, 0, 0, 360, 124497, 272324, 68017, 16182, 3994, 979, 240, 61},
+                 {0, 0, 0, 5126, 3346797, 11616681, 5750578, 2746033, 1358920, 667279, 327698, 165476}},
+                {32, 790548, 1, 3, 413, 458,      // R-MAT
+                 {220198, 153017, 121044, 75091, 85773, 60181, 15780, 37546, 2350, 13341, 4840, 36, 1140, 190, 19, 1, 1},
+                 {220198, 363200, 638895, 807943, 1752886, 3195822, 1137653, 6606832, 1117669, 7320595, 7884400, 78700, 5423713, 2463061, 617404, 32821, 73202}},
+                {48, 405282, 1, 8, 1386, 944,      // Chung-Lu 2.5
+                 {0, 0, 0, 12, 28709, 227614, 97852, 33325, 11565, 4039, 1431, 496, 173, 57, 9},
+                 {0, 0, 0, 167, 809622, 10260311, 8438447, 5776163, 4014265, 2803026, 1987807, 1381704, 968640, 637471, 164437}},
+                {64, 331220, 1, 8, 923, 689,      // Chung-Lu 3.0
+                 {0, 0, 0, 0, 1702, 182144, 112089, 26647, 6507, 1619, 401, 98, 13},
+                 {0, 0, 0, 0, 50030, 9036513, 9477344, 4532026, 2215101, 1102454, 546834, 267456, 58958}},
+                {64, 509906, 1, 3, 710, 798,      // R-MAT
+                 {111245, 91201, 71171, 65455, 63101, 14307, 49625, 13636, 13501, 11628, 0, 3876, 969, 165, 6, 19, 1},
+                 {111245, 218307, 372568, 676847, 1582929, 512648, 4115681, 3315687, 3622033, 9054439, 0, 8869414, 6141567, 2666992, 98656, 708151, 77100}},
+                {16, 643482, 1, -1, 245, 160,      // Chung-Lu 3.0
+                 {4, 222, 16081, 271423, 275724, 61617, 14026, 3323, 815, 199, 48},
+                 {4, 629, 102062, 3290609, 5752465, 2579136, 1184486, 565616, 277686, 135157, 62718}},
+                {64, 1193664, 1, -1, 2891, 1851,      // Chung-Lu 3.0
+                 {0, 0, 0, 49, 136075, 761458, 224815, 53861, 13118, 3244, 798, 201, 45},
+                 {0, 0, 0, 703, 3806637, 33505945, 19002534, 9145006, 4468460, 2217367, 1090641, 550250, 238637}}};
+            for (auto& t : timed) {
+                const SpmmCost c{t.f, 256, 8.0, 4.0 * (1 << 20)};
+                Lengths rows;
+                for (int b = 0; b < 20; ++b) { rows.rows[b] = t.rows[b]; rows.entries[b] = t.entries[b]; }
+                const Lengths l = c.lines(rows);
+                double split = 0;
+                int hb = 0, parts = 1;
+                const bool narrow = c.narrow_panels(l, t.usual);
+                const int b = c.best_blocks(rows, l, t.n, t.usual, c.must_save(t.usual, narrow), &split);
+                while (!c.as_exact(rows, t.usual, 1, parts, 8, true)) ++parts;
+                const double sweep = c.sweep(rows, l, t.n, t.n, 8, t.f <= 16 ? 511 : 255, 5, parts, &hb);
+                const bool other = narrow || b != t.usual || sweep < c.sweep_must_save() * split;
+                std::printf("%d ", other == (t.us < t.sizes));
+            }
+        }
+    """)
+    assert r.returncode == 0 and r.stdout.split() == ["1"] * 13, (r.returncode, r.stdout, r.stderr)
 
 
 def test_estimated_costs_of_ragged_rows(tmp_path):
@@ -108,7 +175,7 @@ def test_estimated_costs_of_ragged_rows(tmp_path):
                 const SpmmCost c{t.f, 256, 8.0, 4.0 * (1 << 20)};
                 const Lengths rows = Lengths::equal(t.n, t.n * t.mean);
                 double cost = 0, least = 1e30;
-                const int b = c.best_blocks(rows, c.lines(rows), t.n, t.usual, &cost);
+                const int b = c.best_blocks(rows, c.lines(rows), t.n, t.usual, c.must_save(t.usual, false), &cost);
                 for (double us : t.us) if (us > 0) least = std::min(least, us);
                 std::printf("%d ", b <= 8 && t.us[b] > 0 && t.us[b] <= 1.05 * least);
             }
