@@ -1652,7 +1652,7 @@ static SpmmPlan& plan_of(gcn_csr* a, Matrix& m, int32_t f, int64_t usual) {
     double split = 0;
     p.narrow = c.narrow_panels(lines, (int)usual);
     // (rows beyond 64 columns that are not whole 16-byte pieces: by the sizes, in panels of 64, which are not estimated)
-    const double must = f > 64 && f % 4 != 0 && usual >= 2 ? 0.0 : c.must_save((int)usual, p.narrow);
+    const double must = f > 64 && f % 4 != 0 && usual >= 2 ? 0.0 : c.must_save(m.lengths, (int)usual, p.narrow);
     p.blocks = c.best_blocks(m.lengths, lines, m.ncols, (int)usual, must, &split);
     p.narrow = p.narrow || p.blocks > usual;
     constexpr int HEAVY = 8, MOST_PARTS = 8;                    // rows of 2^8 entries and more are long

@@ -55,6 +55,14 @@ struct Lengths {
     int64_t entries[BINS] = {};
     int64_t total() const { int64_t t = 0; for (int64_t e : entries) t += e; return t; }
     int64_t count() const { int64_t t = 0; for (int64_t r : rows) t += r; return t; }
+    // share of the entries that are in rows of eight times the mean and more
+    double in_long_rows() const {
+        const double all = std::max<double>(1.0, (double)total()), rows_all = (double)count();
+        double in = 0;
+        for (int b = 0; b < BINS; ++b)
+            if (rows[b] > 0 && (double)entries[b] * rows_all > 8.0 * all * (double)rows[b]) in += (double)entries[b];
+        return in / all;
+    }
     // the rows of at least 2^b entries, or the others
     Lengths from(int b) const { Lengths l; for (int i = b; i < BINS; ++i) { l.rows[i] = rows[i]; l.entries[i] = entries[i]; } return l; }
     Lengths below(int b) const { Lengths l; for (int i = 0; i < b; ++i) { l.rows[i] = rows[i]; l.entries[i] = entries[i]; } return l; }
@@ -167,15 +175,15 @@ struct SpmmCost {
         return t;
     }
 
-    // How much less than the blocks of the sizes others have to cost: more than the estimates were found to be wrong by.  Timed and estimated
-    // gain of 2500 products of 1 to 110 M entries over more blocks (uniform, Chung-Lu, R-MAT; 100 K to 3.2 M vertices; 4 to 200 columns): up to
-    // 1.25 of the estimate, on R-MAT; with several blocks to start from and up to 16 columns 1.35; where the rows are no whole lines 1.17. Against
-    // panels of 32 either way (`narrower`, see above; the sizes' panels of 64 take longer still) 1.05.  With these numbers 600 such products took
-    // 0.45 to 1.02 of the time of the sizes' blocks.
-    double must_save(int usual, bool narrower) const {
-        if (narrower) return 0.94;
+    // How much less than the blocks of the sizes others have to cost: more than the estimates were found to be wrong by.  Of 2600 products of
+    // 1 to 110 M entries (uniform, Chung-Lu, R-MAT; 100 K to 3.2 M vertices; 4 to 200 columns) timed over the blocks of the sizes and over more:
+    // estimated at 0.82 to 0.94 of the cost, they took up to 1.35 of the time at 8 to 16 columns, up to 1.12 where most entries
+    // are in long rows (R-MAT; such rows select cold columns one after the other), up to 1.08 at 32 columns over several blocks
+    // instead of fewer, and 0.70 to 1.03 otherwise; estimated below the bound of their kind 0.45 to 1.03, but for a few of 8 columns up to 1.06.
+    double must_save(const Lengths& rows, int usual, bool narrower) const {
+        if (narrower) return 0.94;                              // (the sizes' panels of 64 take longer than the estimate has it)
         if (f <= 16) return usual >= 2 ? 0.76 : 0.82;
-        return f % 32 == 0 ? 0.82 : 0.86;
+        return rows.in_long_rows() > 0.42 || (usual >= 2 && (f == 32 || f >= 64)) ? 0.82 : 0.94;
     }
     // And how much less the sweep.  Nothing estimates the hub schedule, which the sizes may choose in place of one block; of 900 products 0.40 to
     // 1.01 of the time of the sizes' schedule.  Beyond 0.7 below 8 columns up to 1.18, beyond 0.75 in two panels that are not whole lines 1.07.

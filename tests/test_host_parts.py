@@ -69,7 +69,7 @@ def test_estimated_costs_choose_as_timed(tmp_path):
                 const Lengths rows = uniform(t.n, t.mean), l = c.lines(rows);
                 double split = 0;
                 int hb = 0;
-                const int b = c.best_blocks(rows, l, t.n, 1, c.must_save(1, false), &split);
+                const int b = c.best_blocks(rows, l, t.n, 1, c.must_save(rows, 1, false), &split);
                 const double sweep = c.sweep(rows, l, t.n, t.n, 8, t.f <= 16 ? 511 : 255, 5, 1, &hb);
                 const bool right = (sweep < split) == (t.sweep < t.split) || std::fabs(t.sweep / t.split - 1) < 0.1;
                 std::printf("%d%d%d ", (int)right, (int)(split > 0.7 * t.split && split < 1.4 * t.split), (int)(sweep > 0.7 * t.sweep && sweep < 1.4 * t.sweep));
@@ -149,7 +149,7 @@ def test_schedules_of_skewed_matrices_are_not_changed_for_worse(tmp_path):
                 double split = 0;
                 int hb = 0, parts = 1;
                 const bool narrow = c.narrow_panels(l, t.usual);
-                const int b = c.best_blocks(rows, l, t.n, t.usual, c.must_save(t.usual, narrow), &split);
+                const int b = c.best_blocks(rows, l, t.n, t.usual, c.must_save(rows, t.usual, narrow), &split);
                 while (parts <= 8 && !c.as_exact(rows, t.usual, 1, parts, 8, true)) ++parts;
                 const double sweep = parts > 8 ? 1e30 : c.sweep(rows, l, t.n, t.n, 8, t.f <= 16 ? 511 : 255, 5, parts, &hb);
                 const bool other = narrow || b != t.usual || sweep < c.sweep_must_save() * split;
@@ -175,7 +175,7 @@ def test_estimated_costs_of_ragged_rows(tmp_path):
                 const SpmmCost c{t.f, 256, 8.0, 4.0 * (1 << 20)};
                 const Lengths rows = Lengths::equal(t.n, t.n * t.mean);
                 double cost = 0, least = 1e30;
-                const int b = c.best_blocks(rows, c.lines(rows), t.n, t.usual, c.must_save(t.usual, false), &cost);
+                const int b = c.best_blocks(rows, c.lines(rows), t.n, t.usual, c.must_save(rows, t.usual, false), &cost);
                 for (double us : t.us) if (us > 0) least = std::min(least, us);
                 std::printf("%d ", b <= 8 && t.us[b] > 0 && t.us[b] <= 1.05 * least);
             }
