@@ -185,9 +185,17 @@ struct SpmmCost {
         if (f <= 16) return usual >= 2 ? 0.76 : 0.82;
         return rows.in_long_rows() > 0.42 || (usual >= 2 && (f == 32 || f >= 64)) ? 0.82 : 0.94;
     }
-    // And how much less the sweep.  Nothing estimates the hub schedule, which the sizes may choose in place of one block; of 900 products 0.40 to
-    // 1.01 of the time of the sizes' schedule.  Beyond 0.7 below 8 columns up to 1.18, beyond 0.75 in two panels that are not whole lines 1.07.
-    double sweep_must_save() const { return f < 8 ? 0.70 : (f > 32 && f < 64 ? 0.75 : 0.84); }
+    // And how much less the sweep.  4000 products timed in it and by the sizes: estimated at 0.84 to 0.92 of the other's cost it took up to 1.03
+    // of the time, at 8 to 15 columns up to 1.12; estimated below 0.75 up to 0.99 in two panels that are no whole lines (33 to 63
+    // columns), beyond 1.05 and more; below 8 columns up to 1.07 beyond 0.7.  Nothing estimates the hub schedule, which the sizes may choose below 32 columns
+    // where most entries are in rows of 64 and more: against it up to 0.89 of the time below 0.8, at 16 columns and more 0.86 below
+    // 0.88, beyond 1.15 and more.
+    double sweep_must_save(const Lengths& rows) const {
+        if (f < 8) return 0.70;
+        if (f > 32 && f < 64) return 0.75;
+        const bool hub = f < 32 && 2 * rows.from(6).total() > rows.total();
+        return f < 16 ? (hub ? 0.80 : 0.88) : (hub ? 0.88 : 0.92);
+    }
 
     // The number of blocks that costs least, `usual` unless another is as much better as `must` says.  No fewer than usual: the
     // pieces of a sum would be longer, and its error larger.
