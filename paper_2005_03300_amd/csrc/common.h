@@ -145,7 +145,8 @@ struct Matrix {
     int32_t max_degree = 0;
     Lengths lengths;             // of its rows (not kept for the long rows of a sweep copy)
     RowOrder order;              // how they lie (likewise)
-    std::vector<SpmmPlan> plans; // schedules chosen so far, one per width
+    Terms terms = Terms::UNKNOWN;
+    std::vector<SpmmPlan> plans; // schedules chosen so far, one per width and kind of terms
     // Other stored orders of the matrix, built on first use (or by a prepare call) and kept until the
     // matrix is destroyed.  blk / swp / hub are the copies the latest product used; a product that needs
     // another key (block width; lane groups, task height and long-row threshold; hub settings) parks the

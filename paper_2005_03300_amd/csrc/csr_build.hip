@@ -463,6 +463,8 @@ static int create_impl(gcn_csr* a, int64_t n, int64_t m, const int32_t* src, con
     a->ncols = n;
     a->nnz = nnz;
     a->A.nrows = a->A.ncols = n;
+    a->A.terms = (flags & GCN_NORM_SYM) ? Terms::BY_BOTH : ((flags & GCN_NORM_ROW) ? Terms::BY_ROW : Terms::ALIKE);
+    a->At.terms = (flags & GCN_NORM_SYM) && sym ? Terms::BY_BOTH : Terms::ALIKE;      // (its rows are as long as a vertex has entries in A's columns)
     GCN_TRY(device_alloc_t(&a->A.rowptr, (size_t)n + 1));
     GCN_TRY(device_alloc_t(&a->A.colidx, (size_t)nnz));
     if (cap > 0) {

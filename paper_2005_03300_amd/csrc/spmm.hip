@@ -1632,11 +1632,12 @@ static bool worth_a_plan(const Matrix& m, int32_t f, int64_t nnz) {
     return f >= 4 && nnz >= PLANNED_NNZ && m.lengths.total() == nnz && m.ncols * panel * 4 > device_info().l2_bytes / 8 * 7;
 }
 
-static SpmmPlan& plan_of(gcn_csr* a, Matrix& m, int32_t f, int64_t usual) {
+static SpmmPlan& plan_of(gcn_csr* a, Matrix& m, int32_t f, Terms terms, int64_t usual) {
     for (SpmmPlan& p : m.plans)
-        if (p.f == f) return p;
+        if (p.f == f && p.terms == terms) return p;
     SpmmPlan p;
     p.f = f;
+    p.terms = terms;
     p.usual = (int32_t)usual;
     const int64_t nnz = m.lengths.total();
     const SpmmCost c{f, device_info().cus, 8.0, (double)device_info().l2_bytes};
@@ -1662,7 +1663,7 @@ static SpmmPlan& plan_of(gcn_csr* a, Matrix& m, int32_t f, int64_t usual) {
     // As many sums per row as keep them as close to the exact ones as the nonzero split's (see as_exact; 30 M pairs, 1 M vertices, 16
     // columns: 10.0e-8 of the norm there, 14.1, 10.5, 9.1 and 8.5e-8 with one to four; another costs 6 % of the product).
     int parts = 1;
-    while (parts <= MOST_PARTS && !c.as_exact(m.lengths, p.usual, heavy_blocks, parts, HEAVY, a->inv_sqrt_deg != nullptr)) ++parts;
+    while (parts <= MOST_PARTS && !c.as_exact(m.lengths, p.usual, heavy_blocks, parts, HEAVY, terms)) ++parts;
     if (parts > 1) sweep = parts > MOST_PARTS ? 1e30 : c.sweep(m.lengths, lines, m.nrows, m.ncols, HEAVY, sweep_rows(W), SWEEP_TASKS, parts, &heavy_blocks);
     // Ragged rows in two panels straddle lines twice (41 columns: no gain).
     p.sweep = sweep < c.sweep_must_save(m.lengths) * split && (f % 4 == 0 || f < 32);
@@ -2010,7 +2011,9 @@ static int launch_product(gcn_csr* a, Matrix& m, int32_t f, const float* X, int6
     if (algo == 3 && f < 4) algo = 2;
     bool hub_first = nblocks < 2;
     if (algo == 2 && cfg.spmm_algo == 0 && cfg.spmm_blocks == 0 && asked.any_schedule && worth_a_plan(m, f, nnz)) {
-        SpmmPlan& p = plan_of(a, m, f, nblocks);
+        // (without the stored values the caller's row factors decide; those of this library are 1 / sqrt(d_i))
+        const Terms terms = o.pattern && m.terms != Terms::BY_BOTH ? Terms::UNKNOWN : m.terms;
+        SpmmPlan& p = plan_of(a, m, f, terms, nblocks);
         *plan = &p;
         if (p.sweep) {
             algo = 3;

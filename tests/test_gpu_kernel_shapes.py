@@ -1033,6 +1033,46 @@ def test_schedules_by_cost_are_no_less_exact(kind, mean, norm):
     a.close()
 
 
+@pytest.mark.parametrize("kind,mean", [("uniform", 17), ("power", 20), ("power", 41)])
+@pytest.mark.parametrize("values", ["none", "row", "sym", "given"])
+def test_schedules_by_cost_of_the_transpose_are_no_less_exact(kind, mean, values):
+    """As above for A^T X (with a mask that lets all through, so that its schedule is free) on directed graphs, whose rows are as long as vertices have
+    incoming edges while the values follow from the outgoing ones, and for A X with values 1 and with the caller's, on rows in
+    proportion to 1 / d_i."""
+    g = G()
+    n = 800_000
+    (src, dst), gen = drawn_graph(kind, n, n * (mean - 1), 175)
+    rename = torch.randperm(n, generator=gen, device="cuda").int()
+    norm = {"none": 0, "row": g.NORM_ROW, "sym": g.NORM_SYM, "given": g.NORM_ROW}[values]
+    a = g.gcn_csr_create(n, rename[src], rename[dst], norm | g.ADD_SELF_LOOPS | g.BUILD_TRANSPOSE)
+    if values == "given":
+        rowptr, colidx, val, _ = a.arrays(False)
+        b = g.gcn_csr_create_from_csr(n, rowptr.clone(), colidx.clone(), val.clone(), g.BUILD_TRANSPOSE)
+        a.close()
+        a = b
+    g.gcn_csr_config(a, g.CFG_PATTERN_SPMM, 0)
+    f = 16
+    X, ones = torch.rand(n, f, generator=gen, device="cuda") * 2 - 1, torch.ones(n, f, device="cuda")
+    for trans in ((0, 1) if values in ("none", "given") else (1,)):
+        rowptr, colidx, val, _ = a.arrays(bool(trans))
+        rows = torch.repeat_interleave(torch.arange(n, device="cuda"), rowptr[1:] - rowptr[:-1])
+        exact = torch.zeros(n, f, dtype=torch.float64, device="cuda")
+        for k in range(0, a.nnz, 1 << 22):
+            part = slice(k, k + (1 << 22))
+            exact.index_add_(0, rows[part], val[part, None].double() * X[colidx[part].long()])
+        error = []
+        for algo in (0, 2):
+            g.gcn_csr_config(a, g.CFG_SPMM_ALGO, algo)
+            g.gcn_csr_config(a, g.CFG_SPMM_BLOCKS, 1 if algo else 0)
+            error.append(float((g.gcn_spmm(a, trans, X, torch.empty(n, f, device="cuda"), g.EPI_MASK, ones).double() - exact).norm() / exact.norm()))
+        sched = g.gcn_csr_last_spmm_schedule(a)
+        g.gcn_csr_config(a, g.CFG_SPMM_ALGO, 0)
+        g.gcn_csr_config(a, g.CFG_SPMM_BLOCKS, 0)
+        print(kind, mean, values, trans, g.gcn_spmm_describe(a, 0, f)[:90] if not trans else sched, error)
+        assert error[0] <= 1.005 * error[1], (kind, mean, values, trans, error)
+    a.close()
+
+
 @pytest.mark.parametrize("n,k,f,usual", [(500_000, 41, 16, "split("), (500_000, 41, 32, "split("), (600_000, 100, 32, "split(")])
 def test_rows_that_fill_no_set_are_not_swept(n, k, f, usual):
     """Row i selects the columns k i to k i + k - 1 (mod n): as long as the rows and columns of a uniform matrix, and as many different columns, but

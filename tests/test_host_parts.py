@@ -150,7 +150,7 @@ def test_schedules_of_skewed_matrices_are_not_changed_for_worse(tmp_path):
                 int hb = 0, parts = 1;
                 const bool narrow = c.narrow_panels(l, t.usual);
                 const int b = c.best_blocks(rows, l, t.n, t.usual, c.must_save(rows, t.usual, narrow), &split);
-                while (parts <= 8 && !c.as_exact(rows, t.usual, 1, parts, 8, true)) ++parts;
+                while (parts <= 8 && !c.as_exact(rows, t.usual, 1, parts, 8, Terms::BY_BOTH)) ++parts;
                 const double sweep = parts > 8 ? 1e30 : c.sweep(rows, l, t.n, t.n, 8, t.f <= 16 ? 511 : 255, 5, parts, &hb);
                 const bool other = narrow || b != t.usual || sweep < c.sweep_must_save(rows) * split;
                 std::printf("%d ", other == (t.us < t.sizes));
@@ -362,11 +362,11 @@ def test_estimated_rounding_errors(tmp_path):
                     const Lengths l = Lengths::equal(1 << 20, (int64_t)mean << 20);
                     for (bool normalised : {false, true}) {
                         int parts = 1;
-                        while (parts < 20 && !c.as_exact(l, 1, 1, parts, 8, normalised)) ++parts;
+                        while (parts < 20 && !c.as_exact(l, 1, 1, parts, 8, normalised ? Terms::BY_BOTH : Terms::UNKNOWN)) ++parts;
                         if (SpmmCost::sweep_error(mean, parts) > SpmmCost::split_error(mean, f <= 16 ? 32 : 64, 1) || parts < 2 || parts > 8)
                             std::printf("mean %d f %d: %d sums ", mean, f, parts);
                     }
-                    if (!c.as_exact(l, 4, 4, 0, 8, true) || c.as_exact(l, 4, 2, 0, 8, true)) std::printf("blocks %d %d ", mean, f);
+                    if (!c.as_exact(l, 4, 4, 0, 8, Terms::BY_BOTH) || c.as_exact(l, 4, 2, 0, 8, Terms::BY_BOTH)) std::printf("blocks %d %d ", mean, f);
                 }
             std::printf("done");
         }
