@@ -1666,7 +1666,7 @@ static SpmmPlan& plan_of(gcn_csr* a, Matrix& m, int32_t f, Terms terms, int64_t 
     while (parts <= MOST_PARTS && !c.as_exact(m.lengths, p.usual, heavy_blocks, parts, HEAVY, terms)) ++parts;
     if (parts > 1) sweep = parts > MOST_PARTS ? 1e30 : c.sweep(m.lengths, lines, m.nrows, m.ncols, HEAVY, sweep_rows(W), SWEEP_TASKS, parts, &heavy_blocks);
     // Ragged rows in two panels straddle lines twice (41 columns: no gain).
-    p.sweep = sweep < c.sweep_must_save(m.lengths) * split && (f % 4 == 0 || f < 32);
+    p.sweep = c.sweep_pays(m.lengths, sweep, split) && (f % 4 == 0 || f < 32);
     if (p.sweep) {
         p.blocks = heavy_blocks;
         p.narrow = true;

@@ -10,7 +10,7 @@
 // columns, 1 to 32 blocks, both schedules).  The cost of a partial row and the share of the blocks that an XCD walks were set again when the
 // XCDs took stretches of the blocks (see chunk_group).  Estimates are within 12 % of the times in the root mean square, worse on
 // R-MAT graphs and on narrow rows; a schedule other than that of the sizes is taken only where its estimated gain is beyond what they were
-// found to be wrong by (must_save, narrow_panels, sweep_must_save), at the price of gains below 10 to 20 %.
+// found to be wrong by (must_save, narrow_panels, sweep_pays), at the price of gains below 10 to 20 %.
 #pragma once
 #include <stdint.h>
 
@@ -182,23 +182,24 @@ struct SpmmCost {
     // How much less than the blocks of the sizes others have to cost: more than the estimates were found to be wrong by.  Of 2600 products of
     // 1 to 110 M entries (uniform, Chung-Lu, R-MAT; 100 K to 3.2 M vertices; 4 to 200 columns) timed over the blocks of the sizes and over more:
     // estimated at 0.82 to 0.94 of the cost, they took up to 1.35 of the time at 8 to 16 columns, up to 1.12 where most entries
-    // are in long rows (R-MAT; such rows select cold columns one after the other), up to 1.08 at 32 columns over several blocks
-    // instead of fewer, and 0.70 to 1.03 otherwise; estimated below the bound of their kind 0.45 to 1.03, but for a few of 8 columns up to 1.06.
+    // are in long rows (R-MAT; such rows select cold columns one after the other), up to 1.08 at 17 to 32 columns over several
+    // blocks instead of fewer, and 0.70 to 1.03 otherwise; estimated below the bound of their kind 0.45 to 1.03, but for a few of 8 columns up to 1.06.
     double must_save(const Lengths& rows, int usual, bool narrower) const {
         if (narrower) return 0.94;                              // (the sizes' panels of 64 take longer than the estimate has it)
-        if (f <= 16) return usual >= 2 ? 0.76 : 0.82;
-        return rows.in_long_rows() > 0.42 || (usual >= 2 && (f == 32 || f >= 64)) ? 0.82 : 0.94;
+        if (f <= 16) return usual >= 2 && f >= 8 ? 0.76 : 0.82;
+        return rows.in_long_rows() > 0.42 || (usual >= 2 && (f <= 32 || f >= 64)) ? 0.82 : 0.94;
     }
-    // And how much less the sweep.  4000 products timed in it and by the sizes: estimated at 0.84 to 0.92 of the other's cost it took up to 1.03
-    // of the time, at 8 to 15 columns up to 1.12; estimated below 0.75 up to 0.99 in two panels that are no whole lines (33 to 63
-    // columns), beyond 1.05 and more; below 8 columns up to 1.07 beyond 0.7.  Nothing estimates the hub schedule, which the sizes may choose below 32 columns
-    // where most entries are in rows of 64 and more: against it up to 0.89 of the time below 0.8, at 16 columns and more 0.86 below
-    // 0.88, beyond 1.15 and more.
-    double sweep_must_save(const Lengths& rows) const {
-        if (f < 8) return 0.70;
-        if (f > 32 && f < 64) return 0.75;
-        const bool hub = f < 32 && 2 * rows.from(6).total() > rows.total();
-        return f < 16 ? (hub ? 0.80 : 0.88) : (hub ? 0.88 : 0.92);
+    // Whether the sweep does.  4000 products timed in it and by the sizes: at 16 to 32 columns its estimate is 10 % too high beside the other's, but
+    // for some 8 us of every product (estimated at 0.92 to 1.0 of the other's cost 246 products took 0.57 to 1.07 of the time, 1.02 and more those of
+    // less than 120 us); wider ones took up to 1.00 below 0.92 and 1.28 beyond, those that are no whole lines 1.05 beyond 0.85, in two
+    // panels (33 to 63 columns) beyond 0.75; of 8 to 15 columns 0.97 below 0.88, 1.12 beyond; below that 0.85 below 0.7, 1.07 beyond.  Nothing estimates the
+    // hub schedule, which the sizes may choose below 32 columns where most entries are in rows of 64 and more: against it 0.92 of the
+    // time below 0.75, at 16 columns and more 0.86 below 0.88, 1.15 and more beyond.
+    bool sweep_pays(const Lengths& rows, double sweep, double split) const {
+        if (f < 8) return sweep < 0.70 * split;
+        if (f > 32) return sweep < (f < 64 ? 0.75 : (f % 32 == 0 ? 0.92 : 0.85)) * split;
+        if (f < 32 && 2 * rows.from(6).total() > rows.total()) return sweep < (f < 16 ? 0.75 : 0.88) * split;
+        return f < 16 ? sweep < 0.88 * split : sweep + 8.0 < 0.98 * split;
     }
 
     // The number of blocks that costs least, `usual` unless another is as much better as `must` says.  No fewer than usual: the
@@ -294,14 +295,14 @@ struct SpmmCost {
     }
     // Whether sums in that schedule are as close to the exact ones as in the nonzero split over `usual` blocks.
     bool as_exact(const Lengths& rows, int usual, int blocks, int parts, int heavy, Terms terms) const {
-        auto holds = [&](int power, double most = 1.0) {
-            return error(rows, blocks, parts, heavy, power) <= most * error(rows, usual, 0, heavy, power);
-        };
+        // One chain per row grows with the squares of the lengths, which are taken to be alike within a factor of two: measured up to 2 %
+        // further off than the nonzero split where this had them equal (uniform rows of 12, Chung-Lu rows of 20 times 1 / d_i, at 32 columns).
+        const double most = parts == 1 ? 0.9 : 1.0;
+        auto holds = [&](int power) { return error(rows, blocks, parts, heavy, power) <= most * error(rows, usual, 0, heavy, power); };
         switch (terms) {
             case Terms::ALIKE: return holds(0);
             case Terms::BY_BOTH: return holds(-1);
-            // (short rows decide: estimated the same, the sweep was measured 2 % further off, Chung-Lu rows of 20 at 32 columns)
-            case Terms::BY_ROW: return holds(-2, parts > 0 ? 0.9 : 1.0);
+            case Terms::BY_ROW: return holds(-2);
             default: return holds(0) && holds(-2);
         }
     }

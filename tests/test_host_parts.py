@@ -152,7 +152,7 @@ def test_schedules_of_skewed_matrices_are_not_changed_for_worse(tmp_path):
                 const int b = c.best_blocks(rows, l, t.n, t.usual, c.must_save(rows, t.usual, narrow), &split);
                 while (parts <= 8 && !c.as_exact(rows, t.usual, 1, parts, 8, Terms::BY_BOTH)) ++parts;
                 const double sweep = parts > 8 ? 1e30 : c.sweep(rows, l, t.n, t.n, 8, t.f <= 16 ? 511 : 255, 5, parts, &hb);
-                const bool other = narrow || b != t.usual || sweep < c.sweep_must_save(rows) * split;
+                const bool other = narrow || b != t.usual || c.sweep_pays(rows, sweep, split);
                 std::printf("%d ", other == (t.us < t.sizes));
             }
         }
