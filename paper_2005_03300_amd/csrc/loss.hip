@@ -14,18 +14,19 @@ namespace gcn {
 
 static constexpr int LOSS_BLOCKS_MAX = 2048;
 
-template <int L, bool RAGGED>
+template <int L, bool RAGGED, int VEC = 4>
 __global__ __launch_bounds__(256) void k_softmax_nll(int64_t n, int32_t C, const float* __restrict__ Z, int64_t ldz,
                                                      const int32_t* __restrict__ labels, float* __restrict__ G,
                                                      int64_t ldg, float inv_n, double* __restrict__ part) {
-    constexpr int ROWS = 256 / L, VEC = 4;
+    static_assert(VEC == 4 || (VEC == 2 && L == 1 && RAGGED), "at most two classes");
+    constexpr int ROWS = 256 / L, TAIL = VEC == 4 ? 3 : VEC;
     const int li = threadIdx.x % L;
     const int c0 = li * VEC;
-    const bool whole = c0 + VEC <= C;
+    const bool whole = VEC == 4 && c0 + VEC <= C;
     double mine = 0.0;
     for (int64_t i = (int64_t)blockIdx.x * ROWS + threadIdx.x / L; i < n; i += (int64_t)gridDim.x * ROWS) {
         const float* z = Z + i * ldz;
-        float v[VEC] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+        float v[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
         if (!RAGGED && whole) {
             const float4 t = *reinterpret_cast<const float4*>(z + c0);
             v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
@@ -34,7 +35,7 @@ __global__ __launch_bounds__(256) void k_softmax_nll(int64_t n, int32_t C, const
             v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
         } else if constexpr (RAGGED) {
 #pragma unroll
-            for (int e = 0; e < VEC - 1; ++e)
+            for (int e = 0; e < TAIL; ++e)
                 if (c0 + e < C) v[e] = z[c0 + e];
         }
         float m = v[0];
@@ -52,7 +53,7 @@ __global__ __launch_bounds__(256) void k_softmax_nll(int64_t n, int32_t C, const
         const bool labelled = y >= 0;           // negative label: vertex outside the training split
         y = y < 0 ? 0 : (y >= C ? C - 1 : y);   // labels >= C are the caller's error; stay in bounds
         if (G && c0 < C) {
-            float g[VEC];
+            float g[4] = {};
 #pragma unroll
             for (int e = 0; e < VEC; ++e)
                 g[e] = labelled ? (expf(v[e] - lse) - (c0 + e == y ? 1.f : 0.f)) * inv_n : 0.f;
@@ -60,7 +61,7 @@ __global__ __launch_bounds__(256) void k_softmax_nll(int64_t n, int32_t C, const
             else if (whole) *reinterpret_cast<f4u*>(G + i * ldg + c0) = f4u{g[0], g[1], g[2], g[3]};
             else if constexpr (RAGGED) {
 #pragma unroll
-                for (int e = 0; e < VEC - 1; ++e)
+                for (int e = 0; e < TAIL; ++e)
                     if (c0 + e < C) G[i * ldg + c0 + e] = g[e];
             }
         }
@@ -133,19 +134,21 @@ static void launch_rows(int64_t blocks, int64_t n, int32_t C, const float* Z, in
                         float* G, int64_t ldg, double* part, float inv_m, hipStream_t s) {
     const bool aligned = (C % 4 == 0) && (ldz % 4 == 0) && (((uintptr_t)Z & 15u) == 0) &&
                          (!G || ((ldg % 4 == 0) && (((uintptr_t)G & 15u) == 0)));
-    if (!aligned) hipLaunchKernelGGL((k_softmax_nll<L, true>), dim3((unsigned)blocks), dim3(256), 0, s, n, C, Z, ldz, labels, G, ldg, inv_m, part);
+    if (L == 1 && C <= 2) hipLaunchKernelGGL((k_softmax_nll<1, true, 2>), dim3((unsigned)blocks), dim3(256), 0, s, n, C, Z, ldz, labels, G, ldg, inv_m, part);
+    else if (!aligned) hipLaunchKernelGGL((k_softmax_nll<L, true>), dim3((unsigned)blocks), dim3(256), 0, s, n, C, Z, ldz, labels, G, ldg, inv_m, part);
     else hipLaunchKernelGGL((k_softmax_nll<L, false>), dim3((unsigned)blocks), dim3(256), 0, s, n, C, Z, ldz, labels, G, ldg, inv_m, part);
 }
 
 static void dispatch_rows(int64_t n, int32_t C, const float* Z, int64_t ldz, const int32_t* labels,
                           float* G, int64_t ldg, double* part, int64_t* blocks_out, float inv_m, hipStream_t s) {
-    int L = 2;
+    int L = 1;                                  // up to four classes a row is one lane's (two classes, 2 M rows: 12.9 us, two lanes 24.8)
     while (4 * L < C) L <<= 1;
     const int64_t rows_per_block = 256 / L;
     int64_t blocks = (n + rows_per_block - 1) / rows_per_block;
     if (blocks > LOSS_BLOCKS_MAX) blocks = LOSS_BLOCKS_MAX;
     *blocks_out = blocks;
     switch (L) {
+        case 1: launch_rows<1>(blocks, n, C, Z, ldz, labels, G, ldg, part, inv_m, s); break;
         case 2: launch_rows<2>(blocks, n, C, Z, ldz, labels, G, ldg, part, inv_m, s); break;
         case 4: launch_rows<4>(blocks, n, C, Z, ldz, labels, G, ldg, part, inv_m, s); break;
         case 8: launch_rows<8>(blocks, n, C, Z, ldz, labels, G, ldg, part, inv_m, s); break;

@@ -683,7 +683,7 @@ def test_csr_create_from_pairs_at_tile_edges(n, m, symmetrise, loops):
             arr[where] = kept
 
 
-@pytest.mark.parametrize("M,N", [(16, 16), (64, 16), (300, 16), (602, 16), (130, 32), (200, 48), (100, 64), (700, 64)])
+@pytest.mark.parametrize("M,N", [(16, 16), (64, 16), (300, 16), (602, 16), (130, 32), (200, 48), (100, 64), (700, 64), (7, 3), (24, 7)])
 @pytest.mark.parametrize("trips", [1, 2, 7, 8, 9, 16, 17])
 def test_gemm_tn_trips_and_sums(M, N, trips):
     """Numbers of 16-row trips at which the pipeline of the A^T B kernel ends, its sums are put aside, or the last trip is short; wide and
@@ -701,7 +701,7 @@ def test_gemm_tn_trips_and_sums(M, N, trips):
         assert np.linalg.norm(host(Y) - want) <= 5e-7 * np.linalg.norm(want), (K, M, N)
 
 
-@pytest.mark.parametrize("n,C", [(1, 1), (3, 2), (70, 3), (129, 5), (1000, 7), (300, 9), (257, 41), (64, 63), (65, 65), (100, 67), (33, 130), (40, 255), (20, 257)])
+@pytest.mark.parametrize("n,C", [(1, 1), (3, 2), (70, 3), (255, 1), (257, 2), (5000, 2), (513, 3), (300, 4), (129, 5), (1000, 7), (300, 9), (257, 41), (64, 63), (65, 65), (100, 67), (33, 130), (40, 255), (20, 257)])
 @pytest.mark.parametrize("pad,off", [(0, 0), (1, 0), (3, 2), (4, 4)])
 def test_softmax_of_ragged_rows(n, C, pad, off):
     """Rows that are no multiple of a lane's 16 bytes, at any pitch and alignment: loss, gradient, nothing written beside the rows."""
