@@ -528,9 +528,14 @@ static int fused_nt(int32_t C) {
 }
 
 // Four strips and more per wavefront, which pay for its operands and for its partial result (233 K rows, 41 classes, whole layer: 26 us
-// with 2048 workgroups, 21 with a thousand; 1.8 M, 24: 74 and 75).
-static int64_t fused_blocks(int64_t n) {
-    int64_t blocks = ((n + 15) / 16 + 15) / 16;
+// with 2048 workgroups, 21 with a thousand; 1.8 M, 24: 74 and 75), but as many workgroups as there are compute units before any takes a
+// second strip: a strip is a chain of latencies, and beyond 64 classes a workgroup goes through its strips one by one (epochs of
+// 982 rows, 183 classes 66.5 us with 4 workgroups, 36.0 with 62; 12 K, 166: 73.7 with 48, 49.9 with 256).
+static int64_t fused_blocks(int64_t n, int NT) {
+    const int64_t strips = (n + 15) / 16, at_once = NT > 4 ? strips : (strips + 3) / 4;
+    const int64_t cus = device_info().cus;
+    int64_t blocks = (strips + 15) / 16;
+    if (blocks < cus) blocks = at_once < cus ? at_once : cus;
     return blocks > FUSED_BLOCKS_MAX ? FUSED_BLOCKS_MAX : (blocks < 1 ? 1 : blocks);
 }
 
@@ -540,7 +545,7 @@ size_t fused_last_scratch_bytes(int64_t n, int32_t C) {
     const int NT = fused_nt(C);
     if (!NT) return 0;
     const size_t per = (size_t)16 * 16 * NT * sizeof(float);
-    return (size_t)fused_blocks(n) * per + (size_t)FUSED_BLOCKS_MAX * sizeof(double);
+    return (size_t)fused_blocks(n, NT) * per + (size_t)FUSED_BLOCKS_MAX * sizeof(double);
 }
 
 template <int NT>
@@ -566,7 +571,7 @@ int fused_last_launch(int64_t n, int32_t C, const float* T, const float* W, cons
     const int NT = fused_nt(C);
     if (!NT) return fail(GCN_ERR_BADARG, "fused last layer: more than 256 classes");
     if (((uintptr_t)T & 15u) || (S && ((uintptr_t)S & 15u))) return fail(GCN_ERR_BADARG, "fused last layer: unaligned operand");
-    const int64_t blocks = fused_blocks(n);
+    const int64_t blocks = fused_blocks(n, NT);
     const int count = 16 * 16 * NT;
     FusedArgs a;
     a.n = n; a.C = C; a.T = T; a.W = W; a.labels = labels; a.inv_m = 1.0f / (float)n_labelled;
