@@ -801,10 +801,11 @@ static TnShape tn_shape(int64_t M, int64_t N, int64_t K) {
     // but no more workgroups than run side by side: a workgroup loads its next trip while it multiplies, and the partial results
     // are written and read once more.  One per compute unit, two where the partial results are below 1/40 of the operands
     // (200 x 32 over 1 M rows 231 and 199 us; 256 x 64 over 120 K rows 52 and 64); four of the narrow kernel (16 x 16 over 4.4 M rows:
-    // 105 us, two 150, eight 112).  With up to 8192, and partial results below an eighth of the operands: 300 x 16 over 14.2 M
+    // 105 us, two 150, eight 112), eight where a row of both has less than 32 floats, so that lanes are idle and less is on its
+    // way (7 x 3 over 3.8 M rows: 62 us, four 67; 16 x 8 over 3.6 M 72 and 77).  With up to 8192, and partial results below an eighth of the operands: 300 x 16 over 14.2 M
     // rows 3.20 ms (now 2.86, 6.4 TB/s), 128 x 16 over 4.4 M 425 us (364), 256 x 64 over 120 K 89 (52), 602 x 64 over 100 K 255 (127).
     const int64_t cus = device_info().cus, operands = K * (g.Mw + g.Nw);
-    int64_t most = (g.narrow ? 4 : (80 * cus * count <= operands ? 2 : 1)) * cus / ((int64_t)g.ny * g.nz);
+    int64_t most = (g.narrow ? (g.Mw + g.Nw < 32 ? 8 : 4) : (80 * cus * count <= operands ? 2 : 1)) * cus / ((int64_t)g.ny * g.nz);
     // partial results below a third of the operands, unless that leaves fewer than 64 workgroups over K (fewer still where
     // the result alone is large)
     const int64_t fair = operands / (3 * count);
@@ -902,10 +903,14 @@ int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const floa
         }
         // Eight wavefronts share op(B), and no more workgroups than two per compute unit (one where op(B) allows no two) put it into
         // LDS: 128 x 64 on 200 K rows 59 us with 1536 workgroups of four, 40 with 512 of eight; 64 x 64 on 120 K rows 21 and
-        // 17; 16 x 16 on 4.4 M 110 and 100.
+        // 17; 16 x 16 on 4.4 M 110 and 100.  Four per compute unit where a strip leaves in two tiles of single floats, whose stores take
+        // longer than the rest (32 x 23 on 2.4 M 201 and 157; with one tile four take 1.03 of the time, with three 1.07), or of 16 bytes while
+        // operand and result are in the memory-side cache (32 x 32 on 400 K 20.6 and 18.5, on 820 K 37.0 and 34.4; on 1.8 M
+        // 98 and 105).
         constexpr int waves = 8;
         int64_t bx = (ntiles + waves - 1) / waves;
-        const int64_t cap = (int64_t)device_info().cus * (lds > 80 * 1024 ? 1 : 2);
+        const bool four = NT == 2 && lds <= 40 * 1024 && (!wide_c || M * (K + N) * 4 < (192ll << 20));
+        const int64_t cap = (int64_t)device_info().cus * (lds > 80 * 1024 ? 1 : (four ? 4 : 2));
         if (bx > cap) bx = cap;
         const dim3 grid((unsigned)bx, (unsigned)((nt_total + NT - 1) / NT));
         switch (NT) {
