@@ -254,6 +254,9 @@ size_t loss_scratch_bytes();
 // Compute units and L2 size (one XCD's) of the current device, read once per device from the runtime.
 struct DeviceInfo { int cus; int64_t l2_bytes; };
 const DeviceInfo& device_info();
+// Compute units for which kernels are cut whose partial results lie in the caller's workspace: its size, asked before or under another device,
+// and the order of the sums must not depend on the device that is current.
+constexpr int SIZED_FOR_CUS = 256;
 
 // op(A) as stored
 inline Matrix& matrix_of(gcn_csr* a, int trans) { return (trans && !a->symmetric) ? a->At : a->A; }

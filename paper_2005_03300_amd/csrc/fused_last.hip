@@ -533,7 +533,7 @@ static int fused_nt(int32_t C) {
 // 982 rows, 183 classes 66.5 us with 4 workgroups, 36.0 with 62; 12 K, 166: 73.7 with 48, 49.9 with 256).
 static int64_t fused_blocks(int64_t n, int NT) {
     const int64_t strips = (n + 15) / 16, at_once = NT > 4 ? strips : (strips + 3) / 4;
-    const int64_t cus = device_info().cus;
+    constexpr int64_t cus = SIZED_FOR_CUS;
     int64_t blocks = (strips + 15) / 16;
     if (blocks < cus) blocks = at_once < cus ? at_once : cus;
     return blocks > FUSED_BLOCKS_MAX ? FUSED_BLOCKS_MAX : (blocks < 1 ? 1 : blocks);

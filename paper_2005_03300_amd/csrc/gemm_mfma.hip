@@ -804,7 +804,7 @@ static TnShape tn_shape(int64_t M, int64_t N, int64_t K) {
     // 105 us, two 150, eight 112), eight where a row of both has less than 32 floats, so that lanes are idle and less is on its
     // way (7 x 3 over 3.8 M rows: 62 us, four 67; 16 x 8 over 3.6 M 72 and 77).  With up to 8192, and partial results below an eighth of the operands: 300 x 16 over 14.2 M
     // rows 3.20 ms (now 2.86, 6.4 TB/s), 128 x 16 over 4.4 M 425 us (364), 256 x 64 over 120 K 89 (52), 602 x 64 over 100 K 255 (127).
-    const int64_t cus = device_info().cus, operands = K * (g.Mw + g.Nw);
+    const int64_t cus = SIZED_FOR_CUS, operands = K * (g.Mw + g.Nw);
     int64_t most = (g.narrow ? (g.Mw + g.Nw < 32 ? 8 : 4) : (80 * cus * count <= operands ? 2 : 1)) * cus / ((int64_t)g.ny * g.nz);
     // partial results below a third of the operands, unless that leaves fewer than 64 workgroups over K (fewer still where
     // the result alone is large)
