@@ -350,7 +350,7 @@ int spmm_launch(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx, f
                 int epilogue, const float* Zprev, int64_t ldzprev, hipStream_t s, const SpmmOpt& o = SpmmOpt());
 // builds the stored order and sizes the handle's buffers that spmm_launch would need for width f (16-byte
 // aligned operands with leading dimensions that are multiples of 4 assumed), without running the product
-int spmm_prepare(gcn_csr* a, Matrix& m, int32_t f, hipStream_t s, bool any_schedule);
+int spmm_prepare(gcn_csr* a, Matrix& m, int32_t f, hipStream_t s, bool any_schedule, bool pattern = false);
 // grows one of the handle's buffers; the replaced buffer is retired, not freed
 int grow_retire(gcn_csr* a, float** buf, size_t* have, size_t need);
 

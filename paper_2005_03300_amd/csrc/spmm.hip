@@ -2122,10 +2122,11 @@ bool use_value_free(const gcn_csr* a) {
     return mode == 1 || a->nnz / (a->n > 0 ? a->n : 1) >= 64;
 }
 
-int spmm_prepare(gcn_csr* a, Matrix& m, int32_t f, hipStream_t s, bool any_schedule) {
+int spmm_prepare(gcn_csr* a, Matrix& m, int32_t f, hipStream_t s, bool any_schedule, bool pattern) {
     SpmmOpt o;
     o.dry = true;
     o.any_schedule = any_schedule;
+    o.pattern = pattern;
     return spmm_launch(a, m, f, nullptr, f, nullptr, f, GCN_EPI_NONE, nullptr, 0, s, o);
 }
 
@@ -2179,9 +2180,12 @@ extern "C" int gcn_spmm_prepare(gcn_csr* a, int trans, int32_t f, void* stream) 
     if (!a || f <= 0) return fail(GCN_ERR_BADARG, "gcn_spmm_prepare: NULL matrix or f <= 0");
     if (trans && !a->has_t) return fail(GCN_ERR_NOTRANSPOSE, "gcn_spmm_prepare: trans=1 needs GCN_BUILD_TRANSPOSE");
     if (use_value_free(a)) GCN_TRY(grow_retire(a, &a->xs, &a->xs_bytes, (size_t)a->n * (size_t)f * sizeof(float)));
-    // for the layer calls too: their backward and last products are free at every width
-    if (!free_schedule(f, trans, GCN_EPI_NONE)) GCN_TRY(spmm_prepare(a, matrix_of(a, trans), f, (hipStream_t)stream, false));
-    return spmm_prepare(a, matrix_of(a, trans), f, (hipStream_t)stream, true);
+    // for the layer calls too: their backward and last products are free at every width; and for gcn_spmm_pattern, whose schedule may be another
+    // where the stored values tell more than the caller's row factors (see Terms)
+    Matrix& m = matrix_of(a, trans);
+    if (!free_schedule(f, trans, GCN_EPI_NONE)) GCN_TRY(spmm_prepare(a, m, f, (hipStream_t)stream, false));
+    if (m.terms != Terms::BY_BOTH && m.terms != Terms::UNKNOWN) GCN_TRY(spmm_prepare(a, m, f, (hipStream_t)stream, true, true));
+    return spmm_prepare(a, m, f, (hipStream_t)stream, true);
 }
 
 extern "C" int gcn_spmm_describe(gcn_csr* a, int trans, int32_t f, char* out, size_t out_bytes, void* stream) {

@@ -1073,6 +1073,27 @@ def test_schedules_by_cost_of_the_transpose_are_no_less_exact(kind, mean, values
     a.close()
 
 
+@pytest.mark.parametrize("kind,n,mean", [("power", 250_000, 60), ("power", 800_000, 20), ("power", 810_000, 72), ("power", 980_000, 90), ("uniform", 500_000, 25)])
+@pytest.mark.parametrize("norm", ["none", "row", "sym"])
+def test_prepared_products_with_and_without_values_build_nothing(kind, n, mean, norm):
+    """gcn_spmm_prepare builds what gcn_spmm and gcn_spmm_pattern need at that width, also where the one knows the values and the other does not
+    and they take different schedules: no call after it builds an order."""
+    g = G()
+    (src, dst), gen = drawn_graph(kind, n, n * (mean - 1), 176)
+    rename = torch.randperm(n, generator=gen, device="cuda").int()
+    a = g.gcn_csr_create(n, rename[src], rename[dst], {"none": 0, "row": g.NORM_ROW, "sym": g.NORM_SYM}[norm] | g.ADD_SELF_LOOPS | g.BUILD_TRANSPOSE)
+    for f in (8, 16, 32, 64):
+        X, Z, ones = torch.rand(n, f, device="cuda"), torch.empty(n, f, device="cuda"), torch.ones(n, f, device="cuda")
+        for trans in (0, 1):
+            g.gcn_spmm_prepare(a, trans, f)
+            built = g.gcn_build_count()
+            for epi in (g.EPI_NONE, g.EPI_RELU, g.EPI_MASK):
+                g.gcn_spmm(a, trans, X, Z, epi, ones)
+                g.gcn_spmm_pattern(a, trans, X, Z, None, epi, ones)
+            assert g.gcn_build_count() == built, (kind, n, mean, norm, f, trans)
+    a.close()
+
+
 @pytest.mark.parametrize("n,k,f,usual", [(500_000, 41, 16, "split("), (500_000, 41, 32, "split("), (600_000, 100, 32, "split(")])
 def test_rows_that_fill_no_set_are_not_swept(n, k, f, usual):
     """Row i selects the columns k i to k i + k - 1 (mod n): as long as the rows and columns of a uniform matrix, and as many different columns, but
