@@ -6,20 +6,22 @@
 // so that neither product needs a transposition (or, here, floating-point atomics) at run time.
 //
 // Entries are encoded as 64-bit keys row<<cbits|col with cbits the bits of a column (so that the sort takes no pass over
-// unused bits); a radix sort of the keys followed by the removal of equal neighbours yields the canonical row-major
-// order with ascending columns.  The device-wide sort, selection and prefix sum are the ones of prims.h.
+// unused bits); their sort and the removal of equal neighbours yield the canonical row-major order with ascending columns.  Where
+// the rows fall into buckets that a compute unit sorts, that is done by row_sort.h, otherwise by the device-wide sort and selection
+// of prims.h.
 #include <cstring>
 #include <new>
 
 #include "common.h"
 #include "prims.h"
 #include "build_util.h"
+#include "row_sort.h"
 
 namespace gcn {
 
 // ---- kernels ---------------------------------------------------------------------------------
 
-// The keys of the sort: one per stored direction of each input pair, then the diagonal.  A pair with u == v is dropped: with
+// The keys of the radix sort: one per stored direction of each input pair, then the diagonal.  A pair with u == v is dropped: with
 // self loops its key is that of the diagonal entry, which exists anyway; without, it becomes the key n<<cbits, which sorts
 // behind every real one.  The first pass of the sort reads the pairs themselves: a kernel that wrote the keys and one that checked
 // the ids took 104 us for 16.8 M pairs, the pass takes 65 us longer than over written keys.  *bad is set where an id
@@ -426,27 +428,79 @@ static int build_transpose(gcn_csr* a, const uint64_t* keys, unsigned cbits, uin
     return GCN_OK;
 }
 
-static int create_impl(gcn_csr* a, int64_t n, int64_t m, const int32_t* src, const int32_t* dst, uint32_t flags,
-                       hipStream_t s) {
-    const bool sym = flags & GCN_SYMMETRISE, loops = flags & GCN_ADD_SELF_LOOPS;
-    const int mult = sym ? 2 : 1;
-    const int64_t cap = m * mult + (loops ? n : 0);
-    const unsigned cbits = bits_for(n), kbits = cbits + bits_for(n + 1);
+// The entries of A by the sort of row_sort.h: columns, row pointers and, where they are wanted, the sorted keys.  *done stays false where that
+// sort does not take the matrix.
+static int entries_by_rows(gcn_csr* a, int64_t n, int64_t m, const int32_t* src, const int32_t* dst, bool sym, bool loops, unsigned cbits,
+                           bool want_keys, TempBuf& keys, bool* done, hipStream_t s) {
+    using namespace rowsort;
+    const int64_t cap = m * (sym ? 2 : 1) + (loops ? n : 0);
+    unsigned shift;
+    uint32_t nb;
+    if (!takes(n, cap, cbits, &shift, &nb)) return GCN_OK;
+    const Items items{src, dst, m, n, m + (loops ? n : 0), sym, cbits, shift};
+    const int64_t share = (items.items + SHARES - 1) / SHARES;
+    const size_t most_tasks = (size_t)nb + (size_t)(cap / PIECE) + 1;
+    TempBuf info, table, total, start, tasks, at, count, offset, order, crowded, k0, k1;
+    GCN_TRY(info.alloc(sizeof(Info)));
+    GCN_TRY(table.alloc((size_t)SHARES * nb * 4));
+    GCN_TRY(total.alloc((size_t)nb * 4));
+    GCN_TRY(start.alloc((size_t)nb * 4));
+    GCN_TRY(tasks.alloc(most_tasks * sizeof(Task)));
+    GCN_TRY(at.alloc(most_tasks * 4));
+    GCN_TRY(count.alloc(most_tasks * 4));
+    GCN_TRY(offset.alloc(most_tasks * 4));
+    GCN_TRY(order.alloc(most_tasks * 4));
+    GCN_TRY(crowded.alloc(most_tasks * 4));
+    GCN_TRY(k0.alloc((size_t)cap * 4));
+    GCN_TRY(k1.alloc((size_t)cap * 4));
+    GCN_HIP_TRY(hipMemsetAsync(info.p, 0, sizeof(Info), s));
+    hipLaunchKernelGGL(k_part_count, dim3(SHARES), dim3(THREADS), 0, s, items, share, nb, table.as<uint32_t>(), info.as<Info>());
+    GCN_LAUNCH_CHECK();
+    hipLaunchKernelGGL(k_part_shares, dim3((nb + 63) / 64), dim3(THREADS), 0, s, nb, table.as<uint32_t>(), total.as<uint32_t>());
+    GCN_LAUNCH_CHECK();
+    hipLaunchKernelGGL(k_part_tasks, dim3(1), dim3(THREADS), 0, s, nb, (uint64_t)cap * 2, total.as<uint32_t>(), start.as<uint32_t>(), tasks.as<Task>(),
+                       order.as<uint32_t>(), info.as<Info>());
+    GCN_LAUNCH_CHECK();
+    launch_lds<k_part_scatter>(dim3(SHARES), THREADS, SCATTER_LDS, s, items, share, nb, (const uint32_t*)start.as<uint32_t>(),
+                               (const uint32_t*)table.as<uint32_t>(), (const Info*)info.as<Info>(), k0.as<uint32_t>());
+    GCN_LAUNCH_CHECK();
+    const SortArgs sort{cbits, shift, tasks.as<Task>(), order.as<uint32_t>(), k0.as<uint32_t>(), k1.as<uint32_t>(), at.as<uint32_t>(),
+                        count.as<uint32_t>(), crowded.as<uint32_t>(), info.as<Info>()};
+    launch_lds<k_part_sort>(dim3((unsigned)most_tasks), THREADS, sort_lds(shift), s, sort);
+    GCN_LAUNCH_CHECK();
+    launch_lds<k_part_sort_digits>(dim3((unsigned)device_info().cus), THREADS, sort_lds(0), s, sort);
+    GCN_LAUNCH_CHECK();
+    hipLaunchKernelGGL(k_part_offsets, dim3(1), dim3(THREADS), 0, s, (const uint32_t*)count.as<uint32_t>(), offset.as<uint32_t>(), info.as<Info>());
+    GCN_LAUNCH_CHECK();
+    Info h;
+    GCN_HIP_TRY(hipMemcpyAsync(&h, info.p, sizeof h, hipMemcpyDeviceToHost, s));
+    GCN_HIP_TRY(hipStreamSynchronize(s));
+    if (h.bad) return fail(GCN_ERR_RANGE, "gcn_csr_create: a vertex id is outside [0, %lld)", (long long)n);
+    if (h.refused) return GCN_OK;
+    a->nnz = h.kept;
+    GCN_TRY(device_alloc_t(&a->A.colidx, (size_t)h.kept));
+    if (want_keys) GCN_TRY(keys.alloc((size_t)h.kept * 8));
+    hipLaunchKernelGGL(k_part_emit, dim3(h.tasks), dim3(512), 0, s, n, nb, cbits, shift, (const Task*)tasks.as<Task>(), (const uint32_t*)at.as<uint32_t>(),
+                       (const uint32_t*)count.as<uint32_t>(), (const uint32_t*)offset.as<uint32_t>(), (const uint32_t*)k1.as<uint32_t>(), a->A.rowptr,
+                       a->A.colidx, want_keys ? keys.as<uint64_t>() : nullptr);
+    GCN_LAUNCH_CHECK();
+    *done = true;
+    return GCN_OK;
+}
 
-    const bool transpose = flags & GCN_BUILD_TRANSPOSE;
-    // Both directions of every pair are stored and the value formula (1, or 1/sqrt(d_i d_j)) is symmetric: A^T is A,
-    // bit by bit, and one set of arrays and schedules serves both.
-    a->symmetric = transpose && sym && !(flags & GCN_NORM_ROW);
-
-    TempBuf bad, k0, k1, off;
+// The same by a radix sort of 64-bit keys, for any matrix.
+static int entries_by_keys(gcn_csr* a, int64_t n, int64_t m, const int32_t* src, const int32_t* dst, bool sym, bool loops, unsigned cbits,
+                           bool want_keys, TempBuf& keys, hipStream_t s) {
+    const int64_t cap = m * (sym ? 2 : 1) + (loops ? n : 0);
+    const uint64_t none = (uint64_t)n << cbits;
+    TempBuf bad, k1, off;
     GCN_TRY(bad.alloc(sizeof(int)));
     GCN_HIP_TRY(hipMemsetAsync(bad.p, 0, sizeof(int), s));
     int64_t nnz = 0;
-    const uint64_t none = (uint64_t)n << cbits;
     if (cap > 0) {
         GCN_TRY(k1.alloc((size_t)cap * 8));
         GCN_TRY(prims::radix_sort_from(PairKeys{src, dst, m, n, sym, loops, cbits, bad.as<int>()}, k1.as<uint64_t>(), (size_t)cap,
-                                       loops ? cbits + bits_for(n) : kbits, s));
+                                       cbits + bits_for(loops ? n : n + 1), s));
         GCN_TRY(prims::select_positions(cap, prims::FirstOfRun{k1.as<uint64_t>()}, off, s));
         TempBuf result;
         GCN_TRY(result.alloc(sizeof(SortResult)));
@@ -459,22 +513,40 @@ static int create_impl(gcn_csr* a, int64_t n, int64_t m, const int32_t* src, con
         if (h.bad) return fail(GCN_ERR_RANGE, "gcn_csr_create: a vertex id is outside [0, %lld)", (long long)n);
         nnz = h.kept - (!loops && h.last == none ? 1 : 0);
     }
-    a->n = n;
-    a->ncols = n;
     a->nnz = nnz;
-    a->A.nrows = a->A.ncols = n;
-    a->A.terms = (flags & GCN_NORM_SYM) ? Terms::BY_BOTH : ((flags & GCN_NORM_ROW) ? Terms::BY_ROW : Terms::ALIKE);
-    a->At.terms = (flags & GCN_NORM_SYM) && sym ? Terms::BY_BOTH : Terms::ALIKE;      // (its rows are as long as a vertex has entries in A's columns)
-    GCN_TRY(device_alloc_t(&a->A.rowptr, (size_t)n + 1));
     GCN_TRY(device_alloc_t(&a->A.colidx, (size_t)nnz));
     if (cap > 0) {
-        if (transpose && !a->symmetric) GCN_TRY(k0.alloc((size_t)nnz * 8));
+        if (want_keys) GCN_TRY(keys.alloc((size_t)nnz * 8));
         GCN_TRY(prims::select_store(cap, prims::FirstOfRun{k1.as<uint64_t>()},
-                                    EmitEntry{k1.as<uint64_t>(), n, cbits, a->A.rowptr, a->A.colidx, k0.as<uint64_t>()}, off, s));
+                                    EmitEntry{k1.as<uint64_t>(), n, cbits, a->A.rowptr, a->A.colidx, want_keys ? keys.as<uint64_t>() : nullptr}, off, s));
     }
     hipLaunchKernelGGL(k_close_rows, dim3(degree_blocks(n)), dim3(256), 0, s, n, nnz, cap > 0 ? k1.as<uint64_t>() + (cap - 1) : nullptr,
                        cbits, a->A.rowptr);
     GCN_LAUNCH_CHECK();
+    return GCN_OK;
+}
+
+static int create_impl(gcn_csr* a, int64_t n, int64_t m, const int32_t* src, const int32_t* dst, uint32_t flags,
+                       hipStream_t s) {
+    const bool sym = flags & GCN_SYMMETRISE, loops = flags & GCN_ADD_SELF_LOOPS;
+    const unsigned cbits = bits_for(n);
+
+    const bool transpose = flags & GCN_BUILD_TRANSPOSE;
+    // Both directions of every pair are stored and the value formula (1, or 1/sqrt(d_i d_j)) is symmetric: A^T is A,
+    // bit by bit, and one set of arrays and schedules serves both.
+    a->symmetric = transpose && sym && !(flags & GCN_NORM_ROW);
+    a->n = n;
+    a->ncols = n;
+    a->A.nrows = a->A.ncols = n;
+    a->A.terms = (flags & GCN_NORM_SYM) ? Terms::BY_BOTH : ((flags & GCN_NORM_ROW) ? Terms::BY_ROW : Terms::ALIKE);
+    a->At.terms = (flags & GCN_NORM_SYM) && sym ? Terms::BY_BOTH : Terms::ALIKE;      // (its rows are as long as a vertex has entries in A's columns)
+    GCN_TRY(device_alloc_t(&a->A.rowptr, (size_t)n + 1));
+    TempBuf keys;                                          // row << cbits | column of every entry, for the transpose
+    const bool want_keys = transpose && !a->symmetric;
+    bool done = false;
+    GCN_TRY(entries_by_rows(a, n, m, src, dst, sym, loops, cbits, want_keys, keys, &done, s));
+    if (!done) GCN_TRY(entries_by_keys(a, n, m, src, dst, sym, loops, cbits, want_keys, keys, s));
+    const int64_t nnz = a->nnz;
     GCN_TRY(device_alloc_t(&a->deg, (size_t)n));
     GCN_TRY(device_alloc_t(&a->A.val, (size_t)nnz));
     GCN_TRY(build_schedule(a->A, n, nnz, s, a->deg));
@@ -496,7 +568,11 @@ static int create_impl(gcn_csr* a, int64_t n, int64_t m, const int32_t* src, con
         GCN_TRY(inv_sqrt_deg_launch(n, a->deg, a->inv_sqrt_deg, s));
     }
     if (a->symmetric) a->has_t = true;
-    else if (transpose) GCN_TRY(build_transpose(a, k0.as<uint64_t>(), cbits, k1.as<uint64_t>(), s));
+    else if (transpose) {
+        TempBuf sorted;
+        GCN_TRY(sorted.alloc((size_t)nnz * 8));
+        GCN_TRY(build_transpose(a, keys.as<uint64_t>(), cbits, sorted.as<uint64_t>(), s));
+    }
     return GCN_OK;
 }
 

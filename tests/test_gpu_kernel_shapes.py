@@ -683,6 +683,63 @@ def test_csr_create_from_pairs_at_tile_edges(n, m, symmetrise, loops):
             arr[where] = kept
 
 
+def uneven_pairs(kind):
+    """Pairs whose rows do not fall into even buckets, or whose columns do not spread over them."""
+    rs = np.random.default_rng(131)
+    pairs = lambda n, m: (rs.integers(0, n, m), rs.integers(0, n, m))
+    if kind == "even":                           # as many buckets as there may be, tiles that end anywhere
+        n = 4_000_037
+        src, dst = pairs(n, 1_200_007)
+    elif kind == "wide":                         # a bucket is one row of a few, with thousands of keys
+        n = 700
+        src, dst = pairs(n, 1_500_000)
+    elif kind == "hub":                          # two rows fill several pieces each, the columns of one lie close together
+        n = 300_007
+        src, dst = pairs(n, 1_000_000)
+        src[:150_000] = 77
+        src[150_000:260_000], dst[150_000:260_000] = 123_456, rs.integers(5000, 90_000, 110_000)
+    elif kind == "star":                         # one row has nearly everything: by keys
+        n = 500_000
+        src, dst = pairs(n, 600_000)
+        src[:] = 3
+    elif kind == "band":                         # neighbouring columns: by digits
+        n = 60_001
+        src = np.repeat(np.arange(n), 30)
+        dst = np.minimum(src + np.tile(np.arange(30), n), n - 1)
+    elif kind == "repeats":                      # pairs that come back a hundred times
+        n = 40_000
+        src, dst = (np.tile(x, 100) for x in pairs(n, 9_000))
+    elif kind == "same":                         # one pair fills more than a piece: by keys
+        n = 300_000
+        src, dst = pairs(n, 400_000)
+        src[:100_000], dst[:100_000] = 1234, 4321
+    else:                                        # "last": the largest bucket that is not cut, and one more key
+        n = 1 << 19
+        src, dst = pairs(n, 300_000)
+        rows = int(kind[4:])
+        src[:rows], dst[:rows] = 2047 + 2048 * 7, rs.permutation(n)[:rows]
+    return n, src.astype(np.int32), dst.astype(np.int32)
+
+
+@pytest.mark.parametrize("kind", ["even", "wide", "hub", "star", "band", "repeats", "same", "last23000", "last24577"])
+@pytest.mark.parametrize("symmetrise", [False, True])
+def test_csr_create_from_uneven_pairs(kind, symmetrise):
+    """Each way the entries are sorted in (buckets in the LDS, pieces of large buckets, crowded places by digits, all of them by 64-bit
+    keys), bit for bit against the oracle, and the transpose, whose sort starts from the sorted keys."""
+    g = G()
+    n, src, dst = uneven_pairs(kind)
+    for loops, norm, flag in ((True, "sym", g.NORM_SYM), (False, "row", g.NORM_ROW)):
+        flags = flag | (g.SYMMETRISE if symmetrise else 0) | (g.ADD_SELF_LOOPS if loops else 0) | g.BUILD_TRANSPOSE
+        a = g.gcn_csr_create(n, dev(src), dev(dst), flags)
+        for trans in (False, True):
+            ref = oracle.build_csr(n, src, dst, symmetrise=symmetrise, self_loops=loops, norm=norm)
+            ref = oracle.transpose(ref) if trans else ref
+            rowptr, colidx, val, _ = a.arrays(trans)
+            assert np.array_equal(host(rowptr), ref.rowptr) and np.array_equal(host(colidx), ref.colidx), (norm, trans)
+            assert np.array_equal(host(val).view(np.uint32), ref.val.view(np.uint32)), (norm, trans)
+        a.close()
+
+
 @pytest.mark.parametrize("M,N", [(16, 16), (64, 16), (300, 16), (602, 16), (130, 32), (200, 48), (100, 64), (700, 64), (7, 3), (24, 7)])
 @pytest.mark.parametrize("trips", [1, 2, 7, 8, 9, 16, 17])
 def test_gemm_tn_trips_and_sums(M, N, trips):
