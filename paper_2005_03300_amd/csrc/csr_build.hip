@@ -128,7 +128,10 @@ __global__ __launch_bounds__(1024) void k_sample_columns(int64_t nnz, const int3
     if (threadIdx.x == 0) ones[blockIdx.x] = s_ones;
 }
 
-__global__ __launch_bounds__(256) void k_degrees(int64_t n, const int64_t* __restrict__ rowptr, int32_t* __restrict__ deg,
+// As few workgroups as keep the loads going: each of them ends with up to 70 additions to counters that all share (1 M rows, 512 workgroups of
+// 256: 27 us; 128 of 1024: 17).
+constexpr int DEGREE_THREADS = 1024;
+__global__ __launch_bounds__(DEGREE_THREADS) void k_degrees(int64_t n, const int64_t* __restrict__ rowptr, int32_t* __restrict__ deg,
                                                  DegreeSums* __restrict__ sums) {
     __shared__ unsigned s_rows[Lengths::BINS];
     __shared__ unsigned long long s_entries[Lengths::BINS];
@@ -137,7 +140,7 @@ __global__ __launch_bounds__(256) void k_degrees(int64_t n, const int64_t* __res
     int32_t m = 0;
     unsigned nz = 0;
     unsigned long long sum = 0, squares = 0;
-    for (int64_t first = (int64_t)blockIdx.x * 256; first < n; first += (int64_t)gridDim.x * 256) {
+    for (int64_t first = (int64_t)blockIdx.x * DEGREE_THREADS; first < n; first += (int64_t)gridDim.x * DEGREE_THREADS) {
         const int64_t i = first + threadIdx.x;
         int32_t d = 0;
         if (i < n) {
@@ -164,16 +167,16 @@ __global__ __launch_bounds__(256) void k_degrees(int64_t n, const int64_t* __res
         m = o > m ? o : m;
         nz += __shfl_xor(nz, s, 64);
     }
-    __shared__ int32_t s_m[4];
-    __shared__ unsigned s_nz[4];
-    __shared__ unsigned long long s_sum[4], s_squares[4];
+    __shared__ int32_t s_m[DEGREE_THREADS / 64];
+    __shared__ unsigned s_nz[DEGREE_THREADS / 64];
+    __shared__ unsigned long long s_sum[DEGREE_THREADS / 64], s_squares[DEGREE_THREADS / 64];
     if ((threadIdx.x & 63) == 0) {
         const int w = threadIdx.x >> 6;
         s_m[w] = m; s_nz[w] = nz; s_sum[w] = sum; s_squares[w] = squares;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int w = 1; w < 4; ++w) { m = s_m[w] > m ? s_m[w] : m; nz += s_nz[w]; sum += s_sum[w]; squares += s_squares[w]; }
+        for (int w = 1; w < DEGREE_THREADS / 64; ++w) { m = s_m[w] > m ? s_m[w] : m; nz += s_nz[w]; sum += s_sum[w]; squares += s_squares[w]; }
         atomicMax(&sums->max_deg, m);
         if (nz) {
             atomicAdd(&sums->n_nonempty, (unsigned long long)nz);
@@ -187,8 +190,8 @@ __global__ __launch_bounds__(256) void k_degrees(int64_t n, const int64_t* __res
     }
 }
 static unsigned degree_blocks(int64_t n) {
-    const int64_t b = (n + 1023) / 1024;
-    return (unsigned)(b < 1 ? 1 : (b > 512 ? 512 : b));
+    const int64_t b = (n + DEGREE_THREADS - 1) / DEGREE_THREADS;
+    return (unsigned)(b < 1 ? 1 : (b > 128 ? 128 : b));
 }
 
 // val(i,j) = (float)(1 / sqrt(d_i d_j)): exact integer product in double, correctly rounded
@@ -332,10 +335,10 @@ int build_fix_list(const uint32_t* flags, const int32_t* sub_row, const int64_t*
     // both kinds are positioned before the host waits for their numbers, once
     const LeadsCarry longs{flags, sub_row, rp, nnz, true}, shorts{flags, sub_row, rp, nnz, false};
     TempBuf sel, off_long, off_short, totals;
-    GCN_TRY(prims::select_positions(nchunks - 1, longs, off_long, s));
-    GCN_TRY(prims::select_positions(nchunks - 1, shorts, off_short, s));
+    GCN_TRY(prims::select_positions<1>(nchunks - 1, longs, off_long, s));
+    GCN_TRY(prims::select_positions<1>(nchunks - 1, shorts, off_short, s));
     GCN_TRY(totals.alloc(16));
-    hipLaunchKernelGGL(k_two_totals, dim3(1), dim3(1), 0, s, prims::select_total(nchunks - 1, off_long), prims::select_total(nchunks - 1, off_short),
+    hipLaunchKernelGGL(k_two_totals, dim3(1), dim3(1), 0, s, prims::select_total<1>(nchunks - 1, off_long), prims::select_total<1>(nchunks - 1, off_short),
                        totals.as<int64_t>());
     GCN_LAUNCH_CHECK();
     int64_t h[2] = {0, 0};
@@ -345,13 +348,23 @@ int build_fix_list(const uint32_t* flags, const int32_t* sub_row, const int64_t*
     const int64_t nsel = h[0] + h[1];
     if (nsel > 0) {
         GCN_TRY(sel.alloc((size_t)nsel * 4));
-        GCN_TRY(prims::select_store(nchunks - 1, longs, prims::EmitIndex32{sel.as<int32_t>()}, off_long, s));
-        GCN_TRY(prims::select_store(nchunks - 1, shorts, prims::EmitIndex32{sel.as<int32_t>() + h[0]}, off_short, s));
+        GCN_TRY(prims::select_store<1>(nchunks - 1, longs, prims::EmitIndex32{sel.as<int32_t>()}, off_long, s));
+        GCN_TRY(prims::select_store<1>(nchunks - 1, shorts, prims::EmitIndex32{sel.as<int32_t>() + h[0]}, off_short, s));
         GCN_TRY(device_alloc_t(list, (size_t)nsel));
         hipLaunchKernelGGL(k_fix_records, dim3(blocks_for(nsel)), dim3(TPB), 0, s, nsel, sel.as<int32_t>(), sub_row, rp, *list);
         GCN_LAUNCH_CHECK();
     }
     *count = nsel;
+    return GCN_OK;
+}
+
+// The flag words and the rows of every 32nd entry, zeroed.
+static int alloc_subs(Matrix& m, int64_t nnz, hipStream_t s) {
+    const size_t words = (size_t)((nnz + SUB - 1) / SUB) + SUBS_PER_CHUNK;                // padded: one chunk of zero words
+    GCN_TRY(device_alloc_t(&m.flags, words));
+    GCN_TRY(device_alloc_t(&m.sub_row, words));
+    GCN_HIP_TRY(hipMemsetAsync(m.flags, 0, words * sizeof(uint32_t), s));
+    GCN_HIP_TRY(hipMemsetAsync(m.sub_row, 0, words * sizeof(int32_t), s));
     return GCN_OK;
 }
 
@@ -361,7 +374,7 @@ int build_schedule(Matrix& m, int64_t n, int64_t nnz, hipStream_t s, int32_t* de
     TempBuf counters;
     GCN_TRY(counters.alloc(sizeof(DegreeSums)));
     GCN_HIP_TRY(hipMemsetAsync(counters.p, 0, sizeof(DegreeSums), s));
-    hipLaunchKernelGGL(k_degrees, dim3(degree_blocks(n)), dim3(256), 0, s, n, m.rowptr, deg, counters.as<DegreeSums>());
+    hipLaunchKernelGGL(k_degrees, dim3(degree_blocks(n)), dim3(DEGREE_THREADS), 0, s, n, m.rowptr, deg, counters.as<DegreeSums>());
     GCN_LAUNCH_CHECK();
     const bool sampled = nnz >= PLANNED_NNZ;
     static_assert(PLANNED_NNZ >= RowOrder::STRETCH, "windows lie inside the matrix");
@@ -395,13 +408,13 @@ int build_schedule(Matrix& m, int64_t n, int64_t nnz, hipStream_t s, int32_t* de
         GCN_TRY(prims::select_indices(n, epred, m.empty_rows, nullptr, s));
         rp = m.ne_rowptr;
     }
-    GCN_TRY(device_alloc_t(&m.flags, (size_t)m.nsub + SUBS_PER_CHUNK));   // padded: one chunk of zero words
-    GCN_TRY(device_alloc_t(&m.sub_row, (size_t)m.nsub + SUBS_PER_CHUNK));
-    GCN_HIP_TRY(hipMemsetAsync(m.flags, 0, ((size_t)m.nsub + SUBS_PER_CHUNK) * sizeof(uint32_t), s));
-    GCN_HIP_TRY(hipMemsetAsync(m.sub_row, 0, ((size_t)m.nsub + SUBS_PER_CHUNK) * sizeof(int32_t), s));
-    if (nnz > 0) {
+    const bool given = m.flags != nullptr;                     // by k_part_emit, sub_row with the rows themselves
+    if (!given) GCN_TRY(alloc_subs(m, nnz, s));
+    if (nnz > 0 && !given) {
         hipLaunchKernelGGL(k_row_flags, dim3(blocks_for(m.n_ne)), dim3(TPB), 0, s, m.n_ne, rp, m.flags);
         GCN_LAUNCH_CHECK();
+    }
+    if (nnz > 0 && (!given || m.n_ne < n)) {
         hipLaunchKernelGGL(k_sub_rows, dim3(blocks_for(m.nsub)), dim3(TPB), 0, s, m.nsub, m.n_ne, rp, m.sub_row);
         GCN_LAUNCH_CHECK();
     }
@@ -480,9 +493,10 @@ static int entries_by_rows(gcn_csr* a, int64_t n, int64_t m, const int32_t* src,
     a->nnz = h.kept;
     GCN_TRY(device_alloc_t(&a->A.colidx, (size_t)h.kept));
     if (want_keys) GCN_TRY(keys.alloc((size_t)h.kept * 8));
+    GCN_TRY(alloc_subs(a->A, h.kept, s));
     hipLaunchKernelGGL(k_part_emit, dim3(h.tasks), dim3(512), 0, s, n, nb, cbits, shift, (const Task*)tasks.as<Task>(), (const uint32_t*)at.as<uint32_t>(),
                        (const uint32_t*)count.as<uint32_t>(), (const uint32_t*)offset.as<uint32_t>(), (const uint32_t*)k1.as<uint32_t>(), a->A.rowptr,
-                       a->A.colidx, want_keys ? keys.as<uint64_t>() : nullptr);
+                       a->A.colidx, want_keys ? keys.as<uint64_t>() : nullptr, a->A.flags, a->A.sub_row);
     GCN_LAUNCH_CHECK();
     *done = true;
     return GCN_OK;
@@ -520,7 +534,7 @@ static int entries_by_keys(gcn_csr* a, int64_t n, int64_t m, const int32_t* src,
         GCN_TRY(prims::select_store(cap, prims::FirstOfRun{k1.as<uint64_t>()},
                                     EmitEntry{k1.as<uint64_t>(), n, cbits, a->A.rowptr, a->A.colidx, want_keys ? keys.as<uint64_t>() : nullptr}, off, s));
     }
-    hipLaunchKernelGGL(k_close_rows, dim3(degree_blocks(n)), dim3(256), 0, s, n, nnz, cap > 0 ? k1.as<uint64_t>() + (cap - 1) : nullptr,
+    hipLaunchKernelGGL(k_close_rows, dim3(blocks_for(n < (1 << 19) ? n : (1 << 19), 1024)), dim3(256), 0, s, n, nnz, cap > 0 ? k1.as<uint64_t>() + (cap - 1) : nullptr,
                        cbits, a->A.rowptr);
     GCN_LAUNCH_CHECK();
     return GCN_OK;

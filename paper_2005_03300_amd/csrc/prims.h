@@ -123,13 +123,16 @@ template <typename T> int exclusive_scan(const T* in, T* out, size_t n, hipStrea
 // A tile's indices are dealt out 64 at a time to the wavefronts, so that neighbouring lanes read and write neighbouring
 // elements; a wavefront counts and ranks its 64 by ballot (unique over 34.6 M keys: 505 -> 200 us).
 
-constexpr int SEL_ITEMS = 16;
-constexpr int SEL_TILE = P_TPB * SEL_ITEMS;
+// ITEMS: indices per thread.  SEL_ITEMS, or one where a predicate is a chain of loads and the candidates are few: 65 K of them in 16
+// tiles took 16 us per pass, in 256 tiles 4.
 
-template <typename Pred>
+constexpr int SEL_ITEMS = 16;
+template <int ITEMS> constexpr int64_t sel_tiles(int64_t n) { return (n + P_TPB * ITEMS - 1) / (P_TPB * ITEMS); }
+
+template <int SEL_ITEMS, typename Pred>
 __global__ __launch_bounds__(P_TPB) void k_select_count(int64_t n, Pred pred, int64_t* __restrict__ tile_cnt) {
     __shared__ int part[P_WAVES];
-    const int64_t base = (int64_t)blockIdx.x * SEL_TILE + threadIdx.x;
+    const int64_t base = (int64_t)blockIdx.x * (P_TPB * SEL_ITEMS) + threadIdx.x;
     int c = 0;                                     // the same in every lane of a wavefront
 #pragma unroll
     for (int k = 0; k < SEL_ITEMS; ++k) {
@@ -145,12 +148,12 @@ __global__ __launch_bounds__(P_TPB) void k_select_count(int64_t n, Pred pred, in
     }
 }
 
-template <typename Pred, typename Emit>
+template <int SEL_ITEMS, typename Pred, typename Emit>
 __global__ __launch_bounds__(P_TPB) void k_select_emit(int64_t n, Pred pred, Emit emit,
                                                       const int64_t* __restrict__ tile_off) {
     __shared__ int cnt[SEL_ITEMS * P_WAVES];       // kept indices of every 64, in index order
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int64_t base = (int64_t)blockIdx.x * SEL_TILE + threadIdx.x;
+    const int64_t base = (int64_t)blockIdx.x * (P_TPB * SEL_ITEMS) + threadIdx.x;
     unsigned long long kept[SEL_ITEMS];
 #pragma unroll
     for (int k = 0; k < SEL_ITEMS; ++k) {
@@ -159,10 +162,10 @@ __global__ __launch_bounds__(P_TPB) void k_select_emit(int64_t n, Pred pred, Emi
         if (lane == 0) cnt[k * P_WAVES + w] = __popcll(kept[k]);
     }
     __syncthreads();
-    static_assert(SEL_ITEMS * P_WAVES == 64, "one wavefront scans the counts");
+    static_assert(SEL_ITEMS * P_WAVES <= 64, "one wavefront scans the counts");
     if (w == 0) {
-        const int c = cnt[lane];
-        cnt[lane] = (int)wave_inclusive_sum((unsigned)c) - c;
+        const int c = lane < SEL_ITEMS * P_WAVES ? cnt[lane] : 0, before = (int)wave_inclusive_sum((unsigned)c) - c;
+        if (lane < SEL_ITEMS * P_WAVES) cnt[lane] = before;
     }
     __syncthreads();
     const int64_t off = tile_off[blockIdx.x];
@@ -173,21 +176,21 @@ __global__ __launch_bounds__(P_TPB) void k_select_emit(int64_t n, Pred pred, Emi
 }
 
 // The first pass: tile_off receives the position of each tile's first kept index and, behind them, the number of kept ones.
-template <typename Pred> int select_positions(int64_t n, Pred pred, Scratch& tile_off, hipStream_t s) {
-    const int64_t ntiles = (n + SEL_TILE - 1) / SEL_TILE;
+template <int ITEMS = SEL_ITEMS, typename Pred> int select_positions(int64_t n, Pred pred, Scratch& tile_off, hipStream_t s) {
+    const int64_t ntiles = sel_tiles<ITEMS>(n);
     if (ntiles >= (1ll << 31)) return fail(GCN_ERR_RANGE, "select: %lld candidates are too many", (long long)n);
     GCN_TRY(tile_off.alloc((size_t)(ntiles + 1) * 8));
     int64_t* const cnt = tile_off.as<int64_t>();
     GCN_HIP_TRY(hipMemsetAsync(cnt + ntiles, 0, 8, s));
-    hipLaunchKernelGGL(k_select_count<Pred>, dim3((unsigned)ntiles), dim3(P_TPB), 0, s, n, pred, cnt);
+    hipLaunchKernelGGL((k_select_count<ITEMS, Pred>), dim3((unsigned)ntiles), dim3(P_TPB), 0, s, n, pred, cnt);
     GCN_LAUNCH_CHECK();
     return exclusive_scan<int64_t>(cnt, cnt, (size_t)ntiles + 1, s);
 }
-inline const int64_t* select_total(int64_t n, const Scratch& tile_off) { return tile_off.as<int64_t>() + (n + SEL_TILE - 1) / SEL_TILE; }
+template <int ITEMS = SEL_ITEMS> const int64_t* select_total(int64_t n, const Scratch& tile_off) { return tile_off.as<int64_t>() + sel_tiles<ITEMS>(n); }
 
 // The second.
-template <typename Pred, typename Emit> int select_store(int64_t n, Pred pred, Emit emit, const Scratch& tile_off, hipStream_t s) {
-    hipLaunchKernelGGL((k_select_emit<Pred, Emit>), dim3((unsigned)((n + SEL_TILE - 1) / SEL_TILE)), dim3(P_TPB), 0, s, n, pred, emit,
+template <int ITEMS = SEL_ITEMS, typename Pred, typename Emit> int select_store(int64_t n, Pred pred, Emit emit, const Scratch& tile_off, hipStream_t s) {
+    hipLaunchKernelGGL((k_select_emit<ITEMS, Pred, Emit>), dim3((unsigned)sel_tiles<ITEMS>(n)), dim3(P_TPB), 0, s, n, pred, emit,
                        (const int64_t*)tile_off.as<int64_t>());
     GCN_LAUNCH_CHECK();
     return GCN_OK;

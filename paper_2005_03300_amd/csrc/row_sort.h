@@ -5,7 +5,7 @@
 // column), a workgroup sorts a bucket in LDS and drops the repeated keys, and one last pass writes columns and row pointers.  A
 // radix sort of the 8-byte keys (prims.h), which takes over where this does not fit, reads and writes them once per 8 bits and
 // once more to drop the repeated ones.  16.8 M pairs of 1 M vertices, R-MAT (34.6 M keys): 1.35 ms that way; here counting 63 us,
-// scatter 132, sort 288, columns and row pointers 84.  Whole constructions, symmetrised: uniform 20 M pairs of 100 K vertices 2.11 ->
+// scatter 132, sort 288, columns and row pointers 84 (100 with the schedule's words).  Whole constructions, symmetrised: uniform 20 M pairs of 100 K vertices 2.11 ->
 // 1.01 ms, 14 M of 3.9 M 2.17 -> 1.20; R-MAT 38 M of 1 M 3.98 -> 2.18; 100 K pairs of 10 K 0.31 -> 0.23.  Entries that lie in a few
 // buckets are refused after the counting, which costs such constructions 4 to 9 % (8 M pairs of one vertex 1.02 -> 1.10 ms).
 #pragma once
@@ -739,26 +739,45 @@ __global__ __launch_bounds__(THREADS) void k_part_offsets(const uint32_t* __rest
 }
 
 // Columns and row pointers of a task's entries: an entry opens the rows after that of the entry before it, the last piece of a bucket
-// closes the bucket's rows.  keys (or NULL): also row << cbits | column of every entry.
+// closes the bucket's rows.  Also the schedule's flag words (a bit per entry that starts a row, zeroed before) and the row of every 32nd
+// entry: a wavefront takes 64 entries from a multiple of 64 on, so that it owns two words, except for those at the ends of the task.
+// (34 M entries: two passes over the row pointers and a bisection per 32 entries took 54 us, this kernel 100 with them and 84
+// without.)  keys (or NULL): also row << cbits | column of every entry.
 __global__ __launch_bounds__(512) void k_part_emit(int64_t n, uint32_t nb, unsigned cbits, unsigned shift, const Task* __restrict__ tasks,
                                                    const uint32_t* __restrict__ at_of, const uint32_t* __restrict__ count_of,
                                                    const uint32_t* __restrict__ offset, const uint32_t* __restrict__ in,
-                                                   int64_t* __restrict__ rowptr, int32_t* __restrict__ colidx, uint64_t* __restrict__ keys) {
+                                                   int64_t* __restrict__ rowptr, int32_t* __restrict__ colidx, uint64_t* __restrict__ keys,
+                                                   uint32_t* __restrict__ flags, int32_t* __restrict__ sub_row) {
+    static_assert(SUB == 32, "two words per wavefront");
     const Task t = tasks[blockIdx.x];
     const uint32_t count = count_of[blockIdx.x], off = offset[blockIdx.x], cmask = (1u << cbits) - 1u;
     const uint32_t* const from = in + at_of[blockIdx.x];
     const int64_t row0 = (int64_t)t.bucket << shift;
+    const int lane = threadIdx.x & 63;
     int32_t before = -1;                                        // row in the bucket of the entry before the first
     for (uint32_t p = t.part, i = blockIdx.x; p > 0 && before < 0; --p) {
         --i;
         if (count_of[i] > 0) before = (int32_t)(in[at_of[i] + count_of[i] - 1] >> cbits);
     }
-    for (uint32_t j = threadIdx.x; j < count; j += 512) {
-        const uint32_t key = from[j];
-        const int32_t r = (int32_t)(key >> cbits), last = j > 0 ? (int32_t)(from[j - 1] >> cbits) : before;
-        for (int32_t q = last + 1; q <= r; ++q) rowptr[row0 + q] = off + j;
-        colidx[off + j] = (int32_t)(key & cmask);
-        if (keys) keys[off + j] = (uint64_t)(row0 + r) << cbits | (key & cmask);
+    const int32_t lead = (int32_t)(off & 63u);                  // entries of the first 64 that are another task's
+    for (int32_t j0 = (int32_t)(threadIdx.x & ~63u) - lead; j0 < (int32_t)count; j0 += 512) {
+        const int32_t j = j0 + lane;
+        const bool here = j >= 0 && j < (int32_t)count;
+        const uint32_t at = off + (uint32_t)j, key = here ? from[j] : 0;
+        const int32_t r = (int32_t)(key >> cbits), last = here && j > 0 ? (int32_t)(from[j - 1] >> cbits) : before;
+        if (here) {
+            for (int32_t q = last + 1; q <= r; ++q) rowptr[row0 + q] = at;
+            colidx[at] = (int32_t)(key & cmask);
+            if (keys) keys[at] = (uint64_t)(row0 + r) << cbits | (key & cmask);
+            if ((lane & 31) == 0) sub_row[at / SUB] = (int32_t)(row0 + r);
+        }
+        const unsigned long long starts = __ballot(here && r > last);
+        if ((lane & 31) == 0 && j < (int32_t)count && j + 31 >= 0) {
+            const uint32_t word = (uint32_t)(starts >> lane);
+            uint32_t* const f = flags + (int64_t)(off + (int64_t)j) / SUB;
+            if (j >= 0 && j + 32 <= (int32_t)count) *f = word;
+            else atomicOr(f, word);
+        }
     }
     if (t.part + 1 < t.parts) return;
     const int64_t end = t.bucket + 1 < nb ? row0 + (1ll << shift) : n + 1;
