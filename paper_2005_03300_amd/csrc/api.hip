@@ -209,6 +209,15 @@ ScratchScope::~ScratchScope() {
     g_scope_bytes = prev_bytes;
 }
 
+static thread_local EpochEnd* g_epoch_end = nullptr;
+EpochEnd::EpochEnd(void* p, size_t bytes) : room(bytes ? (char*)p : nullptr), left(bytes) {
+    if (room) g_epoch_end = this;
+}
+EpochEnd::~EpochEnd() {
+    if (g_epoch_end == this) g_epoch_end = nullptr;
+}
+EpochEnd* epoch_end() { return g_epoch_end; }
+
 int scratch_get(void** p, size_t bytes, hipStream_t s) {
     if (g_scope_p) {
         if (bytes > g_scope_bytes)

@@ -246,6 +246,53 @@ struct ScratchScope {
     void* prev_p;
     size_t prev_bytes;
 };
+// The additions that an epoch leaves to its end: the partial results of the weight gradients, those of the loss, and the update of the
+// weights, all in one kernel.  While one of these is alive on a thread, the products and the loss that it has room for leave their
+// partial results there (epoch_end); finish() adds them up in the order in which kernels of their own do.
+struct EpochEnd {
+    static constexpr int MOST = 8;
+    struct Sum {                                  // Y (M x N) = the sum of `parts` partial results, each M x N, or N x M when transposed
+        const float* part;
+        float* Y;
+        float* W;                                 // W -= lr Y, or NULL
+        int32_t M, N, parts, transposed, first;   // first: of its workgroups
+    };
+    struct Fused {                                // partial results of the fused last layer (see k_fused_y)
+        const float* part = nullptr;
+        float* Y = nullptr;
+        float* W = nullptr;
+        int32_t C = 0, CP = 0, blocks = 0, first = 0;
+    };
+    struct Args {
+        Sum sums[MOST];
+        Fused fused;
+        const double* lpart = nullptr;
+        double inv_m = 0;
+        float* loss = nullptr;
+        int64_t lparts = 0;
+        int32_t count = 0, loss_at = -1;
+        float lr = 0;
+    } args;
+    char* room;
+    size_t left;
+    float* W = nullptr;                           // of the layer whose gradient comes next
+    EpochEnd(void* p, size_t bytes);              // no room: everything as without it
+    ~EpochEnd();
+    // `bytes` of its room, or NULL
+    void* take(size_t bytes) {
+        const size_t need = (bytes + 255) & ~(size_t)255;
+        if (!room || args.count == MOST || need > left) return nullptr;
+        void* p = room;
+        room += need;
+        left -= need;
+        return p;
+    }
+    void add(const float* part, float* Y, int32_t M, int32_t N, int parts, bool transposed) {
+        args.sums[args.count++] = Sum{part, Y, W, M, N, (int32_t)parts, transposed ? 1 : 0, 0};
+    }
+    int finish(float lr, hipStream_t s);
+};
+EpochEnd* epoch_end();                            // the thread's, or NULL
 // bytes of that scratch the split-K product (ta = 1) and the column sums take for the given shape
 size_t gemm_tn_scratch_bytes(int64_t M, int64_t N, int64_t K);
 size_t colsum_scratch_bytes(int64_t rows, int32_t cols);

@@ -20,6 +20,7 @@
 // Y accumulates in registers over all strips of a wavefront; the wavefronts of a workgroup are added in a fixed
 // order in LDS, the workgroups by a small kernel in a fixed order: bit-reproducible.
 #include "common.h"
+#include "sum_parts.h"
 
 namespace gcn {
 
@@ -478,45 +479,9 @@ __global__ __launch_bounds__(256, 3) void k_fused_last_wide(FusedArgs a) {
 // numbers: 8 us, 24 + 9 + 5 in three launches before.
 __global__ __launch_bounds__(1024) void k_fused_y(int C, int CP, int blocks, const float* __restrict__ part, float* __restrict__ Y,
                                                   const double* __restrict__ lpart, double inv_m, float* __restrict__ loss) {
-    constexpr int GROUPS = 64, AHEAD = 8;
-    __shared__ float s_y[GROUPS][16];
-    __shared__ double s_l[256];
-    const int i = threadIdx.x % 16, j = threadIdx.x / 16;
-    if ((int)blockIdx.x == CP) {                                // the loss
-        double acc = 0.0;
-        if (threadIdx.x < 256) {
-            for (int b = threadIdx.x; b < blocks; b += 256) acc += lpart[b];
-            s_l[threadIdx.x] = acc;
-        }
-        __syncthreads();
-        for (int d = 128; d >= 1; d >>= 1) {
-            if ((int)threadIdx.x < d) s_l[threadIdx.x] += s_l[threadIdx.x + d];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) *loss = (float)(s_l[0] * inv_m);
-        return;
-    }
-    const int e = blockIdx.x * 16 + i;                          // of 16 CP numbers
-    const size_t count = (size_t)16 * CP;
-    const float* p = part + e;
-    float acc = 0.f;
-    int b = j;
-    for (; b + (AHEAD - 1) * GROUPS < blocks; b += AHEAD * GROUPS) {
-        float x[AHEAD];
-#pragma unroll
-        for (int u = 0; u < AHEAD; ++u) x[u] = p[(size_t)(b + u * GROUPS) * count];
-#pragma unroll
-        for (int u = 0; u < AHEAD; ++u) acc += x[u];
-    }
-    for (; b < blocks; b += GROUPS) acc += p[(size_t)b * count];
-    s_y[j][i] = acc;
-    __syncthreads();
-    for (int d = GROUPS / 2; d >= 1; d >>= 1) {
-        if (j < d) s_y[j][i] += s_y[j + d][i];
-        __syncthreads();
-    }
-    const int k = e / CP, c = e % CP;
-    if (j == 0 && c < C) Y[k * C + c] = s_y[0][i];
+    __shared__ SumLds lds;
+    if ((int)blockIdx.x == CP) sum_of_losses(lpart, blocks, inv_m, loss, lds.l);
+    else sum_of_fused(blockIdx.x, C, CP, blocks, part, lds.y, [&](int e, float y) { Y[e] = y; });
 }
 
 static int fused_nt(int32_t C) {
@@ -587,6 +552,12 @@ int fused_last_launch(int64_t n, int32_t C, const float* T, const float* W, cons
         default: launch_fused_wide<4>(a, blocks, s); break;
     }
     GCN_LAUNCH_CHECK();
+    if (EpochEnd* end = epoch_end()) {
+        end->args.fused.part = a.ypart; end->args.fused.Y = Y; end->args.fused.W = end->W;
+        end->args.fused.C = C; end->args.fused.CP = 16 * NT; end->args.fused.blocks = (int32_t)blocks;
+        end->args.lpart = a.lpart; end->args.lparts = blocks; end->args.inv_m = 1.0 / (double)n_labelled; end->args.loss = loss;
+        return GCN_OK;
+    }
     hipLaunchKernelGGL(k_fused_y, dim3((unsigned)(16 * NT + 1)), dim3(1024), 0, s, (int)C, 16 * NT, (int)blocks,
                        (const float*)a.ypart, Y, (const double*)a.lpart, 1.0 / (double)n_labelled, loss);
     GCN_LAUNCH_CHECK();

@@ -11,6 +11,7 @@
 // Operand layout of the 16x16x4 instruction (64 lanes): lane l supplies A[i = l%16][k = l/16] and
 // B[k = l/16][j = l%16], and holds D[i = 4*(l/16) + v][j = l%16] in element v of its accumulator.
 #include "common.h"
+#include "sum_parts.h"
 
 namespace gcn {
 
@@ -650,22 +651,6 @@ __global__ __launch_bounds__(256) void k_gemm_back(TnArgs a, const float* __rest
     a.part[(int64_t)blockIdx.x * 256 + o] = ((s_red[0][o] + s_red[1][o]) + s_red[2][o]) + s_red[3][o];
 }
 
-// Sum of part[p * count] over p = first, first + step, ... below parts, in ascending order; the loads of eight terms
-// are in flight together (the additions are a serial chain, the loads need not be).
-__device__ __forceinline__ float strided_sum(const float* __restrict__ part, int64_t count, int first, int step, int parts) {
-    float s = 0.f;
-    int p = first;
-    for (; p + 7 * step < parts; p += 8 * step) {
-        float v[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = part[(int64_t)(p + e * step) * count];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) s += v[e];
-    }
-    for (; p < parts; p += step) s += part[(int64_t)p * count];
-    return s;
-}
-
 // Stage 1 of the reduction when there are many partials: group g of `groups` sums the partials g, g+groups, ... in
 // ascending order (coalesced over the output index).
 __global__ __launch_bounds__(256) void k_tn_fold(int64_t count, int parts, int groups, const float* __restrict__ part,
@@ -676,25 +661,65 @@ __global__ __launch_bounds__(256) void k_tn_fold(int64_t count, int parts, int g
     out[(int64_t)g * count + o] = strided_sum(part + o, count, g, groups, parts);
 }
 
-// Stage 2: a workgroup takes 64 outputs; wavefront w sums the partials w, w + waves, ... in ascending order, the
-// wavefronts are added in order, then bias, epilogue and store.  `transposed` means part holds C^T (N x M row-major).
+// Stage 2 (see sum_of_parts), then bias, epilogue and store.
 template <int EPI>
 __global__ __launch_bounds__(1024) void k_tn_reduce(int32_t M, int32_t N, int parts, int transposed, const float* __restrict__ part,
                                                     float* __restrict__ C, int64_t ldc, const float* __restrict__ bias,
                                                     const float* __restrict__ Zprev, int64_t ldzprev) {
-    __shared__ float s_sum[16][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
-    const int64_t count = (int64_t)M * N;
-    const int64_t src = (int64_t)blockIdx.x * 64 + lane;
-    if (src < count) s_sum[wave][lane] = strided_sum(part + src, count, wave, waves, parts);
-    __syncthreads();
-    if (wave != 0 || src >= count) return;
-    float s = s_sum[0][lane];
-    for (int w = 1; w < waves; ++w) s += s_sum[w][lane];
-    const int m = (int)(transposed ? src % M : src / N);
-    const int n = (int)(transposed ? src / M : src % N);
-    if (bias) s += bias[n];
-    C[(int64_t)m * ldc + n] = epi<EPI>(s, EPI == GCN_EPI_MASK ? Zprev + (int64_t)m * ldzprev + n : nullptr);
+    __shared__ SumLds lds;
+    sum_of_parts(blockIdx.x, M, N, parts, transposed, part, blockDim.x >> 6, lds.s, [&](int m, int n, float s) {
+        if (bias) s += bias[n];
+        C[(int64_t)m * ldc + n] = epi<EPI>(s, EPI == GCN_EPI_MASK ? Zprev + (int64_t)m * ldzprev + n : nullptr);
+    });
+}
+
+// What EpochEnd collected, in one launch: the sums of the weight gradients, each with the update of its weights, and the loss.  (A chain of
+// three to six launches of 2 to 6 us, most of each the start of a kernel on cold caches.)
+__global__ __launch_bounds__(1024) void k_epoch_end(EpochEnd::Args a) {
+    __shared__ SumLds lds;
+    const int b = (int)blockIdx.x;
+    auto update = [&](float* W, int64_t t, float y) {
+        if (W) W[t] = W[t] - a.lr * y;
+    };
+    if (b == a.loss_at) {
+        sum_of_losses(a.lpart, a.lparts, a.inv_m, a.loss, lds.l);
+        return;
+    }
+    if (a.fused.part && b >= a.fused.first) {
+        sum_of_fused(b - a.fused.first, a.fused.C, a.fused.CP, a.fused.blocks, a.fused.part, lds.y, [&](int e, float y) {
+            a.fused.Y[e] = y;
+            update(a.fused.W, e, y);
+        });
+        return;
+    }
+    int k = 0;
+    while (k + 1 < a.count && b >= a.sums[k + 1].first) ++k;
+    const EpochEnd::Sum& g = a.sums[k];
+    sum_of_parts(b - g.first, g.M, g.N, g.parts, g.transposed, g.part, g.parts < 16 ? g.parts : 16, lds.s, [&](int m, int n, float s) {
+        const int64_t t = (int64_t)m * g.N + n;
+        g.Y[t] = s;
+        update(g.W, t, s);
+    });
+}
+
+int EpochEnd::finish(float lr, hipStream_t s) {
+    args.lr = lr;
+    int blocks = 0;
+    for (int k = 0; k < args.count; ++k) {
+        args.sums[k].first = blocks;
+        if (lr == 0.f) args.sums[k].W = nullptr;
+        blocks += (int)(((int64_t)args.sums[k].M * args.sums[k].N + 63) / 64);
+    }
+    if (args.fused.part) {
+        args.fused.first = blocks;
+        if (lr == 0.f) args.fused.W = nullptr;
+        blocks += args.fused.CP;
+    }
+    if (args.loss) args.loss_at = blocks++;
+    if (blocks == 0) return GCN_OK;
+    hipLaunchKernelGGL(k_epoch_end, dim3((unsigned)blocks), dim3(1024), 0, s, args);
+    GCN_LAUNCH_CHECK();
+    return GCN_OK;
 }
 
 static inline bool al16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
@@ -929,8 +954,10 @@ int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const floa
     if (tb) return GCN_OK;
     const TnShape g = tn_shape(M, N, K);
     if (g.blocks >= (1ll << 31) || g.ny > 65535 || g.nz > 65535 || M * N >= (1ll << 36)) return fail(GCN_ERR_RANGE, "gcn_gemm: output too large");
-    void* scratch = nullptr;
-    GCN_TRY(scratch_get(&scratch, g.scratch_bytes, s));
+    EpochEnd* const end = !bias && epilogue == GCN_EPI_NONE && ldc == N ? epoch_end() : nullptr;
+    void* scratch = end ? end->take(g.scratch_bytes) : nullptr;
+    const bool later = scratch != nullptr;
+    if (!later) GCN_TRY(scratch_get(&scratch, g.scratch_bytes, s));
     TnArgs args;
     args.K = K; args.M = (int32_t)g.Mw; args.N = (int32_t)g.Nw;
     args.A = g.swap ? B : A; args.lda = g.swap ? ldb : lda;
@@ -961,8 +988,12 @@ int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const floa
         red_src = folded;
         red_parts = g.fold;
     }
-    GCN_TRY(reduce_parts_launch((int32_t)M, (int32_t)N, red_parts, g.swap, red_src, C, ldc, bias, epilogue, Zprev, ldzprev, s));
     *handled = true;
+    if (later) {
+        end->add(red_src, C, (int32_t)M, (int32_t)N, red_parts, g.swap);
+        return GCN_OK;
+    }
+    GCN_TRY(reduce_parts_launch((int32_t)M, (int32_t)N, red_parts, g.swap, red_src, C, ldc, bias, epilogue, Zprev, ldzprev, s));
     return GCN_OK;
 }
 
@@ -981,8 +1012,10 @@ int gemm_back_launch(int64_t n, int32_t f_in, int32_t f_out, const float* Hin, i
     if (f_in != 16 || f_out != 16 || n < 64 || ldh % 4 != 0 || !al16(Hin) || !al16(S) || !al16(Zprev) || !al16(Gprev)) return GCN_OK;
     if (!row_by_row(n, Gprev, Hin, ldh) || !row_by_row(n, Gprev, S, 16) || !row_by_row(n, Gprev, Zprev, 16)) return GCN_OK;
     const TnShape g = tn_shape(16, 16, n);
-    void* scratch = nullptr;
-    GCN_TRY(scratch_get(&scratch, g.scratch_bytes, s));
+    EpochEnd* const end = epoch_end();
+    void* scratch = end ? end->take(g.scratch_bytes) : nullptr;
+    const bool later = scratch != nullptr;
+    if (!later) GCN_TRY(scratch_get(&scratch, g.scratch_bytes, s));
     TnArgs args;
     args.K = n; args.M = 16; args.N = 16;
     args.A = Hin; args.lda = ldh; args.B = S; args.ldb = 16;
@@ -993,6 +1026,10 @@ int gemm_back_launch(int64_t n, int32_t f_in, int32_t f_out, const float* Hin, i
     else hipLaunchKernelGGL(k_gemm_back<false>, grid, dim3(256), 0, s, args, W, Zprev, Gprev);
     GCN_LAUNCH_CHECK();
     *handled = true;
+    if (later) {
+        end->add((const float*)scratch, Y, 16, 16, (int)g.blocks, false);
+        return GCN_OK;
+    }
     return reduce_parts_launch(16, 16, (int)g.blocks, false, (const float*)scratch, Y, 16, nullptr, GCN_EPI_NONE, nullptr, 0, s);
 }
 

@@ -9,6 +9,7 @@
 // stride over the rows; every thread adds its rows' losses in double in a fixed order, then a
 // fixed tree joins threads and workgroups, so the loss is reproducible bit for bit.
 #include "common.h"
+#include "sum_parts.h"
 
 namespace gcn {
 
@@ -114,19 +115,10 @@ __global__ __launch_bounds__(256) void k_softmax_nll_wide(int64_t n, int32_t C, 
     if (threadIdx.x == 0) part[blockIdx.x] = (s_w[0] + s_w[1]) + (s_w[2] + s_w[3]);
 }
 
-// Single block: strided sums per thread, then a fixed shared-memory tree.
-__global__ __launch_bounds__(256) void k_loss_final(int64_t parts, const double* __restrict__ part, double inv_n,
+__global__ __launch_bounds__(256) void k_loss_final(int64_t parts, const double* __restrict__ part, double inv_m,
                                                     float* __restrict__ loss) {
     __shared__ double s[256];
-    double acc = 0.0;
-    for (int64_t p = threadIdx.x; p < parts; p += 256) acc += part[p];
-    s[threadIdx.x] = acc;
-    __syncthreads();
-    for (int d = 128; d >= 1; d >>= 1) {
-        if ((int)threadIdx.x < d) s[threadIdx.x] += s[threadIdx.x + d];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *loss = (float)(s[0] * inv_n);
+    sum_of_losses(part, parts, inv_m, loss, s);
 }
 
 template <int L>
@@ -166,8 +158,10 @@ using namespace gcn;
 
 static int softmax_nll_impl(int64_t n, int32_t C, const float* Z, int64_t ldz, const int32_t* labels, int64_t n_labelled,
                             float* loss, float* G, int64_t ldg, hipStream_t s) {
-    void* scratch = nullptr;
-    GCN_TRY(scratch_get(&scratch, loss_scratch_bytes(), s));
+    EpochEnd* const end = epoch_end();
+    void* scratch = end ? end->take(loss_scratch_bytes()) : nullptr;
+    const bool later = scratch != nullptr;
+    if (!later) GCN_TRY(scratch_get(&scratch, loss_scratch_bytes(), s));
     double* part = (double*)scratch;
     int64_t blocks = 0;
     const float inv_m = 1.0f / (float)n_labelled;
@@ -180,6 +174,10 @@ static int softmax_nll_impl(int64_t n, int32_t C, const float* Z, int64_t ldz, c
                            inv_m, part);
     }
     GCN_LAUNCH_CHECK();
+    if (later) {
+        end->args.lpart = part; end->args.lparts = blocks; end->args.inv_m = 1.0 / (double)n_labelled; end->args.loss = loss;
+        return GCN_OK;
+    }
     hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(256), 0, s, blocks, (const double*)part, 1.0 / (double)n_labelled, loss);
     GCN_LAUNCH_CHECK();
     return GCN_OK;

@@ -889,6 +889,51 @@ def test_update_of_many_and_of_tied_layers(tied):
     a.close()
 
 
+@pytest.mark.parametrize("n,dims", [(70_001, (7, 3, 3, 3)), (500, (64, 16, 16, 16)), (5000, (100, 16, 16, 41)), (500, (5, 130, 130, 300)),
+                                    (300, (12,) * 7 + (9,)), (300, (12,) * 8 + (9,))])
+def test_reductions_at_the_end_of_the_epoch(n, dims):
+    """Gradients, loss and update that an epoch adds up in one kernel: the bits of the reductions one by one, which an epoch whose second and
+    third layer share their weights runs; with partial results folded first, both products of width 16 in one pass, the fused last layer, many
+    classes, as many layers as the kernel takes and one more."""
+    g = G()
+    rs = np.random.default_rng(141)
+    L = len(dims) - 1
+    a = g.gcn_csr_create(n, *[dev(rs.integers(0, n, 4 * n).astype(np.int32)) for _ in range(2)], g.ADD_SELF_LOOPS | g.NORM_SYM | g.SYMMETRISE | g.BUILD_TRANSPOSE)
+    H0, y = dev(synth.normal_features(n, dims[0], 142)), dev(rs.integers(-1, dims[-1], n).astype(np.int32))
+    W = [dev(w) for w in synth.glorot_weights(dims, 143)]
+    tied = dims[1] == dims[2] == dims[3]
+    if tied:
+        W[2].copy_(W[1])
+    ws = torch.empty(g.gcn_epoch_workspace_bytes(n, dims), dtype=torch.uint8, device="cuda")
+    got = []
+    for share in (False, True):
+        Ws = list(W)
+        if share and tied:
+            Ws[2] = Ws[1]
+        elif share:                                                # the last layer's gradient beside the first one's weights, one float shared
+            both = torch.empty(W[0].numel() + W[-1].numel() - 1, device="cuda")
+            both[:W[0].numel()] = W[0].reshape(-1)
+            Ws[0] = both[:W[0].numel()].view_as(W[0])
+        Y = [torch.full_like(w, float("nan")) for w in Ws]
+        if share and not tied:
+            Y[-1] = both[W[0].numel() - 1:].view_as(W[-1])
+        loss = torch.full((1,), float("nan"), device="cuda")
+        ws.fill_(255)
+        g.gcn_epoch_masked(a, dims, H0, y, int((y >= 0).sum()), Ws, Y, 0.0, loss, ws)
+        got.append([host(loss)] + [host(v).copy() for v in Y])
+        if not share:
+            before = [host(w).copy() for w in Ws]
+            ws.fill_(255)
+            g.gcn_epoch_masked(a, dims, H0, y, int((y >= 0).sum()), Ws, Y, 0.5, loss, ws)
+            for w, b, v in zip(Ws, before, got[0][1:]):
+                assert np.allclose(host(w), b - np.float32(0.5) * v, rtol=3e-7, atol=1e-9)
+                w.copy_(dev(b))
+    for l in range(L + 1):
+        if tied or l not in (1, L):                                # (without tied layers the shared float changes W[0] under way)
+            assert np.isfinite(got[0][l]).all() and np.array_equal(got[0][l], got[1][l]), l
+    a.close()
+
+
 @pytest.mark.parametrize("f", [4, 7, 16, 20, 32, 41, 48, 64, 130])
 @pytest.mark.parametrize("pairs,loops,blocks", [(500, True, 0), (400_000, True, 1), (400_000, True, 3), (400_000, False, 1), (400_000, False, 3)])
 @pytest.mark.parametrize("values", [0, 1])
