@@ -900,9 +900,16 @@ int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const floa
         const size_t lds = b_bytes(NT);
         if (lds > 150 * 1024) { *scaled = false; return GCN_OK; }
         const int64_t ntiles = (M + 15) / 16;
-        {   // rows that are not whole 128-byte lines, and short rows (up to 208 floats, where the coalesced copy also beats
+        {   // Rows that are not whole 128-byte lines, and short rows (up to 208 floats, where the coalesced copy also beats
             // the strided 64-byte pieces: 128 floats 1.02 -> 0.96 ms on 8.7 M rows; at 256 floats it loses, 3.14 -> 3.23 ms):
-            // contiguous strips through LDS (see k_gemm_tall_flat)
+            // contiguous strips through LDS (see k_gemm_tall_flat), where the operand is beyond the memory-side cache.  Below, the strided
+            // kernel is faster, with the operand in the cache and from memory (300 x 16: 40 K rows 18 and 21 us, 160 K 45 and 48, 320 K 89
+            // and 87, 1.3 M 341 and 316; 128 x 16: 40 K 8.3 and 10.1, 320 K 36 and 39, 640 K 78 and 73), except on short rows that end
+            // inside 64 bytes (100 x 16: 40 K 8.3 and 8.3, 80 K 12.0 and 10.8).  With two tiles of columns it is faster at every size
+            // from 128 floats on (128 x 32: 40 K 9.6 and 12.3, 1.3 M 158 and 160; 300 x 32: 1.3 M 369 and 390; 64 x 32: 640 K
+            // 44.5 and 46.6, 1.3 M 94 and 87).
+            const bool beyond = M * K * 4 >= (224ll << 20);
+            const bool strips = K <= 112 ? beyond || (K % 16 != 0 && M >= 65536) : NT == 1 && beyond;
             const bool wide = (N % 4 == 0) && (ldc % 4 == 0) && al16(C) &&
                               (epilogue != GCN_EPI_MASK || ((ldzprev % 4 == 0) && al16(Zprev)));
             const int kv_need = (int)((K + 15) / 16);
@@ -912,8 +919,8 @@ int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const floa
             int fw = (int)((150 * 1024 - (int64_t)lds) / ((int64_t)KV * 256 * sizeof(float)));
             fw = fw > 4 ? 4 : fw;
             const size_t lds_flat = lds + (size_t)(fw > 0 ? fw : 1) * KV * 256 * sizeof(float);
-            if (fw >= 2 && wide && !ascending && lda == K && (K % 4) == 0 && (((K * 4) % 128) != 0 || K <= 208) && K >= 64 && kv_need <= 19 && NT <= 2 && al16(A) &&
-                lds_flat <= 150 * 1024 && M >= 4096) {
+            if (strips && fw >= 2 && wide && !ascending && lda == K && (K % 4) == 0 && (((K * 4) % 128) != 0 || K <= 208) && K >= 64 && kv_need <= 19 && NT <= 2 && al16(A) &&
+                lds_flat <= 150 * 1024) {
                 int64_t fb = (ntiles + fw - 1) / fw;
                 const int per_cu = (int)((160 * 1024) / lds_flat);
                 const int64_t fcap = 256 * (int64_t)(per_cu < 1 ? 1 : per_cu);
@@ -932,7 +939,9 @@ int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const floa
         // longer than the rest (32 x 23 on 2.4 M 201 and 157; with one tile four take 1.03 of the time, with three 1.07), or of 16 bytes while
         // operand and result are in the memory-side cache (32 x 32 on 400 K 20.6 and 18.5, on 820 K 37.0 and 34.4; on 1.8 M
         // 98 and 105).
-        constexpr int waves = 8;
+        // Four where that leaves no compute unit without a workgroup that eight would (16384 rows: 64 x 16 4.4 -> 4.1 us, 128 x 16 5.6 -> 5.4,
+        // 256 x 64 14.1 -> 12.4; 40 K: 256 x 64 24.8 -> 26.2).
+        const int waves = ntiles <= 8 * (int64_t)device_info().cus ? 4 : 8;
         int64_t bx = (ntiles + waves - 1) / waves;
         const bool four = NT == 2 && lds <= 40 * 1024 && (!wide_c || M * (K + N) * 4 < (192ll << 20));
         const int64_t cap = (int64_t)device_info().cus * (lds > 80 * 1024 ? 1 : (four ? 4 : 2));

@@ -889,6 +889,24 @@ def test_update_of_many_and_of_tied_layers(tied):
     a.close()
 
 
+@pytest.mark.parametrize("K,N,M", [(100, 16, 65_536), (300, 16, 195_740), (64, 32, 917_504), (128, 32, 40_000), (64, 16, 32_768), (16, 8, 32_784)])
+def test_gemm_nn_on_both_sides_of_its_rules(K, N, M):
+    """Row counts at which the product goes to another kernel or to workgroups of another size: the first rows keep their bits, the last ones are
+    what 64 bits give."""
+    g = G()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(155)
+    A, B = torch.randn(M + 17, K, generator=gen, device="cuda"), torch.randn(K, N, generator=gen, device="cuda")
+    few = torch.empty(4000, N, device="cuda")
+    g.gcn_gemm(0, 0, A[:4000], B, few)
+    assert_close(host(few), host(A[:4000].double() @ B.double()), f"{K} {N}")
+    for rows in (M - 1, M, M + 17):
+        C = torch.full((rows, N), float("nan"), device="cuda")
+        g.gcn_gemm(0, 0, A[:rows], B, C)
+        assert torch.equal(C[:4000], few), rows
+        assert_close(host(C[-200:]), host(A[rows - 200:rows].double() @ B.double()), f"{rows} {K} {N}")
+
+
 @pytest.mark.parametrize("n,dims", [(70_001, (7, 3, 3, 3)), (500, (64, 16, 16, 16)), (5000, (100, 16, 16, 41)), (500, (5, 130, 130, 300)),
                                     (300, (12,) * 7 + (9,)), (300, (12,) * 8 + (9,))])
 def test_reductions_at_the_end_of_the_epoch(n, dims):
