@@ -51,6 +51,9 @@ int fail(int code, const char* fmt, ...);
 constexpr int SUB = 32;
 constexpr int CHUNK = 512;
 constexpr int SUBS_PER_CHUNK = CHUNK / SUB;
+// Rows of up to SHORT_ROW entries, as many as k_spmm_short takes at any width (SHORT_LANES lanes at two per row; see short_rows).
+constexpr int SHORT_ROW = 64;
+constexpr int64_t SHORT_LANES = 256 * 8 * 64;
 // Matrices of fewer entries keep the schedule of the sizes.
 constexpr int64_t PLANNED_NNZ = 1 << 20;
 
@@ -147,6 +150,11 @@ struct Matrix {
     RowOrder order;              // how they lie (likewise)
     Terms terms = Terms::UNKNOWN;
     std::vector<SpmmPlan> plans; // schedules chosen so far, one per width and kind of terms
+    // Rows of equal pitch for the kernel of few and short rows (see build_short), or NULL.
+    int32_t* short_col = nullptr;   // [nrows][short_pitch] columns, 0 behind a row's last
+    float* short_val = nullptr;     // likewise
+    int32_t* short_rows = nullptr;  // [nrows] entries of the row, and where they begin modulo CHUNK from bit 16 up
+    int32_t short_pitch = 0;
     // Other stored orders of the matrix, built on first use (or by a prepare call) and kept until the
     // matrix is destroyed.  blk / swp / hub are the copies the latest product used; a product that needs
     // another key (block width; lane groups, task height and long-row threshold; hub settings) parks the
@@ -342,6 +350,7 @@ void launch_lds(dim3 grid, int threads, size_t lds, hipStream_t s, const Args&..
     hipLaunchKernelGGL(Kernel, grid, dim3(threads), lds, s, args...);
 }
 
+int build_short(Matrix& m, hipStream_t s);       // once the values are there
 int build_schedule(Matrix& m, int64_t n, int64_t nnz, hipStream_t s, int32_t* deg = nullptr);   // deg: also receives the row lengths
 // One record per row whose entries run on into further chunks: x, y = the first and the last of them, z = the row (its
 // index among the non-empty rows).  Rows that leave no row start in chunk x come first (n_long of them).

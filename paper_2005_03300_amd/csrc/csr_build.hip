@@ -422,6 +422,48 @@ int build_schedule(Matrix& m, int64_t n, int64_t nnz, hipStream_t s, int32_t* de
     return GCN_OK;
 }
 
+// Four entries of a row per thread.
+__global__ __launch_bounds__(256) void k_short_rows(int64_t nrows, int32_t quads, const int64_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
+                                                    const float* __restrict__ val, int4* __restrict__ col4, float4* __restrict__ val4,
+                                                    int32_t* __restrict__ rows) {
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x, row = t / quads;
+    if (row >= nrows) return;
+    const int k0 = (int)(t % quads) * 4;
+    const int64_t first = rowptr[row];
+    const int len = (int)(rowptr[row + 1] - first);
+    int32_t c[4];
+    float v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        c[e] = k0 + e < len ? colidx[first + k0 + e] : 0;
+        v[e] = k0 + e < len ? val[first + k0 + e] : 0.f;
+    }
+    col4[t] = make_int4(c[0], c[1], c[2], c[3]);
+    val4[t] = make_float4(v[0], v[1], v[2], v[3]);
+    if (k0 == 0) rows[row] = len | (int32_t)(first % CHUNK) << 16;
+}
+
+// A second copy of a matrix of few and short rows, at an equal pitch: a product on it is a chain of memory latencies, and this way the
+// indices need not wait for the row pointers (see k_spmm_short).  At most 33 MB.
+int build_short(Matrix& m, hipStream_t s) {
+    if (m.nrows * 2 > SHORT_LANES || m.max_degree > SHORT_ROW || m.max_degree == 0) return GCN_OK;
+    const int32_t quads = (m.max_degree + 3) / 4;
+    const int64_t threads = m.nrows * quads;
+    m.short_pitch = 4 * quads;
+    if (device_alloc_t(&m.short_col, (size_t)threads * 4) != GCN_OK || device_alloc_t(&m.short_val, (size_t)threads * 4) != GCN_OK ||
+        device_alloc_t(&m.short_rows, (size_t)m.nrows) != GCN_OK) {
+        device_free(m.short_col);                              // without it the other kernels run
+        device_free(m.short_val);
+        m.short_col = nullptr;
+        m.short_val = nullptr;
+        return GCN_OK;
+    }
+    hipLaunchKernelGGL(k_short_rows, dim3(blocks_for(threads)), dim3(TPB), 0, s, m.nrows, quads, m.rowptr, m.colidx, m.val, (int4*)m.short_col,
+                       (float4*)m.short_val, m.short_rows);
+    GCN_LAUNCH_CHECK();
+    return GCN_OK;
+}
+
 // A^T of `a` from A's sorted keys and values: a stable radix sort by the column bits alone (inside a column the rows keep
 // their ascending order) with the values as payload.
 static int build_transpose(gcn_csr* a, const uint64_t* keys, unsigned cbits, uint64_t* scratch_keys, hipStream_t s) {
@@ -437,6 +479,7 @@ static int build_transpose(gcn_csr* a, const uint64_t* keys, unsigned cbits, uin
                        a->At.rowptr, a->At.colidx);
     GCN_LAUNCH_CHECK();
     GCN_TRY(build_schedule(a->At, n, nnz, s));
+    GCN_TRY(build_short(a->At, s));
     a->has_t = true;
     return GCN_OK;
 }
@@ -581,6 +624,7 @@ static int create_impl(gcn_csr* a, int64_t n, int64_t m, const int32_t* src, con
         GCN_TRY(device_alloc_t(&a->inv_sqrt_deg, (size_t)n));
         GCN_TRY(inv_sqrt_deg_launch(n, a->deg, a->inv_sqrt_deg, s));
     }
+    GCN_TRY(build_short(a->A, s));
     if (a->symmetric) a->has_t = true;
     else if (transpose) {
         TempBuf sorted;
@@ -632,6 +676,7 @@ static int from_csr_impl(gcn_csr* a, int64_t n, int64_t ncols, const int64_t* ro
         if (hbad) return fail(GCN_ERR_UNSORTED, "gcn_csr_create_from_csr: columns must be strictly ascending per row and inside [0,n)");
     }
     GCN_TRY(build_schedule(a->A, n, nnz, s, a->deg));
+    GCN_TRY(build_short(a->A, s));
     if (flags & GCN_BUILD_TRANSPOSE) {
         GCN_TRY(k1.alloc((size_t)nnz * 8));
         GCN_TRY(build_transpose(a, keys.as<uint64_t>(), cbits, k1.as<uint64_t>(), s));

@@ -616,12 +616,14 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_few(SplitArgs a) 
 }
 
 // Matrices of few rows, all of them short (SHORT_ROW entries at the most): a lane group takes a row, one wavefront per
-// workgroup so that a thousand rows spread over 63 compute units.  Nothing is staged or joined: the chain is row
-// pointer, indices, gathers (32 in flight), sums, store, and an empty row is simply a sum of nothing.  The sums are those
+// workgroup so that a thousand rows spread over 63 compute units.  Nothing is staged or joined: the chain is
+// indices, gathers, sums, store, and an empty row is simply a sum of nothing.  The rows lie at an equal pitch (build_short),
+// so that the indices do not wait for row pointers.  Eight entries a round, the gathers of the next round sent out as those of this one are
+// used: a kernel that runs for six microseconds pays for every line of its code, which no cache holds when it starts, and 32 entries
+// unrolled took longer for their 6.6 KB than for their one latency (4096 rows of 17 at 16 columns 7.3 -> 6.1 us).  The sums are those
 // of the nonzero-split kernels, term by term: there a row is cut where a lane group's slice of SLICE entries or a chunk
 // ends, and with at most SHORT_ROW entries it has three pieces, F + (H1 + H2), or (F + H1) + H2 when H2 is in the
-// next chunk.  1000 rows of 17 entries at 16 columns: 6.3 us; k_spmm_few 7.7;
-// k_spmm_split 9.7 and k_spmm_fixup 3.9.
+// next chunk.  1000 rows of 17 at 16 columns: 5.4 us; k_spmm_few 7.7; k_spmm_split 9.7 and k_spmm_fixup 3.9.
 // The value of lane `l` of every group of LPR lanes (l a constant once the loop around is unrolled).
 template <int LPR>
 __device__ __forceinline__ int group_lane(int x, int l) {
@@ -636,63 +638,59 @@ __device__ __forceinline__ int group_lane(int x, int l) {
     return __shfl(x, l, LPR);
 }
 
-static constexpr int SHORT_ROW = 64;
-
 template <int LPR, int SLICE, int EPI>
-__global__ __launch_bounds__(64) void k_spmm_short(SplitArgs a, int64_t nrows) {
+__global__ __launch_bounds__(64) void k_spmm_short(SplitArgs a, int64_t nrows, const int32_t* __restrict__ rows, int32_t pitch) {
     constexpr int VEC = 4;
     static_assert(SHORT_ROW <= 2 * SLICE, "at most three pieces");
-    constexpr int U = 32, PER = U / LPR;                        // entries per round, loads of a lane per round
+    constexpr int U = 8, OWN = LPR < U ? U / LPR : 1;           // entries per round, those that a lane holds the indices of
     const int lane = threadIdx.x, li = lane % LPR;
     const int64_t row = ((int64_t)blockIdx.x * 64 + lane) / LPR;
     int col0;
     const bool col_ok = lane_columns<LPR, VEC>(a.f, blockIdx.y, gridDim.y, li, &col0);
-    int64_t rs = 0;
-    int len = 0;
-    if (row < nrows) {
-        rs = a.rp[row];
-        len = (int)(a.rp[row + 1] - rs);
-    }
-    const int b1 = SLICE - (int)(rs & (SLICE - 1)), b2 = b1 + SLICE;       // where the second and the third piece begin
+    const int64_t own = row < nrows ? row : nrows - 1;
+    const int32_t* const cols = a.colidx + own * pitch + li * OWN;
+    const float* const vals = a.val ? a.val + own * pitch + li * OWN : nullptr;
+    const int32_t packed = rows[own];
+    struct Round { int32_t c[OWN]; float v[OWN]; };
+    auto indices = [&](int base, Round& r) {
+#pragma unroll
+        for (int t = 0; t < OWN; ++t) { r.c[t] = 0; r.v[t] = 1.f; }
+        if (li * OWN < U && base + li * OWN < pitch) {          // (pitch is a multiple of four)
+            __builtin_memcpy(r.c, cols + base, sizeof r.c);
+            if (vals) __builtin_memcpy(r.v, vals + base, sizeof r.v);
+        }
+    };
+    const float* const xbase = a.X + col0;
+    const uint32_t xpitch = (uint32_t)a.ldx * 4u;
+    Round now, next;
+    float x[U][VEC];
+    auto gather = [&](const Round& r, int e) { load_vec<VEC>(x[e], at_row(xbase, (uint32_t)group_lane<LPR>(r.c[e % OWN], e / OWN), xpitch)); };
+    indices(0, now);
+    indices(U, next);
+#pragma unroll
+    for (int e = 0; e < U; ++e) gather(now, e);
+    const int len = row < nrows ? packed & 0xffff : 0, rs = packed >> 16;           // rs: modulo CHUNK, and so modulo SLICE
+    const int b1 = SLICE - (rs & (SLICE - 1)), b2 = b1 + SLICE;                     // where the second and the third piece begin
     const bool third_apart = ((rs + b2) & (CHUNK - 1)) == 0;
     float acc[VEC] = {}, first[VEC] = {}, second[VEC] = {};
-    const float* xbase = a.X + col0;
+#pragma unroll 1
     for (int base = 0; __any(base < len); base += U) {
-        int32_t c[PER];
-        float v[PER];
-#pragma unroll
-        for (int t = 0; t < PER; ++t) {
-            const int k = base + li + LPR * t;
-            c[t] = 0;
-            v[t] = 1.f;
-            if (k < len) {
-                c[t] = a.colidx[rs + k];
-                if (a.val) v[t] = a.val[rs + k];
-            }
-        }
-        float x[U][VEC];
 #pragma unroll
         for (int e = 0; e < U; ++e) {
-            const int32_t col = group_lane<LPR>(c[e / LPR], e % LPR);      // past the end: row 0, not used
-            load_vec<VEC>(x[e], at_row(xbase, (uint32_t)col, (uint32_t)a.ldx * 4u));
-        }
-#pragma unroll
-        for (int e = 0; e < U; ++e) {
-            const float ve = __int_as_float(group_lane<LPR>(__float_as_int(v[e / LPR]), e % LPR));
+            const float ve = __int_as_float(group_lane<LPR>(__float_as_int(now.v[e % OWN]), e / OWN));
             const int k = base + e;
-            if (k < len) {
-                if (k == b1) {
+            const bool cut = k == b1 || k == b2;                // (first and second are used where the row goes on beyond b1 and b2)
 #pragma unroll
-                    for (int u = 0; u < VEC; ++u) { first[u] = acc[u]; acc[u] = 0.f; }
-                }
-                if (k == b2) {
-#pragma unroll
-                    for (int u = 0; u < VEC; ++u) { second[u] = acc[u]; acc[u] = 0.f; }
-                }
-#pragma unroll
-                for (int u = 0; u < VEC; ++u) acc[u] = fmaf(ve, x[e][u], acc[u]);
+            for (int u = 0; u < VEC; ++u) {
+                first[u] = k == b1 ? acc[u] : first[u];
+                second[u] = cut ? acc[u] : second[u];
+                const float sum = fmaf(ve, x[e][u], cut ? 0.f : acc[u]);
+                acc[u] = k < len ? sum : acc[u];
             }
+            gather(next, e);                    // of the round after this one; past the end: row 0, not used
         }
+        now = next;
+        indices(base + 2 * U, next);
     }
     if (row >= nrows || !col_ok) return;
     if (len > b2) {
@@ -1243,17 +1241,19 @@ static int short_lanes(int32_t f) {                // as in choose_split: the pi
 }
 static bool short_rows(const Matrix& m, int32_t f) {
     const int lpr = short_lanes(f);
-    return f >= 4 && m.max_degree <= SHORT_ROW && m.nrows * lpr * ((f + 4 * lpr - 1) / (4 * lpr)) <= (int64_t)device_info().cus * 8 * 64;
+    const int64_t lanes = m.nrows * lpr * ((f + 4 * lpr - 1) / (4 * lpr));
+    return f >= 4 && m.short_col && lanes <= SHORT_LANES && lanes <= (int64_t)device_info().cus * 8 * 64;
 }
 
-static int launch_short(const SplitArgs& args, int64_t nrows, int epilogue, hipStream_t s) {
+static int launch_short(const SplitArgs& args, const Matrix& m, int epilogue, hipStream_t s) {
+    const int64_t nrows = m.nrows;
     auto go = [&](auto lpr, auto slice) {
         constexpr int LPR = decltype(lpr)::value, SLICE = decltype(slice)::value;
         const dim3 grid((unsigned)((nrows * LPR + 63) / 64), (unsigned)((args.f + 4 * LPR - 1) / (4 * LPR)));
         switch (epilogue) {
-            case GCN_EPI_NONE: hipLaunchKernelGGL((k_spmm_short<LPR, SLICE, GCN_EPI_NONE>), grid, dim3(64), 0, s, args, nrows); break;
-            case GCN_EPI_RELU: hipLaunchKernelGGL((k_spmm_short<LPR, SLICE, GCN_EPI_RELU>), grid, dim3(64), 0, s, args, nrows); break;
-            default: hipLaunchKernelGGL((k_spmm_short<LPR, SLICE, GCN_EPI_MASK>), grid, dim3(64), 0, s, args, nrows); break;
+            case GCN_EPI_NONE: hipLaunchKernelGGL((k_spmm_short<LPR, SLICE, GCN_EPI_NONE>), grid, dim3(64), 0, s, args, nrows, m.short_rows, m.short_pitch); break;
+            case GCN_EPI_RELU: hipLaunchKernelGGL((k_spmm_short<LPR, SLICE, GCN_EPI_RELU>), grid, dim3(64), 0, s, args, nrows, m.short_rows, m.short_pitch); break;
+            default: hipLaunchKernelGGL((k_spmm_short<LPR, SLICE, GCN_EPI_MASK>), grid, dim3(64), 0, s, args, nrows, m.short_rows, m.short_pitch); break;
         }
     };
     timing_begin(s);
@@ -1758,8 +1758,9 @@ static int run_matrix(gcn_csr* a, Matrix& mm, const int32_t* row_map, int64_t nn
     args.fix_list = mm.fix_list; args.n_fix = mm.n_fix; args.n_fix_long = mm.n_fix_long;
     args.Z = Z; args.ldz = ldz; args.Zprev = Zprev; args.ldzprev = ldzprev;
     if (short_kernel) {
-        args.rp = mm.rowptr;
-        return launch_short(args, mm.nrows, epilogue, s);
+        args.colidx = mm.short_col;
+        if (args.val) args.val = mm.short_val;
+        return launch_short(args, mm, epilogue, s);
     }
     if (o.end && !row_map && choice.kernel == SplitChoice::SPLIT && choice.vec == 4 && mm.n_ne == mm.nrows) {
         // (rows without entries are their bias alone; the other kernels run where a pass more is a launch more, or on ragged widths)

@@ -889,6 +889,43 @@ def test_update_of_many_and_of_tied_layers(tied):
     a.close()
 
 
+@pytest.mark.parametrize("longest", [1, 4, 5, 8, 9, 16, 33, 63, 64])
+@pytest.mark.parametrize("f", [4, 7, 16, 20, 32, 41, 64])
+def test_spmm_short_rows_at_equal_pitch(longest, f):
+    """Rows of up to `longest` entries at a pitch of whole fours: rounds of eight that end inside and behind a row, rows without entries, a
+    first row of the operand that no entry names and that is not finite (what lies behind a row's last entry points there), epilogues, the
+    transpose, the value-free form; an odd number of rows."""
+    g = G()
+    rs = np.random.default_rng(151)
+    n, nc = 1403, 977
+    lengths = rs.integers(0, longest + 1, n)
+    lengths[5] = longest
+    rowptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    colidx = np.concatenate([np.sort(rs.choice(nc - 1, k, replace=False)) + 1 for k in lengths]).astype(np.int32)
+    val = rs.standard_normal(colidx.size).astype(np.float32)
+    a = g.gcn_csr_create_from_csr_rect(n, nc, dev(rowptr), dev(colidx), dev(val), g.BUILD_TRANSPOSE)
+    assert "k_spmm_short" in g.gcn_spmm_describe(a, 0, f)
+    X = synth.normal_features(nc, f, 152)
+    A = np.zeros((n, nc))
+    A[np.repeat(np.arange(n), lengths), colidx] = val
+    want, Zp = A @ X.astype(np.float64), synth.normal_features(n, f, 153)
+    X[0] = np.where(np.arange(f) % 2, np.inf, np.nan)
+    Z = torch.full((n, f), float("nan"), device="cuda")
+    g.gcn_spmm(a, 0, dev(X), Z)
+    plain = host(Z).copy()
+    assert_close(plain, want, f"{longest} {f}")
+    g.gcn_spmm(a, 0, dev(X), Z, g.EPI_MASK, dev(Zp))
+    assert np.array_equal(host(Z), np.where(Zp > 0, plain, 0))
+    scale = rs.random(n).astype(np.float32) + 0.5
+    g.gcn_spmm_pattern(a, 0, dev(X), Z, dev(scale))
+    assert_close(host(Z), scale[:, None] * ((A != 0) @ np.where(np.arange(nc)[:, None] == 0, 0, X).astype(np.float64)), f"value-free {longest} {f}")
+    Xt = synth.normal_features(n, f, 154)
+    Zt = torch.full((nc, f), float("nan"), device="cuda")
+    g.gcn_spmm(a, 1, dev(Xt), Zt)
+    assert_close(host(Zt), A.T @ Xt.astype(np.float64), f"transposed {longest} {f}")
+    a.close()
+
+
 @pytest.mark.parametrize("K,N,M", [(100, 16, 65_536), (300, 16, 195_740), (64, 32, 917_504), (128, 32, 40_000), (64, 16, 32_768), (16, 8, 32_784)])
 def test_gemm_nn_on_both_sides_of_its_rules(K, N, M):
     """Row counts at which the product goes to another kernel or to workgroups of another size: the first rows keep their bits, the last ones are
