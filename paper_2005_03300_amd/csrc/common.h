@@ -286,10 +286,11 @@ struct EpochEnd {
     float* W = nullptr;                           // of the layer whose gradient comes next
     EpochEnd(void* p, size_t bytes);              // no room: everything as without it
     ~EpochEnd();
+    bool fits(size_t bytes) const { return room && args.count < MOST && ((bytes + 255) & ~(size_t)255) <= left; }
     // `bytes` of its room, or NULL
     void* take(size_t bytes) {
         const size_t need = (bytes + 255) & ~(size_t)255;
-        if (!room || args.count == MOST || need > left) return nullptr;
+        if (!fits(bytes)) return nullptr;
         void* p = room;
         room += need;
         left -= need;
@@ -379,6 +380,25 @@ struct LayerEnd {
     bool relu = false;                    // in place
     bool done = false;
 };
+// What an epoch does next with the rows of a product: T = Z op(W) in front of the next sparse product, masked where that is Equation 2's, or
+// the loss.  The kernel of few and short rows does it where the rows are made and sets `done` (see next_of); behind the others it
+// is a launch of its own.
+struct RowsNext {
+    enum Kind { NONE = 0, GEMM = 1, LOSS = 2 } kind = NONE;
+    const float* W = nullptr;             // f x N, or N x f when transposed
+    int32_t N = 0, transposed = 0;
+    float* T = nullptr;                   // n x N
+    const float* mask = nullptr;          // NULL, or n x N: T where it is positive
+    const int32_t* labels = nullptr;      // loss: as gcn_softmax_nll_masked takes them
+    float* G = nullptr;                   // n x f
+    double* part = nullptr;               // a partial sum of every 16 rows
+    float inv_m = 0;
+    bool done = false;
+};
+// The loss of an epoch as what is next to a product of C columns, whose `parts` partial sums lie in what is left of the EpochEnd's room (NONE:
+// it has to be a launch of its own); loss_made takes that room once they do.
+RowsNext loss_next(int32_t C, int64_t parts, const int32_t* labels, int64_t n_labelled, float* G);
+void loss_made(int64_t parts, int64_t n_labelled, float* loss);
 struct SpmmOpt {
     bool pattern = false;
     const float* row_scale = nullptr;
@@ -389,6 +409,7 @@ struct SpmmOpt {
     // such element moves the gradient of the weights by 1e-4 of its norm.
     bool any_schedule = false;
     LayerEnd* end = nullptr;          // only with the epilogue GCN_EPI_NONE
+    RowsNext* next = nullptr;
     bool narrow = false;              // internal, see SpmmPlan::narrow
     // internal to the hub schedule:
     const uint8_t* defer = nullptr;   // rows whose sum is stored raw (no scale, no epilogue)

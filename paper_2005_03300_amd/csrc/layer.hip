@@ -20,10 +20,11 @@ static int resolve_order(int order, int32_t f_in, int32_t f_out) {
 // (only passed when pre_scale() said so for this operand).  `any_order`: no ReLU decides on the result (see SpmmOpt).
 static int norm_spmm(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx, float* xs, float* Z, int64_t ldz,
                      int epilogue, const float* Zprev, int64_t ldzprev, hipStream_t s, bool prescaled, bool any_order,
-                     LayerEnd* end = nullptr) {
+                     LayerEnd* end = nullptr, RowsNext* next = nullptr) {
     PhaseTimer pt(s, GCN_PHASE_SPMM);
     SpmmOpt o;
     o.end = end;
+    o.next = next;
     o.any_order = o.any_schedule = any_order;
     if (!xs || !use_value_free(a)) return spmm_launch(a, m, f, X, ldx, Z, ldz, epilogue, Zprev, ldzprev, s, o);
     if (!prescaled) GCN_TRY(scale_rows_launch(a->n, f, X, ldx, a->inv_sqrt_deg, xs, f, s));
@@ -38,6 +39,18 @@ static const float* pre_scale(const gcn_csr* a, bool operand_is_temporary) {
     return (operand_is_temporary && use_value_free(a)) ? a->inv_sqrt_deg : nullptr;
 }
 
+// T (n x N) = Z op(W), masked, as what is next to a product Z of f columns; NONE where the dense product would add in another order (fewer
+// than 64 rows), is wider than one tile, or scales its rows.
+static RowsNext gemm_next(const gcn_csr* a, int32_t f, const float* W, int32_t N, bool transposed, float* T, const float* mask) {
+    RowsNext next;
+    if (a->n < 64 || f > 16 || f % 4 != 0 || N > 16 || N % 4 != 0 || use_value_free(a)) return next;
+    next.kind = RowsNext::GEMM;
+    next.W = W; next.N = N; next.transposed = transposed;
+    next.T = T;
+    next.mask = mask;
+    return next;
+}
+
 static int timed_gemm(int ta, int tb, int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, const float* B,
                       int64_t ldb, float* C, int64_t ldc, const float* bias, int epilogue, const float* Zprev,
                       int64_t ldzprev, hipStream_t s, const float* row_scale = nullptr) {
@@ -46,10 +59,11 @@ static int timed_gemm(int ta, int tb, int64_t M, int64_t N, int64_t K, const flo
 }
 
 // `xs`: scratch for the value-free product (n x the SpMM width) or NULL; `t_scratch` says that T is
-// a pure temporary which may be overwritten by its scaled copy.
+// a pure temporary which may be overwritten by its scaled copy.  `t_made`: T already holds the dense product.  `next`: what an epoch does with Z.
 static int layer_forward_impl(gcn_csr* a, int32_t f_in, int32_t f_out, const float* Hin, int64_t ldh, const float* W,
                               const float* bias, float* Z, float* Hout, float* T, int order, int act, hipStream_t s,
-                              float* xs = nullptr, bool t_scratch = false, bool t_given = false) {
+                              float* xs = nullptr, bool t_scratch = false, bool t_given = false, bool t_made = false,
+                              RowsNext* next = nullptr) {
     const int64_t n = a->n;
     order = resolve_order(order, f_in, f_out);
     // When the caller passes Hout == Z only the activated matrix is wanted and ReLU is fused into
@@ -57,7 +71,7 @@ static int layer_forward_impl(gcn_csr* a, int32_t f_in, int32_t f_out, const flo
     const bool in_place = (act == GCN_ACT_RELU) && Hout == Z;
     if (order == GCN_ORDER_GEMM_FIRST) {
         const float* ps = pre_scale(a, t_scratch);
-        GCN_TRY(timed_gemm(0, 0, n, f_out, f_in, Hin, ldh, W, f_out, T, f_out, nullptr, GCN_EPI_NONE, nullptr, 0, s, ps));
+        if (!t_made) GCN_TRY(timed_gemm(0, 0, n, f_out, f_in, Hin, ldh, W, f_out, T, f_out, nullptr, GCN_EPI_NONE, nullptr, 0, s, ps));
         // Bias and activation go with the product's store where its schedule can do that, unless H would be written over T, which
         // the product still reads (3.4 M entries, 200 K rows of 64 and of 41 columns: passes of 40 and 26 us, 14 and 4 in the products).
         const bool apart = act != GCN_ACT_RELU || Hout + n * f_out <= T || T + n * f_out <= Hout;
@@ -67,7 +81,7 @@ static int layer_forward_impl(gcn_csr* a, int32_t f_in, int32_t f_out, const flo
         end.relu = in_place;
         GCN_TRY(norm_spmm(a, matrix_of(a, 1), f_out, T, f_out, t_scratch ? T : xs, Z, f_out,
                           (in_place && !bias) ? GCN_EPI_RELU : GCN_EPI_NONE, nullptr, 0, s, ps != nullptr, act == GCN_ACT_NONE,
-                          (bias || end.H) && apart ? &end : nullptr));
+                          (bias || end.H) && apart ? &end : nullptr, next));
         if (end.done && act == GCN_ACT_RELU) return GCN_OK;
         if (bias && !end.done) {                                  // and the activation, when it goes to a matrix of its own
             PhaseTimer pt(s, GCN_PHASE_OTHER);
@@ -101,15 +115,18 @@ static int layer_backward_impl(gcn_csr* a, int32_t f_in, int32_t f_out, const fl
     }
     if (order == GCN_ORDER_GEMM_FIRST) {
         // S = A G;  Y = Hin^T S;  Gprev = (S W^T) (.) sigma'(Zprev)
-        GCN_TRY(norm_spmm(a, matrix_of(a, 0), f_out, G, f_out, xs, S, f_out, GCN_EPI_NONE, nullptr, 0, s, false, true));
-        if (Gprev) {
+        // (an epoch's Gprev lies in no operand's memory; at width 16 the dense products are one launch together)
+        RowsNext next;
+        if (Gprev && s_scratch && !(f_in == 16 && f_out == 16)) next = gemm_next(a, f_out, W, f_in, true, Gprev, Zprev);
+        GCN_TRY(norm_spmm(a, matrix_of(a, 0), f_out, G, f_out, xs, S, f_out, GCN_EPI_NONE, nullptr, 0, s, false, true, nullptr, &next));
+        if (Gprev && !next.done) {
             PhaseTimer pt(s, GCN_PHASE_GEMM);
             bool both = false;
             GCN_TRY(gemm_back_launch(n, f_in, f_out, Hin, ldh, S, W, Zprev, Y, Gprev, s, &both));
             if (both) return GCN_OK;
         }
         GCN_TRY(timed_gemm(1, 0, f_in, f_out, n, Hin, ldh, S, f_out, Y, f_out, nullptr, GCN_EPI_NONE, nullptr, 0, s));
-        if (Gprev)
+        if (Gprev && !next.done)
             GCN_TRY(timed_gemm(0, 1, n, f_in, f_out, S, f_out, W, f_out, Gprev, f_in, nullptr, GCN_EPI_MASK, Zprev, f_in, s));
     } else {
         // Y = (A^T Hin)^T G = T^T G;  Gprev = (A (G W^T)) (.) sigma'(Zprev): the same matrices, with the
@@ -292,6 +309,7 @@ static int epoch_impl(gcn_csr* a, int32_t L_w, const int32_t* dims, const float*
     const bool fuse = fuse_mode != 0 && layer_order(last) == GCN_ORDER_SPMM_FIRST &&
                       fused_last_supported(dims[last], dims[L_w]);
     const float* Hin = H0;
+    bool t_made = false, loss_done = false;
     for (int l = 0; l < L_w; ++l) {
         const bool is_last = (l == last);
         if (is_last && fuse) {
@@ -300,9 +318,14 @@ static int epoch_impl(gcn_csr* a, int32_t L_w, const int32_t* dims, const float*
                                   false, true));
             break;
         }
+        RowsNext next;
+        if (is_last) next = loss_next(dims[L_w], (n + 15) / 16, labels, n_labelled, at(lay.G[last]));
+        else if (layer_order(l + 1) == GCN_ORDER_GEMM_FIRST) next = gemm_next(a, dims[l + 1], W[l + 1], dims[l + 2], false, layer_T(l + 1), nullptr);
         GCN_TRY(layer_forward_impl(a, dims[l], dims[l + 1], Hin, dims[l], W[l], nullptr, at(lay.Z[l]),
                                    is_last ? nullptr : at(lay.Z[l]), layer_T(l), layer_order(l),
-                                   is_last ? GCN_ACT_NONE : GCN_ACT_RELU, s, at(lay.XS), true, l == 0 && P0));
+                                   is_last ? GCN_ACT_NONE : GCN_ACT_RELU, s, at(lay.XS), true, l == 0 && P0, t_made, &next));
+        t_made = !is_last && next.done;
+        loss_done = is_last && next.done;
         Hin = at(lay.H[l]);
     }
     end.W = W[last];
@@ -312,6 +335,8 @@ static int epoch_impl(gcn_csr* a, int32_t L_w, const int32_t* dims, const float*
         GCN_TRY(fused_last_launch(n, dims[L_w], layer_T(last), W[last], labels, n_labelled, loss, Y[last],
                                   last > 0 ? at(lay.S) : nullptr, pre_scale(a, true), keep ? at(lay.Z[last]) : nullptr,
                                   keep ? at(lay.G[last]) : nullptr, ws + lay.scratch, s));
+    } else if (loss_done) {
+        loss_made((n + 15) / 16, n_labelled, loss);
     } else {
         PhaseTimer pt(s, GCN_PHASE_OTHER);
         GCN_TRY(gcn_softmax_nll_masked(n, dims[L_w], at(lay.Z[L_w - 1]), dims[L_w], labels, n_labelled, loss,

@@ -150,6 +150,24 @@ static void dispatch_rows(int64_t n, int32_t C, const float* Z, int64_t ldz, con
     }
 }
 
+RowsNext loss_next(int32_t C, int64_t parts, const int32_t* labels, int64_t n_labelled, float* G) {
+    RowsNext next;
+    const EpochEnd* const end = epoch_end();
+    if (!end || C > 16 || C % 4 != 0 || parts > LOSS_BLOCKS_MAX || !end->fits(loss_scratch_bytes())) return next;
+    next.kind = RowsNext::LOSS;
+    next.part = (double*)end->room;
+    next.labels = labels;
+    next.G = G;
+    next.inv_m = 1.0f / (float)n_labelled;
+    return next;
+}
+
+void loss_made(int64_t parts, int64_t n_labelled, float* loss) {
+    EpochEnd* const end = epoch_end();
+    end->args.lpart = (double*)end->take(loss_scratch_bytes());
+    end->args.lparts = parts; end->args.inv_m = 1.0 / (double)n_labelled; end->args.loss = loss;
+}
+
 size_t loss_scratch_bytes() { return (size_t)LOSS_BLOCKS_MAX * sizeof(double); }
 
 }  // namespace gcn

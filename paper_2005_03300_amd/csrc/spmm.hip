@@ -638,9 +638,14 @@ __device__ __forceinline__ int group_lane(int x, int l) {
     return __shfl(x, l, LPR);
 }
 
-template <int LPR, int SLICE, int EPI>
-__global__ __launch_bounds__(64) void k_spmm_short(SplitArgs a, int64_t nrows, const int32_t* __restrict__ rows, int32_t pitch) {
+// What is next to the rows (RowsNext) is done by the wavefront that made them, 16 rows of up to 16 columns: as a kernel of its own it
+// would run for four microseconds, most of it its start and one chain of latencies, of which all but the stores happen here beside the walk.
+// The matrix instructions and the sums of a row's exponentials are those of k_gemm_tall and k_softmax_nll, bit for bit.  Epochs: 64-16-8 on 4096
+// rows of 17 entries 53 -> 42.5 us (11 launches, now 8), 64-16-16-8 on 1000 67 -> 54, 100-16-4 on 30000 63 -> 53.
+template <int LPR, int SLICE, int EPI, int NEXT = RowsNext::NONE>
+__global__ __launch_bounds__(64) void k_spmm_short(SplitArgs a, int64_t nrows, const int32_t* __restrict__ rows, int32_t pitch, RowsNext nx) {
     constexpr int VEC = 4;
+    static_assert(NEXT == RowsNext::NONE || LPR == 4, "16 rows of a wavefront");
     static_assert(SHORT_ROW <= 2 * SLICE, "at most three pieces");
     constexpr int U = 8, OWN = LPR < U ? U / LPR : 1;           // entries per round, those that a lane holds the indices of
     const int lane = threadIdx.x, li = lane % LPR;
@@ -669,6 +674,20 @@ __global__ __launch_bounds__(64) void k_spmm_short(SplitArgs a, int64_t nrows, c
     indices(U, next);
 #pragma unroll
     for (int e = 0; e < U; ++e) gather(now, e);
+    // the next product's operands: lane (r, kq) holds rows 4 kq .. 4 kq + 3 of column r of op(W), and four columns of row r of the mask
+    const int r = lane & 15, kq = lane >> 4;
+    const int64_t next_row = (int64_t)blockIdx.x * 16 + r;
+    float w[4] = {}, mask[4] = {1.f, 1.f, 1.f, 1.f};
+    int32_t label = -1;
+    if constexpr (NEXT == RowsNext::GEMM) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (4 * kq + e < a.f && r < nx.N) w[e] = nx.transposed ? nx.W[r * a.f + 4 * kq + e] : nx.W[(4 * kq + e) * nx.N + r];
+        if (nx.mask && next_row < nrows && 4 * kq < nx.N) load_vec<4>(mask, nx.mask + next_row * nx.N + 4 * kq);
+    }
+    if constexpr (NEXT == RowsNext::LOSS) {
+        if (row < nrows) label = nx.labels[row];
+    }
     const int len = row < nrows ? packed & 0xffff : 0, rs = packed >> 16;           // rs: modulo CHUNK, and so modulo SLICE
     const int b1 = SLICE - (rs & (SLICE - 1)), b2 = b1 + SLICE;                     // where the second and the third piece begin
     const bool third_apart = ((rs + b2) & (CHUNK - 1)) == 0;
@@ -692,7 +711,7 @@ __global__ __launch_bounds__(64) void k_spmm_short(SplitArgs a, int64_t nrows, c
         now = next;
         indices(base + 2 * U, next);
     }
-    if (row >= nrows || !col_ok) return;
+    if (NEXT == RowsNext::NONE && (row >= nrows || !col_ok)) return;
     if (len > b2) {
 #pragma unroll
         for (int u = 0; u < VEC; ++u) acc[u] = third_apart ? (first[u] + second[u]) + acc[u] : first[u] + (second[u] + acc[u]);
@@ -700,8 +719,56 @@ __global__ __launch_bounds__(64) void k_spmm_short(SplitArgs a, int64_t nrows, c
 #pragma unroll
         for (int u = 0; u < VEC; ++u) acc[u] = first[u] + acc[u];
     }
-    epilogue_store<VEC, EPI>(a.Z + row * a.ldz + col0, EPI == GCN_EPI_MASK ? a.Zprev + row * a.ldzprev + col0 : nullptr, acc,
-                             a.row_scale ? a.row_scale[row] : 1.f, a.defer && a.defer[row]);
+    const bool mine = row < nrows && col_ok;
+    if (mine) epilogue_store<VEC, EPI>(a.Z + row * a.ldz + col0, EPI == GCN_EPI_MASK ? a.Zprev + row * a.ldzprev + col0 : nullptr, acc,
+                                       a.row_scale ? a.row_scale[row] : 1.f, a.defer && a.defer[row]);
+    if constexpr (NEXT == RowsNext::GEMM) {                     // (all lanes)
+        typedef float floatx4 __attribute__((ext_vector_type(4)));
+        floatx4 t = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float ae = __shfl(mine ? acc[e] : 0.f, r * 4 + kq, 64);
+            t = __builtin_amdgcn_mfma_f32_16x16x4f32(w[e], ae, t, 0, 0, 0);
+        }
+        if (next_row < nrows && 4 * kq < nx.N) {
+            float v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = mask[e] > 0.f ? t[e] : 0.f;
+            store_vec<4>(nx.T + next_row * nx.N + 4 * kq, v);
+        }
+    }
+    if constexpr (NEXT == RowsNext::LOSS) {
+        float v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = mine ? acc[e] : -INFINITY;
+        float m = v[0];
+#pragma unroll
+        for (int e = 1; e < 4; ++e) m = fmaxf(m, v[e]);
+        m = fmaxf(m, __shfl_xor(m, 2, 64));
+        m = fmaxf(m, __shfl_xor(m, 1, 64));
+        float sum = 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum += expf(v[e] - m);      // exp(-inf) = 0 behind the last class
+        sum += __shfl_xor(sum, 2, 64);
+        sum += __shfl_xor(sum, 1, 64);
+        const float lse = m + logf(sum);
+        const bool labelled = label >= 0;
+        const int y = label >= a.f ? a.f - 1 : label;           // labels >= C are the caller's error; stay in bounds
+        double loss = 0.0;
+        if (mine) {
+            float d[4], zy = 0.f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                d[e] = labelled ? (expf(v[e] - lse) - (col0 + e == y ? 1.f : 0.f)) * nx.inv_m : 0.f;
+                zy = col0 + e == y ? v[e] : zy;
+            }
+            store_vec<4>(nx.G + row * a.f + col0, d);
+            if (labelled && y >= col0 && y < col0 + 4) loss = (double)lse - (double)zy;
+        }
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) loss += __shfl_xor(loss, d, 64);
+        if (lane == 0) nx.part[blockIdx.x] = loss;
+    }
 }
 
 // Widths above 32 that are no multiple of four, few chunks.  They used to run with one float per lane, a wavefront adding up a
@@ -1245,15 +1312,28 @@ static bool short_rows(const Matrix& m, int32_t f) {
     return f >= 4 && m.short_col && lanes <= SHORT_LANES && lanes <= (int64_t)device_info().cus * 8 * 64;
 }
 
-static int launch_short(const SplitArgs& args, const Matrix& m, int epilogue, hipStream_t s) {
+static int launch_short(const SplitArgs& args, const Matrix& m, int epilogue, hipStream_t s, RowsNext* next) {
     const int64_t nrows = m.nrows;
+    if (next && next->kind != RowsNext::NONE && epilogue != GCN_EPI_MASK && args.f % 4 == 0 && args.f <= 16) {
+        const dim3 grid((unsigned)((nrows + 15) / 16));
+        const RowsNext nx = *next;
+        timing_begin(s);
+        if (nx.kind == RowsNext::LOSS) hipLaunchKernelGGL((k_spmm_short<4, 32, GCN_EPI_NONE, RowsNext::LOSS>), grid, dim3(64), 0, s, args, nrows, m.short_rows, m.short_pitch, nx);
+        else if (epilogue == GCN_EPI_RELU) hipLaunchKernelGGL((k_spmm_short<4, 32, GCN_EPI_RELU, RowsNext::GEMM>), grid, dim3(64), 0, s, args, nrows, m.short_rows, m.short_pitch, nx);
+        else hipLaunchKernelGGL((k_spmm_short<4, 32, GCN_EPI_NONE, RowsNext::GEMM>), grid, dim3(64), 0, s, args, nrows, m.short_rows, m.short_pitch, nx);
+        timing_end(s);
+        GCN_LAUNCH_CHECK();
+        next->done = true;
+        return GCN_OK;
+    }
+    const RowsNext none;
     auto go = [&](auto lpr, auto slice) {
         constexpr int LPR = decltype(lpr)::value, SLICE = decltype(slice)::value;
         const dim3 grid((unsigned)((nrows * LPR + 63) / 64), (unsigned)((args.f + 4 * LPR - 1) / (4 * LPR)));
         switch (epilogue) {
-            case GCN_EPI_NONE: hipLaunchKernelGGL((k_spmm_short<LPR, SLICE, GCN_EPI_NONE>), grid, dim3(64), 0, s, args, nrows, m.short_rows, m.short_pitch); break;
-            case GCN_EPI_RELU: hipLaunchKernelGGL((k_spmm_short<LPR, SLICE, GCN_EPI_RELU>), grid, dim3(64), 0, s, args, nrows, m.short_rows, m.short_pitch); break;
-            default: hipLaunchKernelGGL((k_spmm_short<LPR, SLICE, GCN_EPI_MASK>), grid, dim3(64), 0, s, args, nrows, m.short_rows, m.short_pitch); break;
+            case GCN_EPI_NONE: hipLaunchKernelGGL((k_spmm_short<LPR, SLICE, GCN_EPI_NONE>), grid, dim3(64), 0, s, args, nrows, m.short_rows, m.short_pitch, none); break;
+            case GCN_EPI_RELU: hipLaunchKernelGGL((k_spmm_short<LPR, SLICE, GCN_EPI_RELU>), grid, dim3(64), 0, s, args, nrows, m.short_rows, m.short_pitch, none); break;
+            default: hipLaunchKernelGGL((k_spmm_short<LPR, SLICE, GCN_EPI_MASK>), grid, dim3(64), 0, s, args, nrows, m.short_rows, m.short_pitch, none); break;
         }
     };
     timing_begin(s);
@@ -1760,7 +1840,7 @@ static int run_matrix(gcn_csr* a, Matrix& mm, const int32_t* row_map, int64_t nn
     if (short_kernel) {
         args.colidx = mm.short_col;
         if (args.val) args.val = mm.short_val;
-        return launch_short(args, mm, epilogue, s);
+        return launch_short(args, mm, epilogue, s, o.next);
     }
     if (o.end && !row_map && choice.kernel == SplitChoice::SPLIT && choice.vec == 4 && mm.n_ne == mm.nrows) {
         // (rows without entries are their bias alone; the other kernels run where a pass more is a launch more, or on ragged widths)

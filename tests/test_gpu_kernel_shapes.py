@@ -989,6 +989,56 @@ def test_reductions_at_the_end_of_the_epoch(n, dims):
     a.close()
 
 
+@pytest.mark.parametrize("n,dims,rows", [
+    (63, (20, 16, 8), "short"), (64, (20, 16, 8), "short"), (65, (64, 16, 8), "short"), (4097, (64, 16, 16, 12), "short"), (1000, (8, 8, 4), "short"),
+    (333, (33, 12, 12, 16), "short"), (1000, (16, 4, 12, 4), "short"), (1000, (64, 16, 7), "short"), (1000, (64, 32, 16, 8), "short"),
+    (32_768, (16, 8, 4), "short"), (1000, (40, 16, 20), "short"), (1000, (64, 16, 8), "long"), (300, (20, 16, 8), "empty")])
+def test_epoch_on_short_rows_is_the_calls_one_by_one(n, dims, rows):
+    """The dense product in front of the next sparse one, its masked counterpart in the backward pass and the loss where the kernel of few and
+    short rows makes the rows: the bits of the layer and loss calls, whose kernels run one by one.  One row more or less than
+    the dense kernel takes, the last 16 rows not whole, widths of 4 to 16, as many rows as the kernel is taken for; widths and rows beside its range."""
+    g = G()
+    rs = np.random.default_rng(151)
+    u, v = rs.integers(0, n, (2, 3 * n)).astype(np.int32)
+    flags = g.NORM_SYM | g.SYMMETRISE | g.BUILD_TRANSPOSE
+    if rows == "long":
+        u[:200] = 0
+    if rows == "empty":
+        u, v = u // 2, v // 2                                      # the upper half of the rows has no entries
+    else:
+        flags |= g.ADD_SELF_LOOPS
+    a = g.gcn_csr_create(n, dev(u), dev(v), flags)
+    assert ("k_spmm_short" in g.gcn_spmm_describe(a, 0, dims[1])) == (rows != "long")
+    H0, y = dev(synth.normal_features(n, dims[0], 152)), dev(rs.integers(-1, dims[-1] + 1, n).astype(np.int32))      # (a label too large counts as the last class)
+    count, L = int((y >= 0).sum()), len(dims) - 1
+    W = [dev(w) for w in synth.glorot_weights(dims, 153)]
+    Y = [torch.full_like(w, float("nan")) for w in W]
+    loss = torch.full((1,), float("nan"), device="cuda")
+    ws = torch.empty(g.gcn_epoch_workspace_bytes(n, dims), dtype=torch.uint8, device="cuda")
+    g.gcn_csr_config(a, g.CFG_FUSED_LAST_LAYER, 0)
+    empty = lambda k: torch.full((n, k), float("nan"), device="cuda")
+    Z, T, Gr = ([empty(d) for d in dims[1:]] for _ in range(3))
+    T = [empty(min(p, q)) for p, q in zip(dims, dims[1:])]
+    x = H0
+    for l in range(L):
+        g.gcn_layer_forward(a, x, W[l], Z[l], Z[l] if l < L - 1 else None, T[l], act=g.ACT_RELU if l < L - 1 else g.ACT_NONE)
+        x = Z[l]
+    want_loss = torch.zeros(1, device="cuda")
+    g.gcn_softmax_nll_masked(Z[-1], y, count, want_loss, Gr[-1])
+    want_Y = [torch.empty_like(w) for w in W]
+    for l in range(L - 1, -1, -1):
+        g.gcn_layer_backward(a, Z[l - 1] if l else H0, Z[l - 1] if l else None, W[l], Gr[l], T[l], empty(T[l].shape[1]), want_Y[l], Gr[l - 1] if l else None)
+    for rep in range(2):
+        ws.fill_(255)
+        g.gcn_epoch_masked(a, dims, H0, y, count, W, Y, 0.0, loss, ws)
+        for l in range(L):
+            got_Z, got_G = g.gcn_epoch_view(n, dims, g.ORDER_AUTO, ws, l + 1)
+            assert torch.equal(got_Z, Z[l]) and torch.equal(got_G, Gr[l]) and torch.equal(Y[l], want_Y[l]), (rep, l)
+        # losses are added up in double, here by rows of 16, there by workgroups: the last bit of the float may differ
+        assert abs(float(loss) - float(want_loss)) <= 2.0 ** -23 * abs(float(want_loss))
+    a.close()
+
+
 @pytest.mark.parametrize("f", [4, 7, 16, 20, 32, 41, 48, 64, 130])
 @pytest.mark.parametrize("pairs,loops,blocks", [(500, True, 0), (400_000, True, 1), (400_000, True, 3), (400_000, False, 1), (400_000, False, 3)])
 @pytest.mark.parametrize("values", [0, 1])
