@@ -210,8 +210,8 @@ ScratchScope::~ScratchScope() {
 }
 
 static thread_local EpochEnd* g_epoch_end = nullptr;
-EpochEnd::EpochEnd(void* p, size_t bytes) : room(bytes ? (char*)p : nullptr), left(bytes) {
-    if (room) g_epoch_end = this;
+EpochEnd::EpochEnd(const Room& r) : room(r) {
+    if (room.left[0] || room.left[1]) g_epoch_end = this;
 }
 EpochEnd::~EpochEnd() {
     if (g_epoch_end == this) g_epoch_end = nullptr;

@@ -281,21 +281,26 @@ struct EpochEnd {
         int32_t count = 0, loss_at = -1;
         float lr = 0;
     } args;
-    char* room;
-    size_t left;
+    struct Room {                                 // two pieces of memory, handed out first fit
+        char* at[2] = {};
+        size_t left[2] = {};
+        static size_t whole(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
+        char* find(size_t bytes) const { return whole(bytes) <= left[0] ? at[0] : (whole(bytes) <= left[1] ? at[1] : nullptr); }
+        char* take(size_t bytes) {
+            char* const p = find(bytes);
+            if (!p) return nullptr;
+            const int k = p == at[0] && whole(bytes) <= left[0] ? 0 : 1;
+            at[k] += whole(bytes);
+            left[k] -= whole(bytes);
+            return p;
+        }
+    } room;
     float* W = nullptr;                           // of the layer whose gradient comes next
-    EpochEnd(void* p, size_t bytes);              // no room: everything as without it
+    explicit EpochEnd(const Room& r);             // no room: everything as without it
     ~EpochEnd();
-    bool fits(size_t bytes) const { return room && args.count < MOST && ((bytes + 255) & ~(size_t)255) <= left; }
-    // `bytes` of its room, or NULL
-    void* take(size_t bytes) {
-        const size_t need = (bytes + 255) & ~(size_t)255;
-        if (!fits(bytes)) return nullptr;
-        void* p = room;
-        room += need;
-        left -= need;
-        return p;
-    }
+    // where the next `bytes` will lie, or NULL; and taking them
+    void* next(size_t bytes) const { return args.count < MOST ? room.find(bytes) : nullptr; }
+    void* take(size_t bytes) { return args.count < MOST ? room.take(bytes) : nullptr; }
     void add(const float* part, float* Y, int32_t M, int32_t N, int parts, bool transposed) {
         args.sums[args.count++] = Sum{part, Y, W, M, N, (int32_t)parts, transposed ? 1 : 0, 0};
     }
@@ -306,6 +311,7 @@ EpochEnd* epoch_end();                            // the thread's, or NULL
 size_t gemm_tn_scratch_bytes(int64_t M, int64_t N, int64_t K);
 size_t colsum_scratch_bytes(int64_t rows, int32_t cols);
 size_t loss_scratch_bytes();
+size_t loss_part_bytes(int64_t n);               // what n rows need of it: a workgroup takes four at the least
 
 // Compute units and L2 size (one XCD's) of the current device, read once per device from the runtime.
 struct DeviceInfo { int cus; int64_t l2_bytes; };

@@ -148,7 +148,6 @@ struct EpochLayout {
     size_t S = 0, XS = 0, total = 0;  // XS: pre-scaled SpMM operand of the value-free product
     size_t scratch = 0;               // partial sums of the fused last layer, and the next where they do not fit XS
     size_t part = 0, part_bytes = 0;  // partial sums of the weight gradients and of the loss
-    size_t end = 0, end_bytes = 0;    // the same, side by side, of an epoch that adds them up at its end (EpochEnd)
     std::vector<int> order;
 };
 
@@ -192,15 +191,6 @@ static EpochLayout epoch_layout(int64_t n, int32_t L, const int32_t* dims, int o
     lay.scratch = take((sc + sizeof(float) - 1) / sizeof(float));
     lay.part = tn > xs_bytes ? lay.scratch : lay.XS;
     lay.part_bytes = tn > xs_bytes ? sc : xs_bytes;
-    // Side by side as long as that is little memory: the launches it saves are what a small epoch waits for (4096 vertices, 64-16-8: 59 ->
-    // 50 us; 120 K vertices, 256-64-64-41: 1030 -> 1016).
-    constexpr size_t MOST = 64ull << 20;
-    size_t all = round256(loss_scratch_bytes());
-    for (int l = 0; l < L; ++l) all += round256(gemm_tn_scratch_bytes(dims[l], dims[l + 1], n));
-    if (all <= MOST && L < EpochEnd::MOST) {
-        lay.end_bytes = all;
-        lay.end = take(all / sizeof(float));
-    }
     lay.total = off;
     return lay;
 }
@@ -214,6 +204,24 @@ static bool apart(int32_t L, const int32_t* dims, float* const* W, float* const*
         for (int j = 0; j < L; ++j)
             if (meet(W[i], i, Y[j], j) || (i < j && (meet(W[i], i, W[j], j) || meet(Y[i], i, Y[j], j)))) return false;
     return true;
+}
+
+// Where an epoch leaves the partial sums of all its reductions side by side, to be added up in one launch at its end (EpochEnd; the launches it
+// saves are what a small epoch waits for: 4096 vertices, 64-16-8: 59 -> 50 us; 120 K vertices, 256-64-64-41: 1030 -> 1016).  In memory
+// that is idle from the loss on, so that the workspace is not larger for it: the region of the scaled operand where the products need none
+// (`value_free`), else the first layer's T, which forward has read by then or, with P0 given, nobody does; and the scratch unless the fused
+// last layer (`fuse`) has it.  All of them or none.
+static EpochEnd::Room end_room(const EpochLayout& lay, char* ws, int64_t n, int32_t L, const int32_t* dims, bool value_free, bool p0, bool fuse) {
+    EpochEnd::Room room;
+    if (L >= EpochEnd::MOST) return room;
+    const bool t_idle = p0 || (lay.order[0] == GCN_ORDER_GEMM_FIRST && L >= 2);
+    if (!value_free) { room.at[0] = ws + lay.XS; room.left[0] = lay.scratch - lay.XS; }
+    else if (t_idle) { room.at[0] = ws + lay.T[0]; room.left[0] = lay.G[0] - lay.T[0]; }
+    if (!fuse) { room.at[1] = ws + lay.scratch; room.left[1] = lay.total - lay.scratch; }
+    EpochEnd::Room left = room;                   // in the order in which they are taken
+    bool all = fuse || left.take(loss_part_bytes(n));
+    for (int l = fuse ? L - 2 : L - 1; l >= 0 && all; --l) all = left.take(gemm_tn_scratch_bytes(dims[l], dims[l + 1], n)) != nullptr;
+    return all ? room : EpochEnd::Room();
 }
 
 static int check_dims(int64_t n, int32_t L, const int32_t* dims) {
@@ -295,8 +303,6 @@ static int epoch_impl(gcn_csr* a, int32_t L_w, const int32_t* dims, const float*
     hipStream_t s = (hipStream_t)stream;
     char* ws = (char*)workspace;
     auto at = [&](size_t off) { return (float*)(ws + off); };
-    ScratchScope scratch_scope(ws + lay.part, lay.part_bytes);
-    EpochEnd end(ws + lay.end, apart(L_w, dims, W, Y) ? lay.end_bytes : 0);
     // With P0 = A^T H0 given, layer 1 runs in SpMM-first order on it: Z^1 = P0 W^1, Y^1 = P0^T G^1, and
     // neither direction needs a sparse product.
     auto layer_order = [&](int l) { return (l == 0 && P0) ? (int)GCN_ORDER_SPMM_FIRST : lay.order[l]; };
@@ -308,6 +314,9 @@ static int epoch_impl(gcn_csr* a, int32_t L_w, const int32_t* dims, const float*
     const int fuse_mode = cfg_of(a).fused_last;
     const bool fuse = fuse_mode != 0 && layer_order(last) == GCN_ORDER_SPMM_FIRST &&
                       fused_last_supported(dims[last], dims[L_w]);
+    EpochEnd end(apart(L_w, dims, W, Y) ? end_room(lay, ws, n, L_w, dims, use_value_free(a), P0 != nullptr, fuse) : EpochEnd::Room());
+    // (with room for all of them nothing asks for the scratch, where the others' results may lie)
+    ScratchScope scratch_scope(ws + lay.part, epoch_end() ? 0 : lay.part_bytes);
     const float* Hin = H0;
     bool t_made = false, loss_done = false;
     for (int l = 0; l < L_w; ++l) {

@@ -153,9 +153,10 @@ static void dispatch_rows(int64_t n, int32_t C, const float* Z, int64_t ldz, con
 RowsNext loss_next(int32_t C, int64_t parts, const int32_t* labels, int64_t n_labelled, float* G) {
     RowsNext next;
     const EpochEnd* const end = epoch_end();
-    if (!end || C > 16 || C % 4 != 0 || parts > LOSS_BLOCKS_MAX || !end->fits(loss_scratch_bytes())) return next;
+    if (!end || C > 16 || C % 4 != 0 || parts > LOSS_BLOCKS_MAX) return next;
+    next.part = (double*)end->next(parts * sizeof(double));
+    if (!next.part) return next;
     next.kind = RowsNext::LOSS;
-    next.part = (double*)end->room;
     next.labels = labels;
     next.G = G;
     next.inv_m = 1.0f / (float)n_labelled;
@@ -164,10 +165,11 @@ RowsNext loss_next(int32_t C, int64_t parts, const int32_t* labels, int64_t n_la
 
 void loss_made(int64_t parts, int64_t n_labelled, float* loss) {
     EpochEnd* const end = epoch_end();
-    end->args.lpart = (double*)end->take(loss_scratch_bytes());
+    end->args.lpart = (double*)end->take(parts * sizeof(double));
     end->args.lparts = parts; end->args.inv_m = 1.0 / (double)n_labelled; end->args.loss = loss;
 }
 
+size_t loss_part_bytes(int64_t n) { return (size_t)(n < 4 * LOSS_BLOCKS_MAX ? (n + 3) / 4 : LOSS_BLOCKS_MAX) * sizeof(double); }
 size_t loss_scratch_bytes() { return (size_t)LOSS_BLOCKS_MAX * sizeof(double); }
 
 }  // namespace gcn
@@ -177,7 +179,7 @@ using namespace gcn;
 static int softmax_nll_impl(int64_t n, int32_t C, const float* Z, int64_t ldz, const int32_t* labels, int64_t n_labelled,
                             float* loss, float* G, int64_t ldg, hipStream_t s) {
     EpochEnd* const end = epoch_end();
-    void* scratch = end ? end->take(loss_scratch_bytes()) : nullptr;
+    void* scratch = end ? end->take(loss_part_bytes(n)) : nullptr;
     const bool later = scratch != nullptr;
     if (!later) GCN_TRY(scratch_get(&scratch, loss_scratch_bytes(), s));
     double* part = (double*)scratch;

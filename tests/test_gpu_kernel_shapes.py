@@ -989,6 +989,38 @@ def test_reductions_at_the_end_of_the_epoch(n, dims):
     a.close()
 
 
+@pytest.mark.parametrize("value_free", [0, 1])
+@pytest.mark.parametrize("given", [False, True])
+@pytest.mark.parametrize("n,classes", [(70, 16), (3000, 16), (3000, 8), (3000, 40)])
+def test_partial_results_in_idle_memory(n, classes, given, value_free):
+    """The partial results that an epoch adds up at its end lie where the scaled operand would, or the first layer's T, by whether the products are
+    value-free and whether A^T H0 is given: the bits of the epoch whose tied weights make it add them one by one."""
+    g = G()
+    rs = np.random.default_rng(161)
+    dims = (40, 16, 16, classes)
+    a = g.gcn_csr_create(n, *[dev(rs.integers(0, n, 4 * n).astype(np.int32)) for _ in range(2)], g.ADD_SELF_LOOPS | g.NORM_SYM | g.SYMMETRISE | g.BUILD_TRANSPOSE)
+    g.gcn_csr_config(a, g.CFG_PATTERN_SPMM, value_free)
+    H0, y = dev(synth.normal_features(n, dims[0], 162)), dev(rs.integers(-1, classes, n).astype(np.int32))
+    W = [dev(w) for w in synth.glorot_weights(dims, 163)]
+    run = g.gcn_epoch_preaggregated if given else g.gcn_epoch_masked
+    ws = torch.empty(g.gcn_epoch_workspace_bytes(n, dims), dtype=torch.uint8, device="cuda")
+    got = []
+    for shared in (False, True):
+        both = torch.empty(W[0].numel() + W[1].numel() - 1, device="cuda")
+        Y = [both[:W[0].numel()].view_as(W[0]) if shared else torch.empty_like(W[0]), torch.empty_like(W[1]), torch.empty_like(W[2])]
+        if shared:                                                  # one float of the first two gradients; the first is written last
+            Y[1] = both[W[0].numel() - 1:].view_as(W[1])
+        loss = torch.full((1,), float("nan"), device="cuda")
+        ws.fill_(255)
+        run(a, dims, H0, y, int((y >= 0).sum()), W, Y, 0.0, loss, ws)
+        got.append([host(loss), host(Y[0]), host(Y[1]).reshape(-1)[1:], host(Y[2])])
+    for k, (p, q) in enumerate(zip(*got)):
+        assert np.isfinite(p).all(), k
+        # (losses are added up in double by other groups of rows where a product makes them: the last bit of the float may differ)
+        assert np.array_equal(p, q) if k else abs(p - q) <= 2.0 ** -23 * abs(q), k
+    a.close()
+
+
 @pytest.mark.parametrize("n,dims,rows", [
     (63, (20, 16, 8), "short"), (64, (20, 16, 8), "short"), (65, (64, 16, 8), "short"), (4097, (64, 16, 16, 12), "short"), (1000, (8, 8, 4), "short"),
     (333, (33, 12, 12, 16), "short"), (1000, (16, 4, 12, 4), "short"), (1000, (64, 16, 7), "short"), (1000, (64, 32, 16, 8), "short"),
