@@ -924,14 +924,16 @@ __global__ __launch_bounds__(256, 3) void k_spmm_ragged(SplitArgs a, int lanes) 
 // columns, 33 M: 1.71 -> 1.32 ms.
 template <int VEC, int EPI>
 __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_line(SplitArgs a) {
+    constexpr int UNR = VEC == 2 && EPI == GCN_EPI_MASK ? 8 : 16;      // (with 16 the masked form of two columns runs out of scalar registers)
+    typedef int32_t Ints __attribute__((ext_vector_type(UNR)));
+    typedef float Floats __attribute__((ext_vector_type(UNR)));
     typedef int32_t i16v __attribute__((ext_vector_type(16)));
-    typedef float f16v __attribute__((ext_vector_type(16)));
     typedef const __attribute__((address_space(4))) int32_t* ConstI;        // read-only while the kernel runs
     typedef const __attribute__((address_space(4))) float* ConstF;
     typedef const __attribute__((address_space(4))) i16v* ConstI16;
-    typedef const __attribute__((address_space(4))) f16v* ConstF16;
+    typedef const __attribute__((address_space(4))) Ints* ConstInts;
+    typedef const __attribute__((address_space(4))) Floats* ConstFloats;
     typedef const __attribute__((address_space(1))) char* Global;
-    constexpr int UNR = 16;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t c = chunk_group(a) * WAVES_PER_BLOCK + wave;
     if (c >= a.nchunks) return;
@@ -1028,19 +1030,26 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_line(SplitArgs a)
         asm("" : "+s"(row), "+v"(column));
         load_vec<VEC>(x, (const float*)(const Global)((const Global)row + column));
     };
-    auto fetch = [&](int p, float (&x)[UNR][VEC]) {
-        const i16v cc = *(ConstI16)(cols + p);
+    // A trip's indices, and the values of the trip before it with their row starts, are fetched a trip before they are used: through the
+    // scalar cache too they come from memory, and asked for when needed every trip waited for that twice (with the fix-up: 1.9 M entries at 41
+    // columns 55 -> 50.5 us, masked 67 -> 61.5; 0.7 M in rows of 7 46 -> 35; 1 M at 101 48 -> 42; 29 M at 45, bound by line fills,
+    // 738 -> 727).  (Past the chunk's last whole trip: that one again.)
+    const int whole = nk / UNR * UNR;
+    struct Scalars { Ints cc; Floats vv; uint32_t bits; };
+    Scalars n;
+#pragma unroll
+    for (int e = 0; e < UNR; ++e) n.vv[e] = 1.f;
+    auto ahead = [&](int p) {                                   // indices of trip p, values and starts of the one before
+        const int q = p < whole ? p : whole - UNR, r = p - UNR < whole ? p - UNR : whole - UNR;
+        n.cc = *(ConstInts)(cols + q);
+        if (vals) n.vv = *(ConstFloats)(vals + r);
+        n.bits = (uint32_t)flags[r / SUB] >> (r % SUB);
+    };
+    auto fetch = [&](Ints cc, float (&x)[UNR][VEC]) {
 #pragma unroll
         for (int e = 0; e < UNR; ++e) load_x(x[e], cc[e]);
     };
-    auto sums = [&](int p, const float (&x)[UNR][VEC]) {
-        const uint32_t bits = (uint32_t)flags[p / SUB] >> (p % SUB);
-        f16v vv;
-        if (vals) vv = *(ConstF16)(vals + p);
-        else {
-#pragma unroll
-            for (int e = 0; e < UNR; ++e) vv[e] = 1.f;
-        }
+    auto sums = [&](Floats vv, uint32_t bits, const float (&x)[UNR][VEC]) {
         if (at - named + UNR > 64) name_rows();
 #pragma unroll
         for (int e = 0; e < UNR; ++e) {
@@ -1051,15 +1060,27 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_line(SplitArgs a)
     };
     float xa[UNR][VEC], xb[UNR][VEC];
     int p = 0;
-    if (UNR <= nk) fetch(0, xa);
+    if (whole > 0) {
+        const Ints cc = *(ConstInts)cols;
+        fetch(cc, xa);
+        ahead(UNR);
 #pragma unroll 1
-    for (; p + 2 * UNR <= nk; p += 2 * UNR) {
-        fetch(p + UNR, xb);
-        sums(p, xa);
-        if (p + 3 * UNR <= nk) fetch(p + 2 * UNR, xa);
-        sums(p + UNR, xb);
+        for (;;) {
+            auto half = [&](float (&now)[UNR][VEC], float (&next)[UNR][VEC]) {
+                const Floats vv = n.vv;
+                const uint32_t bits = n.bits;
+                if (p + UNR < whole) fetch(n.cc, next);
+                ahead(p + 2 * UNR);
+                __builtin_amdgcn_sched_barrier(0);
+                sums(vv, bits, now);
+                p += UNR;
+            };
+            half(xa, xb);
+            if (p == whole) break;
+            half(xb, xa);
+            if (p == whole) break;
+        }
     }
-    if (p + UNR <= nk) { sums(p, xa); p += UNR; }
 #pragma unroll 1
     for (; p < nk; ++p) {                       // the end of the last chunk
         float x[VEC];
