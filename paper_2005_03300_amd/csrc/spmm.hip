@@ -53,6 +53,9 @@ struct SplitArgs {
     float* H = nullptr;
     int relu = 0;
     int lds_kb = 0;           // host side: GCN_CFG_SPLIT_LDS_KB
+    const int32_t* empty_rows = nullptr;        // rows without entries that the product's kernel zeroes (see zero_share)
+    int64_t n_empty = 0;
+    int32_t empty_share = 0;  // how many of them go with a chunk
     uint32_t per_xcd = 0;     // 0, or how many consecutive groups of chunks an XCD takes (see chunk_group)
 };
 
@@ -195,6 +198,30 @@ __device__ __forceinline__ void stage_chunk(const SplitArgs& a, int64_t k0, int 
     }
 }
 
+// Zeroes a chunk's share of the rows without entries (any epilogue maps 0 to 0): a launch of its own took 32 us for 0.7 M rows of 64
+// columns, bound by its stores, while the product beside it was short of memory traffic.  The list is asked for together with the
+// chunk (empty_row), the stores are sent before its gathers, 64 rows at a time.  Called by whole wavefronts.
+__device__ __forceinline__ int32_t empty_row(const SplitArgs& a, int64_t c, int i) {
+    if (a.empty_share == 0) return 0;
+    const int64_t q = c * a.empty_share + i;
+    return a.empty_rows[q < a.n_empty ? q : a.n_empty - 1];
+}
+template <int LPR, int VEC>
+__device__ __forceinline__ void zero_share(const SplitArgs& a, int64_t c, int lane, int32_t row, int col0, bool col_ok) {
+    constexpr int G = 64 / LPR;
+    const int64_t left = a.n_empty - c * a.empty_share;
+    const int mine = left < a.empty_share ? (int)left : a.empty_share, g = lane / LPR;
+    const float zero[VEC] = {};
+    for (int i0 = 0; i0 < mine; i0 += 64) {
+        if (i0 > 0) row = empty_row(a, c, i0 + lane);
+        const int count = mine - i0 < 64 ? mine - i0 : 64;
+        for (int i = 0; i < count; i += G) {
+            const int32_t r = __shfl(row, i + g, 64);
+            if (i + g < count && col_ok) store_vec<VEC>(a.Z + (int64_t)r * a.ldz + col0, zero);
+        }
+    }
+}
+
 // What a wavefront keeps in LDS for its chunk.
 template <int LPR, int VEC, bool MASK>
 struct __attribute__((aligned(16))) WaveLds {
@@ -245,7 +272,9 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int64_t grp, Lds*
     if (lane <= SUBS_PER_CHUNK) word = a.flags[j0 + lane];      // padded by a chunk of zero words
     const int32_t q0 = a.sub_row[j0];           // row of the chunk's first entry
     int at = a.sub_row[j0 + g * NW];            // and of this group's first
+    const int32_t empty = empty_row(a, c, lane);
     stage_chunk(a, k0, lane, L.col, L.val);
+    zero_share<LPR, VEC>(a, c, lane, empty, col0, col_ok);
     if (lane <= SUBS_PER_CHUNK) L.flag[lane] = word;
     const int32_t q1 = q0 + 1 - (int32_t)(__builtin_amdgcn_readfirstlane(word) & 1u);       // the first row begun here
     // each wavefront reads only what it wrote; LDS operations of one wavefront complete in order
@@ -486,6 +515,7 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_few(SplitArgs a) 
         const bool continued = k0 + CHUNK < a.nnz && !(a.flags[(c + 1) * SUBS_PER_CHUNK] & 1u);
         uint32_t mask = a.flags[j0];
         q = a.sub_row[j0];
+        const int32_t empty = empty_row(a, c, lane);
         int32_t* lc = s_col[wave];
         float* lv = s_val[wave];
 #pragma unroll
@@ -506,6 +536,7 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_few(SplitArgs a) 
             *reinterpret_cast<int4*>(lc + p) = cc;
             *reinterpret_cast<float4*>(lv + p) = vv;
         }
+        if (wave < OWN) zero_share<LPR, VEC>(a, c, lane, empty, col0, col_ok);
         // each wavefront reads only what it wrote; LDS operations of one wavefront complete in order
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -939,6 +970,7 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_line(SplitArgs a)
     if (c >= a.nchunks) return;
     int col0;                                   // (lanes without columns follow the last one that has some)
     const bool col_ok = lane_columns<64, VEC>(a.f, blockIdx.y, gridDim.y, lane, &col0);
+    if constexpr (VEC == 1) zero_share<64, VEC>(a, c, lane, empty_row(a, c, lane), col0, col_ok);
     const int64_t k0 = c * CHUNK;
     const int nk = a.nnz - k0 < CHUNK ? (int)(a.nnz - k0) : CHUNK;
     const ConstI cols = (ConstI)(uintptr_t)(a.colidx + k0), flags = (ConstI)(uintptr_t)(a.flags + c * SUBS_PER_CHUNK);
@@ -1116,8 +1148,8 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_split_pair(SplitA
 // the schedule was built, so that the carries and the row's sum so far are fetched right away.  A row of 60 K entries
 // has 120 carries: eight are in flight at a time, the additions stay in order.
 template <int LPR, int VEC, int EPI>
-__global__ __launch_bounds__(256) void k_spmm_fixup(SplitArgs a) {
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+__device__ __forceinline__ void fixup_body(const SplitArgs& a, int64_t block) {
+    const int64_t t = block * 256 + threadIdx.x;
     const int li = (int)(t % LPR);
     if (t / LPR >= a.n_fix) return;
     const int col0 = blockIdx.y * (LPR * VEC) + li * VEC;
@@ -1154,6 +1186,19 @@ __global__ __launch_bounds__(256) void k_spmm_fixup(SplitArgs a) {
     if constexpr (EPI == EPI_LAYER)
         layer_store<VEC>(z, a.H ? a.H + row * a.ldz + col0 : nullptr, a.bias ? a.bias + col0 : nullptr, a.relu, cur, scale);
     else epilogue_store<VEC, EPI>(z, EPI == GCN_EPI_MASK ? a.Zprev + row * a.ldzprev + col0 : nullptr, cur, scale, a.defer && a.defer[row]);
+}
+
+template <int LPR, int VEC, int EPI>
+__global__ __launch_bounds__(256) void k_spmm_fixup(SplitArgs a) {
+    fixup_body<LPR, VEC, EPI>(a, blockIdx.x);
+}
+
+// The rows of two matrices that k_spmm_split_pair multiplied, those of `b` (plain sums) in the workgroups from `blocks_a` on:
+// neither list fills the GPU, and one launch takes as long as the slower of two.
+template <int LPR, int VEC, int EPI>
+__global__ __launch_bounds__(256) void k_spmm_fixup_pair(SplitArgs a, SplitArgs b, uint32_t blocks_a) {
+    if (blockIdx.x < blocks_a) fixup_body<LPR, VEC, EPI>(a, blockIdx.x);
+    else fixup_body<LPR, VEC, GCN_EPI_NONE>(b, blockIdx.x - blocks_a);
 }
 
 // Rows without stored entries produce zeros (any epilogue maps 0 to 0).
@@ -1779,6 +1824,18 @@ static SpmmPlan& plan_of(gcn_csr* a, Matrix& m, int32_t f, Terms terms, int64_t 
     return m.plans.back();
 }
 
+// The rows without entries go with the chunks of the product, in equal shares, where there is a list of them and a chunk gets no more
+// of them than it has entries.  Not k_spmm_ragged, whose matrices are small, nor k_spmm_line<2>, whose registers they cost a wavefront.
+static bool share_empty_rows(SplitArgs* args, const Matrix& m, const SplitChoice& c) {
+    const int64_t n_empty = m.nrows - m.n_ne;
+    if (!m.empty_rows || n_empty > m.nchunks * CHUNK) return false;
+    if (c.kernel == SplitChoice::RAGGED || (c.kernel == SplitChoice::LINE && c.vec == 2)) return false;
+    args->empty_rows = m.empty_rows;
+    args->n_empty = n_empty;
+    args->empty_share = (int32_t)((n_empty + m.nchunks - 1) / m.nchunks);
+    return true;
+}
+
 static int zero_empty_rows(const Matrix& m, int32_t f, float* Z, int64_t ldz, hipStream_t s) {
     const int64_t n_empty = m.nrows - m.n_ne;
     if (m.empty_rows && n_empty > 0) {
@@ -1869,7 +1926,8 @@ static int run_matrix(gcn_csr* a, Matrix& mm, const int32_t* row_map, int64_t nn
         args.bias = o.end->bias; args.H = o.end->H; args.relu = o.end->relu;
         o.end->done = true;
     }
-    if (!row_map && mm.n_ne < mm.nrows) GCN_TRY(zero_empty_rows(mm, f, Z, ldz, s));
+    if (!row_map && mm.n_ne < mm.nrows && !share_empty_rows(&args, mm, choice))
+        GCN_TRY(zero_empty_rows(mm, f, Z, ldz, s));
     return run_split(args, epilogue, s, choice);
 }
 
@@ -1917,8 +1975,16 @@ static int launch_pair(const SplitArgs& ra_args, const SplitArgs& rb_args, int e
     }
     timing_end(s);
     GCN_LAUNCH_CHECK();
-    GCN_TRY((launch_fixup<LPR, 4>(ra_args, epilogue, s)));
-    return launch_fixup<LPR, 4>(rb_args, GCN_EPI_NONE, s);
+    const unsigned fa = (unsigned)((ra_args.n_fix * LPR + 255) / 256), fb = (unsigned)((rb_args.n_fix * LPR + 255) / 256);
+    if (fa + fb == 0) return GCN_OK;
+    const dim3 fix(fa + fb, ytiles);
+    switch (epilogue) {
+        case GCN_EPI_NONE: hipLaunchKernelGGL((k_spmm_fixup_pair<LPR, 4, GCN_EPI_NONE>), fix, dim3(256), 0, s, ra_args, rb_args, fa); break;
+        case GCN_EPI_RELU: hipLaunchKernelGGL((k_spmm_fixup_pair<LPR, 4, GCN_EPI_RELU>), fix, dim3(256), 0, s, ra_args, rb_args, fa); break;
+        default: hipLaunchKernelGGL((k_spmm_fixup_pair<LPR, 4, GCN_EPI_MASK>), fix, dim3(256), 0, s, ra_args, rb_args, fa); break;
+    }
+    GCN_LAUNCH_CHECK();
+    return GCN_OK;
 }
 
 // Z = A_rest X (long rows stored raw) and the partial rows of A_hot X_hot in one paired launch, then
@@ -1946,8 +2012,6 @@ static int run_hub(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx
     hipLaunchKernelGGL(k_pack_rows, dim3((unsigned)((h.H * lanes + 255) / 256)), dim3(256), 0, s, h.H, lanes, X, ldx,
                        h.hot_col, h.xhot);
     GCN_LAUNCH_CHECK();
-    if (rest.n_ne < rest.nrows) GCN_TRY(zero_empty_rows(rest, f, Z, ldz, s));
-
     SplitArgs ar;                                  // A_rest over X, into Z
     ar.colidx = rest.colidx; ar.val = o.pattern ? nullptr : rest.val; ar.flags = rest.flags; ar.sub_row = rest.sub_row;
     ar.row_scale = o.row_scale; ar.defer = h.defer;
@@ -1961,6 +2025,7 @@ static int run_hub(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx
     ah.fix_list = b.fix_list; ah.n_fix = b.n_fix; ah.n_fix_long = b.n_fix_long;
     ah.nnz = h.nnz_hot; ah.nsub = hot.nsub; ah.nchunks = hot.nchunks; ah.f = f;
     ah.X = h.xhot; ah.ldx = f; ah.Z = a->partial; ah.ldz = f; ah.Zprev = nullptr; ah.ldzprev = 0; ah.carry = a->carry2;
+    if (rest.n_ne < rest.nrows && !share_empty_rows(&ar, rest, SplitChoice{SplitChoice::SPLIT, f > 16 ? 8 : 4, 4})) GCN_TRY(zero_empty_rows(rest, f, Z, ldz, s));
     if (f > 16) GCN_TRY(launch_pair<8>(ar, ah, epilogue, s));
     else GCN_TRY(launch_pair<4>(ar, ah, epilogue, s));
     return launch_block_reduce<4>(hot.nrows, f, b, h.heavy_rows, o.row_scale, 1, a->partial, Z, ldz, epilogue, Zprev,

@@ -463,6 +463,42 @@ def test_spmm_mask_on_both_sides_of_its_rule(f, lengths):
     a.close()
 
 
+@pytest.mark.parametrize("full,length,f,kernel", [
+    (1000, 65, 13, "k_spmm_split<16,1>"), (1000, 65, 16, "k_spmm_few<4>"), (1000, 65, 64, "k_spmm_few<8>"), (1000, 65, 41, "k_spmm_ragged"),
+    (9000, 65, 3, "k_spmm_split<4,1>"), (9000, 65, 16, "k_spmm_split<4,4>"), (9000, 65, 64, "k_spmm_split<8,4>"),
+    (9000, 65, 41, "k_spmm_line<1>"), (9000, 65, 67, "k_spmm_line<2>"), (9000, 65, 130, "k_spmm_line<1>"), (9000, 65, 132, "k_spmm_split<8,4>")])
+@pytest.mark.parametrize("share", [1, 63, 64, 65, 511, 512, 513])
+def test_rows_without_entries_go_with_the_chunks(full, length, f, kernel, share):
+    """As many empty rows per chunk as fit one step of the zeroing, one less and one more, as many as a chunk takes at the most and one more
+    (a launch of their own); a last chunk with a smaller share or none: they are zero, the other rows have the bits of the
+    matrix without empty rows, and nothing between the rows of a wider output is touched."""
+    g = G()
+    chunks = (full * length + 511) // 512
+    empty = (share - 1) * chunks + max(1, chunks // 3)
+    rs = np.random.default_rng(118)
+    lens = np.zeros(full + empty, np.int64)
+    has = np.sort(rs.choice(full + empty, full, replace=False))
+    lens[has] = length
+    colidx = (rs.integers(0, 2000 - length, full)[:, None] + np.arange(length)).astype(np.int32).reshape(-1)
+    val = rs.standard_normal(colidx.size).astype(np.float32)
+    rowptr = lambda l: dev(np.concatenate([[0], np.cumsum(l)]).astype(np.int64))
+    a = g.gcn_csr_create_from_csr_rect(full + empty, 2000, rowptr(lens), dev(colidx), dev(val), 0)
+    b = g.gcn_csr_create_from_csr_rect(full, 2000, rowptr(lens[has]), dev(colidx), dev(val), 0)
+    X, M = dev(synth.normal_features(2000, f, 119)), dev(synth.normal_features(full + empty, f, 120))
+    at = torch.from_numpy(has).cuda()
+    for m in (a, b):
+        g.gcn_csr_config(m, g.CFG_SPMM_BLOCKS, 1)
+        assert kernel in g.gcn_spmm_describe(m, 0, f)
+    for epi in (g.EPI_NONE, g.EPI_RELU, g.EPI_MASK):
+        Z = torch.full((full + empty, f + 3), float("nan"), device="cuda")
+        g.gcn_spmm(a, 0, X, Z[:, :f], epi, M if epi == g.EPI_MASK else None)
+        want = torch.zeros(full + empty, f, device="cuda")
+        want[at] = g.gcn_spmm(b, 0, X, torch.empty(full, f, device="cuda"), epi, M[at].contiguous() if epi == g.EPI_MASK else None)
+        assert torch.equal(Z[:, :f], want) and bool(Z[:, f:].isnan().all()), epi
+    a.close()
+    b.close()
+
+
 @pytest.mark.parametrize("rows,length,f,blocks,want", [
     (1000, 17, 16, 0, "split(chunks=34,kernel=k_spmm_short<4>)"), (1000, 17, 41, 0, "split(chunks=34,kernel=k_spmm_short<16>)"),
     (1000, 65, 16, 0, "split(chunks=127,kernel=k_spmm_few<4>)"), (1000, 65, 64, 0, "split(chunks=127,kernel=k_spmm_few<8>)"),
