@@ -1395,3 +1395,30 @@ def test_rows_that_fill_no_set_are_not_swept(n, k, f, usual):
         g.gcn_csr_config(a, g.CFG_SPMM_ALGO, 0)
         assert g.gcn_spmm_describe(a, 0, f).startswith(usual)
     a.close()
+
+
+@pytest.mark.parametrize("nnz", [1, 4, 7, 4095, 4096, 4098, 3 * 4096 + 1, 1_000_003])
+@pytest.mark.parametrize("offset", [0, 1, 2, 4])
+def test_export_fills_the_callers_arrays_and_no_more(nnz, offset):
+    """Tiles of 4096 words and their remainders; destinations in pieces of 16 bytes and, `offset` words into an allocation, not; some left out."""
+    from paper_2005_03300_amd import binding
+    g = G()
+    n = nnz // 3 + 1
+    gen = torch.Generator(device="cuda").manual_seed(nnz)
+    cut = torch.sort(torch.randint(0, nnz + 1, (n - 1,), generator=gen, device="cuda")).values
+    rowptr = torch.cat([torch.zeros(1, dtype=torch.int64, device="cuda"), cut, torch.full((1,), nnz, device="cuda")])
+    cols = (torch.arange(nnz, device="cuda") % (nnz + 5)).int()
+    val = torch.rand(nnz, generator=gen, device="cuda")
+    a = g.gcn_csr_create_from_csr_rect(n, nnz + 5, rowptr, cols, val, 0)
+    deg = (rowptr[1:] - rowptr[:-1]).int()
+    want = [rowptr, cols, val, deg]
+    for keep in (15, 10):
+        room = [torch.full((w.numel() + 8,), -7, dtype=w.dtype, device="cuda") for w in want]
+        dst = [r[offset:] if keep >> i & 1 else None for i, r in enumerate(room)]
+        binding._check(binding.lib().gcn_csr_export(a._h, 0, *(binding._ptr(d) if d is not None else None for d in dst), binding._stream()))
+        for i, (r, w) in enumerate(zip(room, want)):
+            expect = torch.full_like(r, -7)
+            if keep >> i & 1:
+                expect[offset:offset + w.numel()] = w
+            assert torch.equal(r, expect), (i, keep)
+    a.close()
