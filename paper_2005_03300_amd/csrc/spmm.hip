@@ -200,7 +200,8 @@ __device__ __forceinline__ void stage_chunk(const SplitArgs& a, int64_t k0, int 
 
 // Zeroes a chunk's share of the rows without entries (any epilogue maps 0 to 0): a launch of its own took 32 us for 0.7 M rows of 64
 // columns, bound by its stores, while the product beside it was short of memory traffic.  The list is asked for together with the
-// chunk (empty_row), the stores are sent before its gathers, 64 rows at a time.  Called by whole wavefronts.
+// chunk (empty_row), the stores are sent before its gathers, 64 rows at a time.  Called by whole wavefronts.  Forms of the kernels
+// of their own (ZERO): in those of matrices without such rows the code for it cost 1 % of products of 11 to 40 us.
 __device__ __forceinline__ int32_t empty_row(const SplitArgs& a, int64_t c, int i) {
     if (a.empty_share == 0) return 0;
     const int64_t q = c * a.empty_share + i;
@@ -250,7 +251,7 @@ struct __attribute__((aligned(16))) WaveLds {
 // them are slower (119 M entries over column blocks: 611 us, 620 with two sets).  12 M entries in rows of 236 at 64 columns, operand
 // in the L2s: 187 -> 168 us; 2 M at 32: 34 -> 27; 33 M, packed hub and rest at 16: 318 -> 293; 9 M in rows of 9 at
 // 32: 203 -> 200 (line fills).
-template <int LPR, int VEC, int EPI, bool AHEAD, class Lds>
+template <int LPR, int VEC, int EPI, bool AHEAD, bool ZERO, class Lds>
 __device__ __forceinline__ void split_body(const SplitArgs& a, int64_t grp, Lds* lds) {
     constexpr int G = 64 / LPR;                 // lane groups per wavefront
     constexpr int LEN = CHUNK / G, NW = LEN / SUB;              // entries and flag words per group
@@ -272,9 +273,10 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int64_t grp, Lds*
     if (lane <= SUBS_PER_CHUNK) word = a.flags[j0 + lane];      // padded by a chunk of zero words
     const int32_t q0 = a.sub_row[j0];           // row of the chunk's first entry
     int at = a.sub_row[j0 + g * NW];            // and of this group's first
-    const int32_t empty = empty_row(a, c, lane);
+    int32_t empty = 0;
+    if constexpr (ZERO) empty = empty_row(a, c, lane);
     stage_chunk(a, k0, lane, L.col, L.val);
-    zero_share<LPR, VEC>(a, c, lane, empty, col0, col_ok);
+    if constexpr (ZERO) zero_share<LPR, VEC>(a, c, lane, empty, col0, col_ok);
     if (lane <= SUBS_PER_CHUNK) L.flag[lane] = word;
     const int32_t q1 = q0 + 1 - (int32_t)(__builtin_amdgcn_readfirstlane(word) & 1u);       // the first row begun here
     // each wavefront reads only what it wrote; LDS operations of one wavefront complete in order
@@ -477,10 +479,10 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int64_t grp, Lds*
     }
 }
 
-template <int LPR, int VEC, int EPI, bool AHEAD = true>
+template <int LPR, int VEC, int EPI, bool AHEAD = true, bool ZERO = false>
 __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_split(SplitArgs a) {
     __shared__ WaveLds<LPR, VEC, EPI == GCN_EPI_MASK && AHEAD> lds[WAVES_PER_BLOCK];
-    split_body<LPR, VEC, EPI, AHEAD>(a, chunk_group(a), lds);
+    split_body<LPR, VEC, EPI, AHEAD, ZERO>(a, chunk_group(a), lds);
 }
 
 // The same product for matrices of few chunks, which is a chain of memory latencies, launches and first executions of
@@ -491,7 +493,7 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_split(SplitArgs a
 // three chunks, its fourth wavefront sums the head of the chunk behind them, and heads are passed to the wavefront before
 // through LDS; a fix-up launch follows only when a row covers a whole further chunk.  The sums are those of
 // k_spmm_split and k_spmm_fixup, term by term.  1000 rows of 17 entries at 16 columns: 9.7 + 3.9 -> 7.7 us.
-template <int LPR, int EPI>
+template <int LPR, int EPI, bool ZERO>
 __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_few(SplitArgs a) {
     constexpr int VEC = 4;
     constexpr int G = 64 / LPR, NW = SUBS_PER_CHUNK / G, OWN = WAVES_PER_BLOCK - 1;
@@ -515,7 +517,8 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_few(SplitArgs a) 
         const bool continued = k0 + CHUNK < a.nnz && !(a.flags[(c + 1) * SUBS_PER_CHUNK] & 1u);
         uint32_t mask = a.flags[j0];
         q = a.sub_row[j0];
-        const int32_t empty = empty_row(a, c, lane);
+        int32_t empty = 0;
+        if constexpr (ZERO) empty = empty_row(a, c, lane);
         int32_t* lc = s_col[wave];
         float* lv = s_val[wave];
 #pragma unroll
@@ -536,7 +539,7 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_few(SplitArgs a) 
             *reinterpret_cast<int4*>(lc + p) = cc;
             *reinterpret_cast<float4*>(lv + p) = vv;
         }
-        if (wave < OWN) zero_share<LPR, VEC>(a, c, lane, empty, col0, col_ok);
+        if (ZERO && wave < OWN) zero_share<LPR, VEC>(a, c, lane, empty, col0, col_ok);
         // each wavefront reads only what it wrote; LDS operations of one wavefront complete in order
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -1139,8 +1142,8 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_split_pair(SplitA
     // both kinds of work in turn.
     __shared__ WaveLds<LPR, VEC, EPI == GCN_EPI_MASK> lds[WAVES_PER_BLOCK];
     const unsigned q = blockIdx.x / 8, r = (blockIdx.x + q) % 8;
-    if ((int)r < ra) split_body<LPR, VEC, EPI, true>(a, (int64_t)q * ra + r, lds);
-    else split_body<LPR, VEC, GCN_EPI_NONE, true>(b, (int64_t)q * rb + (r - ra), lds);
+    if ((int)r < ra) split_body<LPR, VEC, EPI, true, true>(a, (int64_t)q * ra + r, lds);
+    else split_body<LPR, VEC, GCN_EPI_NONE, true, false>(b, (int64_t)q * rb + (r - ra), lds);
 }
 
 // Adds, in ascending chunk order, the carries of the chunks a row runs on into, then applies the epilogue.  One LPR-lane
@@ -1295,12 +1298,17 @@ static int launch_few(const SplitArgs& args, int epilogue, hipStream_t s) {
     constexpr size_t lds = WAVES_PER_BLOCK * SUB * 64 * sizeof(float4);
     SplitArgs few = args;
     few.n_fix = args.n_fix_long;                  // they come first in the list
+    auto go = [&](auto zero) {
+        constexpr bool ZERO = decltype(zero)::value;
+        switch (epilogue) {
+            case GCN_EPI_NONE: launch_lds<k_spmm_few<LPR, GCN_EPI_NONE, ZERO>>(grid, 64 * WAVES_PER_BLOCK, lds, s, few); break;
+            case GCN_EPI_RELU: launch_lds<k_spmm_few<LPR, GCN_EPI_RELU, ZERO>>(grid, 64 * WAVES_PER_BLOCK, lds, s, few); break;
+            default: launch_lds<k_spmm_few<LPR, GCN_EPI_MASK, ZERO>>(grid, 64 * WAVES_PER_BLOCK, lds, s, few); break;
+        }
+    };
     timing_begin(s);
-    switch (epilogue) {
-        case GCN_EPI_NONE: launch_lds<k_spmm_few<LPR, GCN_EPI_NONE>>(grid, 64 * WAVES_PER_BLOCK, lds, s, few); break;
-        case GCN_EPI_RELU: launch_lds<k_spmm_few<LPR, GCN_EPI_RELU>>(grid, 64 * WAVES_PER_BLOCK, lds, s, few); break;
-        default: launch_lds<k_spmm_few<LPR, GCN_EPI_MASK>>(grid, 64 * WAVES_PER_BLOCK, lds, s, few); break;
-    }
+    if (args.empty_share > 0) go(std::true_type());
+    else go(std::false_type());
     timing_end(s);
     GCN_LAUNCH_CHECK();
     return fixup_of<LPR, 4>(few, epilogue, s);
@@ -1312,23 +1320,28 @@ static int launch_split(const SplitArgs& args, int epilogue, hipStream_t s) {
     const dim3 grid(chunk_groups(args), (unsigned)((args.f + tile - 1) / tile));
     const dim3 block(64 * WAVES_PER_BLOCK);
     const size_t pad = occupancy_pad<LPR, VEC>(args.lds_kb, epilogue);
-    timing_begin(s);
-    switch (epilogue) {
-        case GCN_EPI_NONE: hipLaunchKernelGGL((k_spmm_split<LPR, VEC, GCN_EPI_NONE>), grid, block, pad, s, args); break;
-        case GCN_EPI_RELU: hipLaunchKernelGGL((k_spmm_split<LPR, VEC, GCN_EPI_RELU>), grid, block, pad, s, args); break;
-        case EPI_LAYER:                         // (run_matrix)
-            if constexpr (VEC == 4) hipLaunchKernelGGL((k_spmm_split<LPR, VEC, EPI_LAYER>), grid, block, pad, s, args);
-            break;
-        default:
-            if constexpr (VEC == 4 && LPR == 8) {
-                if (many_row_starts(args)) {
-                    hipLaunchKernelGGL((k_spmm_split<LPR, VEC, GCN_EPI_MASK, false>), grid, block, pad, s, args);
-                    break;
+    auto go = [&](auto zero) {
+        constexpr bool ZERO = decltype(zero)::value;
+        switch (epilogue) {
+            case GCN_EPI_NONE: hipLaunchKernelGGL((k_spmm_split<LPR, VEC, GCN_EPI_NONE, true, ZERO>), grid, block, pad, s, args); break;
+            case GCN_EPI_RELU: hipLaunchKernelGGL((k_spmm_split<LPR, VEC, GCN_EPI_RELU, true, ZERO>), grid, block, pad, s, args); break;
+            case EPI_LAYER:                     // (run_matrix; no rows without entries)
+                if constexpr (VEC == 4 && !ZERO) hipLaunchKernelGGL((k_spmm_split<LPR, VEC, EPI_LAYER>), grid, block, pad, s, args);
+                break;
+            default:
+                if constexpr (VEC == 4 && LPR == 8) {
+                    if (many_row_starts(args)) {
+                        hipLaunchKernelGGL((k_spmm_split<LPR, VEC, GCN_EPI_MASK, false, ZERO>), grid, block, pad, s, args);
+                        break;
+                    }
                 }
-            }
-            hipLaunchKernelGGL((k_spmm_split<LPR, VEC, GCN_EPI_MASK>), grid, block, pad, s, args);
-            break;
-    }
+                hipLaunchKernelGGL((k_spmm_split<LPR, VEC, GCN_EPI_MASK, true, ZERO>), grid, block, pad, s, args);
+                break;
+        }
+    };
+    timing_begin(s);
+    if (args.empty_share > 0) go(std::true_type());
+    else go(std::false_type());
     timing_end(s);
     GCN_LAUNCH_CHECK();
     return fixup_of<LPR, VEC>(args, epilogue, s);
