@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "common.h"
+#include "copy_rule.h"
 
 namespace gcn {
 
@@ -410,19 +411,28 @@ __global__ __launch_bounds__(CopyArgs::THREADS) void k_copy_arrays(CopyArgs a) {
     if (at < g.words) ((uint32_t*)(dst + g.pieces))[at] = ((const uint32_t*)(src + g.pieces))[at];
 }
 
-// Whether a kernel can write `bytes` at p, in 16-byte pieces.  Everything else (memory of the host or of another GPU, a range that no one
-// allocation holds, an odd address) is the runtime's copy, which takes or refuses it.
-static bool kernel_may_write(void* p, size_t bytes) {
-    if ((uintptr_t)p % 16 != 0) return false;
-    hipPointerAttribute_t of;
+// What kernel_copies asks of the runtime.
+static MemoryOf memory_of(const void* p) {
+    MemoryOf of;
+    hipPointerAttribute_t what;
     hipDeviceptr_t base = nullptr;
     size_t size = 0;
-    if (hipPointerGetAttributes(&of, p) != hipSuccess || of.type != hipMemoryTypeDevice || of.device != current_device() ||
+    if (hipPointerGetAttributes(&what, p) != hipSuccess || what.type != hipMemoryTypeDevice ||
         hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) != hipSuccess) {
         (void)hipGetLastError();
-        return false;
+        return of;
     }
-    return (char*)p + bytes <= (char*)base + size;
+    of.device = true;
+    of.gpu = what.device;
+    of.base = (uintptr_t)base;
+    of.size = size;
+    return of;
+}
+static int device_of(hipStream_t s) {
+    if (!s) return current_device();
+    hipDevice_t dev = -1;
+    if (hipStreamGetDevice(s, &dev) != hipSuccess) (void)hipGetLastError();
+    return (int)dev;
 }
 
 extern "C" {
@@ -595,10 +605,11 @@ int gcn_csr_export(const gcn_csr* a, int transposed, int64_t* rowptr, int32_t* c
     if (transposed && !a->has_t) return fail(GCN_ERR_NOTRANSPOSE, "matrix was built without GCN_BUILD_TRANSPOSE");
     const Matrix& m = matrix_of(a, transposed);
     hipStream_t s = (hipStream_t)stream;
+    const int current = current_device(), runs_on = device_of(s);
     CopyArgs copy;
     auto add = [&](void* dst, const void* src, size_t bytes) -> int {
         if (!dst || !bytes) return GCN_OK;
-        if (kernel_may_write(dst, bytes)) copy.add(dst, src, bytes);
+        if (kernel_copies(a->device, current, runs_on, memory_of(dst), (uintptr_t)dst, bytes)) copy.add(dst, src, bytes);
         else GCN_HIP_TRY(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, s));
         return GCN_OK;
     };

@@ -372,3 +372,29 @@ def test_estimated_rounding_errors(tmp_path):
         }
     """)
     assert r.returncode == 0 and r.stdout == "done", (r.returncode, r.stdout, r.stderr)
+
+
+def test_a_kernel_copies_only_on_the_matrix_own_gpu(tmp_path):
+    """An export by a kernel: the matrix, the destination and the stream on the current GPU, the whole range in one allocation and a multiple
+    of 16 bytes; a matrix of another GPU, whose memory a kernel there may not reach, goes the runtime's way."""
+    r = run_cpp(tmp_path, """
+        #include <cstdio>
+        #include <initializer_list>
+        #include "copy_rule.h"
+        using namespace gcn;
+        int main() {
+            const MemoryOf here{true, 0, 4096, 1024}, there{true, 1, 4096, 1024}, host{false, -1, 0, 0};
+            std::printf("%d%d%d%d ", kernel_copies(0, 0, 0, here, 4096, 1024), kernel_copies(1, 1, 1, there, 4096, 1024), kernel_copies(0, 0, 0, here, 4112, 1008),
+                        kernel_copies(0, 0, 0, here, 5120, 0));
+            int other = 0;                                    // any of the four on another GPU
+            for (int m = 0; m < 2; ++m)
+                for (int c = 0; c < 2; ++c)
+                    for (int s = -1; s < 2; ++s)
+                        for (const MemoryOf& of : {here, there})
+                            if (!(m == c && c == s && s == of.gpu)) other += kernel_copies(m, c, s, of, 4096, 64);
+            std::printf("%d ", other);
+            std::printf("%d%d%d%d%d%d", kernel_copies(0, 0, 0, host, 4096, 64), kernel_copies(0, 0, 0, here, 4100, 64), kernel_copies(0, 0, 0, here, 4096, 1025),
+                        kernel_copies(0, 0, 0, here, 4112, 1024), kernel_copies(0, 0, 0, here, 4080, 16), kernel_copies(0, 0, 0, here, 4112, ~(size_t)0));
+        }
+    """)
+    assert r.returncode == 0 and r.stdout == "1111 0 000000", (r.returncode, r.stdout, r.stderr)
