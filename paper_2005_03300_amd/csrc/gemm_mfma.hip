@@ -11,6 +11,7 @@
 // Operand layout of the 16x16x4 instruction (64 lanes): lane l supplies A[i = l%16][k = l/16] and
 // B[k = l/16][j = l%16], and holds D[i = 4*(l/16) + v][j = l%16] in element v of its accumulator.
 #include "common.h"
+#include "launch_rules.h"
 #include "sum_parts.h"
 
 namespace gcn {
@@ -939,14 +940,13 @@ int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const floa
         // longer than the rest (32 x 23 on 2.4 M 201 and 157; with one tile four take 1.03 of the time, with three 1.07), or of 16 bytes while
         // operand and result are in the memory-side cache (32 x 32 on 400 K 20.6 and 18.5, on 820 K 37.0 and 34.4; on 1.8 M
         // 98 and 105).
-        // Four where that leaves no compute unit without a workgroup that eight would (16384 rows: 64 x 16 4.4 -> 4.1 us, 128 x 16 5.6 -> 5.4,
-        // 256 x 64 14.1 -> 12.4; 40 K: 256 x 64 24.8 -> 26.2).
-        const int waves = ntiles <= 8 * (int64_t)device_info().cus ? 4 : 8;
+        const int64_t panels = (nt_total + NT - 1) / NT;
+        const int waves = tall_waves(ntiles, panels, K, device_info().cus);
         int64_t bx = (ntiles + waves - 1) / waves;
         const bool four = NT == 2 && lds <= 40 * 1024 && (!wide_c || M * (K + N) * 4 < (192ll << 20));
         const int64_t cap = (int64_t)device_info().cus * (lds > 80 * 1024 ? 1 : (four ? 4 : 2));
         if (bx > cap) bx = cap;
-        const dim3 grid((unsigned)bx, (unsigned)((nt_total + NT - 1) / NT));
+        const dim3 grid((unsigned)bx, (unsigned)panels);
         switch (NT) {
             case 1: launch_tall<1>(args, epilogue, grid, 64 * waves, lds, s); break;
             case 2: launch_tall<2>(args, epilogue, grid, 64 * waves, lds, s); break;

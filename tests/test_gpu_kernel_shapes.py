@@ -962,7 +962,8 @@ def test_spmm_short_rows_at_equal_pitch(longest, f):
     a.close()
 
 
-@pytest.mark.parametrize("K,N,M", [(100, 16, 65_536), (300, 16, 195_740), (64, 32, 917_504), (128, 32, 40_000), (64, 16, 32_768), (16, 8, 32_784)])
+@pytest.mark.parametrize("K,N,M", [(100, 16, 65_536), (300, 16, 195_740), (64, 32, 917_504), (128, 32, 40_000), (64, 16, 32_768), (16, 8, 32_784),
+                                   (64, 16, 14_336), (256, 64, 14_336), (500, 24, 8192), (602, 64, 5000)])
 def test_gemm_nn_on_both_sides_of_its_rules(K, N, M):
     """Row counts at which the product goes to another kernel or to workgroups of another size: the first rows keep their bits, the last ones are
     what 64 bits give."""

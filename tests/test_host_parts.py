@@ -398,3 +398,26 @@ def test_a_kernel_copies_only_on_the_matrix_own_gpu(tmp_path):
         }
     """)
     assert r.returncode == 0 and r.stdout == "1111 0 000000", (r.returncode, r.stdout, r.stderr)
+
+
+def test_workgroups_of_dense_products_read_the_second_operand_once_per_compute_unit(tmp_path):
+    """Four wavefronts only where all workgroups of four are resident at once: the sizes on both sides of the rule that were timed, among them
+    those where four took up to twice as long."""
+    r = run_cpp(tmp_path, """
+        #include <cstdio>
+        #include <initializer_list>
+        #include "launch_rules.h"
+        int main() {
+            struct { int rows, panels, k, waves; } timed[] = {
+                {1000, 1, 16, 4}, {5000, 1, 128, 4}, {14000, 1, 256, 4}, {14336, 1, 300, 4}, {14352, 1, 300, 8}, {20000, 1, 300, 8}, {32768, 1, 64, 8},
+                {5000, 1, 500, 4}, {8192, 1, 500, 4}, {10000, 1, 500, 8}, {16384, 1, 602, 8}, {9000, 2, 602, 8}, {3000, 2, 1200, 8}, {1000, 1, 1900, 8},
+                {5000, 4, 300, 8}, {5000, 2, 300, 4}, {1, 1, 1, 4}, {14249639, 1, 300, 8}};
+            for (auto& t : timed) std::printf("%d", (int)(gcn::tall_waves((t.rows + 15) / 16, t.panels, t.k, 256) == t.waves));
+            for (int cus : {1, 8, 64, 256, 304})                // never more workgroups than compute units
+                for (long long strips = 1; strips < 4 * cus + 9; ++strips)
+                    for (int panels = 1; panels < 7; ++panels)
+                        for (int k : {1, 400, 401, 640, 641})
+                            if (gcn::tall_waves(strips, panels, k, cus) == 4 && (strips + 3) / 4 * panels > cus) std::printf("bad");
+        }
+    """)
+    assert r.returncode == 0 and r.stdout == "1" * 18, (r.returncode, r.stdout, r.stderr)
