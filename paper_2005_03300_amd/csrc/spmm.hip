@@ -21,6 +21,7 @@
 #include <string>
 
 #include "common.h"
+#include "launch_rules.h"
 
 namespace gcn {
 
@@ -1837,15 +1838,15 @@ static SpmmPlan& plan_of(gcn_csr* a, Matrix& m, int32_t f, Terms terms, int64_t 
     return m.plans.back();
 }
 
-// The rows without entries go with the chunks of the product, in equal shares, where there is a list of them and a chunk gets no more
-// of them than it has entries.  Not k_spmm_ragged, whose matrices are small, nor k_spmm_line<2>, whose registers they cost a wavefront.
+// The rows without entries go with the chunks of the product, in equal shares, where there is a list of them and share_of_empty_rows says
+// so.  Not k_spmm_ragged, whose matrices are small, nor k_spmm_line<2>, whose registers they cost a wavefront.
 static bool share_empty_rows(SplitArgs* args, const Matrix& m, const SplitChoice& c) {
+    if (!m.empty_rows || c.kernel == SplitChoice::RAGGED || (c.kernel == SplitChoice::LINE && c.vec == 2)) return false;
     const int64_t n_empty = m.nrows - m.n_ne;
-    if (!m.empty_rows || n_empty > m.nchunks * CHUNK) return false;
-    if (c.kernel == SplitChoice::RAGGED || (c.kernel == SplitChoice::LINE && c.vec == 2)) return false;
+    args->empty_share = share_of_empty_rows(m.nrows, n_empty, m.nchunks, CHUNK, c.lpr, c.vec, args->f, args->ldz, (uintptr_t)args->Z);
+    if (args->empty_share == 0) return false;
     args->empty_rows = m.empty_rows;
     args->n_empty = n_empty;
-    args->empty_share = (int32_t)((n_empty + m.nchunks - 1) / m.nchunks);
     return true;
 }
 

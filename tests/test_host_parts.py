@@ -421,3 +421,34 @@ def test_workgroups_of_dense_products_read_the_second_operand_once_per_compute_u
         }
     """)
     assert r.returncode == 0 and r.stdout == "1" * 18, (r.returncode, r.stdout, r.stderr)
+
+
+def test_empty_rows_go_with_the_chunks_only_where_that_was_faster(tmp_path):
+    """Products of random matrices timed with a launch that zeroes the rows without entries and with a share of them for every chunk: the rule
+    shares where that took less, and not where it took longer, by up to a half; all rows are in some chunk's share."""
+    r = run_cpp(tmp_path, """
+        #include <cstdio>
+        #include "launch_rules.h"
+        using gcn::share_of_empty_rows;
+        int main() {
+            struct { long long n, n_empty, chunks; int lpr, vec, f; double launch, share; } timed[] = {      // microseconds
+                {3000, 136, 20, 16, 4, 64, 1, 1}, {3000, 1807, 13, 4, 4, 16, 12.9, 12.0}, {20000, 12080, 86, 8, 4, 128, 21.9, 20.0}, {20000, 12080, 86, 8, 4, 64, 18.7, 17.9},
+                {3000, 2096, 8, 8, 4, 64, 18.1, 19.2}, {3000, 2096, 8, 32, 1, 31, 35.4, 42.4}, {150001, 119922, 506, 32, 1, 31, 41.9, 45.9}, {400000, 238680, 1755, 32, 1, 31, 57.2, 53.1},
+                {20000, 18576, 86, 32, 1, 31, 25.1, 30.9}, {60000, 48000, 199, 32, 1, 31, 35.2, 43.1}, {1000000, 300000, 6285, 32, 1, 31, 161.8, 161.9}, {400000, 238680, 1755, 64, 1, 41, 62.8, 63.4},
+                {400000, 197550, 2195, 64, 1, 41, 70.4, 74.3}, {1000000, 696210, 5045, 64, 1, 41, 160.5, 149.6}, {60000, 47959, 199, 8, 4, 128, 27.5, 25.1}, {1000000, 696210, 5045, 8, 4, 64, 165.1, 149.6},
+                {1000000, 300000, 7661, 8, 4, 300, 1551, 1701}, {1000000, 800000, 3356, 8, 4, 300, 904, 1294}, {1000000, 800000, 3356, 8, 4, 100, 334, 461}, {2000000, 1200000, 8754, 8, 4, 36, 350, 396},
+                {400000, 280000, 2014, 8, 4, 36, 73.1, 77.5}, {150001, 105000, 757, 8, 4, 200, 110.5, 116.3}, {3000, 600, 27, 8, 4, 300, 18.7, 16.6}, {20000, 10000, 108, 8, 4, 100, 21.6, 20.2},
+                {1000000, 300000, 6285, 8, 4, 128, 355.8, 339.9}, {1000000, 800000, 3356, 8, 4, 160, 330.9, 283.1}, {1000000, 800000, 3356, 8, 4, 20, 72.9, 71.6},
+                {3000000, 2250001, 1500, 4, 4, 16, 1, 2}};                     // more of them than entries
+            for (auto& t : timed) {
+                const int share = share_of_empty_rows(t.n, t.n_empty, t.chunks, 512, t.lpr, t.vec, t.f, t.f, 1 << 20);
+                if (share && (share > 512 || share * t.chunks < t.n_empty)) std::printf("lost ");
+                std::printf("%d", (int)((share > 0) == (t.share <= t.launch * 1.001)));
+            }
+            const long long n = 1000000, e = 800000;
+            std::printf(" %d%d%d%d%d", share_of_empty_rows(n, 0, 10, 512, 8, 4, 16, 16, 0), share_of_empty_rows(n, 5, 0, 512, 8, 4, 16, 16, 0),
+                        share_of_empty_rows(n, e, 3356, 512, 8, 4, 128, 132, 1 << 20), share_of_empty_rows(n, e, 3356, 512, 8, 4, 128, 128, 16),
+                        share_of_empty_rows(n, 10, 10, 512, 8, 4, 16, 17, 4));
+        }
+    """)
+    assert r.returncode == 0 and r.stdout == "1" * 28 + " 00001", (r.returncode, r.stdout, r.stderr)
