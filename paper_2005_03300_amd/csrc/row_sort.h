@@ -5,9 +5,13 @@
 // column), a workgroup sorts a bucket in LDS and drops the repeated keys, and one last pass writes columns and row pointers.  A
 // radix sort of the 8-byte keys (prims.h), which takes over where this does not fit, reads and writes them once per 8 bits and
 // once more to drop the repeated ones.  16.8 M pairs of 1 M vertices, R-MAT (34.6 M keys): 1.35 ms that way; here counting 63 us,
-// scatter 132, sort 288, columns and row pointers 84 (100 with the schedule's words).  Whole constructions, symmetrised: uniform 20 M pairs of 100 K vertices 2.11 ->
-// 1.01 ms, 14 M of 3.9 M 2.17 -> 1.20; R-MAT 38 M of 1 M 3.98 -> 2.18; 100 K pairs of 10 K 0.31 -> 0.23.  Entries that lie in a few
-// buckets are refused after the counting, which costs such constructions 4 to 9 % (8 M pairs of one vertex 1.02 -> 1.10 ms).
+// scatter 132, sort 288, columns and row pointers 84 (100 with the schedule's words).  Whole constructions, symmetrised: uniform
+// 20 M pairs of 100 K vertices 2.11 -> 1.01 ms, 14 M of 3.9 M 2.17 -> 1.20; R-MAT 38 M of 1 M 3.98 -> 2.18; 100 K pairs of 10 K
+// 0.31 -> 0.23.
+// It fits up to 4096 buckets, of 2^(32 - bits of a column) rows at the most: 4,194,304 vertices and 83 M keys.  Larger graphs take the
+// radix sort from the start.  Entries that lie in a few buckets are refused after the counting; that and the kernels behind it,
+// which then do nothing, cost such constructions 30 to 100 us (pairs of one vertex: 32 K 286 -> 310 us, 400 K 373 -> 438, 8 M 835 -> 932,
+// 16.8 M 1689 -> 1774; 2 M power-law pairs of 700 vertices 344 -> 403).
 #pragma once
 #include "common.h"
 
@@ -291,7 +295,7 @@ __device__ __forceinline__ void load_bucket(const SortArgs& a, const Task& t, ui
     }
 }
 
-// Those of a piece: returns how many there are (0, and the task is done, where that is more than CAP) and where they begin.
+// Those of a piece: returns how many there are, up to CAP, and where they begin.
 __device__ __forceinline__ uint32_t fetch_piece(const SortArgs& a, uint32_t id, const Task& t, uint32_t* s_key, uint32_t* s_slot, SortLds& L,
                                                 uint32_t (&key)[KEYS], uint32_t& from) {
     const int lane = threadIdx.x & 63;
@@ -376,6 +380,15 @@ __device__ __forceinline__ uint32_t fetch_piece(const SortArgs& a, uint32_t id, 
     __syncthreads();
     const uint32_t low = L.bound[0], high = L.bound[1];
     from += L.below[0];
+    // More keys than are sorted together: the last prefix has thousands, nearly all of them repeated (sh2 is 8 at the most).  A bit for each of
+    // its keys says which are there, and that is all that is wanted of them; the other prefixes hold a PIECE at the most.
+    const bool crowded = L.below[1] - L.below[0] > CAP;         // (the same for all)
+    uint32_t* const s_bit = s_slot;
+    static_assert(PIECE + (1 << (32 - 2 * BIN_BITS)) <= CAP, "a piece and the keys of a prefix");
+    if (crowded) {
+        if (threadIdx.x < (1u << (32 - 2 * BIN_BITS)) / 32) s_bit[threadIdx.x] = 0;
+        __syncthreads();
+    }
     for (uint32_t j0 = 0; j0 < size; j0 += AT_ONCE * THREADS) {
         uint32_t x[AT_ONCE];
 #pragma unroll
@@ -388,7 +401,13 @@ __device__ __forceinline__ uint32_t fetch_piece(const SortArgs& a, uint32_t id, 
 #pragma unroll
         for (int e = 0; e < AT_ONCE; ++e) {
             const uint32_t prefix = x[e] >> sh2;
-            who[e] = __ballot(j0 + e * THREADS + threadIdx.x < size && prefix >= low && prefix < high);
+            bool mine = j0 + e * THREADS + threadIdx.x < size && prefix >= low && prefix < high;
+            if (crowded && mine && prefix == high - 1) {
+                const uint32_t bit = x[e] & ((1u << sh2) - 1u);
+                if (!(s_bit[bit / 32] >> bit % 32 & 1u)) atomicOr(&s_bit[bit / 32], 1u << bit % 32);
+                mine = false;
+            }
+            who[e] = __ballot(mine);
             found += (uint32_t)__popcll(who[e]);
         }
         uint32_t base = 0;
@@ -396,17 +415,16 @@ __device__ __forceinline__ uint32_t fetch_piece(const SortArgs& a, uint32_t id, 
         base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
 #pragma unroll
         for (int e = 0; e < AT_ONCE; ++e) {
-            const uint32_t to = base + lanes_below(who[e]);
-            if ((who[e] >> lane & 1ull) && to < CAP) s_key[to] = x[e];
+            if (who[e] >> lane & 1ull) s_key[base + lanes_below(who[e])] = x[e];
             base += (uint32_t)__popcll(who[e]);
         }
     }
     __syncthreads();
-    const uint32_t here = L.count;
-    if (here > CAP) {                                           // one prefix has thousands of keys
-        if (threadIdx.x == 0) { a.info->refused = 1; a.at_of[id] = from; a.count_of[id] = 0; }
-        return 0;
+    if (crowded) {
+        if (threadIdx.x < 1u << sh2 && s_bit[threadIdx.x / 32] >> threadIdx.x % 32 & 1u) s_key[atomicAdd(&L.count, 1u)] = (high - 1) << sh2 | threadIdx.x;
+        __syncthreads();
     }
+    const uint32_t here = L.count;
 #pragma unroll
     for (int k = 0; k < KEYS; ++k) {
         const uint32_t j = k * THREADS + threadIdx.x;
@@ -726,7 +744,7 @@ __global__ __launch_bounds__(THREADS) void k_part_sort_digits(SortArgs a) {
 // Where the entries of every task go: offset[task], from the numbers in count[task].
 __global__ __launch_bounds__(THREADS) void k_part_offsets(const uint32_t* __restrict__ count, uint32_t* __restrict__ offset, Info* __restrict__ info) {
     __shared__ uint32_t part[WAVES];
-    const uint32_t tasks = info->refused ? 0 : info->tasks;
+    const uint32_t tasks = info->tasks;                         // (none where the matrix is refused)
     uint32_t run = 0;
     for (uint32_t base = 0; base < tasks; base += THREADS) {
         const uint32_t t = base + threadIdx.x;
