@@ -496,7 +496,7 @@ static int entries_by_rows(gcn_csr* a, int64_t n, int64_t m, const int32_t* src,
     const Items items{src, dst, m, n, m + (loops ? n : 0), sym, cbits, shift};
     const int64_t share = (items.items + SHARES - 1) / SHARES;
     const size_t most_tasks = (size_t)nb + (size_t)(cap / PIECE) + 1;
-    TempBuf info, table, total, start, tasks, at, count, offset, order, crowded, k0, k1;
+    TempBuf info, table, total, start, tasks, at, count, offset, order, crowded, keys32;
     GCN_TRY(info.alloc(sizeof(Info)));
     GCN_TRY(table.alloc((size_t)SHARES * nb * 4));
     GCN_TRY(total.alloc((size_t)nb * 4));
@@ -507,8 +507,10 @@ static int entries_by_rows(gcn_csr* a, int64_t n, int64_t m, const int32_t* src,
     GCN_TRY(offset.alloc(most_tasks * 4));
     GCN_TRY(order.alloc(most_tasks * 4));
     GCN_TRY(crowded.alloc(most_tasks * 4));
-    GCN_TRY(k0.alloc((size_t)cap * 4));
-    GCN_TRY(k1.alloc((size_t)cap * 4));
+    // Both sides of the sort in one block of 8 bytes per key: where the matrix is refused the radix sort takes it for its own keys (two
+    // blocks it could not use raised the peak of such a construction from 16 to 24 bytes per key).
+    GCN_TRY(keys32.alloc((size_t)cap * 8));
+    uint32_t* const k0 = keys32.as<uint32_t>(), * const k1 = k0 + cap;
     GCN_HIP_TRY(hipMemsetAsync(info.p, 0, sizeof(Info), s));
     hipLaunchKernelGGL(k_part_count, dim3(SHARES), dim3(THREADS), 0, s, items, share, nb, table.as<uint32_t>(), info.as<Info>());
     GCN_LAUNCH_CHECK();
@@ -518,9 +520,9 @@ static int entries_by_rows(gcn_csr* a, int64_t n, int64_t m, const int32_t* src,
                        order.as<uint32_t>(), info.as<Info>());
     GCN_LAUNCH_CHECK();
     launch_lds<k_part_scatter>(dim3(SHARES), THREADS, SCATTER_LDS, s, items, share, nb, (const uint32_t*)start.as<uint32_t>(),
-                               (const uint32_t*)table.as<uint32_t>(), (const Info*)info.as<Info>(), k0.as<uint32_t>());
+                               (const uint32_t*)table.as<uint32_t>(), (const Info*)info.as<Info>(), k0);
     GCN_LAUNCH_CHECK();
-    const SortArgs sort{cbits, shift, tasks.as<Task>(), order.as<uint32_t>(), k0.as<uint32_t>(), k1.as<uint32_t>(), at.as<uint32_t>(),
+    const SortArgs sort{cbits, shift, tasks.as<Task>(), order.as<uint32_t>(), k0, k1, at.as<uint32_t>(),
                         count.as<uint32_t>(), crowded.as<uint32_t>(), info.as<Info>()};
     launch_lds<k_part_sort>(dim3((unsigned)most_tasks), THREADS, sort_lds(shift), s, sort);
     GCN_LAUNCH_CHECK();
@@ -538,7 +540,7 @@ static int entries_by_rows(gcn_csr* a, int64_t n, int64_t m, const int32_t* src,
     if (want_keys) GCN_TRY(keys.alloc((size_t)h.kept * 8));
     GCN_TRY(alloc_subs(a->A, h.kept, s));
     hipLaunchKernelGGL(k_part_emit, dim3(h.tasks), dim3(512), 0, s, n, nb, cbits, shift, (const Task*)tasks.as<Task>(), (const uint32_t*)at.as<uint32_t>(),
-                       (const uint32_t*)count.as<uint32_t>(), (const uint32_t*)offset.as<uint32_t>(), (const uint32_t*)k1.as<uint32_t>(), a->A.rowptr,
+                       (const uint32_t*)count.as<uint32_t>(), (const uint32_t*)offset.as<uint32_t>(), (const uint32_t*)k1, a->A.rowptr,
                        a->A.colidx, want_keys ? keys.as<uint64_t>() : nullptr, a->A.flags, a->A.sub_row);
     GCN_LAUNCH_CHECK();
     *done = true;

@@ -125,3 +125,15 @@ def test_a_pair_that_fills_a_piece_is_no_reason_to_sort_again():
     assert sp.plan(n, src, dst, False, False)["crowded"] == 1
     held = held_per_key(G(), n, src, dst)
     assert 16 < held < 27, held
+
+
+@pytest.mark.gpu
+def test_a_refused_construction_reuses_the_keys():
+    """Pairs of one vertex, refused after the counting: the radix sort's two arrays of 64-bit keys (16 bytes per pair) and little else, with the
+    first attempt's arrays among them."""
+    rs = np.random.default_rng(163)
+    n, m = 1 << 20, 1 << 23
+    src, dst = np.full(m, 3), rs.integers(0, n, m)
+    assert sp.plan(n, src, dst, False, False) == "refused"
+    held = held_per_key(G(), n, src, dst)
+    assert 16 < held < 23, held
