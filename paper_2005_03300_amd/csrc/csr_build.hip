@@ -516,7 +516,7 @@ static int entries_by_rows(gcn_csr* a, int64_t n, int64_t m, const int32_t* src,
     GCN_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_part_shares, dim3((nb + 63) / 64), dim3(THREADS), 0, s, nb, table.as<uint32_t>(), total.as<uint32_t>());
     GCN_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_part_tasks, dim3(1), dim3(THREADS), 0, s, nb, (uint64_t)cap * 2, total.as<uint32_t>(), start.as<uint32_t>(), tasks.as<Task>(),
+    hipLaunchKernelGGL(k_part_tasks, dim3(1), dim3(THREADS), 0, s, nb, (uint64_t)cap * MOST_AGAIN, total.as<uint32_t>(), start.as<uint32_t>(), tasks.as<Task>(),
                        order.as<uint32_t>(), info.as<Info>());
     GCN_LAUNCH_CHECK();
     launch_lds<k_part_scatter>(dim3(SHARES), THREADS, SCATTER_LDS, s, items, share, nb, (const uint32_t*)start.as<uint32_t>(),

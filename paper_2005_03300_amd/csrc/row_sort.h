@@ -29,6 +29,9 @@ constexpr uint32_t PIECE = CAP / 6 * 5;            // larger buckets are cut int
 constexpr unsigned BIN_BITS = 12;                  // of the histograms that say where
 constexpr int BINS = 1 << BIN_BITS;
 constexpr int SHARES = 256;                        // workgroups that count and scatter
+// Keys that the pieces of cut buckets read, of all keys: with more the matrix is refused.  With 2 8 M power-law pairs of 100 K vertices were
+// refused (982 us, now 834; 943 by keys), with 8 2 M of 700 were not (536; refused 398).
+constexpr uint64_t MOST_AGAIN = 4;
 
 // The items that make keys: the pairs, then the diagonal.  A pair of equal ends makes none: with self loops the diagonal's key is
 // there anyway.  *bad is set where an id is outside [0, n); such a pair makes no key either.

@@ -15,12 +15,13 @@ def constant(text, name):
 ROW_SORT, PRIMS = (open(os.path.join(CSRC, f)).read() for f in ("row_sort.h", "prims.h"))
 THREADS, KEYS, MAX_BUCKETS, MAX_SHIFT, BIN_BITS, SHARES = (
     constant(ROW_SORT, c) for c in ("THREADS", "KEYS", "MAX_BUCKETS", "MAX_SHIFT", "BIN_BITS", "SHARES"))
-MOST_IN_WINDOW, MOST_BY_RANK, MOST_RANKED = (constant(ROW_SORT, c) for c in ("MOST_IN_WINDOW", "MOST_BY_RANK", "MOST_RANKED"))
+MOST_IN_WINDOW, MOST_BY_RANK, MOST_RANKED, MOST_AGAIN = (
+    constant(ROW_SORT, c) for c in ("MOST_IN_WINDOW", "MOST_BY_RANK", "MOST_RANKED", "MOST_AGAIN"))
 CAP = KEYS * THREADS
 PIECE = CAP // 6 * 5
 ROOM = CAP // 100 * 83
 RS_TILE = constant(PRIMS, "P_TPB") * constant(PRIMS, "RS_ROUNDS")
-for rule in ("PIECE = CAP / 6 * 5;", "ROOM = CAP / 100 * 83;", "(uint64_t)cap * 2,", "CAP = KEYS * THREADS;"):
+for rule in ("PIECE = CAP / 6 * 5;", "ROOM = CAP / 100 * 83;", "(uint64_t)cap * MOST_AGAIN,", "CAP = KEYS * THREADS;"):
     assert rule in ROW_SORT + open(os.path.join(CSRC, "csr_build.hip")).read(), rule
 
 
@@ -49,7 +50,7 @@ def large_places(keys, cbits):
 
 def plan(n, src, dst, symmetrise, loops):
     """None where the bucket sort does not take the sizes, "refused" where it refuses the buckets, else what its tasks are: sizes of the buckets
-    that are not cut, pieces, pieces with a crowded prefix, tasks sorted by digits (and those of them that are pieces), places put in order
+    that are not cut, keys that pieces read (of all keys), pieces, pieces with a crowded prefix, tasks sorted by digits (and those of them that are pieces), places put in order
     by ranks."""
     cbits = max(1, int(n - 1).bit_length())
     cap = len(src) * (2 if symmetrise else 1) + (n if loops else 0)
@@ -67,11 +68,12 @@ def plan(n, src, dst, symmetrise, loops):
     ends = np.searchsorted(bucket, np.arange(buckets(shift) + 1))
     sizes = np.diff(ends)
     parts = np.where(sizes > CAP, (sizes + PIECE - 1) // PIECE, 1)
-    if int((parts * sizes)[parts > 1].sum()) > 2 * cap:
+    again = int((parts * sizes)[parts > 1].sum())
+    if again > MOST_AGAIN * cap:
         return "refused"
     d1 = min(shift + cbits, BIN_BITS)
     sh2 = shift + cbits - d1 - min(shift + cbits - d1, BIN_BITS)
-    found = dict(whole=set(), pieces=0, crowded=0, digits=0, digit_pieces=0, ranked=0)
+    found = dict(whole=set(), read_again=again / cap, pieces=0, crowded=0, digits=0, digit_pieces=0, ranked=0)
     for b in range(buckets(shift)):
         mine = keys[ends[b]:ends[b + 1]]
         prefix = mine >> sh2

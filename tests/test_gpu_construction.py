@@ -40,6 +40,9 @@ def case(kind, symmetrise, loops):
         src[:60_000] = 778
         src[60_000:61_500], dst[60_000:61_500] = 779, 400_000 + np.arange(1500)
         return n, src, dst, lambda p: p["digit_pieces"] == 1 and p["pieces"] == 4
+    if kind == "most_pieces":                    # nearly as many keys read again as are accepted
+        src[:140_000], dst[:140_000] = 780, rs.permutation(n)[:140_000]
+        return n, src, dst, lambda p: p["pieces"] >= 7 and (p["read_again"] > 3 or symmetrise or loops)
     if kind == "same":                           # one pair again and again, more often than keys are sorted together
         src[:60_000], dst[:60_000] = 5000, 9000
         return n, src, dst, lambda p: p["crowded"] >= 1
@@ -66,7 +69,7 @@ def case(kind, symmetrise, loops):
     return n, src, dst, lambda p: (size in p["whole"]) == (size <= sp.CAP) and p["pieces"] == (0 if size <= sp.CAP else 2)
 
 
-KINDS = ["run1500", "run8000", "run10000", "run_in_piece", "same", "same_each_end", "same_all_ones", "few_again"]
+KINDS = ["run1500", "run8000", "run10000", "run_in_piece", "most_pieces", "same", "same_each_end", "same_all_ones", "few_again"]
 KINDS += [f"bucket_{sp.CAP + d}_{again}" for d in (-1, 0, 1) for again in (1, 3)]
 
 
