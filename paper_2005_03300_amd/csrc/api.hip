@@ -363,8 +363,6 @@ void free_matrix(Matrix& m) {
     device_free(m.ne_rowptr);
     device_free(m.empty_rows);
     device_free(m.short_col);
-    device_free(m.short_val);
-    device_free(m.short_rows);
     device_free(m.fix_list);
     free_blocked(m.blk);
     free_sweep(m.swp);

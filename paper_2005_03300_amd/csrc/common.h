@@ -151,7 +151,7 @@ struct Matrix {
     Terms terms = Terms::UNKNOWN;
     std::vector<SpmmPlan> plans; // schedules chosen so far, one per width and kind of terms
     // Rows of equal pitch for the kernel of few and short rows (see build_short), or NULL.
-    int32_t* short_col = nullptr;   // [nrows][short_pitch] columns, 0 behind a row's last
+    int32_t* short_col = nullptr;   // [nrows][short_pitch] columns, 0 behind a row's last; the other two are of the same allocation
     float* short_val = nullptr;     // likewise
     int32_t* short_rows = nullptr;  // [nrows] entries of the row, and where they begin modulo CHUNK from bit 16 up
     int32_t short_pitch = 0;
@@ -357,7 +357,7 @@ void launch_lds(dim3 grid, int threads, size_t lds, hipStream_t s, const Args&..
     hipLaunchKernelGGL(Kernel, grid, dim3(threads), lds, s, args...);
 }
 
-int build_short(Matrix& m, hipStream_t s);       // once the values are there
+int build_short(Matrix& m, int64_t nnz, hipStream_t s);       // once the values are there
 int build_schedule(Matrix& m, int64_t n, int64_t nnz, hipStream_t s, int32_t* deg = nullptr);   // deg: also receives the row lengths
 // One record per row whose entries run on into further chunks: x, y = the first and the last of them, z = the row (its
 // index among the non-empty rows).  Rows that leave no row start in chunk x come first (n_long of them).

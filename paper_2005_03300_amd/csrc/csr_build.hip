@@ -15,6 +15,7 @@
 #include "common.h"
 #include "prims.h"
 #include "build_util.h"
+#include "launch_rules.h"
 #include "row_sort.h"
 
 namespace gcn {
@@ -445,19 +446,15 @@ __global__ __launch_bounds__(256) void k_short_rows(int64_t nrows, int32_t quads
 
 // A second copy of a matrix of few and short rows, at an equal pitch: a product on it is a chain of memory latencies, and this way the
 // indices need not wait for the row pointers (see k_spmm_short).  At most 33 MB.
-int build_short(Matrix& m, hipStream_t s) {
+int build_short(Matrix& m, int64_t nnz, hipStream_t s) {
     if (m.nrows * 2 > SHORT_LANES || m.max_degree > SHORT_ROW || m.max_degree == 0) return GCN_OK;
     const int32_t quads = (m.max_degree + 3) / 4;
     const int64_t threads = m.nrows * quads;
     m.short_pitch = 4 * quads;
-    if (device_alloc_t(&m.short_col, (size_t)threads * 4) != GCN_OK || device_alloc_t(&m.short_val, (size_t)threads * 4) != GCN_OK ||
-        device_alloc_t(&m.short_rows, (size_t)m.nrows) != GCN_OK) {
-        device_free(m.short_col);                              // without it the other kernels run
-        device_free(m.short_val);
-        m.short_col = nullptr;
-        m.short_val = nullptr;
-        return GCN_OK;
-    }
+    if (!short_copy_pays(m.nrows, m.short_pitch, nnz, m.lengths.from(4).count())) return GCN_OK;
+    if (device_alloc_t(&m.short_col, (size_t)threads * 8 + m.nrows) != GCN_OK) return GCN_OK;       // without it the other kernels run
+    m.short_val = (float*)(m.short_col + threads * 4);
+    m.short_rows = m.short_col + threads * 8;
     hipLaunchKernelGGL(k_short_rows, dim3(blocks_for(threads)), dim3(TPB), 0, s, m.nrows, quads, m.rowptr, m.colidx, m.val, (int4*)m.short_col,
                        (float4*)m.short_val, m.short_rows);
     GCN_LAUNCH_CHECK();
@@ -479,7 +476,7 @@ static int build_transpose(gcn_csr* a, const uint64_t* keys, unsigned cbits, uin
                        a->At.rowptr, a->At.colidx);
     GCN_LAUNCH_CHECK();
     GCN_TRY(build_schedule(a->At, n, nnz, s));
-    GCN_TRY(build_short(a->At, s));
+    GCN_TRY(build_short(a->At, nnz, s));
     a->has_t = true;
     return GCN_OK;
 }
@@ -626,7 +623,7 @@ static int create_impl(gcn_csr* a, int64_t n, int64_t m, const int32_t* src, con
         GCN_TRY(device_alloc_t(&a->inv_sqrt_deg, (size_t)n));
         GCN_TRY(inv_sqrt_deg_launch(n, a->deg, a->inv_sqrt_deg, s));
     }
-    GCN_TRY(build_short(a->A, s));
+    GCN_TRY(build_short(a->A, nnz, s));
     if (a->symmetric) a->has_t = true;
     else if (transpose) {
         TempBuf sorted;
@@ -678,7 +675,7 @@ static int from_csr_impl(gcn_csr* a, int64_t n, int64_t ncols, const int64_t* ro
         if (hbad) return fail(GCN_ERR_UNSORTED, "gcn_csr_create_from_csr: columns must be strictly ascending per row and inside [0,n)");
     }
     GCN_TRY(build_schedule(a->A, n, nnz, s, a->deg));
-    GCN_TRY(build_short(a->A, s));
+    GCN_TRY(build_short(a->A, nnz, s));
     if (flags & GCN_BUILD_TRANSPOSE) {
         GCN_TRY(k1.alloc((size_t)nnz * 8));
         GCN_TRY(build_transpose(a, keys.as<uint64_t>(), cbits, k1.as<uint64_t>(), s));

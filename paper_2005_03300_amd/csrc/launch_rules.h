@@ -43,4 +43,13 @@ inline int share_of_empty_rows(int64_t rows, int64_t n_empty, int64_t nchunks, i
     return whole || rows * ldz <= (8 << 20) || (stores <= 10 && rows * ldz <= (64 << 20)) ? (int)share : 0;
 }
 
+// Whether a matrix of short rows gets a copy at an equal pitch for k_spmm_short (see build_short).  Not where the copy is beyond the L2s (3 M
+// places of 8 bytes), more than half padding, and rows of 16 entries and more are in most wavefronts of that kernel (32 rows at the
+// widths that take so many), so that all of its lanes walk as far as these: rows of 0 to 64 entries of which most are
+// short, 5 to 7 columns, against k_spmm_split: 60 K of mean 12.5 15.7 -> 13.1 us, of mean 21 18.0 -> 15.1, 52 K 13.8 -> 13.0; but 44 K
+// (12.7 us) and 60 K of mean 5 with one long row (10.4) stay.
+inline bool short_copy_pays(int64_t rows, int64_t pitch, int64_t nnz, int64_t rows_of_16) {
+    return rows * pitch <= (3 << 20) || 2 * rows * pitch <= 5 * nnz || rows_of_16 * 32 < rows;
+}
+
 }  // namespace gcn

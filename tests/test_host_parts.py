@@ -452,3 +452,19 @@ def test_empty_rows_go_with_the_chunks_only_where_that_was_faster(tmp_path):
         }
     """)
     assert r.returncode == 0 and r.stdout == "1" * 28 + " 00001", (r.returncode, r.stdout, r.stderr)
+
+
+def test_a_padded_copy_of_short_rows_is_made_where_its_kernel_was_faster(tmp_path):
+    """Matrices of 60 K short rows and fewer timed with the kernel of equal pitch and with the nonzero split."""
+    r = run_cpp(tmp_path, """
+        #include <cstdio>
+        #include "launch_rules.h"
+        int main() {
+            struct { int rows, pitch; long long nnz; int rows_of_16; double padded, split; } timed[] = {      // microseconds
+                {60000, 64, 750000, 17700, 15.7, 13.1}, {60000, 64, 1272000, 30100, 18.0, 15.1}, {65500, 64, 831850, 19300, 16.7, 13.5}, {52000, 64, 655200, 15300, 13.8, 13.0},
+                {44000, 64, 550000, 13000, 12.7, 13.6}, {32000, 64, 403200, 9400, 9.9, 12.3}, {60000, 64, 300060, 1, 10.4, 13.1}, {60000, 64, 3840000, 60000, 26.3, 37.3},
+                {60000, 64, 1920000, 45000, 20.7, 21.2}, {60000, 20, 1020000, 60000, 10.8, 11.8}, {60000, 4, 180000, 0, 4.9, 6.7}, {1, 4, 1, 0, 1, 2}};
+            for (auto& t : timed) std::printf("%d", (int)(gcn::short_copy_pays(t.rows, t.pitch, t.nnz, t.rows_of_16) == (t.padded < t.split)));
+        }
+    """)
+    assert r.returncode == 0 and r.stdout == "1" * 12, (r.returncode, r.stdout, r.stderr)
