@@ -25,20 +25,20 @@ inline int tall_waves(int64_t strips, int64_t panels, int64_t k, int64_t cus) {
 // at the rate of the memory and costs a few microseconds.  A lane group of lpr lanes holds a row of a tile of lpr * vec columns.
 // Microseconds with a launch and with shares, random matrices:
 //  - No more than a chunk has entries.
-//  - The stores of a wavefront one after another (and their list, 64 rows at a time) must be short beside the product: up to 20
-//    they are (12.9 -> 12.0 with 139 rows of 16 floats, 21.9 -> 20.0 with 140 of 128), more only where there are
-//    wavefronts enough to hide them, 25 to a store (3000 rows of 64 18.1 -> 19.2 with 32 stores on 16 wavefronts; of 31 35.4 -> 42.4 with
-//    131 on 8, 41.9 -> 45.9 with 118 on 506, 57.2 -> 53.1 with 68 on 1755; of 41 70.4 -> 74.3 with 90 on 2195, 160.5 -> 149.6 with
-//    138 on 5045; of 128 27.5 -> 25.1 with 30 on 796).
+//  - The stores of a wavefront one after another, and their list, 64 rows at a time, must be short beside the product: up to 20
+//    stores of 240 rows they are (12.9 -> 12.0 with 139 rows of 16 floats, 21.9 -> 20.0 with 140 of 128; but masked 12.7 -> 13.9 with
+//    274 of 16), more only where there are wavefronts enough to hide them, 25 to a store (3000 rows of 64 18.1 -> 19.2 with 32
+//    stores on 16 wavefronts; of 31 35.4 -> 42.4 with 131 on 8, 41.9 -> 45.9 with 118 on 506, 57.2 -> 53.1 with 68 on 1755; of 41
+//    70.4 -> 74.3 with 90 on 2195, 160.5 -> 149.6 with 138 on 5045; of 128 27.5 -> 25.1 with 30 on 796).
 //  - Where a row is written tile by tile and the tiles are no whole lines, the pieces of a line must meet in a cache: results up to
-//    the L2s' 32 MB (18.0 -> 16.3 with 100 floats, 12 MB), or up to the 256 MB behind them with few such rows (400 K of 36: 11 stores 68.4 -> 69.0,
-//    17 73.1 -> 77.5).  1 M of 300, 0.3 to 0.8 of them empty, 1551 -> 1701 to 904 -> 1294, of 100 574 -> 595 to 334 -> 461; but of 128
-//    356 -> 340 to 268 -> 234, of 160 466 -> 434 to 331 -> 283.
+//    the L2s' 32 MB (18.0 -> 16.3 with 100 floats, 12 MB), or up to the 256 MB behind them with few such rows (400 K of 36: 11
+//    stores 68.4 -> 69.0, 17 73.1 -> 77.5).  1 M of 300, 0.3 to 0.8 of them empty, 1551 -> 1701 to 904 -> 1294, of 100 574 -> 595
+//    to 334 -> 461; but of 128 356 -> 340 to 268 -> 234, of 160 466 -> 434 to 331 -> 283.
 inline int share_of_empty_rows(int64_t rows, int64_t n_empty, int64_t nchunks, int64_t chunk, int lpr, int vec, int32_t f, int64_t ldz, uintptr_t Z) {
     if (n_empty <= 0 || n_empty > nchunks * chunk) return 0;
     const int64_t tiles = (f + lpr * vec - 1) / (lpr * vec), share = (n_empty + nchunks - 1) / nchunks;
     const int64_t at_once = 64 / lpr, stores = (share + at_once - 1) / at_once;
-    if (stores > 20 && 25 * stores > nchunks * tiles) return 0;
+    if ((stores > 20 || share > 240) && 25 * stores > nchunks * tiles) return 0;
     const bool whole = tiles == 1 || (ldz % 32 == 0 && Z % 128 == 0);
     return whole || rows * ldz <= (8 << 20) || (stores <= 10 && rows * ldz <= (64 << 20)) ? (int)share : 0;
 }

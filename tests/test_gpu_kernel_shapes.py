@@ -467,10 +467,10 @@ def test_spmm_mask_on_both_sides_of_its_rule(f, lengths):
     (1000, 65, 13, "k_spmm_split<16,1>"), (1000, 65, 16, "k_spmm_few<4>"), (1000, 65, 64, "k_spmm_few<8>"), (1000, 65, 41, "k_spmm_ragged"),
     (9000, 65, 3, "k_spmm_split<4,1>"), (9000, 65, 16, "k_spmm_split<4,4>"), (9000, 65, 64, "k_spmm_split<8,4>"),
     (9000, 65, 41, "k_spmm_line<1>"), (9000, 65, 67, "k_spmm_line<2>"), (9000, 65, 130, "k_spmm_line<1>"), (9000, 65, 132, "k_spmm_split<8,4>")])
-@pytest.mark.parametrize("share", [1, 20, 21, 63, 64, 65, 80, 81, 160, 161, 320, 321, 511, 512, 513])
+@pytest.mark.parametrize("share", [1, 20, 21, 63, 64, 65, 80, 81, 160, 161, 240, 241, 511, 512, 513])
 def test_rows_without_entries_go_with_the_chunks(full, length, f, kernel, share):
     """As many empty rows per chunk as fit one step of the zeroing, one less and one more; as many as small products take with their chunks
-    (20 stores of 1 to 16 rows) and one more, and as a chunk takes at the most and one more (a launch of their own); a last chunk with a smaller share or none: they are zero, the other rows have the bits of the
+    (20 stores of 1 to 16 rows, 240 rows) and one more, and as a chunk takes at the most and one more (a launch of their own); a last chunk with a smaller share or none: they are zero, the other rows have the bits of the
     matrix without empty rows, and nothing between the rows of a wider output is touched."""
     g = G()
     chunks = (full * length + 511) // 512
