@@ -607,7 +607,8 @@ int gcn_csr_export(const gcn_csr* a, int transposed, int64_t* rowptr, int32_t* c
     CopyArgs copy;
     auto add = [&](void* dst, const void* src, size_t bytes) -> int {
         if (!dst || !bytes) return GCN_OK;
-        if (kernel_copies(a->device, current, runs_on, memory_of(dst), (uintptr_t)dst, bytes)) copy.add(dst, src, bytes);
+        const uintptr_t to = (uintptr_t)dst;                    // (the runtime is asked only where it matters)
+        if (to % 16 == 0 && kernel_copies(a->device, current, runs_on, memory_of(dst), to, bytes)) copy.add(dst, src, bytes);
         else GCN_HIP_TRY(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, s));
         return GCN_OK;
     };
