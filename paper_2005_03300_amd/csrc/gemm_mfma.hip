@@ -906,7 +906,8 @@ int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const floa
             // contiguous strips through LDS (see k_gemm_tall_flat), where the operand is beyond the memory-side cache.  Below, the strided
             // kernel is faster, with the operand in the cache and from memory (300 x 16: 40 K rows 18 and 21 us, 160 K 45 and 48, 320 K 89
             // and 87, 1.3 M 341 and 316; 128 x 16: 40 K 8.3 and 10.1, 320 K 36 and 39, 640 K 78 and 73), except on short rows that end
-            // inside 64 bytes (100 x 16: 40 K 8.3 and 8.3, 80 K 12.0 and 10.8).  With two tiles of columns it is faster at every size
+            // inside 64 bytes (100 x 16: 40 K 8.3 and 8.3, 80 K 12.0 and 10.8; eight widths from 68 to 108 on 33 K, 45 K and 65 K rows: 0.78 to
+            // 0.98 of the strips' time).  With two tiles of columns it is faster at every size
             // from 128 floats on (128 x 32: 40 K 9.6 and 12.3, 1.3 M 158 and 160; 300 x 32: 1.3 M 369 and 390; 64 x 32: 640 K
             // 44.5 and 46.6, 1.3 M 94 and 87).
             const bool beyond = M * K * 4 >= (224ll << 20);

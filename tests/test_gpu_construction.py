@@ -140,3 +140,47 @@ def test_a_refused_construction_reuses_the_keys():
     assert sp.plan(n, src, dst, False, False) == "refused"
     held = held_per_key(G(), n, src, dst)
     assert 16 < held < 23, held
+
+
+def by_keys(kind, extra, symmetrise, loops):
+    """Pairs whose entries the radix sort of 64-bit keys orders, `extra` more than whole tiles of it."""
+    rs = np.random.default_rng(164)
+    if kind == "few_rows":                       # too many keys for a bucket of one row
+        n, m = 3, 8 * sp.RS_TILE + extra
+        src, dst = rs.integers(0, n, m), rs.integers(0, n, m)
+    elif kind == "all_dropped":
+        n, m = 2, 8 * sp.RS_TILE + extra
+        src = dst = rs.integers(0, n, m)
+    else:                                        # "star": refused after the counting
+        n, m = 3000, 21 * sp.RS_TILE + extra
+        src, dst = np.full(m, n - 1), rs.integers(1000, n, m)
+    return n, src, dst
+
+
+@pytest.mark.parametrize("symmetrise,loops", FORMS)
+@pytest.mark.parametrize("extra", [-1, 0, 1])
+@pytest.mark.parametrize("kind", ["few_rows", "all_dropped", "star"])
+def test_pairs_go_to_the_radix_sort(kind, extra, symmetrise, loops):
+    n, src, dst = by_keys(kind, extra, symmetrise, loops)
+    assert sp.plan(n, src, dst, symmetrise, loops) == ("refused" if kind == "star" else None)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("symmetrise,loops", FORMS)
+@pytest.mark.parametrize("extra", [-1, 0, 1])
+@pytest.mark.parametrize("kind", ["few_rows", "all_dropped", "star"])
+def test_entries_by_the_radix_sort(kind, extra, symmetrise, loops):
+    """The radix sort that reads the pairs, at the edges of its tiles: sizes that the buckets do not take and matrices that they refuse; pairs of
+    equal ends, up to all of them; rows without entries at the front; an id outside the range is refused wherever it stands."""
+    g = G()
+    n, src, dst = by_keys(kind, extra, symmetrise, loops)
+    the_same(g, n, src, dst, symmetrise, loops)
+    src, dst = src.astype(np.int32), dst.astype(np.int32).copy()
+    flags = (g.SYMMETRISE if symmetrise else 0) | (g.ADD_SELF_LOOPS if loops else 0)
+    for where, bad in ((0, -1), (src.size - 1, n), (src.size // 2, 2**31 - 1)):
+        for arr in (src, dst):
+            kept, arr[where] = arr[where], bad
+            with pytest.raises(g.GcnError) as e:
+                g.gcn_csr_create(n, dev(src), dev(dst), flags)
+            assert e.value.code == -2
+            arr[where] = kept
