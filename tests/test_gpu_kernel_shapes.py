@@ -1397,6 +1397,30 @@ def test_rows_that_fill_no_set_are_not_swept(n, k, f, usual):
     a.close()
 
 
+@pytest.mark.parametrize("offset", [0, 1])
+def test_export_in_a_graph(offset):
+    """Captured on a stream of its own and replayed, by the kernel and by the runtime's copies."""
+    from paper_2005_03300_amd import binding
+    g = G()
+    rs = np.random.default_rng(171)
+    a = g.gcn_csr_create(5000, *[dev(rs.integers(0, 5000, 40_000).astype(np.int32)) for _ in range(2)], g.SYMMETRISE | g.ADD_SELF_LOOPS | g.NORM_SYM)
+    want = a.arrays()
+    room = [torch.empty(w.numel() + 4, dtype=w.dtype, device="cuda") for w in want]
+    dst = [r[offset:offset + w.numel()] for r, w in zip(room, want)]
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        binding._check(binding.lib().gcn_csr_export(a._h, 0, *map(binding._ptr, dst), binding._stream()))
+    for k in range(3):
+        for r in room:
+            r.fill_(-7 - k)
+        graph.replay()
+        torch.cuda.synchronize()
+        for d, r, w in zip(dst, room, want):
+            assert torch.equal(d, w) and int((r == -7 - k).sum()) >= 4, k
+    a.close()
+
+
 @pytest.mark.parametrize("nnz", [1, 4, 7, 4095, 4096, 4098, 3 * 4096 + 1, 1_000_003])
 @pytest.mark.parametrize("offset", [0, 1, 2, 4])
 def test_export_fills_the_callers_arrays_and_no_more(nnz, offset):
