@@ -13,6 +13,8 @@
 // which then do nothing, cost such constructions 30 to 100 us (pairs of one vertex: 32 K 286 -> 310 us, 400 K 373 -> 438, 8 M 835 -> 932,
 // 16.8 M 1689 -> 1774; 2 M power-law pairs of 700 vertices 344 -> 403).
 #pragma once
+#include <type_traits>
+
 #include "common.h"
 
 namespace gcn {
@@ -388,44 +390,47 @@ __device__ __forceinline__ uint32_t fetch_piece(const SortArgs& a, uint32_t id, 
     const bool crowded = L.below[1] - L.below[0] > CAP;         // (the same for all)
     uint32_t* const s_bit = s_slot;
     static_assert(PIECE + (1 << (32 - 2 * BIN_BITS)) <= CAP, "a piece and the keys of a prefix");
+    auto collect = [&](auto bits) {                             // (a loop of its own: the test of every key took 16 us more for 34.6 M)
+        for (uint32_t j0 = 0; j0 < size; j0 += AT_ONCE * THREADS) {
+            uint32_t x[AT_ONCE];
+#pragma unroll
+            for (int e = 0; e < AT_ONCE; ++e) {
+                const uint32_t j = j0 + e * THREADS + threadIdx.x;
+                x[e] = keys[j < size ? j : size - 1];
+            }
+            unsigned long long who[AT_ONCE];
+            uint32_t found = 0;
+#pragma unroll
+            for (int e = 0; e < AT_ONCE; ++e) {
+                const uint32_t prefix = x[e] >> sh2;
+                bool mine = j0 + e * THREADS + threadIdx.x < size && prefix >= low && prefix < high;
+                if (decltype(bits)::value && mine && prefix == high - 1) {
+                    const uint32_t bit = x[e] & ((1u << sh2) - 1u);
+                    if (!(s_bit[bit / 32] >> bit % 32 & 1u)) atomicOr(&s_bit[bit / 32], 1u << bit % 32);
+                    mine = false;
+                }
+                who[e] = __ballot(mine);
+                found += (uint32_t)__popcll(who[e]);
+            }
+            uint32_t base = 0;
+            if (lane == 0 && found) base = atomicAdd(&L.count, found);
+            base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+#pragma unroll
+            for (int e = 0; e < AT_ONCE; ++e) {
+                if (who[e] >> lane & 1ull) s_key[base + lanes_below(who[e])] = x[e];
+                base += (uint32_t)__popcll(who[e]);
+            }
+        }
+        __syncthreads();
+    };
     if (crowded) {
         if (threadIdx.x < (1u << (32 - 2 * BIN_BITS)) / 32) s_bit[threadIdx.x] = 0;
         __syncthreads();
-    }
-    for (uint32_t j0 = 0; j0 < size; j0 += AT_ONCE * THREADS) {
-        uint32_t x[AT_ONCE];
-#pragma unroll
-        for (int e = 0; e < AT_ONCE; ++e) {
-            const uint32_t j = j0 + e * THREADS + threadIdx.x;
-            x[e] = keys[j < size ? j : size - 1];
-        }
-        unsigned long long who[AT_ONCE];
-        uint32_t found = 0;
-#pragma unroll
-        for (int e = 0; e < AT_ONCE; ++e) {
-            const uint32_t prefix = x[e] >> sh2;
-            bool mine = j0 + e * THREADS + threadIdx.x < size && prefix >= low && prefix < high;
-            if (crowded && mine && prefix == high - 1) {
-                const uint32_t bit = x[e] & ((1u << sh2) - 1u);
-                if (!(s_bit[bit / 32] >> bit % 32 & 1u)) atomicOr(&s_bit[bit / 32], 1u << bit % 32);
-                mine = false;
-            }
-            who[e] = __ballot(mine);
-            found += (uint32_t)__popcll(who[e]);
-        }
-        uint32_t base = 0;
-        if (lane == 0 && found) base = atomicAdd(&L.count, found);
-        base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
-#pragma unroll
-        for (int e = 0; e < AT_ONCE; ++e) {
-            if (who[e] >> lane & 1ull) s_key[base + lanes_below(who[e])] = x[e];
-            base += (uint32_t)__popcll(who[e]);
-        }
-    }
-    __syncthreads();
-    if (crowded) {
+        collect(std::true_type());
         if (threadIdx.x < 1u << sh2 && s_bit[threadIdx.x / 32] >> threadIdx.x % 32 & 1u) s_key[atomicAdd(&L.count, 1u)] = (high - 1) << sh2 | threadIdx.x;
         __syncthreads();
+    } else {
+        collect(std::false_type());
     }
     const uint32_t here = L.count;
 #pragma unroll
