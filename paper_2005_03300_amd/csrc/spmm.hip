@@ -199,10 +199,11 @@ __device__ __forceinline__ void stage_chunk(const SplitArgs& a, int64_t k0, int 
     }
 }
 
-// Zeroes a chunk's share of the rows without entries (any epilogue maps 0 to 0): a launch of its own took 32 us for 0.7 M rows of 64
-// columns, bound by its stores, while the product beside it was short of memory traffic.  The list is asked for together with the
-// chunk (empty_row), the stores are sent before its gathers, 64 rows at a time.  Called by whole wavefronts.  Forms of the kernels
-// of their own (ZERO): in those of matrices without such rows the code for it cost 1 % of products of 11 to 40 us.
+// Zeroes a chunk's share of the rows without entries (any epilogue maps 0 to 0): a launch of its own took 32 us for 0.7 M rows
+// of 64 columns, bound by its stores, while the product beside it was short of memory traffic.  Where that pays: see
+// share_of_empty_rows.  The list is asked for together with the chunk (empty_row), the stores are sent before its gathers, 64 rows at
+// a time.  Called by whole wavefronts.  Forms of the kernels of their own (ZERO): in those of matrices without such rows the code for it
+// cost 1 % of products of 11 to 40 us (k_spmm_line<1>, whose chunks take longer, 0.1 % on 90 products: one form).
 __device__ __forceinline__ int32_t empty_row(const SplitArgs& a, int64_t c, int i) {
     if (a.empty_share == 0) return 0;
     const int64_t q = c * a.empty_share + i;
@@ -653,12 +654,14 @@ __global__ __launch_bounds__(64 * WAVES_PER_BLOCK) void k_spmm_few(SplitArgs a) 
 // Matrices of few rows, all of them short (SHORT_ROW entries at the most): a lane group takes a row, one wavefront per
 // workgroup so that a thousand rows spread over 63 compute units.  Nothing is staged or joined: the chain is
 // indices, gathers, sums, store, and an empty row is simply a sum of nothing.  The rows lie at an equal pitch (build_short),
-// so that the indices do not wait for row pointers.  Eight entries a round, the gathers of the next round sent out as those of this one are
-// used: a kernel that runs for six microseconds pays for every line of its code, which no cache holds when it starts, and 32 entries
-// unrolled took longer for their 6.6 KB than for their one latency (4096 rows of 17 at 16 columns 7.3 -> 6.1 us).  The sums are those
-// of the nonzero-split kernels, term by term: there a row is cut where a lane group's slice of SLICE entries or a chunk
-// ends, and with at most SHORT_ROW entries it has three pieces, F + (H1 + H2), or (F + H1) + H2 when H2 is in the
-// next chunk.  1000 rows of 17 at 16 columns: 5.4 us; k_spmm_few 7.7; k_spmm_split 9.7 and k_spmm_fixup 3.9.
+// so that the indices do not wait for row pointers.  Eight entries a round, the gathers of the next round sent out as those of
+// this one are used: a kernel of a few microseconds pays for every line of its code, which no cache holds when it starts, and 32
+// entries unrolled took longer for their 6.6 KB than for their one latency.  The sums are those of the nonzero-split kernels,
+// term by term: there a row is cut where a lane group's slice of SLICE entries or a chunk ends, and with at most SHORT_ROW entries
+// it has three pieces, F + (H1 + H2), or (F + H1) + H2 when H2 is in the next chunk.
+// Microseconds at 16 columns, traced: 1000 rows of 17 entries 6.3, k_spmm_few 7.7, k_spmm_split 9.7 and k_spmm_fixup 3.9.  With row
+// pointers and 32 entries a round -> now, one of many in a graph, where an empty kernel takes 2.05: 1000 rows of 17 4.9 -> 4.4, of 40
+// 7.9 -> 6.0, of 64 9.3 -> 8.0, 30 K of 17 8.1 -> 7.6.  Called one by one the host takes longer (5.8 a call, 4.15 of it a launch).
 // The value of lane `l` of every group of LPR lanes (l a constant once the loop around is unrolled).
 template <int LPR>
 __device__ __forceinline__ int group_lane(int x, int l) {
@@ -1398,9 +1401,15 @@ static int launch_short(const SplitArgs& args, const Matrix& m, int epilogue, hi
         const dim3 grid((unsigned)((nrows + 15) / 16));
         const RowsNext nx = *next;
         timing_begin(s);
-        if (nx.kind == RowsNext::LOSS) hipLaunchKernelGGL((k_spmm_short<4, 32, GCN_EPI_NONE, RowsNext::LOSS>), grid, dim3(64), 0, s, args, nrows, m.short_rows, m.short_pitch, nx);
-        else if (epilogue == GCN_EPI_RELU) hipLaunchKernelGGL((k_spmm_short<4, 32, GCN_EPI_RELU, RowsNext::GEMM>), grid, dim3(64), 0, s, args, nrows, m.short_rows, m.short_pitch, nx);
-        else hipLaunchKernelGGL((k_spmm_short<4, 32, GCN_EPI_NONE, RowsNext::GEMM>), grid, dim3(64), 0, s, args, nrows, m.short_rows, m.short_pitch, nx);
+        if (nx.kind == RowsNext::LOSS)
+            hipLaunchKernelGGL((k_spmm_short<4, 32, GCN_EPI_NONE, RowsNext::LOSS>), grid, dim3(64), 0, s, args, nrows, m.short_rows,
+                               m.short_pitch, nx);
+        else if (epilogue == GCN_EPI_RELU)
+            hipLaunchKernelGGL((k_spmm_short<4, 32, GCN_EPI_RELU, RowsNext::GEMM>), grid, dim3(64), 0, s, args, nrows, m.short_rows,
+                               m.short_pitch, nx);
+        else
+            hipLaunchKernelGGL((k_spmm_short<4, 32, GCN_EPI_NONE, RowsNext::GEMM>), grid, dim3(64), 0, s, args, nrows, m.short_rows,
+                               m.short_pitch, nx);
         timing_end(s);
         GCN_LAUNCH_CHECK();
         next->done = true;
@@ -1411,9 +1420,15 @@ static int launch_short(const SplitArgs& args, const Matrix& m, int epilogue, hi
         constexpr int LPR = decltype(lpr)::value, SLICE = decltype(slice)::value;
         const dim3 grid((unsigned)((nrows * LPR + 63) / 64), (unsigned)((args.f + 4 * LPR - 1) / (4 * LPR)));
         switch (epilogue) {
-            case GCN_EPI_NONE: hipLaunchKernelGGL((k_spmm_short<LPR, SLICE, GCN_EPI_NONE>), grid, dim3(64), 0, s, args, nrows, m.short_rows, m.short_pitch, none); break;
-            case GCN_EPI_RELU: hipLaunchKernelGGL((k_spmm_short<LPR, SLICE, GCN_EPI_RELU>), grid, dim3(64), 0, s, args, nrows, m.short_rows, m.short_pitch, none); break;
-            default: hipLaunchKernelGGL((k_spmm_short<LPR, SLICE, GCN_EPI_MASK>), grid, dim3(64), 0, s, args, nrows, m.short_rows, m.short_pitch, none); break;
+            case GCN_EPI_NONE:
+                hipLaunchKernelGGL((k_spmm_short<LPR, SLICE, GCN_EPI_NONE>), grid, dim3(64), 0, s, args, nrows, m.short_rows, m.short_pitch, none);
+                break;
+            case GCN_EPI_RELU:
+                hipLaunchKernelGGL((k_spmm_short<LPR, SLICE, GCN_EPI_RELU>), grid, dim3(64), 0, s, args, nrows, m.short_rows, m.short_pitch, none);
+                break;
+            default:
+                hipLaunchKernelGGL((k_spmm_short<LPR, SLICE, GCN_EPI_MASK>), grid, dim3(64), 0, s, args, nrows, m.short_rows, m.short_pitch, none);
+                break;
         }
     };
     timing_begin(s);
@@ -1501,9 +1516,11 @@ static int launch_block_reduce(int64_t n, int32_t f, const Blocked& b, const int
 // 0.47 G entries over 4.4 M rows of 64 bytes, sweep of one product (and its misses): a wavefront of 256 rows per workgroup, nine per
 // compute unit, indices handed round through the LDS: 4.2 ms (176 M); in registers 4.9 (247 M); two trips asked
 // for at once 5.5.  Workgroups of 5 x 511 rows, two trips at once: 3.4 to 4.3 (200 to 229 M), depending on where the compiler
-// put its waits; this kernel 3.4 (132 M: 138 G entries/s, 39 G misses/s, both ceilings together), and the same with four,
+// put its waits; this kernel 3.4 (132 M: 138 G entries/s, 39 G misses/s), and the same with four,
 // six or seven tasks in the same LDS.  With eight 4.3.  Product: 5.56 -> 4.75 ms; 1.32 G entries, 8.7 M rows 12.1 -> 10.2; 0.12
 // G, 1.2 M rows 1.30 -> 0.91, at 32 columns 1.65 -> 1.22.
+// What bounds it now is the wait: 127 G L2 requests/s and 38 G misses/s are 0.50 and 0.70 of what a gather loop reaches of either,
+// where the hub schedule's pair reaches 0.41 and 0.99 at once.  Nothing is under way when a trip's last gather arrives.
 struct SweepArgs {
     const int32_t* colidx;
     const float* val;            // NULL: value-free product
@@ -2039,7 +2056,8 @@ static int run_hub(gcn_csr* a, Matrix& m, int32_t f, const float* X, int64_t ldx
     ah.fix_list = b.fix_list; ah.n_fix = b.n_fix; ah.n_fix_long = b.n_fix_long;
     ah.nnz = h.nnz_hot; ah.nsub = hot.nsub; ah.nchunks = hot.nchunks; ah.f = f;
     ah.X = h.xhot; ah.ldx = f; ah.Z = a->partial; ah.ldz = f; ah.Zprev = nullptr; ah.ldzprev = 0; ah.carry = a->carry2;
-    if (rest.n_ne < rest.nrows && !share_empty_rows(&ar, rest, SplitChoice{SplitChoice::SPLIT, f > 16 ? 8 : 4, 4})) GCN_TRY(zero_empty_rows(rest, f, Z, ldz, s));
+    if (rest.n_ne < rest.nrows && !share_empty_rows(&ar, rest, SplitChoice{SplitChoice::SPLIT, f > 16 ? 8 : 4, 4}))
+        GCN_TRY(zero_empty_rows(rest, f, Z, ldz, s));
     if (f > 16) GCN_TRY(launch_pair<8>(ar, ah, epilogue, s));
     else GCN_TRY(launch_pair<4>(ar, ah, epilogue, s));
     return launch_block_reduce<4>(hot.nrows, f, b, h.heavy_rows, o.row_scale, 1, a->partial, Z, ldz, epilogue, Zprev,

@@ -43,13 +43,12 @@ __device__ __forceinline__ void sum_of_parts(int group, int32_t M, int32_t N, in
     store((int)(transposed ? src % M : src / N), (int)(transposed ? src / M : src % N), s);
 }
 
-// Y and the loss from the workgroups' partial results.  16 columns of a row of Y per workgroup, a partial result each for
-// its 64 groups of threads, eight of them in flight (one after another, as the compiler left them, 64 waits for memory made
-// 24 us of this); every group's sum, then the 64 of them in pairs.  One more workgroup adds the loss.  2048 partial results of 512
-// numbers: 8 us, 24 + 9 + 5 in three launches before.
-// Here 16 of those results (`group`) of the weight gradient, 16 x C out of 16 x CP.  store(index, sum)
+// `group` of 16 numbers of the fused last layer's weight gradient, 16 x C out of 16 x CP: a partial result each for the 64 groups
+// of threads, eight of them in flight (one after another, as the compiler left them, 64 waits for memory made 24 us of 2048
+// partial results of 512 numbers), every group's sum, then the 64 of them in pairs.  store(index, sum)
 template <typename Store>
-__device__ __forceinline__ void sum_of_fused(int group, int C, int CP, int blocks, const float* __restrict__ part, float (&s_y)[64][16], Store store) {
+__device__ __forceinline__ void sum_of_fused(int group, int C, int CP, int blocks, const float* __restrict__ part, float (&s_y)[64][16],
+                                             Store store) {
     constexpr int GROUPS = 64, AHEAD = 8;
     const int i = threadIdx.x % 16, j = threadIdx.x / 16;
     const int e = group * 16 + i;                               // of 16 CP numbers
