@@ -961,6 +961,35 @@ def test_spmm_short_rows_at_equal_pitch(longest, f):
     a.close()
 
 
+@pytest.mark.parametrize("rows,power,kernel", [(60_001, 4, "k_spmm_split<8,1>"), (44_001, 4, "k_spmm_short<2>"), (60_001, 80, "k_spmm_short<2>")])
+@pytest.mark.parametrize("f", [5, 7])
+def test_short_rows_on_both_sides_of_the_padded_copy(rows, power, kernel, f):
+    """Rows of 0 to 64 entries, most of them short: many whose padded copy would be mostly padding, fewer, and many of which hardly any are long;
+    epilogues and the transpose, whose rows are another distribution."""
+    g = G()
+    rs = np.random.default_rng(158)
+    lengths = (rs.random(rows) ** power * 64.99).astype(np.int64)
+    lengths[11] = 64
+    rowptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    colidx = (np.repeat(rs.integers(0, rows - 65 * 7, rows), lengths) + 7 * (np.arange(rowptr[-1]) - np.repeat(rowptr[:-1], lengths))).astype(np.int32)
+    val = rs.standard_normal(colidx.size).astype(np.float32)
+    a = g.gcn_csr_create_from_csr_rect(rows, rows, dev(rowptr), dev(colidx), dev(val), g.BUILD_TRANSPOSE)
+    assert kernel in g.gcn_spmm_describe(a, 0, f)
+    X, M = synth.normal_features(rows, f, 159), synth.normal_features(rows, f, 160)
+    A = torch.sparse_coo_tensor(torch.from_numpy(np.stack([np.repeat(np.arange(rows), lengths), colidx.astype(np.int64)])),
+                                torch.from_numpy(val).double(), (rows, rows)).coalesce()
+    Z = torch.full((rows, f), float("nan"), device="cuda")
+    g.gcn_spmm(a, 0, dev(X), Z)
+    plain = host(Z).copy()
+    assert_close(plain, torch.sparse.mm(A, torch.from_numpy(X).double()).numpy(), f"{rows} {f}")
+    for epi, want in ((g.EPI_RELU, np.maximum(plain, 0)), (g.EPI_MASK, np.where(M > 0, plain, 0))):
+        g.gcn_spmm(a, 0, dev(X), Z, epi, dev(M))
+        assert np.array_equal(host(Z), want), epi
+    g.gcn_spmm(a, 1, dev(X), Z)
+    assert_close(host(Z), torch.sparse.mm(A.t(), torch.from_numpy(X).double()).numpy(), f"transposed {rows} {f}")
+    a.close()
+
+
 @pytest.mark.parametrize("K,N,M", [(100, 16, 65_536), (300, 16, 195_740), (300, 16, 195_735), (64, 32, 917_504), (128, 32, 40_000), (64, 16, 32_768), (16, 8, 32_784),
                                    (64, 16, 14_336), (256, 64, 14_336), (500, 24, 8192), (602, 64, 5000)])
 def test_gemm_nn_on_both_sides_of_its_rules(K, N, M):
