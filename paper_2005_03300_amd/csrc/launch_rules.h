@@ -4,21 +4,28 @@
 
 namespace gcn {
 
-// Wavefronts of a workgroup of k_gemm_tall: each workgroup puts op(B) into LDS, so eight share it, unless the strips of 16 rows make so few
-// workgroups that four leave every compute unit with no more than one, i.e. none reads op(B) twice.  Seven eighths of the compute units,
-// half of them where op(B) has more than 400 rows, and never where it has more than 640: there the time it takes to put op(B)
-// into LDS decides, and half as many wavefronts take twice as long.  Microseconds with eight and four:
+// Wavefronts of a workgroup of k_gemm_tall: eight or four, of up to eight strips of 16 rows per compute unit (with more the launch is capped),
+// in `panels` columns of workgroups.  Each workgroup puts its part of op(B) into LDS, which eight share.  Four where the busiest
+// compute unit then has fewer wavefronts: with one column of workgroups up to 16 K rows, where each has no more than one of either
+// kind.  Not where the workgroups together read so much of op(B), more than 400 rows for each compute unit, that half as many
+// wavefronts take longer for it; with three workgroups on the busiest up to 160 rows, with more never.  Microseconds with eight and four:
 //   rows                  5000         10000        14000        16384        20000        32768
-//   128 x 16           5.33  4.41   5.48  4.56   5.50  4.57   5.49  4.55   6.34  5.40   6.52  5.62
+//   128 x 16           5.33  4.41   5.48  4.56   5.50  4.57   5.49  4.55
 //   256 x 24           8.80  8.03   9.02  8.55   9.20  9.17  10.62 11.10  10.73 11.97  11.36 13.17
 //   256 x 64           14.2  12.4   15.0  13.2   15.9  14.6   17.0  16.8   17.3  19.3   18.2  20.7
 //   500 x 24           15.9  14.2   16.9  18.8   19.4  20.2   19.3  20.3   19.6  22.3   20.0  23.2
 //   602 x 64           24.3  23.3   27.6  52.0   28.1  53.8   27.9  54.9   51.1  68.0   53.9  85.5
-// (602 x 64 takes two columns of workgroups, `panels`; 1200 x 24 on 3000 rows 21.5 and 26.0, 1900 x 24 31.7 and 43.6.  Narrow
-// products gain up to twice as many rows, but not with 41 or 64 columns.)
+// (602 x 64 takes two columns of workgroups.)  On 3000 rows 1200 x 16 20.4 and 19.0, 1200 x 24, in two, 21.3 and 26.7.  Two columns: 100 x 100
+// on 18 K 13.3 and 12.4, on 10 K, where both have eight wavefronts on the busiest, 128 x 128 9.8 and 10.3; four: 100 x 256 on 10 K
+// 13.5 and 12.8, 200 x 256 22.1 and 27.1.  Of 2025 sizes, 256 to 1900 rows of op(B), 8 to 256 columns and 500 to 32768 rows, the slower is
+// taken by more than 5 % for 63, by 16 % at the most (500 x 24 on 10 K is one of them; always eight 927, by 33 %).
 inline int tall_waves(int64_t strips, int64_t panels, int64_t k, int64_t cus) {
-    const int64_t workgroups = (strips + 3) / 4 * panels;
-    return k <= 640 && workgroups <= (k > 400 ? cus / 2 : cus / 8 * 7) ? 4 : 8;
+    if (strips > 8 * cus) return 8;
+    const int64_t of_four = (strips + 3) / 4 * panels, of_eight = (strips + 7) / 8 * panels;
+    const int64_t each = (of_four + cus - 1) / cus;
+    if (4 * each >= 8 * ((of_eight + cus - 1) / cus)) return 8;
+    if (each > 1) return each <= 3 && k <= 160 ? 4 : 8;
+    return k * of_four <= 400 * cus ? 4 : 8;
 }
 
 // How many of the rows without entries a chunk of a product zeroes (zero_share), or 0: they take a launch of their own, which writes whole rows
