@@ -1449,7 +1449,9 @@ static int launch_short(const SplitArgs& args, const Matrix& m, int epilogue, hi
 
 static inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
-// Adds the partial rows of the column-blocked product in ascending block order, then the epilogue.
+// Adds the partial rows of the column-blocked product in ascending block order, then the epilogue.  Bound by reading them, four at a
+// time: one by one every partial row waited for its number and then for itself (62 K rows of 100 blocks at 16 columns 121 -> 83 us,
+// 4.9 TB/s; 528 K of 15 148 -> 131; 81 K of 8 18 -> 15; 120 K rows of two blocks at 64 columns 16.1 -> 15.4; eight at a time 86, 130, 16 and 17).
 template <int VEC, int EPI>
 __global__ __launch_bounds__(256) void k_block_reduce(int64_t n, int32_t f, int32_t lanes, const int64_t* __restrict__ rq_ptr,
                                                       const int32_t* __restrict__ rq_idx, const int32_t* __restrict__ row_map,
@@ -1466,11 +1468,21 @@ __global__ __launch_bounds__(256) void k_block_reduce(int64_t n, int32_t f, int3
 #pragma unroll
     for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
     if (accumulate) load_vec<VEC>(acc, Z + row * ldz + col0);   // what an earlier pass stored raw for this row
-    for (int64_t k = rq_ptr[i]; k < rq_ptr[i + 1]; ++k) {
-        float part[VEC];
-        load_vec<VEC>(part, P + (int64_t)rq_idx[k] * f + col0);
+    const int64_t first = rq_ptr[i];
+    const int32_t* const list = rq_idx + first;
+    const int count = (int)(rq_ptr[i + 1] - first);
+    constexpr int AT_ONCE = 4;
+    for (int k = 0; k < count; k += AT_ONCE) {
+        float part[AT_ONCE][VEC];
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) acc[v] += part[v];
+        for (int e = 0; e < AT_ONCE; ++e) load_vec<VEC>(part[e], P + (int64_t)list[k + e < count ? k + e : count - 1] * f + col0);
+#pragma unroll
+        for (int e = 0; e < AT_ONCE; ++e) {
+            if (k + e < count) {
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) acc[v] += part[e][v];
+            }
+        }
     }
     const float scale = row_scale ? row_scale[row] : 1.f;
     if constexpr (EPI == EPI_LAYER)

@@ -842,6 +842,29 @@ def test_column_blocks_walked_by_one_xcd_each(f, kernel, chunks):
     a.close()
 
 
+@pytest.mark.parametrize("f", [2, 4, 16, 20, 64])
+@pytest.mark.parametrize("blocks", [2, 4, 5, 9])
+def test_partial_rows_are_added_in_the_order_of_the_blocks(f, blocks):
+    """Rows of 0 to `blocks` partial rows, each the rounded product of one entry: the sums are those of adding one by one, bit for bit."""
+    g = G()
+    n, width = 700, 1024                                        # (columns of a block)
+    rows = [[b * width + (i * 7 + b) % width for b in range(blocks) if (i + b) % 3 or i % (blocks + 1) == blocks][:i % (blocks + 1)] for i in range(n)]
+    rowptr = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int64)
+    col = np.concatenate([np.asarray(r, np.int32) for r in rows if r])
+    val = synth.normal_features(len(col), 1, 71)[:, 0].copy()
+    X = synth.uniform_features(blocks * width, f, 72)
+    a = g.gcn_csr_create_from_csr_rect(n, blocks * width, dev(rowptr), dev(col), dev(val), 0)
+    g.gcn_csr_config(a, g.CFG_SPMM_BLOCKS, blocks)
+    Z = torch.full((n, f), float("nan"), device="cuda")
+    g.gcn_spmm(a, 0, dev(X), Z)
+    want = np.zeros((n, f), np.float32)
+    for i in range(n):
+        for k in range(rowptr[i], rowptr[i + 1]):
+            want[i] = want[i] + val[k] * X[col[k]]
+    np.testing.assert_array_equal(host(Z), want)
+    a.close()
+
+
 @pytest.mark.parametrize("strips", [1, 3, 4, 5, 16, 17, 252, 256, 257, 1008, 1024, 2052, 8192, 8199, 32_768, 33_001])
 @pytest.mark.parametrize("C", [3, 16, 41, 130])
 def test_last_layer_sums_of_workgroups(strips, C):
