@@ -281,15 +281,21 @@ struct EpochEnd {
         int32_t count = 0, loss_at = -1;
         float lr = 0;
     } args;
-    struct Room {                                 // two pieces of memory, handed out first fit
-        char* at[2] = {};
-        size_t left[2] = {};
+    struct Room {                                 // two pieces of memory, handed out first fit, and one for the gradients over few rows
+        static constexpr int PIECES = 3, FEW = 2;
+        char* at[PIECES] = {};
+        size_t left[PIECES] = {};
         static size_t whole(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
-        char* find(size_t bytes) const { return whole(bytes) <= left[0] ? at[0] : (whole(bytes) <= left[1] ? at[1] : nullptr); }
-        char* take(size_t bytes) {
-            char* const p = find(bytes);
-            if (!p) return nullptr;
-            const int k = p == at[0] && whole(bytes) <= left[0] ? 0 : 1;
+        int fits(size_t bytes, bool few) const {
+            for (int k = few ? FEW : 0; k < (few ? PIECES : FEW); ++k)
+                if (whole(bytes) <= left[k]) return k;
+            return PIECES;
+        }
+        char* find(size_t bytes, bool few) const { return fits(bytes, few) < PIECES ? at[fits(bytes, few)] : nullptr; }
+        char* take(size_t bytes, bool few = false) {
+            const int k = fits(bytes, few);
+            if (k == PIECES) return nullptr;
+            char* const p = at[k];
             at[k] += whole(bytes);
             left[k] -= whole(bytes);
             return p;
@@ -299,8 +305,8 @@ struct EpochEnd {
     explicit EpochEnd(const Room& r);             // no room: everything as without it
     ~EpochEnd();
     // where the next `bytes` will lie, or NULL; and taking them
-    void* next(size_t bytes) const { return args.count < MOST ? room.find(bytes) : nullptr; }
-    void* take(size_t bytes) { return args.count < MOST ? room.take(bytes) : nullptr; }
+    void* next(size_t bytes, bool few = false) const { return args.count < MOST ? room.find(bytes, few) : nullptr; }
+    void* take(size_t bytes, bool few = false) { return args.count < MOST ? room.take(bytes, few) : nullptr; }
     void add(const float* part, float* Y, int32_t M, int32_t N, int parts, bool transposed) {
         args.sums[args.count++] = Sum{part, Y, W, M, N, (int32_t)parts, transposed ? 1 : 0, 0};
     }
@@ -309,6 +315,7 @@ struct EpochEnd {
 EpochEnd* epoch_end();                            // the thread's, or NULL
 // bytes of that scratch the split-K product (ta = 1) and the column sums take for the given shape
 size_t gemm_tn_scratch_bytes(int64_t M, int64_t N, int64_t K);
+bool gemm_tn_few(int64_t M, int64_t N, int64_t K);            // a gradient over few rows: as many partial results as a kernel of short rows leaves
 size_t colsum_scratch_bytes(int64_t rows, int32_t cols);
 size_t loss_scratch_bytes();
 size_t loss_part_bytes(int64_t n);               // what n rows need of it: a workgroup takes four at the least
@@ -390,7 +397,8 @@ struct LayerEnd {
 // the loss.  The kernel of few and short rows does it where the rows are made and sets `done` (see next_of); behind the others it
 // is a launch of its own.
 struct RowsNext {
-    enum Kind { NONE = 0, GEMM = 1, LOSS = 2 } kind = NONE;
+    enum Kind { NONE = 0, GEMM = 1, LOSS = 2, GRAD = 4 };
+    int kind = NONE;                      // GEMM, LOSS, GRAD or GEMM | GRAD
     const float* W = nullptr;             // f x N, or N x f when transposed
     int32_t N = 0, transposed = 0;
     float* T = nullptr;                   // n x N
@@ -399,8 +407,16 @@ struct RowsNext {
     float* G = nullptr;                   // n x f
     double* part = nullptr;               // a partial sum of every 16 rows
     float inv_m = 0;
+    const float* H = nullptr;             // gradient: the partial results of H^T Z, H n x M, as the launch of its own leaves them: of every
+    int64_t ldh = 0;                      // 64 rows one of M x f
+    int32_t M = 0;
+    float* ypart = nullptr;
     bool done = false;
 };
+// The weight gradient H^T Z (M x f, over n rows) as what is next to the rows of Z: whether a kernel of them can leave its partial
+// results, and there is room for them; gradient_made takes the room and says that they lie there.
+bool gradient_next(RowsNext& next, int64_t n, int32_t f, const float* H, int64_t ldh, int32_t M);
+void gradient_made(const RowsNext& next, int64_t n, int32_t f, float* Y);
 // The loss of an epoch as what is next to a product of C columns, whose `parts` partial sums lie in what is left of the EpochEnd's room (NONE:
 // it has to be a launch of its own); loss_made takes that room once they do.
 RowsNext loss_next(int32_t C, int64_t parts, const int32_t* labels, int64_t n_labelled, float* G);

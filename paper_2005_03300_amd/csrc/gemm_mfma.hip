@@ -784,6 +784,7 @@ struct TnShape {
     bool swap, narrow;
     int64_t Mw, Nw, blocks, kpb;
     int NT, ny, nz, gw, rw, MG, fold;
+    bool few;
     size_t scratch_bytes;
 };
 
@@ -823,7 +824,10 @@ static TnShape tn_shape(int64_t M, int64_t N, int64_t K) {
     // Workgroups over K: at least two trips of every wavefront each,
     const int64_t rows = g.narrow ? 64 : 16 * g.rw;       // rows per trip of a workgroup
     const int64_t count = g.Mw * g.Nw;
-    int64_t blocks = K / (2 * rows);
+    // or one trip of as few rows as a kernel of short rows takes, which then leaves the same partial results (see gradient_next; as a
+    // launch of their own 64 x 16 over 16 K rows take 8.5 us, with two trips 8.3, over 2 K and 32 K, and other shapes, the same).
+    g.few = K <= 32768 && g.Mw <= 64 && g.Nw <= 16;
+    int64_t blocks = g.few ? (K + rows - 1) / rows : K / (2 * rows);
     // but no more workgroups than run side by side: a workgroup loads its next trip while it multiplies, and the partial results
     // are written and read once more.  One per compute unit, two where the partial results are below 1/40 of the operands
     // (200 x 32 over 1 M rows 231 and 199 us; 256 x 64 over 120 K rows 52 and 64); four of the narrow kernel (16 x 16 over 4.4 M rows:
@@ -866,6 +870,7 @@ int reduce_parts_launch(int32_t M, int32_t N, int parts, bool transposed, const 
 size_t gemm_mfma_tn_scratch_bytes(int64_t M, int64_t N, int64_t K) {
     return tn_shape(M, N, K).scratch_bytes;
 }
+bool gemm_tn_few(int64_t M, int64_t N, int64_t K) { return tn_shape(M, N, K).few; }
 
 int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, const float* B,
                      int64_t ldb, float* C, int64_t ldc, const float* bias, int epilogue, const float* Zprev,
@@ -965,7 +970,7 @@ int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const floa
     const TnShape g = tn_shape(M, N, K);
     if (g.blocks >= (1ll << 31) || g.ny > 65535 || g.nz > 65535 || M * N >= (1ll << 36)) return fail(GCN_ERR_RANGE, "gcn_gemm: output too large");
     EpochEnd* const end = !bias && epilogue == GCN_EPI_NONE && ldc == N ? epoch_end() : nullptr;
-    void* scratch = end ? end->take(g.scratch_bytes) : nullptr;
+    void* scratch = end ? end->take(g.scratch_bytes, g.few) : nullptr;
     const bool later = scratch != nullptr;
     if (!later) GCN_TRY(scratch_get(&scratch, g.scratch_bytes, s));
     TnArgs args;
@@ -1007,6 +1012,22 @@ int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const floa
     return GCN_OK;
 }
 
+bool gradient_next(RowsNext& next, int64_t n, int32_t f, const float* H, int64_t ldh, int32_t M) {
+    if (!epoch_end() || n < 64 || f > 16 || f % 4 != 0 || M > 64) return false;
+    const TnShape g = tn_shape(M, f, n);                        // (64 rows a trip: four wavefronts of 16)
+    if (!g.few || g.kpb != 64 || g.fold) return false;
+    next.ypart = (float*)epoch_end()->next(g.scratch_bytes, true);
+    if (!next.ypart) return false;
+    next.kind |= RowsNext::GRAD;
+    next.H = H; next.ldh = ldh; next.M = M;
+    return true;
+}
+
+void gradient_made(const RowsNext& next, int64_t n, int32_t f, float* Y) {
+    const TnShape g = tn_shape(next.M, f, n);
+    epoch_end()->add((const float*)epoch_end()->take(g.scratch_bytes, true), Y, next.M, f, (int)g.blocks, false);
+}
+
 // Whether Gprev (n rows of 16 floats) shares no memory with a matrix of n rows of 16 floats, `ld` apart, that the same kernel
 // reads, or lies on it row by row: then a row is read and written by one wavefront, in that order.
 static bool row_by_row(int64_t n, const float* Gprev, const float* M, int64_t ld) {
@@ -1023,7 +1044,7 @@ int gemm_back_launch(int64_t n, int32_t f_in, int32_t f_out, const float* Hin, i
     if (!row_by_row(n, Gprev, Hin, ldh) || !row_by_row(n, Gprev, S, 16) || !row_by_row(n, Gprev, Zprev, 16)) return GCN_OK;
     const TnShape g = tn_shape(16, 16, n);
     EpochEnd* const end = epoch_end();
-    void* scratch = end ? end->take(g.scratch_bytes) : nullptr;
+    void* scratch = end ? end->take(g.scratch_bytes, g.few) : nullptr;
     const bool later = scratch != nullptr;
     if (!later) GCN_TRY(scratch_get(&scratch, g.scratch_bytes, s));
     TnArgs args;

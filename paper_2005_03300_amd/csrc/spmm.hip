@@ -680,14 +680,22 @@ __device__ __forceinline__ int group_lane(int x, int l) {
 // would run for four microseconds, most of it its start and one chain of latencies, of which all but the stores happen here beside the walk.
 // The matrix instructions and the sums of a row's exponentials are those of k_gemm_tall and k_softmax_nll, bit for bit.  Epochs: 64-16-8 on 4096
 // rows of 17 entries 53 -> 42.5 us (11 launches, now 8), 64-16-16-8 on 1000 67 -> 54, 100-16-4 on 30000 63 -> 53.
-template <int LPR, int SLICE, int EPI, int NEXT = RowsNext::NONE>
-__global__ __launch_bounds__(64) void k_spmm_short(SplitArgs a, int64_t nrows, const int32_t* __restrict__ rows, int32_t pitch, RowsNext nx) {
+//
+// The weight gradient H^T Z of up to 64 x 16 (MT tiles of 16 columns of H, fetched before the walk) takes workgroups of four of them, whose sums
+// are added up as k_gemm_tn and k_gemm_tn_narrow do it over 64 rows.  It makes the kernel 1 to 2 us longer and saves a launch per layer: epochs of
+// 64-16-8 on 4096 vertices 38.7 -> 34.4 us, 64-16-16-8 54.7 -> 49.9, 50-16-12 on 10 K 45.9 -> 39.9, 100-16-4 on 30 K 56.6 -> 54.2.  Workgroups of
+// eight wavefronts, whose partial results are half as many, took 4 us longer each: fewer compute units fetch the rows.
+template <int LPR, int SLICE, int EPI, int NEXT = RowsNext::NONE, int MT = 1>
+__global__ __launch_bounds__(NEXT & RowsNext::GRAD ? 256 : 64) void k_spmm_short(SplitArgs a, int64_t nrows, const int32_t* __restrict__ rows,
+                                                                                 int32_t pitch, RowsNext nx) {
     constexpr int VEC = 4;
+    constexpr bool GRAD = (NEXT & RowsNext::GRAD) != 0;
     static_assert(NEXT == RowsNext::NONE || LPR == 4, "16 rows of a wavefront");
     static_assert(SHORT_ROW <= 2 * SLICE, "at most three pieces");
     constexpr int U = 8, OWN = LPR < U ? U / LPR : 1;           // entries per round, those that a lane holds the indices of
-    const int lane = threadIdx.x, li = lane % LPR;
-    const int64_t row = ((int64_t)blockIdx.x * 64 + lane) / LPR;
+    const int lane = threadIdx.x & 63, li = lane % LPR, wave = GRAD ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
+    const int64_t unit = GRAD ? (int64_t)blockIdx.x * 4 + wave : (int64_t)blockIdx.x;
+    const int64_t row = (unit * 64 + lane) / LPR;
     int col0;
     const bool col_ok = lane_columns<LPR, VEC>(a.f, blockIdx.y, gridDim.y, li, &col0);
     const int64_t own = row < nrows ? row : nrows - 1;
@@ -714,10 +722,19 @@ __global__ __launch_bounds__(64) void k_spmm_short(SplitArgs a, int64_t nrows, c
     for (int e = 0; e < U; ++e) gather(now, e);
     // the next product's operands: lane (r, kq) holds rows 4 kq .. 4 kq + 3 of column r of op(W), and four columns of row r of the mask
     const int r = lane & 15, kq = lane >> 4;
-    const int64_t next_row = (int64_t)blockIdx.x * 16 + r;
-    float w[4] = {}, mask[4] = {1.f, 1.f, 1.f, 1.f};
+    const int64_t next_row = unit * 16 + r;
+    float w[4] = {}, mask[4] = {1.f, 1.f, 1.f, 1.f}, h[MT][4];
     int32_t label = -1;
-    if constexpr (NEXT == RowsNext::GEMM) {
+    if constexpr (GRAD) {
+#pragma unroll
+        for (int t = 0; t < MT; ++t)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const int64_t hr = unit * 16 + 4 * s + kq;
+                h[t][s] = hr < nrows && 16 * t + r < nx.M ? nx.H[hr * nx.ldh + 16 * t + r] : 0.f;
+            }
+    }
+    if constexpr ((NEXT & RowsNext::GEMM) != 0) {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
             if (4 * kq + e < a.f && r < nx.N) w[e] = nx.transposed ? nx.W[r * a.f + 4 * kq + e] : nx.W[(4 * kq + e) * nx.N + r];
@@ -760,8 +777,38 @@ __global__ __launch_bounds__(64) void k_spmm_short(SplitArgs a, int64_t nrows, c
     const bool mine = row < nrows && col_ok;
     if (mine) epilogue_store<VEC, EPI>(a.Z + row * a.ldz + col0, EPI == GCN_EPI_MASK ? a.Zprev + row * a.ldzprev + col0 : nullptr, acc,
                                        a.row_scale ? a.row_scale[row] : 1.f, a.defer && a.defer[row]);
-    if constexpr (NEXT == RowsNext::GEMM) {                     // (all lanes)
-        typedef float floatx4 __attribute__((ext_vector_type(4)));
+    typedef float floatx4 __attribute__((ext_vector_type(4)));
+    if constexpr (GRAD) {
+        constexpr int ST = 20;                  // row stride of a wavefront's tile
+        __shared__ float s_rows[4][16 * ST];
+        __shared__ float4 s_sum[4][MT][64];
+        float* const tile = s_rows[wave];
+        *reinterpret_cast<float4*>(tile + (lane >> 2) * ST + 4 * li) =
+            mine ? make_float4(acc[0], acc[1], acc[2], acc[3]) : make_float4(0.f, 0.f, 0.f, 0.f);
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        float z[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) z[s] = tile[(4 * s + kq) * ST + r];
+#pragma unroll
+        for (int t = 0; t < MT; ++t) {
+            floatx4 y = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < 4; ++s) y = __builtin_amdgcn_mfma_f32_16x16x4f32(h[t][s], z[s], y, 0, 0, 0);
+            s_sum[wave][t][lane] = make_float4(y[0], y[1], y[2], y[3]);
+        }
+        __syncthreads();
+        if (wave < MT) {
+            const float4 p = s_sum[0][wave][lane], q = s_sum[1][wave][lane], u = s_sum[2][wave][lane], v = s_sum[3][wave][lane];
+            const float sum[4] = {((p.x + q.x) + u.x) + v.x, ((p.y + q.y) + u.y) + v.y, ((p.z + q.z) + u.z) + v.z, ((p.w + q.w) + u.w) + v.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int m = 16 * wave + 4 * kq + e;
+                if (m < nx.M && r < a.f) nx.ypart[((int64_t)blockIdx.x * nx.M + m) * a.f + r] = sum[e];
+            }
+        }
+    }
+    if constexpr ((NEXT & RowsNext::GEMM) != 0) {               // (all lanes)
         floatx4 t = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -805,7 +852,7 @@ __global__ __launch_bounds__(64) void k_spmm_short(SplitArgs a, int64_t nrows, c
         }
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) loss += __shfl_xor(loss, d, 64);
-        if (lane == 0) nx.part[blockIdx.x] = loss;
+        if (lane == 0) nx.part[unit] = loss;
     }
 }
 
@@ -1400,8 +1447,21 @@ static int launch_short(const SplitArgs& args, const Matrix& m, int epilogue, hi
     if (next && next->kind != RowsNext::NONE && epilogue != GCN_EPI_MASK && args.f % 4 == 0 && args.f <= 16) {
         const dim3 grid((unsigned)((nrows + 15) / 16));
         const RowsNext nx = *next;
+        auto gradient = [&](auto kinds, auto tiles) {
+            hipLaunchKernelGGL((k_spmm_short<4, 32, GCN_EPI_NONE, decltype(kinds)::value, decltype(tiles)::value>),
+                               dim3((unsigned)((nrows + 63) / 64)), dim3(256), 0, s, args, nrows, m.short_rows, m.short_pitch, nx);
+        };
+        constexpr std::integral_constant<int, RowsNext::GRAD> grad{};
+        constexpr std::integral_constant<int, RowsNext::GRAD | RowsNext::GEMM> both{};
+        constexpr std::integral_constant<int, 1> one{};
+        constexpr std::integral_constant<int, 4> four{};
         timing_begin(s);
-        if (nx.kind == RowsNext::LOSS)
+        if (nx.kind == grad) {
+            if (nx.M <= 16) gradient(grad, one);
+            else gradient(grad, four);
+        } else if (nx.kind == both) {           // (GEMM: M is at most 16)
+            gradient(both, one);
+        } else if (nx.kind == RowsNext::LOSS)
             hipLaunchKernelGGL((k_spmm_short<4, 32, GCN_EPI_NONE, RowsNext::LOSS>), grid, dim3(64), 0, s, args, nrows, m.short_rows,
                                m.short_pitch, nx);
         else if (epilogue == GCN_EPI_RELU)

@@ -1159,6 +1159,37 @@ def test_epoch_on_short_rows_is_the_calls_one_by_one(n, dims, rows):
     a.close()
 
 
+@pytest.mark.parametrize("n", [64, 65, 127, 129, 1023, 32_768])
+@pytest.mark.parametrize("dims", [(1, 16, 4), (15, 4, 4), (16, 16, 16), (17, 12, 8), (63, 16, 16, 12), (64, 8, 8, 4), (65, 16, 4)])
+def test_gradients_beside_short_rows(n, dims):
+    """Weight gradients made by the kernel of short rows, on both sides of its range (64 columns of H, 16 of Z), the last 64 rows not whole: as
+    close to 64 bits as single launches, and their bits; nothing is written behind the workspace."""
+    g = G()
+    rs = np.random.default_rng(171)
+    u, v = rs.integers(0, n, (2, 2 * n)).astype(np.int32)
+    a = g.gcn_csr_create(n, dev(u), dev(v), g.ADD_SELF_LOOPS | g.NORM_ROW | g.BUILD_TRANSPOSE)
+    assert "k_spmm_short" in g.gcn_spmm_describe(a, 0, dims[1])
+    H0, y = dev(synth.normal_features(n, dims[0], 172)), dev(rs.integers(0, dims[-1], n).astype(np.int32))
+    W, L = [dev(w) for w in synth.glorot_weights(dims, 173)], len(dims) - 1
+    Y, loss = [torch.full_like(w, float("nan")) for w in W], torch.zeros(1, device="cuda")
+    size = g.gcn_epoch_workspace_bytes(n, dims)
+    ws = torch.full((size + 4096,), 255, dtype=torch.uint8, device="cuda")
+    g.gcn_epoch(a, dims, H0, y, W, Y, 0.0, loss, ws[:size])
+    assert bool((ws[size:] == 255).all())
+    rowptr, col, val, _ = a.arrays()
+    A = torch.sparse_csr_tensor(rowptr, col.long(), val.double(), (n, n))
+    for l in range(L - 1, -1, -1):
+        Gl = g.gcn_epoch_view(n, dims, g.ORDER_AUTO, ws[:size], l + 1)[1]
+        Hin = g.gcn_epoch_view(n, dims, g.ORDER_AUTO, ws[:size], l)[0] if l else H0
+        if dims[l + 1] > dims[l]:
+            continue                                                # (A^T H first: another kernel's gradient)
+        assert_close(host(Y[l]), host(Hin.double().T @ (A @ Gl.double())), f"{n} {dims} layer {l + 1}")
+        S, want = torch.empty(n, dims[l + 1], device="cuda"), torch.empty_like(W[l])
+        g.gcn_layer_backward(a, Hin, None, W[l], Gl, None, S, want, None)
+        assert torch.equal(Y[l], want), (n, dims, l)
+    a.close()
+
+
 @pytest.mark.parametrize("f", [4, 7, 16, 20, 32, 41, 48, 64, 130])
 @pytest.mark.parametrize("pairs,loops,blocks", [(500, True, 0), (400_000, True, 1), (400_000, True, 3), (400_000, False, 1), (400_000, False, 3)])
 @pytest.mark.parametrize("values", [0, 1])
