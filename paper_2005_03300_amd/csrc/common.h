@@ -281,13 +281,15 @@ struct EpochEnd {
         int32_t count = 0, loss_at = -1;
         float lr = 0;
     } args;
-    struct Room {                                 // two pieces of memory, handed out first fit, and one for the gradients over few rows
-        static constexpr int PIECES = 3, FEW = 2;
+    struct Room {                                 // two pieces of memory, handed out first fit, and those for the gradients over few rows
+        static constexpr int FEW = 2, PIECES = FEW + MOST;
         char* at[PIECES] = {};
         size_t left[PIECES] = {};
         static size_t whole(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
         int fits(size_t bytes, bool few) const {
-            for (int k = few ? FEW : 0; k < (few ? PIECES : FEW); ++k)
+            for (int k = PIECES - 1; few && k >= FEW; --k)        // (the last layer's is asked for first)
+                if (whole(bytes) <= left[k]) return k;
+            for (int k = 0; k < FEW; ++k)
                 if (whole(bytes) <= left[k]) return k;
             return PIECES;
         }

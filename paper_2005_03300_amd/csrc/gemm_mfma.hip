@@ -826,7 +826,8 @@ static TnShape tn_shape(int64_t M, int64_t N, int64_t K) {
     const int64_t count = g.Mw * g.Nw;
     // or one trip of as few rows as a kernel of short rows takes, which then leaves the same partial results (see gradient_next; as a
     // launch of their own 64 x 16 over 16 K rows take 8.5 us, with two trips 8.3, over 2 K and 32 K, and other shapes, the same).
-    g.few = K <= 32768 && g.Mw <= 64 && g.Nw <= 16;
+    // Only where they take no more memory than K rows of Nw floats, which an epoch has (64 columns: whole shares).
+    g.few = K <= 32768 && g.Mw <= 64 && g.Nw <= 16 && (K + 63) / 64 * g.Mw <= K;
     int64_t blocks = g.few ? (K + rows - 1) / rows : K / (2 * rows);
     // but no more workgroups than run side by side: a workgroup loads its next trip while it multiplies, and the partial results
     // are written and read once more.  One per compute unit, two where the partial results are below 1/40 of the operands

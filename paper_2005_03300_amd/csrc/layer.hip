@@ -154,7 +154,6 @@ struct EpochLayout {
     size_t S = 0, XS = 0, total = 0;  // XS: pre-scaled SpMM operand of the value-free product
     size_t scratch = 0;               // partial sums of the fused last layer, and the next where they do not fit XS
     size_t part = 0, part_bytes = 0;  // partial sums of the weight gradients and of the loss
-    size_t few = 0;                   // those of the gradients over few rows (2 MB at the most each), which other idle memory need not hold
     std::vector<int> order;
 };
 
@@ -198,9 +197,6 @@ static EpochLayout epoch_layout(int64_t n, int32_t L, const int32_t* dims, int o
     lay.scratch = take((sc + sizeof(float) - 1) / sizeof(float));
     lay.part = tn > xs_bytes ? lay.scratch : lay.XS;
     lay.part_bytes = tn > xs_bytes ? sc : xs_bytes;
-    lay.few = off;
-    for (int l = 0; l < L; ++l)
-        if (gemm_tn_few(dims[l], dims[l + 1], n)) take((gemm_tn_scratch_bytes(dims[l], dims[l + 1], n) + sizeof(float) - 1) / sizeof(float));
     lay.total = off;
     return lay;
 }
@@ -220,16 +216,20 @@ static bool apart(int32_t L, const int32_t* dims, float* const* W, float* const*
 // saves are what a small epoch waits for: 4096 vertices, 64-16-8: 59 -> 50 us; 120 K vertices, 256-64-64-41: 1030 -> 1016).  In memory
 // that is idle from the loss on, so that the workspace is not larger for it: the region of the scaled operand where the products need none
 // (`value_free`), else the first layer's T, which forward has read by then or, with P0 given, nobody does; and the scratch unless the fused
-// last layer (`fuse`) has it.  The gradients over few rows, which have more partial results, have memory of their own.  All of them or none.
+// last layer (`fuse`) has it.  The gradients over few rows, which have more partial results, lie
+// in the T of layers whose forward product has read it (tn_shape sees to it that a layer's own would do).  All of them or none.
 static EpochEnd::Room end_room(const EpochLayout& lay, char* ws, int64_t n, int32_t L, const int32_t* dims, bool value_free, bool p0, bool fuse) {
     EpochEnd::Room room;
     if (L >= EpochEnd::MOST) return room;
     const bool t_idle = p0 || (lay.order[0] == GCN_ORDER_GEMM_FIRST && L >= 2);
     if (!value_free) { room.at[0] = ws + lay.XS; room.left[0] = lay.scratch - lay.XS; }
     else if (t_idle) { room.at[0] = ws + lay.T[0]; room.left[0] = lay.G[0] - lay.T[0]; }
-    if (!fuse) { room.at[1] = ws + lay.scratch; room.left[1] = lay.few - lay.scratch; }
-    room.at[EpochEnd::Room::FEW] = ws + lay.few;
-    room.left[EpochEnd::Room::FEW] = lay.total - lay.few;
+    if (!fuse) { room.at[1] = ws + lay.scratch; room.left[1] = lay.total - lay.scratch; }
+    for (int l = value_free && t_idle ? 1 : 0; l < L; ++l)
+        if (lay.order[l] == GCN_ORDER_GEMM_FIRST) {
+            room.at[EpochEnd::Room::FEW + l] = ws + lay.T[l];
+            room.left[EpochEnd::Room::FEW + l] = lay.G[l] - lay.T[l];
+        }
     EpochEnd::Room left = room;                   // in the order in which they are taken
     bool all = fuse || left.take(loss_part_bytes(n));
     for (int l = fuse ? L - 2 : L - 1; l >= 0 && all; --l)
