@@ -652,6 +652,163 @@ __global__ __launch_bounds__(256) void k_gemm_back(TnArgs a, const float* __rest
     a.part[(int64_t)blockIdx.x * 256 + o] = ((s_red[0][o] + s_red[1][o]) + s_red[2][o]) + s_red[3][o];
 }
 
+// The same for 16, 32 or 64 columns of Hin and up to as many of S.  A wavefront takes 16 rows and 16 MT columns of Hin and Gprev; of 64, a
+// pair of wavefronts shares the rows.  The first product takes a row's columns of S four at a time per lane, from memory, and W from LDS; the
+// second takes the same rows of S turned round in LDS, and two columns of Hin per lane, from memory.  The next 16 rows are on
+// their way.  Bound by memory and the fp32 matrix rate together: S is read once where k_gemm_tall and k_gemm_tn read it twice, and Hin once
+// where it is the mask.  Faster than the two at every size (rows 1 K to 1.5 M, 16 to 64 columns of Hin, 2 to 64 of S: 63 layer calls with a
+// product of two entries a row, 1.00 to 1.35 of the time before): 64 x 41 over 120 K rows 81 -> 75 us, 32 x 32 over 0.5 M 109 -> 87, 16 x 5 over 1.5 M
+// 117 -> 101, 64 x 8 over 5 K 14.3 -> 10.9.  256-64-64-41 on 120 K vertices 1016 -> 990 us an epoch.
+template <int NT, int MT, int MH>
+__global__ __launch_bounds__(256 * MH) void k_gemm_back_wide(TnArgs a, const float* __restrict__ W, const float* __restrict__ Zprev,
+                                                             float* __restrict__ Gprev) {
+    constexpr int M = 16 * MT * MH, WS = M + 4;              // row strides: the four quarters of a wavefront on banks of their own
+    constexpr int SS = NT == 1 ? 16 : (NT == 4 ? 80 : 48);
+    constexpr int SETS = 4, TILES = MT * NT;
+    constexpr int TILE_FLOATS = SETS * MH * 16 * SS, SUM_FLOATS = MH * TILES * 256;
+    __shared__ __attribute__((aligned(16))) float s_w[16 * NT * WS];
+    __shared__ __attribute__((aligned(16))) float s_s[TILE_FLOATS > SUM_FLOATS ? TILE_FLOATS : SUM_FLOATS];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int r = lane & 15, g = lane >> 4;
+    const int m0 = 16 * MT * (wave % MH), set = wave / MH;
+    const int N = a.N;
+    for (int j = threadIdx.x; j < 16 * NT * M; j += 256 * MH) {
+        const int m = j / (16 * NT), k = j % (16 * NT);
+        s_w[k * WS + m] = k < N ? W[m * N + k] : 0.f;
+    }
+    __syncthreads();
+    float* const ss = s_s + wave * (16 * SS);
+    const int64_t kb = (int64_t)blockIdx.x * a.k_per_block;
+    const int64_t ke = kb + a.k_per_block < a.K ? kb + a.k_per_block : a.K;
+    auto load_cols = [](float (&h)[MT], const float* p) {
+        if constexpr (MT == 2) {
+            const float2 v = *reinterpret_cast<const float2*>(p);
+            h[0] = v.x; h[1] = v.y;
+        } else h[0] = *p;
+    };
+    struct Rows { floatx4 s[NT], z[MT]; float h[4][MT]; };
+    auto fetch = [&](int64_t k0, Rows& x) {             // (rows past the end: the last one again)
+        const int64_t row = k0 + r < ke ? k0 + r : ke - 1;
+        const float* const sp = a.B + row * N + 4 * g;
+#pragma unroll
+        for (int q = 0; q < NT; ++q) {
+            const int left = N - 16 * q - 4 * g;        // columns from this lane's four on
+            if (q + 1 < NT || left >= 4) x.s[q] = *reinterpret_cast<const floatx4u*>(sp + 16 * q);
+            else x.s[q] = (floatx4){left > 0 ? sp[16 * q] : 0.f, left > 1 ? sp[16 * q + 1] : 0.f, left > 2 ? sp[16 * q + 2] : 0.f, 0.f};
+        }
+#pragma unroll
+        for (int t = 0; t < MT; ++t) x.z[t] = *reinterpret_cast<const floatx4*>(Zprev + row * M + m0 + 16 * t + 4 * g);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int64_t k = k0 + 4 * e + g < ke ? k0 + 4 * e + g : ke - 1;
+            load_cols(x.h[e], a.A + k * a.lda + m0 + MT * r);
+        }
+    };
+    floatx4 acc[MT][NT], total[MT][NT];
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int u = 0; u < NT; ++u) total[t][u] = acc[t][u] = (floatx4){0.f, 0.f, 0.f, 0.f};
+    auto multiply = [&](int64_t k0, Rows& x) {
+        if (k0 + 16 > ke) {
+#pragma unroll
+            for (int q = 0; q < NT; ++q)
+                if (k0 + r >= ke) x.s[q] = (floatx4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int t = 0; t < MT; ++t)
+                    if (k0 + 4 * e + g >= ke) x.h[e][t] = 0.f;
+        }
+        floatx4 d[MT];
+#pragma unroll
+        for (int t = 0; t < MT; ++t) d[t] = (floatx4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < NT; ++q) {
+            *reinterpret_cast<floatx4*>(ss + r * SS + 16 * q + 4 * g) = x.s[q];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int t = 0; t < MT; ++t)
+                    d[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(s_w[(16 * q + 4 * g + e) * WS + m0 + 16 * t + r], x.s[q][e], d[t], 0, 0, 0);
+        }
+        if (k0 + r < ke) {
+#pragma unroll
+            for (int t = 0; t < MT; ++t) {
+                floatx4 o;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) o[v] = x.z[t][v] > 0.f ? d[t][v] : 0.f;
+                *reinterpret_cast<floatx4*>(Gprev + (k0 + r) * M + m0 + 16 * t + 4 * g) = o;
+            }
+        }
+        // each wavefront reads only what it wrote; LDS operations of one wavefront complete in order
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int u = 0; u < NT; ++u) {
+                const float b = ss[(4 * e + g) * SS + 16 * u + r];
+#pragma unroll
+                for (int t = 0; t < MT; ++t) acc[t][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.h[e][t], b, acc[t][u], 0, 0, 0);
+            }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+    constexpr int STEP = 16 * SETS;
+    int64_t k0 = kb + 16 * set;
+    int trip = 0;
+    Rows x, y;
+    if (k0 < ke) fetch(k0, x);
+#pragma unroll 1
+    for (; k0 < ke; k0 += 2 * STEP) {
+        if (k0 + STEP < ke) fetch(k0 + STEP, y);
+        multiply(k0, x);
+        if (k0 + STEP < ke) {
+            if (k0 + 2 * STEP < ke) fetch(k0 + 2 * STEP, x);
+            multiply(k0 + STEP, y);
+        }
+        if ((++trip & 3) == 0) {                        // (as in k_gemm_tn)
+#pragma unroll
+            for (int t = 0; t < MT; ++t)
+#pragma unroll
+                for (int u = 0; u < NT; ++u) { total[t][u] += acc[t][u]; acc[t][u] = (floatx4){0.f, 0.f, 0.f, 0.f}; }
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int u = 0; u < NT; ++u) acc[t][u] += total[t][u];
+    // the sets of rows hold partial sums of the same tiles: added in order 0, 1, 2, 3
+    floatx4* const mine = reinterpret_cast<floatx4*>(s_s) + (wave % MH) * TILES * 64 + lane;
+    for (int w = 1; w < SETS; ++w) {
+        __syncthreads();
+        if (set == w) {
+#pragma unroll
+            for (int t = 0; t < MT; ++t)
+#pragma unroll
+                for (int u = 0; u < NT; ++u) mine[(t * NT + u) * 64] = acc[t][u];
+        }
+        __syncthreads();
+        if (set == 0) {
+#pragma unroll
+            for (int t = 0; t < MT; ++t)
+#pragma unroll
+                for (int u = 0; u < NT; ++u) acc[t][u] += mine[(t * NT + u) * 64];
+        }
+    }
+    if (set != 0) return;
+    // D[4 g + v][r] of tile (t, u) is Y[m0 + MT (4 g + v) + t][16 u + r]
+    float* const out = a.part + (int64_t)blockIdx.x * M * N;
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int u = 0; u < NT; ++u)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                if (16 * u + r < N) out[(int64_t)(m0 + MT * (4 * g + v) + t) * N + 16 * u + r] = acc[t][u][v];
+}
+
 // Stage 1 of the reduction when there are many partials: group g of `groups` sums the partials g, g+groups, ... in
 // ascending order (coalesced over the output index).
 __global__ __launch_bounds__(256) void k_tn_fold(int64_t count, int parts, int groups, const float* __restrict__ part,
@@ -868,6 +1025,16 @@ int reduce_parts_launch(int32_t M, int32_t N, int parts, bool transposed, const 
     return GCN_OK;
 }
 
+// The partial results that are left to add, after the first stage where there is one (in the same scratch, behind them).
+static const float* folded(const TnShape& g, int64_t count, float* part, hipStream_t s, int* parts) {
+    *parts = g.fold ? g.fold : (int)g.blocks;
+    if (!g.fold) return part;
+    float* const out = part + g.blocks * count;
+    hipLaunchKernelGGL(k_tn_fold, dim3((unsigned)((count + 255) / 256), (unsigned)g.fold), dim3(256), 0, s, count, (int)g.blocks, g.fold,
+                       (const float*)part, out);
+    return out;
+}
+
 size_t gemm_mfma_tn_scratch_bytes(int64_t M, int64_t N, int64_t K) {
     return tn_shape(M, N, K).scratch_bytes;
 }
@@ -993,17 +1160,9 @@ int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const floa
     GCN_TN_CASE(1, 2); GCN_TN_CASE(1, 3); GCN_TN_CASE(1, 4);
 #undef GCN_TN_CASE
     GCN_LAUNCH_CHECK();
-    const int64_t count = M * N;
-    const float* red_src = (const float*)scratch;
-    int red_parts = (int)g.blocks;
-    if (g.fold) {
-        float* folded = (float*)scratch + g.blocks * count;
-        hipLaunchKernelGGL(k_tn_fold, dim3((unsigned)((count + 255) / 256), (unsigned)g.fold), dim3(256), 0, s, count,
-                           (int)g.blocks, g.fold, (const float*)scratch, folded);
-        GCN_LAUNCH_CHECK();
-        red_src = folded;
-        red_parts = g.fold;
-    }
+    int red_parts;
+    const float* const red_src = folded(g, M * N, (float*)scratch, s, &red_parts);
+    GCN_LAUNCH_CHECK();
     *handled = true;
     if (later) {
         end->add(red_src, C, (int32_t)M, (int32_t)N, red_parts, g.swap);
@@ -1035,34 +1194,64 @@ static bool row_by_row(int64_t n, const float* Gprev, const float* M, int64_t ld
     return (M == Gprev && ld == 16) || M + (n - 1) * ld + 16 <= Gprev || Gprev + n * 16 <= M;
 }
 
-// Gprev = (S W^T) masked by Zprev, Y = Hin^T S; all of them 16 wide and their rows 16-byte aligned, or *handled stays false.  It also
+// Whether Gprev (n rows of M floats) shares no memory with a matrix of n rows of `cols` floats, `ld` apart.
+static bool no_rows_shared(int64_t n, int32_t M, const float* Gprev, const float* other, int32_t cols, int64_t ld) {
+    return other + (n - 1) * ld + cols <= Gprev || Gprev + n * M <= other;
+}
+
+// Gprev = (S W^T) masked by Zprev, Y = Hin^T S in one kernel, or *handled stays false: Hin 16, 32 or 64 wide, S up to as wide, rows of
+// Hin, Zprev and Gprev 16-byte aligned.  It also
 // stays false where Gprev lies across rows of an operand that another workgroup may not have read yet: the
 // two products one after the other read all of Hin before they write Gprev.
 int gemm_back_launch(int64_t n, int32_t f_in, int32_t f_out, const float* Hin, int64_t ldh, const float* S, const float* W,
                      const float* Zprev, float* Y, float* Gprev, hipStream_t s, bool* handled) {
     *handled = false;
-    if (f_in != 16 || f_out != 16 || n < 64 || ldh % 4 != 0 || !al16(Hin) || !al16(S) || !al16(Zprev) || !al16(Gprev)) return GCN_OK;
-    if (!row_by_row(n, Gprev, Hin, ldh) || !row_by_row(n, Gprev, S, 16) || !row_by_row(n, Gprev, Zprev, 16)) return GCN_OK;
-    const TnShape g = tn_shape(16, 16, n);
+    const bool wide = f_in != 16 || f_out != 16 || !al16(S);          // (k_gemm_back takes rows of S in whole pieces)
+    if (n < 64 || ldh % 4 != 0 || !al16(Hin) || !al16(Zprev) || !al16(Gprev)) return GCN_OK;
+    if (wide) {
+        if ((f_in != 16 && f_in != 32 && f_in != 64) || f_out > f_in) return GCN_OK;
+        if (!no_rows_shared(n, f_in, Gprev, Hin, f_in, ldh) || !no_rows_shared(n, f_in, Gprev, S, f_out, f_out) ||
+            !no_rows_shared(n, f_in, Gprev, Zprev, f_in, f_in)) return GCN_OK;
+        if (Y < W + f_in * f_out && W < Y + f_in * f_out) return GCN_OK;
+    } else {
+        if (!row_by_row(n, Gprev, Hin, ldh) || !row_by_row(n, Gprev, S, 16) || !row_by_row(n, Gprev, Zprev, 16)) return GCN_OK;
+    }
+    const TnShape g = tn_shape(f_in, f_out, n);
     EpochEnd* const end = epoch_end();
     void* scratch = end ? end->take(g.scratch_bytes, g.few) : nullptr;
     const bool later = scratch != nullptr;
     if (!later) GCN_TRY(scratch_get(&scratch, g.scratch_bytes, s));
     TnArgs args;
-    args.K = n; args.M = 16; args.N = 16;
-    args.A = Hin; args.lda = ldh; args.B = S; args.ldb = 16;
+    args.K = n; args.M = f_in; args.N = f_out;
+    args.A = Hin; args.lda = ldh; args.B = S; args.ldb = f_out;
     args.part = (float*)scratch; args.k_per_block = g.kpb;
     args.gw = args.rw = 1;
     const dim3 grid((unsigned)g.blocks);
-    if (Zprev == Hin && ldh == 16) hipLaunchKernelGGL(k_gemm_back<true>, grid, dim3(256), 0, s, args, W, Zprev, Gprev);
+    if (wide) {
+        const int nt = (f_out + 15) / 16;
+        if (f_in == 16) hipLaunchKernelGGL((k_gemm_back_wide<1, 1, 1>), grid, dim3(256), 0, s, args, W, Zprev, Gprev);
+        else if (f_in == 32) {
+            if (nt == 1) hipLaunchKernelGGL((k_gemm_back_wide<1, 2, 1>), grid, dim3(256), 0, s, args, W, Zprev, Gprev);
+            else hipLaunchKernelGGL((k_gemm_back_wide<2, 2, 1>), grid, dim3(256), 0, s, args, W, Zprev, Gprev);
+        } else {
+            if (nt == 1) hipLaunchKernelGGL((k_gemm_back_wide<1, 2, 2>), grid, dim3(512), 0, s, args, W, Zprev, Gprev);
+            else if (nt == 2) hipLaunchKernelGGL((k_gemm_back_wide<2, 2, 2>), grid, dim3(512), 0, s, args, W, Zprev, Gprev);
+            else if (nt == 3) hipLaunchKernelGGL((k_gemm_back_wide<3, 2, 2>), grid, dim3(512), 0, s, args, W, Zprev, Gprev);
+            else hipLaunchKernelGGL((k_gemm_back_wide<4, 2, 2>), grid, dim3(512), 0, s, args, W, Zprev, Gprev);
+        }
+    } else if (Zprev == Hin && ldh == 16) hipLaunchKernelGGL(k_gemm_back<true>, grid, dim3(256), 0, s, args, W, Zprev, Gprev);
     else hipLaunchKernelGGL(k_gemm_back<false>, grid, dim3(256), 0, s, args, W, Zprev, Gprev);
+    GCN_LAUNCH_CHECK();
+    const float* part = (const float*)scratch;
+    int parts = (int)g.blocks;
+    if (wide) part = folded(g, (int64_t)f_in * f_out, (float*)scratch, s, &parts);
     GCN_LAUNCH_CHECK();
     *handled = true;
     if (later) {
-        end->add((const float*)scratch, Y, 16, 16, (int)g.blocks, false);
+        end->add(part, Y, f_in, f_out, parts, false);
         return GCN_OK;
     }
-    return reduce_parts_launch(16, 16, (int)g.blocks, false, (const float*)scratch, Y, 16, nullptr, GCN_EPI_NONE, nullptr, 0, s);
+    return reduce_parts_launch(f_in, f_out, parts, false, part, Y, f_out, nullptr, GCN_EPI_NONE, nullptr, 0, s);
 }
 
 }  // namespace gcn

@@ -1262,6 +1262,42 @@ def test_backward_products_of_width_16(n, pad, own):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("n", [63, 64, 65, 79, 127, 129, 1000, 33_000, 70_001])
+@pytest.mark.parametrize("f_in,f_out", [(16, 1), (16, 5), (16, 15), (16, 16), (32, 3), (32, 16), (32, 17), (32, 32), (64, 2), (64, 16), (64, 17), (64, 33), (64, 41),
+                                        (64, 48), (64, 49), (64, 64)])
+@pytest.mark.parametrize("pad,own", [(0, True), (4, False), (1, False)])
+def test_backward_products_of_one_pass(n, f_in, f_out, pad, own):
+    """Y = H^T S and Gprev = (S W^T) masked where they are one kernel (not: pitches that are no whole 16 bytes, below 64 rows, Gprev over H):
+    columns and rows of S at the edges of its tiles and trips, S at no 16-byte address.  Gprev has the bits of the product of its own."""
+    g = G()
+    rs = np.random.default_rng(244)
+    a = g.gcn_csr_create(n, *[dev(rs.integers(0, n, n).astype(np.int32)) for _ in range(2)], g.ADD_SELF_LOOPS | g.NORM_ROW | g.BUILD_TRANSPOSE)
+    H, Zp, W, Gm = [synth.normal_features(r, c, 245 + i) for i, (r, c) in enumerate(((n, f_in), (n, f_in), (f_in, f_out), (n, f_out)))]
+    Hd = torch.full((n, f_in + pad), float("nan"), device="cuda")
+    Hd[:, :f_in] = dev(H)
+    Hd, Wd, Gd = Hd[:, :f_in], dev(W), dev(Gm)
+    Zd = Hd if own else dev(Zp)
+    S = torch.full((n * f_out + 2,), float("nan"), device="cuda")[1:-1].view(n, f_out)
+    Y = torch.full((f_in, f_out), float("nan"), device="cuda")
+    Gp = torch.full((n + 2, f_in), float("nan"), device="cuda")
+    g.gcn_layer_backward(a, Hd, Zd, Wd, Gd, None, S, Y, Gp[1:-1], g.ORDER_GEMM_FIRST)
+    Sx = S.double()
+    wantY, scale = Hd.double().T @ Sx, float((Hd.double().T.abs() @ Sx.abs()).norm())
+    # sums of up to 70 K products, in chains of 128 and the sums of those: a few roundings of the sums' size, which is below that of the magnitudes
+    assert float((Y.double() - wantY).norm()) <= 4 * 2.0 ** -24 * scale
+    plain = torch.empty(n, f_in, device="cuda")
+    g.gcn_gemm(0, 1, S, Wd, plain, epilogue=g.EPI_MASK, Zprev=Zd)
+    assert torch.equal(Gp[1:-1], plain)
+    assert_close(host(plain), host(torch.where(Zd > 0, Sx @ Wd.double().T, 0.0)), f"{n} {f_in} {f_out}")
+    assert bool(torch.isnan(Gp[0]).all() and torch.isnan(Gp[-1]).all())
+    if pad == 0:
+        over, first = torch.clone(Hd), Y.clone()
+        g.gcn_layer_backward(a, over, over, Wd, Gd, None, S, Y, over, g.ORDER_GEMM_FIRST)
+        assert torch.equal(over, plain) and float((Y - first).norm()) <= 4 * 2.0 ** -24 * scale
+    a.close()
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("n", [64, 1000, 70_001])
 @pytest.mark.parametrize("ldh,first,over", [(20, 0, 0), (20, 0, 4), (16, 16, 0), (16, 0, 16), (24, 8, 0)])
 def test_backward_products_of_width_16_with_gprev_across_the_rows_of_h(n, ldh, first, over):
