@@ -5,7 +5,9 @@
 // L lanes share a row and keep its logits in registers (four per lane, C <= 4 L): one read of Z,
 // one write of G, 16 bytes per lane at any alignment, what is left of a ragged row one by one.  Bound by the instructions of the
 // reductions where a row is short: with a column per lane a wavefront had one row of 41, now it has four (200 K rows: 44.7 -> 26.8
-// us; 300 K rows of 130, three passes before, 232 -> 129 us).  Row maxima and sums are butterfly reductions inside the L lanes.  Workgroups
+// us; 300 K rows of 130, three passes before, 232 -> 129 us), and of the exponentials: one per logit, whose share of the row's sum is the
+// softmax (a second one, of z - lse, made 200 K rows of 41 25.2 us, now 21.9; 1 M 116 and 94; 120 K of 200 46.5 and 39.4; nearer to 64 bits too,
+// G's error 6.5e-8 of its norm and 4.7e-8).  Row maxima and sums are butterfly reductions inside the L lanes.  Workgroups
 // stride over the rows; every thread adds its rows' losses in double in a fixed order, then a
 // fixed tree joins threads and workgroups, so the loss is reproducible bit for bit.
 #include "common.h"
@@ -44,9 +46,12 @@ __global__ __launch_bounds__(256) void k_softmax_nll(int64_t n, int32_t C, const
         for (int e = 1; e < VEC; ++e) m = fmaxf(m, v[e]);
 #pragma unroll
         for (int d = L / 2; d >= 1; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, 64));
-        float ssum = 0.f;
+        float p[VEC], ssum = 0.f;
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) ssum += expf(v[e] - m);          // exp(-inf) = 0 for padding lanes
+        for (int e = 0; e < VEC; ++e) {
+            p[e] = expf(v[e] - m);                  // exp(-inf) = 0 for padding lanes
+            ssum += p[e];
+        }
 #pragma unroll
         for (int d = L / 2; d >= 1; d >>= 1) ssum += __shfl_xor(ssum, d, 64);
         const float lse = m + logf(ssum);
@@ -55,9 +60,10 @@ __global__ __launch_bounds__(256) void k_softmax_nll(int64_t n, int32_t C, const
         y = y < 0 ? 0 : (y >= C ? C - 1 : y);   // labels >= C are the caller's error; stay in bounds
         if (G && c0 < C) {
             float g[4] = {};
+            const float inv = 1.f / ssum;
 #pragma unroll
             for (int e = 0; e < VEC; ++e)
-                g[e] = labelled ? (expf(v[e] - lse) - (c0 + e == y ? 1.f : 0.f)) * inv_n : 0.f;
+                g[e] = labelled ? (p[e] * inv - (c0 + e == y ? 1.f : 0.f)) * inv_n : 0.f;
             if (!RAGGED && whole) *reinterpret_cast<float4*>(G + i * ldg + c0) = make_float4(g[0], g[1], g[2], g[3]);
             else if (whole) *reinterpret_cast<f4u*>(G + i * ldg + c0) = f4u{g[0], g[1], g[2], g[3]};
             else if constexpr (RAGGED) {

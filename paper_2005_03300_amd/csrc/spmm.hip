@@ -831,9 +831,12 @@ __global__ __launch_bounds__(NEXT & RowsNext::GRAD ? 256 : 64) void k_spmm_short
         for (int e = 1; e < 4; ++e) m = fmaxf(m, v[e]);
         m = fmaxf(m, __shfl_xor(m, 2, 64));
         m = fmaxf(m, __shfl_xor(m, 1, 64));
-        float sum = 0.f;
+        float p[4], sum = 0.f;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) sum += expf(v[e] - m);      // exp(-inf) = 0 behind the last class
+        for (int e = 0; e < 4; ++e) {
+            p[e] = expf(v[e] - m);              // exp(-inf) = 0 behind the last class
+            sum += p[e];
+        }
         sum += __shfl_xor(sum, 2, 64);
         sum += __shfl_xor(sum, 1, 64);
         const float lse = m + logf(sum);
@@ -842,9 +845,10 @@ __global__ __launch_bounds__(NEXT & RowsNext::GRAD ? 256 : 64) void k_spmm_short
         double loss = 0.0;
         if (mine) {
             float d[4], zy = 0.f;
+            const float inv = 1.f / sum;        // (as k_softmax_nll)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                d[e] = labelled ? (expf(v[e] - lse) - (col0 + e == y ? 1.f : 0.f)) * nx.inv_m : 0.f;
+                d[e] = labelled ? (p[e] * inv - (col0 + e == y ? 1.f : 0.f)) * nx.inv_m : 0.f;
                 zy = col0 + e == y ? v[e] : zy;
             }
             store_vec<4>(nx.G + row * a.f + col0, d);
