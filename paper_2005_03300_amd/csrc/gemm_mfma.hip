@@ -97,15 +97,17 @@ __device__ __forceinline__ void stage_b(const TallArgs& a, int n0, float* Bs) {
     }
 }
 
-// TR: the two MFMA operands are swapped, so a lane ends up with four consecutive columns of one
-// row of C (element v of tile t is C[row0 + l%16][16t + 4*(l/16) + v]) and stores them with one
-// 16-byte instruction; needs N % 4 == 0 and 16-byte aligned rows of C (and of Zprev for the mask).
+// The two MFMA operands are swapped, so a lane ends up with four consecutive columns of one row of C (element v of tile t is
+// C[row0 + l%16][16t + 4*(l/16) + v]) and stores them with one instruction.  WIDE: N % 4 == 0 and 16-byte aligned rows of C (and of Zprev for
+// the mask); else at any address (with the operands
+// the other way round, single columns of four rows per lane and store: 1.5 M x 16 x 15 41 -> 33 us, x 41 164 -> 116; 0.2 M x 602 x 41 200 -> 166).
 // ASC: the products of an element of C are added in ascending k, like the chain of the plain kernel: an instruction
 // adds its four products in the order of the lane quarters, so quarter kq has to supply k = k0 + 4e + kq to instruction
 // e, and the 16 bytes that it loads at k0 + 4 kq are exchanged between the quarters (a 4 x 4 transposition, four
-// instructions).  Without it instruction e takes k = k0 + 4 kq + e.
-template <int NT, int EPI, bool TR, bool ASC>
-__global__ __launch_bounds__(512) void k_gemm_tall(TallArgs a) {
+// instructions).  Without it instruction e takes k = k0 + 4 kq + e.  op(B) leaves its workgroups no more than four wavefronts to a SIMD, so that
+// the compiler need not save registers for eight (which put fewer reads of it together: 0.2 M x 602 x 41 223 us and 170).
+template <int NT, int EPI, bool WIDE, bool ASC>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, ASC ? 4 : 8))) void k_gemm_tall(TallArgs a) {
     extern __shared__ float Bs[];                       // [Kpad][S]
     const int n0 = blockIdx.y * (NT * 16);
     stage_b<NT>(a, n0, Bs);
@@ -137,8 +139,7 @@ __global__ __launch_bounds__(512) void k_gemm_tall(TallArgs a) {
                     const float* bp = Bs + (k0 + 16 * s + (ASC ? 4 * e + kq : 4 * kq + e)) * a.S + r;
 #pragma unroll
                     for (int t = 0; t < NT; ++t)
-                        acc[t] = TR ? __builtin_amdgcn_mfma_f32_16x16x4f32(bp[16 * t], ae[e], acc[t], 0, 0, 0)
-                                    : __builtin_amdgcn_mfma_f32_16x16x4f32(ae[e], bp[16 * t], acc[t], 0, 0, 0);
+                        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(bp[16 * t], ae[e], acc[t], 0, 0, 0);
                 }
             }
         }
@@ -151,8 +152,7 @@ __global__ __launch_bounds__(512) void k_gemm_tall(TallArgs a) {
                 const float* bp = Bs + (k0 + (ASC ? 4 * e + kq : 4 * kq + e)) * a.S + r;
 #pragma unroll
                 for (int t = 0; t < NT; ++t)
-                    acc[t] = TR ? __builtin_amdgcn_mfma_f32_16x16x4f32(bp[16 * t], ae[e], acc[t], 0, 0, 0)
-                                : __builtin_amdgcn_mfma_f32_16x16x4f32(ae[e], bp[16 * t], acc[t], 0, 0, 0);
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(bp[16 * t], ae[e], acc[t], 0, 0, 0);
             }
         }
         if (k0 < a.K) {                                 // ragged tail (fewer than 16 columns left)
@@ -175,12 +175,11 @@ __global__ __launch_bounds__(512) void k_gemm_tall(TallArgs a) {
                 const float* bp = Bs + k * a.S + r;     // rows K..Kpad-1 of Bs are zero
 #pragma unroll
                 for (int t = 0; t < NT; ++t)
-                    acc[t] = TR ? __builtin_amdgcn_mfma_f32_16x16x4f32(bp[16 * t], ae, acc[t], 0, 0, 0)
-                                : __builtin_amdgcn_mfma_f32_16x16x4f32(ae, bp[16 * t], acc[t], 0, 0, 0);
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(bp[16 * t], ae, acc[t], 0, 0, 0);
             }
         }
-        if constexpr (TR) {
-            const int64_t row = row0 + r;
+        const int64_t row = row0 + r;
+        if constexpr (WIDE) {
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 const int col = n0 + 16 * t + 4 * kq;           // N % 4 == 0: the four columns exist together
@@ -205,17 +204,48 @@ __global__ __launch_bounds__(512) void k_gemm_tall(TallArgs a) {
             }
             continue;
         }
+        // The last two or three columns of a row leave with those before them, which another lane stores too, with the same bits (one by
+        // one they made 1.5 M x 16 x 31 90 us, now 65; 1 M x 64 x 23 75, now 64).
+        const int tail = a.N & 3;
+        const bool shift = tail >= 2 && (a.N & 15) > 4;
+        floatx4 left4[NT];
+        if (shift) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) left4[t][v] = v < 2 ? 0.f : __shfl_up(acc[t][v], 16, 64);
+        }
+        if (row >= a.M) continue;
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-            const int col = n0 + 16 * t + r;
-            if (col >= a.N) continue;
-            const float b = a.bias ? a.bias[col] : 0.f;
+            int col = n0 + 16 * t + 4 * kq, left = a.N - col;
+            if (left <= 0) continue;
+            if (shift && left < 4) {
+                acc[t] = tail == 2 ? (floatx4){left4[t][2], left4[t][3], acc[t][0], acc[t][1]}
+                                   : (floatx4){left4[t][3], acc[t][0], acc[t][1], acc[t][2]};
+                col -= 4 - left;
+                left = 4;
+            }
+            float* const c = a.C + row * a.ldc + col;
+            const float* const z = EPI == GCN_EPI_MASK ? a.Zprev + row * a.ldzprev + col : nullptr;
+            float o[4] = {acc[t][0], acc[t][1], acc[t][2], acc[t][3]};
+            if (left >= 4) {
+                if (a.bias) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int64_t row = row0 + 4 * kq + v;
-                if (row < a.M)
-                    a.C[row * a.ldc + col] =
-                        epi<EPI>(acc[t][v] + b, EPI == GCN_EPI_MASK ? a.Zprev + row * a.ldzprev + col : nullptr);
+                    for (int v = 0; v < 4; ++v) o[v] += a.bias[col + v];
+                }
+                float m[4] = {};
+                if (EPI == GCN_EPI_MASK) {
+                    const float4 x = load4(z);
+                    m[0] = x.x; m[1] = x.y; m[2] = x.z; m[3] = x.w;
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) o[v] = epi<EPI>(o[v], m + v);
+                *reinterpret_cast<floatx4u*>(c) = (floatx4){o[0], o[1], o[2], o[3]};
+            } else {
+#pragma unroll
+                for (int v = 0; v < 3; ++v)
+                    if (v < left) c[v] = epi<EPI>(o[v] + (a.bias ? a.bias[col + v] : 0.f), EPI == GCN_EPI_MASK ? z + v : nullptr);
             }
         }
     }
@@ -882,12 +912,12 @@ int EpochEnd::finish(float lr, hipStream_t s) {
 
 static inline bool al16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
-template <int NT, bool TR, bool ASC>
+template <int NT, bool WIDE, bool ASC>
 static void launch_tall_epi(const TallArgs& args, int epilogue, dim3 grid, int threads, size_t lds, hipStream_t s) {
     switch (epilogue) {
-        case GCN_EPI_NONE: launch_lds<k_gemm_tall<NT, GCN_EPI_NONE, TR, ASC>>(grid, threads, lds, s, args); break;
-        case GCN_EPI_RELU: launch_lds<k_gemm_tall<NT, GCN_EPI_RELU, TR, ASC>>(grid, threads, lds, s, args); break;
-        default: launch_lds<k_gemm_tall<NT, GCN_EPI_MASK, TR, ASC>>(grid, threads, lds, s, args); break;
+        case GCN_EPI_NONE: launch_lds<k_gemm_tall<NT, GCN_EPI_NONE, WIDE, ASC>>(grid, threads, lds, s, args); break;
+        case GCN_EPI_RELU: launch_lds<k_gemm_tall<NT, GCN_EPI_RELU, WIDE, ASC>>(grid, threads, lds, s, args); break;
+        default: launch_lds<k_gemm_tall<NT, GCN_EPI_MASK, WIDE, ASC>>(grid, threads, lds, s, args); break;
     }
 }
 
@@ -1110,14 +1140,13 @@ int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const floa
         }
         // Eight wavefronts share op(B), and no more workgroups than two per compute unit (one where op(B) allows no two) put it into
         // LDS: 128 x 64 on 200 K rows 59 us with 1536 workgroups of four, 40 with 512 of eight; 64 x 64 on 120 K rows 21 and
-        // 17; 16 x 16 on 4.4 M 110 and 100.  Four per compute unit where a strip leaves in two tiles of single floats, whose stores take
-        // longer than the rest (32 x 23 on 2.4 M 201 and 157; with one tile four take 1.03 of the time, with three 1.07), or of 16 bytes while
+        // 17; 16 x 16 on 4.4 M 110 and 100.  Four per compute unit where a strip leaves in two tiles while
         // operand and result are in the memory-side cache (32 x 32 on 400 K 20.6 and 18.5, on 820 K 37.0 and 34.4; on 1.8 M
-        // 98 and 105).
+        // 98 and 105; 64 x 31 on 1 M 87 and 93).
         const int64_t panels = (nt_total + NT - 1) / NT;
         const int waves = tall_waves(ntiles, panels, K, device_info().cus);
         int64_t bx = (ntiles + waves - 1) / waves;
-        const bool four = NT == 2 && lds <= 40 * 1024 && (!wide_c || M * (K + N) * 4 < (192ll << 20));
+        const bool four = NT == 2 && lds <= 40 * 1024 && M * (K + N) * 4 < (192ll << 20);
         const int64_t cap = (int64_t)device_info().cus * (lds > 80 * 1024 ? 1 : (four ? 4 : 2));
         if (bx > cap) bx = cap;
         const dim3 grid((unsigned)bx, (unsigned)panels);

@@ -1262,6 +1262,34 @@ def test_backward_products_of_width_16(n, pad, own):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("N", [1, 2, 3, 5, 6, 7, 15, 17, 18, 19, 21, 22, 23, 31, 33, 35, 41, 47, 63, 65, 66, 67, 70, 80, 96, 130, 131])
+@pytest.mark.parametrize("M,K,tb", [(64, 16, 0), (79, 3, 0), (1001, 64, 0), (1001, 64, 1), (333, 300, 0), (333, 602, 0), (5000, 41, 1)])
+def test_dense_products_of_ragged_rows(M, K, tb, N):
+    """Rows of C that are no whole 16 bytes: the last columns alone in their tile or behind others of it, in one or more shares of the columns, C at any
+    address and pitch; bias and both epilogues; nothing between the rows is written.  The same bits as in rows at a pitch of 16 bytes."""
+    g = G()
+    A, B = synth.normal_features(M, K, 301), synth.normal_features(*((N, K) if tb else (K, N)), 302)
+    bias, Zp = synth.normal_features(1, N, 303)[0], synth.normal_features(M, N, 304)
+    plain = A.astype(np.float64) @ (B.T if tb else B).astype(np.float64)
+    Ad, Bd, bd, Zd = dev(A), dev(B), dev(bias), dev(Zp)
+    # a chain of K products, each step rounded once at the size of the sum of magnitudes, and the bias
+    bound = (K + 2) * 2.0 ** -24 * (np.abs(A).astype(np.float64) @ np.abs(B.T if tb else B) + np.abs(bias)) + 1e-30
+    for epilogue, want in ((g.EPI_NONE, plain + bias), (g.EPI_RELU, np.maximum(plain + bias, 0)), (g.EPI_MASK, np.where(Zp > 0, plain + bias, 0))):
+        got = []
+        for pitch, first in ((N, 0), (N + 1, 3), ((N + 3) // 4 * 4, 0)):
+            memory = torch.full((M * pitch + 8,), 7.0, device="cuda")
+            C = memory[first:first + M * pitch].view(M, pitch)[:, :N]
+            Z = torch.full((M, (N + 3) // 4 * 4), float("nan"), device="cuda")[:, :N]
+            Z.copy_(Zd)
+            g.gcn_gemm(0, tb, Ad, Bd, C, bias=bd, epilogue=epilogue, Zprev=Z if epilogue == g.EPI_MASK else None)
+            got.append(C.clone())
+            assert np.all(np.abs(host(C) - want) <= bound), (pitch, epilogue)
+            C.fill_(7.0)
+            assert bool((memory == 7.0).all()), (pitch, epilogue)
+        assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("n", [63, 64, 65, 79, 127, 129, 1000, 33_000, 70_001])
 @pytest.mark.parametrize("f_in,f_out", [(16, 1), (16, 5), (16, 15), (16, 16), (32, 3), (32, 16), (32, 17), (32, 32), (64, 2), (64, 16), (64, 17), (64, 33), (64, 41),
                                         (64, 48), (64, 49), (64, 64)])
