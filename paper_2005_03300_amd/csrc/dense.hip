@@ -206,13 +206,19 @@ int gemm_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const float* A,
 int colsum_launch(int64_t rows, int32_t cols, const float* G, int64_t ldg, float* out, hipStream_t s) {
     int64_t parts = 0, rpb = 0;
     colsum_split(rows, &parts, &rpb);
-    void* scratch = nullptr;
-    GCN_TRY(scratch_get(&scratch, (size_t)parts * cols * sizeof(float), s));
+    EpochEnd* const end = epoch_end();
+    void* scratch = end ? end->take((size_t)parts * cols * sizeof(float)) : nullptr;
+    const bool later = scratch != nullptr;
+    if (!later) GCN_TRY(scratch_get(&scratch, (size_t)parts * cols * sizeof(float), s));
     int tx = 64;
     while (tx > 4 && tx / 2 >= cols) tx /= 2;
     hipLaunchKernelGGL(k_colsum_partial, dim3((unsigned)parts, (unsigned)((cols + tx - 1) / tx)), dim3(tx, 256 / tx), 0, s, rows,
                        cols, rpb, G, ldg, (float*)scratch);
     GCN_LAUNCH_CHECK();
+    if (later) {
+        end->add((const float*)scratch, out, 1, cols, (int)parts, false);
+        return GCN_OK;
+    }
     return reduce_parts_launch(1, cols, (int)parts, false, (const float*)scratch, out, cols, nullptr, GCN_EPI_NONE, nullptr, 0, s);
 }
 

