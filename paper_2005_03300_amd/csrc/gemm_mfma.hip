@@ -258,6 +258,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, ASC ? 4 
 // LDS buffer and takes the MFMA operands from there; the loads of the next strip are in flight (in registers)
 // while the current strip is multiplied.  Needs lda == K, K % 4 == 0, 16-byte aligned A, and the wide store path
 // (N % 4 == 0, aligned C).  KV = 16-byte loads per lane and strip = ceil(K / 16).
+// A wavefront keeps the results of `held` strips in LDS, where they leave room for as many workgroups, and stores them in one burst: single kilobytes
+// of writes among the reads of all memory cost more than their share (300 x 16 over 1.8 M rows 429 -> 397 us, 228 x 12 over 3 M 606 -> 540; the
+// same reads without any store 2.77 ms of 3.46 on 14 M).
+template <int NT, int KV>
+constexpr int FLAT_HELD = NT == 1 && KV == 19 ? 8 : 0;
 template <int NT, int EPI, int KV>
 __global__ __launch_bounds__(512) void k_gemm_tall_flat(TallArgs a) {
     extern __shared__ float lds[];
@@ -273,6 +278,10 @@ __global__ __launch_bounds__(512) void k_gemm_tall_flat(TallArgs a) {
     const int64_t ntiles = (a.M + 15) / 16;
     const int64_t total = a.M * (int64_t)a.K;           // floats of A
     const int64_t stride = (int64_t)gridDim.x * waves;
+    constexpr int HELD = FLAT_HELD<NT, KV>;
+    float* const Cs = lds + a.Kpad * a.S + (blockDim.x >> 6) * (KV * 256) + (threadIdx.x >> 6) * (HELD * 256);
+    int held = 0;
+    int64_t first = 0;                                  // of the strips held
     float4 pre[KV];
     auto fetch = [&](int64_t tile) {
         const int64_t base = tile * strip_floats;
@@ -341,7 +350,22 @@ __global__ __launch_bounds__(512) void k_gemm_tall_flat(TallArgs a) {
                 const float rs = a.row_scale[row];
                 o.x *= rs; o.y *= rs; o.z *= rs; o.w *= rs;
             }
-            *reinterpret_cast<float4*>(a.C + row * a.ldc + col) = o;
+            if constexpr (HELD) *reinterpret_cast<float4*>(Cs + held * 256 + r * 16 + 4 * kq) = o;
+            else *reinterpret_cast<float4*>(a.C + row * a.ldc + col) = o;
+        }
+        if constexpr (HELD) {
+            if (held == 0) first = tile;
+            if (++held == HELD || tile + stride >= ntiles) {
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                const int col = n0 + 4 * (lane & 3);
+#pragma unroll 4
+                for (int u = 0; u < held; ++u) {
+                    const int64_t to = (first + u * stride) * 16 + (lane >> 2);
+                    if (col < a.N && to < a.M) *reinterpret_cast<float4*>(a.C + to * a.ldc + col) = *reinterpret_cast<const float4*>(Cs + u * 256 + lane * 4);
+                }
+                held = 0;
+            }
         }
         // the next strip overwrites As: this wavefront's LDS operations complete in order
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -1128,7 +1152,8 @@ int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const floa
             // 300 floats: 2: 4.15, 3: 4.29, 4: 3.57, 5: 3.87, 6: 3.74 ms (the same ranking at 64, 128 and 192 floats)
             int fw = (int)((150 * 1024 - (int64_t)lds) / ((int64_t)KV * 256 * sizeof(float)));
             fw = fw > 4 ? 4 : fw;
-            const size_t lds_flat = lds + (size_t)(fw > 0 ? fw : 1) * KV * 256 * sizeof(float);
+            const int held = NT == 1 && KV == 19 ? FLAT_HELD<1, 19> : 0;
+            const size_t lds_flat = lds + (size_t)(fw > 0 ? fw : 1) * (KV + held) * 256 * sizeof(float);
             if (strips && fw >= 2 && wide && !ascending && lda == K && (K % 4) == 0 && (((K * 4) % 128) != 0 || K <= 208) && K >= 64 && kv_need <= 19 && NT <= 2 && al16(A) &&
                 lds_flat <= 150 * 1024) {
                 int64_t fb = (ntiles + fw - 1) / fw;

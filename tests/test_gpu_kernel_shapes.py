@@ -1262,6 +1262,25 @@ def test_backward_products_of_width_16(n, pad, own):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("M,K", [(195_768, 300), (200_003, 300), (277_000, 212), (262_161, 228), (400_001, 148), (459_000, 128)])
+@pytest.mark.parametrize("N", [4, 12, 16])
+def test_dense_products_beyond_the_caches(M, K, N):
+    """Strips through LDS, whose results leave in bursts: the last burst of every wavefront not whole, the last strip not either, columns behind the
+    last one; all epilogues, and the rows around C untouched."""
+    g = G()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(321)
+    A, B, bias, Zp = [torch.randn(r, c, generator=gen, device="cuda") for r, c in ((M, K), (K, N), (1, N), (M, N))]
+    plain = A.double() @ B.double() + bias.double()
+    bound = (K + 2) * 2.0 ** -24 * (A.abs().double() @ B.abs().double() + bias.abs().double())
+    for epilogue, want in ((g.EPI_NONE, plain), (g.EPI_RELU, plain.clamp(min=0)), (g.EPI_MASK, torch.where(Zp > 0, plain, 0.0))):
+        C = torch.full((M + 2, N), float("nan"), device="cuda")
+        g.gcn_gemm(0, 0, A, B, C[1:-1], bias=bias.view(-1), epilogue=epilogue, Zprev=Zp if epilogue == g.EPI_MASK else None)
+        assert bool(((C[1:-1].double() - want).abs() <= bound).all()), epilogue
+        assert bool(torch.isnan(C[0]).all() and torch.isnan(C[-1]).all())
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("n", [1, 63, 1000, 33_000])
 @pytest.mark.parametrize("f_in,f_out", [(1, 1), (16, 16), (64, 41), (300, 16), (20, 70), (16, 200)])
 def test_bias_gradient_beside_the_weight_gradient(n, f_in, f_out):
