@@ -685,9 +685,12 @@ __device__ __forceinline__ int group_lane(int x, int l) {
 // are added up as k_gemm_tn and k_gemm_tn_narrow do it over 64 rows.  It makes the kernel 1 to 2 us longer and saves a launch per layer: epochs of
 // 64-16-8 on 4096 vertices 38.7 -> 34.4 us, 64-16-16-8 54.7 -> 49.9, 50-16-12 on 10 K 45.9 -> 39.9, 100-16-4 on 30 K 56.6 -> 54.2.  Workgroups of
 // eight wavefronts, whose partial results are half as many, took 4 us longer each: fewer compute units fetch the rows.
+struct NoNext {};                                 // (without arguments that it does not read, two products of 1000 rows take 10.4 us and not 10.6)
+template <int NEXT>
+using NextArgs = std::conditional_t<NEXT == RowsNext::NONE, NoNext, RowsNext>;
 template <int LPR, int SLICE, int EPI, int NEXT = RowsNext::NONE, int MT = 1>
 __global__ __launch_bounds__(NEXT & RowsNext::GRAD ? 256 : 64) void k_spmm_short(SplitArgs a, int64_t nrows, const int32_t* __restrict__ rows,
-                                                                                 int32_t pitch, RowsNext nx) {
+                                                                                 int32_t pitch, NextArgs<NEXT> nx) {
     constexpr int VEC = 4;
     constexpr bool GRAD = (NEXT & RowsNext::GRAD) != 0;
     static_assert(NEXT == RowsNext::NONE || LPR == 4, "16 rows of a wavefront");
@@ -1479,19 +1482,18 @@ static int launch_short(const SplitArgs& args, const Matrix& m, int epilogue, hi
         next->done = true;
         return GCN_OK;
     }
-    const RowsNext none;
     auto go = [&](auto lpr, auto slice) {
         constexpr int LPR = decltype(lpr)::value, SLICE = decltype(slice)::value;
         const dim3 grid((unsigned)((nrows * LPR + 63) / 64), (unsigned)((args.f + 4 * LPR - 1) / (4 * LPR)));
         switch (epilogue) {
             case GCN_EPI_NONE:
-                hipLaunchKernelGGL((k_spmm_short<LPR, SLICE, GCN_EPI_NONE>), grid, dim3(64), 0, s, args, nrows, m.short_rows, m.short_pitch, none);
+                hipLaunchKernelGGL((k_spmm_short<LPR, SLICE, GCN_EPI_NONE>), grid, dim3(64), 0, s, args, nrows, m.short_rows, m.short_pitch, NoNext());
                 break;
             case GCN_EPI_RELU:
-                hipLaunchKernelGGL((k_spmm_short<LPR, SLICE, GCN_EPI_RELU>), grid, dim3(64), 0, s, args, nrows, m.short_rows, m.short_pitch, none);
+                hipLaunchKernelGGL((k_spmm_short<LPR, SLICE, GCN_EPI_RELU>), grid, dim3(64), 0, s, args, nrows, m.short_rows, m.short_pitch, NoNext());
                 break;
             default:
-                hipLaunchKernelGGL((k_spmm_short<LPR, SLICE, GCN_EPI_MASK>), grid, dim3(64), 0, s, args, nrows, m.short_rows, m.short_pitch, none);
+                hipLaunchKernelGGL((k_spmm_short<LPR, SLICE, GCN_EPI_MASK>), grid, dim3(64), 0, s, args, nrows, m.short_rows, m.short_pitch, NoNext());
                 break;
         }
     };
