@@ -39,24 +39,24 @@ HBM_PEAK_GBPS = 8000.0
 # other code, carries traffic = null instead of a stale figure.
 MEASURED_TRAFFIC = {
     ("rmat20_spmm_f128", 128): {
-        "bytes": 9913737204,
+        "bytes": 9914115053,
         "kernels": "k_spmm_split<8,4> over 4 panels of 32 columns + k_spmm_fixup",
         "schedule": "split(chunks=63376,kernel=k_spmm_split<8,4>)",
         "profile": "profiles/spmm_split_rmat20_f128.txt"},
     ("chunglu_reddit_gcn_602_16_16_41", 16): {
-        "bytes": 899638513,
+        "bytes": 901503067,
         "kernels": "k_scale_rows + k_spmm_split<4,4> over the column-blocked copy + k_spmm_fixup + k_block_reduce",
         "schedule": "blocked(blocks=8,cols_per_block=29696,partial_rows=1863720,chunks=224269,kernel=k_spmm_split<4,4>)"
                     "; value-free (operand rows pre-scaled by d^-1/2, output rows scaled)",
         "profile": "profiles/spmm_blocked_chunglu_reddit_f16.txt"},
     ("rmat_amazon_gcn_300_16_16_24", 16): {
-        "bytes": 19360365072,
+        "bytes": 19372340289,
         "kernels": "k_pack_rows + k_spmm_split_pair<4,4> (paired launch of the hub schedule) + k_spmm_fixup_pair + k_block_reduce",
         "schedule": "hub(hot_cols=524288,cols_per_block=32768,long_row>=64,nnz_hot=148858651,nnz_rest=96949372,partial_rows=7701691,"
                     "kernel=k_spmm_split_pair<4,4>)",
         "profile": "profiles/spmm_hub_rmat_amazon_f16.txt"},
     ("chunglu_protein_gcn_128_16_16_256", 16): {
-        "bytes": 62124563225,
+        "bytes": 62112371978,
         "kernels": "k_scale_rows + 14 x k_spmm_sweep<4> + k_spmm_split<4,4> (column-blocked, long rows) + k_spmm_fixup + k_block_reduce",
         "schedule": "sweep(entries_per_step=16,rows_per_task=511,long_row>1024,sums_per_row=1,tasks=17115,launches=14,stored=937876992,"
                     "kernel=k_spmm_sweep<4>)"
@@ -65,7 +65,7 @@ MEASURED_TRAFFIC = {
         "profile": "profiles/spmm_sweep_chunglu_protein_f16_default_command.txt"},
 }
 
-MEASURED_ON_CODE = "eb99050687aaf26d"
+MEASURED_ON_CODE = "861fc9b5a928b7a3"
 
 
 def sparse_code_digest() -> str:
