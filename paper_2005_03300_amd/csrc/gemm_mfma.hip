@@ -100,7 +100,11 @@ __device__ __forceinline__ void stage_b(const TallArgs& a, int n0, float* Bs) {
 // The two MFMA operands are swapped, so a lane ends up with four consecutive columns of one row of C (element v of tile t is
 // C[row0 + l%16][16t + 4*(l/16) + v]) and stores them with one instruction.  WIDE: N % 4 == 0 and 16-byte aligned rows of C (and of Zprev for
 // the mask); else at any address (with the operands
-// the other way round, single columns of four rows per lane and store: 1.5 M x 16 x 15 41 -> 33 us, x 41 164 -> 116; 0.2 M x 602 x 41 200 -> 166).
+// the other way round, single columns of four rows per lane and store: 1.5 M x 16 x 15 41 -> 33 us, x 41 164 -> 116; 0.2 M x 602 x 41 200 -> 166; slower
+// by up to 8 % on 50 K and 105 K rows of 400 to 602 floats, where whole 16 bytes take as long).  There the bias comes from LDS, and the columns that end
+// in their tile are handled once, behind the whole tiles: loads of single biases and code for the end in every tile took registers, and scalar ones were
+// saved to memory (with eight tiles 0.2 M x 16 x 127 and bias 35 us, now 27; with sixteen x 255 65 and 44; with four 76 registers, now 63: 0.58 M x 64 x 107 and
+// bias 196 and 158).
 // ASC: the products of an element of C are added in ascending k, like the chain of the plain kernel: an instruction
 // adds its four products in the order of the lane quarters, so quarter kq has to supply k = k0 + 4e + kq to instruction
 // e, and the 16 bytes that it loads at k0 + 4 kq are exchanged between the quarters (a 4 x 4 transposition, four
@@ -108,9 +112,11 @@ __device__ __forceinline__ void stage_b(const TallArgs& a, int n0, float* Bs) {
 // the compiler need not save registers for eight (which put fewer reads of it together: 0.2 M x 602 x 41 223 us and 170).
 template <int NT, int EPI, bool WIDE, bool ASC>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, ASC ? 4 : 8))) void k_gemm_tall(TallArgs a) {
-    extern __shared__ float Bs[];                       // [Kpad][S]
+    extern __shared__ float Bs[];                       // [Kpad][S], then the bias
     const int n0 = blockIdx.y * (NT * 16);
     stage_b<NT>(a, n0, Bs);
+    if (!WIDE && a.bias)
+        for (int j = threadIdx.x; j < 16 * NT; j += blockDim.x) Bs[a.Kpad * a.S + j] = n0 + j < a.N ? a.bias[n0 + j] : 0.f;
     __syncthreads();
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
@@ -204,49 +210,50 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, ASC ? 4 
             }
             continue;
         }
-        // The last two or three columns of a row leave with those before them, which another lane stores too, with the same bits (one by
-        // one they made 1.5 M x 16 x 31 90 us, now 65; 1 M x 64 x 23 75, now 64).
-        const int tail = a.N & 3;
-        const bool shift = tail >= 2 && (a.N & 15) > 4;
-        floatx4 left4[NT];
-        if (shift) {
-#pragma unroll
-            for (int t = 0; t < NT; ++t)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) left4[t][v] = v < 2 ? 0.f : __shfl_up(acc[t][v], 16, 64);
-        }
-        if (row >= a.M) continue;
+        const int left = a.N - n0, full = left >= 16 * NT ? NT : left / 16;        // tiles of 16 columns
+        float* const c = a.C + row * a.ldc + n0 + 4 * kq;
+        const float* const z = EPI == GCN_EPI_MASK ? a.Zprev + row * a.ldzprev + n0 + 4 * kq : nullptr;
+        const float* const bias = Bs + a.Kpad * a.S + 4 * kq;
+        auto store = [&](int at, floatx4 o) {
+            float m[4] = {};
+            if (EPI == GCN_EPI_MASK) {
+                const float4 x = load4(z + at);
+                m[0] = x.x; m[1] = x.y; m[2] = x.z; m[3] = x.w;
+                __builtin_amdgcn_wave_barrier();        // (the mask may be C: all lanes read before any of them stores what another one reads)
+            }
+            *reinterpret_cast<floatx4u*>(c + at) = (floatx4){epi<EPI>(o[0], m), epi<EPI>(o[1], m + 1), epi<EPI>(o[2], m + 2), epi<EPI>(o[3], m + 3)};
+        };
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-            int col = n0 + 16 * t + 4 * kq, left = a.N - col;
-            if (left <= 0) continue;
-            if (shift && left < 4) {
-                acc[t] = tail == 2 ? (floatx4){left4[t][2], left4[t][3], acc[t][0], acc[t][1]}
-                                   : (floatx4){left4[t][3], acc[t][0], acc[t][1], acc[t][2]};
-                col -= 4 - left;
-                left = 4;
+            if (t < full) {
+                floatx4 o = acc[t];
+                if (a.bias) o += *reinterpret_cast<const floatx4*>(bias + 16 * t);
+                if (row < a.M) store(16 * t, o);
             }
-            float* const c = a.C + row * a.ldc + col;
-            const float* const z = EPI == GCN_EPI_MASK ? a.Zprev + row * a.ldzprev + col : nullptr;
-            float o[4] = {acc[t][0], acc[t][1], acc[t][2], acc[t][3]};
-            if (left >= 4) {
-                if (a.bias) {
+        }
+        if (full == NT || left == 16 * full) continue;
+        // The last tile.  The last two or three columns of a row leave with those before them, which another lane stores too, with the same bits
+        // (one by one they made 1.5 M x 16 x 31 90 us, now 65; 1 M x 64 x 23 75, now 64).
+        floatx4 o = acc[0];
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) o[v] += a.bias[col + v];
-                }
-                float m[4] = {};
-                if (EPI == GCN_EPI_MASK) {
-                    const float4 x = load4(z);
-                    m[0] = x.x; m[1] = x.y; m[2] = x.z; m[3] = x.w;
-                }
-#pragma unroll
-                for (int v = 0; v < 4; ++v) o[v] = epi<EPI>(o[v], m + v);
-                *reinterpret_cast<floatx4u*>(c) = (floatx4){o[0], o[1], o[2], o[3]};
-            } else {
-#pragma unroll
-                for (int v = 0; v < 3; ++v)
-                    if (v < left) c[v] = epi<EPI>(o[v] + (a.bias ? a.bias[col + v] : 0.f), EPI == GCN_EPI_MASK ? z + v : nullptr);
+        for (int t = 1; t < NT; ++t)
+            if (t == full) o = acc[t];
+        if (a.bias) o += *reinterpret_cast<const floatx4*>(bias + 16 * full);
+        const int tail = a.N & 3, mine = left - 16 * full - 4 * kq;                // columns from this lane's four on
+        int at = 16 * full;
+        if (tail >= 2 && left - at > 4) {
+            const float x = __shfl_up(o[2], 16, 64), y = __shfl_up(o[3], 16, 64);
+            if (mine == tail) {
+                o = tail == 2 ? (floatx4){x, y, o[0], o[1]} : (floatx4){y, o[0], o[1], o[2]};
+                at -= 4 - tail;
             }
+        }
+        if (row >= a.M || mine <= 0) continue;
+        if (mine >= 4 || at < 16 * full) store(at, o);
+        else {
+#pragma unroll
+            for (int v = 0; v < 3; ++v)
+                if (v < mine) c[at + v] = epi<EPI>(o[v], EPI == GCN_EPI_MASK ? z + at + v : nullptr);
         }
     }
 }
@@ -1113,6 +1120,8 @@ int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const floa
         // per element in that order; keeping the order keeps the bits of the hidden activations, on whose signs
         // the ReLU decides.
         const bool ascending = b_bytes(NT) > 64 * 1024;
+        const bool wide_c = (N % 4 == 0) && (ldc % 4 == 0) && al16(C) &&
+                            (epilogue != GCN_EPI_MASK || ((ldzprev % 4 == 0) && al16(Zprev)));
         while (NT > 1 && b_bytes(NT) > 150 * 1024) --NT;
         // No more tiles than equal shares of the columns take, 80 in three and two and not in four and one, while operand and result are in the
         // memory-side cache: 64 x 80 on 120 K rows 22.9 -> 19.6 us, 256 x 96 82.5 -> 69, 16 x 96 on 200 K 20.0 -> 19.4.  Beyond it the pieces of
@@ -1126,11 +1135,9 @@ int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const floa
         args.Kpad = (int32_t)kpad;
         args.asc = ascending;
         args.S = 16 * NT + 4;
-        const bool wide_c = (N % 4 == 0) && (ldc % 4 == 0) && al16(C) &&
-                            (epilogue != GCN_EPI_MASK || ((ldzprev % 4 == 0) && al16(Zprev)));
         args.row_scale = wide_c ? row_scale : nullptr;       // the 16-byte store path applies it; else the caller does
         *scaled = args.row_scale != nullptr;
-        const size_t lds = b_bytes(NT);
+        const size_t lds = b_bytes(NT) + (bias && !wide_c ? 16 * NT * sizeof(float) : 0);
         if (lds > 150 * 1024) { *scaled = false; return GCN_OK; }
         const int64_t ntiles = (M + 15) / 16;
         {   // Rows that are not whole 128-byte lines, and short rows (up to 208 floats, where the coalesced copy also beats

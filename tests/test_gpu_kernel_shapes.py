@@ -1337,6 +1337,19 @@ def test_dense_products_of_ragged_rows(M, K, tb, N):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("N", [1, 2, 3, 6, 7, 18, 23, 41, 62, 63, 66, 70, 95, 127, 130, 243, 255])
+@pytest.mark.parametrize("M,K,tb", [(64, 16, 0), (1001, 30, 1), (333, 602, 0)])
+def test_result_over_its_own_mask(M, K, tb, N):
+    """A mask that is the result itself: the last columns of a row are read and stored by two lanes."""
+    g = G()
+    A, B, Zp = dev(synth.normal_features(M, K, 341)), dev(synth.normal_features(*((N, K) if tb else (K, N)), 342)), dev(synth.normal_features(M, N, 343))
+    want = torch.empty(M, N, device="cuda")
+    g.gcn_gemm(0, tb, A, B, want, epilogue=g.EPI_MASK, Zprev=Zp)
+    g.gcn_gemm(0, tb, A, B, Zp, epilogue=g.EPI_MASK, Zprev=Zp)
+    assert torch.equal(Zp, want)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("n", [63, 64, 65, 79, 127, 129, 1000, 33_000, 70_001])
 @pytest.mark.parametrize("f_in,f_out", [(16, 1), (16, 5), (16, 15), (16, 16), (32, 3), (32, 16), (32, 17), (32, 32), (64, 2), (64, 16), (64, 17), (64, 33), (64, 41),
                                         (64, 48), (64, 49), (64, 64)])
