@@ -1122,6 +1122,12 @@ int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const floa
         const bool ascending = b_bytes(NT) > 64 * 1024;
         const bool wide_c = (N % 4 == 0) && (ldc % 4 == 0) && al16(C) &&
                             (epilogue != GCN_EPI_MASK || ((ldzprev % 4 == 0) && al16(Zprev)));
+        // Rows of C that are no whole 16 bytes, beyond the memory-side cache: up to 128 columns leave from one wavefront too while two workgroups fit a
+        // compute unit.  In two columns of workgroups the lines that these share are written twice, at different times, and then four columns
+        // at a time are slower than single ones (1.2 M x 128 x 95 411 us with single columns, 535 with four, 340 in one piece; x 44 x 90 278, 316
+        // and 195; 0.5 M x 128 x 127 237, 217 and 167; from 145 rows of op(B) on four in two pieces are the faster, 0.5 M x 160 x 90 299 and 226).  In
+        // whole 16 bytes two pieces stay: 0.5 M x 44 x 96 76, in one 83.
+        if (!wide_c && nt_total > 4 && nt_total <= 8 && M * (K + N) * 4 >= (192ll << 20) && b_bytes(8) <= 80 * 1024) NT = 8;
         while (NT > 1 && b_bytes(NT) > 150 * 1024) --NT;
         // No more tiles than equal shares of the columns take, 80 in three and two and not in four and one, while operand and result are in the
         // memory-side cache: 64 x 80 on 120 K rows 22.9 -> 19.6 us, 256 x 96 82.5 -> 69, 16 x 96 on 200 K 20.0 -> 19.4.  Beyond it the pieces of

@@ -1337,6 +1337,27 @@ def test_dense_products_of_ragged_rows(M, K, tb, N):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("N", [65, 66, 67, 79, 82, 95, 111, 113, 127])
+@pytest.mark.parametrize("K", [3, 44, 144, 145])
+def test_dense_products_of_ragged_rows_beyond_the_caches(N, K):
+    """Rows of 65 to 127 columns leave from one wavefront where operand and result are beyond the memory-side cache, up to 144 rows of op(B); pieces of the rows are
+    other launches.  The same bits, with a bias and either epilogue."""
+    g = G()
+    M = (192 << 20) // (4 * (K + N)) + 21
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(331)
+    A, B, bias, Zp = [torch.randn(r, c, generator=gen, device="cuda") for r, c in ((M, K), (K, N), (1, N), (M, N))]
+    for epilogue in (g.EPI_NONE, g.EPI_RELU, g.EPI_MASK):
+        C, pieces = torch.full((M + 2, N), float("nan"), device="cuda"), torch.empty(M, N, device="cuda")
+        args = lambda r: dict(bias=bias.view(-1), epilogue=epilogue, Zprev=Zp[r] if epilogue == g.EPI_MASK else None)
+        g.gcn_gemm(0, 0, A, B, C[1:-1], **args(slice(None)))
+        for r in (slice(0, M // 3), slice(M // 3, 2 * (M // 3)), slice(2 * (M // 3), M)):
+            g.gcn_gemm(0, 0, A[r], B, pieces[r], **args(r))
+        assert torch.equal(C[1:-1], pieces), epilogue
+        assert bool(torch.isnan(C[0]).all() and torch.isnan(C[-1]).all())
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("N", [1, 2, 3, 6, 7, 18, 23, 41, 62, 63, 66, 70, 95, 127, 130, 243, 255])
 @pytest.mark.parametrize("M,K,tb", [(64, 16, 0), (1001, 30, 1), (333, 602, 0)])
 def test_result_over_its_own_mask(M, K, tb, N):
