@@ -268,8 +268,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, ASC ? 4 
 // A wavefront keeps the results of `held` strips in LDS, where they leave room for as many workgroups, and stores them in one burst: single kilobytes
 // of writes among the reads of all memory cost more than their share (300 x 16 over 1.8 M rows 429 -> 397 us, 228 x 12 over 3 M 606 -> 540; the
 // same reads without any store 2.77 ms of 3.46 on 14 M).
-template <int NT, int KV>
-constexpr int FLAT_HELD = NT == 1 && KV == 19 ? 8 : 0;
+constexpr int flat_held(int NT, int KV) { return NT == 1 && KV == 19 ? 8 : 0; }
 template <int NT, int EPI, int KV>
 __global__ __launch_bounds__(512) void k_gemm_tall_flat(TallArgs a) {
     extern __shared__ float lds[];
@@ -285,7 +284,7 @@ __global__ __launch_bounds__(512) void k_gemm_tall_flat(TallArgs a) {
     const int64_t ntiles = (a.M + 15) / 16;
     const int64_t total = a.M * (int64_t)a.K;           // floats of A
     const int64_t stride = (int64_t)gridDim.x * waves;
-    constexpr int HELD = FLAT_HELD<NT, KV>;
+    constexpr int HELD = flat_held(NT, KV);
     float* const Cs = lds + a.Kpad * a.S + (blockDim.x >> 6) * (KV * 256) + (threadIdx.x >> 6) * (HELD * 256);
     int held = 0;
     int64_t first = 0;                                  // of the strips held
@@ -1165,8 +1164,7 @@ int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const floa
             // 300 floats: 2: 4.15, 3: 4.29, 4: 3.57, 5: 3.87, 6: 3.74 ms (the same ranking at 64, 128 and 192 floats)
             int fw = (int)((150 * 1024 - (int64_t)lds) / ((int64_t)KV * 256 * sizeof(float)));
             fw = fw > 4 ? 4 : fw;
-            const int held = NT == 1 && KV == 19 ? FLAT_HELD<1, 19> : 0;
-            const size_t lds_flat = lds + (size_t)(fw > 0 ? fw : 1) * (KV + held) * 256 * sizeof(float);
+            const size_t lds_flat = lds + (size_t)(fw > 0 ? fw : 1) * (KV + flat_held(NT, KV)) * 256 * sizeof(float);
             if (strips && fw >= 2 && wide && !ascending && lda == K && (K % 4) == 0 && (((K * 4) % 128) != 0 || K <= 208) && K >= 64 && kv_need <= 19 && NT <= 2 && al16(A) &&
                 lds_flat <= 150 * 1024) {
                 int64_t fb = (ntiles + fw - 1) / fw;
