@@ -1309,6 +1309,28 @@ def test_bias_gradient_beside_the_weight_gradient(n, f_in, f_out):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("n", [1, 64, 97, 416, 600, 1000])
+@pytest.mark.parametrize("f_in,f_out", [(256, 256), (257, 256), (40, 1700), (1000, 70)])
+def test_bias_gradient_beside_large_weight_gradients(n, f_in, f_out):
+    """On both sides of 64 K numbers, with 1 to 32 partial results, of which the last are fewer than a step or a single one: the bits that a call without a bias
+    gradient leaves, and the weight gradient as close to 64 bits as its chains of up to 64 rows and their sums allow."""
+    g = G()
+    a = g.gcn_csr_create(n, *[torch.arange(n, dtype=torch.int32, device="cuda")] * 2, g.NORM_ROW | g.BUILD_TRANSPOSE)
+    H, Zp, W, Gm = [dev(synth.normal_features(r, c, 351 + i)) for i, (r, c) in enumerate(((n, f_in), (n, f_in), (f_in, f_out), (n, f_out)))]
+    w = min(f_in, f_out)
+    T, empty = dev(synth.normal_features(n, w, 356)), lambda r, c: torch.full((r, c), float("nan"), device="cuda")
+    S, S1, Y, Y1, Gp, Gp1, db = empty(n, w), empty(n, w), empty(f_in, f_out), empty(f_in, f_out), empty(n, f_in), empty(n, f_in), empty(1, f_out).view(-1)
+    g.gcn_layer_backward(a, H, Zp, W, Gm, T, S1, Y1, Gp1)
+    g.gcn_layer_backward(a, H, Zp, W, Gm, T, S, Y, Gp, dbias=db)
+    assert torch.equal(Y, Y1) and torch.equal(Gp, Gp1)
+    left, right = (H, S) if f_out <= f_in else (T, Gm)
+    want, scale = left.double().T @ right.double(), left.double().abs().T @ right.double().abs()
+    assert bool(((Y.double() - want).abs() <= 100 * 2.0 ** -24 * scale).all())
+    assert np.all(np.abs(host(db) - host(Gm.double().sum(0))) <= 16 * 2.0 ** -24 * host(Gm.double().abs().sum(0)))
+    a.close()
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("N", [1, 2, 3, 5, 6, 7, 15, 17, 18, 19, 21, 22, 23, 31, 33, 35, 41, 47, 63, 65, 66, 67, 70, 80, 96, 130, 131])
 @pytest.mark.parametrize("M,K,tb", [(64, 16, 0), (79, 3, 0), (1001, 64, 0), (1001, 64, 1), (333, 300, 0), (333, 602, 0), (5000, 41, 1)])
 def test_dense_products_of_ragged_rows(M, K, tb, N):
