@@ -10,6 +10,8 @@
 //
 // Operand layout of the 16x16x4 instruction (64 lanes): lane l supplies A[i = l%16][k = l/16] and
 // B[k = l/16][j = l%16], and holds D[i = 4*(l/16) + v][j = l%16] in element v of its accumulator.
+#include <algorithm>
+
 #include "common.h"
 #include "launch_rules.h"
 #include "sum_parts.h"
@@ -913,7 +915,7 @@ __global__ __launch_bounds__(1024) void k_epoch_end(EpochEnd::Args a) {
     int k = 0;
     while (k + 1 < a.count && b >= a.sums[k + 1].first) ++k;
     const EpochEnd::Sum& g = a.sums[k];
-    sum_of_parts(b - g.first, g.M, g.N, g.parts, g.transposed, g.part, g.parts < 16 ? g.parts : 16, lds.s, [&](int m, int n, float s) {
+    sum_of_parts(b - g.first, g.M, g.N, g.parts, g.transposed, g.part, sum_waves(g.parts), lds.s, [&](int m, int n, float s) {
         const int64_t t = (int64_t)m * g.N + n;
         g.Y[t] = s;
         update(g.W, t, s);
@@ -922,8 +924,9 @@ __global__ __launch_bounds__(1024) void k_epoch_end(EpochEnd::Args a) {
 
 int EpochEnd::finish(float lr, hipStream_t s) {
     args.lr = lr;
-    int blocks = 0;
+    int blocks = 0, waves = args.fused.part || args.loss ? 16 : 1;        // (the other two take all of them)
     for (int k = 0; k < args.count; ++k) {
+        waves = std::max(waves, sum_waves(args.sums[k].parts));
         args.sums[k].first = blocks;
         if (lr == 0.f) args.sums[k].W = nullptr;
         blocks += (int)(((int64_t)args.sums[k].M * args.sums[k].N + 63) / 64);
@@ -935,7 +938,7 @@ int EpochEnd::finish(float lr, hipStream_t s) {
     }
     if (args.loss) args.loss_at = blocks++;
     if (blocks == 0) return GCN_OK;
-    hipLaunchKernelGGL(k_epoch_end, dim3((unsigned)blocks), dim3(1024), 0, s, args);
+    hipLaunchKernelGGL(k_epoch_end, dim3((unsigned)blocks), dim3(64 * waves), 0, s, args);
     GCN_LAUNCH_CHECK();
     return GCN_OK;
 }
@@ -1075,7 +1078,7 @@ static TnShape tn_shape(int64_t M, int64_t N, int64_t K) {
 int reduce_parts_launch(int32_t M, int32_t N, int parts, bool transposed, const float* part, float* C, int64_t ldc,
                         const float* bias, int epilogue, const float* Zprev, int64_t ldzprev, hipStream_t s) {
     const int64_t count = (int64_t)M * N;
-    const dim3 grid((unsigned)((count + 63) / 64)), block(64 * (parts >= 16 ? 16 : parts));
+    const dim3 grid((unsigned)((count + 63) / 64)), block(64 * sum_waves(parts));
     switch (epilogue) {
         case GCN_EPI_NONE: hipLaunchKernelGGL(k_tn_reduce<GCN_EPI_NONE>, grid, block, 0, s, M, N, parts, (int)transposed, part, C, ldc, bias, Zprev, ldzprev); break;
         case GCN_EPI_RELU: hipLaunchKernelGGL(k_tn_reduce<GCN_EPI_RELU>, grid, block, 0, s, M, N, parts, (int)transposed, part, C, ldc, bias, Zprev, ldzprev); break;

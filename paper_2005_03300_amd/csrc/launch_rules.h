@@ -50,6 +50,10 @@ inline int share_of_empty_rows(int64_t rows, int64_t n_empty, int64_t nchunks, i
     return whole || rows * ldz <= (8 << 20) || (stores <= 10 && rows * ldz <= (64 << 20)) ? (int)share : 0;
 }
 
+// Wavefronts of a workgroup that adds up 64 results (see sum_of_parts), for the sums of a launch with up to `parts` partial results each: one
+// to a partial result, up to 16.  More of them only wait (16 always: layer calls with a bias, 602-256 on 64 vertices 34.3 us, so 29.1).
+constexpr int sum_waves(int64_t parts) { return parts < 1 ? 1 : (parts < 16 ? (int)parts : 16); }
+
 // Whether a matrix of short rows gets a copy at an equal pitch for k_spmm_short (see build_short).  Not where the copy is beyond the L2s (3 M
 // places of 8 bytes), more than half padding, and rows of 16 entries and more are in most wavefronts of that kernel (32 rows at the
 // widths that take so many), so that all of its lanes walk as far as these: rows of 0 to 64 entries of which most are

@@ -275,7 +275,9 @@ int gcn_layer_backward(gcn_csr* a, int32_t f_in, int32_t f_out, const float* Hin
     if (Gprev && !Zprev) return fail(GCN_ERR_BADARG, "gcn_layer_backward: Gprev needs Zprev");
     hipStream_t s = (hipStream_t)stream;
     const bool y_is_w = Y < W + (int64_t)f_in * f_out && W < Y + (int64_t)f_in * f_out;      // (Gprev comes from what Y has become)
-    if (!dbias || y_is_w) return layer_backward_impl(a, f_in, f_out, Hin, ldh, Zprev, W, G, T, S, Y, dbias, Gprev, order, s);
+    // Weight gradients of more than 64 K numbers are added up by a launch of their own, whose workgroups have less to find out before they load (1000-1000
+    // on 600 vertices 119 us, in one launch 136; 3000-64 39 and 41; 512-256 on 416 38.5 and 39.5, on 64 31.7 and 30.4; 256-256 33.4 and 32.7).
+    if (!dbias || y_is_w || (int64_t)f_in * f_out > 65536) return layer_backward_impl(a, f_in, f_out, Hin, ldh, Zprev, W, G, T, S, Y, dbias, Gprev, order, s);
     // The partial results of both gradients side by side, added up in one launch (32-8 on 5000 vertices 16.5 -> 13.6 us, two layers of 200 K 508 -> 502).
     const size_t sums = EpochEnd::Room::whole(colsum_scratch_bytes(a->n, f_out)), products = EpochEnd::Room::whole(gemm_tn_scratch_bytes(f_in, f_out, a->n));
     void* scratch = nullptr;

@@ -472,3 +472,16 @@ def test_a_padded_copy_of_short_rows_is_made_where_its_kernel_was_faster(tmp_pat
         }
     """)
     assert r.returncode == 0 and r.stdout == "1" * 12, (r.returncode, r.stdout, r.stderr)
+
+
+def test_wavefronts_that_add_up_partial_results(tmp_path):
+    """One to a partial result: none without one, none more than 16."""
+    r = run_cpp(tmp_path, """
+        #include <cstdio>
+        #include <initializer_list>
+        #include "launch_rules.h"
+        int main() {
+            for (long long parts : {0ll, 1ll, 2ll, 15ll, 16ll, 17ll, 1ll << 40}) std::printf("%d ", gcn::sum_waves(parts));
+        }
+    """)
+    assert r.returncode == 0 and r.stdout.split() == "1 1 2 15 16 16 16".split(), (r.returncode, r.stdout, r.stderr)
