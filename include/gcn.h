@@ -22,10 +22,11 @@
  *     earlier stay valid.
  *   - A matrix that gcn_csr_create symmetrised and did not normalise by rows equals its transpose bit by bit: it is
  *     stored once, and gcn_csr_arrays gives the same arrays for both.
- *   - Library-owned scratch exists only for the stand-alone gcn_gemm (ta = 1), gcn_softmax_nll* and the bias
- *     gradient of gcn_layer_backward: one buffer per (device, stream), grown on demand by the first call that
- *     needs more (an allocation), never shared between streams; gcn_scratch_release frees all of them.  The
- *     epoch calls keep these partial sums in the caller's workspace instead.
+ *   - Library-owned scratch exists only for the stand-alone gcn_gemm (ta = 1), gcn_softmax_nll* and the gradients of
+ *     gcn_layer_backward: a buffer per (device, stream), grown on demand by the first call that needs more (an
+ *     allocation), never shared between streams, nor between calls that threads make on one stream at the same time: these get
+ *     buffers of their own.  gcn_scratch_release frees all of them.  The epoch calls keep these partial sums in the caller's
+ *     workspace instead.
  *   - Every function returns GCN_OK (0) or a negative GCN_ERR_* code and never throws or aborts.
  *     gcn_last_error() returns a thread-local message for the last failure on this thread.
  *   - No call is safe to run concurrently with another call that uses the same gcn_csr.  Calls on different

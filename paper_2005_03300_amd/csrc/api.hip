@@ -9,6 +9,7 @@
 
 #include "common.h"
 #include "copy_rule.h"
+#include "scratch_pool.h"
 
 namespace gcn {
 
@@ -193,10 +194,7 @@ void temp_free(void* p) {
 }
 
 // ---- per-stream scratch ------------------------------------------------------------------------
-struct Arena { int device; hipStream_t stream; void* p; size_t bytes; };
-static std::mutex g_scratch_mu;
-static std::vector<Arena> g_arenas;
-static std::vector<void*> g_scratch_retired;
+static ScratchPool g_scratch;
 
 static thread_local void* g_scope_p = nullptr;
 static thread_local size_t g_scope_bytes = 0;
@@ -219,7 +217,7 @@ EpochEnd::~EpochEnd() {
 }
 EpochEnd* epoch_end() { return g_epoch_end; }
 
-int scratch_get(void** p, size_t bytes, hipStream_t s) {
+int ScratchLease::get(void** p, size_t bytes, hipStream_t s) {
     if (g_scope_p) {
         if (bytes > g_scope_bytes)
             return fail(GCN_ERR_WORKSPACE, "workspace scratch region has %zu bytes, %zu needed", g_scope_bytes, bytes);
@@ -228,25 +226,12 @@ int scratch_get(void** p, size_t bytes, hipStream_t s) {
     }
     int dev = 0;
     GCN_HIP_TRY(hipGetDevice(&dev));
-    std::lock_guard<std::mutex> lk(g_scratch_mu);
-    Arena* ar = nullptr;
-    for (auto& x : g_arenas)
-        if (x.device == dev && x.stream == s) { ar = &x; break; }
-    if (!ar) {
-        g_arenas.push_back({dev, s, nullptr, 0});
-        ar = &g_arenas.back();
-    }
-    if (bytes > ar->bytes) {
-        // Work queued (or captured in a graph) earlier may still use the old buffer: keep it.
-        void* fresh = nullptr;
-        const size_t want = bytes + bytes / 4;
-        GCN_TRY(device_alloc(&fresh, want));
-        if (ar->p) g_scratch_retired.push_back(ar->p);
-        ar->p = fresh;
-        ar->bytes = want;
-    }
-    *p = ar->p;
+    GCN_TRY(g_scratch.take(dev, s, bytes, &p_, [](void** q, size_t size) { return device_alloc(q, size); }));
+    *p = p_;
     return GCN_OK;
+}
+ScratchLease::~ScratchLease() {
+    if (p_) g_scratch.give(p_);
 }
 
 int grow_retire(gcn_csr* a, float** buf, size_t* have, size_t need) {
@@ -562,11 +547,7 @@ int gcn_csr_destroy(gcn_csr* a) {
 
 int gcn_scratch_release(void) {
     GCN_HIP_TRY(hipDeviceSynchronize());
-    std::lock_guard<std::mutex> lk(g_scratch_mu);
-    for (auto& x : g_arenas) device_free(x.p);
-    for (void* p : g_scratch_retired) device_free(p);
-    g_arenas.clear();
-    g_scratch_retired.clear();
+    g_scratch.clear([](void* p) { device_free(p); });
     device_pool_release();
     return GCN_OK;
 }

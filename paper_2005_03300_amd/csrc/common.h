@@ -242,10 +242,19 @@ struct TempBuf {   // given back on scope exit
 };
 
 // Library-owned scratch for the split-K partial sums of the weight-gradient product, the column sums and the
-// loss: one buffer per (device, stream), so calls on different streams never share it.  It grows on demand; the
-// buffer it replaces is kept (work queued or captured earlier may still use it) until gcn_scratch_release.
-int scratch_get(void** p, size_t bytes, hipStream_t s);
-// While one of these is alive on a thread, scratch_get on that thread hands out the given caller-owned
+// loss (see ScratchPool): the buffer is the call's from get() to the end of its scope, and no other call's.  It grows on demand; the
+// buffers are kept until gcn_scratch_release.
+class ScratchLease {
+public:
+    ScratchLease() = default;
+    ScratchLease(const ScratchLease&) = delete;
+    ScratchLease& operator=(const ScratchLease&) = delete;
+    ~ScratchLease();
+    int get(void** p, size_t bytes, hipStream_t s);
+private:
+    void* p_ = nullptr;
+};
+// While one of these is alive on a thread, leases of that thread are the given caller-owned
 // buffer instead (GCN_ERR_WORKSPACE if it is too small): the epoch calls keep their partial sums in the
 // caller's workspace.
 struct ScratchScope {

@@ -207,9 +207,10 @@ int colsum_launch(int64_t rows, int32_t cols, const float* G, int64_t ldg, float
     int64_t parts = 0, rpb = 0;
     colsum_split(rows, &parts, &rpb);
     EpochEnd* const end = epoch_end();
+    ScratchLease lease;
     void* scratch = end ? end->take((size_t)parts * cols * sizeof(float)) : nullptr;
     const bool later = scratch != nullptr;
-    if (!later) GCN_TRY(scratch_get(&scratch, (size_t)parts * cols * sizeof(float), s));
+    if (!later) GCN_TRY(lease.get(&scratch, (size_t)parts * cols * sizeof(float), s));
     int tx = 64;
     while (tx > 4 && tx / 2 >= cols) tx /= 2;
     hipLaunchKernelGGL(k_colsum_partial, dim3((unsigned)parts, (unsigned)((cols + tx - 1) / tx)), dim3(tx, 256 / tx), 0, s, rows,

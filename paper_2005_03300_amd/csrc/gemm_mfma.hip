@@ -1211,9 +1211,10 @@ int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const floa
     const TnShape g = tn_shape(M, N, K);
     if (g.blocks >= (1ll << 31) || g.ny > 65535 || g.nz > 65535 || M * N >= (1ll << 36)) return fail(GCN_ERR_RANGE, "gcn_gemm: output too large");
     EpochEnd* const end = !bias && epilogue == GCN_EPI_NONE && ldc == N ? epoch_end() : nullptr;
+    ScratchLease lease;
     void* scratch = end ? end->take(g.scratch_bytes, g.few) : nullptr;
     const bool later = scratch != nullptr;
-    if (!later) GCN_TRY(scratch_get(&scratch, g.scratch_bytes, s));
+    if (!later) GCN_TRY(lease.get(&scratch, g.scratch_bytes, s));
     TnArgs args;
     args.K = K; args.M = (int32_t)g.Mw; args.N = (int32_t)g.Nw;
     args.A = g.swap ? B : A; args.lda = g.swap ? ldb : lda;
@@ -1291,9 +1292,10 @@ int gemm_back_launch(int64_t n, int32_t f_in, int32_t f_out, const float* Hin, i
     }
     const TnShape g = tn_shape(f_in, f_out, n);
     EpochEnd* const end = epoch_end();
+    ScratchLease lease;
     void* scratch = end ? end->take(g.scratch_bytes, g.few) : nullptr;
     const bool later = scratch != nullptr;
-    if (!later) GCN_TRY(scratch_get(&scratch, g.scratch_bytes, s));
+    if (!later) GCN_TRY(lease.get(&scratch, g.scratch_bytes, s));
     TnArgs args;
     args.K = n; args.M = f_in; args.N = f_out;
     args.A = Hin; args.lda = ldh; args.B = S; args.ldb = f_out;

@@ -280,8 +280,9 @@ int gcn_layer_backward(gcn_csr* a, int32_t f_in, int32_t f_out, const float* Hin
     if (!dbias || y_is_w || (int64_t)f_in * f_out > 65536) return layer_backward_impl(a, f_in, f_out, Hin, ldh, Zprev, W, G, T, S, Y, dbias, Gprev, order, s);
     // The partial results of both gradients side by side, added up in one launch (32-8 on 5000 vertices 16.5 -> 13.6 us, two layers of 200 K 508 -> 502).
     const size_t sums = EpochEnd::Room::whole(colsum_scratch_bytes(a->n, f_out)), products = EpochEnd::Room::whole(gemm_tn_scratch_bytes(f_in, f_out, a->n));
+    ScratchLease lease;
     void* scratch = nullptr;
-    GCN_TRY(scratch_get(&scratch, sums + products, s));
+    GCN_TRY(lease.get(&scratch, sums + products, s));
     EpochEnd::Room room;
     room.at[0] = (char*)scratch;
     room.left[0] = sums + products;

@@ -185,9 +185,10 @@ using namespace gcn;
 static int softmax_nll_impl(int64_t n, int32_t C, const float* Z, int64_t ldz, const int32_t* labels, int64_t n_labelled,
                             float* loss, float* G, int64_t ldg, hipStream_t s) {
     EpochEnd* const end = epoch_end();
+    ScratchLease lease;
     void* scratch = end ? end->take(loss_part_bytes(n)) : nullptr;
     const bool later = scratch != nullptr;
-    if (!later) GCN_TRY(scratch_get(&scratch, loss_scratch_bytes(), s));
+    if (!later) GCN_TRY(lease.get(&scratch, loss_scratch_bytes(), s));
     double* part = (double*)scratch;
     int64_t blocks = 0;
     const float inv_m = 1.0f / (float)n_labelled;

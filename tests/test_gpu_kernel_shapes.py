@@ -1309,6 +1309,81 @@ def test_bias_gradient_beside_the_weight_gradient(n, f_in, f_out):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("dims", [((64, 41), (64, 41)), ((16, 16), (100, 70)), ((300, 16), (8, 200))])
+def test_layer_calls_of_two_threads_on_one_stream(dims):
+    """Two threads, a matrix each, one stream: no call's partial results lie where another call's do."""
+    import threading
+    g = G()
+    stream = torch.cuda.Stream()
+    work = []
+    for i, (f_in, f_out) in enumerate(dims):
+        n = 3000 + 7 * i
+        rs = np.random.default_rng(361 + i)
+        a = g.gcn_csr_create(n, *[dev(rs.integers(0, n, n).astype(np.int32)) for _ in range(2)], g.ADD_SELF_LOOPS | g.NORM_ROW | g.BUILD_TRANSPOSE)
+        H, Zp, W, Gm = [dev(synth.normal_features(r, c, 362 + 10 * i + k)) for k, (r, c) in enumerate(((n, f_in), (n, f_in), (f_in, f_out), (n, f_out)))]
+        w = min(f_in, f_out)
+        T, S, Gp = dev(synth.normal_features(n, w, 366 + 10 * i)), torch.empty(n, w, device="cuda"), torch.empty(n, f_in, device="cuda")
+        g.gcn_spmm_prepare(a, 0, w)
+        call = lambda Y, db, a=a, H=H, Zp=Zp, W=W, Gm=Gm, T=T, S=S, Gp=Gp: g.gcn_layer_backward(a, H, Zp, W, Gm, T, S, Y, Gp, dbias=db)
+        outs = [(torch.empty_like(W), torch.empty(f_out, device="cuda")) for _ in range(100)]
+        want = torch.empty_like(W), torch.empty(f_out, device="cuda")
+        call(*want)
+        work.append((a, call, outs, want))
+    torch.cuda.synchronize()
+    errors = []
+
+    def run(call, outs):
+        try:
+            with torch.cuda.stream(stream):
+                for Y, db in outs:
+                    call(Y, db)
+        except Exception as e:                                          # (reported by the test's own thread)
+            errors.append(e)
+    threads = [threading.Thread(target=run, args=(call, outs)) for _, call, outs, _ in work]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert not errors, errors
+    for a, _, outs, want in work:
+        assert all(torch.equal(Y, want[0]) and torch.equal(db, want[1]) for Y, db in outs)
+        a.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("f_in,f_out", [(64, 16), (64, 41), (300, 300)])
+def test_layer_backward_with_a_bias_in_a_graph(f_in, f_out):
+    """Captured after one call of its sizes, replayed between other work and eager calls: the eager results every time."""
+    g = G()
+    n = 5000
+    rs = np.random.default_rng(371)
+    a = g.gcn_csr_create(n, *[dev(rs.integers(0, n, n).astype(np.int32)) for _ in range(2)], g.ADD_SELF_LOOPS | g.NORM_ROW | g.BUILD_TRANSPOSE)
+    H, Zp, W, Gm = [dev(synth.normal_features(r, c, 372 + k)) for k, (r, c) in enumerate(((n, f_in), (n, f_in), (f_in, f_out), (n, f_out)))]
+    w = min(f_in, f_out)
+    T, empty = dev(synth.normal_features(n, w, 376)), lambda r, c: torch.zeros(r, c, device="cuda")
+    S, Y, Gp, db = empty(n, w), empty(f_in, f_out), empty(n, f_in), empty(1, f_out).view(-1)
+    call = lambda: g.gcn_layer_backward(a, H, Zp, W, Gm, T, S, Y, Gp, dbias=db)
+    g.gcn_spmm_prepare(a, 0, w)
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(stream):
+        call()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=stream):
+        call()
+    for rep in range(4):
+        Gm.copy_(dev(synth.normal_features(n, f_out, 380 + rep)))
+        for x in (S, Y, Gp, db):
+            x.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        got = [x.clone() for x in (S, Y, Gp, db)]
+        call()
+        assert all(torch.equal(p, q) for p, q in zip(got, (S, Y, Gp, db))), rep
+    a.close()
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("n", [1, 64, 97, 416, 600, 1000])
 @pytest.mark.parametrize("f_in,f_out", [(256, 256), (257, 256), (40, 1700), (1000, 70)])
 def test_bias_gradient_beside_large_weight_gradients(n, f_in, f_out):

@@ -485,3 +485,65 @@ def test_wavefronts_that_add_up_partial_results(tmp_path):
         }
     """)
     assert r.returncode == 0 and r.stdout.split() == "1 1 2 15 16 16 16".split(), (r.returncode, r.stdout, r.stderr)
+
+
+def test_scratch_of_calls_that_overlap(tmp_path):
+    """A buffer belongs to one call at a time, those of a stream stay on it, and all memory is given back once.  Two threads each write their
+    name into what they are given and find it there when they are done."""
+    r = run_cpp(tmp_path, """
+        #include <atomic>
+        #include <cstdio>
+        #include <cstdlib>
+        #include <set>
+        #include <thread>
+        #include "scratch_pool.h"
+        int main() {
+            gcn::ScratchPool pool;
+            std::set<void*> live;
+            int fails = 0;
+            auto alloc = [&](void** p, size_t bytes) { *p = std::malloc(bytes); live.insert(*p); return 0; };
+            int s1 = 0, s2 = 0;
+            void *a, *b, *c, *d, *e;
+            pool.take(0, &s1, 100, &a, alloc);
+            pool.take(0, &s1, 100, &b, alloc);              // the first one is out
+            pool.take(0, &s2, 100, &c, alloc);
+            pool.take(1, &s1, 100, &d, alloc);
+            std::printf("%d ", (int)live.size());
+            pool.give(a);
+            pool.take(0, &s1, 125, &e, alloc);              // 100 and a quarter
+            std::printf("%d ", (int)(e == a));
+            pool.give(e);
+            pool.give(b);
+            pool.take(0, &s1, 1000, &e, alloc);             // one of the two is replaced, and kept
+            pool.take(0, &s1, 10, &a, alloc);
+            std::printf("%d %d ", (int)live.size(), (int)(a != e));
+            void* none = &s1;
+            const int rc = pool.take(0, &s1, 5000, &none, [&](void**, size_t) { ++fails; return -4; });
+            std::printf("%d %d %d ", rc, fails, (int)(none == &s1));
+            pool.give(a);
+            pool.give(e);
+            pool.take(0, &s1, 600, &b, alloc);
+            pool.take(0, &s1, 60, &a, alloc);
+            std::printf("%d%d ", (int)(b == e), (int)live.size());
+            pool.give(a); pool.give(b); pool.give(c); pool.give(d);
+            std::atomic<int> mixed{0};
+            auto work = [&](int name) {
+                for (int i = 0; i < 20000; ++i) {
+                    void* p;
+                    pool.take(0, &s1, 64, &p, [](void** q, size_t bytes) { *q = std::malloc(bytes); return 0; });
+                    volatile int* const at = (volatile int*)p;
+                    for (int k = 0; k < 16; ++k) at[k] = name;
+                    for (int k = 0; k < 16; ++k) mixed += at[k] != name;
+                    pool.give(p);
+                }
+            };
+            std::thread t(work, 1), u(work, 2);
+            t.join();
+            u.join();
+            int freed = 0;
+            pool.clear([&](void* p) { freed += (int)live.erase(p); std::free(p); });
+            pool.clear([&](void*) { freed += 100; });
+            std::printf("%d %d %d", (int)mixed, freed, (int)live.size());
+        }
+    """)
+    assert r.returncode == 0 and r.stdout.split() == "4 1 5 1 -4 1 1 15 0 5 0".split(), (r.returncode, r.stdout, r.stderr)
