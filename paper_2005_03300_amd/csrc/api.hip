@@ -210,7 +210,7 @@ ScratchScope::~ScratchScope() {
 
 static thread_local EpochEnd* g_epoch_end = nullptr;
 EpochEnd::EpochEnd(const Room& r) : room(r) {
-    if (room.left[0] || room.left[1]) g_epoch_end = this;
+    if (room.any) g_epoch_end = this;
 }
 EpochEnd::~EpochEnd() {
     if (g_epoch_end == this) g_epoch_end = nullptr;

@@ -8,6 +8,7 @@
 #include <string>
 #include <vector>
 
+#include "epoch_layout.h"
 #include "gcn.h"
 #include "largest_asked.h"
 #include "spmm_cost.h"
@@ -267,7 +268,7 @@ struct ScratchScope {
 // weights, all in one kernel.  While one of these is alive on a thread, the products and the loss that it has room for leave their
 // partial results there (epoch_end); finish() adds them up in the order in which kernels of their own do.
 struct EpochEnd {
-    static constexpr int MOST = 8;
+    static constexpr int MOST = EpochRoom::MOST;
     struct Sum {                                  // Y (M x N) = the sum of `parts` partial results, each M x N, or N x M when transposed
         const float* part;
         float* Y;
@@ -290,54 +291,29 @@ struct EpochEnd {
         int32_t count = 0, loss_at = -1;
         float lr = 0;
     } args;
-    struct Room {                                 // two pieces of memory, handed out first fit, and those for the gradients over few rows
-        static constexpr int FEW = 2, PIECES = FEW + MOST;
-        char* at[PIECES] = {};
-        size_t left[PIECES] = {};
-        static size_t whole(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
-        int fits(size_t bytes, bool few) const {
-            for (int k = PIECES - 1; few && k >= FEW; --k)        // (the last layer's is asked for first)
-                if (whole(bytes) <= left[k]) return k;
-            for (int k = 0; k < FEW; ++k)
-                if (whole(bytes) <= left[k]) return k;
-            return PIECES;
-        }
-        char* find(size_t bytes, bool few) const { return fits(bytes, few) < PIECES ? at[fits(bytes, few)] : nullptr; }
-        char* take(size_t bytes, bool few = false) {
-            const int k = fits(bytes, few);
-            if (k == PIECES) return nullptr;
-            char* const p = at[k];
-            at[k] += whole(bytes);
-            left[k] -= whole(bytes);
-            return p;
-        }
+    struct Room {                                 // where the partial results lie: of the loss, of a bias gradient, of the layers' weight gradients
+        void* loss = nullptr;
+        void* bias = nullptr;
+        void* grad[MOST] = {};
+        bool few[MOST] = {};                      // shares of 64 rows (see few_rows)
+        bool any = false;
     } room;
     float* W = nullptr;                           // of the layer whose gradient comes next
+    int layer = 0;                                // and its number
     explicit EpochEnd(const Room& r);             // no room: everything as without it
     ~EpochEnd();
-    // where the next `bytes` will lie, or NULL; and taking them
-    void* next(size_t bytes, bool few = false) const { return args.count < MOST ? room.find(bytes, few) : nullptr; }
-    void* take(size_t bytes, bool few = false) { return args.count < MOST ? room.take(bytes, few) : nullptr; }
     void add(const float* part, float* Y, int32_t M, int32_t N, int parts, bool transposed) {
         args.sums[args.count++] = Sum{part, Y, W, M, N, (int32_t)parts, transposed ? 1 : 0, 0};
     }
     int finish(float lr, hipStream_t s);
 };
 EpochEnd* epoch_end();                            // the thread's, or NULL
-// bytes of that scratch the split-K product (ta = 1) and the column sums take for the given shape
-size_t gemm_tn_scratch_bytes(int64_t M, int64_t N, int64_t K);
-bool gemm_tn_few(int64_t M, int64_t N, int64_t K);            // a gradient over few rows: as many partial results as a kernel of short rows leaves
+// bytes of scratch that the column sums take
 size_t colsum_scratch_bytes(int64_t rows, int32_t cols);
-size_t loss_scratch_bytes();
-size_t loss_part_bytes(int64_t n);               // what n rows need of it: a workgroup takes four at the least
 
 // Compute units and L2 size (one XCD's) of the current device, read once per device from the runtime.
 struct DeviceInfo { int cus; int64_t l2_bytes; };
 const DeviceInfo& device_info();
-// Compute units for which kernels are cut whose partial results lie in the caller's workspace: its size, asked before or under another device,
-// and the order of the sums must not depend on the device that is current.
-constexpr int SIZED_FOR_CUS = 256;
-
 // op(A) as stored
 inline Matrix& matrix_of(gcn_csr* a, int trans) { return (trans && !a->symmetric) ? a->At : a->A; }
 inline const Matrix& matrix_of(const gcn_csr* a, int trans) { return (trans && !a->symmetric) ? a->At : a->A; }
@@ -424,12 +400,12 @@ struct RowsNext {
     float* ypart = nullptr;
     bool done = false;
 };
-// The weight gradient H^T Z (M x f, over n rows) as what is next to the rows of Z: whether a kernel of them can leave its partial
-// results, and there is room for them; gradient_made takes the room and says that they lie there.
+// The weight gradient H^T Z (M x f, over n rows) of the EpochEnd's layer as what is next to the rows of Z: whether a kernel of them can leave its partial
+// results; gradient_made says that they lie there.
 bool gradient_next(RowsNext& next, int64_t n, int32_t f, const float* H, int64_t ldh, int32_t M);
 void gradient_made(const RowsNext& next, int64_t n, int32_t f, float* Y);
-// The loss of an epoch as what is next to a product of C columns, whose `parts` partial sums lie in what is left of the EpochEnd's room (NONE:
-// it has to be a launch of its own); loss_made takes that room once they do.
+// The loss of an epoch as what is next to a product of C columns, whose `parts` partial sums lie in the EpochEnd's room (NONE: it has to be a launch of
+// its own); loss_made says that they do.
 RowsNext loss_next(int32_t C, int64_t parts, const int32_t* labels, int64_t n_labelled, float* G);
 void loss_made(int64_t parts, int64_t n_labelled, float* loss);
 struct SpmmOpt {
@@ -466,13 +442,12 @@ int grow_retire(gcn_csr* a, float** buf, size_t* have, size_t need);
 
 // `row_scale` (optional): row i of C is multiplied by row_scale[i] after bias and epilogue
 int gemm_back_launch(int64_t n, int32_t f_in, int32_t f_out, const float* Hin, int64_t ldh, const float* S, const float* W,
-                     const float* Zprev, float* Y, float* Gprev, hipStream_t s, bool* handled);
+                     const float* Zprev, float* Y, float* Gprev, bool few, hipStream_t s, bool* handled);
+// `few`: a product with ta = 1 is cut into shares of 64 rows (see few_rows)
 int gemm_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, const float* B,
                 int64_t ldb, float* C, int64_t ldc, const float* bias, int epilogue, const float* Zprev,
-                int64_t ldzprev, hipStream_t s, const float* row_scale = nullptr);
+                int64_t ldzprev, hipStream_t s, const float* row_scale = nullptr, bool few = false);
 // the fused last layer of the epoch (f_in = 16, up to 256 classes)
-bool fused_last_supported(int32_t f_in, int32_t C);
-size_t fused_last_scratch_bytes(int64_t n, int32_t C);
 int fused_last_launch(int64_t n, int32_t C, const float* T, const float* W, const int32_t* labels, int64_t n_labelled,
                       float* loss, float* Y, float* S, const float* s_scale, float* Zout, float* Gout, void* scratch,
                       hipStream_t s);

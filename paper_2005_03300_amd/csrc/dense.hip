@@ -158,15 +158,10 @@ static inline unsigned nblocks(int64_t work) { return (unsigned)((work + 255) / 
 
 int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, const float* B,
                      int64_t ldb, float* C, int64_t ldc, const float* bias, int epilogue, const float* Zprev,
-                     int64_t ldzprev, hipStream_t s, bool* handled, const float* row_scale, bool* scaled);
+                     int64_t ldzprev, hipStream_t s, bool* handled, const float* row_scale, bool* scaled, bool few);
 
-size_t gemm_mfma_tn_scratch_bytes(int64_t M, int64_t N, int64_t K);
 int reduce_parts_launch(int32_t M, int32_t N, int parts, bool transposed, const float* part, float* C, int64_t ldc,
                         const float* bias, int epilogue, const float* Zprev, int64_t ldzprev, hipStream_t s);
-
-size_t gemm_tn_scratch_bytes(int64_t M, int64_t N, int64_t K) {
-    return gemm_mfma_tn_scratch_bytes(M, N, K);
-}
 
 static void colsum_split(int64_t rows, int64_t* parts_out, int64_t* rpb_out) {
     int64_t parts = (rows + 127) / 128;
@@ -185,10 +180,10 @@ size_t colsum_scratch_bytes(int64_t rows, int32_t cols) {
 
 int gemm_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, const float* B,
                 int64_t ldb, float* C, int64_t ldc, const float* bias, int epilogue, const float* Zprev,
-                int64_t ldzprev, hipStream_t s, const float* row_scale) {
+                int64_t ldzprev, hipStream_t s, const float* row_scale, bool few) {
     bool handled = false, scaled = false;
     GCN_TRY(gemm_mfma_launch(ta, tb, M, N, K, A, lda, B, ldb, C, ldc, bias, epilogue, Zprev, ldzprev, s, &handled,
-                             row_scale, &scaled));
+                             row_scale, &scaled, few));
     // kernels without a scaling store path leave the row factors to a pass of their own
     auto finish = [&]() { return (row_scale && !scaled) ? scale_rows_launch(M, (int32_t)N, C, ldc, row_scale, C, ldc, s) : (int)GCN_OK; };
     if (handled) return finish();
@@ -208,7 +203,7 @@ int colsum_launch(int64_t rows, int32_t cols, const float* G, int64_t ldg, float
     colsum_split(rows, &parts, &rpb);
     EpochEnd* const end = epoch_end();
     ScratchLease lease;
-    void* scratch = end ? end->take((size_t)parts * cols * sizeof(float)) : nullptr;
+    void* scratch = end ? end->room.bias : nullptr;
     const bool later = scratch != nullptr;
     if (!later) GCN_TRY(lease.get(&scratch, (size_t)parts * cols * sizeof(float), s));
     int tx = 64;
@@ -313,7 +308,7 @@ int gcn_gemm(int ta, int tb, int64_t M, int64_t N, int64_t K, const float* A, in
     if (lda < (ta ? M : K) || ldb < (tb ? K : N) || ldc < N) return fail(GCN_ERR_BADARG, "gcn_gemm: leading dimension too small");
     if (epilogue < GCN_EPI_NONE || epilogue > GCN_EPI_MASK) return fail(GCN_ERR_BADARG, "gcn_gemm: unknown epilogue");
     if (epilogue == GCN_EPI_MASK && (!Zprev || ldzprev < N)) return fail(GCN_ERR_BADARG, "gcn_gemm: mask epilogue needs Zprev with ld >= N");
-    return gemm_launch(ta, tb, M, N, K, A, lda, B, ldb, C, ldc, bias, epilogue, Zprev, ldzprev, (hipStream_t)stream);
+    return gemm_launch(ta, tb, M, N, K, A, lda, B, ldb, C, ldc, bias, epilogue, Zprev, ldzprev, (hipStream_t)stream, nullptr, ta && few_rows(M, N, K));
 }
 
 int gcn_relu(int64_t rows, int32_t cols, const float* Z, int64_t ldz, float* H, int64_t ldh, void* stream) {

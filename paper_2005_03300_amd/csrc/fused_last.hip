@@ -26,8 +26,6 @@ namespace gcn {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-static constexpr int FUSED_BLOCKS_MAX = 2048;
-
 struct FusedArgs {
     int64_t n;
     int32_t C;                // classes
@@ -482,35 +480,6 @@ __global__ __launch_bounds__(1024) void k_fused_y(int C, int CP, int blocks, con
     __shared__ SumLds lds;
     if ((int)blockIdx.x == CP) sum_of_losses(lpart, blocks, inv_m, loss, lds.l);
     else sum_of_fused(blockIdx.x, C, CP, blocks, part, lds.y, [&](int e, float y) { Y[e] = y; });
-}
-
-static int fused_nt(int32_t C) {
-    const int need = (C + 15) / 16;
-    const int have[6] = {1, 2, 3, 4, 8, 16};
-    for (int i = 0; i < 6; ++i)
-        if (have[i] >= need) return have[i];
-    return 0;
-}
-
-// Four strips and more per wavefront, which pay for its operands and for its partial result (233 K rows, 41 classes, whole layer: 26 us
-// with 2048 workgroups, 21 with a thousand; 1.8 M, 24: 74 and 75), but as many workgroups as there are compute units before any takes a
-// second strip: a strip is a chain of latencies, and beyond 64 classes a workgroup goes through its strips one by one (epochs of
-// 982 rows, 183 classes 66.5 us with 4 workgroups, 36.0 with 62; 12 K, 166: 73.7 with 48, 49.9 with 256).
-static int64_t fused_blocks(int64_t n, int NT) {
-    const int64_t strips = (n + 15) / 16, at_once = NT > 4 ? strips : (strips + 3) / 4;
-    constexpr int64_t cus = SIZED_FOR_CUS;
-    int64_t blocks = (strips + 15) / 16;
-    if (blocks < cus) blocks = at_once < cus ? at_once : cus;
-    return blocks > FUSED_BLOCKS_MAX ? FUSED_BLOCKS_MAX : (blocks < 1 ? 1 : blocks);
-}
-
-bool fused_last_supported(int32_t f_in, int32_t C) { return f_in == 16 && C >= 1 && fused_nt(C) != 0; }
-
-size_t fused_last_scratch_bytes(int64_t n, int32_t C) {
-    const int NT = fused_nt(C);
-    if (!NT) return 0;
-    const size_t per = (size_t)16 * 16 * NT * sizeof(float);
-    return (size_t)fused_blocks(n, NT) * per + (size_t)FUSED_BLOCKS_MAX * sizeof(double);
 }
 
 template <int NT>

@@ -998,82 +998,6 @@ static void launch_tn(const TnArgs& args, bool stream, dim3 grid, hipStream_t s)
     else launch_lds<k_gemm_tn<MG, NT, false>>(grid, 64 * args.gw * args.rw, lds, s, args);
 }
 
-// Launch geometry of the A^T B product (K long): which operand goes on the 64-column groups, wavefronts per
-// workgroup, split of K, partial buffers.  Any shape.
-struct TnShape {
-    bool swap, narrow;
-    int64_t Mw, Nw, blocks, kpb;
-    int NT, ny, nz, gw, rw, MG, fold;
-    bool few;
-    size_t scratch_bytes;
-};
-
-static TnShape tn_shape(int64_t M, int64_t N, int64_t K) {
-    TnShape g;
-    // Put the wider of (M, N) on the 64-column groups: if N > M compute C^T = B^T A and let the
-    // reduction write it back transposed.
-    g.swap = N > M;
-    g.Mw = g.swap ? N : M;
-    g.Nw = g.swap ? M : N;
-    const int nt = (int)((g.Nw + 15) / 16);
-    g.ny = (nt + 3) / 4;                                  // up to 64 columns of B per wavefront, in equal shares
-    g.NT = (nt + g.ny - 1) / g.ny;
-    g.narrow = g.Mw <= 32;
-    const int groups = (int)((g.Mw + 63) / 64);
-    g.rw = 1; g.nz = 1; g.gw = 4;
-    if (g.narrow) {
-        g.MG = (int)((g.Mw + 15) / 16);
-    } else {
-        // column groups per wavefront: what two sets of accumulators and two trips leave room for (250 registers)
-        const int mg_max = g.NT >= 2 ? 1 : 3;
-        // wavefronts on different groups: one per group up to 8, else the count in 4..8 that leaves the fewest idle
-        // slots (300 columns: 5 groups on 5 wavefronts instead of 2+1+1+1 on 4)
-        g.gw = groups;
-        if (groups > 8) {
-            int best = 1 << 30;
-            for (int w = 4; w <= 8; ++w) {
-                const int idle = (groups + w - 1) / w * w - groups;
-                if (idle < best) { best = idle; g.gw = w; }
-            }
-        }
-        g.rw = g.gw >= 4 ? 1 : 4 / g.gw;                  // 1 group: 4 sets of rows, 2: 2, 3: 1
-        g.MG = (groups + g.gw - 1) / g.gw;
-        if (g.MG > mg_max) g.MG = mg_max;
-        g.nz = (groups + g.gw * g.MG - 1) / (g.gw * g.MG);
-    }
-    // Workgroups over K: at least two trips of every wavefront each,
-    const int64_t rows = g.narrow ? 64 : 16 * g.rw;       // rows per trip of a workgroup
-    const int64_t count = g.Mw * g.Nw;
-    // or one trip of as few rows as a kernel of short rows takes, which then leaves the same partial results (see gradient_next; as a
-    // launch of their own 64 x 16 over 16 K rows take 8.5 us, with two trips 8.3, over 2 K and 32 K, and other shapes, the same).
-    // Only where they take no more memory than K rows of Nw floats, which an epoch has (64 columns: whole shares).
-    g.few = K <= 32768 && g.Mw <= 64 && g.Nw <= 16 && (K + 63) / 64 * g.Mw <= K;
-    int64_t blocks = g.few ? (K + rows - 1) / rows : K / (2 * rows);
-    // but no more workgroups than run side by side: a workgroup loads its next trip while it multiplies, and the partial results
-    // are written and read once more.  One per compute unit, two where the partial results are below 1/40 of the operands
-    // (200 x 32 over 1 M rows 231 and 199 us; 256 x 64 over 120 K rows 52 and 64); four of the narrow kernel (16 x 16 over 4.4 M rows:
-    // 105 us, two 150, eight 112), eight where a row of both has less than 32 floats, so that lanes are idle and less is on its
-    // way (7 x 3 over 3.8 M rows: 62 us, four 67; 16 x 8 over 3.6 M 72 and 77).  With up to 8192, and partial results below an eighth of the operands: 300 x 16 over 14.2 M
-    // rows 3.20 ms (now 2.86, 6.4 TB/s), 128 x 16 over 4.4 M 425 us (364), 256 x 64 over 120 K 89 (52), 602 x 64 over 100 K 255 (127).
-    const int64_t cus = SIZED_FOR_CUS, operands = K * (g.Mw + g.Nw);
-    int64_t most = (g.narrow ? (g.Mw + g.Nw < 32 ? 8 : 4) : (80 * cus * count <= operands ? 2 : 1)) * cus / ((int64_t)g.ny * g.nz);
-    // partial results below a third of the operands, unless that leaves fewer than 64 workgroups over K (fewer still where
-    // the result alone is large)
-    const int64_t fair = operands / (3 * count);
-    const int64_t least = count >= (1ll << 26) ? 1 : (count > (1ll << 20) ? (1ll << 26) / count : 64);
-    if (most > fair) most = fair;
-    if (most < least) most = least;
-    if (blocks > most) blocks = most;
-    if (blocks < 1) blocks = 1;
-    int64_t kpb = (K + blocks - 1) / blocks;
-    kpb = (kpb + rows - 1) / rows * rows;
-    g.kpb = kpb;
-    g.blocks = (K + kpb - 1) / kpb;
-    g.fold = g.blocks > 512 ? 64 : 0;                     // two-stage reduction when there are many partials
-    g.scratch_bytes = (size_t)(g.blocks + g.fold) * count * sizeof(float);
-    return g;
-}
-
 // C = the sum of `parts` partial results (each M x N, or N x M when transposed) in a fixed order, plus bias, epilogue.
 int reduce_parts_launch(int32_t M, int32_t N, int parts, bool transposed, const float* part, float* C, int64_t ldc,
                         const float* bias, int epilogue, const float* Zprev, int64_t ldzprev, hipStream_t s) {
@@ -1098,14 +1022,9 @@ static const float* folded(const TnShape& g, int64_t count, float* part, hipStre
     return out;
 }
 
-size_t gemm_mfma_tn_scratch_bytes(int64_t M, int64_t N, int64_t K) {
-    return tn_shape(M, N, K).scratch_bytes;
-}
-bool gemm_tn_few(int64_t M, int64_t N, int64_t K) { return tn_shape(M, N, K).few; }
-
 int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, const float* B,
                      int64_t ldb, float* C, int64_t ldc, const float* bias, int epilogue, const float* Zprev,
-                     int64_t ldzprev, hipStream_t s, bool* handled, const float* row_scale, bool* scaled) {
+                     int64_t ldzprev, hipStream_t s, bool* handled, const float* row_scale, bool* scaled, bool few) {
     *handled = false;
     *scaled = false;
     if (!ta) {
@@ -1208,11 +1127,11 @@ int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const floa
     }
     // ta: C = A^T B with K long
     if (tb) return GCN_OK;
-    const TnShape g = tn_shape(M, N, K);
+    const TnShape g = tn_shape(M, N, K, few);
     if (g.blocks >= (1ll << 31) || g.ny > 65535 || g.nz > 65535 || M * N >= (1ll << 36)) return fail(GCN_ERR_RANGE, "gcn_gemm: output too large");
     EpochEnd* const end = !bias && epilogue == GCN_EPI_NONE && ldc == N ? epoch_end() : nullptr;
     ScratchLease lease;
-    void* scratch = end ? end->take(g.scratch_bytes, g.few) : nullptr;
+    void* scratch = end ? end->room.grad[end->layer] : nullptr;
     const bool later = scratch != nullptr;
     if (!later) GCN_TRY(lease.get(&scratch, g.scratch_bytes, s));
     TnArgs args;
@@ -1247,19 +1166,16 @@ int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const floa
 }
 
 bool gradient_next(RowsNext& next, int64_t n, int32_t f, const float* H, int64_t ldh, int32_t M) {
-    if (!epoch_end() || n < 64 || f > 16 || f % 4 != 0 || M > 64) return false;
-    const TnShape g = tn_shape(M, f, n);                        // (64 rows a trip: four wavefronts of 16)
-    if (!g.few || g.kpb != 64 || g.fold) return false;
-    next.ypart = (float*)epoch_end()->next(g.scratch_bytes, true);
-    if (!next.ypart) return false;
+    const EpochEnd* const end = epoch_end();
+    if (!end || !end->room.few[end->layer] || f > 16 || f % 4 != 0 || M > 64) return false;
+    next.ypart = (float*)end->room.grad[end->layer];
     next.kind |= RowsNext::GRAD;
     next.H = H; next.ldh = ldh; next.M = M;
     return true;
 }
 
 void gradient_made(const RowsNext& next, int64_t n, int32_t f, float* Y) {
-    const TnShape g = tn_shape(next.M, f, n);
-    epoch_end()->add((const float*)epoch_end()->take(g.scratch_bytes, true), Y, next.M, f, (int)g.blocks, false);
+    epoch_end()->add(next.ypart, Y, next.M, f, (int)((n + 63) / 64), false);
 }
 
 // Whether Gprev (n rows of 16 floats) shares no memory with a matrix of n rows of 16 floats, `ld` apart, that the same kernel
@@ -1278,7 +1194,7 @@ static bool no_rows_shared(int64_t n, int32_t M, const float* Gprev, const float
 // stays false where Gprev lies across rows of an operand that another workgroup may not have read yet: the
 // two products one after the other read all of Hin before they write Gprev.
 int gemm_back_launch(int64_t n, int32_t f_in, int32_t f_out, const float* Hin, int64_t ldh, const float* S, const float* W,
-                     const float* Zprev, float* Y, float* Gprev, hipStream_t s, bool* handled) {
+                     const float* Zprev, float* Y, float* Gprev, bool few, hipStream_t s, bool* handled) {
     *handled = false;
     const bool wide = f_in != 16 || f_out != 16 || !al16(S);          // (k_gemm_back takes rows of S in whole pieces)
     if (n < 64 || ldh % 4 != 0 || !al16(Hin) || !al16(Zprev) || !al16(Gprev)) return GCN_OK;
@@ -1290,10 +1206,10 @@ int gemm_back_launch(int64_t n, int32_t f_in, int32_t f_out, const float* Hin, i
     } else {
         if (!row_by_row(n, Gprev, Hin, ldh) || !row_by_row(n, Gprev, S, 16) || !row_by_row(n, Gprev, Zprev, 16)) return GCN_OK;
     }
-    const TnShape g = tn_shape(f_in, f_out, n);
+    const TnShape g = tn_shape(f_in, f_out, n, few);
     EpochEnd* const end = epoch_end();
     ScratchLease lease;
-    void* scratch = end ? end->take(g.scratch_bytes, g.few) : nullptr;
+    void* scratch = end ? end->room.grad[end->layer] : nullptr;
     const bool later = scratch != nullptr;
     if (!later) GCN_TRY(lease.get(&scratch, g.scratch_bytes, s));
     TnArgs args;

@@ -8,12 +8,6 @@
 
 namespace gcn {
 
-static int resolve_order(int order, int32_t f_in, int32_t f_out) {
-    if (order == GCN_ORDER_GEMM_FIRST || order == GCN_ORDER_SPMM_FIRST) return order;
-    // The SpMM costs in proportion to its width: run it at min(f_in, f_out).
-    return f_out <= f_in ? GCN_ORDER_GEMM_FIRST : GCN_ORDER_SPMM_FIRST;
-}
-
 // Z = epilogue(op(A) X) with the handle's normalised matrix.  `xs` (n x f, ld f) receives the
 // pre-scaled operand of the value-free form; it may be X itself when X is a temporary with ld f,
 // or NULL to force the valued product.  `prescaled`: the producer of X already applied the row factors
@@ -53,9 +47,9 @@ static RowsNext gemm_next(const gcn_csr* a, int32_t f, const float* W, int32_t N
 
 static int timed_gemm(int ta, int tb, int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, const float* B,
                       int64_t ldb, float* C, int64_t ldc, const float* bias, int epilogue, const float* Zprev,
-                      int64_t ldzprev, hipStream_t s, const float* row_scale = nullptr) {
+                      int64_t ldzprev, hipStream_t s, const float* row_scale = nullptr, bool few = false) {
     PhaseTimer pt(s, GCN_PHASE_GEMM);
-    return gemm_launch(ta, tb, M, N, K, A, lda, B, ldb, C, ldc, bias, epilogue, Zprev, ldzprev, s, row_scale);
+    return gemm_launch(ta, tb, M, N, K, A, lda, B, ldb, C, ldc, bias, epilogue, Zprev, ldzprev, s, row_scale, few);
 }
 
 // `xs`: scratch for the value-free product (n x the SpMM width) or NULL; `t_scratch` says that T is
@@ -103,6 +97,12 @@ static int layer_forward_impl(gcn_csr* a, int32_t f_in, int32_t f_out, const flo
     return GCN_OK;
 }
 
+// Whether the weight gradient of a layer is cut into shares of 64 rows: alike in an epoch, where there is room, and in a call of its own, for the same bits.
+static bool gradient_few(int64_t n, int32_t f_in, int32_t f_out) {
+    if (const EpochEnd* const end = epoch_end()) return end->room.few[end->layer];
+    return few_rows(f_in, f_out, n);
+}
+
 static int layer_backward_impl(gcn_csr* a, int32_t f_in, int32_t f_out, const float* Hin, int64_t ldh,
                                const float* Zprev, const float* W, const float* G, const float* T, float* S, float* Y,
                                float* dbias, float* Gprev, int order, hipStream_t s, float* xs = nullptr,
@@ -113,6 +113,7 @@ static int layer_backward_impl(gcn_csr* a, int32_t f_in, int32_t f_out, const fl
         PhaseTimer pt(s, GCN_PHASE_OTHER);
         GCN_TRY(colsum_launch(n, f_out, G, f_out, dbias, s));
     }
+    const bool few = gradient_few(n, f_in, f_out);
     if (order == GCN_ORDER_GEMM_FIRST) {
         // S = A G;  Y = Hin^T S;  Gprev = (S W^T) (.) sigma'(Zprev)
         // (an epoch's Gprev lies in no operand's memory; at width 16 the dense products are one launch together)
@@ -128,16 +129,16 @@ static int layer_backward_impl(gcn_csr* a, int32_t f_in, int32_t f_out, const fl
         if (Gprev && !next.done) {
             PhaseTimer pt(s, GCN_PHASE_GEMM);
             bool both = false;
-            GCN_TRY(gemm_back_launch(n, f_in, f_out, Hin, ldh, S, W, Zprev, Y, Gprev, s, &both));
+            GCN_TRY(gemm_back_launch(n, f_in, f_out, Hin, ldh, S, W, Zprev, Y, Gprev, few, s, &both));
             if (both) return GCN_OK;
         }
-        GCN_TRY(timed_gemm(1, 0, f_in, f_out, n, Hin, ldh, S, f_out, Y, f_out, nullptr, GCN_EPI_NONE, nullptr, 0, s));
+        GCN_TRY(timed_gemm(1, 0, f_in, f_out, n, Hin, ldh, S, f_out, Y, f_out, nullptr, GCN_EPI_NONE, nullptr, 0, s, nullptr, few));
         if (Gprev && !next.done)
             GCN_TRY(timed_gemm(0, 1, n, f_in, f_out, S, f_out, W, f_out, Gprev, f_in, nullptr, GCN_EPI_MASK, Zprev, f_in, s));
     } else {
         // Y = (A^T Hin)^T G = T^T G;  Gprev = (A (G W^T)) (.) sigma'(Zprev): the same matrices, with the
         // SpMM at width f_in.
-        GCN_TRY(timed_gemm(1, 0, f_in, f_out, n, T, f_in, G, f_out, Y, f_out, nullptr, GCN_EPI_NONE, nullptr, 0, s));
+        GCN_TRY(timed_gemm(1, 0, f_in, f_out, n, T, f_in, G, f_out, Y, f_out, nullptr, GCN_EPI_NONE, nullptr, 0, s, nullptr, few));
         if (Gprev) {
             const float* ps = pre_scale(a, s_scratch);
             GCN_TRY(timed_gemm(0, 1, n, f_in, f_out, G, f_out, W, f_out, S, f_in, nullptr, GCN_EPI_NONE, nullptr, 0, s, ps));
@@ -146,59 +147,6 @@ static int layer_backward_impl(gcn_csr* a, int32_t f_in, int32_t f_out, const fl
         }
     }
     return GCN_OK;
-}
-
-// ---- epoch workspace layout -------------------------------------------------------------------
-struct EpochLayout {
-    std::vector<size_t> Z, H, T, G;   // byte offsets per layer index 0..L_w-1 (layer l = index + 1)
-    size_t S = 0, XS = 0, total = 0;  // XS: pre-scaled SpMM operand of the value-free product
-    size_t scratch = 0;               // partial sums of the fused last layer, and the next where they do not fit XS
-    size_t part = 0, part_bytes = 0;  // partial sums of the weight gradients and of the loss
-    std::vector<int> order;
-};
-
-static size_t round256(size_t b) { return (b + 255) & ~(size_t)255; }
-
-static EpochLayout epoch_layout(int64_t n, int32_t L, const int32_t* dims, int order) {
-    EpochLayout lay;
-    size_t off = 0, smax = 0;
-    auto take = [&](size_t elems) { size_t o = off; off += round256(elems * sizeof(float)); return o; };
-    for (int l = 0; l < L; ++l) {
-        const int32_t fi = dims[l], fo = dims[l + 1];
-        const int ord = resolve_order(order, fi, fo);
-        lay.order.push_back(ord);
-        // Hidden layers keep only H = ReLU(Z): the ReLU is fused into the kernel that produces Z, and
-        // sigma'(Z) = [Z > 0] = [H > 0], so backward never needs Z itself.  The last layer keeps Z.
-        lay.Z.push_back(take((size_t)n * fo));
-        lay.H.push_back(lay.Z.back());
-        lay.T.push_back(take((size_t)n * (ord == GCN_ORDER_GEMM_FIRST ? fo : fi)));
-        lay.G.push_back(take((size_t)n * fo));
-        const size_t sneed = (size_t)n * (ord == GCN_ORDER_GEMM_FIRST ? fo : fi);
-        if (sneed > smax) smax = sneed;
-    }
-    lay.S = take(smax);
-    lay.XS = take(smax);
-    // The partial sums of the reductions over n live in the caller's workspace too, so that an epoch never touches
-    // library-owned scratch (which is per stream and would have to exist before a graph capture).  XS is idle outside
-    // the sparse products: it holds the partial sums of the weight gradients and of the loss where it is large
-    // enough, and a region of their own holds what does not fit.
-    size_t sc = loss_scratch_bytes(), tn = sc;
-    for (int l = 0; l < L; ++l) {
-        const size_t need = gemm_tn_scratch_bytes(dims[l], dims[l + 1], n);
-        if (need > tn) tn = need;
-    }
-    const size_t xs_bytes = smax * sizeof(float);
-    if (tn > xs_bytes && tn > sc) sc = tn;
-    // the fused last layer (SpMM-first order; a single layer can be put into that order by the pre-aggregated epoch)
-    if ((lay.order[L - 1] == GCN_ORDER_SPMM_FIRST || L == 1) && fused_last_supported(dims[L - 1], dims[L])) {
-        const size_t need = fused_last_scratch_bytes(n, dims[L]);
-        if (need > sc) sc = need;
-    }
-    lay.scratch = take((sc + sizeof(float) - 1) / sizeof(float));
-    lay.part = tn > xs_bytes ? lay.scratch : lay.XS;
-    lay.part_bytes = tn > xs_bytes ? sc : xs_bytes;
-    lay.total = off;
-    return lay;
 }
 
 // Whether no two of the weight and gradient matrices share memory (tied weights do: their gradients and updates come one after another).
@@ -212,29 +160,15 @@ static bool apart(int32_t L, const int32_t* dims, float* const* W, float* const*
     return true;
 }
 
-// Where an epoch leaves the partial sums of all its reductions side by side, to be added up in one launch at its end (EpochEnd; the launches it
-// saves are what a small epoch waits for: 4096 vertices, 64-16-8: 59 -> 50 us; 120 K vertices, 256-64-64-41: 1030 -> 1016).  In memory
-// that is idle from the loss on, so that the workspace is not larger for it: the region of the scaled operand where the products need none
-// (`value_free`), else the first layer's T, which forward has read by then or, with P0 given, nobody does; and the scratch unless the fused
-// last layer (`fuse`) has it.  The gradients over few rows, which have more partial results, lie
-// in the T of layers whose forward product has read it (tn_shape sees to it that a layer's own would do).  All of them or none.
-static EpochEnd::Room end_room(const EpochLayout& lay, char* ws, int64_t n, int32_t L, const int32_t* dims, bool value_free, bool p0, bool fuse) {
+static EpochEnd::Room room_at(char* ws, const EpochRoom& at, int32_t L) {
     EpochEnd::Room room;
-    if (L >= EpochEnd::MOST) return room;
-    const bool t_idle = p0 || (lay.order[0] == GCN_ORDER_GEMM_FIRST && L >= 2);
-    if (!value_free) { room.at[0] = ws + lay.XS; room.left[0] = lay.scratch - lay.XS; }
-    else if (t_idle) { room.at[0] = ws + lay.T[0]; room.left[0] = lay.G[0] - lay.T[0]; }
-    if (!fuse) { room.at[1] = ws + lay.scratch; room.left[1] = lay.total - lay.scratch; }
-    for (int l = value_free && t_idle ? 1 : 0; l < L; ++l)
-        if (lay.order[l] == GCN_ORDER_GEMM_FIRST) {
-            room.at[EpochEnd::Room::FEW + l] = ws + lay.T[l];
-            room.left[EpochEnd::Room::FEW + l] = lay.G[l] - lay.T[l];
-        }
-    EpochEnd::Room left = room;                   // in the order in which they are taken
-    bool all = fuse || left.take(loss_part_bytes(n));
-    for (int l = fuse ? L - 2 : L - 1; l >= 0 && all; --l)
-        all = left.take(gemm_tn_scratch_bytes(dims[l], dims[l + 1], n), gemm_tn_few(dims[l], dims[l + 1], n)) != nullptr;
-    return all ? room : EpochEnd::Room();
+    room.any = at.any;
+    if (at.loss != EpochRoom::NOWHERE) room.loss = ws + at.loss;
+    for (int l = 0; l < L && at.any; ++l) {
+        if (at.grad[l] != EpochRoom::NOWHERE) room.grad[l] = ws + at.grad[l];
+        room.few[l] = at.few[l];
+    }
+    return room;
 }
 
 static int check_dims(int64_t n, int32_t L, const int32_t* dims) {
@@ -279,13 +213,13 @@ int gcn_layer_backward(gcn_csr* a, int32_t f_in, int32_t f_out, const float* Hin
     // on 600 vertices 119 us, in one launch 136; 3000-64 39 and 41; 512-256 on 416 38.5 and 39.5, on 64 31.7 and 30.4; 256-256 33.4 and 32.7).
     if (!dbias || y_is_w || (int64_t)f_in * f_out > 65536) return layer_backward_impl(a, f_in, f_out, Hin, ldh, Zprev, W, G, T, S, Y, dbias, Gprev, order, s);
     // The partial results of both gradients side by side, added up in one launch (32-8 on 5000 vertices 16.5 -> 13.6 us, two layers of 200 K 508 -> 502).
-    const size_t sums = EpochEnd::Room::whole(colsum_scratch_bytes(a->n, f_out)), products = EpochEnd::Room::whole(gemm_tn_scratch_bytes(f_in, f_out, a->n));
-    ScratchLease lease;
-    void* scratch = nullptr;
-    GCN_TRY(lease.get(&scratch, sums + products, s));
     EpochEnd::Room room;
-    room.at[0] = (char*)scratch;
-    room.left[0] = sums + products;
+    room.few[0] = gradient_few(a->n, f_in, f_out);
+    const size_t sums = round256(colsum_scratch_bytes(a->n, f_out)), products = tn_shape(f_in, f_out, a->n, room.few[0]).scratch_bytes;
+    ScratchLease lease;
+    GCN_TRY(lease.get(&room.bias, sums + products, s));
+    room.grad[0] = (char*)room.bias + sums;
+    room.any = true;
     EpochEnd end(room);
     GCN_TRY(layer_backward_impl(a, f_in, f_out, Hin, ldh, Zprev, W, G, T, S, Y, dbias, Gprev, order, s));
     PhaseTimer pt(s, GCN_PHASE_OTHER);
@@ -343,9 +277,10 @@ static int epoch_impl(gcn_csr* a, int32_t L_w, const int32_t* dims, const float*
     const int fuse_mode = cfg_of(a).fused_last;
     const bool fuse = fuse_mode != 0 && layer_order(last) == GCN_ORDER_SPMM_FIRST &&
                       fused_last_supported(dims[last], dims[L_w]);
-    EpochEnd end(apart(L_w, dims, W, Y) ? end_room(lay, ws, n, L_w, dims, use_value_free(a), P0 != nullptr, fuse) : EpochEnd::Room());
+    const EpochRoom room = apart(L_w, dims, W, Y) ? epoch_room(lay, n, L_w, dims, use_value_free(a), P0 != nullptr, fuse, fuse_mode == 2) : EpochRoom();
+    EpochEnd end(room_at(ws, room, L_w));
     // (with room for all of them nothing asks for the scratch, where the others' results may lie)
-    ScratchScope scratch_scope(ws + lay.part, epoch_end() ? 0 : lay.part_bytes);
+    ScratchScope scratch_scope(ws + lay.XS, epoch_end() ? 0 : lay.total - lay.XS);
     const float* Hin = H0;
     bool t_made = false, loss_done = false;
     for (int l = 0; l < L_w; ++l) {
@@ -390,6 +325,7 @@ static int epoch_impl(gcn_csr* a, int32_t L_w, const int32_t* dims, const float*
         }
         const float* Hl = l > 0 ? at(lay.H[l - 1]) : H0;
         end.W = W[l];
+        end.layer = l;
         GCN_TRY(layer_backward_impl(a, dims[l], dims[l + 1], Hl, dims[l], l > 0 ? at(lay.Z[l - 1]) : nullptr, W[l],
                                     at(lay.G[l]), layer_T(l), at(lay.S), Y[l], nullptr, l > 0 ? at(lay.G[l - 1]) : nullptr,
                                     layer_order(l), s, at(lay.XS), true));

@@ -15,8 +15,6 @@
 
 namespace gcn {
 
-static constexpr int LOSS_BLOCKS_MAX = 2048;
-
 template <int L, bool RAGGED, int VEC = 4>
 __global__ __launch_bounds__(256) void k_softmax_nll(int64_t n, int32_t C, const float* __restrict__ Z, int64_t ldz,
                                                      const int32_t* __restrict__ labels, float* __restrict__ G,
@@ -139,13 +137,9 @@ static void launch_rows(int64_t blocks, int64_t n, int32_t C, const float* Z, in
 
 static void dispatch_rows(int64_t n, int32_t C, const float* Z, int64_t ldz, const int32_t* labels,
                           float* G, int64_t ldg, double* part, int64_t* blocks_out, float inv_m, hipStream_t s) {
-    int L = 1;                                  // up to four classes a row is one lane's (two classes, 2 M rows: 12.9 us, two lanes 24.8)
-    while (4 * L < C) L <<= 1;
-    const int64_t rows_per_block = 256 / L;
-    int64_t blocks = (n + rows_per_block - 1) / rows_per_block;
-    if (blocks > LOSS_BLOCKS_MAX) blocks = LOSS_BLOCKS_MAX;
+    const int64_t blocks = loss_blocks(n, C);
     *blocks_out = blocks;
-    switch (L) {
+    switch (loss_lanes(C)) {
         case 1: launch_rows<1>(blocks, n, C, Z, ldz, labels, G, ldg, part, inv_m, s); break;
         case 2: launch_rows<2>(blocks, n, C, Z, ldz, labels, G, ldg, part, inv_m, s); break;
         case 4: launch_rows<4>(blocks, n, C, Z, ldz, labels, G, ldg, part, inv_m, s); break;
@@ -160,7 +154,7 @@ RowsNext loss_next(int32_t C, int64_t parts, const int32_t* labels, int64_t n_la
     RowsNext next;
     const EpochEnd* const end = epoch_end();
     if (!end || C > 16 || C % 4 != 0 || parts > LOSS_BLOCKS_MAX) return next;
-    next.part = (double*)end->next(parts * sizeof(double));
+    next.part = (double*)end->room.loss;
     if (!next.part) return next;
     next.kind = RowsNext::LOSS;
     next.labels = labels;
@@ -171,12 +165,9 @@ RowsNext loss_next(int32_t C, int64_t parts, const int32_t* labels, int64_t n_la
 
 void loss_made(int64_t parts, int64_t n_labelled, float* loss) {
     EpochEnd* const end = epoch_end();
-    end->args.lpart = (double*)end->take(parts * sizeof(double));
+    end->args.lpart = (double*)end->room.loss;
     end->args.lparts = parts; end->args.inv_m = 1.0 / (double)n_labelled; end->args.loss = loss;
 }
-
-size_t loss_part_bytes(int64_t n) { return (size_t)(n < 4 * LOSS_BLOCKS_MAX ? (n + 3) / 4 : LOSS_BLOCKS_MAX) * sizeof(double); }
-size_t loss_scratch_bytes() { return (size_t)LOSS_BLOCKS_MAX * sizeof(double); }
 
 }  // namespace gcn
 
@@ -186,7 +177,7 @@ static int softmax_nll_impl(int64_t n, int32_t C, const float* Z, int64_t ldz, c
                             float* loss, float* G, int64_t ldg, hipStream_t s) {
     EpochEnd* const end = epoch_end();
     ScratchLease lease;
-    void* scratch = end ? end->take(loss_part_bytes(n)) : nullptr;
+    void* scratch = end ? end->room.loss : nullptr;
     const bool later = scratch != nullptr;
     if (!later) GCN_TRY(lease.get(&scratch, loss_scratch_bytes(), s));
     double* part = (double*)scratch;
@@ -195,8 +186,7 @@ static int softmax_nll_impl(int64_t n, int32_t C, const float* Z, int64_t ldz, c
     if (C <= 256) {
         dispatch_rows(n, C, Z, ldz, labels, G, ldg, part, &blocks, inv_m, s);
     } else {
-        blocks = (n + 3) / 4;
-        if (blocks > LOSS_BLOCKS_MAX) blocks = LOSS_BLOCKS_MAX;
+        blocks = loss_blocks(n, C);
         hipLaunchKernelGGL(k_softmax_nll_wide, dim3((unsigned)blocks), dim3(256), 0, s, n, C, Z, ldz, labels, G, ldg,
                            inv_m, part);
     }

@@ -1190,6 +1190,46 @@ def test_gradients_beside_short_rows(n, dims):
     a.close()
 
 
+# dense products among an epoch's launches, forward and backward, counted by hand; others: an (empty) span of each layer that goes forward, and the sums with the update
+@pytest.mark.parametrize("dims,n,gemm,other", [((64, 16, 8), n, 1, 3) for n in (64, 65, 127, 128, 129, 1000, 1023, 4095, 4096, 4097, 10_001, 16_383, 16_384)] +
+                         [((64, 16, 8), 16_385, 2, 3), ((65, 16, 8), 4096, 2, 3), ((64, 16, 8), 63, 6, 3), ((32, 16, 8), 32_768, 1, 3), ((33, 16, 16, 12), 5000, 1, 4),
+                          ((16, 8), 200, 1, 2), ((63, 16), 4097, 1, 2), ((64, 16, 41), 4097, 2, 2), ((16, 64, 8), 4096, 4, 3), ((8, 64, 4), 1024, 4, 3)])
+def test_launches_of_an_epoch_on_short_rows(dims, n, gemm, other):
+    """Weight gradients of up to 64 columns beside the rows at any number of them, the loss beside the rows, and all sums and the update in one launch, also where a layer
+    widens; the bits of the layer calls."""
+    g = G()
+    rs = np.random.default_rng(176)
+    u, v = rs.integers(0, n, (2, 2 * n)).astype(np.int32)
+    a = g.gcn_csr_create(n, dev(u), dev(v), g.ADD_SELF_LOOPS | g.NORM_ROW | g.BUILD_TRANSPOSE)
+    assert all("k_spmm_short" in g.gcn_spmm_describe(a, 0, min(p, q)) for p, q in zip(dims, dims[1:]))
+    H0, y = dev(synth.normal_features(n, dims[0], 177)), dev(rs.integers(0, dims[-1], n).astype(np.int32))
+    W, L = [dev(w) for w in synth.glorot_weights(dims, 178)], len(dims) - 1
+    first = [w.clone() for w in W]
+    Y, loss = [torch.full_like(w, float("nan")) for w in W], torch.zeros(1, device="cuda")
+    size = g.gcn_epoch_workspace_bytes(n, dims)
+    ws = torch.full((size + 4096,), 255, dtype=torch.uint8, device="cuda")
+    g.gcn_epoch_prepare(a, dims)
+    g.gcn_config(g.CFG_TIMING, 1)
+    try:
+        g.gcn_timing_read_phases()
+        g.gcn_epoch(a, dims, H0, y, W, Y, 0.5, loss, ws[:size])
+        spans = g.gcn_timing_read_phases()
+    finally:
+        g.gcn_config(g.CFG_TIMING, 0)
+    assert (spans["gemm"][0], spans["other"][0]) == (gemm, other), spans
+    assert bool((ws[size:] == 255).all())
+    assert all(torch.equal(w, w0 - 0.5 * y1) for w, w0, y1 in zip(W, first, Y))
+    for l in range(L - 1, -1, -1):
+        if dims[l + 1] > dims[l]:
+            continue                                                # (A^T H first: its T is the epoch's own)
+        Gl = g.gcn_epoch_view(n, dims, g.ORDER_AUTO, ws[:size], l + 1)[1]
+        Hin = g.gcn_epoch_view(n, dims, g.ORDER_AUTO, ws[:size], l)[0] if l else H0
+        S, want = torch.empty(n, dims[l + 1], device="cuda"), torch.empty_like(W[l])
+        g.gcn_layer_backward(a, Hin, None, first[l], Gl, None, S, want, None)
+        assert torch.equal(Y[l], want), l
+    a.close()
+
+
 @pytest.mark.parametrize("f", [4, 7, 16, 20, 32, 41, 48, 64, 130])
 @pytest.mark.parametrize("pairs,loops,blocks", [(500, True, 0), (400_000, True, 1), (400_000, True, 3), (400_000, False, 1), (400_000, False, 3)])
 @pytest.mark.parametrize("values", [0, 1])

@@ -3,13 +3,14 @@ import os
 import subprocess
 import textwrap
 
-CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2005_03300_amd", "csrc")
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2005_03300_amd", "csrc")
 
 
 def run_cpp(tmp_path, body):
     src, exe = tmp_path / "t.cpp", tmp_path / "t"
     src.write_text(textwrap.dedent(body))
-    subprocess.run(["g++", "-std=c++17", "-O1", "-pthread", "-I", CSRC, str(src), "-o", str(exe)], check=True)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-pthread", "-I", CSRC, "-I", os.path.join(ROOT, "include"), str(src), "-o", str(exe)], check=True)
     return subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
 
 
@@ -547,3 +548,91 @@ def test_scratch_of_calls_that_overlap(tmp_path):
         }
     """)
     assert r.returncode == 0 and r.stdout.split() == "4 1 5 1 -4 1 1 15 0 5 0".split(), (r.returncode, r.stdout, r.stderr)
+
+
+def test_room_for_the_end_of_an_epoch(tmp_path):
+    """Partial results lie in memory that is idle from the loss on, apart from each other; wherever the plain shares fit the scaled operand's region and the scratch (or the
+    first T) in turn, there is room; and gradients over few rows get theirs: the first layer's at any number of rows, also with a last share that is not whole."""
+    r = run_cpp(tmp_path, """
+        #include <algorithm>
+        #include <cmath>
+        #include <cstdio>
+        #include <random>
+        #include "epoch_layout.h"
+        using namespace gcn;
+        struct Range { size_t from, to; };
+        static bool in_order(const EpochLayout& lay, int64_t n, int L, const int32_t* dims, bool vf, bool p0, bool fuse) {      // the plain shares, first fit
+            size_t left[2] = {0, 0};
+            if (L >= 8) return false;
+            if (!vf) left[0] = lay.scratch - lay.XS;
+            else if (p0 || (lay.order[0] == GCN_ORDER_GEMM_FIRST && L >= 2)) left[0] = lay.G[0] - lay.T[0];
+            if (!fuse) left[1] = lay.total - lay.scratch;
+            bool some = left[0] || left[1];
+            auto take = [&](size_t b) {
+                b = round256(b);
+                for (size_t& l : left) if (b <= l) { l -= b; return true; }
+                return false;
+            };
+            bool all = fuse || take((size_t)std::min<int64_t>((n + 3) / 4, 2048) * 8);
+            for (int l = fuse ? L - 2 : L - 1; l >= 0 && all; --l) all = take(tn_shape(dims[l], dims[l + 1], n, false).scratch_bytes);
+            return all && some;
+        }
+        int main() {
+            std::mt19937 rng(5);
+            auto pick = [&](int a, int b) { return a + (int)(rng() % (unsigned)(b - a + 1)); };
+            const int widths[] = {1, 3, 4, 8, 12, 16, 16, 16, 20, 32, 48, 63, 64, 64, 100, 300};
+            int lost = 0, bad = 0, few = 0, could = 0;
+            for (int i = 0; i < 200000; ++i) {
+                int64_t n = (int64_t)std::exp(pick(0, 1100) / 100.0);
+                if (pick(0, 2) == 0) n = (n / 64 + 1) * 64;
+                if (pick(0, 9) == 0) n *= 50;
+                const int L = pick(1, 8);
+                int32_t dims[9];
+                for (int l = 0; l <= L; ++l) dims[l] = pick(0, 9) ? widths[pick(0, 15)] : pick(1, 300);
+                const int order = pick(0, 4) % 3;
+                const bool vf = pick(0, 2) == 0, p0 = pick(0, 3) == 0;
+                const EpochLayout lay = epoch_layout(n, L, dims, order);
+                const int mode = pick(0, 3) % 3;
+                const bool fuse = mode && !(lay.order[L - 1] == GCN_ORDER_GEMM_FIRST && !(L == 1 && p0)) && fused_last_supported(dims[L - 1], dims[L]);
+                const bool keep = fuse && mode == 2;
+                const EpochRoom room = epoch_room(lay, n, L, dims, vf, p0, fuse, keep);
+                if (!room.any) { lost += in_order(lay, n, L, dims, vf, p0, fuse); continue; }
+                std::vector<Range> idle, used;
+                if (!vf) idle.push_back({lay.XS, fuse ? lay.scratch : lay.total});
+                else if (!fuse) idle.push_back({lay.scratch, lay.total});
+                if (!(fuse && L == 1)) for (int l = 0; l < L; ++l)
+                    if ((l == 0 && p0) || lay.order[l] == GCN_ORDER_GEMM_FIRST) idle.push_back({lay.T[l], lay.G[l]});
+                if (fuse && !keep) idle.push_back({lay.T[L - 1], lay.S});
+                auto use = [&](size_t at, size_t bytes) {
+                    const Range u = {at, at + bytes};
+                    bool inside = false;
+                    for (const Range& r : idle) inside = inside || (r.from <= u.from && u.to <= r.to);
+                    for (const Range& r : used) if (u.from < r.to && r.from < u.to) inside = false;
+                    if (!inside || at % 256) ++bad;
+                    used.push_back(u);
+                };
+                if (!fuse) {
+                    use(room.loss, loss_part_bytes(n, dims[L]));
+                    if (!p0 && room.loss >= lay.T[L - 1] && room.loss < lay.G[L - 1]) ++bad;           // (the loss may come from the product that reads it)
+                }
+                for (int l = fuse ? L - 2 : L - 1; l >= 0; --l) {
+                    use(room.grad[l], tn_shape(dims[l], dims[l + 1], n, room.few[l]).scratch_bytes);
+                    if (room.few[l] && !few_rows(dims[l], dims[l + 1], n)) ++bad;
+                    could += few_rows(dims[l], dims[l + 1], n);
+                    few += room.few[l];
+                }
+            }
+            std::printf("%d %d %d ", lost, bad, (int)(few > 10000 && few > 0.95 * could));
+            const int32_t a[] = {16, 64, 8}, b[] = {8, 64, 4}, g[] = {4, 10}, h[] = {5, 16, 32, 8}, c[] = {64, 16, 8}, d[] = {64, 16, 41}, e[] = {64, 16}, f[] = {63, 16, 16, 12};
+            int none = 0, plain = 0;
+            for (int64_t n = 64; n <= 16384; n += n < 5000 ? 1 : 61) {
+                auto room = [&](int L, const int32_t* dims, bool fuse) { return epoch_room(epoch_layout(n, L, dims, 0), n, L, dims, false, false, fuse, false); };
+                const EpochRoom r[] = {room(2, c, false), room(2, d, true), room(2, d, false), room(1, e, false), room(3, f, false), room(1, g, false), room(3, h, false)};
+                none += !room(2, a, false).any + !room(2, b, false).any;
+                for (const EpochRoom& x : r) { none += !x.any; plain += !x.few[0]; }
+                none += (size_t)epoch_layout(n, 2, c, 0).total - epoch_layout(n, 2, c, 0).XS < tn_shape(64, 16, n, true).scratch_bytes;     // without room: one after another
+            }
+            std::printf("%d %d", none, plain);
+        }
+    """)
+    assert r.returncode == 0 and r.stdout.split() == "0 0 1 0 0".split(), (r.returncode, r.stdout, r.stderr)
