@@ -719,7 +719,7 @@ __global__ __launch_bounds__(256) void k_gemm_back(TnArgs a, const float* __rest
 // second takes the same rows of S turned round in LDS, and two columns of Hin per lane, from memory.  The next 16 rows are on
 // their way.  Bound by memory and the fp32 matrix rate together: S is read once where k_gemm_tall and k_gemm_tn read it twice, and Hin once
 // where it is the mask.  Faster than the two at every size (rows 1 K to 1.5 M, 16 to 64 columns of Hin, 2 to 64 of S: 63 layer calls with a
-// product of two entries a row, 1.00 to 1.35 of the time before): 64 x 41 over 120 K rows 81 -> 75 us, 32 x 32 over 0.5 M 109 -> 87, 16 x 5 over 1.5 M
+// product of two entries a row, 1.00 to 1.35 times as fast; other widths of Hin have no such kernel): 64 x 41 over 120 K rows 81 -> 75 us, 32 x 32 over 0.5 M 109 -> 87, 16 x 5 over 1.5 M
 // 117 -> 101, 64 x 8 over 5 K 14.3 -> 10.9.  256-64-64-41 on 120 K vertices 1016 -> 990 us an epoch.
 template <int NT, int MT, int MH>
 __global__ __launch_bounds__(256 * MH) void k_gemm_back_wide(TnArgs a, const float* __restrict__ W, const float* __restrict__ Zprev,

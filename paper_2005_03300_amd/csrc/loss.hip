@@ -84,7 +84,7 @@ __global__ __launch_bounds__(256) void k_softmax_nll(int64_t n, int32_t C, const
     if (threadIdx.x == 0) part[blockIdx.x] = (s_w[0] + s_w[1]) + (s_w[2] + s_w[3]);
 }
 
-// Any C: lanes loop over the columns and re-read the row (three passes, served by the caches).
+// Any C: lanes loop over the columns and re-read the row (three passes, served by the caches), and take a second exponential: they do not hold the first.
 __global__ __launch_bounds__(256) void k_softmax_nll_wide(int64_t n, int32_t C, const float* __restrict__ Z,
                                                           int64_t ldz, const int32_t* __restrict__ labels,
                                                           float* __restrict__ G, int64_t ldg, float inv_n,

@@ -684,8 +684,9 @@ __device__ __forceinline__ int group_lane(int x, int l) {
 // The weight gradient H^T Z of up to 64 x 16 (MT tiles of 16 columns of H, fetched before the walk) takes workgroups of four of them, whose sums
 // are added up as k_gemm_tn and k_gemm_tn_narrow do it over 64 rows.  It makes the kernel 1 to 2 us longer and saves a launch per layer: epochs of
 // 64-16-8 on 4096 vertices 38.7 -> 34.4 us, 64-16-16-8 54.7 -> 49.9, 50-16-12 on 10 K 45.9 -> 39.9, 100-16-4 on 30 K 56.6 -> 54.2.  Workgroups of
-// eight wavefronts, whose partial results are half as many, took 4 us longer each: fewer compute units fetch the rows.
-struct NoNext {};                                 // (without arguments that it does not read, two products of 1000 rows take 10.4 us and not 10.6)
+// eight wavefronts, whose partial results are half as many, took 4 us longer each: fewer compute units fetch the rows.  (The rows of Z, an epoch's S, are stored there
+// too, although nothing reads them then.)
+struct NoNext {};                                 // (the plain product has nothing to be told of what is next; in time there is no difference)
 template <int NEXT>
 using NextArgs = std::conditional_t<NEXT == RowsNext::NONE, NoNext, RowsNext>;
 template <int LPR, int SLICE, int EPI, int NEXT = RowsNext::NONE, int MT = 1>

@@ -1349,6 +1349,46 @@ def test_bias_gradient_beside_the_weight_gradient(n, f_in, f_out):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("C", [1, 2, 3, 4, 7, 16, 41, 130, 256, 300])
+def test_loss_of_rows_with_infinities(C):
+    """Logits of minus infinity are classes that have no share; a NaN or an infinity makes its own row NaN and no other; a row outside the split counts for
+    nothing whatever it holds."""
+    g = G()
+    n = 777
+    Z, labels = synth.normal_features(n, C, 391), np.zeros(n, np.int32)
+    rs = np.random.default_rng(392)
+    if C > 1:
+        Z[:400][rs.random((400, C)) < 0.5] = -np.inf
+        Z[np.arange(400), rs.integers(0, C, 400)] = 0.5
+        labels[:400] = Z[:400].argmax(1)
+        labels[400:] = rs.integers(0, C, n - 400)
+    odd = {700: np.nan, 701: np.inf, 702: -np.inf, 703: np.nan}
+    for row, value in odd.items():
+        Z[row, (0 if row < 702 else slice(None))] = value
+    for inside in (False, True):
+        labels[700:704] = 0 if inside else -1
+        keep = labels >= 0
+        Gd, loss = torch.full((n, C), 7.0, device="cuda"), torch.zeros(1, device="cuda")
+        g.gcn_softmax_nll_masked(dev(Z), dev(labels), int(keep.sum()), loss, Gd)
+        got = host(Gd)
+        with np.errstate(invalid="ignore"):
+            z = Z.astype(np.float64)
+            p = np.exp(z - z.max(1, keepdims=True))
+            s = p.sum(1, keepdims=True)
+            want = (p / s - np.eye(C)[np.maximum(labels, 0)]) / keep.sum()
+            nll = np.log(s[:, 0]) - (z - z.max(1, keepdims=True))[np.arange(n), np.maximum(labels, 0)]
+        want[~keep] = 0
+        np.testing.assert_array_equal(np.isnan(got), np.isnan(want))
+        finite = ~np.isnan(want)
+        # a share has a relative error of a few roundings of the exponential, of the sum and of the division
+        assert np.all(np.abs(got[finite] - want[finite]) <= (20 + C) * 2.0 ** -24 / keep.sum())
+        if inside:
+            assert np.isnan(float(loss))
+        else:
+            assert abs(float(loss) - nll[keep].mean()) <= 1e-6 * max(1.0, abs(nll[keep].mean()))
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("dims", [((64, 41), (64, 41)), ((16, 16), (100, 70)), ((300, 16), (8, 200))])
 def test_layer_calls_of_two_threads_on_one_stream(dims):
     """Two threads, a matrix each, one stream: no call's partial results lie where another call's do."""
