@@ -14,12 +14,18 @@ constexpr int SIZED_FOR_CUS = 256;
 
 // A gradient over few rows, M x N, which is cut into shares of 64 of them: as many as a workgroup of the kernel of few and short rows makes, which then
 // leaves the same partial results (see gradient_next).  In an epoch that saves a launch (17 K to 24 K rows: 0.87 to 0.96 of the time of an epoch with
-// longer shares, 32 K 0.90 to 0.97).  As launches of their own the shares of 64 rows are the faster too, up to 24 K rows (64 x 16 over 8 K rows
-// 7.2 -> 6.0 us; layer calls on 17 K rows 0.88 to 0.94 of the time); on 32 K 16 x 16 takes 7.1 and 6.3.  With more than 32 columns, not beyond
+// longer shares, 32 K 0.90 to 0.97), and a layer's own call is cut alike, for the same bits.  With more than 32 columns, not beyond
 // 16 K rows: more workgroups than compute units.
 inline bool few_rows(int64_t M, int64_t N, int64_t K) {
     const int64_t wide = M > N ? M : N, narrow = M > N ? N : M;
     return K >= 64 && narrow <= 16 && (wide <= 32 ? K <= 32768 : wide <= 64 && K <= 16384);
+}
+
+// The same for a product by itself, which has no rows to wait for: one trip of a workgroup is the faster only while there are few of them (16 x 16 over 1000
+// rows 4.6 us and 5.3 with longer shares, 32 x 16 over 12 K 6.3 and 6.8, over 20 K 6.7 and 7.0, but 16 x 16 over 32 K 6.7 and 6.0; 64 x 16 over 8 K 5.9 and
+// 6.2, alike from 12 K on).
+inline bool few_rows_alone(int64_t M, int64_t N, int64_t K) {
+    return few_rows(M, N, K) && K <= (M <= 32 && N <= 32 ? 20000 : 12000);
 }
 
 // Launch geometry of the A^T B product (K long): which operand goes on the 64-column groups, wavefronts per

@@ -636,3 +636,26 @@ def test_room_for_the_end_of_an_epoch(tmp_path):
         }
     """)
     assert r.returncode == 0 and r.stdout.split() == "0 0 1 0 0".split(), (r.returncode, r.stdout, r.stderr)
+
+
+def test_products_by_themselves_are_cut_for_few_rows_where_that_is_faster(tmp_path):
+    """Shares of 64 rows of a product by itself: up to 20 K rows, 12 K with more than 32 columns on a side, and never where an epoch's gradient would not have them; beyond, the
+    longer shares of other products."""
+    r = run_cpp(tmp_path, """
+        #include <cstdio>
+        #include "epoch_layout.h"
+        using namespace gcn;
+        int main() {
+            int wrong = 0;
+            for (int M = 1; M <= 80; ++M)
+                for (int N = 1; N <= 80; ++N)
+                    for (int64_t K : {1, 63, 64, 1000, 12000, 12001, 16384, 20000, 20001, 32768, 40000}) {
+                        const int wide = M > N ? M : N, narrow = M > N ? N : M;
+                        const bool want = K >= 64 && narrow <= 16 && (wide <= 32 ? K <= 20000 : wide <= 64 && K <= 12000);
+                        wrong += few_rows_alone(M, N, K) != want || (want && !few_rows(M, N, K));
+                    }
+            std::printf("%d %d %d %d", wrong, (int)tn_shape(16, 16, 32768, few_rows_alone(16, 16, 32768)).blocks,
+                        (int)tn_shape(16, 16, 32768, few_rows(16, 16, 32768)).blocks, (int)tn_shape(16, 16, 1000, few_rows_alone(16, 16, 1000)).blocks);
+        }
+    """)
+    assert r.returncode == 0 and r.stdout.split() == "0 256 512 16".split(), (r.returncode, r.stdout, r.stderr)
