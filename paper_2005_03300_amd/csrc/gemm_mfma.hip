@@ -111,9 +111,11 @@ __device__ __forceinline__ void stage_b(const TallArgs& a, int n0, float* Bs) {
 // adds its four products in the order of the lane quarters, so quarter kq has to supply k = k0 + 4e + kq to instruction
 // e, and the 16 bytes that it loads at k0 + 4 kq are exchanged between the quarters (a 4 x 4 transposition, four
 // instructions).  Without it instruction e takes k = k0 + 4 kq + e.  op(B) leaves its workgroups no more than four wavefronts to a SIMD, so that
-// the compiler need not save registers for eight (which put fewer reads of it together: 0.2 M x 602 x 41 223 us and 170).
+// the compiler need not save registers for eight (which put fewer reads of it together: 0.2 M x 602 x 41 223 us and 170).  Not with the wide stores: the
+// code is the same there, but each wavefront is given the registers of a fourth of a SIMD, and the second column of workgroups comes in later (137 K x 256 x 100 and
+// bias 93 us without that, 104 with it; 110 K and no bias 74 and 82).
 template <int NT, int EPI, bool WIDE, bool ASC>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, ASC ? 4 : 8))) void k_gemm_tall(TallArgs a) {
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, ASC && !WIDE ? 4 : 8))) void k_gemm_tall(TallArgs a) {
     extern __shared__ float Bs[];                       // [Kpad][S], then the bias
     const int n0 = blockIdx.y * (NT * 16);
     stage_b<NT>(a, n0, Bs);
