@@ -1052,11 +1052,7 @@ int gemm_mfma_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const floa
         // whole 16 bytes two pieces stay: 0.5 M x 44 x 96 76, in one 83.
         if (!wide_c && nt_total > 4 && nt_total <= 8 && M * (K + N) * 4 >= (192ll << 20) && b_bytes(8) <= 80 * 1024) NT = 8;
         while (NT > 1 && b_bytes(NT) > 150 * 1024) --NT;
-        // No more tiles than equal shares of the columns take, 80 in three and two and not in four and one, while operand and result are in the
-        // memory-side cache: 64 x 80 on 120 K rows 22.9 -> 19.6 us, 256 x 96 82.5 -> 69, 16 x 96 on 200 K 20.0 -> 19.4.  Beyond it the pieces of
-        // 48 columns, which are no whole lines, cost more (1 M rows of 16 x 96 148 and 164, of 128 x 67 327 and 384).
-        const int shares = (nt_total + NT - 1) / NT, equal = (nt_total + shares - 1) / shares;
-        if (equal <= 4 && M * (K + N) * 4 < (192ll << 20)) NT = equal;
+        if (const int tiles = equal_shares(M, N, K, epilogue == GCN_EPI_MASK, NT)) NT = tiles;
         TallArgs args;
         args.M = M; args.N = (int32_t)N; args.K = (int32_t)K;
         args.A = A; args.lda = lda; args.B = B; args.ldb = ldb; args.tb = tb;

@@ -28,6 +28,18 @@ inline int tall_waves(int64_t strips, int64_t panels, int64_t k, int64_t cus) {
     return k * of_four <= 400 * cus ? 4 : 8;
 }
 
+// Tiles of 16 columns per wavefront of a dense product whose columns go in equal shares of at most NT tiles, 80 as three and two and not as four and
+// one; 0: as many as NT.  While operand and result are in the memory-side cache: 64 x 80 on 120 K rows 22.9 -> 19.6 us, 256 x 96 82.5 -> 69, 16 x 96 on
+// 200 K 20.0 -> 19.4.  Beyond it the pieces of 48 columns, which are no whole lines, cost more (1 M rows of 16 x 96 148 and 164, of 128 x 67
+// 327 and 384).  With a mask, which is read in the same pieces, while it and the result are in the L2s (32 MB; 16 x 80 on 20 K rows 0.92 of
+// the time, on 120 K 16.9 and 19.4 us, 3 x 68 on 200 K 29.5 and 32.7, 41 x 80 on 326 K 63 and 77), and where the product takes longer than they do
+// (128 x 68 to 96 on 65 K to 200 K 0.91 to 1.04, 256 x 80 on 120 K 0.82).
+inline int equal_shares(int64_t M, int64_t N, int64_t K, bool mask, int NT) {
+    const int tiles = (int)((N + 15) / 16), shares = (tiles + NT - 1) / NT, equal = (tiles + shares - 1) / shares;
+    if (equal > 4 || M * (K + N) * 4 >= (192ll << 20)) return 0;
+    return !mask || K >= 128 || M * N * 8 <= (32ll << 20) ? equal : 0;
+}
+
 // How many of the rows without entries a chunk of a product zeroes (zero_share), or 0: they take a launch of their own, which writes whole rows
 // at the rate of the memory and costs a few microseconds.  A lane group of lpr lanes holds a row of a tile of lpr * vec columns.
 // Microseconds with a launch and with shares, random matrices:

@@ -659,3 +659,30 @@ def test_products_by_themselves_are_cut_for_few_rows_where_that_is_faster(tmp_pa
         }
     """)
     assert r.returncode == 0 and r.stdout.split() == "0 256 512 16".split(), (r.returncode, r.stdout, r.stderr)
+
+
+def test_equal_shares_of_the_columns(tmp_path):
+    """Equal shares of the columns only where their pieces meet in a cache; with a mask that is the L2s, unless the product takes longer."""
+    r = run_cpp(tmp_path, """
+        #include <cstdio>
+        #include <initializer_list>
+        #include "launch_rules.h"
+        using namespace gcn;
+        int main() {
+            std::printf("%d %d %d %d %d %d ", equal_shares(120000, 80, 64, false, 4), equal_shares(120000, 80, 16, true, 4), equal_shares(20000, 80, 16, true, 4),
+                        equal_shares(120000, 80, 256, true, 4), equal_shares(326000, 80, 41, true, 4), equal_shares(1000000, 96, 16, false, 4));
+            int wrong = 0;
+            for (int64_t M : {64, 20000, 65000, 200000, 1000000})
+                for (int64_t N = 1; N <= 600; ++N)
+                    for (int NT : {1, 2, 3, 4, 8, 16})
+                        for (int mask = 0; mask < 2; ++mask) {
+                            if (NT > (N + 15) / 16) continue;
+                            const int got = equal_shares(M, N, 32, mask, NT);
+                            if (got == 0) continue;
+                            const int64_t tiles = (N + 15) / 16, shares = (tiles + NT - 1) / NT;
+                            wrong += got > NT || got > 4 || (tiles + got - 1) / got != shares;
+                        }
+            std::printf("%d", wrong);
+        }
+    """)
+    assert r.returncode == 0 and r.stdout.split() == "3 0 3 3 0 0 0".split(), (r.returncode, r.stdout, r.stderr)
