@@ -99,11 +99,11 @@ __device__ __forceinline__ void stage_b(const TallArgs& a, int n0, float* Bs) {
     }
 }
 
-// The two MFMA operands are swapped, so a lane ends up with four consecutive columns of one row of C (element v of tile t is
+// How the rows of C leave.  By the two MFMA operands in turned order a lane ends up with four consecutive columns of one row of C (element v of tile t is
 // C[row0 + l%16][16t + 4*(l/16) + v]) and stores them with one instruction.  WIDE: N % 4 == 0 and 16-byte aligned rows of C (and of Zprev for
-// the mask); else at any address (with the operands
-// the other way round, single columns of four rows per lane and store: 1.5 M x 16 x 15 41 -> 33 us, x 41 164 -> 116; 0.2 M x 602 x 41 200 -> 166; slower
-// by up to 8 % on 50 K and 105 K rows of 400 to 602 floats, where whole 16 bytes take as long).  There the bias comes from LDS, and the columns that end
+// the mask); ANY: at any address (SINGLE, the operands
+// the other way round and single columns of four rows per lane and store: 1.5 M x 16 x 15 41 -> 33 us, x 41 164 -> 116; 0.2 M x 602 x 41 200 -> 166); SINGLE: up to
+// 16 columns where it is the faster, see single_columns.  ANY takes the bias from LDS, and the columns that end
 // in their tile are handled once, behind the whole tiles: loads of single biases and code for the end in every tile took registers, and scalar ones were
 // saved to memory (with eight tiles 0.2 M x 16 x 127 and bias 35 us, now 27; with sixteen x 255 65 and 44; with four 76 registers, now 63: 0.58 M x 64 x 107 and
 // bias 196 and 158).
@@ -114,12 +114,17 @@ __device__ __forceinline__ void stage_b(const TallArgs& a, int n0, float* Bs) {
 // the compiler need not save registers for eight (which put fewer reads of it together: 0.2 M x 602 x 41 223 us and 170).  Not with the wide stores: the
 // code is the same there, but each wavefront is given the registers of a fourth of a SIMD, and the second column of workgroups comes in later (137 K x 256 x 100 and
 // bias 93 us without that, 104 with it; 110 K and no bias 74 and 82).
-template <int NT, int EPI, bool WIDE, bool ASC>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, ASC && !WIDE ? 4 : 8))) void k_gemm_tall(TallArgs a) {
+enum TallStore { SINGLE, ANY, WIDE };
+template <int NT, int EPI, int STORE, bool ASC>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, ASC && STORE != WIDE ? 4 : 8))) void k_gemm_tall(TallArgs a) {
     extern __shared__ float Bs[];                       // [Kpad][S], then the bias
+    static_assert(STORE != SINGLE || NT == 1, "one tile");
+    auto product = [](float b, float x, floatx4 c) {
+        return STORE == SINGLE ? __builtin_amdgcn_mfma_f32_16x16x4f32(x, b, c, 0, 0, 0) : __builtin_amdgcn_mfma_f32_16x16x4f32(b, x, c, 0, 0, 0);
+    };
     const int n0 = blockIdx.y * (NT * 16);
     stage_b<NT>(a, n0, Bs);
-    if (!WIDE && a.bias)
+    if (STORE != WIDE && a.bias)
         for (int j = threadIdx.x; j < 16 * NT; j += blockDim.x) Bs[a.Kpad * a.S + j] = n0 + j < a.N ? a.bias[n0 + j] : 0.f;
     __syncthreads();
 
@@ -149,7 +154,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, ASC && !
                     const float* bp = Bs + (k0 + 16 * s + (ASC ? 4 * e + kq : 4 * kq + e)) * a.S + r;
 #pragma unroll
                     for (int t = 0; t < NT; ++t)
-                        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(bp[16 * t], ae[e], acc[t], 0, 0, 0);
+                        acc[t] = product(bp[16 * t], ae[e], acc[t]);
                 }
             }
         }
@@ -162,7 +167,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, ASC && !
                 const float* bp = Bs + (k0 + (ASC ? 4 * e + kq : 4 * kq + e)) * a.S + r;
 #pragma unroll
                 for (int t = 0; t < NT; ++t)
-                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(bp[16 * t], ae[e], acc[t], 0, 0, 0);
+                    acc[t] = product(bp[16 * t], ae[e], acc[t]);
             }
         }
         if (k0 < a.K) {                                 // ragged tail (fewer than 16 columns left)
@@ -185,11 +190,21 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, ASC && !
                 const float* bp = Bs + k * a.S + r;     // rows K..Kpad-1 of Bs are zero
 #pragma unroll
                 for (int t = 0; t < NT; ++t)
-                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(bp[16 * t], ae, acc[t], 0, 0, 0);
+                    acc[t] = product(bp[16 * t], ae, acc[t]);
             }
         }
+        if constexpr (STORE == SINGLE) {                // element v is C[row0 + 4 kq + v][r]
+            if (r >= a.N) continue;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int64_t row = row0 + 4 * kq + v;
+                if (row < a.M)
+                    a.C[row * a.ldc + r] = epi<EPI>(a.bias ? acc[0][v] + Bs[a.Kpad * a.S + r] : acc[0][v], EPI == GCN_EPI_MASK ? a.Zprev + row * a.ldzprev + r : nullptr);
+            }
+            continue;
+        }
         const int64_t row = row0 + r;
-        if constexpr (WIDE) {
+        if constexpr (STORE == WIDE) {
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 const int col = n0 + 16 * t + 4 * kq;           // N % 4 == 0: the four columns exist together
@@ -947,12 +962,12 @@ int EpochEnd::finish(float lr, hipStream_t s) {
 
 static inline bool al16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
-template <int NT, bool WIDE, bool ASC>
+template <int NT, int STORE, bool ASC>
 static void launch_tall_epi(const TallArgs& args, int epilogue, dim3 grid, int threads, size_t lds, hipStream_t s) {
     switch (epilogue) {
-        case GCN_EPI_NONE: launch_lds<k_gemm_tall<NT, GCN_EPI_NONE, WIDE, ASC>>(grid, threads, lds, s, args); break;
-        case GCN_EPI_RELU: launch_lds<k_gemm_tall<NT, GCN_EPI_RELU, WIDE, ASC>>(grid, threads, lds, s, args); break;
-        default: launch_lds<k_gemm_tall<NT, GCN_EPI_MASK, WIDE, ASC>>(grid, threads, lds, s, args); break;
+        case GCN_EPI_NONE: launch_lds<k_gemm_tall<NT, GCN_EPI_NONE, STORE, ASC>>(grid, threads, lds, s, args); break;
+        case GCN_EPI_RELU: launch_lds<k_gemm_tall<NT, GCN_EPI_RELU, STORE, ASC>>(grid, threads, lds, s, args); break;
+        default: launch_lds<k_gemm_tall<NT, GCN_EPI_MASK, STORE, ASC>>(grid, threads, lds, s, args); break;
     }
 }
 
@@ -963,13 +978,19 @@ static void launch_tall(const TallArgs& args, int epilogue, dim3 grid, int threa
                       (epilogue != GCN_EPI_MASK || ((args.ldzprev % 4 == 0) && al16(args.Zprev)));
     if constexpr (NT <= 4) {
         if (args.asc) {
-            if (wide) launch_tall_epi<NT, true, true>(args, epilogue, grid, threads, lds, s);
-            else launch_tall_epi<NT, false, true>(args, epilogue, grid, threads, lds, s);
+            if (wide) launch_tall_epi<NT, WIDE, true>(args, epilogue, grid, threads, lds, s);
+            else launch_tall_epi<NT, ANY, true>(args, epilogue, grid, threads, lds, s);
             return;
         }
     }
-    if (wide) launch_tall_epi<NT, true, false>(args, epilogue, grid, threads, lds, s);
-    else launch_tall_epi<NT, false, false>(args, epilogue, grid, threads, lds, s);
+    if constexpr (NT == 1) {
+        if (!wide && single_columns((args.M + 15) / 16, args.K, device_info().cus)) {
+            launch_tall_epi<NT, SINGLE, false>(args, epilogue, grid, threads, lds, s);
+            return;
+        }
+    }
+    if (wide) launch_tall_epi<NT, WIDE, false>(args, epilogue, grid, threads, lds, s);
+    else launch_tall_epi<NT, ANY, false>(args, epilogue, grid, threads, lds, s);
 }
 
 template <int NT, int KV>

@@ -40,6 +40,19 @@ inline int equal_shares(int64_t M, int64_t N, int64_t K, bool mask, int NT) {
     return !mask || K >= 128 || M * N * 8 <= (32ll << 20) ? equal : 0;
 }
 
+// Whether rows of up to 15 columns, no whole 16 bytes, leave k_gemm_tall as single columns of four rows (SINGLE) and not four columns at a time: where
+// every wavefront has one long strip and the busiest compute unit two workgroups of eight, 32 K to 64 K rows.  All of them read at the same time there, and
+// that form of the loop puts fewer reads of op(B) together; with fewer workgroups, or a second strip for some wavefronts, it is the slower.  Microseconds
+// with single columns and with four, 15 columns (30 K, 80 K and 200 K rows: as they were when all ragged rows left so):
+//   rows              30 K          33 K          40 K          60 K          65 K          80 K          200 K
+//   of 300 floats 10.9   9.0    12.0  11.6    13.3  13.8    15.1  16.3    15.8  17.1    22.7  20.4    48.9  44.7
+//   of 409        13.7  12.2    15.5  17.1    16.9  17.9    19.2  20.5    20.1  21.6    29.4  26.2    80.0  73.3
+//   of 602        18.3  16.0    21.1  23.3    23.2  24.5    26.3  28.4    27.8  29.9    41.3  36.5   116   111
+//   of 700        20.8  18.2    23.5  26.1    25.8  27.4    29.5  31.9    31.0  33.8    46.5  41.1   133   123
+// (Of 250 floats 36 K to 65 K rows take 0.92 to 1.02 with four; around 100 K rows of 409 and 602 single columns would be the faster too, by 6 to 8 %, of
+// 300, 500 and 700 they are not.)
+inline bool single_columns(int64_t strips, int64_t k, int64_t cus) { return k >= 300 && strips > 8 * cus && strips <= 16 * cus; }
+
 // How many of the rows without entries a chunk of a product zeroes (zero_share), or 0: they take a launch of their own, which writes whole rows
 // at the rate of the memory and costs a few microseconds.  A lane group of lpr lanes holds a row of a tile of lpr * vec columns.
 // Microseconds with a launch and with shares, random matrices:

@@ -1535,6 +1535,35 @@ def test_dense_products_of_ragged_rows_beyond_the_caches(N, K):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("M", [32768, 32769, 36001, 65535, 65537])
+@pytest.mark.parametrize("K,N", [(300, 1), (302, 15), (409, 7), (602, 14)])
+def test_dense_products_of_single_columns(M, K, N):
+    """Up to 15 columns over 32 K to 64 K rows of 300 floats and more leave as single columns, pieces of the rows four columns at a time: the same bits, with and without a
+    bias, with either epilogue and a mask that is the result, and nothing between the rows is written."""
+    g = G()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(337)
+    A, B, bias, Zp = [torch.randn(r, c, generator=gen, device="cuda") for r, c in ((M, K), (K, N), (1, N), (M, N))]
+    parts = [slice(0, M // 3), slice(M // 3, 2 * (M // 3)), slice(2 * (M // 3), M)]
+    for epilogue in (g.EPI_NONE, g.EPI_RELU, g.EPI_MASK):
+        for b in (None, bias.view(-1)):
+            C, pieces = torch.full((M + 2, N + 2), float("nan"), device="cuda"), torch.empty(M, N, device="cuda")
+            args = lambda r: dict(bias=b, epilogue=epilogue, Zprev=Zp[r] if epilogue == g.EPI_MASK else None)
+            g.gcn_gemm(0, 0, A, B, C[1:-1, :N], **args(slice(None)))
+            for r in parts:
+                g.gcn_gemm(0, 0, A[r], B, pieces[r], **args(r))
+            assert torch.equal(C[1:-1, :N], pieces), epilogue
+            assert bool(torch.isnan(C[0]).all() and torch.isnan(C[-1]).all() and torch.isnan(C[:, N:]).all())
+            if epilogue == g.EPI_MASK:
+                over = Zp.clone()
+                g.gcn_gemm(0, 0, A, B, over, bias=b, epilogue=epilogue, Zprev=over)
+                assert torch.equal(over, pieces)
+    rows = torch.randint(0, M, (200,), generator=gen, device="cuda")
+    g.gcn_gemm(0, 0, A, B, C[1:-1, :N])
+    assert_close(host(C[1:-1, :N][rows]), host(A[rows].double() @ B.double()), f"{M} x {K} x {N}")
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("N", [1, 2, 3, 6, 7, 18, 23, 41, 62, 63, 66, 70, 95, 127, 130, 243, 255])
 @pytest.mark.parametrize("M,K,tb", [(64, 16, 0), (1001, 30, 1), (333, 602, 0)])
 def test_result_over_its_own_mask(M, K, tb, N):

@@ -686,3 +686,16 @@ def test_equal_shares_of_the_columns(tmp_path):
         }
     """)
     assert r.returncode == 0 and r.stdout.split() == "3 0 3 3 0 0 0".split(), (r.returncode, r.stdout, r.stderr)
+
+
+def test_single_columns_where_all_wavefronts_have_one_strip(tmp_path):
+    r = run_cpp(tmp_path, """
+        #include <cstdio>
+        #include "launch_rules.h"
+        using namespace gcn;
+        int main() {
+            auto of = [](long rows, long k) { return (int)single_columns((rows + 15) / 16, k, 256); };
+            std::printf("%d %d %d %d %d %d %d", of(32768, 409), of(32769, 409), of(65536, 300), of(65537, 300), of(40000, 299), of(30000, 700), of(200000, 700));
+        }
+    """)
+    assert r.returncode == 0 and r.stdout.split() == "0 1 1 0 0 0 0".split(), (r.returncode, r.stdout, r.stderr)
