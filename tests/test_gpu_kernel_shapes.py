@@ -1535,6 +1535,23 @@ def test_dense_products_of_ragged_rows_beyond_the_caches(N, K):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("n,C", [(3, 300), (1024, 300), (1025, 300), (2048, 300), (2049, 300), (8192, 300), (8197, 300), (131_072, 2), (131_073, 2)])
+def test_loss_sums_on_both_sides_of_two_terms_a_thread(n, C):
+    """Partial sums of the loss, 1 to 2048: up to 512 are added as they come, more of them eight at a time.  A row's loss is off by the roundings of its C exponentials' sum
+    and of a few operations behind it, the sum over the rows in double by none of that size."""
+    g = G()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(347)
+    Z, y = torch.randn(n, C, generator=gen, device="cuda"), torch.randint(0, C, (n,), generator=gen, device="cuda", dtype=torch.int32)
+    loss, again, grad = torch.full((1,), float("nan"), device="cuda"), torch.empty(1, device="cuda"), torch.empty(n, C, device="cuda")
+    g.gcn_softmax_nll(Z, y, loss, grad)
+    want = float(torch.nn.functional.cross_entropy(Z.double().cpu(), y.long().cpu()))
+    assert abs(float(loss) - want) <= (C + 32) * 2.0 ** -24 * max(1.0, want)
+    g.gcn_softmax_nll(Z, y, again)
+    assert torch.equal(again, loss)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("M", [32768, 32769, 36001, 65535, 65537])
 @pytest.mark.parametrize("K,N", [(300, 1), (302, 15), (409, 7), (602, 14)])
 def test_dense_products_of_single_columns(M, K, N):
